@@ -11,6 +11,7 @@ Inputs follow the recipes of the benchmark configurations: programs of 10 to 30 
 10 two-argument functions (or full binary trees over 8 two-argument functions), N(0,1) feature maps, He-normal weights
 with the residual branch damped to a fifth at its last convolution, as networks of this kind are initialised and end
 up (an undamped branch doubles the maps' variance at every one of up to 30 modules, and no such network answers anything);
+training steps with non-negative maps and weights, every unit active (see _prepare_programs);
 tokens with a shared component and gate columns shifted along it until the experts' load follows Zipf's law.
 """
 from __future__ import annotations
@@ -176,13 +177,27 @@ def _prepare_programs(case, seed):
     n = len(ar)
     g = torch.Generator(device="cuda").manual_seed(seed)
 
-    def normal(*shape, std=1.0, dtype=dt):
-        return (torch.randn(*shape, generator=g, device="cuda") * std).to(dtype)
+    def normal(*shape, std=1.0, dtype=dt, positive=False):
+        v = torch.randn(*shape, generator=g, device="cuda") * std
+        return (v.abs() if positive else v).to(dtype)
 
-    weights = dict(w1=normal(n, C, 2 * C, std=math.sqrt(2 / (2 * C))), b1=normal(n, C, std=0.01, dtype=torch.float32),
-                   w3a=normal(n, C, 3, 3, C, std=math.sqrt(2 / (9 * C))), b3a=normal(n, C, std=0.01, dtype=torch.float32),
-                   w3b=normal(n, C, 3, 3, C, std=0.2 * math.sqrt(2 / (9 * C))), b3b=normal(n, C, std=0.01, dtype=torch.float32))
-    feats = normal(B, S, S, C)
+    # Gradients of a deep ReLU network are not continuous: where a stored activation next to zero rounds the other way, a unit
+    # passes its gradient or does not, and with random signs two correct bf16 implementations differ by 8 % in every gradient.
+    # Training steps therefore take the signs away: every unit is active, and the gradients can be compared.  The work is
+    # the same.  (The mean of |N(0,1)| is 0.8; the scales below keep the maps near it: a convolution passes 0.8 * 0.3 of
+    # its input's mean, a join averages.)
+    if train:
+        def pos(*shape, fan, gain):
+            return normal(*shape, std=gain / (0.8 * fan), positive=True)
+
+        weights = dict(w1=pos(n, C, 2 * C, fan=2 * C, gain=1.0), b1=normal(n, C, std=0.01, dtype=torch.float32, positive=True),
+                       w3a=pos(n, C, 3, 3, C, fan=9 * C, gain=0.3), b3a=normal(n, C, std=0.01, dtype=torch.float32, positive=True),
+                       w3b=pos(n, C, 3, 3, C, fan=9 * C, gain=0.3), b3b=normal(n, C, std=0.01, dtype=torch.float32, positive=True))
+    else:
+        weights = dict(w1=normal(n, C, 2 * C, std=math.sqrt(2 / (2 * C))), b1=normal(n, C, std=0.01, dtype=torch.float32),
+                       w3a=normal(n, C, 3, 3, C, std=math.sqrt(2 / (9 * C))), b3a=normal(n, C, std=0.01, dtype=torch.float32),
+                       w3b=normal(n, C, 3, 3, C, std=0.2 * math.sqrt(2 / (9 * C))), b3b=normal(n, C, std=0.01, dtype=torch.float32))
+    feats = normal(B, S, S, C, positive=train)
     prog, off = _draw_programs(case, seed)
     flags = SCHEDULES[case["schedule"]] | (dyn.DYNB_PLAN_KEEP if train else 0)
     # buffers a program keeps from batch to batch, sized with this batch
@@ -331,12 +346,11 @@ def tolerance(case):
         # 2e-4 from hidden rows and outputs that round to the neighbouring bfloat16; in a large batch a token or two may have
         # two gate logits within 1e-6 of each other and take another last expert
         return {"rel": 1e-3 if case["T"] <= 512 else 1e-3 + 0.7 / math.sqrt(case["T"])}
-    if case["dtype"] == "f32":
-        # 1e-6; a backward pass has single ReLU decisions that fall the other way (2.5e-3 of a tensor at most)
-        return {"rel": 1e-2 if case["kind"] == "train" else 5e-6}
+    if case["kind"] == "train":                          # 1.5e-4 in bf16, 6e-7 in fp32: no ReLU decision depends on a rounding
+        return {"rel": 1e-3 if case["dtype"] == "bf16" else 3e-6}
+    if case["dtype"] == "f32":                           # 1e-6
+        return {"rel": 5e-6}
     # stored activations that round to the neighbouring bfloat16, module after module (5.5e-3, 2.9e-3, 1.1e-3 by depth; 9e-3,
-    # 6e-3, 5e-3 in the probabilities); in the backward pass also the ReLU decisions they turn (8e-2, 5.7e-2, 2.4e-2)
+    # 6e-3, 5e-3 in the probabilities)
     depth = {"chains": 0, "balanced": 1, "small": 2}[case["trees"]]
-    if case["kind"] == "train":
-        return {"rel": (0.3, 0.2, 0.1)[depth]}
-    return {"rel": ((3.5e-2, 2.4e-2, 2e-2) if case["head"] else (2.2e-2, 1.2e-2, 5e-3))[depth]}
+    return {"rel": ((3e-2, 2.4e-2, 2e-2) if case["head"] else (2.2e-2, 1.2e-2, 5e-3))[depth]}
