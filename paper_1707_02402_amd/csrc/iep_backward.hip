@@ -293,32 +293,26 @@ __device__ __forceinline__ float* route_mf(const BmArgs& a, int32_t r)
     return r >= 0 ? a.gy + size_t(r) * (mf::P * mf::C) : a.gleaf + size_t(-1 - r) * (mf::P * mf::C);
 }
 
-// dst[function][tile][tap][j][lane][i] = W(o, tap, k) with o = tile*32 + rho(lane % 32) (the row permutation of the
-// forward pass's packed weights), k = (lane/32)*64 + j*8 + i, where
-//   mode 0: W = src[function][o][tap][k]                 conv3x3 as given (ntap 9)
-//   mode 1: W = src[function][k][8 - tap][o]             conv3x3 transposed, taps flipped (ntap 9)
-//   mode 2: W = src[function][o][tap*128 + k]            conv1x1 over 2C inputs, half `tap` (ntap 2)
-//   mode 3: W = src[function][k][tap*128 + o]            conv1x1 transposed, half `tap` (ntap 2)
-__global__ void k_bwd_pack(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int n_types, int ntap, int mode)
+// dst[function][tile][fragment][lane][i] = W(o, tap, k) with o = tile*32 + rho(lane % 32) (the row permutation of the
+// forward pass's packed weights), k = (lane/32)*64 + j*8 + i, (tap, j) of the fragment as in iep_mfma.h, where
+//   ntap 9: W = src[function][k][8 - tap][o]             conv3x3 transposed, taps flipped
+//   ntap 2: W = src[function][k][tap*128 + o]            conv1x1 transposed, half `tap`
+__global__ void k_bwd_pack(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int n_types, int ntap)
 {
     const size_t total = size_t(n_types) * 4 * ntap * 8 * 64;
     for (size_t q = size_t(blockIdx.x) * blockDim.x + threadIdx.x; q < total; q += size_t(gridDim.x) * blockDim.x) {
-        const int lane = int(q & 63), j = int((q >> 6) & 7);
-        const size_t rest = q >> 9;
-        const int tap = int(rest % ntap), tile = int((rest / ntap) & 3);
-        const size_t type = rest / (size_t(ntap) * 4);
+        const int lane = int(q & 63);
+        const size_t rest = q >> 6;
+        const int f = int(rest % (size_t(ntap) * 8)), tile = int((rest / (size_t(ntap) * 8)) & 3);
+        const size_t type = rest / (size_t(ntap) * 32);
+        const int tap = ntap == 9 ? mf::frag_kh(f) * 3 + mf::frag_kw(f) : f >> 3, j = ntap == 9 ? mf::frag_step(f) : f & 7;
         const int m = lane & 31;
         const int o = tile * 32 + ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3), k0 = (lane >> 5) * 64 + j * 8;
         uint32_t v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int k = k0 + i;
-            size_t e;
-            if (mode == 0) e = ((type * 128 + o) * 9 + tap) * 128 + k;
-            else if (mode == 1) e = ((type * 128 + k) * 9 + (8 - tap)) * 128 + o;
-            else if (mode == 2) e = (type * 128 + o) * 256 + tap * 128 + k;
-            else e = (type * 128 + k) * 256 + tap * 128 + o;
-            v[i] = src[e];
+            v[i] = src[ntap == 9 ? ((type * 128 + k) * 9 + (8 - tap)) * 128 + o : (type * 128 + k) * 256 + tap * 128 + o];
         }
         dst[q] = u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
     }
@@ -329,20 +323,19 @@ __global__ void k_bwd_pack(const bf16_t* __restrict__ src, u32x4* __restrict__ d
 // which every lane touches a line of its own costs about 125 clocks to issue, so nothing is loaded or stored in the
 // accumulator layout: masks come from the LDS bytes, the residual term and the result go through the staging area.
 namespace bn {
-constexpr int MASK_OFF = mf::TILE_BYTES;                 // y mask bytes [P][16], then mid mask bytes [P][16]
+constexpr int MASK_OFF = (mf::TILE_BYTES + 255) / 256 * 256; // y mask bytes [P][16], then mid mask bytes [P][16]
 constexpr int MASK_BYTES = 2 * mf::P * 16 + 128;         // (+ padding to a multiple of 256)
 constexpr int STAGE_OFF = MASK_OFF + MASK_BYTES;
 constexpr int STAGE_PITCH = mf::C * 4 + 16;              // bytes per pixel: 128 floats + a bank-shifting pad
-constexpr int STAGE_PIX = 128;                           // pixels per round: four pixel tiles
+constexpr int STAGE_PIX = 112;                           // pixels per round: four pixel tiles (8 image rows)
 constexpr int LDS_BYTES = STAGE_OFF + STAGE_PIX * STAGE_PITCH;
 static_assert(MASK_BYTES % 256 == 0 && LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
 }  // namespace bn
 
-template <int RW>
 __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 {
     using namespace mf;
-    constexpr int MTW = MT7, NT = 1, XS = 4, NTHR = 256;
+    constexpr int MTW = MT7, RW = 12, XW = 6, NTHR = 256;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int per_xcd = gridDim.x >> 3;
     const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -359,10 +352,10 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     const bool binary = a.arity[it.type] == 2;                        // uniform over the workgroup
     const size_t item_off = size_t(a.first_item + logical) * (P * C);
 
-    const size_t frag3 = (size_t(it.type) * 4 + wave) * 9 * 8, frag1 = (size_t(it.type) * 4 + wave) * 2 * 8;
-    const bf16_t* wrow_bT[NT] = {a.pk3bT + frag3 * FRAG + lane * 8};
-    const bf16_t* wrow_aT[NT] = {a.pk3aT + frag3 * FRAG + lane * 8};
-    bf16x8 ring[RW][NT];
+    const size_t frag3 = (size_t(it.type) * 4 + wave) * 72, frag1 = (size_t(it.type) * 4 + wave) * 16;
+    const bf16_t* wrow_bT = a.pk3bT + frag3 * FRAG + lane * 8;
+    const bf16_t* wrow_aT = a.pk3aT + frag3 * FRAG + lane * 8;
+    bf16x8 ring[RW];
 
     auto centre_addr = [&](int c) -> uint32_t {                       // 16-byte piece c of a map -> its place in the halo tile
         const int p = c >> 4, part = c & 15;
@@ -394,15 +387,8 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
             if (c < P * 16) { glo[i] = gy4[2 * c]; ghi[i] = gy4[2 * c + 1]; yv[i] = y4[c]; }
         }
         __builtin_amdgcn_sched_barrier(0);
-        ring_fill<NT, RW>(ring, wrow_bT);                             // arrives while the tile is written
-        for (int c = tid; c < 60 * 16; c += NTHR) {                   // zero border
-            const int q = c >> 4, part = c & 15;
-            int row, col;
-            if (q < 16) { row = 0; col = q; }
-            else if (q < 32) { row = HALO - 1; col = q - 16; }
-            else { row = 1 + ((q - 32) >> 1); col = ((q - 32) & 1) ? HALO - 1 : 0; }
-            *reinterpret_cast<u32x4*>(lds_raw + uint32_t(row * ROW_BYTES + col * PIX_BYTES + part * 16)) = u32x4{0u, 0u, 0u, 0u};
-        }
+        ring_fill<RW>(ring, wrow_bT);                             // arrives while the tile is written
+        for (int c = tid; c < BORDER_PIX * 16; c += NTHR) zero_border_piece(c);
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
             const int c = tid + i * NTHR;
@@ -420,26 +406,25 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         }
     }
 
-    uint32_t xaddr[MTW];                                              // top-left tap of this lane's pixel, its 64-channel half
-#pragma unroll
-    for (int t = 0; t < MTW; ++t) {
-        const int p = min(t * 32 + r, P - 1);
-        xaddr[t] = uint32_t((p / S) * ROW_BYTES + (p % S) * PIX_BYTES + h * 128);
-    }
+    // this lane's LDS address for the first row pair; in tile t it holds the pixel in column px of image row 2 t + py
+    const uint32_t x0 = pair_lane_addr(lane);
+    const int px = r & 15, py = r >> 4;
+    const bool real = px < S;                                         // columns 14, 15 are padding
+    auto pixel = [&](int t) { return (2 * t + py) * S + px; };
     const int chan = n0 + 16 * h;                                     // this lane's 16 accumulator elements: channels chan .. chan+15
-    f32x16 acc[MTW][NT];
+    f32x16 acc[MTW];
     auto zero_acc = [&]() {
 #pragma unroll
         for (int t = 0; t < MTW; ++t)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[t][0][i] = 0.f;
+            for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
     };
-    auto centre = [&](int t) -> uint32_t { return xaddr[t] - uint32_t(h * 128) + CENTER; };
-    // acc[t][0][8q .. 8q+7] where the mask bit is set, as 8 packed bf16
+    auto centre = [&](int t) -> uint32_t { return x0 - uint32_t(h * 128) + uint32_t(CENTER + 2 * t * ROW_BYTES); };
+    // acc[t][8q .. 8q+7] where the mask bit is set, as 8 packed bf16
     auto packed_masked = [&](int t, int q, uint32_t bits) -> u32x4 {
         float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (bits >> (8 * q + i)) & 1u ? acc[t][0][8 * q + i] : 0.f;
+        for (int i = 0; i < 8; ++i) v[i] = (bits >> (8 * q + i)) & 1u ? acc[t][8 * q + i] : 0.f;
         return u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
     };
     // Accumulators -> the fp32 staging area, four pixel tiles per round; then every thread takes 16-byte pieces
@@ -448,8 +433,8 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     auto through_lds = [&](auto&& pre, auto&& fn) {
 #pragma unroll
         for (int round = 0; round < 2; ++round) {
-            const int t0 = round * 4, t1 = round == 0 ? 4 : MTW, p0 = t0 * 32, p1 = round == 0 ? 128 : P;
-            constexpr int NI = 128 * 16 / NTHR;                       // pieces per thread of the larger round
+            const int t0 = round * 4, t1 = round == 0 ? 4 : MTW, p0 = t0 * 28, p1 = round == 0 ? 112 : P;
+            constexpr int NI = 112 * 16 / NTHR;                       // pieces per thread of the larger round
             decltype(pre(0)) ahead[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -459,11 +444,11 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
             __syncthreads();                                          // the area (and, the first time, the tile) is free
 #pragma unroll
             for (int t = 0; t < MTW; ++t)
-                if (t >= t0 && t < t1) {
+                if (t >= t0 && t < t1 && real) {
 #pragma unroll
                     for (int b = 0; b < 4; ++b)
-                        *reinterpret_cast<f32x4*>(lds_raw + bn::STAGE_OFF + uint32_t(((t - t0) * 32 + r) * bn::STAGE_PITCH + (chan + 4 * b) * 4)) =
-                            f32x4{acc[t][0][4 * b], acc[t][0][4 * b + 1], acc[t][0][4 * b + 2], acc[t][0][4 * b + 3]};
+                        *reinterpret_cast<f32x4*>(lds_raw + bn::STAGE_OFF + uint32_t((pixel(t) - p0) * bn::STAGE_PITCH + (chan + 4 * b) * 4)) =
+                            f32x4{acc[t][4 * b], acc[t][4 * b + 1], acc[t][4 * b + 2], acc[t][4 * b + 3]};
                 }
             __syncthreads();
 #pragma unroll
@@ -496,7 +481,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     }
     zero_acc();
     NCLK(1);
-    kloop<MTW, NT, RW, XS, false>(acc, xaddr, ring, wrow_bT, wrow_aT);
+    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_bT, wrow_aT);
     NCLK(2);
 #pragma unroll
     for (int i = 0; i < NIT; ++i) {
@@ -506,9 +491,9 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < MTW; ++t)
-        if (t * 32 + r < P) {
+        if (real) {
             // this lane's 16 mask bits: the bytes of the two pieces that hold its channels
-            const uint32_t mm = *reinterpret_cast<const uint16_t*>(lds_raw + bn::MASK_OFF + P * 16 + (t * 32 + r) * 16 + (chan >> 3));
+            const uint32_t mm = *reinterpret_cast<const uint16_t*>(lds_raw + bn::MASK_OFF + P * 16 + pixel(t) * 16 + (chan >> 3));
 #pragma unroll
             for (int q = 0; q < 2; ++q)
                 *reinterpret_cast<u32x4*>(lds_raw + centre(t) + uint32_t((chan + q * 8) * 2)) = packed_masked(t, q, mm);
@@ -528,7 +513,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     // the residual's and would vanish below the bfloat16 quantum of the latter at every level.
     zero_acc();
     NCLK(3);
-    kloop<MTW, NT, RW, XS, false>(acc, xaddr, ring, wrow_aT, wrow_aT);
+    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_aT, wrow_aT);
     NCLK(4);
     auto residual = [&](int c, f32x4& lo, f32x4& hi, const f32x4& g0, const f32x4& g1) {
         const uint32_t yb = lds_raw[bn::MASK_OFF + c];
@@ -570,16 +555,17 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     }
     __syncthreads();
     {
-        const bf16_t* t1row[NT] = {a.pk1T + frag1 * FRAG + lane * 8};
-        const bf16_t* t1row2[NT] = {t1row[0] + 8 * FRAG};
-        bf16x8 ring1[8][NT];
-        ring_fill<NT, 8>(ring1, t1row);
+        const bf16_t* t1row = a.pk1T + frag1 * FRAG + lane * 8;
+        bf16x8 w1f[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w1f[j] = *reinterpret_cast<const bf16x8*>(t1row + j * FRAG);
+        auto caddr = [&](int t) { return centre(t) + uint32_t(h * 128); };
         zero_acc();
-        kloop<MTW, NT, 8, XS, true>(acc, xaddr, ring1, t1row, t1row2);
+        kloop1<MTW, true>(acc, caddr, w1f, t1row + 8 * FRAG);
         float* d0 = route_mf(a, a.gdst0[logical]);
         through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d0, c, lo, hi); });
         zero_acc();
-        kloop<MTW, NT, 8, XS, true>(acc, xaddr, ring1, t1row2, t1row2);
+        kloop1<MTW, false>(acc, caddr, w1f, nullptr);
         float* d1 = route_mf(a, a.gdst1[logical]);
         through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d1, c, lo, hi); });
     }
@@ -985,7 +971,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bwd_node_mfma<8>), hipFuncAttributeMaxDynamicSharedMemorySize, bn::LDS_BYTES),
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bwd_node_mfma), hipFuncAttributeMaxDynamicSharedMemorySize, bn::LDS_BYTES),
                 "hipFuncSetAttribute(k_bwd_node_mfma)");
         HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bwd_wgrad_mfma), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * mf::TILE_BYTES),
                 "hipFuncSetAttribute(k_bwd_wgrad_mfma)");
@@ -1011,14 +997,14 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     }
 
     // weights in fragment order, as given and transposed
-    auto pack = [&](const void* src, size_t at, int ntap, int mode) {
+    auto pack = [&](const void* src, size_t at, int ntap) {
         const size_t pieces = size_t(nt) * 4 * ntap * 512;
         hipLaunchKernelGGL(k_bwd_pack, dim3(unsigned(std::min<size_t>((pieces + 255) / 256, 4096))), dim3(256), 0, st,
-                           static_cast<const bf16_t*>(src), reinterpret_cast<u32x4*>(ws + at), nt, ntap, mode);
+                           static_cast<const bf16_t*>(src), reinterpret_cast<u32x4*>(ws + at), nt, ntap);
     };
-    pack(w->w3b, L.pk3bT, 9, 1);
-    pack(w->w3a, L.pk3aT, 9, 1);
-    if (p->has_binary) pack(w->w1, L.pk1T, 2, 3);
+    pack(w->w3b, L.pk3bT, 9);
+    pack(w->w3a, L.pk3aT, 9);
+    if (p->has_binary) pack(w->w1, L.pk1T, 2);
 
     float* gy = reinterpret_cast<float*>(ws + L.gy);
     const unsigned bx_map = unsigned(std::min<size_t>((chw + 255) / 256, 64));
@@ -1046,7 +1032,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         a.gdst0 = reinterpret_cast<const int32_t*>(pd + KT.gdst0) + l.start;
         a.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + l.start;
         const unsigned grid = unsigned((l.count + 7) / 8 * 8);
-        hipLaunchKernelGGL((k_bwd_node_mfma<8>), dim3(grid), dim3(256), bn::LDS_BYTES, st, a);
+        hipLaunchKernelGGL(k_bwd_node_mfma, dim3(grid), dim3(256), bn::LDS_BYTES, st, a);
     }
     {
         WgArgs q;

@@ -66,7 +66,6 @@ __device__ long long* g_phase_clk = nullptr;      // [workgroup][wave][16]
 struct MfArgs {
     const dynb_item* items;
     int32_t count;
-    int32_t any_binary;
     const uint8_t* arity;     // device [n_types]
     const bf16_t* feats;
     bf16_t* out;
@@ -84,8 +83,9 @@ struct MfArgs {
 };
 
 
-// dst[function][tile][tap][j][lane][i] = src[function][co = tile*32 + rho(lane%32)][tap][ci = (lane/32)*64 + j*8 + i]
-// one thread per 16-byte piece; ntap = 9 for a conv3x3, 2 for the two halves of the conv1x1 over 2C inputs.
+// dst[function][tile][fragment][lane][i] = src[function][co = tile*32 + rho(lane%32)][tap][ci = (lane/32)*64 + j*8 + i] with
+// (tap, j) of the fragment as in iep_mfma.h; one thread per 16-byte piece; ntap = 9 for a conv3x3, 2 for the two halves
+// of the conv1x1 over 2C inputs.
 // rho permutes the channels inside a tile: MFMA output row m = 8b + 4h + c (accumulator element 4b + c
 // of lane half h) is given channel 16h + 4b + c, so that the 16 accumulator elements of a lane are 16
 // consecutive channels and leave the kernel as two 16-byte stores.
@@ -93,78 +93,61 @@ __global__ void k_pack_weights(const u32x4* __restrict__ src, u32x4* __restrict_
 {
     const size_t total = size_t(n_types) * 4 * ntap * 8 * 64;
     for (size_t q = size_t(blockIdx.x) * blockDim.x + threadIdx.x; q < total; q += size_t(gridDim.x) * blockDim.x) {
-        const int lane = int(q & 63), j = int((q >> 6) & 7);
-        const size_t rest = q >> 9;
-        const int tap = int(rest % ntap), tile = int((rest / ntap) & 3);
-        const size_t type = rest / (size_t(ntap) * 4);
+        const int lane = int(q & 63);
+        const size_t rest = q >> 6;
+        const int f = int(rest % (size_t(ntap) * 8)), tile = int((rest / (size_t(ntap) * 8)) & 3);
+        const size_t type = rest / (size_t(ntap) * 32);
+        const int tap = ntap == 9 ? mf::frag_kh(f) * 3 + mf::frag_kw(f) : f >> 3, j = ntap == 9 ? mf::frag_step(f) : f & 7;
         const int m = lane & 31;
         const int co = tile * 32 + ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3), ci0 = (lane >> 5) * 64 + j * 8;
         dst[q] = src[(((type * 128 + co) * ntap + tap) * 128 + ci0) >> 3];
     }
 }
 
-// WM selects how a node is spread over workgroups.
-//   WM = 2: one node per workgroup: wave w owns channel tile w (32 channels) and all 7 pixel tiles.
-//   WM = 3: half a node per workgroup: output rows 0..6 or 7..13.  The workgroup convolves an 8-row window (rows
-//           0..7 or 6..13: the second conv needs one row of the first conv's output beyond its own rows), i.e. 112
-//           pixels = 4 pixel tiles; wave w owns channel tile w of all four.  Two CUs share a node, which halves the
-//           latency of narrow launch groups at the price of 8/7 of the MFMA work.
-//   WM = 4: the layout of WM = 2 inside at most 256 registers (two sets of activation fragments instead of four),
-//           so that two workgroups share a CU and one's staging, swap and epilogue run under the other's MFMAs.
-// WM = 2 and 3 own a CU (up to 512 registers per lane) and, unless ALLOW_DEEP is off, keep a weight ring of 24
-// steps that is filled before the argument map is staged.
-// One workgroup's share of a launch group: position `logical` (a node, half a node or a pair of nodes,
-// depending on the layout) of the items a.items[0 .. a.count).
-// KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m, as they enter the LDS tile.
-template <int WMODE, bool ALLOW_DEEP = true, bool KEEP = false>
+// HALF selects how a node is spread over workgroups.
+//   whole: one node per workgroup: wave w owns channel tile w (32 channels) and all 7 pixel tiles.
+//   half:  half a node per workgroup: output rows 0..6 or 7..13.  The workgroup convolves an 8-row window (rows
+//          0..7 or 6..13: the second conv needs one row of the first conv's output beyond its own rows), i.e.
+//          4 pixel tiles; wave w owns channel tile w of all four.  Two CUs share a node, which shortens
+//          narrow launch groups at the price of 8/7 of the MFMA work.
+// Both fit 256 registers and half of a CU's LDS, so that two workgroups share a CU where a launch group is wide enough,
+// and one's staging, swap and epilogue run under the other's MFMAs.  (A whole-node layout of its own for groups of
+// up to one node per CU, with twice the weight ring in 346 registers, was 3 % slower: the accumulators then live in
+// the upper half of the register file, and every other use of them is a copy.)
+// One workgroup's share of a launch group: position `logical` (a node or half a node) of the items a.items[0 .. a.count).
+// KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m.
+template <bool HALF, bool KEEP = false>
 __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 {
     using namespace mf;
-    static_assert(WMODE == 2 || WMODE == 3 || WMODE == 4, "layouts");
-    constexpr int WM = (WMODE == 4) ? 2 : WMODE;
-    constexpr int NPW = 1;                    // nodes per workgroup
-    constexpr int WPN = 4;                    // waves per node
-    constexpr int NT = 1;                     // channel tiles per wave
-    constexpr bool HALF = (WM == 3);
     constexpr int MTW = HALF ? 4 : MT7;       // pixel tiles per wave: all of the node's (or of the half node's window)
-    constexpr int NTHR = 64 * WPN;            // threads that stage one node
-    constexpr bool DEEP = ALLOW_DEEP && (WMODE == 2 || WMODE == 3);
-    constexpr int RW = DEEP ? 24 : 8;         // weight ring depth in K-steps
-    constexpr int XS = (WMODE == 4) ? 2 : 4;  // register sets of activation fragments (look-ahead of XS / 2 steps)
+    constexpr int NTHR = 256;
+    constexpr int RW = 12;                    // weight ring in fragments
+    constexpr int XW = HALF ? 12 : 10;        // register sets of activation fragments
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
-    const int first = HALF ? (logical >> 1) : logical * NPW;
-    if (first >= a.count) return;
+    const int node = HALF ? (logical >> 1) : logical;
+    if (node >= a.count) return;
     // pixel window of this workgroup: image rows [wrow0, wrow0 + wrows); output rows [orow0, orow1)
     const int wrow0 = HALF ? (logical & 1) * 6 : 0;
     constexpr int wrows = HALF ? 8 : S;
-    constexpr int NPIX = wrows * S;           // 196 or 112
     const int orow0 = HALF ? (logical & 1) * 7 : 0, orow1 = HALF ? orow0 + 7 : S;
 
     PHASE(0);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int node_local = wave / WPN, wi = wave % WPN;
-    const bool active = first + node_local < a.count;                 // wave-uniform
-    const dynb_item it = a.items[active ? first + node_local : first];
-    const bool binary = active && a.arity[it.type] == 2;
-    const uint32_t tile = uint32_t(node_local) * TILE_BYTES;
+    const dynb_item it = a.items[node];
+    const bool binary = a.arity[it.type] == 2;                        // uniform over the workgroup
     const int r = lane & 31, h = lane >> 5;
-    const int n0 = wi * 32 * NT;              // first output channel of this wave
+    const int n0 = wave * 32;                 // first output channel of this wave
+    const size_t keep_at = size_t(a.first_item + node) * P;           // first pixel of this item's kept maps
 
-    // packed weights of this wave's channel tiles: fragment (tap, j) of a conv follows at (tap*8 + j) * FRAG
-    const bf16_t* wrow_a[NT];
-    const bf16_t* wrow_b[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const size_t frag0 = (size_t(it.type) * 4 + (n0 >> 5) + nt) * 9 * 8;
-        wrow_a[nt] = a.w3a + frag0 * FRAG + lane * 8;
-        wrow_b[nt] = a.w3b + frag0 * FRAG + lane * 8;
-    }
-    bf16x8 ring[RW][NT];
+    // packed weights of this wave's channel tile
+    const bf16_t* wrow_a = a.w3a + (size_t(it.type) * 4 + wave) * 72 * FRAG + lane * 8;
+    const bf16_t* wrow_b = a.w3b + (size_t(it.type) * 4 + wave) * 72 * FRAG + lane * 8;
+    bf16x8 ring[RW];
 
     // ---- gather: zero border once, then the argument map into the centre of the halo tile;
     // all global loads of the map are issued before the first LDS write, so one memory latency is paid
-    const int tl = tid % NTHR;
     // rows of the argument map that the window's 3x3 taps can touch
     const int srow0 = wrow0 > 0 ? wrow0 - 1 : 0;
     const int srow1 = wrow0 + wrows + 1 < S ? wrow0 + wrows + 1 : S;
@@ -176,77 +159,86 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
         const u32x4* s4 = reinterpret_cast<const u32x4*>(src);
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
-            const int c = c_lo + tl + i * NTHR;
+            const int c = c_lo + tid + i * NTHR;
             if (c < c_hi) tmp[i] = s4[c];
         }
     };
     auto stage_store = [&]() {
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
-            const int c = c_lo + tl + i * NTHR;
+            const int c = c_lo + tid + i * NTHR;
             if (c < c_hi) {
                 const int p = c >> 4, part = c & 15;
-                const uint32_t addr = tile + uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16);
+                const uint32_t addr = uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16);
                 *reinterpret_cast<u32x4*>(lds_raw + addr) = tmp[i];
             }
         }
     };
-    auto stage = [&](const bf16_t* src) { stage_load(src); stage_store(); };
+    // the centre of the halo tile -> a map, this workgroup's output rows, in coalesced 16-byte pieces
+    auto copy_out = [&](bf16_t* dst) {
+        constexpr int OUTPIECES = (HALF ? 7 : S) * S * 16;
+#pragma unroll
+        for (int i = 0; i < (OUTPIECES + NTHR - 1) / NTHR; ++i) {
+            const int c = orow0 * S * 16 + tid + i * NTHR;
+            if (c < orow1 * S * 16) {
+                const int p = c >> 4, part = c & 15;
+                reinterpret_cast<u32x4*>(dst)[c] = *reinterpret_cast<const u32x4*>(
+                    lds_raw + uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16));
+            }
+        }
+    };
+    auto arg_map = [&](int32_t s) { return s >= 0 ? a.slots + size_t(s) * (P * C) : a.feats + size_t(-1 - s) * (P * C); };
     // Loads return in the order they were issued: the argument map (needed first) goes ahead of the weight ring,
     // whose fragments then arrive while the map is written to the tile.
-    if (active) stage_load(it.src0 >= 0 ? a.slots + size_t(it.src0) * (P * C) : a.feats + size_t(-1 - it.src0) * (P * C));
+    stage_load(arg_map(it.src0));
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (DEEP)
-        if (!a.any_binary) ring_fill<NT, RW>(ring, wrow_a);
-    if (active) {
-        for (int c = tl; c < 60 * 16; c += NTHR) {
-            const int q = c >> 4, part = c & 15;
-            int row, col;
-            if (q < 16) { row = 0; col = q; }
-            else if (q < 32) { row = HALO - 1; col = q - 16; }
-            else { row = 1 + ((q - 32) >> 1); col = ((q - 32) & 1) ? HALO - 1 : 0; }
-            *reinterpret_cast<u32x4*>(lds_raw + tile + uint32_t(row * ROW_BYTES + col * PIX_BYTES + part * 16)) =
-                u32x4{0u, 0u, 0u, 0u};
-        }
-        stage_store();
+    // biases through LDS: b3a, b3b, b1 (requested here, not where a wave would wait for them)
+    float bias_reg[2] = {0.f, 0.f};
+    {
+        const float* const b0 = tid < C ? a.b3a : a.b3b;
+        if (b0) bias_reg[0] = b0[size_t(it.type) * C + (tid & (C - 1))];
+        if (binary && a.b1 && tid < C) bias_reg[1] = a.b1[size_t(it.type) * C + tid];
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if (!binary) ring_fill<RW>(ring, wrow_a);
+    for (int c = tid; c < BORDER_PIX * 16; c += NTHR) zero_border_piece(c);
+    *reinterpret_cast<float*>(lds_raw + BIAS_OFF + tid * 4) = bias_reg[0];
+    if (tid < C) *reinterpret_cast<float*>(lds_raw + BIAS_OFF + (2 * C + tid) * 4) = bias_reg[1];
+    stage_store();
 
-    // per-lane LDS addresses: top-left tap of the pixel this lane feeds to the MFMA B operand,
-    // already advanced to this lane half's 64-channel run
-    uint32_t xaddr[MTW];
-#pragma unroll
-    for (int t = 0; t < MTW; ++t) {
-        const int p = wrow0 * S + min(t * 32 + r, NPIX - 1);
-        xaddr[t] = tile + uint32_t((p / S) * ROW_BYTES + (p % S) * PIX_BYTES + h * 128);
-    }
-    // this lane's 16 accumulator elements of channel tile nt are channels n0 + nt*32 + 16*h + (0..15)
-    // (the packed weights carry the matching row permutation)
-    auto chan = [&](int nt) -> int { return n0 + nt * 32 + 16 * h; };
-    f32x16 acc[MTW][NT];
+    // this lane's LDS address for the window's first row pair; the pixel it ends up with in tile t is column px of
+    // window row 2 t + py (columns 14 and 15 are padding)
+    const uint32_t x0 = pair_lane_addr(lane) + uint32_t(wrow0 * ROW_BYTES);
+    const int px = r & 15, py = r >> 4;
+    const bool real = px < S;
+    // its 16 accumulator elements are channels chan .. chan + 15 (the packed weights carry the matching row permutation)
+    const int chan = n0 + 16 * h;
+    f32x16 acc[MTW];
 
-    auto init_bias = [&](const float* bias) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                if (bias) v = *reinterpret_cast<const f32x4*>(bias + size_t(it.type) * C + chan(nt) + b * 4);
-#pragma unroll
-                for (int t = 0; t < MTW; ++t) {
-                    acc[t][nt][4 * b + 0] = v.x; acc[t][nt][4 * b + 1] = v.y;
-                    acc[t][nt][4 * b + 2] = v.z; acc[t][nt][4 * b + 3] = v.w;
-                }
-            }
+    auto bias4 = [&](int which, int b) {      // channels chan + 4 b .. + 3 of b3a (0), b3b (1), b1 (2)
+        return *reinterpret_cast<const f32x4*>(lds_raw + BIAS_OFF + uint32_t((which * C + chan + b * 4) * 4));
     };
-    // byte address of this lane's centre pixel of tile t (channel 0)
-    auto centre = [&](int t) -> uint32_t { return xaddr[t] - uint32_t(h * 128) + CENTER; };
-    // ReLU(acc[t][nt][8q .. 8q+7]) as 8 packed bf16 (q = 0, 1)
-    auto packed = [&](int t, int nt, int q) -> u32x4 {
+    auto init_bias = [&](int which) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const f32x4 v = bias4(which, b);
+#pragma unroll
+            for (int t = 0; t < MTW; ++t) {
+                acc[t][4 * b + 0] = v.x; acc[t][4 * b + 1] = v.y;
+                acc[t][4 * b + 2] = v.z; acc[t][4 * b + 3] = v.w;
+            }
+        }
+    };
+    // byte address of this lane's centre pixel of tile t, its first channel
+    const uint32_t c0 = x0 - uint32_t(h * 128) + uint32_t(CENTER + chan * 2);
+    auto centre = [&](int t) -> uint32_t { return c0 + uint32_t(2 * t * ROW_BYTES); };
+    // ReLU(acc[t][8q .. 8q+7]) as 8 packed bf16 (q = 0, 1)
+    auto packed = [&](int t, int q) -> u32x4 {
         u32x4 pk;
-        pk.x = relu_bf16x2(pack_bf16x2(acc[t][nt][8 * q + 0], acc[t][nt][8 * q + 1]));
-        pk.y = relu_bf16x2(pack_bf16x2(acc[t][nt][8 * q + 2], acc[t][nt][8 * q + 3]));
-        pk.z = relu_bf16x2(pack_bf16x2(acc[t][nt][8 * q + 4], acc[t][nt][8 * q + 5]));
-        pk.w = relu_bf16x2(pack_bf16x2(acc[t][nt][8 * q + 6], acc[t][nt][8 * q + 7]));
+        pk.x = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 0], acc[t][8 * q + 1]));
+        pk.y = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 2], acc[t][8 * q + 3]));
+        pk.z = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 4], acc[t][8 * q + 5]));
+        pk.w = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 6], acc[t][8 * q + 7]));
         return pk;
     };
 
@@ -256,139 +248,108 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 
     // ---- binary functions: u = ReLU(conv1x1(concat(arg0, arg1)) + b1), built in the same tile.
     // The first conv3x3 reads u one row beyond the window, so in half-node mode the 1x1 runs on its
-    // own 9-row window (rows 0..8 or 5..13: 126 pixels, still 4 tiles).
-    if (a.any_binary) {                                   // uniform over the launch group
-        const int urow0 = HALF ? (wrow0 > 0 ? wrow0 - 1 : 0) : 0;
+    // own 9-row window (rows 0..8 or 5..13: 126 pixels, in tiles of 32 consecutive ones that is still 4 tiles).
+    if (binary) {
+        const int urow0 = wrow0 > 0 ? wrow0 - 1 : 0;
         constexpr int UPIX = HALF ? 9 * S : P;
-        uint32_t uaddr[MTW];
+        uint32_t ua[HALF ? MTW : 1];
+        if constexpr (HALF) {
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            const int p = urow0 * S + min(t * 32 + r, UPIX - 1);
-            uaddr[t] = tile + uint32_t((p / S) * ROW_BYTES + (p % S) * PIX_BYTES + h * 128);
-        }
-        const bf16_t* w1row[NT];                          // first half of the 1x1 weights (argument 0), then the second
-        const bf16_t* w1row2[NT];
+            for (int t = 0; t < MTW; ++t) {
+                const int p = urow0 * S + min(t * 32 + r, UPIX - 1);
+                ua[t] = uint32_t(CENTER + (p / S) * ROW_BYTES + (p % S) * PIX_BYTES + h * 128);
+            }
+        } else ua[0] = x0 + uint32_t(CENTER);
+        auto uaddr = [&](int t) { return HALF ? ua[HALF ? t : 0] : ua[0] + uint32_t(2 * t * ROW_BYTES); };
+        // the first half of the 1x1 weights (argument 0), then the second: its fragments are fetched under the first
+        // half's loop and wait while the second argument is staged
+        const bf16_t* w1row = a.w1 + (size_t(it.type) * 4 + wave) * 16 * FRAG + lane * 8;
+        bf16x8 w1f[8];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            w1row[nt] = a.w1 + ((size_t(it.type) * 4 + (n0 >> 5) + nt) * 2 * 8) * FRAG + lane * 8;
-            w1row2[nt] = w1row[nt] + 8 * FRAG;
-        }
-        // the second half's fragments are fetched under the first half's loop and wait in the ring while the second
-        // argument is staged
-        bf16x8 ring1[8][NT];
-        if (binary) {
-            ring_fill<NT, 8>(ring1, w1row);
-            init_bias(a.b1);
-            kloop<MTW, NT, 8, XS, true>(acc, uaddr, ring1, w1row, w1row2);
-        }
+        for (int j = 0; j < 8; ++j) w1f[j] = *reinterpret_cast<const bf16x8*>(w1row + j * FRAG);
+        stage_load(arg_map(it.src1));                     // arrives under the first half's loop
+        __builtin_amdgcn_sched_barrier(0);
+        init_bias(2);
+        kloop1<MTW, true>(acc, uaddr, w1f, w1row + 8 * FRAG);
         __syncthreads();
-        if (binary) stage(it.src1 >= 0 ? a.slots + size_t(it.src1) * (P * C) : a.feats + size_t(-1 - it.src1) * (P * C));
+        stage_store();
         __syncthreads();
-        if (binary) kloop<MTW, NT, 8, XS, true>(acc, uaddr, ring1, w1row2, w1row2);
+        kloop1<MTW, false>(acc, uaddr, w1f, nullptr);
+        ring_fill<RW>(ring, wrow_a);                      // (only now: the loops above need the registers)
         __syncthreads();
-        if (binary) {                                     // ReLU(acc) -> bf16 -> centre of the halo tile (in place)
 #pragma unroll
-            for (int t = 0; t < MTW; ++t)
-                if (t * 32 + r < UPIX) {
+        for (int t = 0; t < MTW; ++t)                     // ReLU(acc) -> bf16 -> centre of the halo tile (in place)
+            if (HALF ? t * 32 + r < UPIX : real) {
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const u32x4 pk = packed(t, nt, q);
-                            *reinterpret_cast<u32x4*>(lds_raw + uaddr[t] - uint32_t(h * 128) + CENTER +
-                                                      uint32_t((chan(nt) + q * 8) * 2)) = pk;
-                            // (half-node layouts: the two windows overlap; both write the same values there)
-                            if constexpr (KEEP)
-                                *reinterpret_cast<u32x4*>(a.keep_u + (size_t(a.first_item + first + node_local) * P + urow0 * S + t * 32 + r) * C +
-                                                          chan(nt) + q * 8) = pk;
-                        }
+                for (int q = 0; q < 2; ++q) {
+                    const u32x4 pk = packed(t, q);
+                    *reinterpret_cast<u32x4*>(lds_raw + uaddr(t) - uint32_t(h * 128) + uint32_t((chan + q * 8) * 2)) = pk;
                 }
-        }
+            }
         __syncthreads();
+        if constexpr (KEEP) copy_out(a.keep_u + keep_at * C);
     }
 
     // ---- first conv3x3 + ReLU, result replaces the tile; the old centre values become the residual
     PHASE(3);
-    if (active) {
-        if (!DEEP || a.any_binary) ring_fill<NT, RW>(ring, wrow_a);   // (after the 1x1 convolution, whose loops need the registers)
-        init_bias(a.b3a);
-        kloop<MTW, NT, RW, XS, false>(acc, xaddr, ring, wrow_a, wrow_b);   // leaves the ring filled for the second conv
-    }
+    init_bias(0);
+    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_a, wrow_b);       // leaves the ring filled for the second conv
     PHASE(4);
     __syncthreads();
     PHASE(5);
-    if (active) {
-        auto bias8 = [&](int ch, f32x4& lo, f32x4& hi) {
-            lo = f32x4{0.f, 0.f, 0.f, 0.f};
-            hi = lo;
-            if (a.b3b) {
-                const float* bp = a.b3b + size_t(it.type) * C + ch;
-                lo = *reinterpret_cast<const f32x4*>(bp);
-                hi = *reinterpret_cast<const f32x4*>(bp + 4);
+    if (real) {
+        // acc[t][8q .. 8q+7]: ReLU'd bf16 into the tile, old centre values + bias back into acc
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const f32x4 blo = bias4(1, 2 * q), bhi = bias4(1, 2 * q + 1);
+#pragma unroll
+            for (int t = 0; t < MTW; ++t) {
+                u32x4* at = reinterpret_cast<u32x4*>(lds_raw + centre(t) + uint32_t(q * 16));
+                const u32x4 res = *at;
+                const u32x4 pk = packed(t, q);
+                *at = pk;
+                acc[t][8 * q + 0] = __uint_as_float(res.x << 16) + blo.x;
+                acc[t][8 * q + 1] = __uint_as_float(res.x & 0xffff0000u) + blo.y;
+                acc[t][8 * q + 2] = __uint_as_float(res.y << 16) + blo.z;
+                acc[t][8 * q + 3] = __uint_as_float(res.y & 0xffff0000u) + blo.w;
+                acc[t][8 * q + 4] = __uint_as_float(res.z << 16) + bhi.x;
+                acc[t][8 * q + 5] = __uint_as_float(res.z & 0xffff0000u) + bhi.y;
+                acc[t][8 * q + 6] = __uint_as_float(res.w << 16) + bhi.z;
+                acc[t][8 * q + 7] = __uint_as_float(res.w & 0xffff0000u) + bhi.w;
             }
-        };
-        // acc[t][nt][8q .. 8q+7]: ReLU'd bf16 into the tile, old centre values + bias back into acc
-        auto swap8 = [&](int t, int nt, int q, const f32x4& blo, const f32x4& bhi) {
-            const uint32_t addr = centre(t) + uint32_t((chan(nt) + q * 8) * 2);
-            const u32x4 res = *reinterpret_cast<const u32x4*>(lds_raw + addr);
-            const u32x4 pk = packed(t, nt, q);
-            *reinterpret_cast<u32x4*>(lds_raw + addr) = pk;
-            if constexpr (KEEP)
-                *reinterpret_cast<u32x4*>(a.keep_m + (size_t(a.first_item + first + node_local) * P + wrow0 * S + t * 32 + r) * C +
-                                          chan(nt) + q * 8) = pk;
-            acc[t][nt][8 * q + 0] = __uint_as_float(res.x << 16) + blo.x;
-            acc[t][nt][8 * q + 1] = __uint_as_float(res.x & 0xffff0000u) + blo.y;
-            acc[t][nt][8 * q + 2] = __uint_as_float(res.y << 16) + blo.z;
-            acc[t][nt][8 * q + 3] = __uint_as_float(res.y & 0xffff0000u) + blo.w;
-            acc[t][nt][8 * q + 4] = __uint_as_float(res.z << 16) + bhi.x;
-            acc[t][nt][8 * q + 5] = __uint_as_float(res.z & 0xffff0000u) + bhi.y;
-            acc[t][nt][8 * q + 6] = __uint_as_float(res.w << 16) + bhi.z;
-            acc[t][nt][8 * q + 7] = __uint_as_float(res.w & 0xffff0000u) + bhi.w;
-        };
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                f32x4 blo, bhi;
-                bias8(chan(nt) + q * 8, blo, bhi);
-#pragma unroll
-                for (int t = 0; t < MTW; ++t)
-                    if (t * 32 + r < NPIX) swap8(t, nt, q, blo, bhi);
-            }
+        }
     }
     PHASE(6);
     __syncthreads();
     PHASE(7);
 
-    // ---- second conv3x3 on top of (residual + bias), ReLU, scatter
-    if (active) {
-        kloop<MTW, NT, RW, XS, false>(acc, xaddr, ring, wrow_b, wrow_b);
-        PHASE(8);
-        bf16_t* dst = it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C);
+    if constexpr (KEEP) copy_out(a.keep_m + keep_at * C);
+
+    // ---- second conv3x3 on top of (residual + bias), ReLU, scatter.  The result leaves through the tile: in the
+    // accumulators a lane holds 32 bytes of a pixel, and stores in which every lane touches a line of its own take 4.4k
+    // clocks of a whole-node workgroup's 53k, the way through LDS with coalesced stores 3.6k.
+    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_b, wrow_b);
+    PHASE(8);
+    __syncthreads();
+    if (real) {
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            const int pl = t * 32 + r;
-            const int p = wrow0 * S + pl;
-            if (pl < NPIX && p >= orow0 * S && p < orow1 * S) {
+        for (int t = 0; t < MTW; ++t)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        *reinterpret_cast<u32x4*>(dst + size_t(p) * C + chan(nt) + q * 8) = packed(t, nt, q);
-            }
-        }
+            for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(lds_raw + centre(t) + uint32_t(q * 16)) = packed(t, q);
     }
+    __syncthreads();
+    copy_out(it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C));
     PHASE(9);
 }
 
-template <int WMODE, bool KEEP = false>
-__global__ __launch_bounds__(256, WMODE == 4 ? 2 : 1) void k_module_mfma(MfArgs a)
+template <bool HALF, bool KEEP = false>
+__global__ __launch_bounds__(256, 2) void k_module_mfma(MfArgs a)
 {
     // Workgroup -> position in the launch group.  Consecutive workgroup ids land on different
     // XCDs; give every XCD one contiguous run of items (items are sorted by function id) so that
     // a function's weights stay in as few L2s as possible.
     const int per_xcd = gridDim.x >> 3;
-    module_body<WMODE, true, KEEP>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    module_body<HALF, KEEP>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
 }
 
 // ---- one dependency-driven launch per batch ---------------------------------------------------------
@@ -456,10 +417,9 @@ __global__ __launch_bounds__(256, 1) void k_module_persist(MfArgs a, PersistArgs
         MfArgs b = a;
         b.items = items + (t >> 2);
         b.count = 1;
-        b.any_binary = (a.arity[b.items[0].type] == 2);
         const int part = t & 3;
-        if (part == 0) module_body<2, false>(b, 0);          // both layouts in one kernel: the shallow weight ring fits
-        else module_body<3, false>(b, part - 1);
+        if (part == 0) module_body<false>(b, 0);
+        else module_body<true>(b, part - 1);
         // Publish: every wave waits until its stores of the result have reached the L2 (all waves of a
         // workgroup sit behind the same one), then one thread writes that L2's dirty lines back to memory,
         // where every CU can see them, and raises the flag (the agent-scope release does both).
@@ -634,27 +594,10 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         int cus = 0;
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "hipDeviceGetAttribute");
         cu_count[dev & 63] = cus > 0 ? cus : 256;
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_persist),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_persist)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_mfma<2>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_mfma<2>)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_mfma<3>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_mfma<3>)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_mfma<4>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_mfma<4>)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_mfma<2, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_mfma<2, keep>)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_mfma<3, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_mfma<3, keep>)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_module_mfma<4, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_module_mfma<4, keep>)");
+        for (const void* f : {reinterpret_cast<const void*>(k_module_persist), reinterpret_cast<const void*>(k_module_mfma<false>),
+                              reinterpret_cast<const void*>(k_module_mfma<true>), reinterpret_cast<const void*>(k_module_mfma<false, true>),
+                              reinterpret_cast<const void*>(k_module_mfma<true, true>)})
+            HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, mf::LDS_BYTES), "hipFuncSetAttribute(module kernels)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
     const char* d = static_cast<const char*>(p->dev_buf);
@@ -700,10 +643,9 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         if (!p->keep) {
             a.items = reinterpret_cast<const dynb_item*>(d);
             a.count = int32_t(p->items.size());
-            a.any_binary = 0;
             const int resident = cu_count[dev & 63];          // one workgroup per CU (73 KB of LDS, all registers)
             const unsigned grid = unsigned(std::min<int>(q.n_tickets, resident));
-            hipLaunchKernelGGL(k_module_persist, dim3(grid), dim3(256), mf::TILE_BYTES, st, a, q);
+            hipLaunchKernelGGL(k_module_persist, dim3(grid), dim3(256), mf::LDS_BYTES, st, a, q);
             if (timed) dynb::timing_mark(st, 0, a.count);
             HIP_TRY(hipGetLastError(), "dynbatch_execute(dependency-driven kernel)");
             return DYNB_OK;
@@ -716,29 +658,15 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         a.items = reinterpret_cast<const dynb_item*>(d) + l.start;
         a.first_item = l.start;
         a.count = l.count;
-        a.any_binary = l.any_binary;
-        // half a node per workgroup while that still fits the chip's 256 CUs in one round, one node per
-        // workgroup up to 256 nodes; beyond that, and whenever several batches are in flight (their narrow
-        // groups share the chip), the 256-register variant with two workgroups per CU
-        int wm = (p->throughput || l.count > 256) ? 4 : (l.count <= 128) ? 3 : 2;
+        // half a node per workgroup while that still fits the chip's 256 CUs in one round; beyond that, and whenever
+        // several batches are in flight (their narrow groups share the chip), one node per workgroup
+        bool half = !p->throughput && l.count <= 128;
 #ifdef DYNB_PHASE_CLOCKS
-        if (const char* f = getenv("DYNB_FORCE_WM")) wm = atoi(f);
+        if (const char* f = getenv("DYNB_FORCE_HALF")) half = atoi(f) != 0;
 #endif
-        const int nwg = (wm == 3) ? 2 * l.count : l.count;
-        const unsigned grid = unsigned((nwg + 7) / 8 * 8);
-        if (p->keep) {
-            if (wm == 4)
-                hipLaunchKernelGGL((k_module_mfma<4, true>), dim3(grid), dim3(256), mf::TILE_BYTES, st, a);
-            else if (wm == 3)
-                hipLaunchKernelGGL((k_module_mfma<3, true>), dim3(grid), dim3(256), mf::TILE_BYTES, st, a);
-            else
-                hipLaunchKernelGGL((k_module_mfma<2, true>), dim3(grid), dim3(256), mf::TILE_BYTES, st, a);
-        } else if (wm == 4)
-            hipLaunchKernelGGL((k_module_mfma<4>), dim3(grid), dim3(256), mf::TILE_BYTES, st, a);
-        else if (wm == 3)
-            hipLaunchKernelGGL((k_module_mfma<3>), dim3(grid), dim3(256), mf::TILE_BYTES, st, a);
-        else
-            hipLaunchKernelGGL((k_module_mfma<2>), dim3(grid), dim3(256), mf::TILE_BYTES, st, a);
+        const unsigned grid = unsigned(((half ? 2 * l.count : l.count) + 7) / 8 * 8);
+        auto* kernel = half ? (p->keep ? k_module_mfma<true, true> : k_module_mfma<true>) : (p->keep ? k_module_mfma<false, true> : k_module_mfma<false>);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), mf::LDS_BYTES, st, a);
         if (timed && !coarse) dynb::timing_mark(st, int32_t(&l - p->launches.data()), l.count);
     }
     if (coarse) dynb::timing_mark(st, 0, evals);

@@ -14,11 +14,18 @@ constexpr int S = 14;                    // spatial size
 constexpr int P = S * S;                 // 196 pixels
 constexpr int HALO = 16;                 // tile side with zero border
 constexpr int PIX_BYTES = 272;           // 128 channels bf16 + 16 bytes pad: 17 granules of 16 bytes
-// Row pitch in 16-byte granules is 16*17 + 14 = 286 = 14 (mod 16), so that the 16 consecutive
-// raster pixels of one MFMA fragment (which cross a 14-pixel image row) still fall on 16 distinct
-// granules mod 16, i.e. on all 64 LDS banks: pixel (y, x) sits at granule 14 y + x (mod 16).
-constexpr int ROW_BYTES = HALO * PIX_BYTES + 14 * 16;  // 4576
-constexpr int TILE_BYTES = HALO * ROW_BYTES;           // 73216
+// A pixel (y, x) sits at granule x (mod 16): the pixels of one image row, which half a fragment reads, fall on
+// distinct granules, i.e. on all 64 LDS banks.
+// Rows are 17 pixels wide: columns 15 and 16 and the next row's column 0 are zeros, which is what the two padding columns
+// of a pixel tile (below) read, whatever the tap.  (Zeros and not the last pixel again: the chip is at its power limit in
+// these kernels, and the matrix pipes take less of it for zeros; the K loop alone, on all CUs, runs at 1.62 instead of
+// 1.52 PFLOP/s.)
+constexpr int ROW_PIX = HALO + 1;
+constexpr int ROW_BYTES = ROW_PIX * PIX_BYTES;         // 4624
+constexpr int TILE_BYTES = HALO * ROW_BYTES + PIX_BYTES;   // 74256: the last row's neighbour is a zero pixel of its own
+constexpr int BORDER_PIX = 2 * ROW_PIX + (HALO - 2) * 3 + 1;
+constexpr int BIAS_OFF = TILE_BYTES;                    // behind the tile: three vectors of C biases
+constexpr int LDS_BYTES = TILE_BYTES + 3 * C * 4;       // 75792: two workgroups per CU
 constexpr int CENTER = ROW_BYTES + PIX_BYTES;           // (+1,+1) from the top-left tap
 }  // namespace mf
 
@@ -34,107 +41,159 @@ __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr)
 //     D[32 channels][32 pixels] += W[32 channels][16 k] * X[16 k][32 pixels]
 // with the weights as the A operand and the activations as the B operand: a lane then ends up with
 // 16 channels of one pixel (consecutive ones, thanks to the row permutation of the packed weights),
-// which it can store as 16-byte pieces.  196 pixels make 7 pixel tiles (224 rows, the last 28 are
-// padding).  A wave owns one channel tile and all pixel tiles of its node.
+// which it can store as 16-byte pieces.  A pixel tile is two image rows of 14 pixels, each padded to 16 columns (the
+// padding columns read zeros and are dropped): 14 rows make 7 tiles, 224 columns for 196 pixels, the same
+// as tiles of 32 consecutive pixels would need, but a fragment then depends on its first image row alone: the
+// fragment that the upper tap row reads for one tile is the one that the lower tap row reads for the tile above.
+// A wave owns one channel tile and all pixel tiles of its node.
 //
-// K order.  Within a tap the 128 input channels are consumed in 8 steps of 16; lane half h = lane/32
-// supplies channels h*64 + j*8 .. +7 in step j (any pairing works as long as both operands agree).
+// K order.  dx (tap column) outermost, then the 128 input channels in 8 steps of 16, then the tap rows in the order 0, 2,
+// 1; lane half h = lane/32 supplies channels h*64 + j*8 .. +7 in step j (any pairing works as long as both
+// operands agree).  All layouts and both passes keep this order, so results do not depend on the layout.
 // Weight fragments.  In the caller's [Cout][kh][kw][Cin] layout one fragment load would touch 64
 // different cache lines (32 rows x 2 halves), which makes the vector L1 the bottleneck.  The
-// weights are therefore repacked (k_pack_weights) into fragment order
-//     [function][channel tile 4][tap][step 8][lane 64][8 bf16]
+// weights are therefore repacked (k_pack_weights) into fragment order, in the order of their use,
+//     conv3x3 [function][channel tile 4][dx 3][step 8][tap row 0, 2, 1][lane 64][8 bf16]
+//     conv1x1 [function][channel tile 4][argument 2][step 8][lane 64][8 bf16]
 // so that the 64 lanes of a fragment load read one contiguous kilobyte.
 constexpr int MT7 = 7;
 
 namespace mf {
 constexpr int FRAG = 512;   // elements of one packed weight fragment: 64 lanes x 8 bf16 = 1 KB
+
+// tap (kh, kw) and step of fragment f (0 .. 71) of a packed conv3x3
+__host__ __device__ constexpr int frag_kw(int f) { return f / 24; }
+__host__ __device__ constexpr int frag_step(int f) { return f / 3 % 8; }
+__host__ __device__ constexpr int frag_kh(int f) { return f % 3 == 0 ? 0 : f % 3 == 1 ? 2 : 1; }
 }
 
-// ---- K loop -----------------------------------------------------------------------------------------
-// acc[t][nt] += W * X over one 3x3 convolution (9 taps x 8 steps of 16 input channels) or, CENTER_ONLY, over the
-// 8 steps of the centre tap (one half of the 1x1 convolution).  Software pipelined by hand:
-//   * activation fragments live in XS register sets; the LDS reads that fill the set of the step XS/2 ahead are
-//     interleaved one by one with the MFMAs of the current step, so LDS traffic is spread evenly under them;
-//   * weight fragments live in a ring of RW steps (the caller's registers); the slot of the previous step is
-//     refilled from global memory right after the first pixel tile of the current step, RW - 1 steps ahead of its
-//     use (issuing the load directly behind the MFMAs that still read the slot would stall the wave);
+// LDS byte offset, from the tile's first byte, of what lane `lane` reads for the tile row pair that starts at tile row 0,
+// tap column 0: image row lane%32/16, column lane%16 (for columns 14, 15 the zeros from column 15 on), its half of the channels
+__device__ __forceinline__ uint32_t pair_lane_addr(int lane)
+{
+    const int r = lane & 31;
+    return uint32_t((r >> 4) * mf::ROW_BYTES + ((r & 15) < mf::S ? r & 15 : mf::S + 1) * mf::PIX_BYTES + (lane >> 5) * 128);
+}
+
+// writes piece c (16 bytes; c < 16 BORDER_PIX) of the halo tile's zero border
+__device__ __forceinline__ void zero_border_piece(int c)
+{
+    using namespace mf;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const int q = c >> 4;
+    int row, col;
+    if (q < ROW_PIX) { row = 0; col = q; }
+    else if (q < 2 * ROW_PIX + 1) { row = HALO - 1; col = q - ROW_PIX; }        // (and the pixel behind the last row)
+    else { row = 1 + (q - 2 * ROW_PIX - 1) / 3; col = (q - 2 * ROW_PIX - 1) % 3; if (col > 0) col += HALO - 2; }
+    *reinterpret_cast<u32x4*>(lds_raw + uint32_t(row * ROW_BYTES + col * PIX_BYTES + (c & 15) * 16)) = u32x4{0u, 0u, 0u, 0u};
+}
+
+// ---- K loop of a conv3x3 ----------------------------------------------------------------------------
+// acc[t] += W * X over 9 taps x 8 steps of 16 input channels.  x0: this lane's address for the first row pair of the
+// window (pair_lane_addr of the window's first tile row).  Per (dx, step) the wave reads the 2 MTW + 1 fragments whose
+// row pairs start at tile rows 0 .. 2 MTW and multiplies each with every tap row that needs it: even ones with tap row 0
+// (tile s/2) and tap row 2 (tile s/2 - 1), odd ones with tap row 1.  MTW = 7: 15 LDS reads for 21 MFMAs.
+// The loop itself is bound by the matrix pipes: 17.4k clocks per conv3x3 of a lone workgroup with everything hot in L2
+// (504 MFMAs per wave are 16.1k; the LDS reads add 0.1k, the weight loads 0.6k), 18.3k in the kernel.  On the whole chip it
+// is bound by power, not by any pipe (the clock falls to 1.7-1.9 GHz of 2.4): register-only MFMAs on random data reach
+// 1.70 PFLOP/s, the LDS reads cost 7 % of that and the weight loads 11 %, which is why every fragment is read once per
+// use of its rows and once per workgroup.
+// Software pipelined by hand:
+//   * activation fragments live in XW register sets and are requested XW - 1 fragments ahead, one request before the
+//     MFMAs of each fragment;
+//   * weight fragments live in a ring of RW register sets (RW/3 steps); the previous step's are refilled from global
+//     memory behind the first MFMAs of the current step, RW/3 - 1 steps ahead of their use (issuing the load directly
+//     behind the MFMAs that still read the slot would stall the wave);
 //   * scheduler fences keep that order (the compiler would otherwise sink every load to its use).
 // The ring is filled by ring_fill, a call of its own so that the caller can issue it long before the loop; the
 // last chunk refills the ring with the first fragments of the NEXT loop (wnext), which then starts full.
-// Measured on this chip: a workgroup receives about 27 bytes per clock of weight fragments whatever the
-// look-ahead, so a loop is only MFMA-bound if every fragment is fetched once per workgroup: each wave owns one
-// channel tile (32 output channels) and all pixel tiles of its node (NT = 1); with two nodes per workgroup a
-// wave would own NT = 2 channel tiles of one node.
-template <int NT, int RW>
-__device__ __forceinline__ void ring_fill(bf16x8 (&wf)[RW][NT], const bf16_t* (&wrow)[NT])
+// Consecutive MFMAs never use the same accumulator.
+template <int RW>
+__device__ __forceinline__ void ring_fill(bf16x8 (&wf)[RW], const bf16_t* wrow)
 {
 #pragma unroll
-    for (int j = 0; j < RW - 1; ++j) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) wf[j][nt] = *reinterpret_cast<const bf16x8*>(wrow[nt] + j * mf::FRAG);
+    for (int j = 0; j < RW - 3; ++j) {
+        wf[j] = *reinterpret_cast<const bf16x8*>(wrow + j * mf::FRAG);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-template <int MTW, int NT, int RW, int XS, bool CENTER_ONLY>
-__device__ __forceinline__ void kloop(f32x16 (&acc)[MTW][NT], const uint32_t (&xaddr)[MTW], bf16x8 (&wf)[RW][NT],
-                                      const bf16_t* (&wrow)[NT], const bf16_t* (&wnext)[NT])
+template <int MTW, int RW, int XW>
+__device__ __forceinline__ void kloop3(f32x16 (&acc)[MTW], const uint32_t x0, bf16x8 (&wf)[RW], const bf16_t* wrow, const bf16_t* wnext)
 {
-    constexpr int NSTEP = CENTER_ONLY ? 8 : 72;
-    constexpr int NCHUNK = NSTEP / RW, XA = XS / 2;
-    static_assert(NSTEP % RW == 0 && RW % 8 == 0 && RW % XS == 0 && (XS == 2 || XS == 4), "ring shapes");
-    static_assert(RW == 8 || RW == 24, "a chunk is one tap or one kernel row");
-    // byte offset of step j (0 .. RW) of a chunk from the chunk's first tap: taps advance by a pixel, steps by 16 bytes
-    auto in_chunk = [](int j) -> uint32_t { return uint32_t((j / 8) * mf::PIX_BYTES + (j % 8) * 16); };
-    auto chunk_base = [](int c) -> uint32_t {
-        if (CENTER_ONLY) return uint32_t(mf::CENTER);
-        if (RW == 24) return uint32_t(c) * mf::ROW_BYTES;
-        return uint32_t(c / 3) * mf::ROW_BYTES + uint32_t(c % 3) * mf::PIX_BYTES;
+    constexpr int NF = 2 * MTW + 1, STEPS = RW / 3, NCHUNK = 24 / STEPS, G = STEPS * NF;
+    static_assert(RW % 3 == 0 && (STEPS == 8 || STEPS == 4) && G % XW == 0, "ring shapes");
+    // the row pairs are taken in the order 0, 2, 1, 4, 3, 6, 5, ...: one and two MFMAs per fragment in turn
+    auto row_of = [](int k) -> int { return k == 0 ? 0 : (k & 1) ? k + 1 : k - 1; };
+    // fragment g of a chunk: byte offset from the chunk's first tap and channel step
+    auto at = [&](int g) -> uint32_t {
+        return uint32_t(row_of(g % NF) * mf::ROW_BYTES + (g / NF) * 16);
     };
-    bf16x8 x[XS][MTW];
+    auto chunk_base = [](int c) -> uint32_t {
+        return STEPS == 8 ? uint32_t(c) * mf::PIX_BYTES : uint32_t(c >> 1) * mf::PIX_BYTES + uint32_t(c & 1) * 64;
+    };
+    bf16x8 x[XW];
 #pragma unroll
-    for (int jj = 0; jj < XA; ++jj)
-#pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            x[jj][t] = lds_read_frag(xaddr[t] + chunk_base(0) + in_chunk(jj));
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int g = 0; g < XW - 1; ++g) {
+        x[g] = lds_read_frag(x0 + at(g));
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll 1
     for (int c = 0; c < NCHUNK; ++c) {
         const bool last = c + 1 >= NCHUNK;
-        uint32_t xa[MTW], xn[MTW];                      // this chunk's and the next chunk's activations
+        const uint32_t xa = x0 + chunk_base(c), xn = x0 + chunk_base(last ? c : c + 1);   // after the last chunk: re-read valid data
+        const bf16_t* cur = wrow + (c * RW + RW - 3) * mf::FRAG;        // the last step of this chunk
+        const bf16_t* nxt = last ? wnext : wrow + (c + 1) * RW * mf::FRAG;   // the next chunk / the next loop
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            xa[t] = xaddr[t] + chunk_base(c);
-            xn[t] = xaddr[t] + chunk_base(last ? c : c + 1);        // after the last chunk: re-read valid data
-        }
-        const bf16_t* cur[NT];                          // fragment RW - 1 of this chunk
-        const bf16_t* nxt[NT];                          // fragments 0 .. RW - 2 of the next chunk / the next loop
+        for (int st = 0; st < STEPS; ++st) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            cur[nt] = wrow[nt] + (c * RW + RW - 1) * mf::FRAG;
-            nxt[nt] = last ? wnext[nt] : wrow[nt] + (c + 1) * RW * mf::FRAG;
-        }
-#pragma unroll
-        for (int j = 0; j < RW; ++j) {
-            const int ja = j + XA;                      // the step whose activations are fetched now
-#pragma unroll
-            for (int t = 0; t < MTW; ++t) {
-                x[ja % XS][t] = lds_read_frag(ja >= RW ? xn[t] + in_chunk(ja - RW) : xa[t] + in_chunk(ja));
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[t][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j][nt], x[j % XS][t], acc[t][nt], 0, 0, 0);
+            for (int k = 0; k < NF; ++k) {
+                const int g = st * NF + k, ga = g + XW - 1;
+                x[ga % XW] = lds_read_frag(ga >= G ? xn + at(ga - G) : xa + at(ga));
+                const int s = row_of(k), t = s / 2;
+                auto mul = [&](int tile, int w) { acc[tile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[st * 3 + w], x[g % XW], acc[tile], 0, 0, 0); };
+                if (s & 1) mul(t, 2);                  // tap row 1
+                else {
+                    if (t > 0) mul(t - 1, 1);          // tap row 2 of the tile above
+                    if (t < MTW) mul(t, 0);            // tap row 0
+                }
                 __builtin_amdgcn_sched_barrier(0);
-                if (t == 0) {                           // refill the slot of the previous step
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        wf[(j + RW - 1) % RW][nt] = j == 0 ? *reinterpret_cast<const bf16x8*>(cur[nt])
-                                                           : *reinterpret_cast<const bf16x8*>(nxt[nt] + (j - 1) * mf::FRAG);
+                if (k >= 1 && k <= 3) {                // refill the slots of the previous step
+                    wf[(st * 3 + k + RW - 4) % RW] = *reinterpret_cast<const bf16x8*>(st == 0 ? cur + (k - 1) * mf::FRAG : nxt + ((st - 1) * 3 + k - 1) * mf::FRAG);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
     }
+}
+
+// ---- conv1x1 over one argument ----------------------------------------------------------------------
+// acc[t] += W * X over 8 steps of 16 input channels; xaddr(t): this lane's pixel of tile t (centre of the halo tile, its
+// half of the channels).  The 8 weight fragments are the caller's registers; WNEXT: they are replaced by those of the
+// next call as they are used.
+template <int MTW, bool WNEXT, typename Addr>
+__device__ __forceinline__ void kloop1(f32x16 (&acc)[MTW], const Addr& xaddr, bf16x8 (&wf)[8], const bf16_t* wnext)
+{
+    constexpr int XW = 6, G = 8 * MTW;          // activation fragments: register sets, fragments in all
+    bf16x8 x[XW];
+    auto at = [&](int g) { return xaddr(g % MTW) + uint32_t(g / MTW * 16); };
+#pragma unroll
+    for (int g = 0; g < XW - 1; ++g) {
+        x[g] = lds_read_frag(at(g));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+#pragma unroll
+        for (int t = 0; t < MTW; ++t) {
+            const int g = j * MTW + t, ga = g + XW - 1;
+            if (ga < G) x[ga % XW] = lds_read_frag(at(ga));
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], x[g % XW], acc[t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (WNEXT && t == 0 && j > 0) wf[j - 1] = *reinterpret_cast<const bf16x8*>(wnext + (j - 1) * mf::FRAG);
+        }
+    }
+    if (WNEXT) wf[7] = *reinterpret_cast<const bf16x8*>(wnext + 7 * mf::FRAG);
 }
 
 }  // namespace

@@ -434,3 +434,20 @@ def test_a_wait_that_expires_is_reported_and_every_workgroup_still_exits(dyn, ut
     good = dyn.dynbatch_execute(plan, weights, feats, workspace=ws)          # the next call clears the status word
     dyn.dynbatch_execute_check(plan, feats, ws)
     assert (util.to_host(good) == util.iep_run(dyn, w)).all()
+
+
+@pytest.mark.parametrize("nodes", [1, 128, 129, 256, 257])
+def test_half_and_whole_node_layouts_at_the_width_where_they_change(dyn, util, oracle, nodes):
+    """Launch groups of up to 128 nodes spread a node over two workgroups, wider ones and DYNB_PLAN_THROUGHPUT plans give
+    it one: the same bits, one- and two-argument functions mixed, and a few examples against the oracle."""
+    arity = np.array([0, 1, 2, 1, 2], np.uint8)
+    progs = [np.array([1 + i % 4] + [0] * (1 + (i % 2)), np.int32) for i in range(nodes)]
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    w = iep.IepWorkload("widths", "bf16", arity, np.concatenate(progs), off, 128, 14, 14,
+                        iep.make_feats(nodes, nodes, 14, 14, 128, "bf16"), *iep.make_weights(78, arity, 128, "bf16"))
+    got = util.iep_run(dyn, w)
+    assert (util.iep_run(dyn, w, dyn.DYNB_PLAN_THROUGHPUT) == got).all()
+    sample = sorted({0, nodes // 2, nodes - 1})
+    ref = oracle.iep_forward_workload(w.subset(sample))
+    for j, i in enumerate(sample):
+        assert util.normwise(got[i], ref[j]) < TOL["bf16"], i
