@@ -92,11 +92,10 @@ enum {
      * bit-identical either way.  See dynbatch_execute_check for the bounded waits.                 */
     DYNB_PLAN_PERSISTENT = 16,
     /* Optional, any scheduling mode: keep every node's result (a slot of its own in the workspace, no
-     * reuse) so that dynbatch_backward can run after dynbatch_execute.  On the fast path (bf16, C = 128,
-     * 14 x 14) dynbatch_execute also saves the two intermediate maps of every node (the output of the 1x1
-     * convolution of two-argument functions and of the first 3x3 convolution) in the workspace, and a plan
-     * that also carries DYNB_PLAN_PERSISTENT runs one launch per label.  Larger workspace (three maps per
-     * node).  The plan view then lists the tables the backward pass works from.                     */
+     * reuse) so that dynbatch_backward can run after dynbatch_execute.  dynbatch_execute also saves the two
+     * intermediate maps of every node (the output of the 1x1 convolution of two-argument functions and of
+     * the first 3x3 convolution) in the workspace, and a plan that also carries DYNB_PLAN_PERSISTENT runs
+     * one launch per label.  Larger workspace (three maps per node).  The plan view then lists the tables the backward pass works from.                     */
     DYNB_PLAN_KEEP = 32
 };
 
@@ -263,8 +262,8 @@ size_t dynbatch_workspace_bytes(const dynb_plan* plan, const dynb_shape* shape);
  *   workspace  device, >= dynbatch_workspace_bytes, 256-byte aligned; contents are scratch, and
  *              nothing else may read or write it until the call's work on `stream` has finished
  *              (calls in flight on different streams need a workspace each)
- * The fast path (bf16, C = 128, 14 x 14) runs fused MFMA kernels; every other shape runs generic
- * kernels with the same semantics.  Errors: DYNB_E_INVAL, DYNB_E_WORKSPACE (workspace too small
+ * The fast path (bf16, C = 128, 14 x 14) runs fused MFMA kernels; every other shape runs
+ * implicit-GEMM convolutions with the same semantics.  Errors: DYNB_E_INVAL, DYNB_E_WORKSPACE (workspace too small
  * or plan not uploaded), DYNB_E_UNSUPPORTED (dtype; w1 NULL with binary functions), DYNB_E_HIP. */
 int dynbatch_execute(const dynb_plan* plan, const dynb_shape* shape, const dynb_module_weights* w,
                      const void* feats, void* out, void* workspace, size_t workspace_bytes,
@@ -313,8 +312,8 @@ size_t dynbatch_backward_workspace_bytes(const dynb_plan* plan, const dynb_shape
  *   workspace          device, >= dynbatch_backward_workspace_bytes, 256-byte aligned, scratch
  * Any shape and both dtypes.  bf16 with C = 128 and 14 x 14 maps (the shape of the fused forward kernels) runs on
  * MFMAs: gradients travel between nodes as fp32 maps and enter the contractions rounded to bf16, like every other
- * operand of that path.  Other shapes run plain FMA kernels (one thread per output element, fp32 gradients
- * throughout).  Every sum has a fixed order, so two calls give the same bits.  Errors: DYNB_E_INVAL, DYNB_E_WORKSPACE (too small, plan
+ * operand of that path.  Other shapes run implicit GEMMs on the fp32 matrix instructions (fp32
+ * gradients throughout).  Every sum has a fixed order, so two calls give the same bits.  Errors: DYNB_E_INVAL, DYNB_E_WORKSPACE (too small, plan
  * not uploaded), DYNB_E_UNSUPPORTED (plan without DYNB_PLAN_KEEP, dependency graphs, dtype), DYNB_E_HIP. */
 int dynbatch_backward(const dynb_plan* plan, const dynb_shape* shape, const dynb_module_weights* w, const void* feats,
                       const void* out, const void* forward_workspace, const float* dout, const dynb_module_grads* grads,

@@ -1,8 +1,7 @@
 // Backward pass of an executed plan (paper: Results / IEP times the backward pass next to inference and
 // expects the same gains from batching, since the pools are the same).  The launch groups are walked in
-// reverse; inside a group every node is independent, and the gradients of the parameters are summed pool by
-// pool (all nodes of one function in the group in one call), each parameter element by a single thread in item
-// order, so the result does not depend on scheduling.
+// reverse; inside a group every node is independent.  The gradients of the parameters are summed function by function
+// afterwards, over all its nodes in item order, so the result does not depend on scheduling.
 //
 // For a node with residual block input u, mid = ReLU(conv_a(u) + b_a), y = ReLU(u + conv_b(mid) + b_b) and
 // incoming gradient gy:
@@ -12,11 +11,11 @@
 // and for a two-argument function, u = ReLU(conv1x1(concat(a0, a1)) + b1):
 //     dc   = du * [u > 0]                      db_1 += sum_p dc     dW_1 += dc (x) concat
 //     da0  = W1[:, :C]^T dc,  da1 = W1[:, C:]^T dc
-// The node results y come from the forward pass (a plan made with DYNB_PLAN_KEEP leaves every one of them in the
-// workspace); u of two-argument functions and mid are recomputed with the forward pass's generic kernels.
-// Two kernel families with the same semantics, like the forward pass: MFMA kernels for bf16, C = 128, 14 x 14 (further
-// down), and generic kernels for any shape, fp32 or bf16 values and weights, fp32 gradients, one thread per output
-// element, which recompute u and mid with the forward pass's generic kernels.
+// The node results y, u of two-argument functions and mid come from the forward pass (a plan made with DYNB_PLAN_KEEP
+// leaves every one of them in the workspace).
+// Two kernel families with the same semantics, like the forward pass: fused kernels for bf16, C = 128, 14 x 14 (further
+// down), and for any other shape, fp32 or bf16 values and weights, one launch per transposed convolution of a launch
+// group (k_conv, iep_conv.h) and one for the parameter gradients of the whole plan (k_wgrad); fp32 gradients throughout.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,7 +25,7 @@
 #include <vector>
 
 #include "device_utils.h"
-#include "iep_generic.h"
+#include "iep_conv.h"
 #include "iep_mfma.h"
 #include "plan_internal.h"
 
@@ -41,179 +40,186 @@ using dynb::fail;
 
 namespace {
 
-struct BwdArgs {
-    const dynb_item* items;       // the launch group's items
-    const int32_t* gdst0;         // routes of the group's items
-    const int32_t* gdst1;
+// Parameter gradients of every function, any shape: a workgroup owns a 32 x 32 block (output x input channels) of one
+// function's weight gradient, all taps of it, and sums it over the function's items and their pixels,
+//     D[32 co][32 ci] += G[32 co][2 pixels] * IN[2 pixels][32 ci]     (v_mfma_f32_32x32x2: fp32 products and sums)
+// blockIdx.z 0: second 3x3 (G = g, IN = mid), 1: first 3x3 (G = dmid, IN = u); JOIN: the 1x1 (G = dc, IN = the arguments).
+// An item's 32 + 32 channels are staged into LDS as fp32, pixel-major without padding (a fragment, two pixels x 32
+// channels, is then 64 consecutive words), the input with its halo; a step of two pixels reads 1 + TAPS fragments
+// for TAPS MFMAs of 64 clocks.  The waves split an item's pixels and meet in LDS at the end, in wave order.  Maps that do
+// not fit are taken in bands of rows and segments of columns.
+// (Per launch group, one thread per gradient element, the sums took most of a training step's 179 ms at 21 programs,
+// C = 128, 14 x 14.)
+struct WgradArgs {
+    const dynb_item* items;       // all items of the plan
     const uint8_t* arity;
-    int32_t first_item;           // index of items[0] in the plan
-    int32_t count;
-    const void* feats;            // forward inputs / results
+    const int32_t* fn_first;      // the items of function t: fn_items[fn_first[t] .. fn_first[t + 1])
+    const int32_t* fn_items;
+    const void* feats;
     const void* out;
     const void* slots;
-    const void* tmp_u;            // recomputed, [count][HWC] storage type
-    const void* tmp_m;
-    const void* w1;
-    const void* w3a;
-    const void* w3b;
-    float* gy;                    // [n_items][HWC]  gradient with respect to every item's result
-    float* gleaf;                 // [n_leaves][HWC] gradient arriving at every SCENE leaf
-    float* tmp_g;                 // [count][HWC]
-    float* tmp_dm;                // [count][HWC]
-    float* tmp_du;                // [count][HWC]
+    const void* u;
+    const void* mid;
+    const float* gy;
+    const float* dm;
+    const float* du;
+    float* dw[2];                 // by blockIdx.z (JOIN: the first only)
+    float* db[2];
+    int32_t first_type;           // function of blockIdx.y = 0
     int32_t C, H, W;
+    int32_t sw, band;             // columns of a segment, rows of a band
 };
 
-__device__ __forceinline__ float* route(const BwdArgs& a, int32_t r, size_t chw)
+template <typename T, bool JOIN>
+__global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 {
-    return r >= 0 ? a.gy + size_t(r) * chw : a.gleaf + size_t(-1 - r) * chw;
-}
-
-// g = gy * [y > 0]
-template <typename T>
-__global__ void k_bwd_g(BwdArgs a)
-{
-    const int i = blockIdx.y;
-    const dynb_item it = a.items[i];
-    const size_t chw = size_t(a.H) * a.W * a.C;
-    const size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= chw) return;
-    const T* y = it.dst >= 0 ? (const T*)a.slots + size_t(it.dst) * chw : (const T*)a.out + size_t(-1 - it.dst) * chw;
-    a.tmp_g[size_t(i) * chw + e] = load_f32(y + e) > 0.f ? a.gy[size_t(a.first_item + i) * chw + e] : 0.f;
-}
-
-// Transposed 3x3 convolution: r[q][ci] = sum_{co, kh, kw} gin[q - (kh-1, kw-1)][co] * w[t][co][kh][kw][ci]
-// SECOND = false: gin = g, w = w3b, result masked by [mid > 0] -> tmp_dm
-// SECOND = true:  gin = dmid, w = w3a, result + g = du -> the argument's gradient (one-argument functions) or tmp_du
-template <typename T, bool SECOND>
-__global__ void k_bwd_dgrad(BwdArgs a)
-{
-    const int i = blockIdx.y;
-    const dynb_item it = a.items[i];
-    const int C = a.C, H = a.H, W = a.W;
+    constexpr int TAPS = JOIN ? 1 : 9, HALO = JOIN ? 0 : 1, PIX = 32 * 4;       // bytes of a staged pixel
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const int C = a.C, H = a.H, W = a.W, sw = a.sw;
+    const int cb = (C + 31) / 32, n_in = JOIN ? 2 * cb : cb;                     // input blocks; of the join: per argument
+    const int co0 = int(blockIdx.x) / n_in * 32, arg = JOIN && int(blockIdx.x) % n_in >= cb ? 1 : 0;
+    const int ci0 = (int(blockIdx.x) % n_in - arg * cb) * 32;
+    const int type = a.first_type + blockIdx.y, which = blockIdx.z;
+    const int ar = a.arity[type];
     const size_t chw = size_t(H) * W * C;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= int(chw)) return;
-    const int q = e / C, ci = e % C, y = q / W, x = q % W;
-    const float* gin = (SECOND ? a.tmp_dm : a.tmp_g) + size_t(i) * chw;
-    const T* w = (const T*)(SECOND ? a.w3a : a.w3b) + size_t(it.type) * C * 9 * C;
-    float acc = 0.f;
-    for (int kh = 0; kh < 3; ++kh) {
-        const int oy = y - (kh - 1);                  // the output pixel whose tap (kh, kw) reads input pixel q
-        if (oy < 0 || oy >= H) continue;
-        for (int kw = 0; kw < 3; ++kw) {
-            const int ox = x - (kw - 1);
-            if (ox < 0 || ox >= W) continue;
-            const float* gp = gin + (size_t(oy) * W + ox) * C;
-            const T* wk = w + size_t(kh * 3 + kw) * C + ci;
-            for (int co = 0; co < C; ++co) acc += gp[co] * load_f32(wk + size_t(co) * 9 * C);
-        }
-    }
-    if (!SECOND) {
-        const float mid = load_f32((const T*)a.tmp_m + size_t(i) * chw + e);
-        a.tmp_dm[size_t(i) * chw + e] = mid > 0.f ? acc : 0.f;
-    } else {
-        const float du = acc + a.tmp_g[size_t(i) * chw + e];
-        if (a.arity[it.type] == 2) {
-            const float u = load_f32((const T*)a.tmp_u + size_t(i) * chw + e);
-            a.tmp_du[size_t(i) * chw + e] = u > 0.f ? du : 0.f;          // dc = du * [u > 0]
-        } else {
-            route(a, a.gdst0[i], chw)[e] = du;
-        }
-    }
-}
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 31, hk = lane >> 5;
 
-// two-argument functions: da0[p][ci] = sum_co dc[p][co] * w1[co][ci], da1[p][ci] = sum_co dc[p][co] * w1[co][C + ci]
-template <typename T>
-__global__ void k_bwd_join(BwdArgs a)
-{
-    const int i = blockIdx.y;
-    const dynb_item it = a.items[i];
-    if (a.arity[it.type] != 2) return;
-    const int C = a.C;
-    const size_t chw = size_t(a.H) * a.W * C;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= int(chw)) return;
-    const int p = e / C, ci = e % C;
-    const float* dc = a.tmp_du + size_t(i) * chw + size_t(p) * C;
-    const T* w = (const T*)a.w1 + size_t(it.type) * C * 2 * C;
-    float s0 = 0.f, s1 = 0.f;
-    for (int co = 0; co < C; ++co) {
-        s0 += dc[co] * load_f32(w + size_t(co) * 2 * C + ci);
-        s1 += dc[co] * load_f32(w + size_t(co) * 2 * C + C + ci);
-    }
-    route(a, a.gdst0[i], chw)[e] = s0;
-    route(a, a.gdst1[i], chw)[e] = s1;
-}
+    // staged pixels of G: band rows x wp columns (even: a step never crosses a row), of the input: with halo
+    const int wp = (sw + 1) & ~1, half = wp / 2, icols = wp + 2 * HALO;
+    const uint32_t in_off = uint32_t(a.band * wp * PIX);
+    const uint32_t m_wp = recip_of(wp), m_icols = recip_of(icols);
 
-// Parameter gradients of one pool (items [lo, lo + n) of the group, all of function t).
-// 3x3 weights: thread per element (co, kh, kw, ci):  dw += sum_items sum_p G[p][co] * IN[p + (kh-1, kw-1)][ci]
-//   WHICH = 0: conv_b (G = g, IN = mid);  WHICH = 1: conv_a (G = dmid, IN = u)
-template <typename T, int WHICH>
-__global__ void k_bwd_wgrad3(BwdArgs a, int lo, int n, int t, float* __restrict__ dw)
-{
-    const int C = a.C, H = a.H, W = a.W;
-    const size_t chw = size_t(H) * W * C;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= C * 9 * C) return;
-    const int ci = e % C, tap = (e / C) % 9, co = e / (9 * C), kh = tap / 3, kw = tap % 3;
-    float acc = 0.f;
-    for (int i = lo; i < lo + n; ++i) {
-        const float* G = (WHICH == 0 ? a.tmp_g : a.tmp_dm) + size_t(i) * chw;
-        const T* IN;
-        if (WHICH == 0) IN = (const T*)a.tmp_m + size_t(i) * chw;
-        else {
-            const dynb_item it = a.items[i];
-            IN = a.arity[it.type] == 2 ? (const T*)a.tmp_u + size_t(i) * chw
-                                       : (it.src0 >= 0 ? (const T*)a.slots + size_t(it.src0) * chw : (const T*)a.feats + size_t(-1 - it.src0) * chw);
-        }
-        for (int y = 0; y < H; ++y) {
-            const int iy = y + kh - 1;
-            if (iy < 0 || iy >= H) continue;
-            for (int x = 0; x < W; ++x) {
-                const int ix = x + kw - 1;
-                if (ix < 0 || ix >= W) continue;
-                acc += G[(size_t(y) * W + x) * C + co] * load_f32(IN + (size_t(iy) * W + ix) * C + ci);
+    f32x16 acc[TAPS];
+#pragma unroll
+    for (int k = 0; k < TAPS; ++k)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[k][i] = 0.f;
+    float bias = 0.f;                                                            // sum of this lane's G values
+
+    const int lo = JOIN && ar != 2 ? 0 : a.fn_first[type], hi = JOIN && ar != 2 ? 0 : a.fn_first[type + 1];
+#pragma unroll 1
+    for (int idx = lo; idx < hi; ++idx) {
+        const int32_t item = a.fn_items[idx];
+        const dynb_item it = a.items[item];
+        const size_t off = size_t(item) * chw;
+        const float* G = JOIN ? a.du + off : which == 0 ? a.gy + off : a.dm + off;
+        const T* Y = it.dst >= 0 ? (const T*)a.slots + size_t(it.dst) * chw : (const T*)a.out + size_t(-1 - it.dst) * chw;
+        const int32_t s = arg ? it.src1 : it.src0;
+        const T* A = s >= 0 ? (const T*)a.slots + size_t(s) * chw : (const T*)a.feats + size_t(-1 - s) * chw;
+        const T* IN = JOIN ? A : which == 0 ? (const T*)a.mid + off : ar == 2 ? (const T*)a.u + off : A;
+#pragma unroll 1
+        for (int x0 = 0; x0 < W; x0 += sw)
+#pragma unroll 1
+            for (int y0 = 0; y0 < H; y0 += a.band) {
+                const int rows = min(a.band, H - y0), cols = min(sw, W - x0);
+                __syncthreads();                                                 // the last band's fragments have been read
+                constexpr int UN = 4;
+                const int ng = rows * wp * 8, ni = (rows + 2 * HALO) * icols * 8;        // 16-byte pieces
+                for (int base = tid; base < ng; base += 256 * UN) {
+                    f32x4 v[UN];
+#pragma unroll
+                    for (int k = 0; k < UN; ++k) {
+                        const int c = base + k * 256;
+                        const uint32_t pix = uint32_t(c) >> 3, row = div_by(pix, m_wp), col = pix - row * wp;
+                        const int ch = co0 + (c & 7) * 4;
+                        v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (c < ng && int(col) < cols) {
+                            const size_t e = (size_t(y0 + row) * W + x0 + col) * C + ch;
+                            v[k] = !JOIN && which == 0 ? masked_gy(G + e, Y + e, C - ch) : load4(G + e, C - ch);
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < UN; ++k)
+                        if (base + k * 256 < ng) *reinterpret_cast<f32x4*>(lds_raw + size_t(base + k * 256) * 16) = v[k];
+                }
+                for (int base = tid; base < ni; base += 256 * UN) {
+                    f32x4 v[UN];
+#pragma unroll
+                    for (int k = 0; k < UN; ++k) {
+                        const int c = base + k * 256;
+                        const uint32_t pix = uint32_t(c) >> 3, row = div_by(pix, m_icols), col = pix - row * icols;
+                        const int ch = ci0 + (c & 7) * 4, y = y0 + int(row) - HALO, x = x0 + int(col) - HALO;
+                        v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) v[k] = load4(IN + (size_t(y) * W + x) * C + ch, C - ch);
+                    }
+#pragma unroll
+                    for (int k = 0; k < UN; ++k)
+                        if (base + k * 256 < ni) *reinterpret_cast<f32x4*>(lds_raw + in_off + size_t(base + k * 256) * 16) = v[k];
+                }
+                __syncthreads();
+                // this wave's steps: (row y, pixels 2 x and 2 x + 1), read one step ahead
+                const int S = rows * half, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
+                struct Step { float g, in[TAPS]; };
+                auto read = [&](int y, int x, Step& v) {
+                    const uint32_t ga = uint32_t(((y * half + x) * 2 + hk) * PIX + r * 4);
+                    const uint32_t ia = in_off + uint32_t((y * icols + x * 2 + hk) * PIX + r * 4);
+                    v.g = *reinterpret_cast<const float*>(lds_raw + ga);
+#pragma unroll
+                    for (int k = 0; k < TAPS; ++k)
+                        v.in[k] = *reinterpret_cast<const float*>(lds_raw + ia + uint32_t(((k / 3) * icols + k % 3) * PIX));
+                };
+                auto multiply = [&](const Step& v) {
+                    bias += v.g;
+#pragma unroll
+                    for (int k = 0; k < TAPS; ++k) acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.g, v.in[k], acc[k], 0, 0, 0);
+                };
+                if (s0 < s1) {
+                    int y = s0 / half, x = s0 - y * half;
+                    Step p, q;
+                    read(y, x, p);
+#pragma unroll 1
+                    for (int st = s0; st < s1; st += 2) {
+                        if (++x == half) { x = 0; ++y; }
+                        if (st + 1 < s1) read(y, x, q);
+                        multiply(p);
+                        if (st + 1 >= s1) break;
+                        if (++x == half) { x = 0; ++y; }
+                        if (st + 2 < s1) read(y, x, p);
+                        multiply(q);
+                    }
+                }
             }
+    }
+    // partial sums of the waves through LDS, three taps at a time: [wave][tap][b][lane] of four rows each
+    f32x4* red = reinterpret_cast<f32x4*>(lds_raw);
+    constexpr int R = JOIN ? 1 : 3;
+#pragma unroll
+    for (int k0 = 0; k0 < TAPS; k0 += R) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                red[((wave * R + k) * 4 + b) * 64 + lane] = f32x4{acc[k0 + k][4 * b], acc[k0 + k][4 * b + 1], acc[k0 + k][4 * b + 2], acc[k0 + k][4 * b + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < R; ++k) {                                            // this thread: rows 8 wave + 4 hk .. + 3, column r
+            f32x4 v = red[(k * 4 + wave) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const f32x4 q = red[((w * R + k) * 4 + wave) * 64 + lane];
+                v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+            }
+            const int co = co0 + 8 * wave + 4 * hk, ci = ci0 + r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (co + e < C && ci < C) {
+                    const size_t row = size_t(type) * C + co + e;
+                    a.dw[which][JOIN ? row * 2 * C + arg * C + ci : (row * 9 + k0 + k) * C + ci] = v[e];
+                }
         }
     }
-    dw[size_t(t) * C * 9 * C + e] += acc;
-}
-
-// biases of a pool: thread per channel; WHICH = 0: db_b from g, 1: db_a from dmid, 2: db_1 from dc
-template <int WHICH>
-__global__ void k_bwd_bias(BwdArgs a, int lo, int n, int t, float* __restrict__ db)
-{
-    const int C = a.C;
-    const size_t P = size_t(a.H) * a.W, chw = P * C;
-    const int co = blockIdx.x * blockDim.x + threadIdx.x;
-    if (co >= C) return;
-    const float* G = WHICH == 0 ? a.tmp_g : WHICH == 1 ? a.tmp_dm : a.tmp_du;
-    float acc = 0.f;
-    for (int i = lo; i < lo + n; ++i)
-        for (size_t p = 0; p < P; ++p) acc += G[size_t(i) * chw + p * C + co];
-    db[size_t(t) * C + co] += acc;
-}
-
-// 1x1 weights of a pool of two-argument functions: thread per (co, cj), cj over the 2C concatenated channels
-template <typename T>
-__global__ void k_bwd_wgrad1(BwdArgs a, int lo, int n, int t, float* __restrict__ dw)
-{
-    const int C = a.C;
-    const size_t P = size_t(a.H) * a.W, chw = P * C;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= C * 2 * C) return;
-    const int cj = e % (2 * C), co = e / (2 * C);
-    float acc = 0.f;
-    for (int i = lo; i < lo + n; ++i) {
-        const dynb_item it = a.items[i];
-        const int32_t s = cj < C ? it.src0 : it.src1;
-        const T* in = s >= 0 ? (const T*)a.slots + size_t(s) * chw : (const T*)a.feats + size_t(-1 - s) * chw;
-        const float* dc = a.tmp_du + size_t(i) * chw;
-        const int c = cj < C ? cj : cj - C;
-        for (size_t p = 0; p < P; ++p) acc += dc[p * C + co] * load_f32(in + p * C + c);
+    if (ci0 == 0 && arg == 0) {                                                  // bias: the lane halves and the waves in order
+        __syncthreads();
+        float* sum = reinterpret_cast<float*>(lds_raw);
+        sum[tid] = bias;
+        __syncthreads();
+        if (tid < 32 && co0 + tid < C) {
+            float v = 0.f;
+            for (int w = 0; w < 8; ++w) v += sum[w * 32 + tid];
+            a.db[which][size_t(type) * C + co0 + tid] = v;
+        }
     }
-    dw[size_t(t) * C * 2 * C + e] += acc;
 }
 
 __global__ void k_bwd_fill(float* p, size_t n, float v)
@@ -819,10 +825,10 @@ __global__ void k_bwd_wgrad_sum(WsArgs a)
 }
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
-size_t elt_bytes(int dtype) { return dtype == DYNB_BF16 ? 2 : 4; }
 
+// workspace away from the fused kernels' shape: one map per item each, fp32
 struct BwdLayout {
-    size_t gy, gleaf, tmp_u, tmp_m, tmp_g, tmp_dm, tmp_du, total;
+    size_t gy, gleaf, dm, du, total;
 };
 
 BwdLayout bwd_layout(const dynb_plan* p, const dynb_shape* s)
@@ -834,13 +840,37 @@ BwdLayout bwd_layout(const dynb_plan* p, const dynb_shape* s)
     auto take = [&](size_t bytes) { size_t at = o; o += align256(std::max<size_t>(bytes, 4)); return at; };
     L.gy = take(n_items * chw * 4);
     L.gleaf = take(n_leaf * chw * 4);
-    L.tmp_u = take(size_t(p->max_launch) * chw * elt_bytes(s->dtype));
-    L.tmp_m = take(size_t(p->max_launch) * chw * elt_bytes(s->dtype));
-    L.tmp_g = take(size_t(p->max_launch) * chw * 4);
-    L.tmp_dm = take(size_t(p->max_launch) * chw * 4);
-    L.tmp_du = take(size_t(p->max_launch) * chw * 4);
+    L.dm = take(n_items * chw * 4);
+    L.du = take(p->has_binary ? n_items * chw * 4 : 0);
     L.total = o;
     return L;
+}
+
+// parameter gradients of all functions, zeros for functions without items
+template <typename T, bool JOIN>
+int launch_wgrad(WgradArgs a, int n_types, hipStream_t st)
+{
+    constexpr int LDS_MAX = 80 * 1024, HALO = JOIN ? 0 : 1;               // two workgroups per CU
+    static std::atomic<uint64_t> attr_set{0};                             // one bit per device
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+    if (!(attr_set.load() >> (dev & 63) & 1)) {
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad<T, JOIN>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX),
+                "hipFuncSetAttribute(k_wgrad)");
+        attr_set.fetch_or(uint64_t(1) << (dev & 63));
+    }
+    const int n_seg = (a.W + 31) / 32;
+    a.sw = (a.W + n_seg - 1) / n_seg;
+    const int wp = (a.sw + 1) & ~1, icols = wp + 2 * HALO;
+    a.band = std::min(a.H, (LDS_MAX / 128 - 2 * HALO * icols) / (wp + icols));      // >= 8: sw <= 32
+    const size_t lds = std::max<size_t>(size_t(a.band * wp + (a.band + 2 * HALO) * icols) * 128, size_t(JOIN ? 1 : 3) * 16 * 1024);
+    const int cb = (a.C + 31) / 32;
+    for (int t0 = 0; t0 < n_types; t0 += 32768) {
+        a.first_type = t0;
+        hipLaunchKernelGGL((k_wgrad<T, JOIN>), dim3(unsigned(cb * cb * (JOIN ? 2 : 1)), unsigned(std::min(32768, n_types - t0)), JOIN ? 1 : 2),
+                           dim3(256), lds, st, a);
+    }
+    return DYNB_OK;
 }
 
 template <typename T>
@@ -849,19 +879,12 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
 {
     const BwdLayout L = bwd_layout(p, s);
     const size_t chw = size_t(s->C) * s->H * s->W;
-    const int C = s->C, B = p->B;
+    const int B = p->B;
     // the routing tables were uploaded with the plan
     const dynb_keep_tables KT = dynb_plan_keep_tables(p);
     const char* pd = static_cast<const char*>(p->dev_buf);
     const int32_t* d_leaf_first = reinterpret_cast<const int32_t*>(pd + KT.leaf_first);
     const int32_t* d_root_item = reinterpret_cast<const int32_t*>(pd + KT.root_item);
-
-    auto fill = [&](float* ptr, size_t n) {
-        if (ptr && n) hipLaunchKernelGGL(k_bwd_fill, dim3(unsigned(std::min<size_t>((n + 255) / 256, 4096))), dim3(256), 0, st, ptr, n, 0.f);
-    };
-    const size_t nt = size_t(p->n_types);
-    fill(g->dw3a, nt * C * 9 * C); fill(g->dw3b, nt * C * 9 * C); fill(g->db3a, nt * C); fill(g->db3b, nt * C);
-    fill(g->dw1, nt * C * 2 * C); fill(g->db1, nt * C);
 
     float* gy = reinterpret_cast<float*>(ws + L.gy);
     const unsigned bx_map = unsigned(std::min<size_t>((chw + 255) / 256, 64));
@@ -869,74 +892,63 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
         hipLaunchKernelGGL(k_bwd_seed, dim3(bx_map, unsigned(std::min(32768, B - e0))), dim3(256), 0, st, dout + size_t(e0) * chw,
                            d_root_item + e0, gy, chw);
 
-    const char* d = static_cast<const char*>(p->dev_buf);
-    const dynb_item* d_items = reinterpret_cast<const dynb_item*>(d);
-    const uint8_t* d_arity = reinterpret_cast<const uint8_t*>(d + dynb_plan_arity_offset(p));
-    GenArgs ga;                                     // recomputation of u and mid with the forward kernels
-    ga.arity = d_arity;
-    ga.feats = feats; ga.out = nullptr; ga.slots = const_cast<void*>(fwd_ws);
-    ga.w1 = w->w1; ga.b1 = w->b1; ga.w3a = w->w3a; ga.b3a = w->b3a; ga.w3b = w->w3b; ga.b3b = w->b3b;
-    ga.C = s->C; ga.H = s->H; ga.W = s->W;
-    BwdArgs ba;
-    ba.arity = d_arity;
-    ba.feats = feats; ba.out = out; ba.slots = fwd_ws;
-    ba.w1 = w->w1; ba.w3a = w->w3a; ba.w3b = w->w3b;
-    ba.gy = gy; ba.gleaf = reinterpret_cast<float*>(ws + L.gleaf);
-    ba.C = s->C; ba.H = s->H; ba.W = s->W;
-    const unsigned bx = unsigned((chw + 255) / 256);
-    const unsigned bw3 = unsigned((size_t(C) * 9 * C + 255) / 256), bw1 = unsigned((size_t(C) * 2 * C + 255) / 256), bb = unsigned((C + 255) / 256);
-
+    const dynb_item* d_items = reinterpret_cast<const dynb_item*>(pd);
+    ConvArgs a = {};
+    a.arity = reinterpret_cast<const uint8_t*>(pd + dynb_plan_arity_offset(p));
+    a.feats = feats; a.out = const_cast<void*>(out); a.slots = const_cast<void*>(fwd_ws);
+    const size_t map = chw * sizeof(T);
+    a.mid = static_cast<char*>(const_cast<void*>(fwd_ws)) + dynb_generic_keep_offset(p, map);
+    a.u = static_cast<char*>(a.mid) + dynb_generic_kept_maps(p) * map;
+    a.gy = gy; a.gleaf = reinterpret_cast<float*>(ws + L.gleaf);
+    a.dm = reinterpret_cast<float*>(ws + L.dm); a.du = reinterpret_cast<float*>(ws + L.du);
+    a.C = s->C; a.H = s->H; a.W = s->W;
     for (size_t li = p->launches.size(); li-- > 0;) {
         const dynb_launch& l = p->launches[li];
         // a launch group wider than one grid (65535 rows) is walked in slices; its nodes are independent
         for (int off = 0; off < l.count; off += 32768) {
             const int cnt = std::min(32768, l.count - off);
-            const int first = l.start + off;
-            ga.items = d_items + first; ga.count = cnt;
-            ga.tmp_u = ws + L.tmp_u; ga.tmp_m = ws + L.tmp_m;
-            ba.items = d_items + first; ba.first_item = first; ba.count = cnt;
-            ba.gdst0 = reinterpret_cast<const int32_t*>(pd + KT.gdst0) + first;
-            ba.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + first;
-            ba.tmp_u = ws + L.tmp_u; ba.tmp_m = ws + L.tmp_m;
-            ba.tmp_g = reinterpret_cast<float*>(ws + L.tmp_g); ba.tmp_dm = reinterpret_cast<float*>(ws + L.tmp_dm);
-            ba.tmp_du = reinterpret_cast<float*>(ws + L.tmp_du);
-            const dim3 grid(bx, unsigned(cnt));
-            if (l.any_binary) hipLaunchKernelGGL((k_gen_join<T>), grid, dim3(256), 0, st, ga);
-            hipLaunchKernelGGL((k_gen_conv<T, false>), grid, dim3(256), 0, st, ga);
-            hipLaunchKernelGGL((k_bwd_g<T>), grid, dim3(256), 0, st, ba);
-            hipLaunchKernelGGL((k_bwd_dgrad<T, false>), grid, dim3(256), 0, st, ba);
-            hipLaunchKernelGGL((k_bwd_dgrad<T, true>), grid, dim3(256), 0, st, ba);
-            if (l.any_binary) hipLaunchKernelGGL((k_bwd_join<T>), grid, dim3(256), 0, st, ba);
-            // parameter gradients, pool by pool: runs of equal function id (the items of a group are sorted by function)
-            int lo = 0;
-            while (lo < cnt) {
-                const int t = p->items[first + lo].type;
-                int n = 1;
-                while (lo + n < cnt && p->items[first + lo + n].type == t) ++n;
-                hipLaunchKernelGGL((k_bwd_wgrad3<T, 0>), dim3(bw3), dim3(256), 0, st, ba, lo, n, t, g->dw3b);
-                hipLaunchKernelGGL((k_bwd_wgrad3<T, 1>), dim3(bw3), dim3(256), 0, st, ba, lo, n, t, g->dw3a);
-                hipLaunchKernelGGL((k_bwd_bias<0>), dim3(bb), dim3(256), 0, st, ba, lo, n, t, g->db3b);
-                hipLaunchKernelGGL((k_bwd_bias<1>), dim3(bb), dim3(256), 0, st, ba, lo, n, t, g->db3a);
-                if (p->arity[t] == 2) {
-                    hipLaunchKernelGGL((k_bwd_wgrad1<T>), dim3(bw1), dim3(256), 0, st, ba, lo, n, t, g->dw1);
-                    hipLaunchKernelGGL((k_bwd_bias<2>), dim3(bb), dim3(256), 0, st, ba, lo, n, t, g->db1);
-                }
-                lo += n;
-            }
+            a.first_item = a.first_kept = l.start + off;
+            a.items = d_items + a.first_item;
+            a.gdst0 = reinterpret_cast<const int32_t*>(pd + KT.gdst0) + a.first_item;
+            a.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + a.first_item;
+            a.w = w->w3b;
+            int rc = launch_conv<T, CV_DSECOND>(a, cnt, st);
+            a.w = w->w3a;
+            if (rc == DYNB_OK) rc = launch_conv<T, CV_DFIRST>(a, cnt, st);
+            a.w = w->w1;
+            if (rc == DYNB_OK && l.any_binary) rc = launch_conv<T, CV_DJOIN>(a, cnt, st);
+            if (rc != DYNB_OK) return fail(rc, "dynbatch_backward: a convolution could not be launched");
         }
     }
+    WgradArgs q = {};
+    q.items = d_items; q.arity = a.arity;
+    q.fn_first = reinterpret_cast<const int32_t*>(pd + KT.fn_first);
+    q.fn_items = reinterpret_cast<const int32_t*>(pd + KT.fn_items);
+    q.feats = feats; q.out = out; q.slots = fwd_ws; q.u = a.u; q.mid = a.mid;
+    q.gy = gy; q.dm = a.dm; q.du = a.du;
+    q.C = s->C; q.H = s->H; q.W = s->W;
+    q.dw[0] = g->dw3b; q.db[0] = g->db3b; q.dw[1] = g->dw3a; q.db[1] = g->db3a;
+    int rc = launch_wgrad<T, false>(q, p->n_types, st);
+    if (rc != DYNB_OK) return rc;
+    if (p->has_binary) {
+        q.dw[0] = g->dw1; q.db[0] = g->db1;
+        rc = launch_wgrad<T, true>(q, p->n_types, st);
+        if (rc != DYNB_OK) return rc;
+    } else {
+        auto fill = [&](float* ptr, size_t n) {
+            if (ptr && n) hipLaunchKernelGGL(k_bwd_fill, dim3(unsigned(std::min<size_t>((n + 255) / 256, 4096))), dim3(256), 0, st, ptr, n, 0.f);
+        };
+        fill(g->dw1, size_t(p->n_types) * s->C * 2 * s->C);
+        fill(g->db1, size_t(p->n_types) * s->C);
+    }
     for (int e0 = 0; e0 < B; e0 += 32768)
-        hipLaunchKernelGGL(k_bwd_leaves, dim3(bx_map, unsigned(std::min(32768, B - e0))), dim3(256), 0, st, ba.gleaf, d_leaf_first + e0,
+        hipLaunchKernelGGL(k_bwd_leaves, dim3(bx_map, unsigned(std::min(32768, B - e0))), dim3(256), 0, st, a.gleaf, d_leaf_first + e0,
                            d_root_item + e0, dout + size_t(e0) * chw, g->dfeats + size_t(e0) * chw, chw);
     HIP_TRY(hipGetLastError(), "dynbatch_backward");
     return DYNB_OK;
 }
 
-#ifdef DYNB_BWD_FORCE_GENERIC          // development aid: the generic kernels at every shape
-bool fast_shape(const dynb_shape*) { return false; }
-#else
 bool fast_shape(const dynb_shape* s) { return s->dtype == DYNB_BF16 && s->C == 128 && s->H == 14 && s->W == 14; }
-#endif
 
 // workspace of the MFMA path
 struct BmLayout {

@@ -7,8 +7,8 @@
 //                      LDS halo tile, conv1x1 (binary functions), conv3x3, ReLU, conv3x3, residual
 //                      add and ReLU all run from that tile on MFMA, and the result is scattered to
 //                      the node's slot (or to the output tensor for a root).
-//   * generic kernels — any C/H/W, fp32 or bf16 storage, fp32 accumulate, one thread per output
-//                      element; three small kernels per launch group.
+//   * k_conv         — any C/H/W, fp32 or bf16 storage, fp32 accumulate (iep_conv.h): one launch per convolution of a
+//                      launch group, tiles small enough to spread narrow groups over the chip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,7 +18,7 @@
 #include <string>
 
 #include "device_utils.h"
-#include "iep_generic.h"
+#include "iep_conv.h"
 #include "iep_mfma.h"
 #include "plan_internal.h"
 #include "timing.h"
@@ -502,6 +502,7 @@ extern "C" int dynbatch_plan_upload(dynb_plan* p, void* dev_buf, size_t bytes, v
         put(t.gdst1, p->grad_dst1.data(), p->grad_dst1.size() * 4);
         put(t.leaf_first, p->leaf_first.data(), p->leaf_first.size() * 4);
         put(t.root_item, p->root_item.data(), p->root_item.size() * 4);
+        put(t.fn_first, p->fn_first.data(), p->fn_first.size() * 4);
         put(t.fn_items, p->fn_items.data(), p->fn_items.size() * 4);
         put(t.units, p->wg_units.data(), p->wg_units.size() * sizeof(dynb_wg_unit));
         put(t.groups, p->wg_groups.data(), p->wg_groups.size() * sizeof(dynb_wg_group));
@@ -519,7 +520,7 @@ extern "C" size_t dynbatch_workspace_bytes(const dynb_plan* p, const dynb_shape*
     if (s->dtype != DYNB_F32 && s->dtype != DYNB_BF16) return 0;
     const size_t map = size_t(s->C) * s->H * s->W * elt_bytes(s->dtype);    // slots are packed
     size_t n = size_t(p->n_slots);
-    if (!fast_shape(s)) n += 2 * size_t(p->max_launch);                       // u and mid of one launch group
+    if (!fast_shape(s)) n += 2 * dynb_generic_kept_maps(p);                   // mid and u
     size_t bytes = align256(n * map);
     if (fast_shape(s)) bytes += align256(packed_weight_bytes(p->n_types));    // weights in MFMA fragment order
     if (fast_shape(s)) bytes += persist_sync_bytes(p);                        // ready flags, ticket counter, status
@@ -527,45 +528,42 @@ extern "C" size_t dynbatch_workspace_bytes(const dynb_plan* p, const dynb_shape*
     return std::max<size_t>(bytes, 256);
 }
 
+// Shapes without a fused kernel: one launch per convolution of a launch group.  u and mid live behind the slots: one map per
+// item of the widest group, or, for the backward pass of a DYNB_PLAN_KEEP plan, one per item of the plan.
 template <typename T>
 static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_module_weights* w, const void* feats,
                        void* out, char* ws, hipStream_t st)
 {
-    const size_t chw = size_t(s->C) * s->H * s->W;
-    const size_t map = chw * sizeof(T);
+    const size_t map = size_t(s->C) * s->H * s->W * sizeof(T);
     const char* d = static_cast<const char*>(p->dev_buf);
-    GenArgs a;
+    ConvArgs a = {};
     a.arity = reinterpret_cast<const uint8_t*>(d + plan_items_bytes(p) + plan_leaf_bytes(p));
     a.feats = feats; a.out = out; a.slots = ws;
-    a.tmp_u = ws + size_t(p->n_slots) * map;
-    a.tmp_m = ws + (size_t(p->n_slots) + p->max_launch) * map;
-    a.w1 = w->w1; a.b1 = w->b1; a.w3a = w->w3a; a.b3a = w->b3a; a.w3b = w->w3b; a.b3b = w->b3b;
+    a.mid = ws + dynb_generic_keep_offset(p, map);
+    a.u = static_cast<char*>(a.mid) + dynb_generic_kept_maps(p) * map;
     a.C = s->C; a.H = s->H; a.W = s->W;
-    const unsigned bx = unsigned((chw + 255) / 256);
     const bool timed = dynb::timing_on(), coarse = dynb::timing_coarse();
     if (timed) dynb::timing_mark(st, dynb::ST_SETUP, 0);
     int32_t evals = 0;
     for (const dynb_launch& l : p->launches) {
         evals += l.count;
-        a.items = reinterpret_cast<const dynb_item*>(d) + l.start;
-        a.count = l.count;
-        const bool any_binary = l.any_binary != 0;
         // grid.y is limited to 65535: split very wide launch groups
         for (int off = 0; off < l.count; off += 32768) {
-            GenArgs b = a;
-            b.items = a.items + off;
-            b.count = std::min(32768, l.count - off);
-            b.tmp_u = static_cast<char*>(a.tmp_u) + size_t(off) * map;
-            b.tmp_m = static_cast<char*>(a.tmp_m) + size_t(off) * map;
-            dim3 grid(bx, unsigned(b.count));
-            if (any_binary) hipLaunchKernelGGL((k_gen_join<T>), grid, dim3(256), 0, st, b);
-            hipLaunchKernelGGL((k_gen_conv<T, false>), grid, dim3(256), 0, st, b);
-            hipLaunchKernelGGL((k_gen_conv<T, true>), grid, dim3(256), 0, st, b);
+            const int count = std::min(32768, l.count - off);
+            a.items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
+            a.first_kept = p->keep ? l.start + off : off;
+            int rc = DYNB_OK;
+            if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = launch_conv<T, CV_JOIN>(a, count, st); }
+            a.w = w->w3a; a.bias = w->b3a;
+            if (rc == DYNB_OK) rc = launch_conv<T, CV_FIRST>(a, count, st);
+            a.w = w->w3b; a.bias = w->b3b;
+            if (rc == DYNB_OK) rc = launch_conv<T, CV_SECOND>(a, count, st);
+            if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a convolution could not be launched");
         }
         if (timed && !coarse) dynb::timing_mark(st, int32_t(&l - p->launches.data()), l.count);
     }
     if (coarse) dynb::timing_mark(st, 0, evals);
-    HIP_TRY(hipGetLastError(), "dynbatch_execute(generic kernels)");
+    HIP_TRY(hipGetLastError(), "dynbatch_execute(convolution kernels)");
     return DYNB_OK;
 }
 

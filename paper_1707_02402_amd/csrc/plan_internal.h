@@ -74,7 +74,7 @@ inline size_t dynb_plan_leaf_bytes(const dynb_plan* p) { return dynb_align256(p-
 inline size_t dynb_plan_arity_offset(const dynb_plan* p) { return dynb_plan_items_bytes(p) + dynb_plan_leaf_bytes(p); }
 inline size_t dynb_plan_arity_bytes(const dynb_plan* p) { return dynb_align256(p->arity.size()); }
 inline size_t dynb_plan_ticket_bytes(const dynb_plan* p) { return dynb_align256(p->tickets.size() * sizeof(int32_t)); }
-struct dynb_keep_tables { size_t gdst0, gdst1, leaf_first, root_item, fn_items, units, groups, order, end; };   // byte offsets
+struct dynb_keep_tables { size_t gdst0, gdst1, leaf_first, root_item, fn_first, fn_items, units, groups, order, end; };   // byte offsets
 inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
 {
     dynb_keep_tables t;
@@ -84,6 +84,7 @@ inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
     t.gdst1 = take(p->grad_dst1.size() * 4);
     t.leaf_first = take(p->leaf_first.size() * 4);
     t.root_item = take(p->root_item.size() * 4);
+    t.fn_first = take(p->fn_first.size() * 4);
     t.fn_items = take(p->fn_items.size() * 4);
     t.units = take(p->wg_units.size() * sizeof(dynb_wg_unit));
     t.groups = take(p->wg_groups.size() * sizeof(dynb_wg_group));
@@ -105,6 +106,11 @@ inline size_t dynb_fast_sync_offset(const dynb_plan* p)
 inline size_t dynb_fast_sync_bytes(const dynb_plan* p) { return p->persistent ? dynb_align256((size_t(p->n_slots) + 2) * sizeof(int32_t)) : 0; }
 inline size_t dynb_fast_keep_offset(const dynb_plan* p) { return dynb_fast_sync_offset(p) + dynb_fast_sync_bytes(p); }
 inline size_t dynb_fast_keep_bytes(const dynb_plan* p) { return p->keep ? dynb_align256(2 * p->items.size() * dynb_fast_map_bytes()) : 0; }
+
+// ... and on every other shape: slots | mid | u, for every item of a DYNB_PLAN_KEEP plan (the backward pass reads them),
+// else for the items of one launch group; `map` = bytes of one map
+inline size_t dynb_generic_keep_offset(const dynb_plan* p, size_t map) { return size_t(p->n_slots) * map; }
+inline size_t dynb_generic_kept_maps(const dynb_plan* p) { return p->keep ? p->items.size() : size_t(p->max_launch); }
 
 namespace dynb {
 void set_error(const std::string& msg);

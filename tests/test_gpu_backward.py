@@ -78,7 +78,7 @@ def test_config0_fp32_every_gradient(dyn, util, oracle, flags):
         assert maxnorm(got[name], getattr(ref, name)) < 1e-4, (name, maxnorm(got[name], getattr(ref, name)))
 
 
-@pytest.mark.parametrize("C,H,W,B", [(5, 3, 7, 9), (33, 4, 4, 6), (3, 1, 1, 4)])
+@pytest.mark.parametrize("C,H,W,B", [(5, 3, 7, 9), (33, 4, 4, 6), (3, 1, 1, 4), (17, 1, 65, 4), (66, 35, 3, 3), (34, 12, 33, 5)])
 def test_ragged_shapes_fp32_with_single_scene_programs(dyn, util, oracle, C, H, W, B):
     w = iep.small_mixed(seed=C + B, B=B, C=C, H=H, W=W, dtype="f32", min_len=1, max_len=9)
     dout = np.random.default_rng(C).standard_normal(w.feats.shape).astype(np.float32)

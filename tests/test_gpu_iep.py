@@ -47,6 +47,28 @@ def test_generic_kernels_on_ragged_shapes(dyn, util, oracle, dtype, C, H, W):
             assert (got[i] == w.feats[i]).all()
 
 
+@pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 1, 1, 1, 3), ("f32", 17, 1, 65, 3), ("bf16", 31, 33, 2, 3), ("f32", 130, 3, 5, 40),
+                                           ("bf16", 33, 5, 33, 4), ("bf16", 66, 7, 32, 40), ("f32", 260, 6, 30, 2), ("bf16", 16, 9, 7, 200)])
+def test_convolution_tiles_at_their_edges(dyn, util, oracle, dtype, C, H, W, B):
+    """Remainders of every tile dimension (16 pixels, 16 channels, 16 or 32 summed channels, segments of 32 columns, panels of
+    summed channels) and all workgroup tiles; weights and maps at addresses that only their element type aligns."""
+    import torch
+    w = iep.small_mixed(seed=C + W, B=B, C=C, H=H, W=W, dtype=dtype, min_len=2, max_len=7)
+    ref = oracle.iep_forward_workload(w)
+
+    def shifted(t):
+        return None if t is None else torch.cat([t.flatten()[:1], t.flatten()])[1:].view(t.shape)
+
+    weights = {k: shifted(t) for k, t in util.iep_weights_dev(w).items()}
+    feats = shifted(util.to_dev(w.feats, dtype))
+    assert feats.data_ptr() % 16 == feats.element_size()
+    plan = dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, 0)
+    dyn.dynbatch_plan_upload(plan)
+    got = util.to_host(dyn.dynbatch_execute(plan, weights, feats, out=torch.full_like(feats, float("nan"))))
+    for i in range(w.B):
+        assert util.normwise(got[i], ref[i]) < TOL[dtype], i
+
+
 @pytest.mark.parametrize("flags", [0, 1, 2, 3])
 def test_mfma_path_small_batch_every_element(dyn, util, oracle, flags):
     """bf16, C=128, 14x14: 13 pixel tiles with a ragged last tile, unary and binary functions,
