@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                         v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
                         if (c < ng && int(col) < cols) {
                             const size_t e = (size_t(y0 + row) * W + x0 + col) * C + ch;
-                            v[k] = !JOIN && which == 0 ? masked_gy(G + e, Y + e, C - ch) : load4(G + e, C - ch);
+                            v[k] = !JOIN && which == 0 ? masked_gy<false>(G + e, Y + e, C - ch) : load4<false>(G + e, C - ch);
                         }
                     }
 #pragma unroll
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                         const uint32_t pix = uint32_t(c) >> 3, row = div_by(pix, m_icols), col = pix - row * icols;
                         const int ch = ci0 + (c & 7) * 4, y = y0 + int(row) - HALO, x = x0 + int(col) - HALO;
                         v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) v[k] = load4(IN + (size_t(y) * W + x) * C + ch, C - ch);
+                        if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) v[k] = load4<false>(IN + (size_t(y) * W + x) * C + ch, C - ch);
                     }
 #pragma unroll
                     for (int k = 0; k < UN; ++k)
@@ -272,7 +272,6 @@ struct BmArgs {
     const dynb_item* items;       // the launch group's items
     const int32_t* gdst0;         // routes of the group's items
     const int32_t* gdst1;
-    const uint8_t* arity;
     int32_t first_item;
     int32_t count;
     const bf16_t* feats;
@@ -355,7 +354,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 #define NCLK(i) do {} while (0)
 #endif
     const dynb_item it = a.items[logical];
-    const bool binary = a.arity[it.type] == 2;                        // uniform over the workgroup
+    const bool binary = it.src1 != DYNB_NO_ARG;                        // uniform over the workgroup
     const size_t item_off = size_t(a.first_item + logical) * (P * C);
 
     const size_t frag3 = (size_t(it.type) * 4 + wave) * 72, frag1 = (size_t(it.type) * 4 + wave) * 16;
@@ -894,7 +893,6 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
 
     const dynb_item* d_items = reinterpret_cast<const dynb_item*>(pd);
     ConvArgs a = {};
-    a.arity = reinterpret_cast<const uint8_t*>(pd + dynb_plan_arity_offset(p));
     a.feats = feats; a.out = const_cast<void*>(out); a.slots = const_cast<void*>(fwd_ws);
     const size_t map = chw * sizeof(T);
     a.mid = static_cast<char*>(const_cast<void*>(fwd_ws)) + dynb_generic_keep_offset(p, map);
@@ -908,20 +906,20 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
         for (int off = 0; off < l.count; off += 32768) {
             const int cnt = std::min(32768, l.count - off);
             a.first_item = a.first_kept = l.start + off;
-            a.items = d_items + a.first_item;
+            const dynb_item* items = d_items + a.first_item;
             a.gdst0 = reinterpret_cast<const int32_t*>(pd + KT.gdst0) + a.first_item;
             a.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + a.first_item;
             a.w = w->w3b;
-            int rc = launch_conv<T, CV_DSECOND>(a, cnt, st);
+            int rc = launch_conv<T, CV_DSECOND>(items, a, cnt, st);
             a.w = w->w3a;
-            if (rc == DYNB_OK) rc = launch_conv<T, CV_DFIRST>(a, cnt, st);
+            if (rc == DYNB_OK) rc = launch_conv<T, CV_DFIRST>(items, a, cnt, st);
             a.w = w->w1;
-            if (rc == DYNB_OK && l.any_binary) rc = launch_conv<T, CV_DJOIN>(a, cnt, st);
+            if (rc == DYNB_OK && l.any_binary) rc = launch_conv<T, CV_DJOIN>(items, a, cnt, st);
             if (rc != DYNB_OK) return fail(rc, "dynbatch_backward: a convolution could not be launched");
         }
     }
     WgradArgs q = {};
-    q.items = d_items; q.arity = a.arity;
+    q.items = d_items; q.arity = reinterpret_cast<const uint8_t*>(pd + dynb_plan_arity_offset(p));
     q.fn_first = reinterpret_cast<const int32_t*>(pd + KT.fn_first);
     q.fn_items = reinterpret_cast<const int32_t*>(pd + KT.fn_items);
     q.feats = feats; q.out = out; q.slots = fwd_ws; q.u = a.u; q.mid = a.mid;
@@ -1028,7 +1026,6 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     const dynb_item* d_items = reinterpret_cast<const dynb_item*>(d);
     const uint8_t* d_arity = reinterpret_cast<const uint8_t*>(d + dynb_plan_arity_offset(p));
     BmArgs a;
-    a.arity = d_arity;
     a.feats = static_cast<const bf16_t*>(feats); a.out = static_cast<const bf16_t*>(out); a.slots = static_cast<const bf16_t*>(fwd_ws);
     a.pk3bT = reinterpret_cast<const bf16_t*>(ws + L.pk3bT); a.pk3aT = reinterpret_cast<const bf16_t*>(ws + L.pk3aT);
     a.pk1T = reinterpret_cast<const bf16_t*>(ws + L.pk1T);

@@ -31,8 +31,6 @@ namespace {
 enum ConvMode { CV_JOIN, CV_FIRST, CV_SECOND, CV_DSECOND, CV_DFIRST, CV_DJOIN };
 
 struct ConvArgs {
-    const dynb_item* items;
-    const uint8_t* arity;         // device [n_types]
     int32_t first_item;           // index of items[0] among the items that gy, dm and du hold a map for
     int32_t first_kept;           // index of items[0] among the maps of u and mid
     const void* feats;
@@ -55,6 +53,7 @@ struct ConvArgs {
     int32_t tiles_per_seg;        // workgroup tiles of a segment's H x sw pixels
     int32_t n_ctile;              // channel tiles
     int32_t ck;                   // input channels staged at a time
+    uint32_t m_sw;                // recip20_of(sw)
 };
 
 typedef u32x4 u32x4_any __attribute__((aligned(2)));      // 16 and 8 bytes at any element's address
@@ -74,11 +73,11 @@ __device__ __forceinline__ float* conv_route(const ConvArgs& a, int32_t r, size_
     return r >= 0 ? a.gy + size_t(r) * chw : a.gleaf + size_t(-1 - r) * chw;
 }
 
-// elements p[0 .. 3] as floats, zeros from n on (n may be negative); reads nothing behind p[n - 1]
-template <typename T> __device__ __forceinline__ f32x4 load4(const T* p, int n)
+// elements p[0 .. 3] as floats, zeros from n on (n may be negative); reads nothing behind p[n - 1].  FULL: n >= 4 is known
+template <bool FULL, typename T> __device__ __forceinline__ f32x4 load4(const T* p, int n)
 {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (n >= 4) {
+    if (FULL || n >= 4) {
         if constexpr (sizeof(T) == 4) v = *reinterpret_cast<const f32x4_any*>(p);
         else {
             const u32x2 q = *reinterpret_cast<const u32x2_any*>(p);
@@ -89,9 +88,9 @@ template <typename T> __device__ __forceinline__ f32x4 load4(const T* p, int n)
             if (i < n) v[i] = load_f32(p + i);
     return v;
 }
-template <typename T> __device__ __forceinline__ void store4(T* p, int n, const f32x4& v)
+template <bool FULL, typename T> __device__ __forceinline__ void store4(T* p, int n, const f32x4& v)
 {
-    if (n >= 4) {
+    if (FULL || n >= 4) {
         if constexpr (sizeof(T) == 4) *reinterpret_cast<f32x4_any*>(p) = v;
         else *reinterpret_cast<u32x2_any*>(p) = u32x2{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
     } else
@@ -99,10 +98,10 @@ template <typename T> __device__ __forceinline__ void store4(T* p, int n, const 
             if (i < n) store_f32(p + i, v[i]);
 }
 // one 16-byte piece of a row in its own type: 4 floats or 8 bfloat16, zeros from n on
-template <typename T> __device__ __forceinline__ u32x4 load_piece(const T* p, int n)
+template <bool FULL, typename T> __device__ __forceinline__ u32x4 load_piece(const T* p, int n)
 {
     constexpr int N = 16 / int(sizeof(T));
-    if (n >= N) return *reinterpret_cast<const u32x4_any*>(p);
+    if (FULL || n >= N) return *reinterpret_cast<const u32x4_any*>(p);
     u32x4 v = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int i = 0; i < N; ++i)
@@ -114,18 +113,23 @@ template <typename T> __device__ __forceinline__ u32x4 load_piece(const T* p, in
 }
 
 // The gradient that enters an item's second convolution, g = gy [y > 0], four channels of it
-template <typename T> __device__ __forceinline__ f32x4 masked_gy(const float* gy, const T* y, int n)
+template <bool FULL, typename T> __device__ __forceinline__ f32x4 masked_gy(const float* gy, const T* y, int n)
 {
-    f32x4 g = load4(gy, n);
-    const f32x4 v = load4(y, n);
+    f32x4 g = load4<FULL>(gy, n);
+    const f32x4 v = load4<FULL>(y, n);
 #pragma unroll
     for (int i = 0; i < 4; ++i) g[i] = v[i] > 0.f ? g[i] : 0.f;
     return g;
 }
 
-// v / d for v * d < 2^32, d > 1, with m = recip_of(d)
-__device__ __forceinline__ uint32_t recip_of(uint32_t d) { return 0xffffffffu / d + 1u; }
+// Divisions (some thirty instructions) by a few values that a workgroup divides by again and again:
+// v / d for d > 1, v * d < 2^32, with m = recip_of(d)
+__host__ __device__ constexpr uint32_t recip_of(uint32_t d) { return 0xffffffffu / d + 1u; }
 __device__ __forceinline__ uint32_t div_by(uint32_t v, uint32_t m) { return __umulhi(v, m); }
+// v / d for v < 4096, v * d < 2^20, with m = recip20_of(d); here v are the steps of a panel (at most 9 x 142: a 3x3 stages
+// at least 9 pixels), pixels of a tile (1300) and columns of a segment (32)
+__host__ __device__ constexpr uint32_t recip20_of(uint32_t d) { return ((1u << 20) + d - 1) / d; }
+__device__ __forceinline__ uint32_t div20_by(uint32_t v, uint32_t m) { return v * m >> 20; }
 
 template <ConvMode MODE> struct ConvTraits {
     static constexpr bool JOINS = MODE == CV_JOIN || MODE == CV_DJOIN;
@@ -138,45 +142,55 @@ template <ConvMode MODE> struct ConvTraits {
 __host__ __device__ inline int conv_pixel_bytes(int ck, int elt) { return ck * elt + 16; }
 __host__ __device__ inline int conv_rows(int first, int n_pix, int sw, int halo) { return (first + n_pix - 1) / sw - first / sw + 1 + 2 * halo; }
 
-template <typename T, ConvMode MODE, int MT, int NT>
-__global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
+// FULL: C is a multiple of the channels of a step, so that no piece is ever cut short.  (What handles the others doubles the
+// code, and a launch of a few microseconds feels every line of it that the instruction cache has to fetch.)
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+__global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArgs a)
 {
     using Tr = ConvTraits<MODE>;
     using E = std::conditional_t<Tr::BWD, float, T>;      // element type of the staged input: gradients are fp32
     constexpr bool F32 = sizeof(E) == 4;
-    constexpr int TAPS = Tr::TAPS, HALO = Tr::HALO, ES = int(sizeof(E)), KS = F32 ? 16 : 32, PE = 16 / ES, RD = 4;
+    constexpr int TAPS = Tr::TAPS, HALO = Tr::HALO, ES = int(sizeof(E)), KS = F32 ? 16 : 32, PE = 16 / ES;
+    // Steps that the weights are requested ahead: a step is 128 (fp32) or 16 (bf16) clocks of MFMAs per 16 x 16 tile, an
+    // answer takes 500 to 2000.  Even; at C = 128 a wave has 18 or 9 steps.
+    constexpr int RD = F32 ? 6 : 10;
     constexpr int BM = MT * 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
     const int i = blockIdx.y;
-    const dynb_item it = a.items[i];
-    const bool binary = a.arity[it.type] == 2;            // uniform over the workgroup
+    const dynb_item it = items[i];
+    const bool binary = it.src1 != DYNB_NO_ARG;           // uniform over the workgroup
     if (Tr::JOINS && !binary) return;
     const int C = a.C, H = a.H, W = a.W, sw = a.sw;
     const size_t chw = size_t(H) * W * C;
-    const int ctile = blockIdx.x % a.n_ctile, ptile = blockIdx.x / a.n_ctile;      // channel tiles of the same pixels are neighbours
-    const int seg = ptile / a.tiles_per_seg, q0 = (ptile % a.tiles_per_seg) * BM, n_q = H * sw;
-    const int x0 = seg * sw, y0 = q0 / sw;
+    const int ptile = int(blockIdx.x) / a.n_ctile, ctile = int(blockIdx.x) - ptile * a.n_ctile;   // channel tiles of the same pixels are neighbours
+    const int seg = sw == W ? 0 : ptile / a.tiles_per_seg, q0 = (ptile - seg * a.tiles_per_seg) * BM, n_q = H * sw;
+    const int x0 = seg * sw, y0 = q0 / sw, r0 = q0 - y0 * sw;     // the tile's first pixel: row y0, column x0 + r0
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int NO = MODE == CV_DJOIN ? 2 * C : C;          // output channels
     const int n0 = ctile * NT * 16;
 
     const int pix_bytes = conv_pixel_bytes(a.ck, ES), cols = sw + 2 * HALO, row_bytes = cols * pix_bytes;
-    const int n_q_here = min(BM, n_q - q0);
-    const int rows = conv_rows(q0, n_q_here, sw, HALO);
+    const int rows = int(div20_by(r0 + min(BM, n_q - q0) - 1, a.m_sw)) + 1 + 2 * HALO;
 
-    // this lane's weights: output channel n0 + 16 nt + r (the last one again behind the end, whose results are dropped)
-    int n_of[NT];
+    // this lane's weights: output channel n0 + 16 nt + r (the last one again behind the end, whose results are dropped), as
+    // byte offsets from the tile's first row (forward) or column (backward), to which a step adds a uniform offset
+    const char* const w_tile = reinterpret_cast<const char*>((const T*)a.w + size_t(it.type) * C * (Tr::JOINS ? 2 * C : 9 * C)
+                                                             + (Tr::BWD ? size_t(n0) : size_t(n0) * (Tr::JOINS ? 2 * C : 9 * C)));
+    const int w_pitch = (Tr::JOINS ? 2 : 9) * C;          // elements between two rows of weights
+    uint32_t w_at[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) n_of[nt] = min(n0 + nt * 16 + r, NO - 1);
-    const T* w_type = (const T*)a.w + size_t(it.type) * C * (Tr::JOINS ? 2 * C : 9 * C);
+    for (int nt = 0; nt < NT; ++nt) {
+        const uint32_t n = uint32_t(min(n0 + nt * 16 + r, NO - 1) - n0);
+        w_at[nt] = Tr::BWD ? (uint32_t(g * PE) * uint32_t(w_pitch) + n) * uint32_t(sizeof(T)) : (n * uint32_t(w_pitch) + uint32_t(g * PE)) * uint32_t(sizeof(T));
+    }
 
     // this lane's pixels: LDS address of the top left tap, first channel of its piece
     uint32_t x_at[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-        const int q = min(q0 + t * 16 + r, n_q - 1), y = q / sw, x = q - y * sw;
-        x_at[t] = uint32_t((y - y0) * row_bytes + x * pix_bytes + g * 16);
+        const int q = r0 + min(t * 16 + r, n_q - 1 - q0), y = int(div20_by(q, a.m_sw)), x = q - y * sw;
+        x_at[t] = uint32_t(y * row_bytes + x * pix_bytes + g * 16);
     }
     f32x4 acc[MT][NT];
 #pragma unroll
@@ -194,6 +208,32 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
         else return a.du + size_t(a.first_item + i) * chw;
     };
     const T* y_map = MODE == CV_DSECOND || MODE == CV_DFIRST ? conv_dst<T>(a, it.dst, chw) : nullptr;   // the item's result
+    const T* u_map = binary ? (const T*)a.u + size_t(a.first_kept + i) * chw : conv_src<T>(a, it.src0, chw);
+
+    // ---- what the results of this wave (tiles wave, wave + 4, ...) are combined with
+    constexpr int NF = (MT * NT + 3) / 4;
+    struct Out { f32x4 p, q; size_t e; int o, n; };       // n: channels of this lane's pixel that exist (0: no such pixel)
+    Out fin[NF];
+    auto request_operands = [&]() {
+#pragma unroll
+        for (int k = 0; k < NF; ++k) {
+            const int tt = wave + 4 * k, t = tt / NT, nt = tt % NT;
+            const int q = r0 + t * 16 + r, y = int(div20_by(q, a.m_sw)), x = x0 + q - y * sw;
+            Out& f = fin[k];
+            f.o = n0 + nt * 16 + g * 4;                   // lane: pixel r, output channels o .. o + 3
+            f.n = tt < MT * NT && q0 - r0 + q < n_q && x < W ? max(0, min(4, NO - f.o)) : 0;
+            f.e = (size_t(y0 + y) * W + x) * C + f.o;
+            f.p = f.q = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (f.n <= 0) continue;
+            if (!Tr::BWD && a.bias) f.p = load4<FULL>(a.bias + size_t(it.type) * C + f.o, f.n);
+            if constexpr (MODE == CV_SECOND) f.q = load4<FULL>(u_map + f.e, f.n);
+            if constexpr (MODE == CV_DSECOND) f.p = load4<FULL>((const T*)a.mid + size_t(a.first_kept + i) * chw + f.e, f.n);
+            if constexpr (MODE == CV_DFIRST) {
+                f.p = masked_gy<FULL>(a.gy + size_t(a.first_item + i) * chw + f.e, y_map + f.e, f.n);
+                if (binary) f.q = load4<FULL>(u_map + f.e, f.n);
+            }
+        }
+    };
 
     const int panels = (C + a.ck - 1) / a.ck;
 #pragma unroll 1
@@ -201,74 +241,78 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
         const int arg = MODE == CV_JOIN && panel >= panels ? 1 : 0;
         const int c0 = (panel - arg * panels) * a.ck;
         const int nj = min(a.ck / KS, (C - c0 + KS - 1) / KS);
-        const int S = nj * TAPS, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
-        const uint32_t m_nj = recip_of(nj);
-        auto tap_of = [&](int s) -> int { return TAPS == 1 ? 0 : nj == 1 ? s : int(div_by(s, m_nj)); };
-        // weights of step s = tap * nj + j
-        auto load_w = [&](int s, u32x4 (&w)[NT]) {
-            const int tap = tap_of(s), j = s - tap * nj;
-            const int c = c0 + j * KS + g * PE;           // first of this lane's PE input channels
+        const int S = nj * TAPS, s0 = S * wave / 4, n_steps = S * (wave + 1) / 4 - s0;
+
+        // Step s is a tap and KS input channels, channels first.  Weights and pixels of a step lie at uniform offsets.
+        // (The data gradient of a 3x3 takes the weights' taps backwards and sums over their rows.)
+        const uint32_t m_nj = recip20_of(nj);
+        const int w_chan = KS * (Tr::BWD ? w_pitch : 1), w_tap = Tr::BWD ? -C : C;
+        const char* const w_panel = w_tile + (Tr::BWD ? ptrdiff_t(c0) * w_pitch + (Tr::JOINS ? 0 : 8 * C) : ptrdiff_t(arg * C) + c0) * ptrdiff_t(sizeof(T));
+        auto load_w = [&](int step, u32x4 (&w)[NT]) {
+            const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj;
+            const char* p = w_panel + (ptrdiff_t(tap) * w_tap + ptrdiff_t(j) * w_chan) * ptrdiff_t(sizeof(T));
+            const bool inside = FULL || c0 + (j + 1) * KS <= C;          // uniform
+            const int c = c0 + j * KS + g * PE;           // first of this lane's PE summed channels
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                if constexpr (!Tr::BWD) {
-                    const T* p = w_type + (Tr::JOINS ? size_t(n_of[nt]) * 2 * C + arg * C : (size_t(n_of[nt]) * 9 + tap) * C) + c;
-                    w[nt] = load_piece(p, c0 + (j + 1) * KS <= C ? PE : C - c);
-                } else {
-                    // W[k][o]: the channels that are summed are the weights' output channels (rows)
-                    const size_t pitch = Tr::JOINS ? size_t(2) * C : size_t(9) * C;
-                    const T* p = w_type + size_t(c) * pitch + (Tr::JOINS ? 0 : (8 - tap) * C) + n_of[nt];
-                    const int n = c0 + (j + 1) * KS <= C ? 4 : C - c;
+                if constexpr (!Tr::BWD) w[nt] = load_piece<FULL>(reinterpret_cast<const T*>(p + w_at[nt]), inside ? PE : C - c);
+                else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w[nt][e] = __float_as_uint(e < n ? load_f32(p + size_t(e) * pitch) : 0.f);
+                    for (int e = 0; e < 4; ++e)
+                        w[nt][e] = inside || c + e < C ? __float_as_uint(load_f32(reinterpret_cast<const T*>(p + (w_at[nt] + uint32_t(e * w_pitch) * uint32_t(sizeof(T)))))) : 0u;
                 }
             }
         };
+        // No branch around a request: the counter that a wave waits on counts requests, and behind a branch the compiler
+        // can only wait for all of them.  Past the end the last step is requested again.
         u32x4 ring[RD][NT];
 #pragma unroll
-        for (int u = 0; u < RD; ++u)
-            if (s0 + u < s1) load_w(s0 + u, ring[u]);
+        for (int u = 0; u < RD; ++u) load_w(max(0, min(u, n_steps - 1)), ring[u]);
 
         // ---- stage rows x cols pixels x nj * KS channels
         if (panel > 0) __syncthreads();
         {
             const E* src = input_map(arg);
             const int np = nj * (KS / PE), n_pieces = rows * cols * np;
-            const uint32_t m_np = recip_of(np), m_cols = recip_of(cols);
-            constexpr int UN = 8;
+            const uint32_t m_np = recip_of(np), m_cols = recip20_of(cols);
+            constexpr int UN = 6;
             for (int base = tid; base < n_pieces; base += 256 * UN) {
                 u32x4 v[UN];
                 uint32_t at[UN];
+                uint32_t keep[UN];
 #pragma unroll
                 for (int k = 0; k < UN; ++k) {
                     const int c = base + k * 256;
-                    v[k] = u32x4{0u, 0u, 0u, 0u};
-                    const uint32_t pix = div_by(c, m_np), part = c - pix * np, row = cols == 1 ? pix : div_by(pix, m_cols), col = pix - row * cols;
+                    const uint32_t pix = div_by(c, m_np), part = c - pix * np, row = div20_by(pix, m_cols), col = pix - row * cols;
                     at[k] = row * row_bytes + col * pix_bytes + part * 16;
                     const int y = y0 - HALO + int(row), x = x0 - HALO + int(col), ch = c0 + int(part) * PE;
-                    if (c < n_pieces && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) {
-                        const size_t e = (size_t(y) * W + x) * C + ch;
-                        if constexpr (MODE == CV_DSECOND) v[k] = __builtin_bit_cast(u32x4, masked_gy(src + e, y_map + e, C - ch));
-                        else v[k] = load_piece(src + e, C - ch);
-                    }
+                    const bool inside = c < n_pieces && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W);
+                    keep[k] = inside ? ~0u : 0u;
+                    const size_t e = inside ? (size_t(y) * W + x) * C + ch : 0;      // outside: any piece, replaced by zeros below
+                    if constexpr (MODE == CV_DSECOND) v[k] = __builtin_bit_cast(u32x4, masked_gy<FULL>(src + e, y_map + e, inside ? C - ch : 0));
+                    else v[k] = load_piece<FULL>(src + e, inside ? C - ch : 0);
                 }
 #pragma unroll
                 for (int k = 0; k < UN; ++k)
-                    if (base + k * 256 < n_pieces) *reinterpret_cast<u32x4*>(lds_raw + at[k]) = v[k];
+                    if (base + k * 256 < n_pieces) *reinterpret_cast<u32x4*>(__builtin_assume_aligned(lds_raw + at[k], 16)) = v[k] & keep[k];
+                // Everything has arrived.  Said aloud, because pieces that were requested and not stored would otherwise count
+                // as outstanding, and every wait from here on would be for more than it needs.
+                __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0)
             }
         }
+        if (panel == 0) request_operands();
         __syncthreads();
 
-        // ---- this wave's steps
-#pragma unroll 1
-        for (int s = s0; s < s1; s += RD) {
+        // ---- this wave's steps: the pixels of the next step are read under the MFMAs of this one
+        if (n_steps > 0) {
+            u32x4 x[2][MT];
+            auto read_x = [&](int step, u32x4 (&v)[MT]) {
+                const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
+                const uint32_t off = uint32_t(kh * row_bytes + kw * pix_bytes + j * (KS * ES));
 #pragma unroll
-            for (int u = 0; u < RD; ++u) {
-                if (s + u >= s1) break;
-                const int tap = tap_of(s + u), j = s + u - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
-                const uint32_t off = uint32_t(kh * row_bytes + kw * pix_bytes + j * KS * ES);
-                u32x4 x[MT];
-#pragma unroll
-                for (int t = 0; t < MT; ++t) x[t] = *reinterpret_cast<const u32x4*>(lds_raw + x_at[t] + off);
+                for (int t = 0; t < MT; ++t) v[t] = *reinterpret_cast<const u32x4*>(lds_raw + x_at[t] + off);
+            };
+            auto multiply = [&](const u32x4 (&w)[NT], const u32x4 (&v)[MT]) {
                 if constexpr (F32) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -276,15 +320,35 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
                         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                             for (int t = 0; t < MT; ++t)
-                                acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ring[u][nt][e]), __uint_as_float(x[t][e]), acc[t][nt], 0, 0, 0);
+                                acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[nt][e]), __uint_as_float(v[t][e]), acc[t][nt], 0, 0, 0);
                 } else {
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                         for (int t = 0; t < MT; ++t)
-                            acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ring[u][nt]), __builtin_bit_cast(bf16x8, x[t]), acc[t][nt], 0, 0, 0);
+                            acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[nt]), __builtin_bit_cast(bf16x8, v[t]), acc[t][nt], 0, 0, 0);
                 }
-                if (s + u + RD < s1) load_w(s + u + RD, ring[u]);
+            };
+            const int last = n_steps - 1;
+            read_x(0, x[0]);
+            int s = 0;
+#pragma unroll 1
+            for (; s + RD < n_steps; s += RD) {
+#pragma unroll
+                for (int u = 0; u < RD; ++u) {
+                    read_x(min(s + u + 1, last), x[(u + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(ring[u], x[u & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_w(min(s + u + RD, last), ring[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < RD; ++u) {
+                if (s + u >= n_steps) break;
+                read_x(min(s + u + 1, last), x[(u + 1) & 1]);
+                multiply(ring[u], x[u & 1]);
             }
         }
     }
@@ -297,106 +361,120 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) red[(wave * MT * NT + t * NT + nt) * 64 + lane] = acc[t][nt];
     __syncthreads();
-    for (int tt = wave; tt < MT * NT; tt += 4) {
-        const int t = tt / NT, nt = tt % NT;
-        const int q = q0 + t * 16 + r, y = q / sw, x = x0 + q - y * sw;
-        const int o = n0 + nt * 16 + g * 4, n = min(4, NO - o);          // lane: pixel r, output channels o .. o + 3
-        if (q >= n_q || x >= W || n <= 0) continue;
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+        const Out& f = fin[k];
+        if (f.n <= 0) continue;
+        const int tt = wave + 4 * k, o = f.o, n = f.n;
         f32x4 v = red[tt * 64 + lane];
 #pragma unroll
         for (int w = 1; w < 4; ++w) {
             const f32x4 p = red[(w * MT * NT + tt) * 64 + lane];
             v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
         }
-        const size_t e = (size_t(y) * W + x) * C + o;
         if constexpr (!Tr::BWD) {
-            if (a.bias) {
-                const f32x4 b = load4(a.bias + size_t(it.type) * C + o, n);
-                v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w;
-            }
-            T* dst;
-            if constexpr (MODE == CV_JOIN) dst = (T*)a.u + size_t(a.first_kept + i) * chw;
-            else if constexpr (MODE == CV_FIRST) dst = (T*)a.mid + size_t(a.first_kept + i) * chw;
-            else {
-                const T* u = binary ? (const T*)a.u + size_t(a.first_kept + i) * chw : conv_src<T>(a, it.src0, chw);
-                const f32x4 b = load4(u + e, n);
-                v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w;
-                dst = conv_dst<T>(a, it.dst, chw);
-            }
+            v.x += f.p.x; v.y += f.p.y; v.z += f.p.z; v.w += f.p.w;
+            if constexpr (MODE == CV_SECOND) { v.x += f.q.x; v.y += f.q.y; v.z += f.q.z; v.w += f.q.w; }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = fmaxf(v[k], 0.f);
-            store4(dst + e, n, v);
+            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c], 0.f);
+            T* dst = MODE == CV_SECOND ? conv_dst<T>(a, it.dst, chw) : (T*)(MODE == CV_JOIN ? a.u : a.mid) + size_t(a.first_kept + i) * chw;
+            store4<FULL>(dst + f.e, n, v);
         } else if constexpr (MODE == CV_DSECOND) {                       // dmid = result [mid > 0]
-            const f32x4 m = load4((const T*)a.mid + size_t(a.first_kept + i) * chw + e, n);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = m[k] > 0.f ? v[k] : 0.f;
-            store4(a.dm + size_t(a.first_item + i) * chw + e, n, v);
+            for (int c = 0; c < 4; ++c) v[c] = f.p[c] > 0.f ? v[c] : 0.f;
+            store4<FULL>(a.dm + size_t(a.first_item + i) * chw + f.e, n, v);
         } else if constexpr (MODE == CV_DFIRST) {                        // du = result + g
-            const f32x4 b = masked_gy(a.gy + size_t(a.first_item + i) * chw + e, y_map + e, n);
-            v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w;
+            v.x += f.p.x; v.y += f.p.y; v.z += f.p.z; v.w += f.p.w;
             if (binary) {                                                // dc = du [u > 0]
-                const f32x4 u = load4((const T*)a.u + size_t(a.first_kept + i) * chw + e, n);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) v[k] = u[k] > 0.f ? v[k] : 0.f;
-                store4(a.du + size_t(a.first_item + i) * chw + e, n, v);
-            } else store4(conv_route(a, a.gdst0[i], chw) + e, n, v);
+                for (int c = 0; c < 4; ++c) v[c] = f.q[c] > 0.f ? v[c] : 0.f;
+                store4<FULL>(a.du + size_t(a.first_item + i) * chw + f.e, n, v);
+            } else store4<FULL>(conv_route(a, a.gdst0[i], chw) + f.e, n, v);
         } else {                                                         // channels 0 .. C - 1: first argument, C .. 2 C - 1: second
-            float* d0 = conv_route(a, a.gdst0[i], chw) + e;
-            float* d1 = conv_route(a, a.gdst1[i], chw) + e - C;
-            if (o + n <= C) store4(d0, n, v);
-            else if (o >= C) store4(d1, n, v);
+            float* d0 = conv_route(a, a.gdst0[i], chw) + f.e;
+            float* d1 = conv_route(a, a.gdst1[i], chw) + f.e - C;
+            if (FULL || o + n <= C || o >= C) store4<FULL>(o >= C ? d1 : d0, n, v);
             else
-                for (int k = 0; k < 4; ++k)
-                    if (k < n) (o + k < C ? d0 : d1)[k] = v[k];
+                for (int c = 0; c < 4; ++c)
+                    if (c < n) (o + c < C ? d0 : d1)[c] = v[c];
         }
     }
 }
 
-template <typename T, ConvMode MODE, int MT, int NT>
-int launch_conv_tile(ConvArgs a, int count, hipStream_t st)
+// ---- launching
+constexpr int CONV_LDS_MAX = 80 * 1024;                                  // two workgroups per CU
+
+// staged pixels of a tile of mt x 16 pixels, which start anywhere in a row
+inline int conv_tile_pixels(const ConvArgs& a, int mt, int halo)
+{
+    const int n_pix = std::min(mt * 16, a.H * a.sw);
+    return std::min(conv_rows(a.sw - 1, n_pix, a.sw, halo), a.H + 2 * halo) * (a.sw + 2 * halo);
+}
+
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t st)
 {
     using Tr = ConvTraits<MODE>;
     constexpr int ES = Tr::BWD ? 4 : int(sizeof(T)), KS = ES == 4 ? 16 : 32;
-    constexpr int LDS_MAX = 80 * 1024;                                   // two workgroups per CU
     static std::atomic<uint64_t> attr_set{0};                            // one bit per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return DYNB_E_HIP;
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv<T, MODE, MT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv<T, MODE, MT, NT, FULL>), hipFuncAttributeMaxDynamicSharedMemorySize, CONV_LDS_MAX) != hipSuccess)
             return DYNB_E_HIP;
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
     const int n_q = a.H * a.sw, n_seg = (a.W + a.sw - 1) / a.sw;
     a.tiles_per_seg = (n_q + MT * 16 - 1) / (MT * 16);
     a.n_ctile = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + NT * 16 - 1) / (NT * 16);
-    // a tile's pixels start anywhere in a row
-    const int n_pix = std::min(MT * 16, n_q);
-    const int pixels = std::min(conv_rows(a.sw - 1, n_pix, a.sw, Tr::HALO), a.H + 2 * Tr::HALO) * (a.sw + 2 * Tr::HALO);
+    const int pixels = conv_tile_pixels(a, MT, Tr::HALO);
     // as many channels at a time as fit, in panels of nearly equal size
     const int steps = (a.C + KS - 1) / KS;
-    const int fit = std::max(1, (LDS_MAX / pixels - 16) / (KS * ES));
+    const int fit = std::max(1, (CONV_LDS_MAX / pixels - 16) / (KS * ES));
     const int panels = (steps + fit - 1) / fit;
     a.ck = (steps + panels - 1) / panels * KS;
+    a.m_sw = recip20_of(a.sw);
     const size_t lds = std::max<size_t>(size_t(pixels) * conv_pixel_bytes(a.ck, ES), size_t(4) * MT * NT * 1024);
-    if (lds > LDS_MAX) return DYNB_E_UNSUPPORTED;                        // cannot happen: sw <= 32
-    hipLaunchKernelGGL((k_conv<T, MODE, MT, NT>), dim3(unsigned(n_seg * a.tiles_per_seg * a.n_ctile), unsigned(count)), dim3(256), lds, st, a);
+    if (lds > CONV_LDS_MAX) return DYNB_E_UNSUPPORTED;                   // cannot happen: sw <= 32
+    hipLaunchKernelGGL((k_conv<T, MODE, MT, NT, FULL>), dim3(unsigned(n_seg * a.tiles_per_seg * a.n_ctile), unsigned(count)), dim3(256), lds, st, items, a);
     return DYNB_OK;
 }
 
-// One convolution for `count` (<= 65535) items.  The tile is the largest that still makes two workgroups per CU (256 CUs): small
-// tiles read the weights and stage the halo more often per output, but a launch that leaves CUs idle takes as long
-// as its one workgroup does.
-template <typename T, ConvMode MODE>
-int launch_conv(ConvArgs a, int count, hipStream_t st)
+// One convolution for `count` (<= 65535) items.  The tile is the one that finishes first in a simple account of a CU's time:
+// it runs ceil(workgroups / 256) workgroups, each with its MFMAs (a quarter of the steps per SIMD), the staging of its
+// pixels at about 24 bytes per clock, and about 1200 clocks of its own.  Large tiles read weights and halos less
+// often per output; small ones split the launch into CU-sized shares more finely.  Measured for fp32, C = 128, 14 x 14, us:
+//     items      1     6     9     12    15    18    21    25
+//     4 x 2    15.7  15.8  16.3  16.5  16.9  27.3  27.6  27.4
+//     2 x 2    10.0  10.4  10.9  17.0  17.1  17.9  23.4  23.9
+//     2 x 1     7.4  10.9  11.4  14.9  19.0  19.6  23.2  26.3
+template <typename T, ConvMode MODE, bool FULL>
+int launch_conv_full(const dynb_item* items, ConvArgs a, int count, hipStream_t st)
 {
+    using Tr = ConvTraits<MODE>;
+    constexpr int ES = Tr::BWD ? 4 : int(sizeof(T)), KS = ES == 4 ? 16 : 32, STEP_CLOCKS = ES == 4 ? 128 : 16;
     const int n_seg = (a.W + 31) / 32;
     a.sw = (a.W + n_seg - 1) / n_seg;
-    const long long ptiles = (long long)n_seg * ((a.H * a.sw + 15) / 16), ctiles = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + 15) / 16;
-    auto groups = [&](int mt, int nt) { return (long long)count * ((ptiles + mt - 1) / mt) * ((ctiles + nt - 1) / nt); };
-    if (groups(4, 2) >= 512) return launch_conv_tile<T, MODE, 4, 2>(a, count, st);
-    if (groups(4, 1) >= 512) return launch_conv_tile<T, MODE, 4, 1>(a, count, st);
-    if (groups(2, 1) >= 512) return launch_conv_tile<T, MODE, 2, 1>(a, count, st);
-    return launch_conv_tile<T, MODE, 1, 1>(a, count, st);
+    const long long ptiles = (long long)((a.W + a.sw - 1) / a.sw) * ((a.H * a.sw + 15) / 16), ctiles = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + 15) / 16;
+    const long long steps = (long long)((a.C + KS - 1) / KS) * Tr::TAPS * (MODE == CV_JOIN ? 2 : 1);
+    auto clocks = [&](int mt, int nt) {
+        const long long groups = (long long)count * ((ptiles + mt - 1) / mt) * ((ctiles + nt - 1) / nt);
+        const long long staged = (long long)conv_tile_pixels(a, mt, Tr::HALO) * a.C * ES * (MODE == CV_JOIN || MODE == CV_DSECOND ? 2 : 1);
+        return (groups + 255) / 256 * (mt * nt * ((steps + 3) / 4) * STEP_CLOCKS + staged / 24 + 1200);
+    };
+    const long long c42 = clocks(4, 2), c22 = clocks(2, 2), c21 = clocks(2, 1), c11 = clocks(1, 1);
+    const long long best = std::min(std::min(c42, c22), std::min(c21, c11));
+    if (best == c42) return launch_conv_tile<T, MODE, 4, 2, FULL>(items, a, count, st);
+    if (best == c22) return launch_conv_tile<T, MODE, 2, 2, FULL>(items, a, count, st);
+    if (best == c21) return launch_conv_tile<T, MODE, 2, 1, FULL>(items, a, count, st);
+    return launch_conv_tile<T, MODE, 1, 1, FULL>(items, a, count, st);
+}
+
+template <typename T, ConvMode MODE>
+int launch_conv(const dynb_item* items, const ConvArgs& a, int count, hipStream_t st)
+{
+    constexpr int KS = ConvTraits<MODE>::BWD || sizeof(T) == 4 ? 16 : 32;
+    return a.C % KS == 0 ? launch_conv_full<T, MODE, true>(items, a, count, st) : launch_conv_full<T, MODE, false>(items, a, count, st);
 }
 
 }  // namespace

@@ -66,7 +66,6 @@ __device__ long long* g_phase_clk = nullptr;      // [workgroup][wave][16]
 struct MfArgs {
     const dynb_item* items;
     int32_t count;
-    const uint8_t* arity;     // device [n_types]
     const bf16_t* feats;
     bf16_t* out;
     bf16_t* slots;
@@ -136,7 +135,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     PHASE(0);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const dynb_item it = a.items[node];
-    const bool binary = a.arity[it.type] == 2;                        // uniform over the workgroup
+    const bool binary = it.src1 != DYNB_NO_ARG;                        // uniform over the workgroup
     const int r = lane & 31, h = lane >> 5;
     const int n0 = wave * 32;                 // first output channel of this wave
     const size_t keep_at = size_t(a.first_item + node) * P;           // first pixel of this item's kept maps
@@ -384,10 +383,9 @@ __global__ __launch_bounds__(256, 1) void k_module_persist(MfArgs a, PersistArgs
             if (tk < q.n_tickets) {
                 go = 1;
                 const dynb_item it = items[q.tickets[tk] >> 2];
-                const int nsrc = a.arity[it.type];
-                for (int s = 0; s < nsrc && go == 1; ++s) {
+                for (int s = 0; s < 2 && go == 1; ++s) {
                     const int32_t src = s == 0 ? it.src0 : it.src1;
-                    if (src < 0) continue;                    // an example's feature map: always there
+                    if (src < 0) continue;                    // an example's feature map (always there) or no argument
                     int32_t polls = 0;
                     while (load_relaxed(q.ready + src) < 2) {
                         if (polls >= q.spin_limit || load_relaxed(q.status) != 0) {
@@ -537,7 +535,6 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
     const size_t map = size_t(s->C) * s->H * s->W * sizeof(T);
     const char* d = static_cast<const char*>(p->dev_buf);
     ConvArgs a = {};
-    a.arity = reinterpret_cast<const uint8_t*>(d + plan_items_bytes(p) + plan_leaf_bytes(p));
     a.feats = feats; a.out = out; a.slots = ws;
     a.mid = ws + dynb_generic_keep_offset(p, map);
     a.u = static_cast<char*>(a.mid) + dynb_generic_kept_maps(p) * map;
@@ -550,14 +547,14 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
         // grid.y is limited to 65535: split very wide launch groups
         for (int off = 0; off < l.count; off += 32768) {
             const int count = std::min(32768, l.count - off);
-            a.items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
+            const dynb_item* items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
             a.first_kept = p->keep ? l.start + off : off;
             int rc = DYNB_OK;
-            if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = launch_conv<T, CV_JOIN>(a, count, st); }
+            if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = launch_conv<T, CV_JOIN>(items, a, count, st); }
             a.w = w->w3a; a.bias = w->b3a;
-            if (rc == DYNB_OK) rc = launch_conv<T, CV_FIRST>(a, count, st);
+            if (rc == DYNB_OK) rc = launch_conv<T, CV_FIRST>(items, a, count, st);
             a.w = w->w3b; a.bias = w->b3b;
-            if (rc == DYNB_OK) rc = launch_conv<T, CV_SECOND>(a, count, st);
+            if (rc == DYNB_OK) rc = launch_conv<T, CV_SECOND>(items, a, count, st);
             if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a convolution could not be launched");
         }
         if (timed && !coarse) dynb::timing_mark(st, int32_t(&l - p->launches.data()), l.count);
@@ -600,7 +597,6 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
     }
     const char* d = static_cast<const char*>(p->dev_buf);
     MfArgs a;
-    a.arity = reinterpret_cast<const uint8_t*>(d + plan_items_bytes(p) + plan_leaf_bytes(p));
     a.feats = static_cast<const bf16_t*>(feats);
     a.out = static_cast<bf16_t*>(out);
     a.slots = reinterpret_cast<bf16_t*>(ws);

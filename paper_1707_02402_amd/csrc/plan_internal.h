@@ -11,9 +11,11 @@
 // One module evaluation as the kernels see it.  src/dst >= 0 name a workspace slot; a negative
 // value v names example -1-v: as a source its feature map (the SCENE output), as a destination
 // its row of the output tensor (the node is that example's root).
+constexpr int32_t DYNB_NO_ARG = INT32_MIN;      // no example has that index
+
 struct dynb_item {
     int32_t src0;
-    int32_t src1;   // unused for unary functions
+    int32_t src1;   // DYNB_NO_ARG: the function takes one argument (a kernel need not look the arity up)
     int32_t dst;
     int32_t type;
 };

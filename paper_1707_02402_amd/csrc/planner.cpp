@@ -301,7 +301,7 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
             };
             dynb_item it;
             it.src0 = src(p->child0[n]);
-            it.src1 = src(p->child1[n]);
+            it.src1 = arity[p->type[n]] == 2 ? src(p->child1[n]) : DYNB_NO_ARG;
             it.dst = is_root ? -1 - example[n] : slot[n];
             it.type = p->type[n];
             ++p->launches.back().count;
