@@ -142,18 +142,135 @@ template <ConvMode MODE> struct ConvTraits {
 __host__ __device__ inline int conv_pixel_bytes(int ck, int elt) { return ck * elt + 16; }
 __host__ __device__ inline int conv_rows(int first, int n_pix, int sw, int halo) { return (first + n_pix - 1) / sw - first / sw + 1 + 2 * halo; }
 
-// FULL: C is a multiple of the channels of a step, so that no piece is ever cut short.  (What handles the others doubles the
-// code, and a launch of a few microseconds feels every line of it that the instruction cache has to fetch.)
+// The steps of a sum: step s is a tap and KS input channels, channels first.  A wave takes steps s0 .. s0 + n_steps of NT
+// channel tiles and MT pixel tiles.  Weights and pixels of a step lie at uniform offsets from the lane's own places.
+// (The data gradient of a 3x3 takes the weights' taps backwards and sums over their rows.)
+// request() asks for the first RD steps' weights, run() multiplies.  There is no branch around a request: the counter that
+// a wave waits on counts requests, and behind a branch the compiler can only wait for all of them.  Past the end the
+// last step is requested again.  The pixels of the next step are read under the MFMAs of this one.
+// FULL: C is a multiple of KS, so that no piece is ever cut short.  (What handles the others doubles the code, and a launch of
+// a few microseconds feels every line of it that the instruction cache has to fetch.)
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+struct ConvSteps {
+    using Tr = ConvTraits<MODE>;
+    using E = std::conditional_t<Tr::BWD, float, T>;      // element type of the staged input: gradients are fp32
+    static constexpr bool F32 = sizeof(E) == 4;
+    static constexpr int TAPS = Tr::TAPS, ES = int(sizeof(E)), KS = F32 ? 16 : 32, PE = 16 / ES;
+    // Steps that the weights are requested ahead: a step is 128 (fp32) or 16 (bf16) clocks of MFMAs per 16 x 16 tile, an
+    // answer takes 500 to 2000.  Even; at C = 128 a wave of k_conv has 18 or 9 steps.
+    static constexpr int RD = F32 ? 6 : 10;
+
+    uint32_t w_at[NT], x_at[MT];      // this lane's weights (bytes from w_panel) and pixels (LDS address of the top left tap)
+    const char* w_panel;
+    int C, c0, nj, s0, n_steps, w_pitch, w_chan, w_tap, g, row_bytes, pix_bytes;
+    uint32_t m_nj;
+    u32x4 ring[RD][NT];
+
+    // weights of `type` for output channels n0 .. of NO (the last one again behind the end, whose results are dropped)
+    __device__ __forceinline__ const char* weights(const void* w, int type, int C_, int n0, int NO, int lane)
+    {
+        C = C_;
+        g = lane >> 4;
+        w_pitch = (Tr::JOINS ? 2 : 9) * C;                // elements between two rows of weights
+        w_chan = KS * (Tr::BWD ? w_pitch : 1);
+        w_tap = Tr::BWD ? -C : C;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const uint32_t n = uint32_t(min(n0 + nt * 16 + (lane & 15), NO - 1) - n0);
+            w_at[nt] = Tr::BWD ? (uint32_t(g * PE) * uint32_t(w_pitch) + n) * uint32_t(sizeof(T)) : (n * uint32_t(w_pitch) + uint32_t(g * PE)) * uint32_t(sizeof(T));
+        }
+        return reinterpret_cast<const char*>((const T*)w + size_t(type) * C * w_pitch + (Tr::BWD ? size_t(n0) : size_t(n0) * w_pitch));
+    }
+    // summed channels first .. of `pieces` KS channels; of the join: of argument `arg`
+    __device__ __forceinline__ void panel(const char* w_tile, int first, int pieces, int arg)
+    {
+        c0 = first;
+        nj = pieces;
+        m_nj = recip20_of(nj);
+        w_panel = w_tile + (Tr::BWD ? ptrdiff_t(c0) * w_pitch + (Tr::JOINS ? 0 : 8 * C) : ptrdiff_t(arg * C) + c0) * ptrdiff_t(sizeof(T));
+    }
+    __device__ __forceinline__ void load_w(int step, u32x4 (&w)[NT]) const
+    {
+        const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj;
+        const char* p = w_panel + (ptrdiff_t(tap) * w_tap + ptrdiff_t(j) * w_chan) * ptrdiff_t(sizeof(T));
+        const bool inside = FULL || c0 + (j + 1) * KS <= C;              // uniform
+        const int c = c0 + j * KS + g * PE;               // first of this lane's PE summed channels
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if constexpr (!Tr::BWD) w[nt] = load_piece<FULL>(reinterpret_cast<const T*>(p + w_at[nt]), inside ? PE : C - c);
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    w[nt][e] = inside || c + e < C ? __float_as_uint(load_f32(reinterpret_cast<const T*>(p + (w_at[nt] + uint32_t(e * w_pitch) * uint32_t(sizeof(T)))))) : 0u;
+            }
+        }
+    }
+    __device__ __forceinline__ void read_x(int step, u32x4 (&v)[MT]) const
+    {
+        extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+        const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
+        const uint32_t off = uint32_t(kh * row_bytes + kw * pix_bytes + j * (KS * ES));
+#pragma unroll
+        for (int t = 0; t < MT; ++t) v[t] = *reinterpret_cast<const u32x4*>(lds_raw + x_at[t] + off);
+    }
+    static __device__ __forceinline__ void multiply(f32x4 (&acc)[MT][NT], const u32x4 (&w)[NT], const u32x4 (&v)[MT])
+    {
+        if constexpr (F32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int t = 0; t < MT; ++t)
+                        acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[nt][e]), __uint_as_float(v[t][e]), acc[t][nt], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+                    acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[nt]), __builtin_bit_cast(bf16x8, v[t]), acc[t][nt], 0, 0, 0);
+        }
+    }
+    __device__ __forceinline__ void request()
+    {
+#pragma unroll
+        for (int u = 0; u < RD; ++u) load_w(max(0, min(u, n_steps - 1)), ring[u]);
+    }
+    __device__ __forceinline__ void run(f32x4 (&acc)[MT][NT])
+    {
+        if (n_steps <= 0) return;
+        u32x4 x[2][MT];
+        const int last = n_steps - 1;
+        read_x(0, x[0]);
+        int s = 0;
+#pragma unroll 1
+        for (; s + RD < n_steps; s += RD) {
+#pragma unroll
+            for (int u = 0; u < RD; ++u) {
+                read_x(min(s + u + 1, last), x[(u + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(acc, ring[u], x[u & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                load_w(min(s + u + RD, last), ring[u]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RD; ++u) {
+            if (s + u >= n_steps) break;
+            read_x(min(s + u + 1, last), x[(u + 1) & 1]);
+            multiply(acc, ring[u], x[u & 1]);
+        }
+    }
+};
+
 template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
 __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArgs a)
 {
     using Tr = ConvTraits<MODE>;
-    using E = std::conditional_t<Tr::BWD, float, T>;      // element type of the staged input: gradients are fp32
-    constexpr bool F32 = sizeof(E) == 4;
-    constexpr int TAPS = Tr::TAPS, HALO = Tr::HALO, ES = int(sizeof(E)), KS = F32 ? 16 : 32, PE = 16 / ES;
-    // Steps that the weights are requested ahead: a step is 128 (fp32) or 16 (bf16) clocks of MFMAs per 16 x 16 tile, an
-    // answer takes 500 to 2000.  Even; at C = 128 a wave has 18 or 9 steps.
-    constexpr int RD = F32 ? 6 : 10;
+    using Steps = ConvSteps<T, MODE, MT, NT, FULL>;
+    using E = typename Steps::E;
+    constexpr int HALO = Tr::HALO, ES = Steps::ES, KS = Steps::KS, PE = Steps::PE;
     constexpr int BM = MT * 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
@@ -173,24 +290,14 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
     const int pix_bytes = conv_pixel_bytes(a.ck, ES), cols = sw + 2 * HALO, row_bytes = cols * pix_bytes;
     const int rows = int(div20_by(r0 + min(BM, n_q - q0) - 1, a.m_sw)) + 1 + 2 * HALO;
 
-    // this lane's weights: output channel n0 + 16 nt + r (the last one again behind the end, whose results are dropped), as
-    // byte offsets from the tile's first row (forward) or column (backward), to which a step adds a uniform offset
-    const char* const w_tile = reinterpret_cast<const char*>((const T*)a.w + size_t(it.type) * C * (Tr::JOINS ? 2 * C : 9 * C)
-                                                             + (Tr::BWD ? size_t(n0) : size_t(n0) * (Tr::JOINS ? 2 * C : 9 * C)));
-    const int w_pitch = (Tr::JOINS ? 2 : 9) * C;          // elements between two rows of weights
-    uint32_t w_at[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const uint32_t n = uint32_t(min(n0 + nt * 16 + r, NO - 1) - n0);
-        w_at[nt] = Tr::BWD ? (uint32_t(g * PE) * uint32_t(w_pitch) + n) * uint32_t(sizeof(T)) : (n * uint32_t(w_pitch) + uint32_t(g * PE)) * uint32_t(sizeof(T));
-    }
-
-    // this lane's pixels: LDS address of the top left tap, first channel of its piece
-    uint32_t x_at[MT];
+    Steps steps;
+    const char* const w_tile = steps.weights(a.w, it.type, C, n0, NO, lane);
+    steps.row_bytes = row_bytes;
+    steps.pix_bytes = pix_bytes;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int q = r0 + min(t * 16 + r, n_q - 1 - q0), y = int(div20_by(q, a.m_sw)), x = q - y * sw;
-        x_at[t] = uint32_t(y * row_bytes + x * pix_bytes + g * 16);
+        steps.x_at[t] = uint32_t(y * row_bytes + x * pix_bytes + g * 16);
     }
     f32x4 acc[MT][NT];
 #pragma unroll
@@ -241,33 +348,11 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
         const int arg = MODE == CV_JOIN && panel >= panels ? 1 : 0;
         const int c0 = (panel - arg * panels) * a.ck;
         const int nj = min(a.ck / KS, (C - c0 + KS - 1) / KS);
-        const int S = nj * TAPS, s0 = S * wave / 4, n_steps = S * (wave + 1) / 4 - s0;
-
-        // Step s is a tap and KS input channels, channels first.  Weights and pixels of a step lie at uniform offsets.
-        // (The data gradient of a 3x3 takes the weights' taps backwards and sums over their rows.)
-        const uint32_t m_nj = recip20_of(nj);
-        const int w_chan = KS * (Tr::BWD ? w_pitch : 1), w_tap = Tr::BWD ? -C : C;
-        const char* const w_panel = w_tile + (Tr::BWD ? ptrdiff_t(c0) * w_pitch + (Tr::JOINS ? 0 : 8 * C) : ptrdiff_t(arg * C) + c0) * ptrdiff_t(sizeof(T));
-        auto load_w = [&](int step, u32x4 (&w)[NT]) {
-            const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj;
-            const char* p = w_panel + (ptrdiff_t(tap) * w_tap + ptrdiff_t(j) * w_chan) * ptrdiff_t(sizeof(T));
-            const bool inside = FULL || c0 + (j + 1) * KS <= C;          // uniform
-            const int c = c0 + j * KS + g * PE;           // first of this lane's PE summed channels
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                if constexpr (!Tr::BWD) w[nt] = load_piece<FULL>(reinterpret_cast<const T*>(p + w_at[nt]), inside ? PE : C - c);
-                else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        w[nt][e] = inside || c + e < C ? __float_as_uint(load_f32(reinterpret_cast<const T*>(p + (w_at[nt] + uint32_t(e * w_pitch) * uint32_t(sizeof(T)))))) : 0u;
-                }
-            }
-        };
-        // No branch around a request: the counter that a wave waits on counts requests, and behind a branch the compiler
-        // can only wait for all of them.  Past the end the last step is requested again.
-        u32x4 ring[RD][NT];
-#pragma unroll
-        for (int u = 0; u < RD; ++u) load_w(max(0, min(u, n_steps - 1)), ring[u]);
+        steps.panel(w_tile, c0, nj, arg);
+        const int S = nj * Tr::TAPS;
+        steps.s0 = S * wave / 4;                          // this wave's share
+        steps.n_steps = S * (wave + 1) / 4 - steps.s0;
+        steps.request();
 
         // ---- stage rows x cols pixels x nj * KS channels
         if (panel > 0) __syncthreads();
@@ -303,54 +388,7 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
         if (panel == 0) request_operands();
         __syncthreads();
 
-        // ---- this wave's steps: the pixels of the next step are read under the MFMAs of this one
-        if (n_steps > 0) {
-            u32x4 x[2][MT];
-            auto read_x = [&](int step, u32x4 (&v)[MT]) {
-                const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
-                const uint32_t off = uint32_t(kh * row_bytes + kw * pix_bytes + j * (KS * ES));
-#pragma unroll
-                for (int t = 0; t < MT; ++t) v[t] = *reinterpret_cast<const u32x4*>(lds_raw + x_at[t] + off);
-            };
-            auto multiply = [&](const u32x4 (&w)[NT], const u32x4 (&v)[MT]) {
-                if constexpr (F32) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                            for (int t = 0; t < MT; ++t)
-                                acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[nt][e]), __uint_as_float(v[t][e]), acc[t][nt], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int t = 0; t < MT; ++t)
-                            acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[nt]), __builtin_bit_cast(bf16x8, v[t]), acc[t][nt], 0, 0, 0);
-                }
-            };
-            const int last = n_steps - 1;
-            read_x(0, x[0]);
-            int s = 0;
-#pragma unroll 1
-            for (; s + RD < n_steps; s += RD) {
-#pragma unroll
-                for (int u = 0; u < RD; ++u) {
-                    read_x(min(s + u + 1, last), x[(u + 1) & 1]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    multiply(ring[u], x[u & 1]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_w(min(s + u + RD, last), ring[u]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < RD; ++u) {
-                if (s + u >= n_steps) break;
-                read_x(min(s + u + 1, last), x[(u + 1) & 1]);
-                multiply(ring[u], x[u & 1]);
-            }
-        }
+        steps.run(acc);
     }
 
     // ---- partial sums through LDS; wave w finishes tiles w, w + 4, ...
@@ -398,6 +436,191 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
                 for (int c = 0; c < 4; ++c)
                     if (c < n) (o + c < C ? d0 : d1)[c] = v[c];
         }
+    }
+}
+
+// ---- a whole module per workgroup -----------------------------------------------------------------------------------
+// Small maps and few channels: a module is then a few microseconds of one CU, no more than a launch takes to get going (the
+// kernel's arguments, the item, its map: three memory latencies, one after the other), and three launches for it would be
+// spent on that (8 programs, fp32, C = 16, 8 x 8, whole pass: 53 -> 34 us).  A workgroup of 8 waves owns an item; the input map and mid live in two LDS tiles with zero borders, a unit of
+// work is MT x 16 pixels x 16 output channels, a wave takes every eighth.  Joins read their arguments' fragments straight
+// from global memory (every element is used once per channel tile) and leave u in the first tile.
+struct NodeArgs {
+    const void* w1; const float* b1;
+    const void* w3a; const float* b3a;
+    const void* w3b; const float* b3b;
+    int32_t count;
+    int32_t keep;                 // u and mid are also written to the maps of the backward pass
+};
+
+template <typename T, int MT, bool FULL>
+__global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* items, NodeArgs nw, ConvArgs a)
+{
+    using First = ConvSteps<T, CV_FIRST, MT, 1, FULL>;
+    using Second = ConvSteps<T, CV_SECOND, MT, 1, FULL>;
+    using Join = ConvSteps<T, CV_JOIN, MT, 1, FULL>;
+    constexpr int ES = int(sizeof(T)), KS = First::KS, PE = First::PE, NTHR = 512, NWAVE = 8;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    // consecutive workgroups go to the chip's 8 dies in turn: every die gets one run of items (they are sorted by function)
+    const int i = int(blockIdx.x & 7) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
+    if (i >= nw.count) return;
+    const dynb_item it = items[i];
+    const bool binary = it.src1 != DYNB_NO_ARG;           // uniform over the workgroup
+    const int C = a.C, H = a.H, W = a.W, P = H * W, cols = W + 2;
+    const size_t chw = size_t(P) * C;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int nj = a.ck / KS, pix_bytes = conv_pixel_bytes(a.ck, ES), row_bytes = cols * pix_bytes, tile_bytes = (H + 2) * row_bytes;
+    const int n_ct = (C + 15) / 16, n_units = n_ct * ((P + MT * 16 - 1) / (MT * 16));
+
+    // unit u: channel tile u % n_ct of pixel tiles u / n_ct * MT ..
+    int n0 = 0, p0 = 0;
+    uint32_t at[MT];                                      // tile offset of this lane's pixel (top left tap), without channels
+    auto unit = [&](int u) {
+        const int pt = u / n_ct;
+        n0 = (u - pt * n_ct) * 16;
+        p0 = pt * MT * 16;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const int p = min(p0 + t * 16 + r, P - 1), y = int(div20_by(p, a.m_sw));
+            at[t] = uint32_t(y * row_bytes + (p - y * W) * pix_bytes);
+        }
+    };
+    const uint32_t centre = uint32_t(row_bytes + pix_bytes);
+    f32x4 acc[MT][1];
+    auto clear = [&]() {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[t][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto prepare = [&](auto& steps, const void* w, uint32_t tile) {
+        steps.panel(steps.weights(w, it.type, C, n0, C, lane), 0, nj, 0);
+        steps.row_bytes = row_bytes;
+        steps.pix_bytes = pix_bytes;
+        steps.s0 = 0;
+        steps.n_steps = nj * 9;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) steps.x_at[t] = tile + at[t] + uint32_t(g * 16);
+        steps.request();
+    };
+    auto bias_of = [&](const float* b) -> f32x4 {
+        return b ? load4<FULL>(b + size_t(it.type) * C + n0 + g * 4, C - n0 - g * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // fn(pixel index, its tile offset, channels o .. o + n - 1 of it): this lane's results of pixel tile t
+    auto results = [&](auto&& fn) {
+        const int o = n0 + g * 4, n = min(4, C - o);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const int p = p0 + t * 16 + r;
+            if (p < P && n > 0) fn(t, p, o, n);
+        }
+    };
+
+    if (wave < n_units) unit(wave);
+    First first;
+    if (!binary && wave < n_units) prepare(first, nw.w3a, 0);
+
+    // ---- both tiles: zeros, and the argument's map in the middle of the first
+    {
+        const T* src = conv_src<T>(a, it.src0, chw);
+        const int np = a.ck * ES / 16, n_map = binary ? 0 : (H + 2) * cols * np;       // 16-byte pieces
+        const uint32_t m_np = recip_of(np), m_cols = recip20_of(cols);
+        constexpr int UN = 4;
+        for (int base = tid; base < n_map; base += NTHR * UN) {
+            u32x4 v[UN];
+            uint32_t to[UN], mask[UN];
+#pragma unroll
+            for (int k = 0; k < UN; ++k) {
+                const int c = base + k * NTHR;
+                const uint32_t pix = div_by(c, m_np), part = c - pix * np, row = div20_by(pix, m_cols), col = pix - row * cols;
+                to[k] = row * row_bytes + col * pix_bytes + part * 16;
+                const int y = int(row) - 1, x = int(col) - 1, ch = int(part) * PE;
+                const bool inside = c < n_map && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W);
+                mask[k] = inside ? ~0u : 0u;
+                v[k] = load_piece<FULL>(src + (inside ? (size_t(y) * W + x) * C + ch : 0), inside ? C - ch : 0);
+            }
+#pragma unroll
+            for (int k = 0; k < UN; ++k)
+                if (base + k * NTHR < n_map) *reinterpret_cast<u32x4*>(__builtin_assume_aligned(lds_raw + to[k], 16)) = v[k] & mask[k];
+            __builtin_amdgcn_s_waitcnt(0x0f70);           // vmcnt(0), see k_conv
+        }
+        for (int c = tid + (binary ? 0 : tile_bytes / 16); c < 2 * tile_bytes / 16; c += NTHR)
+            *reinterpret_cast<u32x4*>(lds_raw + size_t(c) * 16) = u32x4{0u, 0u, 0u, 0u};
+    }
+    __syncthreads();
+
+    if (binary) {
+        // ---- u = ReLU(conv1x1(concat(arguments)) + b1) into the first tile
+        for (int u = wave; u < n_units; u += NWAVE) {
+            unit(u);
+            const f32x4 b = bias_of(nw.b1);
+            Join join;
+            const char* w_tile = join.weights(nw.w1, it.type, C, n0, C, lane);
+            join.s0 = 0;
+            join.n_steps = nj;
+            clear();
+#pragma unroll 1
+            for (int arg = 0; arg < 2; ++arg) {
+                const T* src = conv_src<T>(a, arg ? it.src1 : it.src0, chw);
+                join.panel(w_tile, 0, nj, arg);
+                constexpr int UN = 4;
+#pragma unroll 1
+                for (int j0 = 0; j0 < nj; j0 += UN) {
+                    u32x4 w[UN][1], x[UN][MT];
+#pragma unroll
+                    for (int k = 0; k < UN; ++k) {
+                        const int j = min(j0 + k, nj - 1), c = j * KS + g * PE;
+                        join.load_w(j, w[k]);
+#pragma unroll
+                        for (int t = 0; t < MT; ++t) x[k][t] = load_piece<FULL>(src + size_t(min(p0 + t * 16 + r, P - 1)) * C + c, C - c);
+                    }
+#pragma unroll
+                    for (int k = 0; k < UN; ++k)
+                        if (j0 + k < nj) Join::multiply(acc, w[k], x[k]);
+                }
+            }
+            results([&](int t, int p, int o, int n) {
+                f32x4 v = acc[t][0];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c], 0.f);
+                store4<FULL>(reinterpret_cast<T*>(lds_raw + at[t] + centre) + o, n, v);
+                if (nw.keep) store4<FULL>((T*)a.u + size_t(a.first_kept + i) * chw + size_t(p) * C + o, n, v);
+            });
+        }
+        if (wave < n_units) { unit(wave); prepare(first, nw.w3a, 0); }
+        __syncthreads();
+    }
+
+    // ---- mid = ReLU(conv3x3(first tile) + b3a) into the second tile
+    for (int u = wave; u < n_units; u += NWAVE) {
+        if (u != wave) { unit(u); prepare(first, nw.w3a, 0); }
+        const f32x4 b = bias_of(nw.b3a);
+        clear();
+        first.run(acc);
+        results([&](int t, int p, int o, int n) {
+            f32x4 v = acc[t][0];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c], 0.f);
+            store4<FULL>(reinterpret_cast<T*>(lds_raw + tile_bytes + at[t] + centre) + o, n, v);
+            if (nw.keep) store4<FULL>((T*)a.mid + size_t(a.first_kept + i) * chw + size_t(p) * C + o, n, v);
+        });
+    }
+    Second second;
+    if (wave < n_units) { unit(wave); prepare(second, nw.w3b, uint32_t(tile_bytes)); }
+    __syncthreads();
+
+    // ---- result = ReLU(conv3x3(second tile) + b3b + first tile)
+    T* const dst = conv_dst<T>(a, it.dst, chw);
+    for (int u = wave; u < n_units; u += NWAVE) {
+        if (u != wave) { unit(u); prepare(second, nw.w3b, uint32_t(tile_bytes)); }
+        const f32x4 b = bias_of(nw.b3b);
+        clear();
+        second.run(acc);
+        results([&](int t, int p, int o, int n) {
+            f32x4 v = acc[t][0];
+            const f32x4 res = load4<FULL>(reinterpret_cast<const T*>(lds_raw + at[t] + centre) + o, n);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c] + res[c], 0.f);
+            store4<FULL>(dst + size_t(p) * C + o, n, v);
+        });
     }
 }
 
@@ -475,6 +698,50 @@ int launch_conv(const dynb_item* items, const ConvArgs& a, int count, hipStream_
 {
     constexpr int KS = ConvTraits<MODE>::BWD || sizeof(T) == 4 ? 16 : 32;
     return a.C % KS == 0 ? launch_conv_full<T, MODE, true>(items, a, count, st) : launch_conv_full<T, MODE, false>(items, a, count, st);
+}
+
+// Whole modules by k_node, where that takes one CU no longer than two or three launches of k_conv take to get going (5 us
+// each) and two tiles fit LDS.  A CU's time: its MFMAs, or its weights, of which one CU was seen to take in some 12 bytes a clock
+// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 24 to 32 us against 2 x 5 to 3 x 7).
+template <typename T>
+bool node_shape(const ConvArgs& a)
+{
+    constexpr int ES = int(sizeof(T)), KS = ES == 4 ? 16 : 32, STEP_CLOCKS = ES == 4 ? 128 : 16;
+    const long long steps = (a.C + KS - 1) / KS, P = (long long)a.H * a.W;
+    const long long lds = 2ll * (a.H + 2) * (a.W + 2) * conv_pixel_bytes(int(steps * KS), ES);
+    if (a.W > 64 || P > 2048 || lds > 160 * 1024) return false;
+    const long long mfma = (P + 15) / 16 * ((a.C + 15) / 16) * steps * 9 * 2 * STEP_CLOCKS / 4, weights = 2ll * 9 * a.C * a.C * ES / 12;
+    return std::max(mfma, weights) <= 10000;
+}
+
+template <typename T, int MT, bool FULL>
+int launch_node_tile(const dynb_item* items, const NodeArgs& nw, const ConvArgs& a, hipStream_t st)
+{
+    static std::atomic<uint64_t> attr_set{0};                            // one bit per device
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return DYNB_E_HIP;
+    if (!(attr_set.load() >> (dev & 63) & 1)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_node<T, MT, FULL>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+            return DYNB_E_HIP;
+        attr_set.fetch_or(uint64_t(1) << (dev & 63));
+    }
+    const size_t lds = size_t(2) * (a.H + 2) * (a.W + 2) * conv_pixel_bytes(a.ck, int(sizeof(T)));
+    hipLaunchKernelGGL((k_node<T, MT, FULL>), dim3(unsigned((nw.count + 7) / 8 * 8)), dim3(512), lds, st, items, nw, a);
+    return DYNB_OK;
+}
+
+template <typename T>
+int launch_node(const dynb_item* items, const NodeArgs& nw, ConvArgs a, hipStream_t st)
+{
+    constexpr int KS = sizeof(T) == 4 ? 16 : 32;
+    a.ck = (a.C + KS - 1) / KS * KS;
+    a.m_sw = recip20_of(a.W);
+    const int pt = (a.H * a.W + 15) / 16, ct = (a.C + 15) / 16;
+    // pixel tiles per unit: 4 read the weights a quarter as often, 1 gives all waves work where there are few tiles
+    const bool wide = ((pt + 3) / 4 * ct + 7) / 8 * 4 <= (pt * ct + 7) / 8;
+    const bool full = a.C % KS == 0;
+    if (wide) return full ? launch_node_tile<T, 4, true>(items, nw, a, st) : launch_node_tile<T, 4, false>(items, nw, a, st);
+    return full ? launch_node_tile<T, 1, true>(items, nw, a, st) : launch_node_tile<T, 1, false>(items, nw, a, st);
 }
 
 }  // namespace

@@ -542,10 +542,17 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
     const bool timed = dynb::timing_on(), coarse = dynb::timing_coarse();
     if (timed) dynb::timing_mark(st, dynb::ST_SETUP, 0);
     int32_t evals = 0;
+    const bool whole = node_shape<T>(a);
     for (const dynb_launch& l : p->launches) {
         evals += l.count;
+        if (whole) {
+            a.first_kept = l.start;
+            const NodeArgs nw = {w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b, l.count, p->keep ? 1 : 0};
+            const int rc = launch_node<T>(reinterpret_cast<const dynb_item*>(d) + l.start, nw, a, st);
+            if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a launch group could not be launched");
+        }
         // grid.y is limited to 65535: split very wide launch groups
-        for (int off = 0; off < l.count; off += 32768) {
+        for (int off = 0; !whole && off < l.count; off += 32768) {
             const int count = std::min(32768, l.count - off);
             const dynb_item* items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
             a.first_kept = p->keep ? l.start + off : off;

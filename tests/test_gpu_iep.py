@@ -48,10 +48,11 @@ def test_generic_kernels_on_ragged_shapes(dyn, util, oracle, dtype, C, H, W):
 
 
 @pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 1, 1, 1, 3), ("f32", 17, 1, 65, 3), ("bf16", 31, 33, 2, 3), ("f32", 130, 3, 5, 40),
-                                           ("bf16", 33, 5, 33, 4), ("bf16", 66, 7, 32, 40), ("f32", 260, 6, 30, 2), ("bf16", 16, 9, 7, 200)])
+                                           ("bf16", 33, 5, 33, 4), ("bf16", 66, 7, 32, 40), ("f32", 260, 6, 30, 2), ("bf16", 16, 9, 7, 200),
+                                           ("f32", 16, 2, 64, 3), ("f32", 24, 8, 9, 30), ("bf16", 64, 14, 14, 5), ("bf16", 40, 14, 14, 4)])
 def test_convolution_tiles_at_their_edges(dyn, util, oracle, dtype, C, H, W, B):
     """Remainders of every tile dimension (16 pixels, 16 channels, 16 or 32 summed channels, segments of 32 columns, panels of
-    summed channels) and all workgroup tiles; weights and maps at addresses that only their element type aligns."""
+    summed channels), all workgroup tiles, whole modules per workgroup and a launch per convolution; weights and maps at addresses that only their element type aligns."""
     import torch
     w = iep.small_mixed(seed=C + W, B=B, C=C, H=H, W=W, dtype=dtype, min_len=2, max_len=7)
     ref = oracle.iep_forward_workload(w)
