@@ -103,34 +103,45 @@ __global__ void k_pack_weights(const u32x4* __restrict__ src, u32x4* __restrict_
     }
 }
 
-// HALF selects how a node is spread over workgroups.
-//   whole: one node per workgroup: wave w owns channel tile w (32 channels) and all 7 pixel tiles.
-//   half:  half a node per workgroup: output rows 0..6 or 7..13.  The workgroup convolves an 8-row window (rows
-//          0..7 or 6..13: the second conv needs one row of the first conv's output beyond its own rows), i.e.
-//          4 pixel tiles; wave w owns channel tile w of all four.  Two CUs share a node, which shortens
-//          narrow launch groups at the price of 8/7 of the MFMA work.
-// Both fit 256 registers and half of a CU's LDS, so that two workgroups share a CU where a launch group is wide enough,
+// A node is spread over PARTS workgroups, each with a share of the output rows:
+//   PARTS      output rows      rows of the first conv's window (pixel tiles)    of the second's
+//     1            14                      14 (7)                                    14 (7)
+//     2             7                       8 (4)                                     8 (4)
+//     4             4                       6 (3)                                     4 (2)
+//     7             2                       4 (2)                                     2 (1)
+// (the second conv needs one row of the first conv's output beyond its own rows on either side).  Wave w owns channel
+// tile w of all of them.  More parts shorten narrow launch groups at the price of MFMA work (14, 16, 20, 21 tiles a
+// node) and of reading the weights once per part: one node takes 14.7 us in 2 parts, of which 7.7 are MFMAs.
+// All fit 256 registers and half of a CU's LDS, so that two workgroups share a CU where a launch group is wide enough,
 // and one's staging, swap and epilogue run under the other's MFMAs.  (A whole-node layout of its own for groups of
 // up to one node per CU, with twice the weight ring in 346 registers, was 3 % slower: the accumulators then live in
 // the upper half of the register file, and every other use of them is a copy.)
-// One workgroup's share of a launch group: position `logical` (a node or half a node) of the items a.items[0 .. a.count).
+template <int PARTS> struct PartShape;        // output rows, pixel tiles of the two convs, rows of u, fragments in the weight ring, activation register sets
+template <> struct PartShape<1> { static constexpr int ROWS = 14, MTA = 7, MTB = 7, UROWS = 14, RW = 12, XA = 10, XB = 10; };
+template <> struct PartShape<2> { static constexpr int ROWS = 7, MTA = 4, MTB = 4, UROWS = 9, RW = 12, XA = 12, XB = 12; };
+template <> struct PartShape<4> { static constexpr int ROWS = 4, MTA = 3, MTB = 2, UROWS = 8, RW = 24, XA = 8, XB = 8; };
+template <> struct PartShape<7> { static constexpr int ROWS = 2, MTA = 2, MTB = 1, UROWS = 6, RW = 24, XA = 8, XB = 8; };
+// One workgroup's share of a launch group: position `logical` (a node, or a part of one) of the items a.items[0 .. a.count).
 // KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m.
-template <bool HALF, bool KEEP = false>
+template <int PARTS, bool KEEP = false>
 __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 {
     using namespace mf;
-    constexpr int MTW = HALF ? 4 : MT7;       // pixel tiles per wave: all of the node's (or of the half node's window)
+    using Shape = PartShape<PARTS>;
+    constexpr bool WHOLE = PARTS == 1;
+    constexpr int MTA = Shape::MTA, MTB = Shape::MTB, UROWS = Shape::UROWS;
+    constexpr int MTU = WHOLE ? MT7 : (UROWS * S + 31) / 32;     // tiles of the join: row pairs, or 32 consecutive pixels
     constexpr int NTHR = 256;
-    constexpr int RW = 12;                    // weight ring in fragments
-    constexpr int XW = HALF ? 12 : 10;        // register sets of activation fragments
+    constexpr int RW = Shape::RW;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
-    const int node = HALF ? (logical >> 1) : logical;
+    const int node = logical / PARTS, part = logical % PARTS;
     if (node >= a.count) return;
-    // pixel window of this workgroup: image rows [wrow0, wrow0 + wrows); output rows [orow0, orow1)
-    const int wrow0 = HALF ? (logical & 1) * 6 : 0;
-    constexpr int wrows = HALF ? 8 : S;
-    const int orow0 = HALF ? (logical & 1) * 7 : 0, orow1 = HALF ? orow0 + 7 : S;
+    // image rows: output [orow0, orow1), windows of the convs [row_a, row_a + 2 MTA) and [row_b, row_b + 2 MTB), u
+    // [urow0, urow0 + UROWS), every one of them moved inside the map
+    const int orow0 = part * Shape::ROWS, orow1 = min(orow0 + Shape::ROWS, S);
+    const int row_a = min(max(orow0 - 1, 0), S - 2 * MTA), row_b = min(orow0, S - 2 * MTB);
+    const int urow0 = min(max(row_a - 1, 0), S - UROWS);
 
     PHASE(0);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -147,12 +158,9 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 
     // ---- gather: zero border once, then the argument map into the centre of the halo tile;
     // all global loads of the map are issued before the first LDS write, so one memory latency is paid
-    // rows of the argument map that the window's 3x3 taps can touch
-    const int srow0 = wrow0 > 0 ? wrow0 - 1 : 0;
-    const int srow1 = wrow0 + wrows + 1 < S ? wrow0 + wrows + 1 : S;
-    constexpr int MAXPIECES = (HALF ? 9 : S) * S * 16;
-    constexpr int NIT = (MAXPIECES + NTHR - 1) / NTHR;
-    const int c_lo = srow0 * S * 16, c_hi = srow1 * S * 16;
+    // (the rows of u are those that the first conv's taps can touch)
+    constexpr int NIT = (UROWS * S * 16 + NTHR - 1) / NTHR;
+    const int c_lo = urow0 * S * 16, c_hi = c_lo + UROWS * S * 16;
     u32x4 tmp[NIT];
     auto stage_load = [&](const bf16_t* src) {
         const u32x4* s4 = reinterpret_cast<const u32x4*>(src);
@@ -175,7 +183,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     };
     // the centre of the halo tile -> a map, this workgroup's output rows, in coalesced 16-byte pieces
     auto copy_out = [&](bf16_t* dst) {
-        constexpr int OUTPIECES = (HALF ? 7 : S) * S * 16;
+        constexpr int OUTPIECES = Shape::ROWS * S * 16;
 #pragma unroll
         for (int i = 0; i < (OUTPIECES + NTHR - 1) / NTHR; ++i) {
             const int c = orow0 * S * 16 + tid + i * NTHR;
@@ -205,39 +213,36 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     if (tid < C) *reinterpret_cast<float*>(lds_raw + BIAS_OFF + (2 * C + tid) * 4) = bias_reg[1];
     stage_store();
 
-    // this lane's LDS address for the window's first row pair; the pixel it ends up with in tile t is column px of
-    // window row 2 t + py (columns 14 and 15 are padding)
-    const uint32_t x0 = pair_lane_addr(lane) + uint32_t(wrow0 * ROW_BYTES);
-    const int px = r & 15, py = r >> 4;
-    const bool real = px < S;
+    // this lane's LDS address for the first row pair of the convs' windows; the pixel it ends up with in tile t is column
+    // r & 15 of window row 2 t + r / 16 (columns 14 and 15 are padding)
+    const uint32_t x_a = pair_lane_addr(lane) + uint32_t(row_a * ROW_BYTES), x_b = pair_lane_addr(lane) + uint32_t(row_b * ROW_BYTES);
+    const bool real = (r & 15) < S;
     // its 16 accumulator elements are channels chan .. chan + 15 (the packed weights carry the matching row permutation)
     const int chan = n0 + 16 * h;
-    f32x16 acc[MTW];
 
     auto bias4 = [&](int which, int b) {      // channels chan + 4 b .. + 3 of b3a (0), b3b (1), b1 (2)
         return *reinterpret_cast<const f32x4*>(lds_raw + BIAS_OFF + uint32_t((which * C + chan + b * 4) * 4));
     };
-    auto init_bias = [&](int which) {
+    auto init_bias = [&](auto& acc, int which) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const f32x4 v = bias4(which, b);
 #pragma unroll
-            for (int t = 0; t < MTW; ++t) {
-                acc[t][4 * b + 0] = v.x; acc[t][4 * b + 1] = v.y;
-                acc[t][4 * b + 2] = v.z; acc[t][4 * b + 3] = v.w;
+            for (auto& t : acc) {
+                t[4 * b + 0] = v.x; t[4 * b + 1] = v.y;
+                t[4 * b + 2] = v.z; t[4 * b + 3] = v.w;
             }
         }
     };
-    // byte address of this lane's centre pixel of tile t, its first channel
-    const uint32_t c0 = x0 - uint32_t(h * 128) + uint32_t(CENTER + chan * 2);
-    auto centre = [&](int t) -> uint32_t { return c0 + uint32_t(2 * t * ROW_BYTES); };
-    // ReLU(acc[t][8q .. 8q+7]) as 8 packed bf16 (q = 0, 1)
-    auto packed = [&](int t, int q) -> u32x4 {
+    // byte address of this lane's centre pixel of tile t of a window, its first channel
+    auto centre = [&](uint32_t x, int t) -> uint32_t { return x - uint32_t(h * 128) + uint32_t(CENTER + chan * 2 + 2 * t * ROW_BYTES); };
+    // ReLU(acc[8q .. 8q+7]) as 8 packed bf16 (q = 0, 1)
+    auto packed = [&](const f32x16& acc, int q) -> u32x4 {
         u32x4 pk;
-        pk.x = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 0], acc[t][8 * q + 1]));
-        pk.y = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 2], acc[t][8 * q + 3]));
-        pk.z = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 4], acc[t][8 * q + 5]));
-        pk.w = relu_bf16x2(pack_bf16x2(acc[t][8 * q + 6], acc[t][8 * q + 7]));
+        pk.x = relu_bf16x2(pack_bf16x2(acc[8 * q + 0], acc[8 * q + 1]));
+        pk.y = relu_bf16x2(pack_bf16x2(acc[8 * q + 2], acc[8 * q + 3]));
+        pk.z = relu_bf16x2(pack_bf16x2(acc[8 * q + 4], acc[8 * q + 5]));
+        pk.w = relu_bf16x2(pack_bf16x2(acc[8 * q + 6], acc[8 * q + 7]));
         return pk;
     };
 
@@ -246,20 +251,22 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     PHASE(2);
 
     // ---- binary functions: u = ReLU(conv1x1(concat(arg0, arg1)) + b1), built in the same tile.
-    // The first conv3x3 reads u one row beyond the window, so in half-node mode the 1x1 runs on its
-    // own 9-row window (rows 0..8 or 5..13: 126 pixels, in tiles of 32 consecutive ones that is still 4 tiles).
+    // The first conv3x3 reads u one row beyond its window, so in parts of a node the 1x1 runs on its own window of
+    // UROWS rows, in tiles of 32 consecutive pixels.
+    f32x16 acc_a[MTA];
     if (binary) {
-        const int urow0 = wrow0 > 0 ? wrow0 - 1 : 0;
-        constexpr int UPIX = HALF ? 9 * S : P;
-        uint32_t ua[HALF ? MTW : 1];
-        if constexpr (HALF) {
+        constexpr int UPIX = UROWS * S;
+        f32x16 acc_u[WHOLE ? 1 : MTU];                   // (whole nodes: the registers of acc_a)
+        auto& acc = [&]() -> auto& { if constexpr (WHOLE) return acc_a; else return acc_u; }();
+        uint32_t ua[WHOLE ? 1 : MTU];
+        if constexpr (!WHOLE) {
 #pragma unroll
-            for (int t = 0; t < MTW; ++t) {
+            for (int t = 0; t < MTU; ++t) {
                 const int p = urow0 * S + min(t * 32 + r, UPIX - 1);
                 ua[t] = uint32_t(CENTER + (p / S) * ROW_BYTES + (p % S) * PIX_BYTES + h * 128);
             }
-        } else ua[0] = x0 + uint32_t(CENTER);
-        auto uaddr = [&](int t) { return HALF ? ua[HALF ? t : 0] : ua[0] + uint32_t(2 * t * ROW_BYTES); };
+        } else ua[0] = x_a + uint32_t(CENTER);
+        auto uaddr = [&](int t) { return WHOLE ? ua[0] + uint32_t(2 * t * ROW_BYTES) : ua[WHOLE ? 0 : t]; };
         // the first half of the 1x1 weights (argument 0), then the second: its fragments are fetched under the first
         // half's loop and wait while the second argument is staged
         const bf16_t* w1row = a.w1 + (size_t(it.type) * 4 + wave) * 16 * FRAG + lane * 8;
@@ -268,20 +275,20 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
         for (int j = 0; j < 8; ++j) w1f[j] = *reinterpret_cast<const bf16x8*>(w1row + j * FRAG);
         stage_load(arg_map(it.src1));                     // arrives under the first half's loop
         __builtin_amdgcn_sched_barrier(0);
-        init_bias(2);
-        kloop1<MTW, true>(acc, uaddr, w1f, w1row + 8 * FRAG);
+        init_bias(acc, 2);
+        kloop1<MTU, true>(acc, uaddr, w1f, w1row + 8 * FRAG);
         __syncthreads();
         stage_store();
         __syncthreads();
-        kloop1<MTW, false>(acc, uaddr, w1f, nullptr);
+        kloop1<MTU, false>(acc, uaddr, w1f, nullptr);
         ring_fill<RW>(ring, wrow_a);                      // (only now: the loops above need the registers)
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < MTW; ++t)                     // ReLU(acc) -> bf16 -> centre of the halo tile (in place)
-            if (HALF ? t * 32 + r < UPIX : real) {
+        for (int t = 0; t < MTU; ++t)                     // ReLU(acc) -> bf16 -> centre of the halo tile (in place)
+            if (WHOLE ? real : t * 32 + r < UPIX) {
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    const u32x4 pk = packed(t, q);
+                    const u32x4 pk = packed(acc[t], q);
                     *reinterpret_cast<u32x4*>(lds_raw + uaddr(t) - uint32_t(h * 128) + uint32_t((chan + q * 8) * 2)) = pk;
                 }
             }
@@ -291,31 +298,46 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 
     // ---- first conv3x3 + ReLU, result replaces the tile; the old centre values become the residual
     PHASE(3);
-    init_bias(0);
-    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_a, wrow_b);       // leaves the ring filled for the second conv
+    init_bias(acc_a, 0);
+    kloop3<MTA, RW, Shape::XA>(acc_a, x_a, ring, wrow_a, wrow_b);       // leaves the ring filled for the second conv
     PHASE(4);
     __syncthreads();
     PHASE(5);
+    // (one window for both convs: the second accumulates in the registers of the first)
+    constexpr bool SAME = MTA == MTB;
+    f32x16 acc_own[SAME ? 1 : MTB];
+    auto& acc_b = [&]() -> auto& { if constexpr (SAME) return acc_a; else return acc_own; }();
     if (real) {
-        // acc[t][8q .. 8q+7]: ReLU'd bf16 into the tile, old centre values + bias back into acc
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        // ReLU(acc_a) into the tile, old centre values + bias into acc_b.  A wave reads and writes its own channels only, and
+        // its reads come first: where the windows are the same, piece by piece, else all of them
+        auto old = [&](int t, int q) { return *reinterpret_cast<const u32x4*>(lds_raw + centre(x_b, t) + uint32_t(q * 16)); };
+        auto residual = [&](int t, int q, const u32x4& res) {
             const f32x4 blo = bias4(1, 2 * q), bhi = bias4(1, 2 * q + 1);
+            f32x16& acc = acc_b[t];
+            acc[8 * q + 0] = __uint_as_float(res.x << 16) + blo.x;
+            acc[8 * q + 1] = __uint_as_float(res.x & 0xffff0000u) + blo.y;
+            acc[8 * q + 2] = __uint_as_float(res.y << 16) + blo.z;
+            acc[8 * q + 3] = __uint_as_float(res.y & 0xffff0000u) + blo.w;
+            acc[8 * q + 4] = __uint_as_float(res.z << 16) + bhi.x;
+            acc[8 * q + 5] = __uint_as_float(res.z & 0xffff0000u) + bhi.y;
+            acc[8 * q + 6] = __uint_as_float(res.w << 16) + bhi.z;
+            acc[8 * q + 7] = __uint_as_float(res.w & 0xffff0000u) + bhi.w;
+        };
+        auto replace = [&](int t, int q) { *reinterpret_cast<u32x4*>(lds_raw + centre(x_a, t) + uint32_t(q * 16)) = packed(acc_a[t], q); };
+        if constexpr (SAME) {
 #pragma unroll
-            for (int t = 0; t < MTW; ++t) {
-                u32x4* at = reinterpret_cast<u32x4*>(lds_raw + centre(t) + uint32_t(q * 16));
-                const u32x4 res = *at;
-                const u32x4 pk = packed(t, q);
-                *at = pk;
-                acc[t][8 * q + 0] = __uint_as_float(res.x << 16) + blo.x;
-                acc[t][8 * q + 1] = __uint_as_float(res.x & 0xffff0000u) + blo.y;
-                acc[t][8 * q + 2] = __uint_as_float(res.y << 16) + blo.z;
-                acc[t][8 * q + 3] = __uint_as_float(res.y & 0xffff0000u) + blo.w;
-                acc[t][8 * q + 4] = __uint_as_float(res.z << 16) + bhi.x;
-                acc[t][8 * q + 5] = __uint_as_float(res.z & 0xffff0000u) + bhi.y;
-                acc[t][8 * q + 6] = __uint_as_float(res.w << 16) + bhi.z;
-                acc[t][8 * q + 7] = __uint_as_float(res.w & 0xffff0000u) + bhi.w;
-            }
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int t = 0; t < MTA; ++t) {
+                    const u32x4 res = old(t, q);
+                    replace(t, q);
+                    residual(t, q, res);
+                }
+        } else {
+#pragma unroll
+            for (int t = 0; t < MTB; ++t) { residual(t, 0, old(t, 0)); residual(t, 1, old(t, 1)); }
+#pragma unroll
+            for (int t = 0; t < MTA; ++t) { replace(t, 0); replace(t, 1); }
         }
     }
     PHASE(6);
@@ -327,28 +349,28 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     // ---- second conv3x3 on top of (residual + bias), ReLU, scatter.  The result leaves through the tile: in the
     // accumulators a lane holds 32 bytes of a pixel, and stores in which every lane touches a line of its own take 4.4k
     // clocks of a whole-node workgroup's 53k, the way through LDS with coalesced stores 3.6k.
-    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_b, wrow_b);
+    kloop3<MTB, RW, Shape::XB, false>(acc_b, x_b, ring, wrow_b, wrow_b);
     PHASE(8);
     __syncthreads();
     if (real) {
 #pragma unroll
-        for (int t = 0; t < MTW; ++t)
+        for (int t = 0; t < MTB; ++t)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(lds_raw + centre(t) + uint32_t(q * 16)) = packed(t, q);
+            for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(lds_raw + centre(x_b, t) + uint32_t(q * 16)) = packed(acc_b[t], q);
     }
     __syncthreads();
     copy_out(it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C));
     PHASE(9);
 }
 
-template <bool HALF, bool KEEP = false>
+template <int PARTS, bool KEEP = false>
 __global__ __launch_bounds__(256, 2) void k_module_mfma(MfArgs a)
 {
     // Workgroup -> position in the launch group.  Consecutive workgroup ids land on different
     // XCDs; give every XCD one contiguous run of items (items are sorted by function id) so that
     // a function's weights stay in as few L2s as possible.
     const int per_xcd = gridDim.x >> 3;
-    module_body<HALF, KEEP>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    module_body<PARTS, KEEP>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
 }
 
 // ---- one dependency-driven launch per batch ---------------------------------------------------------
@@ -416,8 +438,8 @@ __global__ __launch_bounds__(256, 1) void k_module_persist(MfArgs a, PersistArgs
         b.items = items + (t >> 2);
         b.count = 1;
         const int part = t & 3;
-        if (part == 0) module_body<false>(b, 0);
-        else module_body<true>(b, part - 1);
+        if (part == 0) module_body<1>(b, 0);
+        else module_body<2>(b, part - 1);
         // Publish: every wave waits until its stores of the result have reached the L2 (all waves of a
         // workgroup sit behind the same one), then one thread writes that L2's dirty lines back to memory,
         // where every CU can see them, and raises the flag (the agent-scope release does both).
@@ -596,9 +618,11 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         int cus = 0;
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "hipDeviceGetAttribute");
         cu_count[dev & 63] = cus > 0 ? cus : 256;
-        for (const void* f : {reinterpret_cast<const void*>(k_module_persist), reinterpret_cast<const void*>(k_module_mfma<false>),
-                              reinterpret_cast<const void*>(k_module_mfma<true>), reinterpret_cast<const void*>(k_module_mfma<false, true>),
-                              reinterpret_cast<const void*>(k_module_mfma<true, true>)})
+        for (const void* f : {reinterpret_cast<const void*>(k_module_persist),
+                              reinterpret_cast<const void*>(k_module_mfma<1, false>), reinterpret_cast<const void*>(k_module_mfma<1, true>),
+                              reinterpret_cast<const void*>(k_module_mfma<2, false>), reinterpret_cast<const void*>(k_module_mfma<2, true>),
+                              reinterpret_cast<const void*>(k_module_mfma<4, false>), reinterpret_cast<const void*>(k_module_mfma<4, true>),
+                              reinterpret_cast<const void*>(k_module_mfma<7, false>), reinterpret_cast<const void*>(k_module_mfma<7, true>)})
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, mf::LDS_BYTES), "hipFuncSetAttribute(module kernels)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
@@ -659,14 +683,14 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         a.items = reinterpret_cast<const dynb_item*>(d) + l.start;
         a.first_item = l.start;
         a.count = l.count;
-        // half a node per workgroup while that still fits the chip's 256 CUs in one round; beyond that, and whenever
-        // several batches are in flight (their narrow groups share the chip), one node per workgroup
-        bool half = !p->throughput && l.count <= 128;
-#ifdef DYNB_PHASE_CLOCKS
-        if (const char* f = getenv("DYNB_FORCE_HALF")) half = atoi(f) != 0;
-#endif
-        const unsigned grid = unsigned(((half ? 2 * l.count : l.count) + 7) / 8 * 8);
-        auto* kernel = half ? (p->keep ? k_module_mfma<true, true> : k_module_mfma<true>) : (p->keep ? k_module_mfma<false, true> : k_module_mfma<false>);
+        // as many parts per node as still fit the chip's 256 CUs in one round; beyond that, and whenever several batches are in
+        // flight (their narrow groups share the chip), one node per workgroup
+        const int parts = p->throughput || l.count > 128 ? 1 : l.count > 64 ? 2 : l.count > 36 ? 4 : 7;
+        const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
+        auto* kernel = parts == 7   ? (p->keep ? k_module_mfma<7, true> : k_module_mfma<7>)
+                       : parts == 4 ? (p->keep ? k_module_mfma<4, true> : k_module_mfma<4>)
+                       : parts == 2 ? (p->keep ? k_module_mfma<2, true> : k_module_mfma<2>)
+                                    : (p->keep ? k_module_mfma<1, true> : k_module_mfma<1>);
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), mf::LDS_BYTES, st, a);
         if (timed && !coarse) dynb::timing_mark(st, int32_t(&l - p->launches.data()), l.count);
     }

@@ -106,8 +106,9 @@ __device__ __forceinline__ void zero_border_piece(int c)
 //     behind the MFMAs that still read the slot would stall the wave);
 //   * scheduler fences keep that order (the compiler would otherwise sink every load to its use).
 // The ring is filled by ring_fill, a call of its own so that the caller can issue it long before the loop; the
-// last chunk refills the ring with the first fragments of the NEXT loop (wnext), which then starts full.
-// Consecutive MFMAs never use the same accumulator.
+// last chunk refills the ring with the first fragments of the NEXT loop (wnext), which then starts full (NEXT = false: there
+// is none, and the requests, which cannot be left out without losing count of the others, are for one fragment).
+// Consecutive MFMAs never use the same accumulator (but for MTW = 1, which has one).
 template <int RW>
 __device__ __forceinline__ void ring_fill(bf16x8 (&wf)[RW], const bf16_t* wrow)
 {
@@ -118,7 +119,7 @@ __device__ __forceinline__ void ring_fill(bf16x8 (&wf)[RW], const bf16_t* wrow)
     }
 }
 
-template <int MTW, int RW, int XW>
+template <int MTW, int RW, int XW, bool NEXT = true>
 __device__ __forceinline__ void kloop3(f32x16 (&acc)[MTW], const uint32_t x0, bf16x8 (&wf)[RW], const bf16_t* wrow, const bf16_t* wnext)
 {
     constexpr int NF = 2 * MTW + 1, STEPS = RW / 3, NCHUNK = 24 / STEPS, G = STEPS * NF;
@@ -144,6 +145,7 @@ __device__ __forceinline__ void kloop3(f32x16 (&acc)[MTW], const uint32_t x0, bf
         const uint32_t xa = x0 + chunk_base(c), xn = x0 + chunk_base(last ? c : c + 1);   // after the last chunk: re-read valid data
         const bf16_t* cur = wrow + (c * RW + RW - 3) * mf::FRAG;        // the last step of this chunk
         const bf16_t* nxt = last ? wnext : wrow + (c + 1) * RW * mf::FRAG;   // the next chunk / the next loop
+        const int nfrag = !NEXT && last ? 0 : mf::FRAG;                      // (no next loop: one fragment again and again)
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
 #pragma unroll
@@ -158,8 +160,9 @@ __device__ __forceinline__ void kloop3(f32x16 (&acc)[MTW], const uint32_t x0, bf
                     if (t < MTW) mul(t, 0);            // tap row 0
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if (k >= 1 && k <= 3) {                // refill the slots of the previous step
-                    wf[(st * 3 + k + RW - 4) % RW] = *reinterpret_cast<const bf16x8*>(st == 0 ? cur + (k - 1) * mf::FRAG : nxt + ((st - 1) * 3 + k - 1) * mf::FRAG);
+                constexpr int K0 = NF > 3 ? 1 : 0;
+                if (k >= K0 && k < K0 + 3) {           // refill the slots of the previous step
+                    wf[(st * 3 + k - K0 + RW - 3) % RW] = *reinterpret_cast<const bf16x8*>(st == 0 ? cur + (k - K0) * mf::FRAG : nxt + ((st - 1) * 3 + k - K0) * nfrag);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
