@@ -136,6 +136,56 @@ __global__ __launch_bounds__(256) void k_gate(const bf16_t* __restrict__ x, cons
     }
 }
 
+// The same product for a few tokens: a workgroup owns 16 tokens x 16 experts, both matrices, and its four waves split the
+// sum, so that a handful of tokens still gives a workgroup to many CUs and every wave has all it needs in flight at once
+// (37 tokens, d = 512, 256 experts: 4 workgroups of k_gate and 8 K-chunks one after the other, 7.4 us, against 48
+// workgroups that wait for memory once).  Fragments come straight from global memory.
+constexpr int GS_UN = 4;               // K-steps of 32 requested together
+
+__global__ __launch_bounds__(256) void k_gate_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg,
+                                                    const bf16_t* __restrict__ Wn, const float* __restrict__ noise,
+                                                    float* __restrict__ logits, int T, int d, int E)
+{
+    __shared__ f32x4 part[4][2][64];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int t0 = blockIdx.y * 16, e0 = blockIdx.x * 16;
+    const bf16_t* const px = x + size_t(min(t0 + r, T - 1)) * d;
+    const bf16_t* const pg = Wg + size_t(min(e0 + r, E - 1)) * d;
+    const bf16_t* const pn = (noise ? Wn : Wg) + size_t(min(e0 + r, E - 1)) * d;
+    const int S = (d + 31) / 32, s1 = S * (wave + 1) / 4;
+    f32x4 ag = {0.f, 0.f, 0.f, 0.f}, an = {0.f, 0.f, 0.f, 0.f};
+    for (int s = S * wave / 4; s < s1; s += GS_UN) {
+        u32x4 vx[GS_UN], vg[GS_UN], vn[GS_UN];
+#pragma unroll
+        for (int u = 0; u < GS_UN; ++u) {
+            const int k = (s + u) * 32 + g * 8;
+            const bool in = s + u < s1 && k < d;              // d is a multiple of 8; outside: anything, replaced by zeros
+            const int at = in ? k : 0;
+            const uint32_t m = in ? ~0u : 0u;
+            vx[u] = *reinterpret_cast<const u32x4*>(px + at) & m;
+            vg[u] = *reinterpret_cast<const u32x4*>(pg + at) & m;
+            if (noise) vn[u] = *reinterpret_cast<const u32x4*>(pn + at) & m;
+        }
+#pragma unroll
+        for (int u = 0; u < GS_UN; ++u) {
+            const bf16x8 fx = __builtin_bit_cast(bf16x8, vx[u]);
+            ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx, __builtin_bit_cast(bf16x8, vg[u]), ag, 0, 0, 0);
+            if (noise) an = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx, __builtin_bit_cast(bf16x8, vn[u]), an, 0, 0, 0);
+        }
+    }
+    part[wave][0][lane] = ag;
+    part[wave][1][lane] = an;
+    __syncthreads();
+    // thread: expert e0 + r, token t0 + 4 g + wave (element `wave` of the lane's accumulators)
+    const int e = e0 + r, t = t0 + 4 * g + wave;
+    if (e >= E || t >= T) return;
+    float v = 0.f, z = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { v += part[w][0][lane][wave]; z += part[w][1][lane][wave]; }
+    if (noise) v += noise[size_t(t) * E + e] * softplus_f(z);
+    logits[size_t(t) * E + e] = v;
+}
+
 // The same product for wide gates: a workgroup owns a CU and a tile of 256 tokens x 128 experts, both gate matrices
 // at once.  A 64 x 64 tile takes in 24 KB per K-chunk for 8 MFMAs per wave (96 B per MFMA clock), three times what
 // a CU receives from L2; this tile takes in 64 KB for 64 MFMAs per wave (32 B per MFMA clock).  Operands go through LDS in K-chunks of 64, double buffered, one barrier per chunk.  A wave owns 128
@@ -571,6 +621,84 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_place(const int32_t* __restrict_
     inv[a] = pos;
 }
 
+// The whole grouping of at most SMALL_USES uses in one workgroup, where the five kernels above are five launches with next to
+// nothing to do (18 us for 74 uses): counts and places of the experts in LDS; every wave ranks its 64 uses among
+// themselves, then the waves add theirs to the counts in turn.  `tiles` (if not null): the row tiles of the expert layers, {expert, first row, rows, 0} each, rows = 0 from the
+// last one on to max_tiles, so that a workgroup of those layers finds its tile with one load.
+constexpr int SMALL_USES = 1024, SMALL_EXPERTS = 4096;
+struct alignas(16) RowTile { int32_t expert, row0, rows, pad; };
+
+__global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict__ idx, int32_t* __restrict__ counts,
+                                                      int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
+                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                      RowTile* __restrict__ tiles, int max_tiles, int A, int E)
+{
+    __shared__ int32_t first[SMALL_EXPERTS];              // counts, then the experts' first places
+    __shared__ int32_t wsum[16], wtsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int my = tid < A ? idx[tid] : -1;
+    for (int e = tid; e < E; e += 1024) first[e] = 0;
+    int local = 0, same = 0;                              // uses of this expert in earlier lanes, in the whole wave
+#pragma unroll 16
+    for (int j = 0; j < 64; ++j) {
+        const bool m = __builtin_amdgcn_readlane(my, j) == my;
+        same += m;
+        local += m && j < lane;
+    }
+    __syncthreads();
+    int before = 0;                                       // earlier uses of this expert
+    for (int w = 0; w < (A + 63) / 64; ++w) {
+        if (wave == w && my >= 0) {
+            before = first[my] + local;
+            if (local == same - 1) first[my] = before + 1;          // (behind the wave's reads: its LDS accesses are executed in order)
+        }
+        __syncthreads();
+    }
+    int carry = 0, tcarry = 0;
+    for (int e0 = 0; e0 < E; e0 += 1024) {                // as k_offsets
+        const int e = e0 + tid;
+        const int c = e < E ? first[e] : 0;
+        const int tl = (c + TM - 1) / TM;
+        int inc = c, tinc = tl;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            const int to = __shfl_up(tinc, off);
+            if (lane >= off) { inc += o; tinc += to; }
+        }
+        if (lane == 63) { wsum[wave] = inc; wtsum[wave] = tinc; }
+        __syncthreads();
+        int b = 0, tb = 0, all = 0, tall = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int s = wsum[w], t = wtsum[w];
+            if (w < wave) { b += s; tb += t; }
+            all += s;
+            tall += t;
+        }
+        if (e < E) {
+            const int at = carry + b + inc - c, tat = tcarry + tb + tinc - tl;
+            counts[e] = c;
+            offsets[e] = at;
+            tile_start[e] = tat;
+            first[e] = at;
+            if (tiles)
+                for (int t = 0; t < tl; ++t) tiles[tat + t] = RowTile{e, at + t * TM, min(TM, c - t * TM), 0};
+        }
+        carry += all;
+        tcarry += tall;
+        __syncthreads();
+    }
+    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
+    if (tiles)
+        for (int t = tcarry + tid; t < max_tiles; t += 1024) tiles[t] = RowTile{0, 0, 0, 0};
+    if (my >= 0) {
+        const int pos = first[my] + before;
+        perm[pos] = tid;
+        inv[tid] = pos;
+    }
+}
+
 // ------------------------------------------------------------------------------------------ permute / combine
 // xs[inv[t*k + j]] = x[t] for j < k: one wave per token reads the row once and scatters it to the
 // token's k places in the expert-sorted order (reading by sorted position instead would fetch every
@@ -838,6 +966,96 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__
     else gemm_tile<RELU, 4>(in, We, out, row0, rows, nb, N, K, Ws, Xs, gather, kdiv);
 }
 
+// The expert layers for few rows per expert.  There a layer is a stream of weights, each multiplied with a handful of rows: what
+// counts is how much of it is in flight.  k_grouped_gemm asks for one K-chunk at a time and for 256 features per workgroup;
+// with some 40 live experts that is 160 workgroups with 40 KB in flight each, 31 to 39 us for 38 MB.  Here a workgroup
+// owns 64 features of a row tile, a wave 16 of them, and weights go straight from memory into registers, SK_RD K-steps (1 KB
+// each) ahead; two consecutive steps read one 128-byte line per row.  The rows pass through LDS, 32 KB of them at a time: four
+// waves that read their fragments from global memory are answered at 16 bytes per clock (neighbouring lanes hold different
+// rows), which alone took 8 us.
+// Same MFMAs in the same order as the tiles of up to 32 rows there.
+constexpr int SK_RD = 16;
+constexpr int SK_LDS = 33 * 1024;                              // 16 ML rows of 1024 / ML channels and 16 bytes
+
+template <bool RELU, int ML>
+__device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ in, const bf16_t* __restrict__ We, bf16_t* __restrict__ out,
+                                            const RowTile tile, int n0, int N, int K, const int32_t* __restrict__ gather, int kdiv,
+                                            unsigned char* lds)
+{
+    constexpr int RD = SK_RD, KB = 1024 / ML, SB = KB / 32, PITCH = KB * 2 + 16, PIECES = KB / 8, NP = 16 * ML * PIECES / 256;
+    static_assert(16 * ML * PITCH <= SK_LDS && SB % 8 == 0, "LDS block");
+    constexpr int U = SB < RD ? SB : RD;                       // steps per trip: a divisor of a block's
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const bf16_t* const pw = We + size_t(min(n0 + r, N - 1)) * K;
+    const int S = (K + 31) / 32, last = S - 1;
+    u32x4 w[U];
+    // past the end the last step again; behind K (a multiple of 8) anything, replaced by zeros
+    auto fetch = [&](int s, u32x4& v) {
+        const int k = min(s, last) * 32 + g * 8;
+        v = *reinterpret_cast<const u32x4*>(pw + (k < K ? k : 0)) & (k < K ? ~0u : 0u);
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) fetch(u, w[u]);
+    f32x4 acc[ML];
+#pragma unroll
+    for (int m = 0; m < ML; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < S; b += SB) {                          // a block of channels
+        if (b > 0) __syncthreads();
+        u32x4 v[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int c = tid + i * 256, row = tile.row0 + min(c / PIECES, tile.rows - 1), k = b * 32 + c % PIECES * 8;
+            v[i] = *reinterpret_cast<const u32x4*>(in + size_t(gather ? gather[row] / kdiv : row) * K + (k < K ? k : 0)) & (k < K ? ~0u : 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int c = tid + i * 256;
+            *reinterpret_cast<u32x4*>(__builtin_assume_aligned(lds + c / PIECES * PITCH + c % PIECES * 16, 16)) = v[i];
+        }
+        __syncthreads();
+        for (int s = b; s < min(S, b + SB); s += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s + u < S) {
+#pragma unroll
+                    for (int m = 0; m < ML; ++m) {
+                        const u32x4 x = *reinterpret_cast<const u32x4*>(lds + (m * 16 + r) * PITCH + (s + u - b) * 64 + g * 16);
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[u]), __builtin_bit_cast(bf16x8, x), acc[m], 0, 0, 0);
+                    }
+                }
+                fetch(s + u + U, w[u]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    // lane: features n0 + 4 g .. + 3 of rows 16 m + r
+    const int n = n0 + g * 4;
+#pragma unroll
+    for (int m = 0; m < ML; ++m) {
+        const int row = m * 16 + r;
+        if (row >= tile.rows || n >= N) continue;
+        u32x2 pk = {pack_bf16x2(acc[m].x, acc[m].y), pack_bf16x2(acc[m].z, acc[m].w)};
+        if (RELU) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }
+        *reinterpret_cast<u32x2*>(out + size_t(tile.row0 + row) * N + n) = pk;
+    }
+}
+
+template <bool RELU>
+__global__ __launch_bounds__(256, 3) void k_grouped_skinny(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
+                                                        const RowTile* __restrict__ tiles, int N, int K, int n_tiles_n,
+                                                        const int32_t* __restrict__ gather, int kdiv)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char lds[SK_LDS];
+    const int m = blockIdx.x / n_tiles_n;
+    const RowTile tile = tiles[m];
+    const int n0 = (int(blockIdx.x) - m * n_tiles_n) * 64 + int(threadIdx.x >> 6) * 16;      // (a wave may have no features; it stages)
+    if (tile.rows == 0) return;
+    const bf16_t* We = W + size_t(tile.expert) * N * K;
+    if (tile.rows <= 16) skinny_tile<RELU, 1>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
+    else if (tile.rows <= 32) skinny_tile<RELU, 2>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
+    else skinny_tile<RELU, 4>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
+}
+
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct Layout {
@@ -962,7 +1180,11 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             hipLaunchKernelGGL((k_gate_big<false>), grid, dim3(256), GB_LDS_BYTES, st, xb, static_cast<const bf16_t*>(Wg),
                                static_cast<const bf16_t*>(Wn), noise, logits, T_big, d, E, ntt, net, per_die);
     }
-    if (T > T_big)
+    // fewer 64 x 64 tiles than half the chip has CUs: the kernel with the small tiles
+    if (T_big == 0 && size_t((E + 63) / 64) * size_t((T + 63) / 64) < 128)
+        hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),
+                           static_cast<const bf16_t*>(Wn), noise, logits, T, d, E);
+    else if (T > T_big)
         hipLaunchKernelGGL(k_gate, dim3((E + 63) / 64, (T - T_big + 63) / 64), dim3(256), 0, st, xb + size_t(T_big) * d,
                            static_cast<const bf16_t*>(Wg), static_cast<const bf16_t*>(Wn), noise ? noise + size_t(T_big) * E : nullptr,
                            logits + size_t(T_big) * E, T - T_big, d, E);
@@ -984,23 +1206,41 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     else
         hipLaunchKernelGGL((k_topk<0>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
     if (timed) dynb::timing_mark(st, dynb::ST_TOPK, 0);
-    // m3 stable counting sort
-    const size_t nbc = size_t(E) * L.nblk;
-    hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
-    hipLaunchKernelGGL(k_rank_blocks, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, A, L.nblk);
-    hipLaunchKernelGGL(k_scan_blocks, dim3((E + 3) / 4), dim3(256), 0, st, blockcnt, counts, E, L.nblk);
-    hipLaunchKernelGGL(k_offsets, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, E);
-    hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, L.nblk);
-    if (timed) dynb::timing_mark(st, dynb::ST_SORT, 0);
-    // m4 permute: as a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop), else inside the
-    // first expert layer's operand load, which reads token perm[pos] / k for sorted position pos
+    // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
+    // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
+    // m3 stable counting sort: few uses in one workgroup.  With at most 16 rows per expert on average the expert layers then
+    // run on small tiles; their table takes the room of the stacked tokens, which no kernel writes then (at most one tile
+    // per use, 16 bytes each like the smallest token)
+    const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
+    const bool skinny = small && fused_permute && A <= 16 * E;
+    const int skinny_tiles = std::min(A, E) + A / TM;          // at least as many as there are
+    RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
+    if (small) {
+        hipLaunchKernelGGL(k_group_small, dim3(1), dim3(1024), 0, st, topk_idx, counts, offsets, tile_start, perm, inv, tiles,
+                           std::min(skinny_tiles, A), A, E);
+    } else {
+        const size_t nbc = size_t(E) * L.nblk;
+        hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
+        hipLaunchKernelGGL(k_rank_blocks, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, A, L.nblk);
+        hipLaunchKernelGGL(k_scan_blocks, dim3((E + 3) / 4), dim3(256), 0, st, blockcnt, counts, E, L.nblk);
+        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, E);
+        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, L.nblk);
+    }
+    if (timed) dynb::timing_mark(st, dynb::ST_SORT, 0);
+    // m4 permute
     if (!fused_permute) hipLaunchKernelGGL(k_permute, dim3((T + 3) / 4), dim3(256), 0, st, xb, inv, xs, T, d, k);
     if (timed) dynb::timing_mark(st, dynb::ST_PERMUTE, 0);
     // m5 grouped expert FFN: at most ceil(A/TM) + E row tiles exist
     const long long max_mtiles = (long long)(A + TM - 1) / TM + E;
     const int nt1 = (h + TN - 1) / TN, nt2 = (d + TN - 1) / TN;
-    if (naive_stride <= 0) {
+    if (skinny) {
+        const int m = std::min(skinny_tiles, A), ns1 = (h + 63) / 64, ns2 = (d + 63) / 64;
+        hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(m * ns1)), dim3(256), 0, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, h, d, ns1, perm, k);
+        if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
+        hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(m * ns2)), dim3(256), 0, st, hid, static_cast<const bf16_t*>(W2), y, tiles, d, h, ns2, nullptr, 1);
+        if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
+    } else if (naive_stride <= 0) {
         const long long span = 8ll * XCD_CHUNK;
         hipLaunchKernelGGL((k_grouped_gemm<true>), dim3(unsigned((max_mtiles * nt1 + span - 1) / span * span)), dim3(256), 0, st,
                            fused_permute ? xb : xs, static_cast<const bf16_t*>(W1), hid, offsets, tile_start, E, h, d, nt1,

@@ -255,6 +255,24 @@ def test_config4_targeted_tokens_with_empty_experts(dyn, util, oracle):
     print(f"config 4: {len(tokens)} tokens through {len(experts)} experts, per-token error max {errs.max():.2e}")
 
 
+@pytest.mark.parametrize("T,d,h,E,k,noise", [(1, 8, 8, 1, 1, True), (3, 40, 24, 5, 5, True), (17, 72, 136, 70, 2, False), (37, 512, 1024, 256, 2, False),
+                                             (64, 1000, 520, 64, 8, True), (128, 64, 96, 64, 8, True), (129, 64, 64, 64, 8, False), (100, 64, 72, 4097, 2, True),
+                                             (300, 48, 104, 40, 2, True)])
+def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
+    """The kernels for a few tokens, at the edges of their tiles (16 tokens, experts, features; 32 summed channels; rows of an
+    expert up to and over 16, 32 and 64) and of their range (1024 uses, 4096 experts, 16 rows per expert)."""
+    m = moe.small(seed=T + E, T=T, d=d, h=h, E=E, k=k, zipf_s=1.1 if E < 1000 else 0.3)
+    W1, W2 = stack(m)
+    out, aux = util.moe_run(dyn, m, W1, W2, noise=noise)
+    ref_logits = oracle.moe_logits(m.x, m.Wg, m.Wn if noise else None, m.noise if noise else None)
+    assert util.normwise(aux["logits"], ref_logits) < LOGIT_TOL
+    r = oracle.moe_route(aux["logits"], k)
+    for name in ("topk_idx", "counts", "offsets", "perm", "inv"):
+        assert (getattr(r, name) == aux[name]).all(), name
+    ref = oracle.moe_experts(m.x, r.topk_idx, r.topk_w, W1, W2)
+    assert per_token_errors(out, ref).max() < OUT_TOL
+
+
 def test_naive_per_use_loop_equals_batched_layer(dyn, util):
     """Results / MoE: the naive version loops over the k*b uses; same kernels, so the same bits as long as
     no group fills a 64-row tile (full tiles are multiplied with the 32x32x16 MFMA shape, which sums in
