@@ -41,6 +41,8 @@ def run_head(dyn, util, roots, head, dtype):
     ("bf16", 70, 128, 14, 14, 32, 256, 28),   # the fast shape: several row tiles, fc 1 cut along k
     ("f32", 130, 16, 8, 8, 16, 64, 28),
     ("bf16", 1, 128, 14, 14, 8, 8, 2),
+    ("f32", 3, 16, 4, 4, 8, 64, 2100),        # too many answers for one workgroup per example
+    ("bf16", 2, 136, 7, 7, 16, 72, 65),       # three chunks along k, answers and units that no wave count divides
 ])
 def test_every_probability_against_the_oracle(dyn, util, oracle, dtype, B, C, H, W, Cc, F, A):
     roots = np.abs(iep.make_feats(B + C, B, H, W, C, dtype))          # root maps are outputs of a ReLU: non-negative
