@@ -256,7 +256,7 @@ __global__ void k_bwd_leaves(const float* __restrict__ gleaf, const int32_t* __r
 // ------------------------------------------------------------------------------------------
 // The transposed convolutions are convolutions with the taps flipped and the channel roles exchanged, so a node's
 // backward step has the shape of its forward step and runs on the same building blocks (LDS halo tile, packed
-// weight fragments, software-pipelined K loop), one node per workgroup, wave w owning channel tile w.  The forward
+// weight fragments, software-pipelined K loop), a node or a part of one per workgroup, wave w owning channel tile w.  The forward
 // pass of a DYNB_PLAN_KEEP plan has left u (two-argument functions) and mid of every item in its workspace.
 //   tile <- g = gy * [y > 0]   (bf16)
 //   conv(g; W_b flipped^T)     -> dmid = result * [mid > 0], written into the tile in place of g
@@ -337,14 +337,23 @@ constexpr int LDS_BYTES = STAGE_OFF + STAGE_PIX * STAGE_PITCH;
 static_assert(MASK_BYTES % 256 == 0 && LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
 }  // namespace bn
 
+// PARTS workgroups share a node (PartShape): narrow launch groups took 37 us with one.
+template <int PARTS>
 __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 {
     using namespace mf;
-    constexpr int MTW = MT7, RW = 12, XW = 6, NTHR = 256;
+    using Shape = PartShape<PARTS>;
+    constexpr int MTA = Shape::MTA, MTB = Shape::MTB, UROWS = Shape::UROWS, RW = Shape::RW, NTHR = 256;
+    constexpr int XA = PARTS == 1 ? 6 : Shape::XA, XB = PARTS == 1 ? 6 : Shape::XB;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int per_xcd = gridDim.x >> 3;
     const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (logical >= a.count) return;
+    const int node = logical / PARTS, part = logical % PARTS;
+    if (node >= a.count) return;
+    // image rows: results [orow0, orow1), windows of the two convs from row_a and row_b, g from urow0
+    const int orow0 = part * Shape::ROWS, orow1 = min(orow0 + Shape::ROWS, S);
+    const int row_a = min(max(orow0 - 1, 0), S - 2 * MTA), row_b = min(orow0, S - 2 * MTB), urow0 = min(max(row_a - 1, 0), S - UROWS);
+    const int own_lo = orow0 * S * 16, own_hi = orow1 * S * 16;       // 16-byte pieces of this workgroup's rows of a map
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int r = lane & 31, h = lane >> 5, n0 = wave * 32;
 #ifdef DYNB_NODE_CLOCKS
@@ -353,9 +362,9 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 #else
 #define NCLK(i) do {} while (0)
 #endif
-    const dynb_item it = a.items[logical];
+    const dynb_item it = a.items[node];
     const bool binary = it.src1 != DYNB_NO_ARG;                        // uniform over the workgroup
-    const size_t item_off = size_t(a.first_item + logical) * (P * C);
+    const size_t item_off = size_t(a.first_item + node) * (P * C);
 
     const size_t frag3 = (size_t(it.type) * 4 + wave) * 72, frag1 = (size_t(it.type) * 4 + wave) * 16;
     const bf16_t* wrow_bT = a.pk3bT + frag3 * FRAG + lane * 8;
@@ -379,8 +388,9 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 
     // ---- g = gy * [y > 0] as bf16 into the tile, saved for dW_b and db_b; mask bytes of y and mid; all loads are
     // issued before the first use
-    constexpr int NIT = (P * 16 + NTHR - 1) / NTHR;
+    constexpr int NIT = (UROWS * S * 16 + NTHR - 1) / NTHR;
     {
+        const int c_lo = urow0 * S * 16 + tid, c_hi = (urow0 + UROWS) * S * 16;
         const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
         const u32x4* y4 = reinterpret_cast<const u32x4*>(yp);
         u32x4* sg4 = reinterpret_cast<u32x4*>(a.sv_g + item_off);
@@ -388,16 +398,16 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         u32x4 yv[NIT];
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
-            const int c = tid + i * NTHR;
-            if (c < P * 16) { glo[i] = gy4[2 * c]; ghi[i] = gy4[2 * c + 1]; yv[i] = y4[c]; }
+            const int c = c_lo + i * NTHR;
+            if (c < c_hi) { glo[i] = gy4[2 * c]; ghi[i] = gy4[2 * c + 1]; yv[i] = y4[c]; }
         }
         __builtin_amdgcn_sched_barrier(0);
         ring_fill<RW>(ring, wrow_bT);                             // arrives while the tile is written
         for (int c = tid; c < BORDER_PIX * 16; c += NTHR) zero_border_piece(c);
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
-            const int c = tid + i * NTHR;
-            if (c < P * 16) {
+            const int c = c_lo + i * NTHR;
+            if (c < c_hi) {
                 const uint32_t yb = piece_mask(yv[i]);
                 u32x4 pk;
                 pk.x = pack_bf16x2(yb & 1u ? glo[i].x : 0.f, yb & 2u ? glo[i].y : 0.f);
@@ -405,61 +415,66 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
                 pk.z = pack_bf16x2(yb & 16u ? ghi[i].x : 0.f, yb & 32u ? ghi[i].y : 0.f);
                 pk.w = pack_bf16x2(yb & 64u ? ghi[i].z : 0.f, yb & 128u ? ghi[i].w : 0.f);
                 *reinterpret_cast<u32x4*>(lds_raw + centre_addr(c)) = pk;
-                sg4[c] = pk;
+                if (PARTS == 1 || (c >= own_lo && c < own_hi)) sg4[c] = pk;
                 lds_raw[bn::MASK_OFF + c] = static_cast<unsigned char>(yb);
             }
         }
     }
 
-    // this lane's LDS address for the first row pair; in tile t it holds the pixel in column px of image row 2 t + py
-    const uint32_t x0 = pair_lane_addr(lane);
+    // this lane's LDS address for the first row pair of the windows; in tile t it holds the pixel in column px of window row
+    // 2 t + py
+    const uint32_t x_a = pair_lane_addr(lane) + uint32_t(row_a * ROW_BYTES), x_b = pair_lane_addr(lane) + uint32_t(row_b * ROW_BYTES);
     const int px = r & 15, py = r >> 4;
     const bool real = px < S;                                         // columns 14, 15 are padding
-    auto pixel = [&](int t) { return (2 * t + py) * S + px; };
+    auto pixel = [&](int row, int t) { return (row + 2 * t + py) * S + px; };
     const int chan = n0 + 16 * h;                                     // this lane's 16 accumulator elements: channels chan .. chan+15
-    f32x16 acc[MTW];
-    auto zero_acc = [&]() {
+    f32x16 acc_a[MTA];
+    constexpr bool SAME = MTA == MTB;                                 // one window: the second conv takes the first's registers
+    f32x16 acc_own[SAME ? 1 : MTB];
+    auto& acc = [&]() -> auto& { if constexpr (SAME) return acc_a; else return acc_own; }();
+    auto zero = [](auto& accs) {
 #pragma unroll
-        for (int t = 0; t < MTW; ++t)
+        for (auto& v : accs)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+            for (int i = 0; i < 16; ++i) v[i] = 0.f;
     };
-    auto centre = [&](int t) -> uint32_t { return x0 - uint32_t(h * 128) + uint32_t(CENTER + 2 * t * ROW_BYTES); };
-    // acc[t][8q .. 8q+7] where the mask bit is set, as 8 packed bf16
-    auto packed_masked = [&](int t, int q, uint32_t bits) -> u32x4 {
+    auto centre = [&](uint32_t x, int t) -> uint32_t { return x - uint32_t(h * 128) + uint32_t(CENTER + 2 * t * ROW_BYTES); };
+    // acc[8q .. 8q+7] where the mask bit is set, as 8 packed bf16
+    auto packed_masked = [&](const f32x16& acc, int q, uint32_t bits) -> u32x4 {
         float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (bits >> (8 * q + i)) & 1u ? acc[t][8 * q + i] : 0.f;
+        for (int i = 0; i < 8; ++i) v[i] = (bits >> (8 * q + i)) & 1u ? acc[8 * q + i] : 0.f;
         return u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
     };
-    // Accumulators -> the fp32 staging area, four pixel tiles per round; then every thread takes 16-byte pieces
+    // Accumulators of the second window -> the fp32 staging area, four pixel tiles per round; then every thread takes 16-byte pieces
     // (8 channels of a pixel) out of it: fn(c, lo, hi, pre(c)) with c the piece's index in the whole map.  pre(c)
     // is evaluated for all of a thread's pieces before the round's barriers, so what it loads is there afterwards.
     auto through_lds = [&](auto&& pre, auto&& fn) {
 #pragma unroll
-        for (int round = 0; round < 2; ++round) {
-            const int t0 = round * 4, t1 = round == 0 ? 4 : MTW, p0 = t0 * 28, p1 = round == 0 ? 112 : P;
-            constexpr int NI = 112 * 16 / NTHR;                       // pieces per thread of the larger round
+        for (int round = 0; round < (MTB + 3) / 4; ++round) {
+            const int t0 = round * 4, t1 = min(t0 + 4, MTB), p0 = row_b * S + t0 * 28;
+            const int lo = PARTS == 1 ? p0 * 16 : own_lo, hi = PARTS == 1 ? p0 * 16 + (t1 - t0) * 28 * 16 : own_hi;   // (parts: one round)
+            constexpr int NI = ((MTB < 4 ? MTB : 4) * 28 * 16 + NTHR - 1) / NTHR;     // pieces per thread of the larger round
             decltype(pre(0)) ahead[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                const int c = p0 * 16 + tid + i * NTHR;
-                if (c < p1 * 16) ahead[i] = pre(c);
+                const int c = lo + tid + i * NTHR;
+                if (c < hi) ahead[i] = pre(c);
             }
             __syncthreads();                                          // the area (and, the first time, the tile) is free
 #pragma unroll
-            for (int t = 0; t < MTW; ++t)
+            for (int t = 0; t < MTB; ++t)
                 if (t >= t0 && t < t1 && real) {
 #pragma unroll
                     for (int b = 0; b < 4; ++b)
-                        *reinterpret_cast<f32x4*>(lds_raw + bn::STAGE_OFF + uint32_t((pixel(t) - p0) * bn::STAGE_PITCH + (chan + 4 * b) * 4)) =
+                        *reinterpret_cast<f32x4*>(lds_raw + bn::STAGE_OFF + uint32_t((pixel(row_b, t) - p0) * bn::STAGE_PITCH + (chan + 4 * b) * 4)) =
                             f32x4{acc[t][4 * b], acc[t][4 * b + 1], acc[t][4 * b + 2], acc[t][4 * b + 3]};
                 }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                const int c = p0 * 16 + tid + i * NTHR;
-                if (c < p1 * 16) {
+                const int c = lo + tid + i * NTHR;
+                if (c < hi) {
                     const uint32_t at = bn::STAGE_OFF + uint32_t(((c >> 4) - p0) * bn::STAGE_PITCH + (c & 15) * 32);
                     fn(c, *reinterpret_cast<const f32x4*>(lds_raw + at), *reinterpret_cast<const f32x4*>(lds_raw + at + 16), ahead[i]);
                 }
@@ -478,47 +493,49 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 
     // ---- dmid = conv(g; W_b flipped, transposed) * [mid > 0], written into the tile in place of g
     // (mid is requested now and turned into mask bytes after the loop)
-    u32x4 mv[NIT];
+    constexpr int NIM = (2 * MTA * S * 16 + NTHR - 1) / NTHR;
+    const int m_lo = row_a * S * 16 + tid, m_hi = (row_a + 2 * MTA) * S * 16;
+    u32x4 mv[NIM];
 #pragma unroll
-    for (int i = 0; i < NIT; ++i) {
-        const int c = tid + i * NTHR;
-        if (c < P * 16) mv[i] = reinterpret_cast<const u32x4*>(a.sv_m + item_off)[c];
+    for (int i = 0; i < NIM; ++i) {
+        const int c = m_lo + i * NTHR;
+        if (c < m_hi) mv[i] = reinterpret_cast<const u32x4*>(a.sv_m + item_off)[c];
     }
-    zero_acc();
+    zero(acc_a);
     NCLK(1);
-    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_bT, wrow_aT);
+    kloop3<MTA, RW, XA>(acc_a, x_a, ring, wrow_bT, wrow_aT);
     NCLK(2);
 #pragma unroll
-    for (int i = 0; i < NIT; ++i) {
-        const int c = tid + i * NTHR;
-        if (c < P * 16) lds_raw[bn::MASK_OFF + P * 16 + c] = static_cast<unsigned char>(piece_mask(mv[i]));
+    for (int i = 0; i < NIM; ++i) {
+        const int c = m_lo + i * NTHR;
+        if (c < m_hi) lds_raw[bn::MASK_OFF + P * 16 + c] = static_cast<unsigned char>(piece_mask(mv[i]));
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < MTW; ++t)
+    for (int t = 0; t < MTA; ++t)
         if (real) {
             // this lane's 16 mask bits: the bytes of the two pieces that hold its channels
-            const uint32_t mm = *reinterpret_cast<const uint16_t*>(lds_raw + bn::MASK_OFF + P * 16 + pixel(t) * 16 + (chan >> 3));
+            const uint32_t mm = *reinterpret_cast<const uint16_t*>(lds_raw + bn::MASK_OFF + P * 16 + pixel(row_a, t) * 16 + (chan >> 3));
 #pragma unroll
             for (int q = 0; q < 2; ++q)
-                *reinterpret_cast<u32x4*>(lds_raw + centre(t) + uint32_t((chan + q * 8) * 2)) = packed_masked(t, q, mm);
+                *reinterpret_cast<u32x4*>(lds_raw + centre(x_a, t) + uint32_t((chan + q * 8) * 2)) = packed_masked(acc_a[t], q, mm);
         }
     __syncthreads();
     {                                                                 // dmid saved for dW_a and db_a, out of the tile
         u32x4* sdm4 = reinterpret_cast<u32x4*>(a.sv_dm + item_off);
 #pragma unroll
-        for (int i = 0; i < NIT; ++i) {
-            const int c = tid + i * NTHR;
-            if (c < P * 16) sdm4[c] = *reinterpret_cast<const u32x4*>(lds_raw + centre_addr(c));
+        for (int i = 0; i < (Shape::ROWS * S * 16 + NTHR - 1) / NTHR; ++i) {
+            const int c = own_lo + tid + i * NTHR;
+            if (c < own_hi) sdm4[c] = *reinterpret_cast<const u32x4*>(lds_raw + centre_addr(c));
         }
     }
 
     // ---- du = g + conv(dmid; W_a flipped, transposed).  The residual term g is added in fp32, from the gradient map
     // itself, not from its bf16 copy in the tile: down a chain of modules the convolution's share is small against
     // the residual's and would vanish below the bfloat16 quantum of the latter at every level.
-    zero_acc();
+    zero(acc);
     NCLK(3);
-    kloop3<MTW, RW, XW>(acc, x0, ring, wrow_aT, wrow_aT);
+    kloop3<MTB, RW, XB, false>(acc, x_b, ring, wrow_aT, wrow_aT);
     NCLK(4);
     auto residual = [&](int c, f32x4& lo, f32x4& hi, const f32x4& g0, const f32x4& g1) {
         const uint32_t yb = lds_raw[bn::MASK_OFF + c];
@@ -527,7 +544,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     };
     const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
     if (!binary) {
-        float* dst = route_mf(a, a.gdst0[logical]);
+        float* dst = route_mf(a, a.gdst0[node]);
         through_lds([&](int c) { return Grad{gy4[2 * c], gy4[2 * c + 1]}; },
                     [&](int c, f32x4 lo, f32x4 hi, const Grad& g) {
                         residual(c, lo, hi, g.g0, g.g1);
@@ -564,14 +581,14 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         bf16x8 w1f[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) w1f[j] = *reinterpret_cast<const bf16x8*>(t1row + j * FRAG);
-        auto caddr = [&](int t) { return centre(t) + uint32_t(h * 128); };
-        zero_acc();
-        kloop1<MTW, true>(acc, caddr, w1f, t1row + 8 * FRAG);
-        float* d0 = route_mf(a, a.gdst0[logical]);
+        auto caddr = [&](int t) { return centre(x_b, t) + uint32_t(h * 128); };
+        zero(acc);
+        kloop1<MTB, true>(acc, caddr, w1f, t1row + 8 * FRAG);
+        float* d0 = route_mf(a, a.gdst0[node]);
         through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d0, c, lo, hi); });
-        zero_acc();
-        kloop1<MTW, false>(acc, caddr, w1f, nullptr);
-        float* d1 = route_mf(a, a.gdst1[logical]);
+        zero(acc);
+        kloop1<MTB, false>(acc, caddr, w1f, nullptr);
+        float* d1 = route_mf(a, a.gdst1[node]);
         through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d1, c, lo, hi); });
     }
 }
@@ -981,8 +998,9 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bwd_node_mfma), hipFuncAttributeMaxDynamicSharedMemorySize, bn::LDS_BYTES),
-                "hipFuncSetAttribute(k_bwd_node_mfma)");
+        for (const void* f : {reinterpret_cast<const void*>(k_bwd_node_mfma<1>), reinterpret_cast<const void*>(k_bwd_node_mfma<2>),
+                              reinterpret_cast<const void*>(k_bwd_node_mfma<4>), reinterpret_cast<const void*>(k_bwd_node_mfma<7>)})
+            HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bn::LDS_BYTES), "hipFuncSetAttribute(k_bwd_node_mfma)");
         HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bwd_wgrad_mfma), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * mf::TILE_BYTES),
                 "hipFuncSetAttribute(k_bwd_wgrad_mfma)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
@@ -1040,8 +1058,10 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         a.items = d_items + l.start; a.first_item = l.start; a.count = l.count;
         a.gdst0 = reinterpret_cast<const int32_t*>(pd + KT.gdst0) + l.start;
         a.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + l.start;
-        const unsigned grid = unsigned((l.count + 7) / 8 * 8);
-        hipLaunchKernelGGL(k_bwd_node_mfma, dim3(grid), dim3(256), bn::LDS_BYTES, st, a);
+        const int parts = p->throughput ? 1 : parts_for(l.count);
+        const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
+        auto* kernel = parts == 7 ? k_bwd_node_mfma<7> : parts == 4 ? k_bwd_node_mfma<4> : parts == 2 ? k_bwd_node_mfma<2> : k_bwd_node_mfma<1>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), bn::LDS_BYTES, st, a);
     }
     {
         WgArgs q;

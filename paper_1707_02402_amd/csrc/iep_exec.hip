@@ -103,24 +103,11 @@ __global__ void k_pack_weights(const u32x4* __restrict__ src, u32x4* __restrict_
     }
 }
 
-// A node is spread over PARTS workgroups, each with a share of the output rows:
-//   PARTS      output rows      rows of the first conv's window (pixel tiles)    of the second's
-//     1            14                      14 (7)                                    14 (7)
-//     2             7                       8 (4)                                     8 (4)
-//     4             4                       6 (3)                                     4 (2)
-//     7             2                       4 (2)                                     2 (1)
-// (the second conv needs one row of the first conv's output beyond its own rows on either side).  Wave w owns channel
-// tile w of all of them.  More parts shorten narrow launch groups at the price of MFMA work (14, 16, 20, 21 tiles a
-// node) and of reading the weights once per part: one node takes 14.7 us in 2 parts, of which 7.7 are MFMAs.
+// (How a node is spread over workgroups: PartShape, iep_mfma.h.)
 // All fit 256 registers and half of a CU's LDS, so that two workgroups share a CU where a launch group is wide enough,
 // and one's staging, swap and epilogue run under the other's MFMAs.  (A whole-node layout of its own for groups of
 // up to one node per CU, with twice the weight ring in 346 registers, was 3 % slower: the accumulators then live in
 // the upper half of the register file, and every other use of them is a copy.)
-template <int PARTS> struct PartShape;        // output rows, pixel tiles of the two convs, rows of u, fragments in the weight ring, activation register sets
-template <> struct PartShape<1> { static constexpr int ROWS = 14, MTA = 7, MTB = 7, UROWS = 14, RW = 12, XA = 10, XB = 10; };
-template <> struct PartShape<2> { static constexpr int ROWS = 7, MTA = 4, MTB = 4, UROWS = 9, RW = 12, XA = 12, XB = 12; };
-template <> struct PartShape<4> { static constexpr int ROWS = 4, MTA = 3, MTB = 2, UROWS = 8, RW = 24, XA = 8, XB = 8; };
-template <> struct PartShape<7> { static constexpr int ROWS = 2, MTA = 2, MTB = 1, UROWS = 6, RW = 24, XA = 8, XB = 8; };
 // One workgroup's share of a launch group: position `logical` (a node, or a part of one) of the items a.items[0 .. a.count).
 // KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m.
 template <int PARTS, bool KEEP = false>
@@ -685,7 +672,7 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         a.count = l.count;
         // as many parts per node as still fit the chip's 256 CUs in one round; beyond that, and whenever several batches are in
         // flight (their narrow groups share the chip), one node per workgroup
-        const int parts = p->throughput || l.count > 128 ? 1 : l.count > 64 ? 2 : l.count > 36 ? 4 : 7;
+        const int parts = p->throughput ? 1 : parts_for(l.count);
         const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
         auto* kernel = parts == 7   ? (p->keep ? k_module_mfma<7, true> : k_module_mfma<7>)
                        : parts == 4 ? (p->keep ? k_module_mfma<4, true> : k_module_mfma<4>)

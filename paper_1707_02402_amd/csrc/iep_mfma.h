@@ -199,4 +199,24 @@ __device__ __forceinline__ void kloop1(f32x16 (&acc)[MTW], const Addr& xaddr, bf
     if (WNEXT) wf[7] = *reinterpret_cast<const bf16x8*>(wnext + 7 * mf::FRAG);
 }
 
+// ---- parts of a node --------------------------------------------------------------------------------
+// A node is spread over PARTS workgroups, each with a share of the output rows:
+//   PARTS      output rows      rows of the first conv's window (pixel tiles)    of the second's
+//     1            14                      14 (7)                                    14 (7)
+//     2             7                       8 (4)                                     8 (4)
+//     4             4                       6 (3)                                     4 (2)
+//     7             2                       4 (2)                                     2 (1)
+// (the second conv needs one row of the first conv's output beyond its own rows on either side).  Wave w owns channel
+// tile w of all of them.  More parts shorten narrow launch groups at the price of MFMA work (14, 16, 20, 21 tiles a
+// node) and of reading the weights once per part: one node takes 14.7 us in 2 parts, of which 7.7 are MFMAs.
+// The backward pass has the same geometry: du is the result, dmid what lies between the convs, g (rows of u) what goes in.
+template <int PARTS> struct PartShape;        // output rows, pixel tiles of the two convs, rows of u, fragments in the weight ring, activation register sets
+template <> struct PartShape<1> { static constexpr int ROWS = 14, MTA = 7, MTB = 7, UROWS = 14, RW = 12, XA = 10, XB = 10; };
+template <> struct PartShape<2> { static constexpr int ROWS = 7, MTA = 4, MTB = 4, UROWS = 9, RW = 12, XA = 12, XB = 12; };
+template <> struct PartShape<4> { static constexpr int ROWS = 4, MTA = 3, MTB = 2, UROWS = 8, RW = 24, XA = 8, XB = 8; };
+template <> struct PartShape<7> { static constexpr int ROWS = 2, MTA = 2, MTB = 1, UROWS = 6, RW = 24, XA = 8, XB = 8; };
+
+// parts per node of a launch group of `count` nodes: as many as still fit the chip's 256 CUs in one round
+inline int parts_for(int count) { return count > 128 ? 1 : count > 64 ? 2 : count > 36 ? 4 : 7; }
+
 }  // namespace
