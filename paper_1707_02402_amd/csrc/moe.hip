@@ -611,19 +611,43 @@ __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restr
 
 __global__ __launch_bounds__(SORT_BLOCK) void k_place(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank,
                                                       const int32_t* __restrict__ blockoff, const int32_t* __restrict__ offsets,
-                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv, int A, int nblk)
+                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv, int A, int per_block,
+                                                      int expert_stride, int block_stride)
 {
     const int a = blockIdx.x * SORT_BLOCK + threadIdx.x;
     if (a >= A) return;
     const int e = idx[a];
-    const int pos = offsets[e] + blockoff[size_t(e) * nblk + blockIdx.x] + lrank[a];
+    const int pos = offsets[e] + blockoff[size_t(e) * expert_stride + size_t(a / per_block) * block_stride] + lrank[a];
     perm[pos] = a;
     inv[a] = pos;
 }
 
+// The use of thread tid of 1024 among the block's first `n`: the number of earlier uses of its expert `my` (-1: none).  Every wave ranks
+// its 64 uses among themselves, then the waves add theirs to count[] (LDS, zero before; the experts' uses after) in turn.
+__device__ __forceinline__ int rank_in_block(int my, int n, int32_t* count)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int local = 0, same = 0;                              // uses of this expert in earlier lanes, in the whole wave
+#pragma unroll 16
+    for (int j = 0; j < 64; ++j) {
+        const bool m = __builtin_amdgcn_readlane(my, j) == my;
+        same += m;
+        local += m && j < lane;
+    }
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < (n + 63) / 64; ++w) {
+        if (wave == w && my >= 0) {
+            before = count[my] + local;
+            if (local == same - 1) count[my] = before + 1;          // (behind the wave's reads: its LDS accesses are executed in order)
+        }
+        __syncthreads();
+    }
+    return before;
+}
+
 // The whole grouping of at most SMALL_USES uses in one workgroup, where the five kernels above are five launches with next to
-// nothing to do (18 us for 74 uses): counts and places of the experts in LDS; every wave ranks its 64 uses among
-// themselves, then the waves add theirs to the counts in turn.  `tiles` (if not null): the row tiles of the expert layers, {expert, first row, rows, 0} each, rows = 0 from the
+// nothing to do (18 us for 74 uses): counts and places of the experts in LDS.  `tiles` (if not null): the row tiles of the expert layers, {expert, first row, rows, 0} each, rows = 0 from the
 // last one on to max_tiles, so that a workgroup of those layers finds its tile with one load.
 constexpr int SMALL_USES = 1024, SMALL_EXPERTS = 4096;
 struct alignas(16) RowTile { int32_t expert, row0, rows, pad; };
@@ -638,22 +662,7 @@ __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict_
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int my = tid < A ? idx[tid] : -1;
     for (int e = tid; e < E; e += 1024) first[e] = 0;
-    int local = 0, same = 0;                              // uses of this expert in earlier lanes, in the whole wave
-#pragma unroll 16
-    for (int j = 0; j < 64; ++j) {
-        const bool m = __builtin_amdgcn_readlane(my, j) == my;
-        same += m;
-        local += m && j < lane;
-    }
-    __syncthreads();
-    int before = 0;                                       // earlier uses of this expert
-    for (int w = 0; w < (A + 63) / 64; ++w) {
-        if (wave == w && my >= 0) {
-            before = first[my] + local;
-            if (local == same - 1) first[my] = before + 1;          // (behind the wave's reads: its LDS accesses are executed in order)
-        }
-        __syncthreads();
-    }
+    const int before = rank_in_block(my, A, first);
     int carry = 0, tcarry = 0;
     for (int e0 = 0; e0 < E; e0 += 1024) {                // as k_offsets
         const int e = e0 + tid;
@@ -697,6 +706,69 @@ __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict_
         perm[pos] = tid;
         inv[tid] = pos;
     }
+}
+
+// The same for more uses, in three launches: blocks of 1024 uses are ranked with the experts' counts in LDS and leave all of their
+// counts, zeros included (nothing has to be cleared), as blockcnt[block][expert]; one workgroup turns them into
+// places, an expert per thread.  For up to SMALL_EXPERTS experts and MID_BLOCKS blocks, beyond which that workgroup's
+// walk over the blocks takes longer than the launches it saves.  (8192 uses of 256 experts: 23 us in five launches.)
+constexpr int MID_BLOCKS = 64;
+__global__ __launch_bounds__(1024) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
+{
+    __shared__ int32_t count[SMALL_EXPERTS];
+    const int a = blockIdx.x * 1024 + threadIdx.x;
+    const int my = a < A ? idx[a] : -1;
+    for (int e = threadIdx.x; e < E; e += 1024) count[e] = 0;
+    const int before = rank_in_block(my, min(1024, A - int(blockIdx.x) * 1024), count);
+    if (a < A) lrank[a] = before;
+    for (int e = threadIdx.x; e < E; e += 1024) blockcnt[size_t(blockIdx.x) * E + e] = count[e];
+}
+
+__global__ __launch_bounds__(1024) void k_places(int32_t* __restrict__ blockcnt, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                 int32_t* __restrict__ tile_start, int E, int nblk)
+{
+    __shared__ int32_t wsum[16], wtsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int carry = 0, tcarry = 0;
+    for (int e0 = 0; e0 < E; e0 += 1024) {
+        const int e = e0 + tid;
+        int c = 0;
+        if (e < E) {
+            for (int b0 = 0; b0 < nblk; b0 += 16) {
+                int v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = b0 + i < nblk ? blockcnt[size_t(b0 + i) * E + e] : 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    if (b0 + i < nblk) blockcnt[size_t(b0 + i) * E + e] = c;
+                    c += v[i];
+                }
+            }
+        }
+        const int tl = (c + TM - 1) / TM;                    // from here on as k_offsets
+        int inc = c, tinc = tl;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            const int to = __shfl_up(tinc, off);
+            if (lane >= off) { inc += o; tinc += to; }
+        }
+        if (lane == 63) { wsum[wave] = inc; wtsum[wave] = tinc; }
+        __syncthreads();
+        int before = 0, tbefore = 0, all = 0, tall = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int s = wsum[w], t = wtsum[w];
+            if (w < wave) { before += s; tbefore += t; }
+            all += s;
+            tall += t;
+        }
+        if (e < E) { counts[e] = c; offsets[e] = carry + before + inc - c; tile_start[e] = tcarry + tbefore + tinc - tl; }
+        carry += all;
+        tcarry += tall;
+        __syncthreads();
+    }
+    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
 }
 
 // ------------------------------------------------------------------------------------------ permute / combine
@@ -1219,13 +1291,18 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     if (small) {
         hipLaunchKernelGGL(k_group_small, dim3(1), dim3(1024), 0, st, topk_idx, counts, offsets, tile_start, perm, inv, tiles,
                            std::min(skinny_tiles, A), A, E);
+    } else if (E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024) {
+        const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for)
+        hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(1024), 0, st, topk_idx, lrank, blockcnt, A, E);
+        hipLaunchKernelGGL(k_places, dim3(1), dim3(1024), 0, st, blockcnt, counts, offsets, tile_start, E, nblk);
+        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, 1024, 1, E);
     } else {
         const size_t nbc = size_t(E) * L.nblk;
         hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
         hipLaunchKernelGGL(k_rank_blocks, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, A, L.nblk);
         hipLaunchKernelGGL(k_scan_blocks, dim3((E + 3) / 4), dim3(256), 0, st, blockcnt, counts, E, L.nblk);
         hipLaunchKernelGGL(k_offsets, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, E);
-        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, L.nblk);
+        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, SORT_BLOCK, L.nblk, 1);
     }
     if (timed) dynb::timing_mark(st, dynb::ST_SORT, 0);
     // m4 permute

@@ -273,6 +273,15 @@ def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
     assert per_token_errors(out, ref).max() < OUT_TOL
 
 
+@pytest.mark.parametrize("T,E,k", [(1025, 7, 1), (1024, 4096, 2), (513, 300, 2), (8192, 40, 8), (8200, 33, 8), (600, 4097, 2)])
+def test_grouping_of_many_uses(dyn, util, oracle, T, E, k):
+    """Blocks of 1024 uses with a remainder of one, the most experts and the most uses of that path, and what lies beyond."""
+    m = moe.small(seed=T + k, T=T, d=16, h=16, E=E, k=k, zipf_s=0.8)
+    W1, W2 = stack(m)
+    _, aux = util.moe_run(dyn, m, W1, W2)
+    check_routing(oracle, m, aux)
+
+
 def test_naive_per_use_loop_equals_batched_layer(dyn, util):
     """Results / MoE: the naive version loops over the k*b uses; same kernels, so the same bits as long as
     no group fills a 64-row tile (full tiles are multiplied with the 32x32x16 MFMA shape, which sums in
