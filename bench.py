@@ -311,7 +311,7 @@ def main():
         wws = torch.empty(dyn.dynbatch_workspace_bytes(wplan, w.C, w.H, w.W, dyn.DYNB_BF16), dtype=torch.uint8, device="cuda")
         ms_ = gpu_ms(lambda: dyn.dynbatch_execute(wplan, weights, wfeats, wout, wws), K, warm_ms=40.0)
         tf = nw * FLOP_UNARY / ms_ / 1e9
-        wide.update({"kernel": "k_module_mfma<4> (two workgroups per CU)", "ms": round(ms_, 4), "tflops": round(tf, 1),
+        wide.update({"kernel": "k_module_mfma<1> (two workgroups per CU)", "ms": round(ms_, 4), "tflops": round(tf, 1),
                      "frac": round(tf / PEAK_BF16_TFLOPS, 4),
                      "frac_of_measured_peak": None if peak is None else round(tf / peak["mfma_bf16_tflops"], 4),
                      "warm_up": "40 ms of the same launches before the timed ones"})

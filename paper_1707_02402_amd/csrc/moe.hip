@@ -725,7 +725,7 @@ __global__ __launch_bounds__(1024) void k_rank_wide(const int32_t* __restrict__ 
 }
 
 __global__ __launch_bounds__(1024) void k_places(int32_t* __restrict__ blockcnt, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                 int32_t* __restrict__ tile_start, int E, int nblk)
+                                                 int32_t* __restrict__ tile_start, RowTile* __restrict__ tiles, int max_tiles, int E, int nblk)
 {
     __shared__ int32_t wsum[16], wtsum[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -763,12 +763,21 @@ __global__ __launch_bounds__(1024) void k_places(int32_t* __restrict__ blockcnt,
             all += s;
             tall += t;
         }
-        if (e < E) { counts[e] = c; offsets[e] = carry + before + inc - c; tile_start[e] = tcarry + tbefore + tinc - tl; }
+        if (e < E) {
+            const int at = carry + before + inc - c, tat = tcarry + tbefore + tinc - tl;
+            counts[e] = c;
+            offsets[e] = at;
+            tile_start[e] = tat;
+            if (tiles)
+                for (int t = 0; t < tl; ++t) tiles[tat + t] = RowTile{e, at + t * TM, min(TM, c - t * TM), 0};
+        }
         carry += all;
         tcarry += tall;
         __syncthreads();
     }
     if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
+    if (tiles)
+        for (int t = tcarry + tid; t < max_tiles; t += 1024) tiles[t] = RowTile{0, 0, 0, 0};
 }
 
 // ------------------------------------------------------------------------------------------ permute / combine
@@ -1038,7 +1047,7 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__
     else gemm_tile<RELU, 4>(in, We, out, row0, rows, nb, N, K, Ws, Xs, gather, kdiv);
 }
 
-// The expert layers for few rows per expert.  There a layer is a stream of weights, each multiplied with a handful of rows: what
+// The expert layers for few tiles (the rule stands where it is applied).  There a layer is a stream of weights, each multiplied with a handful of rows: what
 // counts is how much of it is in flight.  k_grouped_gemm asks for one K-chunk at a time and for 256 features per workgroup;
 // with some 40 live experts that is 160 workgroups with 40 KB in flight each, 31 to 39 us for 38 MB.  Here a workgroup
 // owns 64 features of a row tile, a wave 16 of them, and weights go straight from memory into registers, SK_RD K-steps (1 KB
@@ -1281,20 +1290,24 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
     // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
-    // m3 stable counting sort: few uses in one workgroup.  With at most 16 rows per expert on average the expert layers then
-    // run on small tiles; their table takes the room of the stacked tokens, which no kernel writes then (at most one tile
-    // per use, 16 bytes each like the smallest token)
+    // m3 stable counting sort: few uses in one workgroup, more in three launches, beyond that in five.  Where the expert layers
+    // have too few 64 x 256 tiles to keep the chip's memory busy with k_grouped_gemm they run on small tiles.  The line, us
+    // a layer pair with k_grouped_gemm / k_grouped_skinny by the number of its tiles: 200: 99 / 57, 256: 77 / 53, 520: 190 /
+    // 109, 768: 118 / 124, 1024: 225 / 239, 9000: 1640 / 1950.  (The number is a bound; of up to 1024 uses fewer experts are
+    // live: 1040: 108 / 81, 1088: 148 / 141, 1152: 290 / 268.)  The tiles' table takes the room of the stacked tokens, which
+    // no kernel writes then (at most one tile per use, 16 bytes each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
-    const bool skinny = small && fused_permute && A <= 16 * E;
-    const int skinny_tiles = std::min(A, E) + A / TM;          // at least as many as there are
+    const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
+    const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
+    const bool skinny = (small || mid) && fused_permute && (long long)skinny_tiles * ((std::max(h, d) + TN - 1) / TN) <= (small ? 1200 : 640);
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
     if (small) {
         hipLaunchKernelGGL(k_group_small, dim3(1), dim3(1024), 0, st, topk_idx, counts, offsets, tile_start, perm, inv, tiles,
-                           std::min(skinny_tiles, A), A, E);
-    } else if (E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024) {
+                           skinny_tiles, A, E);
+    } else if (mid) {
         const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for)
         hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(1024), 0, st, topk_idx, lrank, blockcnt, A, E);
-        hipLaunchKernelGGL(k_places, dim3(1), dim3(1024), 0, st, blockcnt, counts, offsets, tile_start, E, nblk);
+        hipLaunchKernelGGL(k_places, dim3(1), dim3(1024), 0, st, blockcnt, counts, offsets, tile_start, tiles, skinny_tiles, E, nblk);
         hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, 1024, 1, E);
     } else {
         const size_t nbc = size_t(E) * L.nblk;
@@ -1312,7 +1325,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     const long long max_mtiles = (long long)(A + TM - 1) / TM + E;
     const int nt1 = (h + TN - 1) / TN, nt2 = (d + TN - 1) / TN;
     if (skinny) {
-        const int m = std::min(skinny_tiles, A), ns1 = (h + 63) / 64, ns2 = (d + 63) / 64;
+        const int m = skinny_tiles, ns1 = (h + 63) / 64, ns2 = (d + 63) / 64;
         hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(m * ns1)), dim3(256), 0, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, h, d, ns1, perm, k);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
         hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(m * ns2)), dim3(256), 0, st, hid, static_cast<const bf16_t*>(W2), y, tiles, d, h, ns2, nullptr, 1);
