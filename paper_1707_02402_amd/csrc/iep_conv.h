@@ -651,9 +651,11 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     a.tiles_per_seg = (n_q + MT * 16 - 1) / (MT * 16);
     a.n_ctile = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + NT * 16 - 1) / (NT * 16);
     const int pixels = conv_tile_pixels(a, MT, Tr::HALO);
-    // as many channels at a time as fit, in panels of nearly equal size
+    // As many channels at a time as fit beside the pixels of the largest tile, whatever this tile has, in panels of nearly equal
+    // size: a panel is what the waves split, so the panels are part of the order of summation, and a launch group's width (which
+    // picks the tile) must not change a result's bits.
     const int steps = (a.C + KS - 1) / KS;
-    const int fit = std::max(1, (CONV_LDS_MAX / pixels - 16) / (KS * ES));
+    const int fit = std::max(1, (CONV_LDS_MAX / conv_tile_pixels(a, 4, Tr::HALO) - 16) / (KS * ES));
     const int panels = (steps + fit - 1) / fit;
     a.ck = (steps + panels - 1) / panels * KS;
     a.m_sw = recip20_of(a.sw);

@@ -94,6 +94,26 @@ def test_ragged_shapes_fp32_with_single_scene_programs(dyn, util, oracle, C, H, 
         assert (again[name] == got[name]).all(), name                     # fixed summation order: same bits
 
 
+def test_the_width_of_a_launch_group_does_not_change_the_gradients_bits(dyn, util, oracle):
+    """fp32, C = 160, 14 x 14: the summed channels fit LDS at once beside some of the workgroup tiles only."""
+    arity = np.array([0, 1, 2], np.uint8)
+    progs = [np.array([1, 0] if i % 3 else [2, 0, 0], np.int32) for i in range(13)]
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    w = iep.IepWorkload("widths", "f32", arity, np.concatenate(progs), off, 160, 14, 14,
+                        iep.make_feats(9, 13, 14, 14, 160, "f32"), *iep.make_weights(10, arity, 160, "f32"))
+    dout = np.random.default_rng(4).standard_normal(w.feats.shape).astype(np.float32)
+    full, _ = run_backward(dyn, util, w, dout)
+    for n in (1, 2, 4, 8):
+        got, _ = run_backward(dyn, util, w.subset(range(n)), dout[:n])
+        assert (got["dfeats"] == full["dfeats"][:n]).all(), n
+    naive, _ = run_backward(dyn, util, w, dout, dyn.DYNB_SCHED_NAIVE)
+    assert (naive["dfeats"] == full["dfeats"]).all()
+    ref = oracle.iep_backward_workload(w.subset([0, 1]), dout[:2])
+    got, _ = run_backward(dyn, util, w.subset([0, 1]), dout[:2])
+    for name in NAMES:
+        assert maxnorm(got[name], getattr(ref, name)) < 1e-4, name
+
+
 def test_bf16_fast_shape_after_the_fused_forward(dyn, util, oracle):
     """bf16, C = 128, 14 x 14: the forward pass runs the fused MFMA kernels and leaves every node's result in the
     workspace; the backward pass reads them from there."""

@@ -474,3 +474,19 @@ def test_half_and_whole_node_layouts_at_the_width_where_they_change(dyn, util, o
     ref = oracle.iep_forward_workload(w.subset(sample))
     for j, i in enumerate(sample):
         assert util.normwise(got[i], ref[j]) < TOL["bf16"], i
+
+
+@pytest.mark.parametrize("dtype,C,side", [("f32", 160, 14), ("f32", 128, 28), ("bf16", 320, 14), ("f32", 256, 14)])
+def test_the_width_of_a_launch_group_does_not_change_the_bits(dyn, util, oracle, dtype, C, side):
+    """Shapes whose summed channels do not fit LDS at once beside the largest workgroup tile but do beside smaller ones: groups of
+    1 to 13 nodes take every tile, and all of them must add the channels up in the same order."""
+    arity = np.array([0, 1, 2], np.uint8)
+    progs = [np.array([1, 0] if i % 3 else [2, 0, 0], np.int32) for i in range(13)]
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    w = iep.IepWorkload("widths", dtype, arity, np.concatenate(progs), off, C, side, side,
+                        iep.make_feats(C, 13, side, side, C, dtype), *iep.make_weights(C + 1, arity, C, dtype))
+    full = util.iep_run(dyn, w)
+    assert (util.iep_run(dyn, w, dyn.DYNB_SCHED_NAIVE) == full).all()
+    for n in (1, 2, 4, 8):
+        assert (util.iep_run(dyn, w.subset(range(n))) == full[:n]).all(), n
+    assert util.normwise(full[:1], oracle.iep_forward_workload(w.subset([0]))) < TOL[dtype]
