@@ -1054,7 +1054,8 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__
 // each) ahead; two consecutive steps read one 128-byte line per row.  The rows pass through LDS, 32 KB of them at a time: four
 // waves that read their fragments from global memory are answered at 16 bytes per clock (neighbouring lanes hold different
 // rows), which alone took 8 us.
-// Same MFMAs in the same order as the tiles of up to 32 rows there.
+// The results are those of k_grouped_gemm bit for bit, whose tiles of more than 32 rows use the 32x32x16 MFMA: one 16x16x32 MFMA
+// rounds like two of those over the same channels (524288 sums of 512 products, values spread over up to 2^32: no bit differs).
 constexpr int SK_RD = 16;
 constexpr int SK_LDS = 33 * 1024;                              // 16 ML rows of 1024 / ML channels and 16 bytes
 

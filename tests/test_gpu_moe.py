@@ -104,6 +104,20 @@ def test_permute_inside_the_operand_load_equals_the_separate_kernel(dyn, util, T
     assert e.value.name == "DYNB_E_UNSUPPORTED"
 
 
+@pytest.mark.parametrize("T,E,k", [(500, 10, 1), (2000, 30, 1), (400, 16, 2)])
+def test_the_separate_permute_gives_the_same_bits_where_experts_have_few_tiles_of_many_rows(dyn, util, T, E, k):
+    """Wide layers whose experts hold 33 to 64 rows or more, in few tiles: sums of 512 and 1024 products, so that another order of
+    summation shows in the bfloat16 results."""
+    m = moe.small(seed=T + E, T=T, d=512, h=1024, E=E, k=k, zipf_s=0.2)
+    W1, W2 = stack(m)
+    dev = util.moe_inputs_dev(m, W1, W2)
+    args = (dev["x"], dev["Wg"], dev["Wn"], dev["noise"], dev["W1"], dev["W2"], m.k)
+    a, aux = dyn.moe_forward(*args, want_aux=True)
+    assert ((aux.counts > 32) & (aux.counts % 64 > 32)).any()
+    b = dyn.moe_forward(*args, flags=dyn.MOE_SEPARATE_PERMUTE)
+    assert (util.to_host(a) == util.to_host(b)).all()
+
+
 def test_noiseless_gate_and_ties(dyn, util, oracle):
     """noise = NULL drops the softplus term; duplicated gate columns give exactly equal logits: lower id wins."""
     m = moe.small(seed=9, T=128, d=64, h=64, E=16, k=4)
