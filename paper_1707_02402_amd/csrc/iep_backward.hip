@@ -97,16 +97,22 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
     float bias = 0.f;                                                            // sum of this lane's G values
 
     const int lo = JOIN && ar != 2 ? 0 : a.fn_first[type], hi = JOIN && ar != 2 ? 0 : a.fn_first[type + 1];
-#pragma unroll 1
-    for (int idx = lo; idx < hi; ++idx) {
+    struct Maps { const float* G; const T* Y; const T* IN; };                    // Y: the item's result, whose ReLU masks G (which 0)
+    auto maps = [&](int idx) -> Maps {
         const int32_t item = a.fn_items[idx];
         const dynb_item it = a.items[item];
         const size_t off = size_t(item) * chw;
-        const float* G = JOIN ? a.du + off : which == 0 ? a.gy + off : a.dm + off;
-        const T* Y = it.dst >= 0 ? (const T*)a.slots + size_t(it.dst) * chw : (const T*)a.out + size_t(-1 - it.dst) * chw;
         const int32_t s = arg ? it.src1 : it.src0;
         const T* A = s >= 0 ? (const T*)a.slots + size_t(s) * chw : (const T*)a.feats + size_t(-1 - s) * chw;
-        const T* IN = JOIN ? A : which == 0 ? (const T*)a.mid + off : ar == 2 ? (const T*)a.u + off : A;
+        return {JOIN ? a.du + off : which == 0 ? a.gy + off : a.dm + off,
+                it.dst >= 0 ? (const T*)a.slots + size_t(it.dst) * chw : (const T*)a.out + size_t(-1 - it.dst) * chw,
+                JOIN ? A : which == 0 ? (const T*)a.mid + off : ar == 2 ? (const T*)a.u + off : A};
+    };
+#pragma unroll 1
+    for (int idx = lo; idx < hi; ++idx) {
+        const Maps m = maps(idx);
+        const float* const G = m.G;
+        const T *const Y = m.Y, *const IN = m.IN;
 #pragma unroll 1
         for (int x0 = 0; x0 < W; x0 += sw)
 #pragma unroll 1
@@ -180,6 +186,25 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                 }
             }
     }
+    // The staged zeros (outside the map, in the padding column of an odd width) are factors here, and a zero times an infinity is
+    // NaN: a sum that came out NaN is taken again without them (again: bit 4 tap + e for the thread's four rows).
+    uint64_t again = 0;
+    auto direct = [&](int tap, int co, int ci) -> float {
+        float sum = 0.f;
+#pragma unroll 1
+        for (int idx = lo; idx < hi; ++idx) {
+            const Maps m = maps(idx);
+#pragma unroll 1
+            for (int p = 0; p < H * W; ++p) {
+                const int y = p / W + (JOIN ? 0 : tap / 3 - 1), x = p % W + (JOIN ? 0 : tap % 3 - 1);
+                if (unsigned(y) >= unsigned(H) || unsigned(x) >= unsigned(W)) continue;
+                const size_t e = size_t(p) * C + co;
+                const float g = !JOIN && which == 0 && !(load_f32(m.Y + e) > 0.f) ? 0.f : m.G[e];
+                sum += g * load_f32(m.IN + (size_t(y) * W + x) * C + ci);
+            }
+        }
+        return sum;
+    };
     // partial sums of the waves through LDS, three taps at a time: [wave][tap][b][lane] of four rows each
     f32x4* red = reinterpret_cast<f32x4*>(lds_raw);
     constexpr int R = JOIN ? 1 : 3;
@@ -204,10 +229,17 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (co + e < C && ci < C) {
+                    if (v[e] != v[e]) again |= uint64_t(1) << ((k0 + k) * 4 + e);
                     const size_t row = size_t(type) * C + co + e;
                     a.dw[which][JOIN ? row * 2 * C + arg * C + ci : (row * 9 + k0 + k) * C + ci] = v[e];
                 }
         }
+    }
+#pragma unroll 1
+    for (; again; again &= again - 1) {
+        const int b = __builtin_ctzll(again), co = co0 + 8 * wave + 4 * hk + (b & 3), ci = ci0 + r;
+        const size_t row = size_t(type) * C + co;
+        a.dw[which][JOIN ? row * 2 * C + arg * C + ci : (row * 9 + (b >> 2)) * C + ci] = direct(b >> 2, co, ci);
     }
     if (ci0 == 0 && arg == 0) {                                                  // bias: the lane halves and the waves in order
         __syncthreads();

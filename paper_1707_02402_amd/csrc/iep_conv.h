@@ -264,6 +264,34 @@ struct ConvSteps {
     }
 };
 
+// A tap outside the map contributes nothing, whatever its weight; the matrix instructions multiply a zero with it, which is NaN for
+// a weight that is not finite.  Nothing else brings a NaN in from outside, so a sum at the map's border that came out NaN is taken
+// again, tap by tap: rare, and out of the way of the others.
+__device__ __forceinline__ bool any_nan(const f32x4& v, int n)          // among channels 0 .. n - 1
+{
+    return __builtin_expect((v.x != v.x) | (n > 1 && v.y != v.y) | (n > 2 && v.z != v.z) | (n > 3 && v.w != v.w), 0);
+}
+__device__ __forceinline__ bool at_border(int y, int x, int H, int W) { return y == 0 || x == 0 || y == H - 1 || x == W - 1; }
+// w: the function's weights.  pixel(kh, kw, c): channel c of the pixel under tap (kh, kw), as a float.  BWD: the data gradient (taps
+// backwards, sums over the weights' rows)
+template <bool BWD, typename T, typename Pixel>
+__device__ __forceinline__ f32x4 direct_sum(const T* w, int C, int H, int W, int y, int x, int o, int n, Pixel&& pixel)
+{
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int tap = 0; tap < 9; ++tap) {
+        const int kh = tap / 3, kw = tap - 3 * kh;
+        if (unsigned(y + kh - 1) >= unsigned(H) || unsigned(x + kw - 1) >= unsigned(W)) continue;
+#pragma unroll 1
+        for (int c = 0; c < C; ++c) {
+            const float v = pixel(kh, kw, c);
+            const T* p = BWD ? w + (size_t(c) * 9 + 8 - tap) * C + o : w + (size_t(o) * 9 + tap) * C + c;
+            for (int e = 0; e < n; ++e) sum[e] += v * load_f32(p + size_t(e) * (BWD ? 1 : 9 * size_t(C)));
+        }
+    }
+    return sum;
+}
+
 template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
 __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArgs a)
 {
@@ -410,6 +438,17 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
             const f32x4 p = red[(w * MT * NT + tt) * 64 + lane];
             v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
         }
+        if constexpr (!Tr::JOINS) {
+            if (any_nan(v, n)) {
+                const int p = int((f.e - o) / C), y = p / W, x = p - y * W;
+                const E* in = input_map(0);
+                if (at_border(y, x, H, W)) v = direct_sum<Tr::BWD>((const T*)a.w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
+                    const size_t e = (size_t(y + kh - 1) * W + (x + kw - 1)) * C + c;
+                    if constexpr (MODE == CV_DSECOND) return load_f32(y_map + e) > 0.f ? in[e] : 0.f;
+                    else return load_f32(in + e);
+                });
+            }
+        }
         if constexpr (!Tr::BWD) {
             v.x += f.p.x; v.y += f.p.y; v.z += f.p.z; v.w += f.p.w;
             if constexpr (MODE == CV_SECOND) { v.x += f.q.x; v.y += f.q.y; v.z += f.q.z; v.w += f.q.w; }
@@ -514,6 +553,16 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         }
     };
 
+    // a convolution's sum, taken again where any_nan says so; w: its weights, tile: where its input is
+    auto checked = [&](const f32x4& v, const void* w, uint32_t tile, int t, int p, int o, int n) -> f32x4 {
+        if (!any_nan(v, n)) return v;
+        const int y = p / W, x = p - y * W;
+        if (!at_border(y, x, H, W)) return v;
+        return direct_sum<false>((const T*)w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
+            return load_f32(reinterpret_cast<const T*>(lds_raw + tile + at[t] + uint32_t(kh * row_bytes + kw * pix_bytes)) + c);
+        });
+    };
+
     if (wave < n_units) unit(wave);
     First first;
     if (!binary && wave < n_units) prepare(first, nw.w3a, 0);
@@ -596,7 +645,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         clear();
         first.run(acc);
         results([&](int t, int p, int o, int n) {
-            f32x4 v = acc[t][0];
+            f32x4 v = checked(acc[t][0], nw.w3a, 0, t, p, o, n);
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c], 0.f);
             store4<FULL>(reinterpret_cast<T*>(lds_raw + tile_bytes + at[t] + centre) + o, n, v);
@@ -615,7 +664,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         clear();
         second.run(acc);
         results([&](int t, int p, int o, int n) {
-            f32x4 v = acc[t][0];
+            f32x4 v = checked(acc[t][0], nw.w3b, uint32_t(tile_bytes), t, p, o, n);
             const f32x4 res = load4<FULL>(reinterpret_cast<const T*>(lds_raw + at[t] + centre) + o, n);
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c] + res[c], 0.f);

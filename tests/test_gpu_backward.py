@@ -114,6 +114,43 @@ def test_the_width_of_a_launch_group_does_not_change_the_gradients_bits(dyn, uti
         assert maxnorm(got[name], getattr(ref, name)) < 1e-4, name
 
 
+def same_where_not_finite(got, ref, bar):
+    fin = np.isfinite(ref)
+    assert (np.isinf(got) == np.isinf(ref)).all() and (np.isnan(got) == np.isnan(ref)).all()
+    assert (np.sign(got[np.isinf(ref)]) == np.sign(ref[np.isinf(ref)])).all()
+    assert maxnorm(got[fin], ref[fin]) < bar
+
+
+@pytest.mark.parametrize("C,H,W", [(16, 8, 7), (20, 9, 33), (3, 4, 5), (33, 1, 1)])
+def test_what_lies_outside_the_map_contributes_nothing_to_a_gradient(dyn, util, oracle, C, H, W):
+    """Infinite gradients and map values next to the zeros that stand for what lies outside the map (and for the padding column of an
+    odd width), and infinite weights at taps that never lie inside."""
+    from tests.test_gpu_iep import active_workload
+    w = active_workload("f32", C, H, W)
+    dout = np.abs(np.random.default_rng(5).standard_normal(w.feats.shape)).astype(np.float32) + np.float32(0.1)
+    bad = dout.copy()
+    bad[:, 0, 0, 1] = np.inf                                  # g at a corner: the taps that look out of the map get nothing of it
+    ref, (got, _) = oracle.iep_backward_workload(w, bad), run_backward(dyn, util, w, bad)
+    assert np.isfinite(ref.dw3b).any() and np.isinf(ref.dw3b).any()
+    for name in ("dw3b", "db3b"):
+        same_where_not_finite(got[name], getattr(ref, name), 1e-4)
+    v = active_workload("f32", C, H, W)
+    v.feats[:, 0, W - 1, 2] = np.inf                          # u beside the padding column
+    ref, (got, _) = oracle.iep_backward_workload(v.subset([0, 2]), dout[[0, 2]]), run_backward(dyn, util, v.subset([0, 2]), dout[[0, 2]])
+    assert np.isinf(ref.dw3a).any() and np.isfinite(ref.dw3a).any()
+    same_where_not_finite(got["dw3a"], ref.dw3a, 1e-4)
+    ref, (got, _) = oracle.iep_backward_workload(v, dout), run_backward(dyn, util, v, dout)
+    same_where_not_finite(got["dw1"], ref.dw1, 1e-4)          # the join's arguments
+    v = active_workload("f32", C, 1, W)
+    for t in (v.w3a, v.w3b):
+        t[1, 1, 0, :, 2] = np.inf
+        t[2, 0, 2, :, 1] = np.nan
+    ref, (got, _) = oracle.iep_backward_workload(v, dout[:, :1]), run_backward(dyn, util, v, np.ascontiguousarray(dout[:, :1]))
+    for name in NAMES:
+        assert np.isfinite(getattr(ref, name)).all(), name
+        assert maxnorm(got[name], getattr(ref, name)) < 1e-4, name
+
+
 def test_bf16_fast_shape_after_the_fused_forward(dyn, util, oracle):
     """bf16, C = 128, 14 x 14: the forward pass runs the fused MFMA kernels and leaves every node's result in the
     workspace; the backward pass reads them from there."""

@@ -490,3 +490,40 @@ def test_the_width_of_a_launch_group_does_not_change_the_bits(dyn, util, oracle,
     for n in (1, 2, 4, 8):
         assert (util.iep_run(dyn, w.subset(range(n))) == full[:n]).all(), n
     assert util.normwise(full[:1], oracle.iep_forward_workload(w.subset([0]))) < TOL[dtype]
+
+
+def active_workload(dtype, C, H, W, seed=3):
+    """One- and two-argument modules with every map and weight positive."""
+    from workloads.rng import round_bf16
+    arity = np.array([0, 1, 2], np.uint8)
+    progs = [np.array(p, np.int32) for p in ([1, 0], [2, 0, 0], [1, 0])]
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    pos = lambda a: (round_bf16(np.abs(a) + np.float32(0.01)) if dtype == "bf16" else np.abs(a) + np.float32(0.01))
+    feats = pos(iep.make_feats(seed, len(progs), H, W, C, dtype))
+    w1, b1, w3a, b3a, w3b, b3b = iep.make_weights(seed, arity, C, dtype)
+    return iep.IepWorkload("active", dtype, arity, np.concatenate(progs), off, C, H, W, feats, pos(w1), np.abs(b1), pos(w3a), np.abs(b3a),
+                           pos(w3b), np.abs(b3b))
+
+
+@pytest.mark.parametrize("dtype,C,H,W", [("f32", 16, 8, 8), ("f32", 20, 9, 33), ("f32", 3, 4, 5), ("bf16", 32, 5, 6), ("bf16", 40, 15, 15),
+                                         ("f32", 64, 14, 14), ("bf16", 12, 3, 3)])
+def test_a_tap_outside_the_map_contributes_nothing_whatever_its_weight(dyn, util, oracle, dtype, C, H, W):
+    """An infinite weight at tap (0, 0) makes its channel infinite wherever the tap lies inside the map, and nowhere else; on maps
+    of one row (column) the whole upper tap row (left tap column) never does."""
+    w = active_workload(dtype, C, H, W)
+    w.w3b[1:, 1, 0, 0, 2] = np.inf
+    got, ref = util.iep_run(dyn, w), oracle.iep_forward_workload(w)
+    inf = np.isinf(ref)
+    assert inf[:, 1:, 1:, 1].all() and not inf[:, 0].any() and not inf[:, :, 0].any()
+    assert (np.isinf(got) == inf).all()
+    assert util.normwise(got[~inf], ref[~inf]) < TOL[dtype]
+    for shape, taps in (((1, W), (slice(0, 1), slice(0, 3))), ((H, 1), (slice(0, 3), slice(2, 3)))):
+        w = active_workload(dtype, C, *shape)
+        if dtype == "bf16" and (C * shape[0] * shape[1]) % 2:
+            continue
+        for t in (w.w3a, w.w3b):
+            t[1, 1, taps[0], taps[1], 2] = np.inf
+            t[2, 0, taps[0], taps[1], 1] = np.nan
+        got, ref = util.iep_run(dyn, w), oracle.iep_forward_workload(w)
+        assert np.isfinite(ref).all()
+        assert util.normwise(got, ref) < TOL[dtype], shape
