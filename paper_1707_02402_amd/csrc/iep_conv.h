@@ -267,9 +267,9 @@ struct ConvSteps {
 // A tap outside the map contributes nothing, whatever its weight; the matrix instructions multiply a zero with it, which is NaN for
 // a weight that is not finite.  Nothing else brings a NaN in from outside, so a sum at the map's border that came out NaN is taken
 // again, tap by tap: rare, and out of the way of the others.
-__device__ __forceinline__ bool any_nan(const f32x4& v, int n)          // among channels 0 .. n - 1
+__device__ __forceinline__ bool any_nan(const f32x4& v)                 // (one too many is no harm: a direct sum is always right)
 {
-    return __builtin_expect((v.x != v.x) | (n > 1 && v.y != v.y) | (n > 2 && v.z != v.z) | (n > 3 && v.w != v.w), 0);
+    return __builtin_expect(__builtin_isunordered(v.x, v.y) | __builtin_isunordered(v.z, v.w), 0);
 }
 __device__ __forceinline__ bool at_border(int y, int x, int H, int W) { return y == 0 || x == 0 || y == H - 1 || x == W - 1; }
 // w: the function's weights.  pixel(kh, kw, c): channel c of the pixel under tap (kh, kw), as a float.  BWD: the data gradient (taps
@@ -427,28 +427,8 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) red[(wave * MT * NT + t * NT + nt) * 64 + lane] = acc[t][nt];
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-        const Out& f = fin[k];
-        if (f.n <= 0) continue;
-        const int tt = wave + 4 * k, o = f.o, n = f.n;
-        f32x4 v = red[tt * 64 + lane];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const f32x4 p = red[(w * MT * NT + tt) * 64 + lane];
-            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-        }
-        if constexpr (!Tr::JOINS) {
-            if (any_nan(v, n)) {
-                const int p = int((f.e - o) / C), y = p / W, x = p - y * W;
-                const E* in = input_map(0);
-                if (at_border(y, x, H, W)) v = direct_sum<Tr::BWD>((const T*)a.w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
-                    const size_t e = (size_t(y + kh - 1) * W + (x + kw - 1)) * C + c;
-                    if constexpr (MODE == CV_DSECOND) return load_f32(y_map + e) > 0.f ? in[e] : 0.f;
-                    else return load_f32(in + e);
-                });
-            }
-        }
+    auto finish = [&](const Out& f, f32x4 v) {
+        const int o = f.o, n = f.n;
         if constexpr (!Tr::BWD) {
             v.x += f.p.x; v.y += f.p.y; v.z += f.p.z; v.w += f.p.w;
             if constexpr (MODE == CV_SECOND) { v.x += f.q.x; v.y += f.q.y; v.z += f.q.z; v.w += f.q.w; }
@@ -474,6 +454,42 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
             else
                 for (int c = 0; c < 4; ++c)
                     if (c < n) (o + c < C ? d0 : d1)[c] = v[c];
+        }
+    };
+    bool again[NF];
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+        const Out& f = fin[k];
+        again[k] = false;
+        if (f.n <= 0) continue;
+        const int tt = wave + 4 * k;
+        f32x4 v = red[tt * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+            const f32x4 p = red[(w * MT * NT + tt) * 64 + lane];
+            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+        }
+        if (!Tr::JOINS) again[k] = any_nan(v);
+        finish(f, v);
+    }
+    if constexpr (!Tr::JOINS) {
+        bool any = again[0];
+#pragma unroll
+        for (int k = 1; k < NF; ++k) any |= again[k];
+        // The end, right here: the compiler's branch to it over what follows waits for instructions that nobody has fetched (7 x 7
+        // maps: 1.5 % of a pass).
+        asm volatile("s_cmp_lg_u64 %0, 0\n\ts_cbranch_scc1 1f\n\ts_endpgm\n1:" ::"s"(__ballot(any)) : "scc", "memory");
+#pragma unroll
+        for (int k = 0; k < NF; ++k) {
+            const Out& f = fin[k];
+            const int p = int((f.e - f.o) / C), y = p / W, x = p - y * W;
+            if (!again[k] || !at_border(y, x, H, W)) continue;
+            const E* in = input_map(0);
+            finish(f, direct_sum<Tr::BWD>((const T*)a.w + size_t(it.type) * C * 9 * C, C, H, W, y, x, f.o, f.n, [&](int kh, int kw, int c) {
+                const size_t e = (size_t(y + kh - 1) * W + (x + kw - 1)) * C + c;
+                if constexpr (MODE == CV_DSECOND) return load_f32(y_map + e) > 0.f ? in[e] : 0.f;
+                else return load_f32(in + e);
+            }));
         }
     }
 }
@@ -555,7 +571,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
 
     // a convolution's sum, taken again where any_nan says so; w: its weights, tile: where its input is
     auto checked = [&](const f32x4& v, const void* w, uint32_t tile, int t, int p, int o, int n) -> f32x4 {
-        if (!any_nan(v, n)) return v;
+        if (!any_nan(v)) return v;
         const int y = p / W, x = p - y * W;
         if (!at_border(y, x, H, W)) return v;
         return direct_sum<false>((const T*)w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
