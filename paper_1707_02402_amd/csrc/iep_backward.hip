@@ -235,12 +235,6 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                 }
         }
     }
-#pragma unroll 1
-    for (; again; again &= again - 1) {
-        const int b = __builtin_ctzll(again), co = co0 + 8 * wave + 4 * hk + (b & 3), ci = ci0 + r;
-        const size_t row = size_t(type) * C + co;
-        a.dw[which][JOIN ? row * 2 * C + arg * C + ci : (row * 9 + (b >> 2)) * C + ci] = direct(b >> 2, co, ci);
-    }
     if (ci0 == 0 && arg == 0) {                                                  // bias: the lane halves and the waves in order
         __syncthreads();
         float* sum = reinterpret_cast<float*>(lds_raw);
@@ -251,6 +245,13 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
             for (int w = 0; w < 8; ++w) v += sum[w * 32 + tid];
             a.db[which][size_t(type) * C + co0 + tid] = v;
         }
+    }
+    end_unless(again != 0);
+#pragma unroll 1
+    for (; again; again &= again - 1) {
+        const int b = __builtin_ctzll(again), co = co0 + 8 * wave + 4 * hk + (b & 3), ci = ci0 + r;
+        const size_t row = size_t(type) * C + co;
+        a.dw[which][JOIN ? row * 2 * C + arg * C + ci : (row * 9 + (b >> 2)) * C + ci] = direct(b >> 2, co, ci);
     }
 }
 
