@@ -272,6 +272,12 @@ __device__ __forceinline__ bool any_nan(const f32x4& v)                 // (one 
     return __builtin_expect(__builtin_isunordered(v.x, v.y) | __builtin_isunordered(v.z, v.w), 0);
 }
 __device__ __forceinline__ bool at_border(int y, int x, int H, int W) { return y == 0 || x == 0 || y == H - 1 || x == W - 1; }
+// Ends the wave unless one of its lanes says otherwise.  (The compiler's branch to the end over what follows waits for instructions
+// that nobody has fetched, 1.5 % of a pass at 7 x 7, where launches are short.)
+__device__ __forceinline__ void end_unless(bool lane)
+{
+    asm volatile("s_cmp_lg_u64 %0, 0\n\ts_cbranch_scc1 1f\n\ts_endpgm\n1:" ::"s"(__ballot(lane)) : "scc", "memory");
+}
 // w: the function's weights.  pixel(kh, kw, c): channel c of the pixel under tap (kh, kw), as a float.  BWD: the data gradient (taps
 // backwards, sums over the weights' rows)
 template <bool BWD, typename T, typename Pixel>
@@ -476,9 +482,7 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
         bool any = again[0];
 #pragma unroll
         for (int k = 1; k < NF; ++k) any |= again[k];
-        // The end, right here: the compiler's branch to it over what follows waits for instructions that nobody has fetched (7 x 7
-        // maps: 1.5 % of a pass).
-        asm volatile("s_cmp_lg_u64 %0, 0\n\ts_cbranch_scc1 1f\n\ts_endpgm\n1:" ::"s"(__ballot(any)) : "scc", "memory");
+        end_unless(any);
 #pragma unroll
         for (int k = 0; k < NF; ++k) {
             const Out& f = fin[k];
@@ -491,6 +495,52 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
                 else return load_f32(in + e);
             }));
         }
+    }
+}
+
+// ---- one thread per output element ----------------------------------------------------------------------------------
+// Few channels, or maps of a few pixels: a 16 x 16 tile of the matrix instructions is then mostly padding, and taps that lie
+// outside the map (8 of 9 on a 1 x 1 map) are multiplied all the same.  1000 modules, us, this kernel / k_conv / k_node:
+// fp32 C = 3, 14 x 14: 33 / 89 / 55; bf16 C = 4, 28 x 28: 140 / 701 / 318; 20000 modules, fp32 C = 24, 1 x 1: 53 / 387 / 475.
+template <typename T, ConvMode MODE>
+__global__ __launch_bounds__(256) void k_conv_plain(const dynb_item* items, ConvArgs a)
+{
+    using Tr = ConvTraits<MODE>;
+    static_assert(!Tr::BWD, "forward convolutions");
+    const int i = blockIdx.y;
+    const dynb_item it = items[i];
+    const bool binary = it.src1 != DYNB_NO_ARG;           // uniform over the workgroup
+    if (Tr::JOINS && !binary) return;
+    const int C = a.C, H = a.H, W = a.W;
+    const size_t chw = size_t(H) * W * C;
+    const int e = int(blockIdx.x * 256u + threadIdx.x);
+    if (unsigned(e) >= chw) return;
+    const int p = e / C, co = e - p * C;
+    float acc = a.bias ? a.bias[size_t(it.type) * C + co] : 0.f;
+    if constexpr (Tr::JOINS) {
+        const T* w = (const T*)a.w + (size_t(it.type) * C + co) * 2 * C;
+        const T* x0 = conv_src<T>(a, it.src0, chw) + size_t(p) * C;
+        const T* x1 = conv_src<T>(a, it.src1, chw) + size_t(p) * C;
+        for (int ci = 0; ci < C; ++ci) acc += load_f32(x0 + ci) * load_f32(w + ci);
+        for (int ci = 0; ci < C; ++ci) acc += load_f32(x1 + ci) * load_f32(w + C + ci);
+        store_f32((T*)a.u + size_t(a.first_kept + i) * chw + e, fmaxf(acc, 0.f));
+    } else {
+        T* const mid = (T*)a.mid + size_t(a.first_kept + i) * chw;
+        const T* const u = binary ? (const T*)a.u + size_t(a.first_kept + i) * chw : conv_src<T>(a, it.src0, chw);
+        const T* const in = MODE == CV_SECOND ? mid : u;
+        const T* const w = (const T*)a.w + (size_t(it.type) * C + co) * 9 * C;
+        const int y = p / W, x = p - y * W;
+        for (int kh = 0; kh < 3; ++kh) {
+            if (unsigned(y + kh - 1) >= unsigned(H)) continue;
+            for (int kw = 0; kw < 3; ++kw) {
+                if (unsigned(x + kw - 1) >= unsigned(W)) continue;
+                const T* px = in + (size_t(y + kh - 1) * W + (x + kw - 1)) * C;
+                const T* wk = w + (kh * 3 + kw) * C;
+                for (int ci = 0; ci < C; ++ci) acc += load_f32(px + ci) * load_f32(wk + ci);
+            }
+        }
+        if constexpr (MODE == CV_SECOND) store_f32(conv_dst<T>(a, it.dst, chw) + e, fmaxf(acc + load_f32(u + e), 0.f));
+        else store_f32(mid + e, fmaxf(acc, 0.f));
     }
 }
 
@@ -569,16 +619,6 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         }
     };
 
-    // a convolution's sum, taken again where any_nan says so; w: its weights, tile: where its input is
-    auto checked = [&](const f32x4& v, const void* w, uint32_t tile, int t, int p, int o, int n) -> f32x4 {
-        if (!any_nan(v)) return v;
-        const int y = p / W, x = p - y * W;
-        if (!at_border(y, x, H, W)) return v;
-        return direct_sum<false>((const T*)w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
-            return load_f32(reinterpret_cast<const T*>(lds_raw + tile + at[t] + uint32_t(kh * row_bytes + kw * pix_bytes)) + c);
-        });
-    };
-
     if (wave < n_units) unit(wave);
     First first;
     if (!binary && wave < n_units) prepare(first, nw.w3a, 0);
@@ -654,6 +694,23 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         __syncthreads();
     }
 
+    auto put_mid = [&](int t, int p, int o, int n, f32x4 v, const f32x4& b) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c], 0.f);
+        store4<FULL>(reinterpret_cast<T*>(lds_raw + tile_bytes + at[t] + centre) + o, n, v);
+        if (nw.keep) store4<FULL>((T*)a.mid + size_t(a.first_kept + i) * chw + size_t(p) * C + o, n, v);
+    };
+    T* const dst = conv_dst<T>(a, it.dst, chw);
+    auto put_result = [&](int t, int p, int o, int n, f32x4 v, const f32x4& b) {
+        const f32x4 res = load4<FULL>(reinterpret_cast<const T*>(lds_raw + at[t] + centre) + o, n);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c] + res[c], 0.f);
+        store4<FULL>(dst + size_t(p) * C + o, n, v);
+    };
+    // (any_nan: a NaN in mid concerns all waves and is noted in the padding of the second tile's first pixel, which is zero)
+    uint32_t* const flag = reinterpret_cast<uint32_t*>(lds_raw + tile_bytes + a.ck * ES);
+    bool nan = false;
+
     // ---- mid = ReLU(conv3x3(first tile) + b3a) into the second tile
     for (int u = wave; u < n_units; u += NWAVE) {
         if (u != wave) { unit(u); prepare(first, nw.w3a, 0); }
@@ -661,30 +718,56 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         clear();
         first.run(acc);
         results([&](int t, int p, int o, int n) {
-            f32x4 v = checked(acc[t][0], nw.w3a, 0, t, p, o, n);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c], 0.f);
-            store4<FULL>(reinterpret_cast<T*>(lds_raw + tile_bytes + at[t] + centre) + o, n, v);
-            if (nw.keep) store4<FULL>((T*)a.mid + size_t(a.first_kept + i) * chw + size_t(p) * C + o, n, v);
+            nan |= any_nan(acc[t][0]);
+            put_mid(t, p, o, n, acc[t][0], b);
         });
     }
+    if (nan) *flag = 1;
     Second second;
     if (wave < n_units) { unit(wave); prepare(second, nw.w3b, uint32_t(tile_bytes)); }
     __syncthreads();
+    const uint32_t mid_nan = *flag;
 
     // ---- result = ReLU(conv3x3(second tile) + b3b + first tile)
-    T* const dst = conv_dst<T>(a, it.dst, chw);
+    nan = false;
     for (int u = wave; u < n_units; u += NWAVE) {
         if (u != wave) { unit(u); prepare(second, nw.w3b, uint32_t(tile_bytes)); }
         const f32x4 b = bias_of(nw.b3b);
         clear();
         second.run(acc);
         results([&](int t, int p, int o, int n) {
-            f32x4 v = checked(acc[t][0], nw.w3b, uint32_t(tile_bytes), t, p, o, n);
-            const f32x4 res = load4<FULL>(reinterpret_cast<const T*>(lds_raw + at[t] + centre) + o, n);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c] + res[c], 0.f);
-            store4<FULL>(dst + size_t(p) * C + o, n, v);
+            nan |= any_nan(acc[t][0]);
+            put_result(t, p, o, n, acc[t][0], b);
+        });
+    }
+    end_unless(nan | (mid_nan != 0));
+
+    // ---- rare: sums that any_nan speaks of.  If there were any in mid, mid's border and every result, else this lane's results at the
+    // border.  (A wave gets here alone, or all of them do, with mid_nan.)
+    auto direct = [&](const void* w, uint32_t tile, int t, int p, int o, int n) -> f32x4 {
+        const int y = p / W, x = p - y * W;
+        return direct_sum<false>((const T*)w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
+            return load_f32(reinterpret_cast<const T*>(lds_raw + tile + at[t] + uint32_t(kh * row_bytes + kw * pix_bytes)) + c);
+        });
+    };
+    if (mid_nan) {
+        __syncthreads();
+#pragma unroll 1
+        for (int u = wave; u < n_units; u += NWAVE) {
+            unit(u);
+            const f32x4 b = bias_of(nw.b3a);
+            results([&](int t, int p, int o, int n) {
+                if (at_border(p / W, p % W, H, W)) put_mid(t, p, o, n, direct(nw.w3a, 0, t, p, o, n), b);
+            });
+        }
+        __syncthreads();
+    }
+#pragma unroll 1
+    for (int u = wave; u < n_units; u += NWAVE) {
+        unit(u);
+        const f32x4 b = bias_of(nw.b3b);
+        results([&](int t, int p, int o, int n) {
+            if (mid_nan || (nan && at_border(p / W, p % W, H, W))) put_result(t, p, o, n, direct(nw.w3b, uint32_t(tile_bytes), t, p, o, n), b);
         });
     }
 }
@@ -767,18 +850,51 @@ int launch_conv(const dynb_item* items, const ConvArgs& a, int count, hipStream_
     return a.C % KS == 0 ? launch_conv_full<T, MODE, true>(items, a, count, st) : launch_conv_full<T, MODE, false>(items, a, count, st);
 }
 
+// The three ways to run a module's convolutions are chosen by the shape alone, never by how many modules there are: each adds up in
+// an order of its own, and another schedule must not change a result's bits.
+
+// k_conv_plain, where its products cost less than the tiles' padding: a product inside the map takes it some 3 ps (all CUs
+// busy), a 16 x 16 tile takes k_conv 9 ns (fp32), 14 to 22 ns (bf16, fewer than 16 channels: 32 are summed at a time) or 10 ns (bf16).
+// 20000 modules, us, plain / tiles, on the two sides of the line: fp32 4 x 4, C = 5: 166 / 196, C = 6: 213 / 198; 14 x 14, C = 4:
+// 885 / 906, C = 5: 2210 / 1571; 1 x 1, C = 100: 825 / 2636; bf16 10 x 10, C = 6: 1353 / 2560, C = 8: 1800 / 1382; 3 x 3, C = 12:
+// 356 / 404, C = 16: 988 / 292.
+template <typename T>
+bool plain_shape(const ConvArgs& a)
+{
+    const double taps = (3.0 * a.H - 2) * (3.0 * a.W - 2);               // inside the map, over all pixels
+    const double tiles = double((size_t(a.H) * a.W + 15) / 16) * ((a.C + 15) / 16);
+    return double(a.C) * a.C * taps <= tiles * (sizeof(T) == 4 ? 3000 : a.C < 16 ? 7100 : 3500);
+}
+
+template <typename T, ConvMode MODE>
+int launch_conv_plain(const dynb_item* items, const ConvArgs& a, int count, hipStream_t st)
+{
+    const size_t chw = size_t(a.H) * a.W * a.C;
+    hipLaunchKernelGGL((k_conv_plain<T, MODE>), dim3(unsigned((chw + 255) / 256), unsigned(count)), dim3(256), 0, st, items, a);
+    return DYNB_OK;
+}
+
+// k_node: pixel tiles per unit: 4 read the weights a quarter as often, 1 gives all waves work where there are few tiles
+inline bool node_wide(int pt, int ct) { return ((pt + 3) / 4 * ct + 7) / 8 * 4 <= (pt * ct + 7) / 8; }
+
 // Whole modules by k_node, where that takes one CU no longer than two or three launches of k_conv take to get going (5 us
 // each) and two tiles fit LDS.  A CU's time: its MFMAs, or its weights, of which one CU was seen to take in some 12 bytes a clock
-// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 24 to 32 us against 2 x 5 to 3 x 7).
+// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 24 to 32 us against 2 x 5 to 3 x 7),
+// and with every round of units a wait for weights: one lone module, bf16 C = 48, 14 x 14, 5 rounds: 58 us against 15 by k_conv;
+// C = 20, 20 x 20, 7 rounds: 79 / 20 (and 35 by k_conv_plain); C = 24, 14 x 14, 1 round of wide units: 16 / 15.  Below 16 channels the
+// tiles are cut short and k_conv wins from two rounds on (bf16 C = 8, 14 x 14: 21 / 14) or with many modules (fp32 C = 6, 4 x 4,
+// 20000: 335 / 198); so it does on maps of a few pixels with cut steps (2 x 2, 20000: fp32 C = 20 474 / 386, bf16 C = 16 420 / 282).
 template <typename T>
 bool node_shape(const ConvArgs& a)
 {
     constexpr int ES = int(sizeof(T)), KS = ES == 4 ? 16 : 32, STEP_CLOCKS = ES == 4 ? 128 : 16;
     const long long steps = (a.C + KS - 1) / KS, P = (long long)a.H * a.W;
     const long long lds = 2ll * (a.H + 2) * (a.W + 2) * conv_pixel_bytes(int(steps * KS), ES);
-    if (a.W > 64 || P > 2048 || lds > 160 * 1024) return false;
-    const long long mfma = (P + 15) / 16 * ((a.C + 15) / 16) * steps * 9 * 2 * STEP_CLOCKS / 4, weights = 2ll * 9 * a.C * a.C * ES / 12;
-    return std::max(mfma, weights) <= 10000;
+    if (a.C < 16 || a.W > 64 || P > 2048 || lds > 160 * 1024 || (P < 9 && a.C < 24 && a.C % KS != 0)) return false;
+    const int pt = int(P + 15) / 16, ct = (a.C + 15) / 16;
+    const int rounds = ((node_wide(pt, ct) ? (pt + 3) / 4 : pt) * ct + 7) / 8;
+    const long long mfma = (long long)pt * ct * steps * 9 * 2 * STEP_CLOCKS / 4, weights = 2ll * 9 * a.C * a.C * ES / 12;
+    return rounds <= 2 && std::max(mfma, weights) <= 10000;
 }
 
 template <typename T, int MT, bool FULL>
@@ -804,8 +920,7 @@ int launch_node(const dynb_item* items, const NodeArgs& nw, ConvArgs a, hipStrea
     a.ck = (a.C + KS - 1) / KS * KS;
     a.m_sw = recip20_of(a.W);
     const int pt = (a.H * a.W + 15) / 16, ct = (a.C + 15) / 16;
-    // pixel tiles per unit: 4 read the weights a quarter as often, 1 gives all waves work where there are few tiles
-    const bool wide = ((pt + 3) / 4 * ct + 7) / 8 * 4 <= (pt * ct + 7) / 8;
+    const bool wide = node_wide(pt, ct);
     const bool full = a.C % KS == 0;
     if (wide) return full ? launch_node_tile<T, 4, true>(items, nw, a, st) : launch_node_tile<T, 4, false>(items, nw, a, st);
     return full ? launch_node_tile<T, 1, true>(items, nw, a, st) : launch_node_tile<T, 1, false>(items, nw, a, st);

@@ -8,7 +8,8 @@
 //                      add and ReLU all run from that tile on MFMA, and the result is scattered to
 //                      the node's slot (or to the output tensor for a root).
 //   * k_conv         — any C/H/W, fp32 or bf16 storage, fp32 accumulate (iep_conv.h): one launch per convolution of a
-//                      launch group, tiles small enough to spread narrow groups over the chip.
+//                      launch group, tiles small enough to spread narrow groups over the chip; for small maps k_node, a
+//                      whole module per workgroup, for a few channels or pixels k_conv_plain.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -551,7 +552,7 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
     const bool timed = dynb::timing_on(), coarse = dynb::timing_coarse();
     if (timed) dynb::timing_mark(st, dynb::ST_SETUP, 0);
     int32_t evals = 0;
-    const bool whole = node_shape<T>(a);
+    const bool plain = plain_shape<T>(a), whole = !plain && node_shape<T>(a);
     for (const dynb_launch& l : p->launches) {
         evals += l.count;
         if (whole) {
@@ -566,11 +567,11 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
             const dynb_item* items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
             a.first_kept = p->keep ? l.start + off : off;
             int rc = DYNB_OK;
-            if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = launch_conv<T, CV_JOIN>(items, a, count, st); }
+            if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = (plain ? launch_conv_plain<T, CV_JOIN> : launch_conv<T, CV_JOIN>)(items, a, count, st); }
             a.w = w->w3a; a.bias = w->b3a;
-            if (rc == DYNB_OK) rc = launch_conv<T, CV_FIRST>(items, a, count, st);
+            if (rc == DYNB_OK) rc = (plain ? launch_conv_plain<T, CV_FIRST> : launch_conv<T, CV_FIRST>)(items, a, count, st);
             a.w = w->w3b; a.bias = w->b3b;
-            if (rc == DYNB_OK) rc = launch_conv<T, CV_SECOND>(items, a, count, st);
+            if (rc == DYNB_OK) rc = (plain ? launch_conv_plain<T, CV_SECOND> : launch_conv<T, CV_SECOND>)(items, a, count, st);
             if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a convolution could not be launched");
         }
         if (timed && !coarse) dynb::timing_mark(st, int32_t(&l - p->launches.data()), l.count);

@@ -506,7 +506,7 @@ def active_workload(dtype, C, H, W, seed=3):
 
 
 @pytest.mark.parametrize("dtype,C,H,W", [("f32", 16, 8, 8), ("f32", 20, 9, 33), ("f32", 3, 4, 5), ("bf16", 32, 5, 6), ("bf16", 40, 15, 15),
-                                         ("f32", 64, 14, 14), ("bf16", 12, 3, 3)])
+                                         ("f32", 64, 14, 14), ("bf16", 12, 3, 3), ("f32", 16, 14, 14), ("bf16", 32, 14, 14)])
 def test_a_tap_outside_the_map_contributes_nothing_whatever_its_weight(dyn, util, oracle, dtype, C, H, W):
     """An infinite weight at tap (0, 0) makes its channel infinite wherever the tap lies inside the map, and nowhere else; on maps
     of one row (column) the whole upper tap row (left tap column) never does."""
@@ -527,3 +527,24 @@ def test_a_tap_outside_the_map_contributes_nothing_whatever_its_weight(dyn, util
         got, ref = util.iep_run(dyn, w), oracle.iep_forward_workload(w)
         assert np.isfinite(ref).all()
         assert util.normwise(got, ref) < TOL[dtype], shape
+
+
+@pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 1, 1, 1, 300), ("f32", 4, 14, 14, 5), ("f32", 5, 14, 14, 5), ("f32", 5, 4, 4, 9), ("f32", 6, 4, 4, 9),
+                                           ("f32", 100, 1, 1, 9), ("f32", 15, 8, 8, 9), ("f32", 3, 1, 257, 4), ("bf16", 7, 10, 10, 5), ("bf16", 8, 10, 10, 5),
+                                           ("bf16", 12, 3, 3, 9), ("bf16", 16, 2, 2, 9), ("bf16", 14, 14, 14, 5), ("bf16", 24, 20, 20, 3)])
+def test_few_channels_and_tiny_maps(dyn, util, oracle, dtype, C, H, W, B):
+    """Both sides of the lines between a thread per output element, a workgroup per module and a launch per convolution; every
+    schedule gives the same bits, and maps may lie at any element's address."""
+    import torch
+    w = iep.small_mixed(seed=C + H, B=B, C=C, H=H, W=W, dtype=dtype, min_len=1, max_len=8)
+    ref = oracle.iep_forward_workload(w)
+    base = util.iep_run(dyn, w)
+    for i in range(w.B):
+        assert util.normwise(base[i], ref[i]) < TOL[dtype] or np.abs(ref[i]).max() == 0, i
+    for flags in (1, 2, 3, dyn.DYNB_PLAN_BALANCE):
+        assert (util.iep_run(dyn, w, flags) == base).all(), flags
+    if (base != 0).any() and (dtype == "f32" or (C * H * W) % 2 == 0):
+        feats = util.to_dev(w.feats, dtype)
+        shifted = torch.cat([feats.flatten()[:4 // feats.element_size()], feats.flatten()])[4 // feats.element_size():].view(feats.shape)
+        assert shifted.data_ptr() % 16 == 4
+        assert (util.iep_run(dyn, w, feats=shifted) == base).all()
