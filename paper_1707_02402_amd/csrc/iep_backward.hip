@@ -47,7 +47,7 @@ namespace {
 // An item's 32 + 32 channels are staged into LDS as fp32, pixel-major without padding (a fragment, two pixels x 32
 // channels, is then 64 consecutive words), the input with its halo; a step of two pixels reads 1 + TAPS fragments
 // for TAPS MFMAs of 64 clocks.  The waves split an item's pixels and meet in LDS at the end, in wave order.  Maps that do
-// not fit are taken in bands of rows and segments of columns.
+// not fit are taken in bands of rows and segments of columns; of maps of a few pixels several items are staged at a time.
 // (Per launch group, one thread per gradient element, the sums took most of a training step's 179 ms at 21 programs,
 // C = 128, 14 x 14.)
 struct WgradArgs {
@@ -68,9 +68,10 @@ struct WgradArgs {
     int32_t first_type;           // function of blockIdx.y = 0
     int32_t C, H, W;
     int32_t sw, band;             // columns of a segment, rows of a band
+    int32_t many;                 // MANY: items staged at a time (sw = W, band = H)
 };
 
-template <typename T, bool JOIN>
+template <typename T, bool JOIN, bool MANY>
 __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 {
     constexpr int TAPS = JOIN ? 1 : 9, HALO = JOIN ? 0 : 1, PIX = 32 * 4;       // bytes of a staged pixel
@@ -86,7 +87,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 
     // staged pixels of G: band rows x wp columns (even: a step never crosses a row), of the input: with halo
     const int wp = (sw + 1) & ~1, half = wp / 2, icols = wp + 2 * HALO;
-    const uint32_t in_off = uint32_t(a.band * wp * PIX);
+    const int NI = MANY ? a.many : 1;
+    const uint32_t in_off = uint32_t(NI * a.band * wp * PIX);
     const uint32_t m_wp = recip_of(wp), m_icols = recip_of(icols);
 
     f32x16 acc[TAPS];
@@ -109,29 +111,30 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                 JOIN ? A : which == 0 ? (const T*)a.mid + off : ar == 2 ? (const T*)a.u + off : A};
     };
 #pragma unroll 1
-    for (int idx = lo; idx < hi; ++idx) {
-        const Maps m = maps(idx);
-        const float* const G = m.G;
-        const T *const Y = m.Y, *const IN = m.IN;
+    for (int idx = lo; idx < hi; idx += NI) {
+        const int n = MANY ? min(NI, hi - idx) : 1;
+        const Maps one = maps(idx);
 #pragma unroll 1
         for (int x0 = 0; x0 < W; x0 += sw)
 #pragma unroll 1
             for (int y0 = 0; y0 < H; y0 += a.band) {
-                const int rows = min(a.band, H - y0), cols = min(sw, W - x0);
+                const int rows = min(a.band, H - y0), cols = min(sw, W - x0), irows = rows + 2 * HALO;
                 __syncthreads();                                                 // the last band's fragments have been read
                 constexpr int UN = 4;
-                const int ng = rows * wp * 8, ni = (rows + 2 * HALO) * icols * 8;        // 16-byte pieces
+                const int ng = n * rows * wp * 8, ni = n * irows * icols * 8;            // 16-byte pieces
                 for (int base = tid; base < ng; base += 256 * UN) {
                     f32x4 v[UN];
 #pragma unroll
                     for (int k = 0; k < UN; ++k) {
                         const int c = base + k * 256;
-                        const uint32_t pix = uint32_t(c) >> 3, row = div_by(pix, m_wp), col = pix - row * wp;
+                        const uint32_t pix = uint32_t(c) >> 3, line = div_by(pix, m_wp), col = pix - line * wp;
+                        const int it = MANY ? int(line) / rows : 0, row = int(line) - it * rows;
                         const int ch = co0 + (c & 7) * 4;
                         v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
                         if (c < ng && int(col) < cols) {
+                            const Maps m = MANY ? maps(idx + it) : one;
                             const size_t e = (size_t(y0 + row) * W + x0 + col) * C + ch;
-                            v[k] = !JOIN && which == 0 ? masked_gy<false>(G + e, Y + e, C - ch) : load4<false>(G + e, C - ch);
+                            v[k] = !JOIN && which == 0 ? masked_gy<false>(m.G + e, m.Y + e, C - ch) : load4<false>(m.G + e, C - ch);
                         }
                     }
 #pragma unroll
@@ -143,22 +146,27 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 #pragma unroll
                     for (int k = 0; k < UN; ++k) {
                         const int c = base + k * 256;
-                        const uint32_t pix = uint32_t(c) >> 3, row = div_by(pix, m_icols), col = pix - row * icols;
-                        const int ch = ci0 + (c & 7) * 4, y = y0 + int(row) - HALO, x = x0 + int(col) - HALO;
+                        const uint32_t pix = uint32_t(c) >> 3, line = div_by(pix, m_icols), col = pix - line * icols;
+                        const int it = MANY ? int(line) / irows : 0, row = int(line) - it * irows;
+                        const int ch = ci0 + (c & 7) * 4, y = y0 + row - HALO, x = x0 + int(col) - HALO;
                         v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) v[k] = load4<false>(IN + (size_t(y) * W + x) * C + ch, C - ch);
+                        if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) {
+                            const Maps m = MANY ? maps(idx + it) : one;
+                            v[k] = load4<false>(m.IN + (size_t(y) * W + x) * C + ch, C - ch);
+                        }
                     }
 #pragma unroll
                     for (int k = 0; k < UN; ++k)
                         if (base + k * 256 < ni) *reinterpret_cast<f32x4*>(lds_raw + in_off + size_t(base + k * 256) * 16) = v[k];
                 }
                 __syncthreads();
-                // this wave's steps: (row y, pixels 2 x and 2 x + 1), read one step ahead
-                const int S = rows * half, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
+                // this wave's steps: (row y, pixels 2 x and 2 x + 1), read one step ahead; the rows of the staged items follow each
+                // other, iy is the row of the input that goes with y
+                const int S = n * rows * half, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
                 struct Step { float g, in[TAPS]; };
-                auto read = [&](int y, int x, Step& v) {
+                auto read = [&](int y, int iy, int x, Step& v) {
                     const uint32_t ga = uint32_t(((y * half + x) * 2 + hk) * PIX + r * 4);
-                    const uint32_t ia = in_off + uint32_t((y * icols + x * 2 + hk) * PIX + r * 4);
+                    const uint32_t ia = in_off + uint32_t((iy * icols + x * 2 + hk) * PIX + r * 4);
                     v.g = *reinterpret_cast<const float*>(lds_raw + ga);
 #pragma unroll
                     for (int k = 0; k < TAPS; ++k)
@@ -170,17 +178,23 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                     for (int k = 0; k < TAPS; ++k) acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.g, v.in[k], acc[k], 0, 0, 0);
                 };
                 if (s0 < s1) {
-                    int y = s0 / half, x = s0 - y * half;
+                    int y = s0 / half, x = s0 - y * half, left = 0, iy = y;
+                    if constexpr (MANY) { const int it = y / rows; left = (it + 1) * rows - y; iy += it * 2 * HALO; }     // rows left of this item
+                    auto advance = [&]() {
+                        if (++x < half) return;
+                        x = 0; ++y; ++iy;
+                        if (MANY && --left == 0) { left = rows; iy += 2 * HALO; }
+                    };
                     Step p, q;
-                    read(y, x, p);
+                    read(y, iy, x, p);
 #pragma unroll 1
                     for (int st = s0; st < s1; st += 2) {
-                        if (++x == half) { x = 0; ++y; }
-                        if (st + 1 < s1) read(y, x, q);
+                        advance();
+                        if (st + 1 < s1) read(y, iy, x, q);
                         multiply(p);
                         if (st + 1 >= s1) break;
-                        if (++x == half) { x = 0; ++y; }
-                        if (st + 2 < s1) read(y, x, p);
+                        advance();
+                        if (st + 2 < s1) read(y, iy, x, p);
                         multiply(q);
                     }
                 }
@@ -928,31 +942,42 @@ BwdLayout bwd_layout(const dynb_plan* p, const dynb_shape* s)
     return L;
 }
 
-// parameter gradients of all functions, zeros for functions without items
-template <typename T, bool JOIN>
-int launch_wgrad(WgradArgs a, int n_types, hipStream_t st)
+constexpr int WGRAD_LDS_MAX = 80 * 1024;                                  // two workgroups per CU
+template <typename T, bool JOIN, bool MANY>
+int launch_wgrad_items(WgradArgs a, int n_types, size_t lds, hipStream_t st)
 {
-    constexpr int LDS_MAX = 80 * 1024, HALO = JOIN ? 0 : 1;               // two workgroups per CU
     static std::atomic<uint64_t> attr_set{0};                             // one bit per device
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad<T, JOIN>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX),
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad<T, JOIN, MANY>), hipFuncAttributeMaxDynamicSharedMemorySize, WGRAD_LDS_MAX),
                 "hipFuncSetAttribute(k_wgrad)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
-    const int n_seg = (a.W + 31) / 32;
-    a.sw = (a.W + n_seg - 1) / n_seg;
-    const int wp = (a.sw + 1) & ~1, icols = wp + 2 * HALO;
-    a.band = std::min(a.H, (LDS_MAX / 128 - 2 * HALO * icols) / (wp + icols));      // >= 8: sw <= 32
-    const size_t lds = std::max<size_t>(size_t(a.band * wp + (a.band + 2 * HALO) * icols) * 128, size_t(JOIN ? 1 : 3) * 16 * 1024);
     const int cb = (a.C + 31) / 32;
     for (int t0 = 0; t0 < n_types; t0 += 32768) {
         a.first_type = t0;
-        hipLaunchKernelGGL((k_wgrad<T, JOIN>), dim3(unsigned(cb * cb * (JOIN ? 2 : 1)), unsigned(std::min(32768, n_types - t0)), JOIN ? 1 : 2),
+        hipLaunchKernelGGL((k_wgrad<T, JOIN, MANY>), dim3(unsigned(cb * cb * (JOIN ? 2 : 1)), unsigned(std::min(32768, n_types - t0)), JOIN ? 1 : 2),
                            dim3(256), lds, st, a);
     }
     return DYNB_OK;
+}
+
+// parameter gradients of all functions, zeros for functions without items
+template <typename T, bool JOIN>
+int launch_wgrad(WgradArgs a, int n_types, hipStream_t st)
+{
+    constexpr int HALO = JOIN ? 0 : 1;
+    const int n_seg = (a.W + 31) / 32;
+    a.sw = (a.W + n_seg - 1) / n_seg;
+    const int wp = (a.sw + 1) & ~1, icols = wp + 2 * HALO;
+    a.band = std::min(a.H, (WGRAD_LDS_MAX / 128 - 2 * HALO * icols) / (wp + icols));      // >= 8: sw <= 32
+    // Maps of up to 16 pixels: several items at a time, some 64 pixels, where one item would be a trip to memory (3 us) for a few
+    // MFMAs.  10000 programs of 2 modules, fp32, 1 x 1, a training step: C = 1 31 -> 4.0 ms, C = 16 30 -> 4.2.
+    const long long pixels = (long long)a.H * wp;
+    a.many = pixels <= 16 ? int(64 / pixels) : 1;
+    const size_t lds = std::max<size_t>(size_t(a.many) * (a.band * wp + (a.band + 2 * HALO) * icols) * 128, size_t(JOIN ? 1 : 3) * 16 * 1024);
+    return a.many > 1 ? launch_wgrad_items<T, JOIN, true>(a, n_types, lds, st) : launch_wgrad_items<T, JOIN, false>(a, n_types, lds, st);
 }
 
 template <typename T>

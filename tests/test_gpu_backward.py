@@ -94,6 +94,22 @@ def test_ragged_shapes_fp32_with_single_scene_programs(dyn, util, oracle, C, H, 
         assert (again[name] == got[name]).all(), name                     # fixed summation order: same bits
 
 
+@pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 3, 1, 1, 150), ("f32", 33, 2, 2, 90), ("f32", 20, 3, 3, 40), ("f32", 34, 4, 3, 37), ("f32", 5, 1, 16, 30),
+                                           ("f32", 9, 1, 17, 20), ("bf16", 6, 2, 1, 70)])
+def test_parameter_gradients_of_many_items_on_tiny_maps(dyn, util, oracle, dtype, C, H, W, B):
+    """Maps of up to 16 pixels (columns padded to an even number) are summed several items at a time: more items than one round
+    takes, with a remainder, one- and two-argument functions, and functions that no program uses."""
+    w = iep.small_mixed(seed=C + B, B=B, C=C, H=H, W=W, dtype=dtype, min_len=1, max_len=5)
+    dout = np.random.default_rng(C).standard_normal(w.feats.shape).astype(np.float32)
+    ref = oracle.iep_backward_workload(w, dout, round_bf16=dtype == "bf16")
+    got, _ = run_backward(dyn, util, w, dout)
+    for name in NAMES:
+        assert maxnorm(got[name], getattr(ref, name)) < (1e-4 if dtype == "f32" else 2e-2), (name, maxnorm(got[name], getattr(ref, name)))
+    again, _ = run_backward(dyn, util, w, dout)
+    for name in NAMES:
+        assert (again[name] == got[name]).all(), name
+
+
 def test_the_width_of_a_launch_group_does_not_change_the_gradients_bits(dyn, util, oracle):
     """fp32, C = 160, 14 x 14: the summed channels fit LDS at once beside some of the workgroup tiles only."""
     arity = np.array([0, 1, 2], np.uint8)
