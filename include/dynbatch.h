@@ -356,7 +356,7 @@ size_t dynbatch_classify_workspace_bytes(const dynb_head_shape* shape, int32_t B
  *   logits     device [B][n_answers] fp32 or NULL: the inputs of the softmax, if wanted
  *   workspace  device, >= dynbatch_classify_workspace_bytes, 256-byte aligned, scratch
  * Any sizes are accepted; bf16 layers whose inner extent (C, H*W*Cc, F) is a multiple of 8 run on
- * MFMAs, the others on plain FMAs.  B = 0 succeeds without work.  Errors: DYNB_E_INVAL (NULL,
+ * MFMAs, the others and a last layer of up to 64 answers and few examples on plain FMAs.  B = 0 succeeds without work.  Errors: DYNB_E_INVAL (NULL,
  * sizes <= 0, misaligned), DYNB_E_WORKSPACE, DYNB_E_UNSUPPORTED (dtype, batch too large), DYNB_E_HIP. */
 int dynbatch_classify(const dynb_head_shape* shape, const dynb_head_weights* w, const void* roots, int32_t B,
                       float* probs, float* logits, void* workspace, size_t workspace_bytes, void* stream);

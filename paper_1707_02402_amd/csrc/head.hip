@@ -10,7 +10,8 @@
 //   fc 1       a = conv output [B][H*W*Cc]     w = wf1 [F][H*W*Cc]
 //   fc 2       a = fc 1 output [B][F]          w = wf2 [A][F]
 // bf16 operands whose k extent is a multiple of 8 run on 32x32x16 MFMAs from LDS-staged 64 x 64 tiles;
-// everything else (fp32 storage, odd k) runs a plain FMA tile kernel.  A layer with few output tiles and a long
+// everything else (fp32 storage, odd k) runs a plain FMA tile kernel; a small last layer and the softmax run as one
+// workgroup per example on plain FMAs (k_head_answers).  A layer with few output tiles and a long
 // k (fc 1: 16 tiles, k = 6272) is cut along k into `splits` slices that are summed afterwards in slice order, so
 // the result does not depend on how the workgroups were scheduled.
 #include <hip/hip_runtime.h>
@@ -159,12 +160,26 @@ __global__ __launch_bounds__(256) void k_head_gemm_fma(GemmArgs g)
             }
 }
 
-// out[m][n] = act(bias[n] + part[0][m][n] + part[1][m][n] + ...): a workgroup takes 64 elements, its wave w the slices w, w + 4,
-// ... of them; the four sums are added in wave order.  (One thread per element and 64 slices one after the other took 8 to
-// 13 us for the 256 hidden units of one example.)
+// out[m][n] = act(bias[n] + part[0][m][n] + part[1][m][n] + ...), a thread per element
 template <typename TO, bool RELU>
 __global__ __launch_bounds__(256) void k_head_finish(const float* __restrict__ part, const float* __restrict__ bias, TO* __restrict__ out,
                                                      size_t MN, int N, int splits)
+{
+    for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < MN; e += size_t(gridDim.x) * blockDim.x) {
+        float v = bias ? bias[e % N] : 0.f;
+        for (int z = 0; z < splits; ++z) v += part[size_t(z) * MN + e];
+        if (RELU) v = fmaxf(v, 0.f);
+        store_f32(out + e, v);
+    }
+}
+
+// The same for many slices: a workgroup takes 64 elements, its wave w the slices w, w + 4, ... of them; the four sums are added in
+// wave order.  (One thread per element and 64 slices one after the other took 8 to 13 us for the 256 hidden units of one example;
+// with one slice three of the four waves have nothing to add: 4096 x 1024 answers 42 us a pass by the threads, 59 by the waves.)
+constexpr int FINISH_SLICES = 8;                   // from here on
+template <typename TO, bool RELU>
+__global__ __launch_bounds__(256) void k_head_finish_slices(const float* __restrict__ part, const float* __restrict__ bias, TO* __restrict__ out,
+                                                            size_t MN, int N, int splits)
 {
     __shared__ float sum[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -188,7 +203,7 @@ __global__ __launch_bounds__(256) void k_head_finish(const float* __restrict__ p
 
 // The last layer and the softmax of one example per workgroup: a wave takes every fourth answer, its lanes the hidden units.
 // (As a product, a sum of slices and a softmax they were three launches, 12 us for one example.)
-constexpr int HEAD_ANSWERS = 2048;                 // logits kept in LDS
+constexpr int HEAD_ANSWERS = 64;                   // logits kept in LDS
 template <typename T>
 __global__ __launch_bounds__(256) void k_head_answers(const T* __restrict__ h1, const T* __restrict__ wf2, const float* __restrict__ bf2,
                                                       float* __restrict__ logits, float* __restrict__ probs, int F, int A)
@@ -242,12 +257,13 @@ __global__ __launch_bounds__(256) void k_head_softmax(const float* __restrict__ 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 size_t elt(int dtype) { return dtype == DYNB_BF16 ? 2 : 4; }
 
-// k slices of a layer: enough workgroups to fill the chip, never more than the chunks there are
-int splits_for(int M, int N, int K)
+// k slices of a layer: enough workgroups to fill the chip, never more than the chunks there are.  One: layers that store their result
+// themselves (`direct`) run two chunks on the matrix cores in less time than the launch that would add the halves.
+int splits_for(int M, int N, int K, bool direct)
 {
     const long long tiles = (long long)((M + HT - 1) / HT) * ((N + HT - 1) / HT);
     const int chunks = (K + HKC - 1) / HKC;
-    if (tiles >= 256 || chunks <= 2) return 1;        // (two chunks: shorter than the launch that would add the halves)
+    if (tiles >= 256 || chunks <= (direct ? 2 : 1)) return 1;
     return int(std::max<long long>(1, std::min<long long>(chunks, std::min<long long>(64, (512 + tiles - 1) / tiles))));
 }
 
@@ -260,9 +276,10 @@ HeadLayout head_layout(const dynb_head_shape* s, int32_t B)
 {
     HeadLayout L;
     const size_t P = size_t(s->H) * s->W, M1 = size_t(B) * P;
-    L.s1 = splits_for(int(M1), s->Cc, s->C);
-    L.s2 = splits_for(B, s->F, int(P * s->Cc));
-    L.s3 = splits_for(B, s->n_answers, s->F);
+    auto direct = [&](size_t K) { return s->dtype == DYNB_BF16 && K % 8 == 0; };
+    L.s1 = splits_for(int(M1), s->Cc, s->C, direct(s->C));
+    L.s2 = splits_for(B, s->F, int(P * s->Cc), direct(P * s->Cc));
+    L.s3 = splits_for(B, s->n_answers, s->F, false);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align256(std::max<size_t>(bytes, 4)); return at; };
     L.z = take(M1 * s->Cc * elt(s->dtype));
@@ -300,8 +317,11 @@ void launch_layer(int dtype, const void* a, const void* w, const float* bias, TO
     else hipLaunchKernelGGL((k_head_gemm_fma<float>), grid, dim3(256), 0, st, g);
     if (g.out) return;
     const size_t MN = size_t(M) * N;
-    hipLaunchKernelGGL((k_head_finish<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 63) / 64, 4096))), dim3(256), 0, st,
-                       part, bias, out, MN, N, int(grid.z));
+    const int n_slices = int(grid.z);
+    if (n_slices >= FINISH_SLICES)
+        hipLaunchKernelGGL((k_head_finish_slices<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 63) / 64, 4096))), dim3(256), 0, st, part, bias, out, MN, N, n_slices);
+    else
+        hipLaunchKernelGGL((k_head_finish<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 255) / 256, 4096))), dim3(256), 0, st, part, bias, out, MN, N, n_slices);
 }
 
 }  // namespace
@@ -331,8 +351,13 @@ extern "C" int dynbatch_classify(const dynb_head_shape* s, const dynb_head_weigh
     const int P = s->H * s->W, M1 = B * P, J = P * s->Cc;
     float* part = reinterpret_cast<float*>(ws + L.part);
     float* logits = logits_out ? logits_out : reinterpret_cast<float*>(ws + L.logits);
-    // every example reads the last layer's weights through its own CU: up to 64 K of them
-    const bool answers = s->n_answers <= HEAD_ANSWERS && (long long)s->n_answers * s->F <= 65536;
+    // A workgroup takes a wave's sum and exchange (some 0.4 us) for every fourth answer, and every example streams the weights through
+    // its own CU; the matrix product pays two more launches.  us a pass (bf16, F = 256 but where stated), product / one workgroup:
+    // 28 answers, 1 to 1000 examples 28 / 16, 4096: 29 / 26, 16384: 38 / 66; 64 answers, 1: 28 / 17, 1000: 29 / 21, 4096: 29 / 38;
+    // 128 (F = 128), 1: 28 / 24, 256: 29 / 30; 256, 1: 28 / 35; 1024 (F = 64): 28 / 113; F = 1024: 28 answers, 1000: 29 / 22, 64
+    // answers, 256: 29 / 26, 1000: 29 / 33.
+    const bool answers = s->n_answers <= HEAD_ANSWERS && (long long)s->n_answers * s->F <= 65536 &&
+                         (long long)s->n_answers * s->F * B <= (1 << 25);
     if (s->dtype == DYNB_BF16) {
         bf16_t* z = reinterpret_cast<bf16_t*>(ws + L.z);
         bf16_t* h1 = reinterpret_cast<bf16_t*>(ws + L.h1);

@@ -43,6 +43,9 @@ def run_head(dyn, util, roots, head, dtype):
     ("bf16", 1, 128, 14, 14, 8, 8, 2),
     ("f32", 3, 16, 4, 4, 8, 64, 2100),        # too many answers for one workgroup per example
     ("bf16", 2, 136, 7, 7, 16, 72, 65),       # three chunks along k, answers and units that no wave count divides
+    ("f32", 3, 8, 2, 2, 8, 64, 64),           # the most answers for one workgroup per example
+    ("bf16", 512, 8, 1, 1, 8, 1024, 64),      # the most examples for that many weights, and one more
+    ("bf16", 513, 8, 1, 1, 8, 1024, 64),
 ])
 def test_every_probability_against_the_oracle(dyn, util, oracle, dtype, B, C, H, W, Cc, F, A):
     roots = np.abs(iep.make_feats(B + C, B, H, W, C, dtype))          # root maps are outputs of a ReLU: non-negative
