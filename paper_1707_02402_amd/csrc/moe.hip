@@ -710,9 +710,10 @@ __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict_
 
 // The same for more uses, in three launches: blocks of 1024 uses are ranked with the experts' counts in LDS and leave all of their
 // counts, zeros included (nothing has to be cleared), as blockcnt[block][expert]; one workgroup turns them into
-// places, an expert per thread.  For up to SMALL_EXPERTS experts and MID_BLOCKS blocks, beyond which that workgroup's
-// walk over the blocks takes longer than the launches it saves.  (8192 uses of 256 experts: 23 us in five launches.)
-constexpr int MID_BLOCKS = 64;
+// places, an expert per thread.  For up to SMALL_EXPERTS experts, MID_BLOCKS blocks and MID_COUNTS counts, beyond which that
+// workgroup's walk over the counts takes longer than the launches it saves; us, five launches / three: 8 blocks x 256 experts 23 / 14.5,
+// 64 x 1024 24 / 20.5, 40 x 2048 25.4 / 23.4, 20 x 4096 27.9 / 27.4, 64 x 2048 26.4 / 27.4, 40 x 3000 27.3 / 30.2, 64 x 4096 30.6 / 41.
+constexpr int MID_BLOCKS = 64, MID_COUNTS = 82 * 1024;
 __global__ __launch_bounds__(1024) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
 {
     __shared__ int32_t count[SMALL_EXPERTS];
@@ -1262,8 +1263,9 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             hipLaunchKernelGGL((k_gate_big<false>), grid, dim3(256), GB_LDS_BYTES, st, xb, static_cast<const bf16_t*>(Wg),
                                static_cast<const bf16_t*>(Wn), noise, logits, T_big, d, E, ntt, net, per_die);
     }
-    // fewer 64 x 64 tiles than half the chip has CUs: the kernel with the small tiles
-    if (T_big == 0 && size_t((E + 63) / 64) * size_t((T + 63) / 64) < 128)
+    // up to four 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d = 1024,
+    // noisy: 500 21 / 11, 1000 21 / 17, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; d = 64: 1764 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
+    if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1024)
         hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),
                            static_cast<const bf16_t*>(Wn), noise, logits, T, d, E);
     else if (T > T_big)
@@ -1298,7 +1300,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // live: 1040: 108 / 81, 1088: 148 / 141, 1152: 290 / 268.)  The tiles' table takes the room of the stacked tokens, which
     // no kernel writes then (at most one tile per use, 16 bytes each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
-    const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
+    const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024 && (long long)E * ((A + 1023) / 1024) <= MID_COUNTS;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
     const bool skinny = (small || mid) && fused_permute && (long long)skinny_tiles * ((std::max(h, d) + TN - 1) / TN) <= (small ? 1200 : 640);
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
@@ -1413,8 +1415,8 @@ extern "C" int moe_forward_static(const moe_shape* s, const void* x, const void*
     void* ws = nullptr;
     rc = static_scratch_ptr(&ws);
     if (rc != DYNB_OK) return rc;
-    // every buffer of the layout is written before it is read, and the one table that must start
-    // at zero (blockcnt) is cleared by a fill kernel inside the layer: the previous call's contents do not matter
+    // every buffer of the layout is written before it is read (blockcnt, where it has to start at zero, by a fill kernel
+    // inside the layer): the previous call's contents do not matter
     return moe_run(s, x, Wg, Wn, noise, W1, W2, out, aux, ws, size_t(MOE_STATIC_SCRATCH_BYTES), stream, 0);
 }
 

@@ -271,10 +271,12 @@ def test_config4_targeted_tokens_with_empty_experts(dyn, util, oracle):
 
 @pytest.mark.parametrize("T,d,h,E,k,noise", [(1, 8, 8, 1, 1, True), (3, 40, 24, 5, 5, True), (17, 72, 136, 70, 2, False), (37, 512, 1024, 256, 2, False),
                                              (64, 1000, 520, 64, 8, True), (128, 64, 96, 64, 8, True), (129, 64, 64, 64, 8, False), (100, 64, 72, 4097, 2, True),
-                                             (300, 48, 104, 40, 2, True), (700, 264, 520, 33, 2, True), (900, 1100 // 8 * 8, 64, 9, 3, False)])
+                                             (300, 48, 104, 40, 2, True), (700, 264, 520, 33, 2, True), (900, 1100 // 8 * 8, 64, 9, 3, False),
+                                             (1024, 64, 16, 256, 1, True), (1025, 72, 16, 256, 1, False)])
 def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
     """The kernels for a few tokens, at the edges of their tiles (16 tokens, experts, features; 32 summed channels; rows of an
-    expert up to and over 16, 32 and 64; blocks of 1024, 512 and 256 summed channels) and of their range (1024 uses, 4096 experts)."""
+    expert up to and over 16, 32 and 64; blocks of 1024, 512 and 256 summed channels) and of their range (1024 gate tiles, 1024
+    uses, 4096 experts)."""
     m = moe.small(seed=T + E, T=T, d=d, h=h, E=E, k=k, zipf_s=1.1 if E < 1000 else 0.3)
     W1, W2 = stack(m)
     out, aux = util.moe_run(dyn, m, W1, W2, noise=noise)
@@ -287,9 +289,9 @@ def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
     assert per_token_errors(out, ref).max() < OUT_TOL
 
 
-@pytest.mark.parametrize("T,E,k", [(1025, 7, 1), (1024, 4096, 2), (513, 300, 2), (8192, 40, 8), (8200, 33, 8), (600, 4097, 2)])
+@pytest.mark.parametrize("T,E,k", [(1025, 7, 1), (1024, 4096, 2), (513, 300, 2), (8192, 40, 8), (8200, 33, 8), (600, 4097, 2), (2560, 4096, 8), (2561, 4096, 8)])
 def test_grouping_of_many_uses(dyn, util, oracle, T, E, k):
-    """Blocks of 1024 uses with a remainder of one, the most experts and the most uses of that path, and what lies beyond."""
+    """Blocks of 1024 uses with a remainder of one, the most experts, uses and counts of that path, and what lies beyond."""
     m = moe.small(seed=T + k, T=T, d=16, h=16, E=E, k=k, zipf_s=0.8)
     W1, W2 = stack(m)
     _, aux = util.moe_run(dyn, m, W1, W2)
