@@ -1263,9 +1263,10 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             hipLaunchKernelGGL((k_gate_big<false>), grid, dim3(256), GB_LDS_BYTES, st, xb, static_cast<const bf16_t*>(Wg),
                                static_cast<const bf16_t*>(Wn), noise, logits, T_big, d, E, ntt, net, per_die);
     }
-    // up to four 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d = 1024,
-    // noisy: 500 21 / 11, 1000 21 / 17, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; d = 64: 1764 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
-    if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1024)
+    // up to some five 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d =
+    // 1024, noisy: 500 21 / 11, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; without noise: 1000 15.5 / 12.8, 2000 16.4 / 20; d = 64: 1764
+    // 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
+    if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1200)
         hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),
                            static_cast<const bf16_t*>(Wn), noise, logits, T, d, E);
     else if (T > T_big)
@@ -1297,12 +1298,22 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // have too few 64 x 256 tiles to keep the chip's memory busy with k_grouped_gemm they run on small tiles.  The line, us
     // a layer pair with k_grouped_gemm / k_grouped_skinny by the number of its tiles: 200: 99 / 57, 256: 77 / 53, 520: 190 /
     // 109, 768: 118 / 124, 1024: 225 / 239, 9000: 1640 / 1950.  (The number is a bound; of up to 1024 uses fewer experts are
-    // live: 1040: 108 / 81, 1088: 148 / 141, 1152: 290 / 268.)  The tiles' table takes the room of the stacked tokens, which
-    // no kernel writes then (at most one tile per use, 16 bytes each like the smallest token).
+    // live: 1040: 108 / 81, 1088: 148 / 141, 1152: 290 / 268.)  Of the two layers each takes its own kernel: k_grouped_skinny pays some
+    // 11 us for every round of 768 workgroups (three a CU) whatever they sum, so a layer of many features and short sums is not for
+    // it, nor is one of a few workgroups and short sums.  us a layer, features x summed channels, rounds: 512 x 64, 2.4: 13 / 33;
+    // 1024 x 128, 4.4: 16 / 50; 256 x 256, 1.2: 27 / 19, 2.8: 26 / 34; 1024 x 512, 1.6: 37 / 28, 2.1: 36 / 35; 2048 x 512, 4.8: 50 / 59; 2048 x
+    // 1024, 3.3: 84 / 70, 4.8: 90 / 99; 512 x 2048, 1.2: 120 / 63; 448 x 128, 0.1: 7 / 10; 72 x 120, 0.4: 14 / 7.6; tiles of 49 rows on average, 1024 x 1024, 2.6: 54 / 78.
+    // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
+    // each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
     const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024 && (long long)E * ((A + 1023) / 1024) <= MID_COUNTS;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
-    const bool skinny = (small || mid) && fused_permute && (long long)skinny_tiles * ((std::max(h, d) + TN - 1) / TN) <= (small ? 1200 : 640);
+    const bool few_tiles = (small || mid) && fused_permute && (long long)skinny_tiles * ((std::max(h, d) + TN - 1) / TN) <= (small ? 1200 : 640);
+    auto skinny_layer = [&](int N, int K) {                        // rounds <= 1.6 + K / 300 (1.6 for full tiles); not too little in all
+        const long long groups = (long long)skinny_tiles * ((N + 63) / 64);
+        return few_tiles && groups * 300 <= 768 * (480ll + (A < 32ll * skinny_tiles ? K : 0)) && (K >= 224 || A >= 128 || groups * 5 >= 768);
+    };
+    const bool skinny1 = skinny_layer(h, d), skinny2 = skinny_layer(d, h), skinny = skinny1 || skinny2;
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
     if (small) {
         hipLaunchKernelGGL(k_group_small, dim3(1), dim3(1024), 0, st, topk_idx, counts, offsets, tile_start, perm, inv, tiles,
@@ -1327,20 +1338,22 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // m5 grouped expert FFN: at most ceil(A/TM) + E row tiles exist
     const long long max_mtiles = (long long)(A + TM - 1) / TM + E;
     const int nt1 = (h + TN - 1) / TN, nt2 = (d + TN - 1) / TN;
-    if (skinny) {
-        const int m = skinny_tiles, ns1 = (h + 63) / 64, ns2 = (d + 63) / 64;
-        hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(m * ns1)), dim3(256), 0, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, h, d, ns1, perm, k);
-        if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
-        hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(m * ns2)), dim3(256), 0, st, hid, static_cast<const bf16_t*>(W2), y, tiles, d, h, ns2, nullptr, 1);
-        if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
-    } else if (naive_stride <= 0) {
+    if (naive_stride <= 0) {
         const long long span = 8ll * XCD_CHUNK;
-        hipLaunchKernelGGL((k_grouped_gemm<true>), dim3(unsigned((max_mtiles * nt1 + span - 1) / span * span)), dim3(256), 0, st,
-                           fused_permute ? xb : xs, static_cast<const bf16_t*>(W1), hid, offsets, tile_start, E, h, d, nt1,
-                           XCD_CHUNK, fused_permute ? perm : nullptr, k);
+        if (skinny1)
+            hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(skinny_tiles * ((h + 63) / 64))), dim3(256), 0, st, xb,
+                               static_cast<const bf16_t*>(W1), hid, tiles, h, d, (h + 63) / 64, perm, k);
+        else
+            hipLaunchKernelGGL((k_grouped_gemm<true>), dim3(unsigned((max_mtiles * nt1 + span - 1) / span * span)), dim3(256), 0, st,
+                               fused_permute ? xb : xs, static_cast<const bf16_t*>(W1), hid, offsets, tile_start, E, h, d, nt1,
+                               XCD_CHUNK, fused_permute ? perm : nullptr, k);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
-        hipLaunchKernelGGL((k_grouped_gemm<false>), dim3(unsigned((max_mtiles * nt2 + span - 1) / span * span)), dim3(256), 0, st,
-                           hid, static_cast<const bf16_t*>(W2), y, offsets, tile_start, E, d, h, nt2, XCD_CHUNK, nullptr, 1);
+        if (skinny2)
+            hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(skinny_tiles * ((d + 63) / 64))), dim3(256), 0, st, hid,
+                               static_cast<const bf16_t*>(W2), y, tiles, d, h, (d + 63) / 64, nullptr, 1);
+        else
+            hipLaunchKernelGGL((k_grouped_gemm<false>), dim3(unsigned((max_mtiles * nt2 + span - 1) / span * span)), dim3(256), 0, st,
+                               hid, static_cast<const bf16_t*>(W2), y, offsets, tile_start, E, d, h, nt2, XCD_CHUNK, nullptr, 1);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else {
         // the paper's naive version: loop over the k*b expert uses, one expert call (two layers) per use

@@ -272,11 +272,12 @@ def test_config4_targeted_tokens_with_empty_experts(dyn, util, oracle):
 @pytest.mark.parametrize("T,d,h,E,k,noise", [(1, 8, 8, 1, 1, True), (3, 40, 24, 5, 5, True), (17, 72, 136, 70, 2, False), (37, 512, 1024, 256, 2, False),
                                              (64, 1000, 520, 64, 8, True), (128, 64, 96, 64, 8, True), (129, 64, 64, 64, 8, False), (100, 64, 72, 4097, 2, True),
                                              (300, 48, 104, 40, 2, True), (700, 264, 520, 33, 2, True), (900, 1100 // 8 * 8, 64, 9, 3, False),
-                                             (1024, 64, 16, 256, 1, True), (1025, 72, 16, 256, 1, False)])
+                                             (1200, 64, 16, 256, 1, True), (1201, 72, 16, 256, 1, False), (300, 64, 1024, 200, 2, False),
+                                             (300, 1024, 64, 200, 2, False)])
 def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
     """The kernels for a few tokens, at the edges of their tiles (16 tokens, experts, features; 32 summed channels; rows of an
-    expert up to and over 16, 32 and 64; blocks of 1024, 512 and 256 summed channels) and of their range (1024 gate tiles, 1024
-    uses, 4096 experts)."""
+    expert up to and over 16, 32 and 64; blocks of 1024, 512 and 256 summed channels) and of their range (1200 gate tiles, 1024
+    uses, 4096 experts; one expert layer on small tiles and the other not)."""
     m = moe.small(seed=T + E, T=T, d=d, h=h, E=E, k=k, zipf_s=1.1 if E < 1000 else 0.3)
     W1, W2 = stack(m)
     out, aux = util.moe_run(dyn, m, W1, W2, noise=noise)
