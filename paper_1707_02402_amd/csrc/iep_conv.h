@@ -558,6 +558,60 @@ struct NodeArgs {
     int32_t keep;                 // u and mid are also written to the maps of the backward pass
 };
 
+struct NodeKernelArgs { const dynb_item* items; NodeArgs nw; ConvArgs a; };             // k_node's parameters
+
+// The rare end of k_node: sums that any_nan speaks of.  mid_nan (all waves): mid's border and every result are taken again, else this
+// lane's results at the border.  Everything is read anew, so that the kernel need not hold registers for it (it had to move
+// scalar registers into vector lanes: 2 % of a pass, fp32, C = 32, 8 x 8).
+template <typename T, int MT>
+__device__ __forceinline__ void node_again(bool mid_nan, bool nan)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const void* args = (const void*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const NodeKernelArgs k = *static_cast<const NodeKernelArgs*>(args);
+    const ConvArgs& a = k.a;
+    const int i = int(blockIdx.x & 7) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
+    const dynb_item it = k.items[i];
+    const int C = a.C, H = a.H, W = a.W, P = H * W, pix_bytes = conv_pixel_bytes(a.ck, int(sizeof(T))), row_bytes = (W + 2) * pix_bytes;
+    const uint32_t second = uint32_t((H + 2) * row_bytes);                              // the second tile
+    const size_t chw = size_t(P) * C;
+    const int lane = threadIdx.x & 63, n_ct = (C + 15) / 16, n_units = n_ct * ((P + MT * 16 - 1) / (MT * 16));
+    T* const dst = conv_dst<T>(a, it.dst, chw);
+    // this wave's results of a convolution: fn(pixel, y, x, channels o .. o + n - 1, sum, bias, address of the pixel's top left tap)
+    auto each = [&](const void* w, const float* bias, uint32_t tile, bool inner, auto&& fn) {
+#pragma unroll 1
+        for (int u = threadIdx.x >> 6; u < n_units; u += 8)
+#pragma unroll 1
+            for (int t = 0; t < MT; ++t) {
+                const int pt = u / n_ct, p = (pt * MT + t) * 16 + (lane & 15), y = p / W, x = p - y * W;
+                const int o = (u - pt * n_ct) * 16 + (lane >> 4) * 4, n = min(4, C - o);
+                if (p >= P || n <= 0 || !(inner || at_border(y, x, H, W))) continue;
+                const uint32_t at = uint32_t(y * row_bytes + x * pix_bytes);
+                const f32x4 b = bias ? load4<false>(bias + size_t(it.type) * C + o, n) : f32x4{0.f, 0.f, 0.f, 0.f};
+                fn(p, o, n, at + uint32_t(row_bytes + pix_bytes), b,
+                   direct_sum<false>((const T*)w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
+                       return load_f32(reinterpret_cast<const T*>(lds_raw + tile + at + uint32_t(kh * row_bytes + kw * pix_bytes)) + c);
+                   }));
+            }
+    };
+    if (mid_nan) {
+        __syncthreads();
+        each(k.nw.w3a, k.nw.b3a, 0, false, [&](int p, int o, int n, uint32_t centre, const f32x4& b, f32x4 v) {
+            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c], 0.f);
+            store4<false>(reinterpret_cast<T*>(lds_raw + second + centre) + o, n, v);
+            if (k.nw.keep) store4<false>((T*)a.mid + size_t(a.first_kept + i) * chw + size_t(p) * C + o, n, v);
+        });
+        __syncthreads();
+    }
+    if (mid_nan || nan)
+        each(k.nw.w3b, k.nw.b3b, second, mid_nan, [&](int p, int o, int n, uint32_t centre, const f32x4& b, f32x4 v) {
+            const f32x4 res = load4<false>(reinterpret_cast<const T*>(lds_raw + centre) + o, n);
+            for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c] + b[c] + res[c], 0.f);
+            store4<false>(dst + size_t(p) * C + o, n, v);
+        });
+}
+
 template <typename T, int MT, bool FULL>
 __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* items, NodeArgs nw, ConvArgs a)
 {
@@ -726,7 +780,6 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
     Second second;
     if (wave < n_units) { unit(wave); prepare(second, nw.w3b, uint32_t(tile_bytes)); }
     __syncthreads();
-    const uint32_t mid_nan = *flag;
 
     // ---- result = ReLU(conv3x3(second tile) + b3b + first tile)
     nan = false;
@@ -740,36 +793,10 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
             put_result(t, p, o, n, acc[t][0], b);
         });
     }
-    end_unless(nan | (mid_nan != 0));
-
-    // ---- rare: sums that any_nan speaks of.  If there were any in mid, mid's border and every result, else this lane's results at the
-    // border.  (A wave gets here alone, or all of them do, with mid_nan.)
-    auto direct = [&](const void* w, uint32_t tile, int t, int p, int o, int n) -> f32x4 {
-        const int y = p / W, x = p - y * W;
-        return direct_sum<false>((const T*)w + size_t(it.type) * C * 9 * C, C, H, W, y, x, o, n, [&](int kh, int kw, int c) {
-            return load_f32(reinterpret_cast<const T*>(lds_raw + tile + at[t] + uint32_t(kh * row_bytes + kw * pix_bytes)) + c);
-        });
-    };
-    if (mid_nan) {
-        __syncthreads();
-#pragma unroll 1
-        for (int u = wave; u < n_units; u += NWAVE) {
-            unit(u);
-            const f32x4 b = bias_of(nw.b3a);
-            results([&](int t, int p, int o, int n) {
-                if (at_border(p / W, p % W, H, W)) put_mid(t, p, o, n, direct(nw.w3a, 0, t, p, o, n), b);
-            });
-        }
-        __syncthreads();
-    }
-#pragma unroll 1
-    for (int u = wave; u < n_units; u += NWAVE) {
-        unit(u);
-        const f32x4 b = bias_of(nw.b3b);
-        results([&](int t, int p, int o, int n) {
-            if (mid_nan || (nan && at_border(p / W, p % W, H, W))) put_result(t, p, o, n, direct(nw.w3b, uint32_t(tile_bytes), t, p, o, n), b);
-        });
-    }
+    // (Read before these sums, the flag would wait for their weights: the compiler gives it a register that they return behind.)
+    const uint32_t mid_nan = __builtin_amdgcn_readfirstlane(*flag);
+    end_unless(nan || mid_nan != 0);
+    node_again<T, MT>(mid_nan != 0, nan);
 }
 
 // ---- launching
