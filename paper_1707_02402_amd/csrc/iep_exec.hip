@@ -555,17 +555,18 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
     const bool plain = plain_shape<T>(a), whole = !plain && node_shape<T>(a);
     for (const dynb_launch& l : p->launches) {
         evals += l.count;
-        if (whole) {
-            a.first_kept = l.start;
-            const NodeArgs nw = {w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b, l.count, p->keep ? 1 : 0};
-            const int rc = launch_node<T>(reinterpret_cast<const dynb_item*>(d) + l.start, nw, a, st);
-            if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a launch group could not be launched");
-        }
-        // grid.y is limited to 65535: split very wide launch groups
-        for (int off = 0; !whole && off < l.count; off += 32768) {
-            const int count = std::min(32768, l.count - off);
+        // a grid has at most 65535 rows and 2^32 threads a row: very wide launch groups are split
+        const int slice = whole ? 1 << 22 : 32768;
+        for (int off = 0; off < l.count; off += slice) {
+            const int count = std::min(slice, l.count - off);
             const dynb_item* items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
             a.first_kept = p->keep ? l.start + off : off;
+            if (whole) {
+                const NodeArgs nw = {w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b, count, p->keep ? 1 : 0};
+                const int rc = launch_node<T>(items, nw, a, st);
+                if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a launch group could not be launched");
+                continue;
+            }
             int rc = DYNB_OK;
             if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = (plain ? launch_conv_plain<T, CV_JOIN> : launch_conv<T, CV_JOIN>)(items, a, count, st); }
             a.w = w->w3a; a.bias = w->b3a;

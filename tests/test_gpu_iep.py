@@ -548,3 +548,21 @@ def test_few_channels_and_tiny_maps(dyn, util, oracle, dtype, C, H, W, B):
         shifted = torch.cat([feats.flatten()[:4 // feats.element_size()], feats.flatten()])[4 // feats.element_size():].view(feats.shape)
         assert shifted.data_ptr() % 16 == 4
         assert (util.iep_run(dyn, w, feats=shifted) == base).all()
+
+
+def test_a_launch_group_of_more_modules_than_one_grid_holds(dyn, util):
+    """2^23 + 1 modules on maps of 2 x 2 x 16: one workgroup of 512 threads each is more than a grid's 2^32 threads.  All programs are
+    alike, and so must the results be."""
+    import torch
+    n = (1 << 23) + 1
+    arity = np.array([0, 1], np.uint8)
+    w = iep.IepWorkload("wide", "f32", arity, np.array([1, 0], np.int32), np.array([0, 2], np.int32), 16, 2, 2,
+                        iep.make_feats(1, 1, 2, 2, 16, "f32"), *iep.make_weights(2, arity, 16, "f32"))
+    one = util.iep_run(dyn, w, return_dev=True)
+    weights = util.iep_weights_dev(w)
+    plan = dyn.dynbatch_plan(np.tile(w.prog, n), np.arange(n + 1, dtype=np.int32) * 2, arity)
+    dyn.dynbatch_plan_upload(plan)
+    feats = util.to_dev(w.feats, "f32").expand(n, 2, 2, 16).contiguous()
+    out = dyn.dynbatch_execute(plan, weights, feats, out=torch.zeros_like(feats))
+    for part in out.split(1 << 20):
+        assert bool((part == one).all())
