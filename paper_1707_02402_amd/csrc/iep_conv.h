@@ -836,7 +836,11 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     a.m_sw = recip20_of(a.sw);
     const size_t lds = std::max<size_t>(size_t(pixels) * conv_pixel_bytes(a.ck, ES), size_t(4) * MT * NT * 1024);
     if (lds > CONV_LDS_MAX) return DYNB_E_UNSUPPORTED;                   // cannot happen: sw <= 32
-    hipLaunchKernelGGL((k_conv<T, MODE, MT, NT, FULL>), dim3(unsigned(n_seg * a.tiles_per_seg * a.n_ctile), unsigned(count)), dim3(256), lds, st, items, a);
+    // A row of a grid holds less than 2^32 threads (and nobody says so: the launch just does less).  Only the gradients of maps of
+    // half a billion pixels with fewer than 4 channels would need more, which a parameter gradient's workgroup walks for many seconds.
+    const long long groups = (long long)n_seg * a.tiles_per_seg * a.n_ctile;
+    if (groups >= 1 << 24) return DYNB_E_UNSUPPORTED;
+    hipLaunchKernelGGL((k_conv<T, MODE, MT, NT, FULL>), dim3(unsigned(groups), unsigned(count)), dim3(256), lds, st, items, a);
     return DYNB_OK;
 }
 
