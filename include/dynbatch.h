@@ -95,7 +95,10 @@ enum {
      * reuse) so that dynbatch_backward can run after dynbatch_execute.  dynbatch_execute also saves the two
      * intermediate maps of every node (the output of the 1x1 convolution of two-argument functions and of
      * the first 3x3 convolution) in the workspace, and a plan that also carries DYNB_PLAN_PERSISTENT runs
-     * one launch per label.  Larger workspace (three maps per node).  The plan view then lists the tables the backward pass works from.                     */
+     * one launch per label.  Larger workspace: three maps per node on the fast path; on other shapes two,
+     * and one more per two-argument node.  dynbatch_backward's workspace holds, on other shapes, two fp32
+     * maps per node, one more per two-argument node and one per leaf.  The plan view then lists the tables
+     * the backward pass works from.                                                              */
     DYNB_PLAN_KEEP = 32
 };
 

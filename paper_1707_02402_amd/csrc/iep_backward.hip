@@ -55,6 +55,7 @@ struct WgradArgs {
     const uint8_t* arity;
     const int32_t* fn_first;      // the items of function t: fn_items[fn_first[t] .. fn_first[t + 1])
     const int32_t* fn_items;
+    const int32_t* u_at;          // where an item's u and du lie among the kept ones
     const void* feats;
     const void* out;
     const void* slots;
@@ -103,12 +104,12 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
     auto maps = [&](int idx) -> Maps {
         const int32_t item = a.fn_items[idx];
         const dynb_item it = a.items[item];
-        const size_t off = size_t(item) * chw;
+        const size_t off = size_t(item) * chw, u_off = ar == 2 ? size_t(a.u_at[item]) * chw : 0;
         const int32_t s = arg ? it.src1 : it.src0;
         const T* A = s >= 0 ? (const T*)a.slots + size_t(s) * chw : (const T*)a.feats + size_t(-1 - s) * chw;
-        return {JOIN ? a.du + off : which == 0 ? a.gy + off : a.dm + off,
+        return {JOIN ? a.du + u_off : which == 0 ? a.gy + off : a.dm + off,
                 it.dst >= 0 ? (const T*)a.slots + size_t(it.dst) * chw : (const T*)a.out + size_t(-1 - it.dst) * chw,
-                JOIN ? A : which == 0 ? (const T*)a.mid + off : ar == 2 ? (const T*)a.u + off : A};
+                JOIN ? A : which == 0 ? (const T*)a.mid + off : ar == 2 ? (const T*)a.u + u_off : A};
     };
 #pragma unroll 1
     for (int idx = lo; idx < hi; idx += NI) {
@@ -922,7 +923,7 @@ __global__ void k_bwd_wgrad_sum(WsArgs a)
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// workspace away from the fused kernels' shape: one map per item each, fp32
+// workspace away from the fused kernels' shape: fp32 maps, gy and dm of every item, du of two-argument functions
 struct BwdLayout {
     size_t gy, gleaf, dm, du, total;
 };
@@ -937,7 +938,7 @@ BwdLayout bwd_layout(const dynb_plan* p, const dynb_shape* s)
     L.gy = take(n_items * chw * 4);
     L.gleaf = take(n_leaf * chw * 4);
     L.dm = take(n_items * chw * 4);
-    L.du = take(p->has_binary ? n_items * chw * 4 : 0);
+    L.du = take(p->n_u * chw * 4);
     L.total = o;
     return L;
 }
@@ -999,13 +1000,16 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
     ConvArgs a = {};
     a.feats = feats; a.out = const_cast<void*>(out); a.slots = const_cast<void*>(fwd_ws);
     const size_t map = chw * sizeof(T);
-    a.mid = static_cast<char*>(const_cast<void*>(fwd_ws)) + dynb_generic_keep_offset(p, map);
-    a.u = static_cast<char*>(a.mid) + dynb_generic_kept_maps(p) * map;
+    a.mid = static_cast<char*>(const_cast<void*>(fwd_ws)) + dynb_generic_mid_offset(p, map);
+    T* const u = reinterpret_cast<T*>(static_cast<char*>(a.mid) + dynb_generic_mids(p) * map);
     a.gy = gy; a.gleaf = reinterpret_cast<float*>(ws + L.gleaf);
-    a.dm = reinterpret_cast<float*>(ws + L.dm); a.du = reinterpret_cast<float*>(ws + L.du);
+    a.dm = reinterpret_cast<float*>(ws + L.dm);
+    float* const du = reinterpret_cast<float*>(ws + L.du);
     a.C = s->C; a.H = s->H; a.W = s->W;
     for (size_t li = p->launches.size(); li-- > 0;) {
         const dynb_launch& l = p->launches[li];
+        a.u = dynb_u_of_group(u, l, chw);
+        a.du = dynb_u_of_group(du, l, chw);
         // a launch group wider than one grid (65535 rows) is walked in slices; its nodes are independent
         for (int off = 0; off < l.count; off += 32768) {
             const int cnt = std::min(32768, l.count - off);
@@ -1026,8 +1030,9 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
     q.items = d_items; q.arity = reinterpret_cast<const uint8_t*>(pd + dynb_plan_arity_offset(p));
     q.fn_first = reinterpret_cast<const int32_t*>(pd + KT.fn_first);
     q.fn_items = reinterpret_cast<const int32_t*>(pd + KT.fn_items);
-    q.feats = feats; q.out = out; q.slots = fwd_ws; q.u = a.u; q.mid = a.mid;
-    q.gy = gy; q.dm = a.dm; q.du = a.du;
+    q.u_at = reinterpret_cast<const int32_t*>(pd + KT.u_at);
+    q.feats = feats; q.out = out; q.slots = fwd_ws; q.u = u; q.mid = a.mid;
+    q.gy = gy; q.dm = a.dm; q.du = du;
     q.C = s->C; q.H = s->H; q.W = s->W;
     q.dw[0] = g->dw3b; q.db[0] = g->db3b; q.dw[1] = g->dw3a; q.db[1] = g->db3a;
     int rc = launch_wgrad<T, false>(q, p->n_types, st);

@@ -33,10 +33,11 @@ enum ConvMode { CV_JOIN, CV_FIRST, CV_SECOND, CV_DSECOND, CV_DFIRST, CV_DJOIN };
 struct ConvArgs {
     int32_t first_item;           // index of items[0] among the items that gy, dm and du hold a map for
     int32_t first_kept;           // index of items[0] among the maps of u and mid
+    // (u and du of kept plans hold maps for two-argument functions only, and the pointers are such that the same indices find them)
     const void* feats;
     void* out;
     void* slots;
-    void* u;                      // results of joins, one map per item
+    void* u;                      // results of joins
     void* mid;                    // results of first convolutions, one map per item
     const void* w;                // the weights of this mode's convolution, in the caller's layout
     const float* bias;

@@ -515,6 +515,7 @@ extern "C" int dynbatch_plan_upload(dynb_plan* p, void* dev_buf, size_t bytes, v
         put(t.units, p->wg_units.data(), p->wg_units.size() * sizeof(dynb_wg_unit));
         put(t.groups, p->wg_groups.data(), p->wg_groups.size() * sizeof(dynb_wg_group));
         put(t.order, p->wg_order.data(), p->wg_order.size() * 4);
+        put(t.u_at, p->u_at.data(), p->u_at.size() * 4);
     }
     if (t.end) HIP_TRY(hipMemcpyAsync(dev_buf, h, t.end, hipMemcpyHostToDevice, st), "dynbatch_plan_upload");
     p->dev_buf = dev_buf;
@@ -528,7 +529,7 @@ extern "C" size_t dynbatch_workspace_bytes(const dynb_plan* p, const dynb_shape*
     if (s->dtype != DYNB_F32 && s->dtype != DYNB_BF16) return 0;
     const size_t map = size_t(s->C) * s->H * s->W * elt_bytes(s->dtype);    // slots are packed
     size_t n = size_t(p->n_slots);
-    if (!fast_shape(s)) n += 2 * dynb_generic_kept_maps(p);                   // mid and u
+    if (!fast_shape(s)) n += dynb_generic_mids(p) + dynb_generic_us(p);
     size_t bytes = align256(n * map);
     if (fast_shape(s)) bytes += align256(packed_weight_bytes(p->n_types));    // weights in MFMA fragment order
     if (fast_shape(s)) bytes += persist_sync_bytes(p);                        // ready flags, ticket counter, status
@@ -536,8 +537,8 @@ extern "C" size_t dynbatch_workspace_bytes(const dynb_plan* p, const dynb_shape*
     return std::max<size_t>(bytes, 256);
 }
 
-// Shapes without a fused kernel: one launch per convolution of a launch group.  u and mid live behind the slots: one map per
-// item of the widest group, or, for the backward pass of a DYNB_PLAN_KEEP plan, one per item of the plan.
+// Shapes without a fused kernel.  mid and u live behind the slots: one map each per item of the widest group, or, for the backward
+// pass of a DYNB_PLAN_KEEP plan, mid of every item of the plan and u of its two-argument functions.
 template <typename T>
 static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_module_weights* w, const void* feats,
                        void* out, char* ws, hipStream_t st)
@@ -546,8 +547,9 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
     const char* d = static_cast<const char*>(p->dev_buf);
     ConvArgs a = {};
     a.feats = feats; a.out = out; a.slots = ws;
-    a.mid = ws + dynb_generic_keep_offset(p, map);
-    a.u = static_cast<char*>(a.mid) + dynb_generic_kept_maps(p) * map;
+    a.mid = ws + dynb_generic_mid_offset(p, map);
+    T* const u = reinterpret_cast<T*>(static_cast<char*>(a.mid) + dynb_generic_mids(p) * map);
+    a.u = u;
     a.C = s->C; a.H = s->H; a.W = s->W;
     const bool timed = dynb::timing_on(), coarse = dynb::timing_coarse();
     if (timed) dynb::timing_mark(st, dynb::ST_SETUP, 0);
@@ -555,6 +557,7 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
     const bool plain = plain_shape<T>(a), whole = !plain && node_shape<T>(a);
     for (const dynb_launch& l : p->launches) {
         evals += l.count;
+        if (p->keep) a.u = dynb_u_of_group(u, l, map / sizeof(T));
         // a grid has at most 65535 rows and 2^32 threads a row: very wide launch groups are split
         const int slice = whole ? 1 << 22 : 32768;
         for (int off = 0; off < l.count; off += slice) {

@@ -24,6 +24,9 @@ struct dynb_launch {
     int32_t start;       // first item
     int32_t count;
     int32_t any_binary;  // some item of the group is a two-argument function (the kernels take the conv1x1 path)
+    // DYNB_PLAN_KEEP: the group's items from its first to its last two-argument function have a kept u (and du) each
+    int32_t u_lo = 0;    // the first of them, an item of the plan
+    int32_t u_first = 0; // ... and its place among the kept maps
 };
 
 // mode 0: second conv3x3 (part = kernel row), 1: first conv3x3 (part = kernel row), 2: conv1x1 (part = argument)
@@ -55,6 +58,8 @@ struct dynb_plan {
     bool shared_nodes = false;           // built by dynbatch_plan_dag: a node may have several consumers
     std::vector<int32_t> grad_dst0, grad_dst1;
     std::vector<int32_t> leaf_first;     // [B+1] leaves of example e are leaf_first[e] .. leaf_first[e+1]
+    std::vector<int32_t> u_at;           // [n_items] place of an item's u among the kept maps (two-argument functions)
+    size_t n_u = 0;                      // kept maps of u
     std::vector<int32_t> root_item;      // [B] item that evaluates the example's root, -1 if the root is a SCENE leaf
     std::vector<int32_t> fn_first;       // [n_types+1] the items of function t are fn_items[fn_first[t] .. fn_first[t+1])
     std::vector<int32_t> fn_items;       // item indices grouped by function, ascending inside a function
@@ -76,7 +81,7 @@ inline size_t dynb_plan_leaf_bytes(const dynb_plan* p) { return dynb_align256(p-
 inline size_t dynb_plan_arity_offset(const dynb_plan* p) { return dynb_plan_items_bytes(p) + dynb_plan_leaf_bytes(p); }
 inline size_t dynb_plan_arity_bytes(const dynb_plan* p) { return dynb_align256(p->arity.size()); }
 inline size_t dynb_plan_ticket_bytes(const dynb_plan* p) { return dynb_align256(p->tickets.size() * sizeof(int32_t)); }
-struct dynb_keep_tables { size_t gdst0, gdst1, leaf_first, root_item, fn_first, fn_items, units, groups, order, end; };   // byte offsets
+struct dynb_keep_tables { size_t gdst0, gdst1, leaf_first, root_item, fn_first, fn_items, units, groups, order, u_at, end; };   // byte offsets
 inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
 {
     dynb_keep_tables t;
@@ -91,6 +96,7 @@ inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
     t.units = take(p->wg_units.size() * sizeof(dynb_wg_unit));
     t.groups = take(p->wg_groups.size() * sizeof(dynb_wg_group));
     t.order = take(p->wg_order.size() * 4);
+    t.u_at = take(p->u_at.size() * 4);
     t.end = o;
     return t;
 }
@@ -109,10 +115,17 @@ inline size_t dynb_fast_sync_bytes(const dynb_plan* p) { return p->persistent ? 
 inline size_t dynb_fast_keep_offset(const dynb_plan* p) { return dynb_fast_sync_offset(p) + dynb_fast_sync_bytes(p); }
 inline size_t dynb_fast_keep_bytes(const dynb_plan* p) { return p->keep ? dynb_align256(2 * p->items.size() * dynb_fast_map_bytes()) : 0; }
 
-// ... and on every other shape: slots | mid | u, for every item of a DYNB_PLAN_KEEP plan (the backward pass reads them),
-// else for the items of one launch group; `map` = bytes of one map
-inline size_t dynb_generic_keep_offset(const dynb_plan* p, size_t map) { return size_t(p->n_slots) * map; }
-inline size_t dynb_generic_kept_maps(const dynb_plan* p) { return p->keep ? p->items.size() : size_t(p->max_launch); }
+// ... and on every other shape: slots | mid | u; for a DYNB_PLAN_KEEP plan mid of every item and u of the two-argument functions (the
+// backward pass reads them), else both for the items of one launch group; `map` = bytes of one map
+inline size_t dynb_generic_mid_offset(const dynb_plan* p, size_t map) { return size_t(p->n_slots) * map; }
+inline size_t dynb_generic_mids(const dynb_plan* p) { return p->keep ? p->items.size() : size_t(p->max_launch); }
+inline size_t dynb_generic_us(const dynb_plan* p) { return !p->has_binary ? 0 : p->keep ? p->n_u : size_t(p->max_launch); }
+// What the kernels add an item's number to, to find its u among the kept ones of `maps`: the group's share starts with item u_lo
+// (items outside it have none, and their numbers are not used)
+template <typename T> T* dynb_u_of_group(T* maps, const dynb_launch& l, size_t map_elements)
+{
+    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(maps) + (uintptr_t(l.u_first) - uintptr_t(l.u_lo)) * map_elements * sizeof(T));
+}
 
 namespace dynb {
 void set_error(const std::string& msg);

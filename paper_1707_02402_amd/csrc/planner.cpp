@@ -341,6 +341,17 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
         p->fn_items.resize(p->items.size());
         std::vector<int32_t> at(p->fn_first.begin(), p->fn_first.end() - 1);
         for (size_t i = 0; i < p->items.size(); ++i) p->fn_items[at[p->items[i].type]++] = int32_t(i);
+        // room for u of two-argument functions: every group from its first to its last (they are sorted by function)
+        p->u_at.assign(p->items.size(), 0);
+        for (dynb_launch& l : p->launches) {
+            int32_t lo = l.start + l.count, hi = l.start;
+            for (int32_t i = l.start; i < l.start + l.count; ++i)
+                if (arity[p->items[i].type] == 2) { lo = std::min(lo, i); hi = i + 1; }
+            if (lo >= hi) continue;
+            l.u_lo = lo;
+            l.u_first = int32_t(p->n_u);
+            for (int32_t i = lo; i < hi; ++i) p->u_at[i] = int32_t(p->n_u++);
+        }
         // units of the parameter-gradient kernel
         // (every function has its groups, also those without a gradient of that kind: their sum is zero; the
         // conv1x1 groups exist only if the batch uses a two-argument function at all)

@@ -110,6 +110,24 @@ def test_parameter_gradients_of_many_items_on_tiny_maps(dyn, util, oracle, dtype
         assert (again[name] == got[name]).all(), name
 
 
+@pytest.mark.parametrize("C,H,W", [(20, 9, 10), (16, 8, 8), (4, 5, 3)])
+def test_one_and_two_argument_functions_in_any_order_of_their_numbers(dyn, util, oracle, C, H, W):
+    """The kept maps of two-argument functions lie in one run per launch group, one-argument functions in between or not."""
+    import dataclasses
+    w = iep.small_mixed(seed=C, B=17, C=C, H=H, W=W, dtype="f32", min_len=1, max_len=9)
+    assert w.arity.tolist() == [0, 1, 1, 1, 2, 2]
+    order = np.array([0, 2, 4, 5, 1, 3])                      # new number of every function
+    back = np.argsort(order)
+    mixed = dataclasses.replace(w, arity=w.arity[back], prog=order[w.prog].astype(np.int32), **{k: getattr(w, k)[back] for k in ("w1", "b1", "w3a", "b3a", "w3b", "b3b")})
+    dout = np.random.default_rng(C).standard_normal(w.feats.shape).astype(np.float32)
+    ref = oracle.iep_backward_workload(mixed, dout)
+    for flags in (0, 1, 2, 3, dyn.DYNB_PLAN_BALANCE):
+        got, out = run_backward(dyn, util, mixed, dout, flags)
+        assert util.normwise(out, oracle.iep_forward_workload(mixed)) < 1e-4
+        for name in NAMES:
+            assert maxnorm(got[name], getattr(ref, name)) < 1e-4, (flags, name)
+
+
 def test_the_width_of_a_launch_group_does_not_change_the_gradients_bits(dyn, util, oracle):
     """fp32, C = 160, 14 x 14: the summed channels fit LDS at once beside some of the workgroup tiles only."""
     arity = np.array([0, 1, 2], np.uint8)

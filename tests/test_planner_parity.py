@@ -316,3 +316,21 @@ def test_backward_tables_of_a_keep_plan(dyn):
     # without the flag there are no such tables
     v0 = dyn.dynbatch_plan_view(dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, dyn.DYNB_PLAN_BALANCE))
     assert v0.n_wg_units == 0 and len(v0.fn_items) == 0 and len(v0.grad_dst0) == 0
+
+
+@pytest.mark.parametrize("dtype,elt", [("f32", 4), ("bf16", 2)])
+def test_workspaces_of_a_keep_plan_away_from_the_fused_shape(dyn, dtype, elt):
+    """Forward: a slot and mid per module, u per two-argument module.  Backward (fp32): the gradients of a module's result and of mid
+    per module, of u per two-argument module, and one map per SCENE leaf."""
+    code = dyn.DYNB_BF16 if dtype == "bf16" else dyn.DYNB_F32
+    C, H, W = 48, 7, 9
+    up = lambda v: (v + 255) // 256 * 256
+    programs = [(w.prog, w.prog_off, w.arity) for w in (iep.config2(B=40), iep.config1(B=3))]
+    programs.append((np.array([1, 1, 0, 0, 1, 0], np.int32), np.array([0, 3, 4, 6], np.int32), np.array([0, 1], np.uint8)))
+    for prog, off, arity in programs:
+        for flags in (0, dyn.DYNB_PLAN_BALANCE, dyn.DYNB_SCHED_NAIVE):
+            plan = dyn.dynbatch_plan(prog, off, arity, flags | dyn.DYNB_PLAN_KEEP)
+            v = dyn.dynbatch_plan_view(plan)
+            n, two, leaves, m = v.n_compute_nodes, int((arity[prog] == 2).sum()), int((arity[prog] == 0).sum()), C * H * W
+            assert dyn.dynbatch_workspace_bytes(plan, C, H, W, code) == up((v.n_slots + n + two) * m * elt)
+            assert dyn.dynbatch_backward_workspace_bytes(plan, C, H, W, code) == sum(max(256, up(k * m * 4)) for k in (n, leaves, n, two))
