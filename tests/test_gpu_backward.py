@@ -237,6 +237,36 @@ def test_bf16_single_modules(dyn, util, oracle):
         assert (again[name] == got[name]).all(), name                     # no atomics: same bits
 
 
+@pytest.mark.parametrize("nodes", [1, 36, 37, 64, 65, 128, 129, 256, 257])
+def test_bf16_single_modules_in_every_layout_of_a_node(dyn, util, oracle, nodes):
+    """Random-sign data, so that every mask matters, in groups of the widths where a node is spread over 7, 4, 2 workgroups or 1: the
+    gradients of sampled examples against the oracle, the sums against a DYNB_PLAN_THROUGHPUT plan (one workgroup per node, the same
+    units of parameter gradients) bit for bit.  (dout is zero outside the sample: the full batch's parameter gradients are those of the sample.)"""
+    arity = np.array([0, 1, 2, 1, 2], np.uint8)
+    progs = [np.array([1 + i % 4] + [0] * (1 + i % 2), np.int32) for i in range(nodes)]
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    w = iep.IepWorkload("layouts", "bf16", arity, np.concatenate(progs), off, 128, 14, 14,
+                        iep.make_feats(nodes, nodes, 14, 14, 128, "bf16"), *iep.make_weights(79, arity, 128, "bf16"))
+    sample = sorted({0, nodes // 3, nodes // 2 + 1, nodes - 2, nodes - 1} & set(range(nodes)))
+    sub = w.subset(sample)
+    dsub = np.random.default_rng(nodes).standard_normal(sub.feats.shape).astype(np.float32)
+    # (one result in some 50000 is so near zero that fp32 and fp64 sums round to different sides of it; it gets no gradient)
+    dsub[(util.iep_run(dyn, sub) > 0) != (oracle.iep_backward_workload(sub, dsub, round_bf16=True).roots > 0)] = 0
+    dout = np.zeros(w.feats.shape, np.float32)
+    dout[sample] = dsub
+    ref = oracle.iep_backward_workload(sub, dsub, round_bf16=True)
+    got, _ = run_backward(dyn, util, w, dout)
+    for name in NAMES:
+        g = got[name][sample] if name == "dfeats" else got[name]
+        assert maxnorm(g, getattr(ref, name)) < 1e-2, (name, maxnorm(g, getattr(ref, name)))
+        assert frob(g, getattr(ref, name)) < 5e-3, (name, frob(g, getattr(ref, name)))
+    dense = np.random.default_rng(nodes + 1).standard_normal(w.feats.shape).astype(np.float32)
+    a, _ = run_backward(dyn, util, w, dense)
+    b, _ = run_backward(dyn, util, w, dense, dyn.DYNB_PLAN_THROUGHPUT)
+    for name in NAMES:
+        assert (a[name] == b[name]).all(), name
+
+
 def _sampled(w, seed):
     """dout that is zero outside a sample of the examples, and the sample as a workload of its own.  The backward
     pass is linear in dout and examples are independent, so every parameter gradient of the full batch equals that
@@ -253,7 +283,7 @@ def test_config2_full_batch_with_every_unit_active(dyn, util, oracle):
     """The benchmark's programs, shapes and launch configuration (256 programs, 27 labels, balanced launch groups,
     MFMA kernels) with non-negative weights, biases and feature maps: every ReLU is active, the network is linear,
     and nothing but rounding separates the two sides at any depth.  This pins the routing of the gradients through
-    4066 nodes, the sums over all nodes of a function and every launch shape; the masks are pinned by the tests above."""
+    4066 nodes, the sums over all nodes of a function and every launch shape; the masks are pinned by the tests above, in every layout."""
     import dataclasses
     from workloads.rng import round_bf16, stream
     w = iep.config2()

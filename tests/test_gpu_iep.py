@@ -459,10 +459,23 @@ def test_a_wait_that_expires_is_reported_and_every_workgroup_still_exits(dyn, ut
     assert (util.to_host(good) == util.iep_run(dyn, w)).all()
 
 
-@pytest.mark.parametrize("nodes", [1, 128, 129, 256, 257])
-def test_half_and_whole_node_layouts_at_the_width_where_they_change(dyn, util, oracle, nodes):
-    """Launch groups of up to 128 nodes spread a node over two workgroups, wider ones and DYNB_PLAN_THROUGHPUT plans give
-    it one: the same bits, one- and two-argument functions mixed, and a few examples against the oracle."""
+def kept_maps(dyn, util, w, flags):
+    """u and mid as the execution of a plan that keeps them leaves them at the end of its workspace (zeros where nothing is kept)."""
+    import torch
+    plan = dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, flags | dyn.DYNB_PLAN_KEEP)
+    dyn.dynbatch_plan_upload(plan)
+    feats = util.to_dev(w.feats, w.dtype)
+    ws = torch.zeros(dyn.dynbatch_workspace_bytes(plan, w.C, w.H, w.W, dyn.DYNB_BF16), dtype=torch.uint8, device="cuda")
+    dyn.dynbatch_execute(plan, util.iep_weights_dev(w), feats, workspace=ws)
+    kept = 2 * dyn.dynbatch_plan_view(plan).n_compute_nodes * w.C * w.H * w.W * 2
+    return ws[-((kept + 255) // 256 * 256):].cpu().numpy()
+
+
+@pytest.mark.parametrize("nodes", [1, 36, 37, 64, 65, 128, 129, 256, 257])
+def test_layouts_of_a_node_at_the_widths_where_they_change(dyn, util, oracle, nodes):
+    """Launch groups spread a node over 7 (up to 36 nodes), 4 (64), 2 (128) workgroups or 1; DYNB_PLAN_THROUGHPUT plans always give it
+    one: the same bits, one- and two-argument functions mixed, and a few examples against the oracle.  Plans that keep u and mid store
+    them from the same layouts."""
     arity = np.array([0, 1, 2, 1, 2], np.uint8)
     progs = [np.array([1 + i % 4] + [0] * (1 + (i % 2)), np.int32) for i in range(nodes)]
     off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
@@ -470,6 +483,8 @@ def test_half_and_whole_node_layouts_at_the_width_where_they_change(dyn, util, o
                         iep.make_feats(nodes, nodes, 14, 14, 128, "bf16"), *iep.make_weights(78, arity, 128, "bf16"))
     got = util.iep_run(dyn, w)
     assert (util.iep_run(dyn, w, dyn.DYNB_PLAN_THROUGHPUT) == got).all()
+    assert (util.iep_run(dyn, w, dyn.DYNB_PLAN_KEEP) == got).all()
+    assert (kept_maps(dyn, util, w, 0) == kept_maps(dyn, util, w, dyn.DYNB_PLAN_THROUGHPUT)).all()
     sample = sorted({0, nodes // 2, nodes - 1})
     ref = oracle.iep_forward_workload(w.subset(sample))
     for j, i in enumerate(sample):
