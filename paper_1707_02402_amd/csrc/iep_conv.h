@@ -13,7 +13,7 @@
 // fp32 operands use v_mfma_f32_16x16x4 (fp32 products and sums: 157 TFLOP/s on the chip, the vector unit without packed
 // instructions half of that), bf16 operands v_mfma_f32_16x16x32_bf16.  The kernel before this one gave every output element
 // to a thread that read its 9 C products' operands from the caches: 21 training programs in fp32 at C = 128, 14 x 14
-// went from 179 to 3.2 ms, 64 programs in bf16 at 7 x 7 from 45 to 0.61 ms.
+// went from 179 to 2.5 ms, 64 programs in bf16 at 7 x 7 from 45 to 0.6 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -849,10 +849,11 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
 // it runs ceil(workgroups / 256) workgroups, each with its MFMAs (a quarter of the steps per SIMD), the staging of its
 // pixels at about 24 bytes per clock, and about 1200 clocks of its own.  Large tiles read weights and halos less
 // often per output; small ones split the launch into CU-sized shares more finely.  Measured for fp32, C = 128, 14 x 14, us:
-//     items      1     6     9     12    15    18    21    25
-//     4 x 2    15.7  15.8  16.3  16.5  16.9  27.3  27.6  27.4
-//     2 x 2    10.0  10.4  10.9  17.0  17.1  17.9  23.4  23.9
-//     2 x 1     7.4  10.9  11.4  14.9  19.0  19.6  23.2  26.3
+//     items      1     2     4     6     9     12    15    18    21    25
+//     4 x 2    15.2  15.0  15.1  15.4  15.8  16.3  16.6  27.1  27.1  27.2
+//     2 x 2    10.4  10.5  10.6  10.8  10.9  17.4  17.7  18.1  23.6  23.2
+//     2 x 1     7.6   7.6   7.9  11.5  11.6  15.4  19.7  21.7  23.3  26.3
+//     1 x 1     6.5   6.7   9.0  11.2  15.1  17.6  23.1  25.6  28.0  32.6
 template <typename T, ConvMode MODE, bool FULL>
 int launch_conv_full(const dynb_item* items, ConvArgs a, int count, hipStream_t st)
 {
@@ -906,7 +907,9 @@ int launch_conv_plain(const dynb_item* items, const ConvArgs& a, int count, hipS
     return DYNB_OK;
 }
 
-// k_node: pixel tiles per unit: 4 read the weights a quarter as often, 1 gives all waves work where there are few tiles
+// k_node: pixel tiles per unit: 4 read the weights a quarter as often, 1 gives all waves work where there are few tiles.  us for one
+// module, 1 / 4 tiles: fp32 C = 16, 8 x 8 6.1 / 9.5, 14 x 14 12.3 / 10.1; C = 32, 7 x 7 12.0 / 14.5; bf16 C = 16, 14 x 14 21.6 / 14.4, 20 x 20 33.8 /
+// 16.1; C = 24, 14 x 14 34.8 / 16.1; C = 32, 14 x 14 14.7 / 9.8.
 inline bool node_wide(int pt, int ct) { return ((pt + 3) / 4 * ct + 7) / 8 * 4 <= (pt * ct + 7) / 8; }
 
 // Whole modules by k_node, where that takes one CU no longer than two or three launches of k_conv take to get going (5 us

@@ -3,7 +3,7 @@
 //
 // Two kernel families with the same semantics:
 //   * k_module_mfma  — bf16, C = 128, 14 x 14: one fused kernel per launch group.  A workgroup
-//                      owns a node or half a node; the node's input map is gathered straight into an
+//                      owns a node or a part of one; the node's input map is gathered straight into an
 //                      LDS halo tile, conv1x1 (binary functions), conv3x3, ReLU, conv3x3, residual
 //                      add and ReLU all run from that tile on MFMA, and the result is scattered to
 //                      the node's slot (or to the output tensor for a root).

@@ -14,12 +14,13 @@ constexpr int S = 14;                    // spatial size
 constexpr int P = S * S;                 // 196 pixels
 constexpr int HALO = 16;                 // tile side with zero border
 constexpr int PIX_BYTES = 272;           // 128 channels bf16 + 16 bytes pad: 17 granules of 16 bytes
-// A pixel (y, x) sits at granule x (mod 16): the pixels of one image row, which half a fragment reads, fall on
-// distinct granules, i.e. on all 64 LDS banks.
+// A pixel (y, x) sits at granule x + y (mod 16): the pixels of one image row, which half a fragment reads, fall on distinct
+// granules, i.e. on all 64 LDS banks.  The two rows of a fragment are one granule apart, and an LDS pass takes lanes of both:
+// the counters report 0.45 of the LDS cycles as bank conflicts, under MFMAs that take longer.
 // Rows are 17 pixels wide: columns 15 and 16 and the next row's column 0 are zeros, which is what the two padding columns
 // of a pixel tile (below) read, whatever the tap.  (Zeros and not the last pixel again: the chip is at its power limit in
-// these kernels, and the matrix pipes take less of it for zeros; the K loop alone, on all CUs, runs at 1.62 instead of
-// 1.52 PFLOP/s.)
+// these kernels, and the matrix pipes take less of it for zeros: builds that run the K loop alone, on all CUs, reach 1.62 instead
+// of 1.52 PFLOP/s.)
 constexpr int ROW_PIX = HALO + 1;
 constexpr int ROW_BYTES = ROW_PIX * PIX_BYTES;         // 4624
 constexpr int TILE_BYTES = HALO * ROW_BYTES + PIX_BYTES;   // 74256: the last row's neighbour is a zero pixel of its own
@@ -95,7 +96,7 @@ __device__ __forceinline__ void zero_border_piece(int c)
 // (tile s/2) and tap row 2 (tile s/2 - 1), odd ones with tap row 1.  MTW = 7: 15 LDS reads for 21 MFMAs.
 // The loop itself is bound by the matrix pipes: 17.4k clocks per conv3x3 of a lone workgroup with everything hot in L2
 // (504 MFMAs per wave are 16.1k; the LDS reads add 0.1k, the weight loads 0.6k), 18.3k in the kernel.  On the whole chip it
-// is bound by power, not by any pipe (the clock falls to 1.7-1.9 GHz of 2.4): register-only MFMAs on random data reach
+// is bound by power, not by any pipe (the clock falls to 1.7-1.9 GHz of 2.4): in such builds register-only MFMAs on random data reach
 // 1.70 PFLOP/s, the LDS reads cost 7 % of that and the weight loads 11 %, which is why every fragment is read once per
 // use of its rows and once per workgroup.
 // Software pipelined by hand:
