@@ -41,7 +41,7 @@ constexpr int TN = 256;           // output features of one grouped-GEMM tile
 constexpr int NTW = TN / 64;      // 16-feature sub-tiles per wave (4 waves split the features)
 constexpr int MAX_K = 8;          // uses of a token whose places are kept in registers (more are looked up)
 constexpr int MG = 8;             // row tiles of one expert that walk the feature tiles together
-constexpr int XCD_CHUNK = 128;    // consecutive grouped-GEMM tiles dealt to one XCD
+constexpr int XCD_CHUNK = 128;    // most consecutive grouped-GEMM tiles dealt to one XCD
 
 __device__ __forceinline__ bf16x8 ldg_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
@@ -1011,7 +1011,7 @@ template <bool RELU>
 __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W,
                                                       bf16_t* __restrict__ out, const int32_t* __restrict__ offsets,
                                                       const int32_t* __restrict__ tile_start, int E, int N, int K,
-                                                      int n_tiles_n, int chunk, const int32_t* __restrict__ gather, int kdiv)
+                                                      int n_tiles_n, const int32_t* __restrict__ gather, int kdiv)
 {
     __shared__ __attribute__((aligned(16))) bf16_t Ws[TN * LDP];
     __shared__ __attribute__((aligned(16))) bf16_t Xs[TM * LDP];
@@ -1019,20 +1019,25 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__
     // inside a group the row tiles that share one feature tile are adjacent (feature tile outer, row
     // tile inner), so a weight tile is fetched from HBM once and then found in L2 by the other row
     // tiles of its group.  Consecutive workgroup ids land on different XCDs (8 of them, each with
-    // its own L2), so the numbering is dealt to the XCDs in runs of `chunk` tiles: everything that
-    // shares weights or activation rows stays behind one L2.
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    const long long lin = (long long)(j / chunk * 8 + xcd) * chunk + j % chunk;
-    if (lin >= (long long)tile_start[E] * n_tiles_n) return;
-    const int lin_m = int(lin / n_tiles_n);
-    int lo = 0, hi = E;                          // largest e with tile_start[e] <= lin_m
+    // its own L2), so the numbering is dealt to the XCDs in equal runs of at most XCD_CHUNK tiles:
+    // everything that shares weights or activation rows stays behind one L2, and every XCD gets as many runs.
+    const uint32_t total = uint32_t(tile_start[E]) * uint32_t(n_tiles_n);      // (below 2^31: check_shape bounds the grid; at least one tile)
+    const uint32_t runs = (total + 8 * XCD_CHUNK - 1) / (8 * XCD_CHUNK), chunk = (total + 8 * runs - 1) / (8 * runs);
+    const uint32_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const uint32_t lin = (j / chunk * 8 + xcd) * chunk + j % chunk;
+    if (j >= runs * chunk || lin >= total) return;
+    const int lin_m = int(lin / uint32_t(n_tiles_n));
+    // largest e with tile_start[e] <= lin_m, 64 places looked at together: two trips to memory for up to 4096 experts
+    int lo = 0, hi = E;
     while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tile_start[mid] <= lin_m) lo = mid; else hi = mid;
+        const int stride = (hi - lo + 63) / 64, at = lo + int(threadIdx.x & 63) * stride;
+        const int below = __popcll(__ballot(at < hi && tile_start[min(at, E)] <= lin_m));   // (place 0 always is)
+        lo += (below - 1) * stride;
+        hi = min(lo + stride, hi);
     }
     const int e = lo;
     const int mt_e = tile_start[e + 1] - tile_start[e];
-    const int i = int(lin - (long long)tile_start[e] * n_tiles_n);   // tile of this expert, 0 .. mt_e * n_tiles_n
+    const int i = int(lin) - tile_start[e] * n_tiles_n;   // tile of this expert, 0 .. mt_e * n_tiles_n
     const int mg = i / (MG * n_tiles_n);
     const int rem = i - mg * MG * n_tiles_n;
     const int gsize = min(MG, mt_e - mg * MG);
@@ -1346,14 +1351,14 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         else
             hipLaunchKernelGGL((k_grouped_gemm<true>), dim3(unsigned((max_mtiles * nt1 + span - 1) / span * span)), dim3(256), 0, st,
                                fused_permute ? xb : xs, static_cast<const bf16_t*>(W1), hid, offsets, tile_start, E, h, d, nt1,
-                               XCD_CHUNK, fused_permute ? perm : nullptr, k);
+                               fused_permute ? perm : nullptr, k);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
         if (skinny2)
             hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(skinny_tiles * ((d + 63) / 64))), dim3(256), 0, st, hid,
                                static_cast<const bf16_t*>(W2), y, tiles, d, h, (d + 63) / 64, nullptr, 1);
         else
             hipLaunchKernelGGL((k_grouped_gemm<false>), dim3(unsigned((max_mtiles * nt2 + span - 1) / span * span)), dim3(256), 0, st,
-                               hid, static_cast<const bf16_t*>(W2), y, offsets, tile_start, E, d, h, nt2, XCD_CHUNK, nullptr, 1);
+                               hid, static_cast<const bf16_t*>(W2), y, offsets, tile_start, E, d, h, nt2, nullptr, 1);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else {
         // the paper's naive version: loop over the k*b expert uses, one expert call (two layers) per use
@@ -1368,9 +1373,9 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             for (int pos = off[e]; pos < off[e + 1]; ++pos) {
                 if (pos % naive_stride) continue;
                 hipLaunchKernelGGL((k_grouped_gemm<true>), dim3((nt1 + 7) / 8 * 8), dim3(256), 0, st, xs + size_t(pos) * d,
-                                   w1 + size_t(e) * h * d, hid + size_t(pos) * h, unit, unit + 2, 1, h, d, nt1, 1, nullptr, 1);
+                                   w1 + size_t(e) * h * d, hid + size_t(pos) * h, unit, unit + 2, 1, h, d, nt1, nullptr, 1);
                 hipLaunchKernelGGL((k_grouped_gemm<false>), dim3((nt2 + 7) / 8 * 8), dim3(256), 0, st, hid + size_t(pos) * h,
-                                   w2 + size_t(e) * d * h, y + size_t(pos) * d, unit, unit + 2, 1, d, h, nt2, 1, nullptr, 1);
+                                   w2 + size_t(e) * d * h, y + size_t(pos) * d, unit, unit + 2, 1, d, h, nt2, nullptr, 1);
             }
         if (timed) { dynb::timing_mark(st, dynb::ST_FFN1, 0); dynb::timing_mark(st, dynb::ST_FFN2, 0); }
     }
