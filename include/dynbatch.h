@@ -155,11 +155,12 @@ typedef struct {
                                     fn_first[t+1]), ascending                                      */
     const int32_t* fn_items;     /* [n_compute_nodes]                                             */
     int32_t n_types;
-    int32_t n_wg_units;          /* units of work of the parameter-gradient kernel                */
+    int32_t n_wg_units;          /* partial sums of the parameter-gradient kernel                 */
     const int32_t* wg_units;     /* [n_wg_units][8]: mode (0 second conv3x3, 1 first conv3x3, 2 conv1x1),
                                     function, part (kernel row, or argument for mode 2), begin, end (a chunk
                                     fn_items[begin .. end) of at most 16 items), 3 unused            */
-    const int32_t* wg_order;     /* [n_wg_units] unit taken by every workgroup of that kernel     */
+    const int32_t* wg_order;     /* [n_wg_units] the units, longest chunks first: the order in which that kernel's
+                                    workgroups take the chunks                                     */
 } dynb_plan_view;
 
 /* Builds the plan for a minibatch of programs (Background / Visual Reasoning Programs: the fixed

@@ -674,26 +674,32 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     }
 }
 
-// Parameter gradients.  A unit of work sums one chunk of a function's items for one (mode, part):
+// Parameter gradients.  A unit is the partial sum over one chunk of a function's items for one (mode, part):
 //   mode 0: conv_b, part = kernel row kh:  dW_b[co][kh][kw][ci] = sum_items sum_p g[p][co]    mid[p + (kh-1, kw-1)][ci]
 //   mode 1: conv_a, part = kernel row kh:  dW_a[co][kh][kw][ci] = sum_items sum_p dmid[p][co] u[p + (kh-1, kw-1)][ci]
 //   mode 2: conv1x1, part = argument:      dW_1[co][part*C + ci] = sum_items sum_p dc[p][co]  arg_part[p][ci]
-// and with part 0 the bias gradient, the sum of g / dmid / dc over items and pixels.
-// The contraction runs over pixels, the dimension in which neither map is contiguous.  Both maps of an item are
-// copied into LDS halo tiles (pixel-major like the forward pass's tile) and the MFMA operands are read from
-// there four bytes (two channels of a pixel) at a time: lane (m, hk) holds, for the 8 pixels x = 8 hk .. 8 hk + 7 of image
-// row y, channels 2 m and 2 m + 1, which are row m of the wave's two interleaved channel tiles; a K step is an image
-// row (x = 14, 15 are zeros).  For a kernel row the three taps' fragments of the
-// input map are the same 10 pixels shifted by one, so they are read once.  The reads of row y + 1 are issued ahead of
-// the MFMAs of row y and packed into fragments behind them.  D[ci][co] accumulates in registers over the unit's items, in item order, and is written to the
-// unit's partial result; k_bwd_wgrad_sum adds the partial results of a (function, part) in chunk order.  Nothing is
-// atomic.  The bias gradient is the same contraction with a fragment of ones in place of the input map.
+// and with part 0 the bias gradient, the sum of g / dmid / dc over items and pixels.  k_bwd_wgrad_sum adds the units of a (function,
+// part) in chunk order.  Nothing is atomic.
+//
+// A workgroup sums one chunk for a quadrant of the channels, 64 output x 64 input ones, and all nine taps (of the 1x1: one argument); a
+// wave 32 x 32 of them:  D[co][ci] += G[co][16 pixels] IN[16 pixels][ci]  (v_mfma_f32_32x32x16_bf16), a K step being an image row
+// (14 pixels and 2 zeros).  The contraction runs over pixels, the dimension in which neither map is contiguous: both
+// half maps of an item are copied into LDS as they are, pixel by pixel, and read with the transposing LDS load, whose lanes get four
+// pixels of one channel each.  An input row is read for the three tap columns and multiplied with the three gradient rows that its
+// tap rows want, so a step of 9 MFMAs (288 clocks) reads 8 KB, where one kernel row at a time for all 128 x 128 channels reads 18 KB four
+// bytes a lane and packs the operands with 72 permutes for 12.  57 KB of LDS and 256 registers: two workgroups share a CU, and one's
+// copying runs under the other's MFMAs.  256 programs (4276 modules): 747 -> 397 us, MFMA
+// busy 0.38 -> 0.66 of the time, no bank conflicts; the rest is the end of the last round of workgroups and waits for maps.
+// A staged pixel is 128 bytes without padding; its halves (32 channels, what a wave reads) are exchanged in every other pair
+// of pixels, so that the four pixels x 64 bytes that 32 lanes read lie on all 64 banks.
 struct WgArgs {
     const dynb_item* items;       // all items of the plan
-    const uint8_t* arity;
     const dynb_wg_unit* units;
-    const int32_t* order;         // workgroup -> unit
+    const int32_t* order;         // the units, longest chunks first
+    const int32_t* fn_first;
     const int32_t* fn_items;
+    int32_t n_chunks;             // chunks of the 3x3s: three units each
+    int32_t n_joins;              // units of the 1x1, behind the others
     const bf16_t* feats;
     const bf16_t* slots;
     const bf16_t* sv_u;
@@ -704,190 +710,184 @@ struct WgArgs {
     float* partial;               // [unit][3][C][C] weight gradient ([tap][co][ci]; conv1x1: tap 0 only), then [C] bias gradient
 };
 constexpr size_t WG_PARTIAL = size_t(3) * 128 * 128 + 128;           // floats per unit
+constexpr int WG_ROW = 16 * 128, WG_MAP = mf::S * WG_ROW;            // LDS: bytes of an image row (columns 14, 15 are zeros), of a half map
 
-template <int MODE>
-__device__ __forceinline__ void wgrad_unit(const WgArgs& a, const dynb_wg_unit un, float* __restrict__ part_out)
+// four pixels (at this lane's pixel address and its three neighbours') of one channel per lane
+__device__ __forceinline__ i16x4 lds_read_pixels(uint32_t addr)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    using lds_i16x4 = __attribute__((address_space(3))) i16x4;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>((__attribute__((address_space(3))) unsigned char*)lds_raw + addr));
+}
+
+// CONV: un is the first of the chunk's three units (kernel row 0), the others follow `stride` units apart
+template <bool CONV>
+__device__ __forceinline__ void wgrad_chunk(const WgArgs& a, const dynb_wg_unit un, const int32_t unit, const int32_t stride, const int quad)
 {
     using namespace mf;
-    constexpr int NTAP = MODE == 2 ? 1 : 3, NV = MODE == 2 ? 8 : 10, NTHR = 256;
+    constexpr int K = CONV ? 3 : 1, NTHR = 256;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int part = un.part;
-    const int ar = a.arity[un.type];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int m = lane & 31, hk = lane >> 5, wi = wave & 1, wj = wave >> 1;
-    constexpr uint32_t TILE_G = TILE_BYTES;                            // the gradient map's tile follows the input map's
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wi = wave & 1, wj = wave >> 1, ci_half = quad & 1, co_half = quad >> 1;
 
-    for (int c = tid; c < 2 * TILE_BYTES / 16; c += NTHR) reinterpret_cast<u32x4*>(lds_raw)[c] = u32x4{0u, 0u, 0u, 0u};
-
-    f32x16 acc[NTAP][2][2], accb[2];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-#pragma unroll
-        for (int k = 0; k < NTAP; ++k)
-#pragma unroll
-            for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-                for (int cj = 0; cj < 2; ++cj) acc[k][ct][cj][i] = 0.f;
-        accb[0][i] = 0.f; accb[1][i] = 0.f;
-    }
-    constexpr int NIT = (P * 16 + NTHR - 1) / NTHR;
-    u32x4 tin[NIT], tg[NIT];
-    auto load = [&](int idx) {
-        const int32_t item = a.fn_items[idx];
+    // the chunk's items, one per lane (at most 16): where the input map and the gradient map start, this quadrant's halves of them
+    uint64_t in_at, g_at;
+    {
+        const int32_t item = a.fn_items[min(un.begin + (lane & (DYNB_WG_CHUNK - 1)), un.end - 1)];
         const dynb_item it = a.items[item];
         const size_t off = size_t(item) * (P * C);
-        const bf16_t* G = (MODE == 0 ? a.sv_g : MODE == 1 ? a.sv_dm : a.sv_dc) + off;
-        const bf16_t* IN;
-        if (MODE == 0) IN = a.sv_m + off;
-        else if (MODE == 1 && ar == 2) IN = a.sv_u + off;
-        else {
-            const int32_t s = (MODE == 2 && part == 1) ? it.src1 : it.src0;
-            IN = s >= 0 ? a.slots + size_t(s) * (P * C) : a.feats + size_t(-1 - s) * (P * C);
-        }
+        const int32_t s = !CONV && un.part == 1 ? it.src1 : it.src0;
+        const bf16_t* IN = un.mode == 0                              ? a.sv_m + off
+                           : un.mode == 1 && it.src1 != DYNB_NO_ARG ? a.sv_u + off
+                           : s >= 0                                  ? a.slots + size_t(s) * (P * C)
+                                                                     : a.feats + size_t(-1 - s) * (P * C);
+        const bf16_t* G = (un.mode == 0 ? a.sv_g : un.mode == 1 ? a.sv_dm : a.sv_dc) + off;
+        in_at = reinterpret_cast<uint64_t>(IN + ci_half * 64);
+        g_at = reinterpret_cast<uint64_t>(G + co_half * 64);
+    }
+    // (said to be global: a flat load would count among the LDS accesses, and every wait for a fragment would be for the maps too)
+    using global_bytes = const __attribute__((address_space(1))) unsigned char*;
+    using global_piece = const __attribute__((address_space(1))) u32x4*;
+    auto of_lane = [](uint64_t v, int l) -> global_bytes {
+        const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l)), hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), l));
+        return reinterpret_cast<global_bytes>(uint64_t(hi) << 32 | lo);
+    };
+    // zeros in columns 14 and 15 of both maps' rows
+    for (int c = tid; c < 2 * S * 16; c += NTHR) *reinterpret_cast<u32x4*>(lds_raw + uint32_t((c >> 4) * WG_ROW + S * 128 + (c & 15) * 16)) = u32x4{0u, 0u, 0u, 0u};
+
+    // copying: 16-byte pieces, eight per pixel.  Their addresses are made anew for every item (here(), whose value the compiler cannot carry
+    // through the loop): kept, they would take the registers that the next item's maps wait in.
+    constexpr int NP = (P * 8 + NTHR - 1) / NTHR;
+    u32x4 tin[NP], tg[NP];
+    auto here = [&]() -> uint32_t {
+        uint32_t t = uint32_t(tid);
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto load = [&](int n) {
+        const global_bytes in = of_lane(in_at, n), g = of_lane(g_at, n);
+        const uint32_t t = here();
 #pragma unroll
-        for (int i = 0; i < NIT; ++i) {
-            const int c = tid + i * NTHR;
-            if (c < P * 16) { tin[i] = reinterpret_cast<const u32x4*>(IN)[c]; tg[i] = reinterpret_cast<const u32x4*>(G)[c]; }
+        for (int i = 0; i < NP; ++i) {                                // (the last pixel again where there are no more)
+            const uint32_t p = (t >> 3) + uint32_t(i * (NTHR / 8)), at = (i + 1 < NP ? p : min(p, uint32_t(P - 1))) * (C * 2) + (t & 7) * 16;
+            tin[i] = *reinterpret_cast<global_piece>(in + at);
+            tg[i] = *reinterpret_cast<global_piece>(g + at);
         }
     };
     auto store = [&]() {
+        const uint32_t t = here();
 #pragma unroll
-        for (int i = 0; i < NIT; ++i) {
-            const int c = tid + i * NTHR;
-            if (c < P * 16) {
-                const int p = c >> 4, piece = c & 15;
-                const uint32_t addr = uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + piece * 16);
-                *reinterpret_cast<u32x4*>(lds_raw + addr) = tin[i];
-                *reinterpret_cast<u32x4*>(lds_raw + TILE_G + addr) = tg[i];
+        for (int i = 0; i < NP; ++i)
+            if (i + 1 < NP || t + uint32_t(i * NTHR) < uint32_t(P * 8)) {
+                const uint32_t p = (t >> 3) + uint32_t(i * (NTHR / 8)), y = p / S, x = p - y * S;
+                const uint32_t at = y * WG_ROW + x * 128 + (((t >> 2) ^ (x >> 1)) & 1u) * 64 + (t & 3) * 16;
+                *reinterpret_cast<u32x4*>(lds_raw + at) = tin[i];
+                *reinterpret_cast<u32x4*>(lds_raw + WG_MAP + at) = tg[i];
             }
-        }
     };
-    // A wave's two channel tiles interleave: tile c of its 64 channels holds channels 2 m + c (m = MFMA row / column),
-    // so that one 32-bit LDS read gives a lane its value of both tiles (a pixel's channels 2 m and 2 m + 1).
-    auto rd32 = [&](uint32_t addr) -> uint32_t { return *reinterpret_cast<const uint32_t*>(lds_raw + addr); };
-    // eight dwords (pixels), tile c in half c of every dword -> the 8 bf16 of tile c, one v_perm per pair of pixels
-    auto frag_of = [](const uint32_t* v, int c) -> bf16x8 {
-        const uint32_t sel = c ? 0x07060302u : 0x05040100u;
-        auto pair = [sel](uint32_t first, uint32_t second) { return __builtin_amdgcn_perm(second, first, sel); };
-        const u32x4 w = {pair(v[0], v[1]), pair(v[2], v[3]), pair(v[4], v[5]), pair(v[6], v[7])};
-        return __builtin_bit_cast(bf16x8, w);
+    // This lane's address for pixels x .. x + 3 (x = its K half's first pixel, plus 4 for the second four, plus the tap column's -1, 0, 1):
+    // the group of 16 lanes reads 16 channels, four lanes a pixel.  Columns beyond the row are zeros: column 15.
+    auto lane_at = [&](int half, int shift) -> uint32_t {
+        int x = (lane >> 5) * 8 + ((lane >> 2) & 3) + shift;
+        if (x < 0 || x > 15) x = 15;
+        return uint32_t(x * 128 + ((half ^ (x >> 1)) & 1) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
     };
-    const u32x4 ones_w = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_w);
-    // tile row / first tile column of this lane's 8 pixels of image row y:
-    //   gradient map and conv1x1 input: row y + 1, column 1 + 8 hk;  conv3x3 input for kernel row kh: row y + kh, column 8 hk
-    const uint32_t g_lane = TILE_G + uint32_t(ROW_BYTES + (1 + 8 * hk) * PIX_BYTES + (wj * 64 + 2 * m) * 2);
-    const uint32_t in_lane = MODE == 2 ? uint32_t(ROW_BYTES + (1 + 8 * hk) * PIX_BYTES + (wi * 64 + 2 * m) * 2)
-                                       : uint32_t(part * ROW_BYTES + (8 * hk) * PIX_BYTES + (wi * 64 + 2 * m) * 2);
-    struct Raw { uint32_t g[8]; uint32_t in[NV]; };                    // one row's values as they come from LDS
-    struct Row { bf16x8 gf[2]; bf16x8 inf[2][NTAP]; };                 // ... and packed into operand fragments
-    // The upper lane half's last pixels do not exist (x = 14, 15) or lie beyond the tile (conv3x3 input, tile columns
-    // 16, 17).  Tile column 15 is the zero border: the gradient map's x = 14 is that column already, and the lanes
-    // whose pixel would lie beyond it read column 15 again, so every such value is a zero without any select.
-    constexpr int ILIM = MODE == 2 ? 7 : 8;                            // first index of an input value beyond column 15
-    const uint32_t g_off7 = (hk ? 6u : 7u) * PIX_BYTES;
-    const uint32_t in_offa = (hk ? uint32_t(ILIM - 1) : uint32_t(ILIM)) * PIX_BYTES;
-    const uint32_t in_offb = (hk ? uint32_t(ILIM - 1) : uint32_t(ILIM + 1)) * PIX_BYTES;
-    const uint32_t g_lane7 = g_lane + g_off7, in_lanea = in_lane + in_offa, in_laneb = in_lane + in_offb;
-    auto issue_row = [&](int y, Raw& rw) {
-        const uint32_t yo = uint32_t(y * ROW_BYTES);
-        const uint32_t gb = g_lane + yo, g7 = g_lane7 + yo, ib = in_lane + yo, ia = in_lanea + yo, ibb = in_laneb + yo;
+    uint32_t in_lane[K][2];
 #pragma unroll
-        for (int i = 0; i < 7; ++i) rw.g[i] = rd32(gb + uint32_t(i * PIX_BYTES));
-        rw.g[7] = rd32(g7);
+    for (int kw = 0; kw < K; ++kw)
 #pragma unroll
-        for (int i = 0; i < ILIM; ++i) rw.in[i] = rd32(ib + uint32_t(i * PIX_BYTES));
-        rw.in[ILIM] = rd32(ia);
-        if (ILIM + 1 < NV) rw.in[ILIM + 1 < NV ? ILIM + 1 : 0] = rd32(ibb);
+        for (int q = 0; q < 2; ++q) in_lane[kw][q] = lane_at(wi, 4 * q + kw - K / 2);
+    const uint32_t g_lane = lane_at(wj, 0) + uint32_t(WG_MAP);
+    auto frag = [](i16x4 lo, i16x4 hi) -> bf16x8 { return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)); };
+    auto read_in = [&](int y, int kw) { return frag(lds_read_pixels(in_lane[kw][0] + uint32_t(y * WG_ROW)), lds_read_pixels(in_lane[kw][1] + uint32_t(y * WG_ROW))); };
+    auto read_g = [&](int y) { return frag(lds_read_pixels(g_lane + uint32_t(y * WG_ROW)), lds_read_pixels(g_lane + uint32_t(y * WG_ROW + 4 * 128))); };
+
+    f32x16 acc[K][K];
+    float bias = 0.f;                                                 // sum of this lane's channel of G
+#pragma unroll
+    for (int kh = 0; kh < K; ++kh)
+#pragma unroll
+        for (int kw = 0; kw < K; ++kw)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[kh][kw][i] = 0.f;
+    const bool with_bias = (!CONV && un.part == 1) ? false : wi == 0 && ci_half == 0;      // uniform over the wave
+    // (every wave sums G: the fifteen additions of a row cost nothing beside its MFMAs, a second copy of the loop costs registers)
+    auto add_bias = [&](const bf16x8& v) {
+        const u32x4 w = __builtin_bit_cast(u32x4, v);
+        float s[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = __uint_as_float(w[i] << 16) + __uint_as_float(w[i] & 0xffff0000u);
+        bias += (s[0] + s[1]) + (s[2] + s[3]);
     };
-    auto pack_row = [&](const Raw& rw, Row& row) {
+    // steps (input row y, tap column kw): the fragments of step s + 2 and of gradient row y + 2 are requested ahead of its MFMAs
+    constexpr int STEPS = S * K, AHEAD = 2;
+    auto multiply = [&]() {
+        bf16x8 in[AHEAD + 1], g[4];
+        g[0] = read_g(0);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            row.gf[c] = frag_of(rw.g, c);
-#pragma unroll
-            for (int k = 0; k < NTAP; ++k) row.inf[c][k] = frag_of(rw.in + k, c);
-        }
-    };
-    const bool with_bias = part == 0 && wi == 0;                      // uniform over the wave
-    auto mfma_row = [&](const Row& rw, auto WB) {
-#pragma unroll
-        for (int k = 0; k < NTAP; ++k)
-#pragma unroll
-            for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-                for (int cj = 0; cj < 2; ++cj)
-                    acc[k][ct][cj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rw.inf[ct][k], rw.gf[cj], acc[k][ct][cj], 0, 0, 0);
-        if constexpr (decltype(WB)::value) {
-#pragma unroll
-            for (int cj = 0; cj < 2; ++cj) accb[cj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, rw.gf[cj], accb[cj], 0, 0, 0);
-        }
-    };
-    // One step of the row pipeline: the LDS reads of the row after next are issued first, then the MFMAs of row `cur`
-    // run with the packing of row `nxt` (whose reads were issued a step earlier) spread between them: a wave issues one
-    // instruction at a time, and only what it issues while an MFMA executes is free.
-    auto step = [&](int y_issue, Raw& raw_issue, const Raw& raw_pack, Row& nxt, const Row& cur, auto WB) {
-        issue_row(y_issue, raw_issue);
-        mfma_row(cur, WB);
-        pack_row(raw_pack, nxt);
-        constexpr int NMF = NTAP * 4 + (decltype(WB)::value ? 2 : 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 8 + NV, 0);                   // all reads
-        __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);                        // (their addresses)
-#pragma unroll
-        for (int i = 0; i < NMF; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, MODE == 2 ? 8 : 4, 0);
-        }
+        for (int s = 0; s < AHEAD; ++s) in[s] = read_in(s / K, s % K);
+        g[1] = read_g(1);
         __builtin_amdgcn_sched_barrier(0);
-    };
-    auto items = [&](auto WB) {
-        load(un.begin);
-        for (int idx = un.begin; idx < un.end; ++idx) {
-            __syncthreads();                                          // the previous item's fragments have been read
-            store();
-            __syncthreads();
-            if (idx + 1 < un.end) load(idx + 1);                      // arrives under this item's MFMAs
-            Raw r0, r1;
-            Row ra, rb;
-            issue_row(0, r0);
-            issue_row(1, r1);
-            pack_row(r0, ra);
-            __builtin_amdgcn_sched_barrier(0);
-            // rows y and y + 1 per trip: r1 holds row y + 1 on entry, ra row y
-#pragma unroll 1
-            for (int y = 0; y < S; y += 2) {
-                step(y + 2 < S ? y + 2 : y, r0, r1, rb, ra, WB);      // reads row y+2, MFMAs row y, packs row y+1
-                step(y + 3 < S ? y + 3 : y, r1, r0, ra, rb, WB);      // reads row y+3, MFMAs row y+1, packs row y+2
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const int y = s / K, kw = s % K;
+            if (s + AHEAD < STEPS) in[(s + AHEAD) % (AHEAD + 1)] = read_in((s + AHEAD) / K, (s + AHEAD) % K);
+            if (kw == 0 && y + 2 < S) g[(y + 2) & 3] = read_g(y + 2);
+            if (kw == 0) add_bias(g[y & 3]);
+            auto mul = [&](int kh, int row) {
+                acc[kh][kw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g[row & 3], in[s % (AHEAD + 1)], acc[kh][kw], 0, 0, 0);
+            };
+            if constexpr (K == 1) mul(0, y);
+            else {
+                mul(1, y);
+                if (y > 0) mul(2, y - 1);                             // tap row kh of output row y + 1 - kh
+                if (y + 1 < S) mul(0, y + 1);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (with_bias) items(std::true_type{});
-    else items(std::false_type{});
-    // D[ci][co] of tiles (ct, cj): this lane holds co = wj*64 + 2 m + cj and, in elements 4 b .. 4 b + 3, the rows
-    // 8 b + 4 hk + (0..3), i.e. ci = wi*64 + 2 (8 b + 4 hk + e) + ct: the two ci tiles together give 8 consecutive ci
+    const int n_items = un.end - un.begin;
+    load(0);
+#pragma unroll 1
+    for (int n = 0; n < n_items; ++n) {
+        __syncthreads();                                              // the previous item's fragments have been read
+        store();
+        __syncthreads();
+        load(min(n + 1, n_items - 1));                                // arrives under this item's MFMAs
+        multiply();
+    }
+    // D[co][ci]: lane ci = lane % 32, element i: co = 8 (i / 4) + 4 (lane / 32) + i % 4; a store writes two rows of 128 bytes
+    float* out = a.partial + size_t(unit) * WG_PARTIAL;
+    const int m = lane & 31, hk = lane >> 5;
+    float* const to = out + (size_t(co_half * 64 + wj * 32 + 4 * hk) * C + ci_half * 64 + wi * 32 + m);
 #pragma unroll
-    for (int cj = 0; cj < 2; ++cj) {
-        const int co = wj * 64 + 2 * m + cj;
+    for (int kh = 0; kh < K; ++kh)
 #pragma unroll
-        for (int k = 0; k < NTAP; ++k)
+        for (int kw = 0; kw < K; ++kw)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int ci = wi * 64 + 16 * b + 8 * hk;
-                float* dst = part_out + (size_t(k) * C + co) * C + ci;
-                *reinterpret_cast<f32x4*>(dst) = f32x4{acc[k][0][cj][4 * b], acc[k][1][cj][4 * b], acc[k][0][cj][4 * b + 1], acc[k][1][cj][4 * b + 1]};
-                *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[k][0][cj][4 * b + 2], acc[k][1][cj][4 * b + 2], acc[k][0][cj][4 * b + 3], acc[k][1][cj][4 * b + 3]};
-            }
-        if (with_bias && hk == 0) part_out[size_t(3) * C * C + co] = accb[cj][0];
+            for (int i = 0; i < 16; ++i) to[size_t(kh) * stride * WG_PARTIAL + (kw * C + 8 * (i / 4) + i % 4) * C] = acc[kh][kw][i];
+    if (with_bias) {
+        bias += __shfl_xor(bias, 32);
+        if (hk == 0) out[size_t(3) * C * C + co_half * 64 + wj * 32 + m] = bias;
     }
 }
 
-__global__ __launch_bounds__(256, 1) void k_bwd_wgrad_mfma(WgArgs a)
+// Workgroups come in sets of 32: eight chunks, whose four quadrants are taken by workgroups 8 apart, which run on one die and share the
+// maps in its L2.
+__global__ __launch_bounds__(256, 2) void k_bwd_wgrad_mfma(WgArgs a)
 {
-    const int32_t u = a.order[blockIdx.x];
-    const dynb_wg_unit un = a.units[u];
-    float* out = a.partial + size_t(u) * WG_PARTIAL;
-    if (un.mode == 0) wgrad_unit<0>(a, un, out);
-    else if (un.mode == 1) wgrad_unit<1>(a, un, out);
-    else wgrad_unit<2>(a, un, out);
+    const int set = int(blockIdx.x >> 5), x = blockIdx.x & 7, quad = (blockIdx.x >> 3) & 3, conv_sets = (a.n_chunks + 7) / 8;
+    if (set < conv_sets) {
+        if (set * 8 + x >= a.n_chunks) return;
+        const int32_t u = a.order[set * 24 + x];                      // (the parts of eight chunks follow each other in the order)
+        const dynb_wg_unit un = a.units[u];
+        wgrad_chunk<true>(a, un, u, (a.fn_first[un.type + 1] - a.fn_first[un.type] + DYNB_WG_CHUNK - 1) / DYNB_WG_CHUNK, quad);
+    } else {
+        const int j = (set - conv_sets) * 8 + x;
+        if (j >= a.n_joins) return;
+        const int32_t u = 3 * a.n_chunks + j;
+        wgrad_chunk<false>(a, a.units[u], u, 0, quad);
+    }
 }
 
 // dW / db of one (mode, function, part) = its units' partial results added in chunk order
@@ -1091,8 +1091,6 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         for (const void* f : {reinterpret_cast<const void*>(k_bwd_node_mfma<1>), reinterpret_cast<const void*>(k_bwd_node_mfma<2>),
                               reinterpret_cast<const void*>(k_bwd_node_mfma<4>), reinterpret_cast<const void*>(k_bwd_node_mfma<7>)})
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bn::LDS_BYTES), "hipFuncSetAttribute(k_bwd_node_mfma)");
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bwd_wgrad_mfma), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * mf::TILE_BYTES),
-                "hipFuncSetAttribute(k_bwd_wgrad_mfma)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
     const BmLayout L = bm_layout(p);
@@ -1129,7 +1127,6 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
 
     const char* d = static_cast<const char*>(p->dev_buf);
     const dynb_item* d_items = reinterpret_cast<const dynb_item*>(d);
-    const uint8_t* d_arity = reinterpret_cast<const uint8_t*>(d + dynb_plan_arity_offset(p));
     BmArgs a;
     a.feats = static_cast<const bf16_t*>(feats); a.out = static_cast<const bf16_t*>(out); a.slots = static_cast<const bf16_t*>(fwd_ws);
     a.pk3bT = reinterpret_cast<const bf16_t*>(ws + L.pk3bT); a.pk3aT = reinterpret_cast<const bf16_t*>(ws + L.pk3aT);
@@ -1152,15 +1149,19 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     }
     {
         WgArgs q;
-        q.items = d_items; q.arity = d_arity;
+        q.items = d_items;
         q.units = reinterpret_cast<const dynb_wg_unit*>(pd + KT.units);
         q.order = reinterpret_cast<const int32_t*>(pd + KT.order);
+        q.fn_first = reinterpret_cast<const int32_t*>(pd + KT.fn_first);
         q.fn_items = reinterpret_cast<const int32_t*>(pd + KT.fn_items);
+        q.n_chunks = 0; q.n_joins = 0;
+        for (const dynb_wg_group& wg : p->wg_groups) (wg.mode == 2 ? q.n_joins : q.n_chunks) += wg.n_units;
+        q.n_chunks /= 3;                                      // (a unit for each kernel row)
         q.feats = a.feats; q.slots = a.slots;
         q.sv_u = a.sv_u; q.sv_m = a.sv_m; q.sv_g = a.sv_g; q.sv_dm = a.sv_dm; q.sv_dc = a.sv_dc;
         q.partial = reinterpret_cast<float*>(ws + L.partial);
-        if (!p->wg_units.empty())
-            hipLaunchKernelGGL(k_bwd_wgrad_mfma, dim3(unsigned(p->wg_units.size())), dim3(256), 2 * mf::TILE_BYTES, st, q);
+        const unsigned sets = unsigned((q.n_chunks + 7) / 8 + (q.n_joins + 7) / 8);
+        if (sets > 0) hipLaunchKernelGGL(k_bwd_wgrad_mfma, dim3(sets * 32), dim3(256), 2 * WG_MAP, st, q);
         WsArgs r;
         r.groups = reinterpret_cast<const dynb_wg_group*>(pd + KT.groups);
         r.partial = q.partial;

@@ -368,9 +368,9 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
                     p->wg_groups.push_back(g);                     // a function without items has no units: its gradient is zero
                 }
             }
-        // Order in which workgroups take the units: chunks with the most items first (a short tail), and the parts of
-        // one chunk (its kernel rows / arguments read the same maps) 8 workgroups apart: consecutive workgroups go
-        // to the chip's 8 dies in turn, so those parts run on one die at the same time and share its L2.
+        // Order in which workgroups take the units: chunks with the most items first (a short tail), the 3x3s' before the 1x1s', eight chunks
+        // at a time, first the first parts of the eight, then the second ones.  (A workgroup finds a chunk's first part there, and its kernel
+        // rows' units from that.  Chunks of equal length instead of 16 and a rest: no difference.)
         struct Chunk { int32_t first_group, n_parts, chunk, work; };
         std::vector<Chunk> chunks;
         for (size_t gi = 0; gi < p->wg_groups.size();) {

@@ -21,6 +21,7 @@ import numpy as np
 import pytest
 
 from workloads import iep
+from workloads.rng import round_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -265,6 +266,36 @@ def test_bf16_single_modules_in_every_layout_of_a_node(dyn, util, oracle, nodes)
     b, _ = run_backward(dyn, util, w, dense, dyn.DYNB_PLAN_THROUGHPUT)
     for name in NAMES:
         assert (a[name] == b[name]).all(), name
+
+
+@pytest.mark.parametrize("ones,twos", [(1, 0), (1, 1), (16, 15), (17, 16), (33, 17), (150, 2)])
+def test_parameter_gradients_over_chunks_of_items(dyn, util, oracle, ones, twos):
+    """The fused shape's parameter gradients: chunks of up to 16 items of a function, whole ones, one item more, and more chunks than a
+    set of workgroups takes; a one-argument function without items.  Weights, maps and dout are positive: every unit is active on both
+    sides, and no sum cancels, so a gradient is as accurate as its terms: g, dmid and dc are each rounded to bfloat16 (2^-9), at most
+    three roundings on the way to dw1, and the stored activations agree but for a few that round to the neighbour: 3 * 2^-9 = 5.9e-3 of
+    the value, and of the maximum.  (With random signs the terms' sum and not the result's size bounds the error.)"""
+    g = np.random.default_rng(ones)
+    pos = lambda shape, mean: round_bf16((g.random(shape, dtype=np.float32) * 2 * mean).astype(np.float32))
+    C, arity = 128, np.array([0, 1, 2, 1], np.uint8)
+    progs = [np.array([1, 0], np.int32)] * ones + [np.array([2, 0, 0], np.int32)] * twos
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    w = iep.IepWorkload("chunks", "bf16", arity, np.concatenate(progs), off, C, 14, 14, pos((len(progs), 14, 14, C), 0.5),
+                        pos((4, C, 2 * C), 0.5 / (2 * C)), pos((4, C), 0.05), pos((4, C, 3, 3, C), 0.3 / (9 * C)), pos((4, C), 0.05),
+                        pos((4, C, 3, 3, C), 0.3 / (9 * C)), pos((4, C), 0.05))
+    dout = g.random(w.feats.shape, dtype=np.float32)
+    keep = np.arange(len(progs))
+    if ones > 40:                                             # dout is zero but for the first and the last chunks' items: the oracle takes those
+        dout[10:ones - 10] = 0
+        keep = np.r_[0:10, ones - 10:len(progs)]
+    ref = oracle.iep_backward_workload(w.subset(keep), dout[keep], round_bf16=True)
+    got, _ = run_backward(dyn, util, w, dout)
+    for name in NAMES[1:]:
+        assert maxnorm(got[name], getattr(ref, name)) < 6e-3, (name, maxnorm(got[name], getattr(ref, name)))
+        assert not got[name][3].any(), name
+    again, _ = run_backward(dyn, util, w, dout)
+    for name in NAMES:
+        assert (again[name] == got[name]).all(), name
 
 
 def _sampled(w, seed):
