@@ -419,7 +419,9 @@ static_assert(MASK_BYTES % 256 == 0 && LDS_BYTES <= 160 * 1024, "LDS budget of o
 }  // namespace bn
 
 // PARTS workgroups share a node (PartShape): narrow launch groups took 37 us with one.
-template <int PARTS>
+// SPLIT: workgroups that share a part of a one-argument function's node, each with 4 / SPLIT channel tiles of du (parts_for); a two-argument one's
+// join needs all channels of dc, and the first of them does it alone.
+template <int PARTS, int SPLIT = 1>
 __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 {
     using namespace mf;
@@ -429,7 +431,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int per_xcd = gridDim.x >> 3;
     const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    const int node = logical / PARTS, part = logical % PARTS;
+    const int node = logical / (PARTS * SPLIT), part = logical / SPLIT % PARTS, share = logical % SPLIT;
     if (node >= a.count) return;
     // image rows: results [orow0, orow1), windows of the two convs from row_a and row_b, g from urow0
     const int orow0 = part * Shape::ROWS, orow1 = min(orow0 + Shape::ROWS, S);
@@ -445,11 +447,16 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 #endif
     const dynb_item it = a.items[node];
     const bool binary = it.src1 != DYNB_NO_ARG;                        // uniform over the workgroup
+    if (SPLIT > 1 && binary && share > 0) return;
+    const bool shared = SPLIT > 1 && !binary;
+    const int tile_b = shared ? share * (4 / SPLIT) + wave % (4 / SPLIT) : wave;      // channel tile of the second conv
+    const bool second = !shared || wave < 4 / SPLIT;                   // this wave has one
+    auto mine = [&](int c) { return !shared || (c & 15) / (16 / SPLIT) == share; };   // piece c of a map: this workgroup's channels
     const size_t item_off = size_t(a.first_item + node) * (P * C);
 
     const size_t frag3 = (size_t(it.type) * 4 + wave) * 72, frag1 = (size_t(it.type) * 4 + wave) * 16;
     const bf16_t* wrow_bT = a.pk3bT + frag3 * FRAG + lane * 8;
-    const bf16_t* wrow_aT = a.pk3aT + frag3 * FRAG + lane * 8;
+    const bf16_t* wrow_aT = a.pk3aT + (size_t(it.type) * 4 + tile_b) * 72 * FRAG + lane * 8;
     bf16x8 ring[RW];
 
     auto centre_addr = [&](int c) -> uint32_t {                       // 16-byte piece c of a map -> its place in the halo tile
@@ -496,7 +503,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
                 pk.z = pack_bf16x2(yb & 16u ? ghi[i].x : 0.f, yb & 32u ? ghi[i].y : 0.f);
                 pk.w = pack_bf16x2(yb & 64u ? ghi[i].z : 0.f, yb & 128u ? ghi[i].w : 0.f);
                 *reinterpret_cast<u32x4*>(lds_raw + centre_addr(c)) = pk;
-                if (PARTS == 1 || (c >= own_lo && c < own_hi)) sg4[c] = pk;
+                if (PARTS == 1 || (c >= own_lo && c < own_hi && mine(c))) sg4[c] = pk;
                 lds_raw[bn::MASK_OFF + c] = static_cast<unsigned char>(yb);
             }
         }
@@ -508,7 +515,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     const int px = r & 15, py = r >> 4;
     const bool real = px < S;                                         // columns 14, 15 are padding
     auto pixel = [&](int row, int t) { return (row + 2 * t + py) * S + px; };
-    const int chan = n0 + 16 * h;                                     // this lane's 16 accumulator elements: channels chan .. chan+15
+    const int chan = n0 + 16 * h, chan_b = tile_b * 32 + 16 * h;      // this lane's 16 accumulator elements: channels chan .. chan+15; of the second conv
     f32x16 acc_a[MTA];
     constexpr bool SAME = MTA == MTB;                                 // one window: the second conv takes the first's registers
     f32x16 acc_own[SAME ? 1 : MTB];
@@ -540,22 +547,22 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int c = lo + tid + i * NTHR;
-                if (c < hi) ahead[i] = pre(c);
+                if (c < hi && mine(c)) ahead[i] = pre(c);
             }
             __syncthreads();                                          // the area (and, the first time, the tile) is free
 #pragma unroll
             for (int t = 0; t < MTB; ++t)
-                if (t >= t0 && t < t1 && real) {
+                if (t >= t0 && t < t1 && real && second) {
 #pragma unroll
                     for (int b = 0; b < 4; ++b)
-                        *reinterpret_cast<f32x4*>(lds_raw + bn::STAGE_OFF + uint32_t((pixel(row_b, t) - p0) * bn::STAGE_PITCH + (chan + 4 * b) * 4)) =
+                        *reinterpret_cast<f32x4*>(lds_raw + bn::STAGE_OFF + uint32_t((pixel(row_b, t) - p0) * bn::STAGE_PITCH + (chan_b + 4 * b) * 4)) =
                             f32x4{acc[t][4 * b], acc[t][4 * b + 1], acc[t][4 * b + 2], acc[t][4 * b + 3]};
                 }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int c = lo + tid + i * NTHR;
-                if (c < hi) {
+                if (c < hi && mine(c)) {
                     const uint32_t at = bn::STAGE_OFF + uint32_t(((c >> 4) - p0) * bn::STAGE_PITCH + (c & 15) * 32);
                     fn(c, *reinterpret_cast<const f32x4*>(lds_raw + at), *reinterpret_cast<const f32x4*>(lds_raw + at + 16), ahead[i]);
                 }
@@ -607,7 +614,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 #pragma unroll
         for (int i = 0; i < (Shape::ROWS * S * 16 + NTHR - 1) / NTHR; ++i) {
             const int c = own_lo + tid + i * NTHR;
-            if (c < own_hi) sdm4[c] = *reinterpret_cast<const u32x4*>(lds_raw + centre_addr(c));
+            if (c < own_hi && mine(c)) sdm4[c] = *reinterpret_cast<const u32x4*>(lds_raw + centre_addr(c));
         }
     }
 
@@ -616,7 +623,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     // the residual's and would vanish below the bfloat16 quantum of the latter at every level.
     zero(acc);
     NCLK(3);
-    kloop3<MTB, RW, XB, false>(acc, x_b, ring, wrow_aT, wrow_aT);
+    if (second) kloop3<MTB, RW, XB, false>(acc, x_b, ring, wrow_aT, wrow_aT);
     NCLK(4);
     auto residual = [&](int c, f32x4& lo, f32x4& hi, const f32x4& g0, const f32x4& g1) {
         const uint32_t yb = lds_raw[bn::MASK_OFF + c];
@@ -1089,7 +1096,8 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
     if (!(attr_set.load() >> (dev & 63) & 1)) {
         for (const void* f : {reinterpret_cast<const void*>(k_bwd_node_mfma<1>), reinterpret_cast<const void*>(k_bwd_node_mfma<2>),
-                              reinterpret_cast<const void*>(k_bwd_node_mfma<4>), reinterpret_cast<const void*>(k_bwd_node_mfma<7>)})
+                              reinterpret_cast<const void*>(k_bwd_node_mfma<4>), reinterpret_cast<const void*>(k_bwd_node_mfma<7>),
+                              reinterpret_cast<const void*>(k_bwd_node_mfma<7, 2>), reinterpret_cast<const void*>(k_bwd_node_mfma<7, 4>)})
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bn::LDS_BYTES), "hipFuncSetAttribute(k_bwd_node_mfma)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
@@ -1144,7 +1152,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         a.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + l.start;
         const int parts = p->throughput ? 1 : parts_for(l.count);
         const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
-        auto* kernel = parts == 7 ? k_bwd_node_mfma<7> : parts == 4 ? k_bwd_node_mfma<4> : parts == 2 ? k_bwd_node_mfma<2> : k_bwd_node_mfma<1>;
+        auto* kernel = parts == 28 ? k_bwd_node_mfma<7, 4> : parts == 14 ? k_bwd_node_mfma<7, 2> : parts == 7 ? k_bwd_node_mfma<7> : parts == 4 ? k_bwd_node_mfma<4> : parts == 2 ? k_bwd_node_mfma<2> : k_bwd_node_mfma<1>;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), bn::LDS_BYTES, st, a);
     }
     {

@@ -110,8 +110,9 @@ __global__ void k_pack_weights(const u32x4* __restrict__ src, u32x4* __restrict_
 // up to one node per CU, with twice the weight ring in 346 registers, was 3 % slower: the accumulators then live in
 // the upper half of the register file, and every other use of them is a copy.)
 // One workgroup's share of a launch group: position `logical` (a node, or a part of one) of the items a.items[0 .. a.count).
-// KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m.
-template <int PARTS, bool KEEP = false>
+// KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m.  SPLIT: workgroups that share a part, each with
+// 4 / SPLIT channel tiles of the second conv (parts_for).
+template <int PARTS, bool KEEP = false, int SPLIT = 1>
 __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 {
     using namespace mf;
@@ -123,7 +124,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     constexpr int RW = Shape::RW;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
-    const int node = logical / PARTS, part = logical % PARTS;
+    const int node = logical / (PARTS * SPLIT), part = logical / SPLIT % PARTS, share = logical % SPLIT;
     if (node >= a.count) return;
     // image rows: output [orow0, orow1), windows of the convs [row_a, row_a + 2 MTA) and [row_b, row_b + 2 MTB), u
     // [urow0, urow0 + UROWS), every one of them moved inside the map
@@ -141,7 +142,8 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
 
     // packed weights of this wave's channel tile
     const bf16_t* wrow_a = a.w3a + (size_t(it.type) * 4 + wave) * 72 * FRAG + lane * 8;
-    const bf16_t* wrow_b = a.w3b + (size_t(it.type) * 4 + wave) * 72 * FRAG + lane * 8;
+    const int tile_b = SPLIT == 1 ? wave : share * (4 / SPLIT) + wave % (4 / SPLIT);  // the second conv's; waves beyond 4 / SPLIT have none
+    const bf16_t* wrow_b = a.w3b + (size_t(it.type) * 4 + tile_b) * 72 * FRAG + lane * 8;
     bf16x8 ring[RW];
 
     // ---- gather: zero border once, then the argument map into the centre of the halo tile;
@@ -169,13 +171,13 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
             }
         }
     };
-    // the centre of the halo tile -> a map, this workgroup's output rows, in coalesced 16-byte pieces
+    // the centre of the halo tile -> a map, this workgroup's output rows (and share of the channels), in coalesced 16-byte pieces
     auto copy_out = [&](bf16_t* dst) {
         constexpr int OUTPIECES = Shape::ROWS * S * 16;
 #pragma unroll
         for (int i = 0; i < (OUTPIECES + NTHR - 1) / NTHR; ++i) {
             const int c = orow0 * S * 16 + tid + i * NTHR;
-            if (c < orow1 * S * 16) {
+            if (c < orow1 * S * 16 && (SPLIT == 1 || (c & 15) / (16 / SPLIT) == share)) {
                 const int p = c >> 4, part = c & 15;
                 reinterpret_cast<u32x4*>(dst)[c] = *reinterpret_cast<const u32x4*>(
                     lds_raw + uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16));
@@ -206,10 +208,10 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     const uint32_t x_a = pair_lane_addr(lane) + uint32_t(row_a * ROW_BYTES), x_b = pair_lane_addr(lane) + uint32_t(row_b * ROW_BYTES);
     const bool real = (r & 15) < S;
     // its 16 accumulator elements are channels chan .. chan + 15 (the packed weights carry the matching row permutation)
-    const int chan = n0 + 16 * h;
+    const int chan = n0 + 16 * h, chan_b = tile_b * 32 + 16 * h;             // (of the first and of the second conv)
 
     auto bias4 = [&](int which, int b) {      // channels chan + 4 b .. + 3 of b3a (0), b3b (1), b1 (2)
-        return *reinterpret_cast<const f32x4*>(lds_raw + BIAS_OFF + uint32_t((which * C + chan + b * 4) * 4));
+        return *reinterpret_cast<const f32x4*>(lds_raw + BIAS_OFF + uint32_t((which * C + (which == 1 ? chan_b : chan) + b * 4) * 4));
     };
     auto init_bias = [&](auto& acc, int which) {
 #pragma unroll
@@ -224,6 +226,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     };
     // byte address of this lane's centre pixel of tile t of a window, its first channel
     auto centre = [&](uint32_t x, int t) -> uint32_t { return x - uint32_t(h * 128) + uint32_t(CENTER + chan * 2 + 2 * t * ROW_BYTES); };
+    auto centre_b = [&](int t) -> uint32_t { return x_b - uint32_t(h * 128) + uint32_t(CENTER + chan_b * 2 + 2 * t * ROW_BYTES); };
     // ReLU(acc[8q .. 8q+7]) as 8 packed bf16 (q = 0, 1)
     auto packed = [&](const f32x16& acc, int q) -> u32x4 {
         u32x4 pk;
@@ -289,28 +292,36 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     init_bias(acc_a, 0);
     kloop3<MTA, RW, Shape::XA>(acc_a, x_a, ring, wrow_a, wrow_b);       // leaves the ring filled for the second conv
     PHASE(4);
-    __syncthreads();
-    PHASE(5);
     // (one window for both convs: the second accumulates in the registers of the first)
     constexpr bool SAME = MTA == MTB;
+    static_assert(!SAME || SPLIT == 1, "a part that is shared has its own window for the second conv");
     f32x16 acc_own[SAME ? 1 : MTB];
     auto& acc_b = [&]() -> auto& { if constexpr (SAME) return acc_a; else return acc_own; }();
+    const bool second = SPLIT == 1 || wave < 4 / SPLIT;                // uniform over the wave
+    auto old = [&](int t, int q) { return *reinterpret_cast<const u32x4*>(lds_raw + centre_b(t) + uint32_t(q * 16)); };
+    auto residual = [&](int t, int q, const u32x4& res) {
+        const f32x4 blo = bias4(1, 2 * q), bhi = bias4(1, 2 * q + 1);
+        f32x16& acc = acc_b[t];
+        acc[8 * q + 0] = __uint_as_float(res.x << 16) + blo.x;
+        acc[8 * q + 1] = __uint_as_float(res.x & 0xffff0000u) + blo.y;
+        acc[8 * q + 2] = __uint_as_float(res.y << 16) + blo.z;
+        acc[8 * q + 3] = __uint_as_float(res.y & 0xffff0000u) + blo.w;
+        acc[8 * q + 4] = __uint_as_float(res.z << 16) + bhi.x;
+        acc[8 * q + 5] = __uint_as_float(res.z & 0xffff0000u) + bhi.y;
+        acc[8 * q + 6] = __uint_as_float(res.w << 16) + bhi.z;
+        acc[8 * q + 7] = __uint_as_float(res.w & 0xffff0000u) + bhi.w;
+    };
+    auto residuals = [&]() {
+#pragma unroll
+        for (int t = 0; t < MTB; ++t) { residual(t, 0, old(t, 0)); residual(t, 1, old(t, 1)); }
+    };
+    // (of a shared part, a wave's channels of the second conv are another wave's of the first: read before anyone replaces them)
+    if (SPLIT > 1 && second && real) residuals();
+    __syncthreads();
+    PHASE(5);
     if (real) {
         // ReLU(acc_a) into the tile, old centre values + bias into acc_b.  A wave reads and writes its own channels only, and
         // its reads come first: where the windows are the same, piece by piece, else all of them
-        auto old = [&](int t, int q) { return *reinterpret_cast<const u32x4*>(lds_raw + centre(x_b, t) + uint32_t(q * 16)); };
-        auto residual = [&](int t, int q, const u32x4& res) {
-            const f32x4 blo = bias4(1, 2 * q), bhi = bias4(1, 2 * q + 1);
-            f32x16& acc = acc_b[t];
-            acc[8 * q + 0] = __uint_as_float(res.x << 16) + blo.x;
-            acc[8 * q + 1] = __uint_as_float(res.x & 0xffff0000u) + blo.y;
-            acc[8 * q + 2] = __uint_as_float(res.y << 16) + blo.z;
-            acc[8 * q + 3] = __uint_as_float(res.y & 0xffff0000u) + blo.w;
-            acc[8 * q + 4] = __uint_as_float(res.z << 16) + bhi.x;
-            acc[8 * q + 5] = __uint_as_float(res.z & 0xffff0000u) + bhi.y;
-            acc[8 * q + 6] = __uint_as_float(res.w << 16) + bhi.z;
-            acc[8 * q + 7] = __uint_as_float(res.w & 0xffff0000u) + bhi.w;
-        };
         auto replace = [&](int t, int q) { *reinterpret_cast<u32x4*>(lds_raw + centre(x_a, t) + uint32_t(q * 16)) = packed(acc_a[t], q); };
         if constexpr (SAME) {
 #pragma unroll
@@ -322,8 +333,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
                     residual(t, q, res);
                 }
         } else {
-#pragma unroll
-            for (int t = 0; t < MTB; ++t) { residual(t, 0, old(t, 0)); residual(t, 1, old(t, 1)); }
+            if constexpr (SPLIT == 1) residuals();
 #pragma unroll
             for (int t = 0; t < MTA; ++t) { replace(t, 0); replace(t, 1); }
         }
@@ -337,28 +347,28 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     // ---- second conv3x3 on top of (residual + bias), ReLU, scatter.  The result leaves through the tile: in the
     // accumulators a lane holds 32 bytes of a pixel, and stores in which every lane touches a line of its own take 4.4k
     // clocks of a whole-node workgroup's 53k, the way through LDS with coalesced stores 3.6k.
-    kloop3<MTB, RW, Shape::XB, false>(acc_b, x_b, ring, wrow_b, wrow_b);
+    if (second) kloop3<MTB, RW, Shape::XB, false>(acc_b, x_b, ring, wrow_b, wrow_b);
     PHASE(8);
     __syncthreads();
-    if (real) {
+    if (second && real) {
 #pragma unroll
         for (int t = 0; t < MTB; ++t)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(lds_raw + centre(x_b, t) + uint32_t(q * 16)) = packed(acc_b[t], q);
+            for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(lds_raw + centre_b(t) + uint32_t(q * 16)) = packed(acc_b[t], q);
     }
     __syncthreads();
     copy_out(it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C));
     PHASE(9);
 }
 
-template <int PARTS, bool KEEP = false>
+template <int PARTS, bool KEEP = false, int SPLIT = 1>
 __global__ __launch_bounds__(256, 2) void k_module_mfma(MfArgs a)
 {
     // Workgroup -> position in the launch group.  Consecutive workgroup ids land on different
     // XCDs; give every XCD one contiguous run of items (items are sorted by function id) so that
     // a function's weights stay in as few L2s as possible.
     const int per_xcd = gridDim.x >> 3;
-    module_body<PARTS, KEEP>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    module_body<PARTS, KEEP, SPLIT>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
 }
 
 // ---- one dependency-driven launch per batch ---------------------------------------------------------
@@ -614,7 +624,9 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
                               reinterpret_cast<const void*>(k_module_mfma<1, false>), reinterpret_cast<const void*>(k_module_mfma<1, true>),
                               reinterpret_cast<const void*>(k_module_mfma<2, false>), reinterpret_cast<const void*>(k_module_mfma<2, true>),
                               reinterpret_cast<const void*>(k_module_mfma<4, false>), reinterpret_cast<const void*>(k_module_mfma<4, true>),
-                              reinterpret_cast<const void*>(k_module_mfma<7, false>), reinterpret_cast<const void*>(k_module_mfma<7, true>)})
+                              reinterpret_cast<const void*>(k_module_mfma<7, false>), reinterpret_cast<const void*>(k_module_mfma<7, true>),
+                              reinterpret_cast<const void*>(k_module_mfma<7, false, 2>), reinterpret_cast<const void*>(k_module_mfma<7, true, 2>),
+                              reinterpret_cast<const void*>(k_module_mfma<7, false, 4>), reinterpret_cast<const void*>(k_module_mfma<7, true, 4>)})
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, mf::LDS_BYTES), "hipFuncSetAttribute(module kernels)");
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
@@ -679,7 +691,9 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         // flight (their narrow groups share the chip), one node per workgroup
         const int parts = p->throughput ? 1 : parts_for(l.count);
         const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
-        auto* kernel = parts == 7   ? (p->keep ? k_module_mfma<7, true> : k_module_mfma<7>)
+        auto* kernel = parts == 28  ? (p->keep ? k_module_mfma<7, true, 4> : k_module_mfma<7, false, 4>)
+                       : parts == 14 ? (p->keep ? k_module_mfma<7, true, 2> : k_module_mfma<7, false, 2>)
+                       : parts == 7 ? (p->keep ? k_module_mfma<7, true> : k_module_mfma<7>)
                        : parts == 4 ? (p->keep ? k_module_mfma<4, true> : k_module_mfma<4>)
                        : parts == 2 ? (p->keep ? k_module_mfma<2, true> : k_module_mfma<2>)
                                     : (p->keep ? k_module_mfma<1, true> : k_module_mfma<1>);

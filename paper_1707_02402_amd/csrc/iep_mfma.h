@@ -217,7 +217,11 @@ template <> struct PartShape<2> { static constexpr int ROWS = 7, MTA = 4, MTB = 
 template <> struct PartShape<4> { static constexpr int ROWS = 4, MTA = 3, MTB = 2, UROWS = 8, RW = 24, XA = 8, XB = 8; };
 template <> struct PartShape<7> { static constexpr int ROWS = 2, MTA = 2, MTB = 1, UROWS = 6, RW = 24, XA = 8, XB = 8; };
 
-// parts per node of a launch group of `count` nodes: as many as still fit the chip's 256 CUs in one round
-inline int parts_for(int count) { return count > 128 ? 1 : count > 64 ? 2 : count > 36 ? 4 : 7; }
+// Workgroups per node of a launch group of `count` nodes: as many as still fit the chip's 256 CUs in one round.  14 and 28: 7 parts whose
+// second conv is shared by 2 or 4 workgroups, 64 or 32 output channels each (SPLIT): what a part waits for are weights, 295 KB a conv at some
+// 30 bytes a clock, and of the second conv each then reads a half or a quarter.  (The first conv's channels are all needed by every
+// one.)  us a program's pass, 7 parts / shared: one program 204 / 182, three 258 / 230; 5 training programs 765 / 725.  (Requesting the first conv's weights
+// into the die's L2 while the argument is on its way, a share per workgroup: 3-5 % slower.)
+inline int parts_for(int count) { return count > 128 ? 1 : count > 64 ? 2 : count > 36 ? 4 : count > 18 ? 7 : count > 9 ? 14 : 28; }
 
 }  // namespace

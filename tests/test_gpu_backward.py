@@ -268,6 +268,12 @@ def test_bf16_single_modules_in_every_layout_of_a_node(dyn, util, oracle, nodes)
         assert (a[name] == b[name]).all(), name
 
 
+@pytest.mark.parametrize("nodes", [4, 9, 10, 18, 19])
+def test_bf16_single_modules_in_the_layouts_whose_second_convolution_is_shared(dyn, util, oracle, nodes):
+    """Up to 9 and up to 18 nodes: four and two workgroups take the channels of du of a one-argument function's part."""
+    test_bf16_single_modules_in_every_layout_of_a_node(dyn, util, oracle, nodes)
+
+
 @pytest.mark.parametrize("ones,twos", [(1, 0), (1, 1), (16, 15), (17, 16), (33, 17), (150, 2)])
 def test_parameter_gradients_over_chunks_of_items(dyn, util, oracle, ones, twos):
     """The fused shape's parameter gradients: chunks of up to 16 items of a function, whole ones, one item more, and more chunks than a

@@ -491,6 +491,13 @@ def test_layouts_of_a_node_at_the_widths_where_they_change(dyn, util, oracle, no
         assert util.normwise(got[i], ref[j]) < TOL["bf16"], i
 
 
+@pytest.mark.parametrize("nodes", [4, 9, 10, 18, 19])
+def test_layouts_whose_second_convolution_is_shared(dyn, util, oracle, nodes):
+    """Up to 9 and up to 18 nodes: four and two workgroups take the output channels of a part's second convolution."""
+    test_layouts_of_a_node_at_the_widths_where_they_change(dyn, util, oracle, nodes)
+
+
+
 @pytest.mark.parametrize("dtype,C,side", [("f32", 160, 14), ("f32", 128, 28), ("bf16", 320, 14), ("f32", 256, 14)])
 def test_the_width_of_a_launch_group_does_not_change_the_bits(dyn, util, oracle, dtype, C, side):
     """Shapes whose summed channels do not fit LDS at once beside the largest workgroup tile but do beside smaller ones: groups of
