@@ -522,6 +522,7 @@ extern "C" int dynbatch_plan_upload(dynb_plan* p, void* dev_buf, size_t bytes, v
         put(t.root_item, p->root_item.data(), p->root_item.size() * 4);
         put(t.fn_first, p->fn_first.data(), p->fn_first.size() * 4);
         put(t.fn_items, p->fn_items.data(), p->fn_items.size() * 4);
+        put(t.fn_order, p->fn_order.data(), p->fn_order.size() * 4);
         put(t.units, p->wg_units.data(), p->wg_units.size() * sizeof(dynb_wg_unit));
         put(t.groups, p->wg_groups.data(), p->wg_groups.size() * sizeof(dynb_wg_group));
         put(t.order, p->wg_order.data(), p->wg_order.size() * 4);
@@ -687,7 +688,7 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         a.items = reinterpret_cast<const dynb_item*>(d) + l.start;
         a.first_item = l.start;
         a.count = l.count;
-        // as many parts per node as still fit the chip's 256 CUs in one round; beyond that, and whenever several batches are in
+        // as many workgroups per node as still fit the chip's 256 CUs in one round; beyond that, and whenever several batches are in
         // flight (their narrow groups share the chip), one node per workgroup
         const int parts = p->throughput ? 1 : parts_for(l.count);
         const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);

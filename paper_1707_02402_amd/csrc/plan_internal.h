@@ -63,6 +63,7 @@ struct dynb_plan {
     std::vector<int32_t> root_item;      // [B] item that evaluates the example's root, -1 if the root is a SCENE leaf
     std::vector<int32_t> fn_first;       // [n_types+1] the items of function t are fn_items[fn_first[t] .. fn_first[t+1])
     std::vector<int32_t> fn_items;       // item indices grouped by function, ascending inside a function
+    std::vector<int32_t> fn_order;       // [n_types] functions by their number of items, most first
     // Work list of the parameter-gradient kernel: a function's items are cut into chunks of at most DYNB_WG_CHUNK so that
     // the units fill the chip evenly; a unit sums one chunk for one (convolution, kernel row or argument).
     std::vector<dynb_wg_unit> wg_units;  // grouped: the chunks of one (mode, function, part) are consecutive
@@ -81,7 +82,7 @@ inline size_t dynb_plan_leaf_bytes(const dynb_plan* p) { return dynb_align256(p-
 inline size_t dynb_plan_arity_offset(const dynb_plan* p) { return dynb_plan_items_bytes(p) + dynb_plan_leaf_bytes(p); }
 inline size_t dynb_plan_arity_bytes(const dynb_plan* p) { return dynb_align256(p->arity.size()); }
 inline size_t dynb_plan_ticket_bytes(const dynb_plan* p) { return dynb_align256(p->tickets.size() * sizeof(int32_t)); }
-struct dynb_keep_tables { size_t gdst0, gdst1, leaf_first, root_item, fn_first, fn_items, units, groups, order, u_at, end; };   // byte offsets
+struct dynb_keep_tables { size_t gdst0, gdst1, leaf_first, root_item, fn_first, fn_items, fn_order, units, groups, order, u_at, end; };   // byte offsets
 inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
 {
     dynb_keep_tables t;
@@ -93,6 +94,7 @@ inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
     t.root_item = take(p->root_item.size() * 4);
     t.fn_first = take(p->fn_first.size() * 4);
     t.fn_items = take(p->fn_items.size() * 4);
+    t.fn_order = take(p->fn_order.size() * 4);
     t.units = take(p->wg_units.size() * sizeof(dynb_wg_unit));
     t.groups = take(p->wg_groups.size() * sizeof(dynb_wg_group));
     t.order = take(p->wg_order.size() * 4);

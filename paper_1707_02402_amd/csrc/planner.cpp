@@ -341,6 +341,10 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
         p->fn_items.resize(p->items.size());
         std::vector<int32_t> at(p->fn_first.begin(), p->fn_first.end() - 1);
         for (size_t i = 0; i < p->items.size(); ++i) p->fn_items[at[p->items[i].type]++] = int32_t(i);
+        p->fn_order.resize(p->n_types);
+        for (int32_t t = 0; t < p->n_types; ++t) p->fn_order[t] = t;
+        std::stable_sort(p->fn_order.begin(), p->fn_order.end(),
+                         [&](int32_t a, int32_t b) { return p->fn_first[a + 1] - p->fn_first[a] > p->fn_first[b + 1] - p->fn_first[b]; });
         // room for u of two-argument functions: every group from its first to its last (they are sorted by function)
         p->u_at.assign(p->items.size(), 0);
         for (dynb_launch& l : p->launches) {
