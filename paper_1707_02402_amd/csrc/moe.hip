@@ -100,6 +100,15 @@ __global__ __launch_bounds__(256) void k_gate(const bf16_t* __restrict__ x, cons
     for (int i = 0; i < 16; ++i) { ag[i] = 0.f; an[i] = 0.f; }
     const int nchunk = (d + GKC - 1) / GKC;
     fetch(0);
+    // lane holds expert e0 + eh*32 + q, tokens t0 + th*32 + 8*(i/4) + 4*hk + i%4 in element i.  Its noise values are requested here: behind the
+    // sums, each between the branches around its store, they were sixteen trips to memory in a row (15943 tokens, 359 experts: 21.4 -> 17.9 us).
+    const int e = e0 + eh * 32 + q;
+    auto token = [&](int i) { return t0 + th * 32 + 8 * (i / 4) + 4 * hk + (i % 4); };
+    float nz[16];
+    if (noise) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) nz[i] = noise[size_t(min(token(i), T - 1)) * E + min(e, E - 1)];
+    }
     for (int kc = 0; kc < nchunk; ++kc) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(Ws + (srow + i * 32) * GLDP + part * 8) = wreg[i];
@@ -119,20 +128,12 @@ __global__ __launch_bounds__(256) void k_gate(const bf16_t* __restrict__ x, cons
         }
         __syncthreads();
     }
-    // lane holds expert e0 + eh*32 + q, tokens t0 + th*32 + 8*(i/4) + 4*hk + i%4 in element i
-    const int e = e0 + eh * 32 + q;
     if (e >= E) return;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const int t = t0 + th * 32 + 8 * (i / 4) + 4 * hk + (i % 4);
-        if (t >= T) continue;
         float v = ag[i];
-        if (noise) {
-            const float z = an[i];
-            const float sp = softplus_f(z);
-            v += noise[size_t(t) * E + e] * sp;
-        }
-        logits[size_t(t) * E + e] = v;
+        if (noise) v += nz[i] * softplus_f(an[i]);
+        if (token(i) < T) logits[size_t(token(i)) * E + e] = v;
     }
 }
 
@@ -1244,9 +1245,14 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     const bool timed = dynb::timing_on();
     if (timed) dynb::timing_begin(st);
     // m1 gate
-    // whole tiles of 256 tokens go to k_gate_big where the expert and model widths allow it, the tokens behind the
-    // last whole tile (and every other shape) to k_gate
-    const int T_big = (E % GB_EXP == 0 && d % GKC == 0 && d >= 4 * GKC && size_t(GB_TOK) * size_t(std::max(E, d)) < (size_t(1) << 30))
+    // whole tiles of 256 tokens go to k_gate_big where the expert and model widths allow it and there are enough tiles (a workgroup of
+    // it has a CU for itself, and takes as long however few there are), the tokens behind the last whole tile (and every other shape)
+    // to k_gate.  us, k_gate_big / k_gate by tiles and d; noisy: 32 x 512 22 / 13, 64 x 1024 31 / 22, 128 x 256 18.8 / 16.3, 128 x 512 23 / 22,
+    // 128 x 1024 32.5 / 33.7, 256 x 1024 43 / 62; without noise: 32 x 512 12.4 / 11.3, 64 x 512 13.2 / 12.8, 64 x 1024 18.4 / 18.5, 96 x 512
+    // 14.0 / 15.4, 128 x 256 12.1 / 13.3, 128 x 1024 20 / 27; 500 tokens, d 1024, 256 experts (2 tiles and a rest; k_gate_small): 45 / 11.
+    const size_t big_tiles = size_t(T / GB_TOK) * size_t(E / GB_EXP);
+    const bool many_tiles = noise ? big_tiles * (size_t(d) + 5120) >= 128 * 6144 : big_tiles * (size_t(d) + 1280) >= 64 * 2304;
+    const int T_big = (many_tiles && E % GB_EXP == 0 && d % GKC == 0 && d >= 4 * GKC && size_t(GB_TOK) * size_t(std::max(E, d)) < (size_t(1) << 30))
                           ? T / GB_TOK * GB_TOK : 0;
     if (T_big > 0) {
         static std::atomic<uint64_t> attr_set{0};             // one bit per device: LDS beyond 64 KB
