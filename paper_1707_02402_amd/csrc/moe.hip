@@ -612,13 +612,12 @@ __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restr
 
 __global__ __launch_bounds__(SORT_BLOCK) void k_place(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank,
                                                       const int32_t* __restrict__ blockoff, const int32_t* __restrict__ offsets,
-                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv, int A, int per_block,
-                                                      int expert_stride, int block_stride)
+                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv, int A, int nblk)
 {
     const int a = blockIdx.x * SORT_BLOCK + threadIdx.x;
     if (a >= A) return;
     const int e = idx[a];
-    const int pos = offsets[e] + blockoff[size_t(e) * expert_stride + size_t(a / per_block) * block_stride] + lrank[a];
+    const int pos = offsets[e] + blockoff[size_t(e) * nblk + blockIdx.x] + lrank[a];
     perm[pos] = a;
     inv[a] = pos;
 }
@@ -709,12 +708,12 @@ __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict_
     }
 }
 
-// The same for more uses, in three launches: blocks of 1024 uses are ranked with the experts' counts in LDS and leave all of their
-// counts, zeros included (nothing has to be cleared), as blockcnt[block][expert]; one workgroup turns them into
-// places, an expert per thread.  For up to SMALL_EXPERTS experts, MID_BLOCKS blocks and MID_COUNTS counts, beyond which that
-// workgroup's walk over the counts takes longer than the launches it saves; us, five launches / three: 8 blocks x 256 experts 23 / 14.5,
-// 64 x 1024 24 / 20.5, 40 x 2048 25.4 / 23.4, 20 x 4096 27.9 / 27.4, 64 x 2048 26.4 / 27.4, 40 x 3000 27.3 / 30.2, 64 x 4096 30.6 / 41.
-constexpr int MID_BLOCKS = 64, MID_COUNTS = 82 * 1024;
+// The same for more uses, in two launches: blocks of 1024 uses are ranked with the experts' counts in LDS and leave all of their
+// counts, zeros included (nothing has to be cleared), as blockcnt[block][expert]; then every block adds up all blocks' counts for
+// itself, an expert per thread, and places its uses.  For up to SMALL_EXPERTS experts and MID_BLOCKS blocks; us, the five launches below
+// / three, with one workgroup that turned the counts into places for a third launch / these two, by blocks x experts: 2 x 64 20.6 / 14.0 / 12.5,
+// 8 x 256 21.2 / 14.6 / 13.1, 64 x 1024 23.8 / 20.1 / 16.4, 40 x 2048 24.6 / 23.2 / 18.8, 20 x 4096 26.9 / - / 22.8, 64 x 4096 30.6 / - / 29.4.
+constexpr int MID_BLOCKS = 64;
 __global__ __launch_bounds__(1024) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
 {
     __shared__ int32_t count[SMALL_EXPERTS];
@@ -726,15 +725,21 @@ __global__ __launch_bounds__(1024) void k_rank_wide(const int32_t* __restrict__ 
     for (int e = threadIdx.x; e < E; e += 1024) blockcnt[size_t(blockIdx.x) * E + e] = count[e];
 }
 
-__global__ __launch_bounds__(1024) void k_places(int32_t* __restrict__ blockcnt, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                 int32_t* __restrict__ tile_start, RowTile* __restrict__ tiles, int max_tiles, int E, int nblk)
+// block 0 also writes the experts' tables; tiles as in k_group_small
+__global__ __launch_bounds__(1024) void k_place_wide(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank, const int32_t* __restrict__ blockcnt,
+                                                     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
+                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv, RowTile* __restrict__ tiles, int max_tiles,
+                                                     int A, int E, int nblk)
 {
+    __shared__ int32_t first[SMALL_EXPERTS];              // where this block's uses of an expert start
     __shared__ int32_t wsum[16], wtsum[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, blk = blockIdx.x, a = blk * 1024 + tid;
+    const bool tables = blk == 0;
+    const int my = a < A ? idx[a] : 0, rank = a < A ? lrank[a] : 0;
     int carry = 0, tcarry = 0;
     for (int e0 = 0; e0 < E; e0 += 1024) {
         const int e = e0 + tid;
-        int c = 0;
+        int c = 0, before = 0;                            // uses of this expert in all blocks, in the blocks before this one
         if (e < E) {
             for (int b0 = 0; b0 < nblk; b0 += 16) {
                 int v[16];
@@ -742,12 +747,12 @@ __global__ __launch_bounds__(1024) void k_places(int32_t* __restrict__ blockcnt,
                 for (int i = 0; i < 16; ++i) v[i] = b0 + i < nblk ? blockcnt[size_t(b0 + i) * E + e] : 0;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    if (b0 + i < nblk) blockcnt[size_t(b0 + i) * E + e] = c;
                     c += v[i];
+                    before += b0 + i < blk ? v[i] : 0;
                 }
             }
         }
-        const int tl = (c + TM - 1) / TM;                    // from here on as k_offsets
+        const int tl = (c + TM - 1) / TM;                 // from here on as k_offsets
         int inc = c, tinc = tl;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -757,26 +762,35 @@ __global__ __launch_bounds__(1024) void k_places(int32_t* __restrict__ blockcnt,
         }
         if (lane == 63) { wsum[wave] = inc; wtsum[wave] = tinc; }
         __syncthreads();
-        int before = 0, tbefore = 0, all = 0, tall = 0;
+        int earlier = 0, tearlier = 0, all = 0, tall = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
             const int s = wsum[w], t = wtsum[w];
-            if (w < wave) { before += s; tbefore += t; }
+            if (w < wave) { earlier += s; tearlier += t; }
             all += s;
             tall += t;
         }
         if (e < E) {
-            const int at = carry + before + inc - c, tat = tcarry + tbefore + tinc - tl;
-            counts[e] = c;
-            offsets[e] = at;
-            tile_start[e] = tat;
-            if (tiles)
-                for (int t = 0; t < tl; ++t) tiles[tat + t] = RowTile{e, at + t * TM, min(TM, c - t * TM), 0};
+            const int at = carry + earlier + inc - c, tat = tcarry + tearlier + tinc - tl;
+            first[e] = at + before;
+            if (tables) {
+                counts[e] = c;
+                offsets[e] = at;
+                tile_start[e] = tat;
+                if (tiles)
+                    for (int t = 0; t < tl; ++t) tiles[tat + t] = RowTile{e, at + t * TM, min(TM, c - t * TM), 0};
+            }
         }
         carry += all;
         tcarry += tall;
         __syncthreads();
     }
+    if (a < A) {
+        const int pos = first[my] + rank;
+        perm[pos] = a;
+        inv[a] = pos;
+    }
+    if (!tables) return;
     if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
     if (tiles)
         for (int t = tcarry + tid; t < max_tiles; t += 1024) tiles[t] = RowTile{0, 0, 0, 0};
@@ -1305,7 +1319,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
     // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
-    // m3 stable counting sort: few uses in one workgroup, more in three launches, beyond that in five.  Where the expert layers
+    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.  Where the expert layers
     // have too few 64 x 256 tiles to keep the chip's memory busy with k_grouped_gemm they run on small tiles.  The line, us
     // a layer pair with k_grouped_gemm / k_grouped_skinny by the number of its tiles: 200: 99 / 57, 256: 77 / 53, 520: 190 /
     // 109, 768: 118 / 124, 1024: 225 / 239, 9000: 1640 / 1950.  (The number is a bound; of up to 1024 uses fewer experts are
@@ -1317,7 +1331,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
     // each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
-    const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024 && (long long)E * ((A + 1023) / 1024) <= MID_COUNTS;
+    const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
     const bool few_tiles = (small || mid) && fused_permute && (long long)skinny_tiles * ((std::max(h, d) + TN - 1) / TN) <= (small ? 1200 : 640);
     auto skinny_layer = [&](int N, int K) {                        // rounds <= 1.6 + K / 300 (1.6 for full tiles); not too little in all
@@ -1332,15 +1346,15 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     } else if (mid) {
         const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for)
         hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(1024), 0, st, topk_idx, lrank, blockcnt, A, E);
-        hipLaunchKernelGGL(k_places, dim3(1), dim3(1024), 0, st, blockcnt, counts, offsets, tile_start, tiles, skinny_tiles, E, nblk);
-        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, 1024, 1, E);
+        hipLaunchKernelGGL(k_place_wide, dim3(nblk), dim3(1024), 0, st, topk_idx, lrank, blockcnt, counts, offsets, tile_start, perm, inv, tiles,
+                           skinny_tiles, A, E, nblk);
     } else {
         const size_t nbc = size_t(E) * L.nblk;
         hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
         hipLaunchKernelGGL(k_rank_blocks, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, A, L.nblk);
         hipLaunchKernelGGL(k_scan_blocks, dim3((E + 3) / 4), dim3(256), 0, st, blockcnt, counts, E, L.nblk);
         hipLaunchKernelGGL(k_offsets, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, E);
-        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, SORT_BLOCK, L.nblk, 1);
+        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, L.nblk);
     }
     if (timed) dynb::timing_mark(st, dynb::ST_SORT, 0);
     // m4 permute

@@ -158,6 +158,15 @@ def test_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
     assert util.normwise(out, oracle_experts(oracle, m, r, W1, W2)) < OUT_TOL
 
 
+@pytest.mark.parametrize("T,d,h,E,k", [(3333, 256, 32, 1536, 2),     # 13 x 12 tiles and 5 tokens more, the shortest K loop
+                                        (1801, 320, 32, 3072, 2),     # 7 x 24 tiles and 9 tokens, an odd number of K-chunks
+                                        (2048, 1024, 8, 2048, 1)])    # 8 x 16 tiles, as few as the wide kernel gets at this width
+@pytest.mark.parametrize("noisy", [True, False])
+def test_many_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
+    """As many tiles as the wide gate kernel is chosen for (fewer, the shapes above, go to the 64 x 64 one)."""
+    test_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy)
+
+
 @pytest.mark.parametrize("T,d,h,E,k,zipf", [(1536, 256, 512, 6, 2, 1.5),      # most groups beyond 256 rows, ragged rests
                                              (2048, 128, 256, 3, 1, 0.0),      # near-equal groups, short K loops
                                              (700, 256, 256, 2, 2, 0.0)])      # every token to both experts: 700 rows each
