@@ -495,7 +495,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         }
         __builtin_amdgcn_sched_barrier(0);
         ring_fill<RW>(ring, wrow_bT);                             // arrives while the tile is written
-        for (int c = tid; c < BORDER_PIX * 16; c += NTHR) zero_border_piece(c);
+        zero_border<NTHR>(tid, row_a, row_a + 2 * MTA + 1);
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
             const int c = c_lo + i * NTHR;

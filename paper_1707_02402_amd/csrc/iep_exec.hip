@@ -198,7 +198,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     }
     __builtin_amdgcn_sched_barrier(0);
     if (!binary) ring_fill<RW>(ring, wrow_a);
-    for (int c = tid; c < BORDER_PIX * 16; c += NTHR) zero_border_piece(c);
+    zero_border<NTHR>(tid, row_a, row_a + 2 * MTA + 1);
     *reinterpret_cast<float*>(lds_raw + BIAS_OFF + tid * 4) = bias_reg[0];
     if (tid < C) *reinterpret_cast<float*>(lds_raw + BIAS_OFF + (2 * C + tid) * 4) = bias_reg[1];
     stage_store();

@@ -14,19 +14,21 @@ constexpr int S = 14;                    // spatial size
 constexpr int P = S * S;                 // 196 pixels
 constexpr int HALO = 16;                 // tile side with zero border
 constexpr int PIX_BYTES = 272;           // 128 channels bf16 + 16 bytes pad: 17 granules of 16 bytes
-// A pixel (y, x) sits at granule x + y (mod 16): the pixels of one image row, which half a fragment reads, fall on distinct
-// granules, i.e. on all 64 LDS banks.  The two rows of a fragment are one granule apart, and an LDS pass takes lanes of both:
-// the counters report 0.45 of the LDS cycles as bank conflicts, under MFMAs that take longer.
-// Rows are 17 pixels wide: columns 15 and 16 and the next row's column 0 are zeros, which is what the two padding columns
+// A row is 304 granules of 16 bytes apart from the next, a multiple of the banks: pixel (y, x) sits at granule x (mod 16), and the lanes
+// that an LDS pass takes from the two image rows of a fragment (four consecutive ones of either, shifted against each other) meet
+// distinct banks.  (17 pixels, 289 granules, put the second row one granule further: a conflict in every pass, 0.45 of the LDS
+// cycles.  With 304 the counters say 0.014.  The MFMAs above them hide most of it: 1000 programs 1924 -> 1911 us, 256 programs 621 -> 618.)
+// Of a row 14 pixels are the map's; the pixel before and all behind are zeros, which is what the two padding columns
 // of a pixel tile (below) read, whatever the tap.  (Zeros and not the last pixel again: the chip is at its power limit in
 // these kernels, and the matrix pipes take less of it for zeros: builds that run the K loop alone, on all CUs, reach 1.62 instead
 // of 1.52 PFLOP/s.)
-constexpr int ROW_PIX = HALO + 1;
-constexpr int ROW_BYTES = ROW_PIX * PIX_BYTES;         // 4624
-constexpr int TILE_BYTES = HALO * ROW_BYTES + PIX_BYTES;   // 74256: the last row's neighbour is a zero pixel of its own
-constexpr int BORDER_PIX = 2 * ROW_PIX + (HALO - 2) * 3 + 1;
+constexpr int ROW_BYTES = 304 * 16;
+static_assert(ROW_BYTES >= (HALO + 1) * PIX_BYTES, "room for the zeros on the right");
+constexpr int TILE_BYTES = HALO * ROW_BYTES + PIX_BYTES;   // (the last row's neighbours are zeros of their own)
+constexpr int RIM = (S + 1) * PIX_BYTES;                // first byte of a row behind its last pixel
+constexpr int TOP_PIECES = (ROW_BYTES + PIX_BYTES) / 16, RIM_PIECES = (ROW_BYTES - RIM + PIX_BYTES) / 16;
 constexpr int BIAS_OFF = TILE_BYTES;                    // behind the tile: three vectors of C biases
-constexpr int LDS_BYTES = TILE_BYTES + 3 * C * 4;       // 75792: two workgroups per CU
+constexpr int LDS_BYTES = TILE_BYTES + 3 * C * 4;       // 79632: two workgroups per CU
 constexpr int CENTER = ROW_BYTES + PIX_BYTES;           // (+1,+1) from the top-left tap
 }  // namespace mf
 
@@ -76,17 +78,22 @@ __device__ __forceinline__ uint32_t pair_lane_addr(int lane)
     return uint32_t((r >> 4) * mf::ROW_BYTES + ((r & 15) < mf::S ? r & 15 : mf::S + 1) * mf::PIX_BYTES + (lane >> 5) * 128);
 }
 
-// writes piece c (16 bytes; c < 16 BORDER_PIX) of the halo tile's zero border
-__device__ __forceinline__ void zero_border_piece(int c)
+// Zeros around the map in tile rows lo .. hi (what a workgroup's first conv reads; all sixteen of them took a part of a node 0.2 us more, 2 to 4 % of
+// a narrow level), by threads tid, tid + NTHR, ...: between the last pixel of a row and the first of the next
+// (rim r: behind row r), the whole top row and bottom row where they are among them.
+template <int NTHR>
+__device__ __forceinline__ void zero_border(int tid, int lo, int hi)
 {
     using namespace mf;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int q = c >> 4;
-    int row, col;
-    if (q < ROW_PIX) { row = 0; col = q; }
-    else if (q < 2 * ROW_PIX + 1) { row = HALO - 1; col = q - ROW_PIX; }        // (and the pixel behind the last row)
-    else { row = 1 + (q - 2 * ROW_PIX - 1) / 3; col = (q - 2 * ROW_PIX - 1) % 3; if (col > 0) col += HALO - 2; }
-    *reinterpret_cast<u32x4*>(lds_raw + uint32_t(row * ROW_BYTES + col * PIX_BYTES + (c & 15) * 16)) = u32x4{0u, 0u, 0u, 0u};
+    const int top = lo == 0 ? TOP_PIECES : 0, rim0 = lo == 0 ? 1 : lo - 1, rims = ((hi == HALO - 1 ? HALO - 2 : hi) - rim0 + 1) * RIM_PIECES;
+    const int all = top + rims + (hi == HALO - 1 ? ROW_BYTES / 16 : 0);
+    for (int c = tid; c < all; c += NTHR) {
+        const int q = c - top, row = q / RIM_PIECES;
+        const int at = q < 0 ? c * 16 : q < rims ? (rim0 + row) * ROW_BYTES + RIM + (q - row * RIM_PIECES) * 16
+                                                 : (HALO - 1) * ROW_BYTES + PIX_BYTES + (q - rims) * 16;
+        *reinterpret_cast<u32x4*>(lds_raw + uint32_t(at)) = u32x4{0u, 0u, 0u, 0u};
+    }
 }
 
 // ---- K loop of a conv3x3 ----------------------------------------------------------------------------
