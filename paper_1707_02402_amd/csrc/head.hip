@@ -201,24 +201,59 @@ __global__ __launch_bounds__(256) void k_head_finish_slices(const float* __restr
     }
 }
 
-// The last layer and the softmax of one example per workgroup: a wave takes every fourth answer, its lanes the hidden units.
+// The last layer and the softmax of one example per workgroup: a wave takes every fourth (SLICES: sixteenth) answer, its lanes the hidden units.
 // (As a product, a sum of slices and a softmax they were three launches, 12 us for one example.)
+// SLICES: the hidden units themselves are still partial sums of n_slices slices, part[slice][example][unit]; they are added up here as
+// k_head_finish_slices does it, four threads a unit, each all of its slices in one trip to memory: one launch less, 2.4 us
+// of one program's 178, 3 of 23 programs' 287.
 constexpr int HEAD_ANSWERS = 64;                   // logits kept in LDS
-template <typename T>
-__global__ __launch_bounds__(256) void k_head_answers(const T* __restrict__ h1, const T* __restrict__ wf2, const float* __restrict__ bf2,
-                                                      float* __restrict__ logits, float* __restrict__ probs, int F, int A)
+constexpr int HEAD_UNITS = 2048;                   // hidden units kept in LDS (SLICES)
+struct AnswerArgs {
+    const void* h1;                                // [B][F]
+    const float* part;                             // SLICES
+    const float* bf1;
+    const void* wf2;
+    const float* bf2;
+    float* logits;
+    float* probs;
+    int B, F, A, n_slices;
+};
+template <typename T, bool SLICES>
+__global__ __launch_bounds__(SLICES ? 1024 : 256) void k_head_answers(AnswerArgs g)
 {
+    constexpr int WAVES = SLICES ? 16 : 4;
     __shared__ float row[HEAD_ANSWERS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const T* h = h1 + size_t(blockIdx.x) * F;
-    for (int a = wave; a < A; a += 4) {
-        const T* w = wf2 + size_t(a) * F;
+    __shared__ float unit[SLICES ? HEAD_UNITS : 1], sum[SLICES ? 4 : 1][SLICES ? 256 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, F = g.F, A = g.A;
+    const T* h = static_cast<const T*>(g.h1) + size_t(blockIdx.x) * F;
+    if constexpr (SLICES) {
+        const size_t MN = size_t(g.B) * F;
+        const int q = tid >> 8, r = tid & 255;     // this thread: slices q, q + 4, ... of unit f0 + r
+        for (int f0 = 0; f0 < F; f0 += 256) {
+            const int f = f0 + r;
+            float v = 0.f;
+            if (f < F) {
+                const float* p = g.part + size_t(blockIdx.x) * F + f;
+#pragma unroll 16
+                for (int z = q; z < g.n_slices; z += 4) v += p[size_t(z) * MN];
+            }
+            sum[q][r] = v;
+            __syncthreads();
+            if (q == 0 && f < F) {
+                v = ((sum[0][r] + sum[1][r]) + sum[2][r]) + sum[3][r] + (g.bf1 ? g.bf1[f] : 0.f);
+                unit[f] = round_to<T>(fmaxf(v, 0.f));
+            }
+            __syncthreads();
+        }
+    }
+    for (int a = wave; a < A; a += WAVES) {
+        const T* w = static_cast<const T*>(g.wf2) + size_t(a) * F;
         float v = 0.f;
 #pragma unroll 4
-        for (int f = lane; f < F; f += 64) v = fmaf(load_f32(h + f), load_f32(w + f), v);
+        for (int f = lane; f < F; f += 64) v = fmaf(SLICES ? unit[SLICES ? f : 0] : load_f32(h + f), load_f32(w + f), v);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) row[a] = v + (bf2 ? bf2[a] : 0.f);
+        if (lane == 0) row[a] = v + (g.bf2 ? g.bf2[a] : 0.f);
     }
     __syncthreads();
     if (wave != 0) return;
@@ -231,8 +266,8 @@ __global__ __launch_bounds__(256) void k_head_answers(const T* __restrict__ h1, 
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off);
     for (int a = lane; a < A; a += 64) {
-        logits[size_t(blockIdx.x) * A + a] = row[a];
-        probs[size_t(blockIdx.x) * A + a] = expf(row[a] - mx) / den;
+        g.logits[size_t(blockIdx.x) * A + a] = row[a];
+        g.probs[size_t(blockIdx.x) * A + a] = expf(row[a] - mx) / den;
     }
 }
 
@@ -303,9 +338,10 @@ int check_head(const dynb_head_shape* s, int32_t B, const char* who)
     return DYNB_OK;
 }
 
+// keep: the sum of FINISH_SLICES slices and more is left to the caller; returns their number then, else 0
 template <typename TO, bool RELU>
-void launch_layer(int dtype, const void* a, const void* w, const float* bias, TO* out, float* part, int M, int N, int K,
-                  int splits, hipStream_t st)
+int launch_layer(int dtype, const void* a, const void* w, const float* bias, TO* out, float* part, int M, int N, int K,
+                 int splits, hipStream_t st, bool keep = false)
 {
     GemmArgs g{a, w, part, M, N, K, 0, nullptr, nullptr};
     if (splits == 1 && RELU) { g.out = out; g.bias = bias; }
@@ -315,13 +351,32 @@ void launch_layer(int dtype, const void* a, const void* w, const float* bias, TO
     if (dtype == DYNB_BF16 && K % 8 == 0) hipLaunchKernelGGL(k_head_gemm_mfma, grid, dim3(256), 0, st, g);
     else if (dtype == DYNB_BF16) hipLaunchKernelGGL((k_head_gemm_fma<bf16_t>), grid, dim3(256), 0, st, g);
     else hipLaunchKernelGGL((k_head_gemm_fma<float>), grid, dim3(256), 0, st, g);
-    if (g.out) return;
+    if (g.out) return 0;
     const size_t MN = size_t(M) * N;
     const int n_slices = int(grid.z);
+    if (keep && n_slices >= FINISH_SLICES) return n_slices;
     if (n_slices >= FINISH_SLICES)
         hipLaunchKernelGGL((k_head_finish_slices<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 63) / 64, 4096))), dim3(256), 0, st, part, bias, out, MN, N, n_slices);
     else
         hipLaunchKernelGGL((k_head_finish<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 255) / 256, 4096))), dim3(256), 0, st, part, bias, out, MN, N, n_slices);
+    return 0;
+}
+
+// conv 1x1 and fc 1, then fc 2: with the softmax (answers) or as logits
+template <typename T>
+void launch_head(const dynb_head_shape* s, const dynb_head_weights* w, const HeadLayout& L, const void* roots, int B, char* ws, float* logits, float* probs,
+                 bool answers, hipStream_t st)
+{
+    const int P = s->H * s->W;
+    T* z = reinterpret_cast<T*>(ws + L.z);
+    T* h1 = reinterpret_cast<T*>(ws + L.h1);
+    float* part = reinterpret_cast<float*>(ws + L.part);
+    launch_layer<T, true>(s->dtype, roots, w->wc, w->bc, z, part, B * P, s->Cc, s->C, L.s1, st);
+    const int slices = launch_layer<T, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, P * s->Cc, L.s2, st, answers && s->F <= HEAD_UNITS);
+    const AnswerArgs g = {h1, part, w->bf1, w->wf2, w->bf2, logits, probs, B, s->F, s->n_answers, slices};
+    if (slices > 0) hipLaunchKernelGGL((k_head_answers<T, true>), dim3(unsigned(B)), dim3(1024), 0, st, g);
+    else if (answers) hipLaunchKernelGGL((k_head_answers<T, false>), dim3(unsigned(B)), dim3(256), 0, st, g);
+    else launch_layer<float, false>(s->dtype, h1, w->wf2, w->bf2, logits, part, B, s->n_answers, s->F, L.s3, st);
 }
 
 }  // namespace
@@ -348,8 +403,6 @@ extern "C" int dynbatch_classify(const dynb_head_shape* s, const dynb_head_weigh
         return fail(DYNB_E_INVAL, "dynbatch_classify: bf16 tensors must be 16-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
-    const int P = s->H * s->W, M1 = B * P, J = P * s->Cc;
-    float* part = reinterpret_cast<float*>(ws + L.part);
     float* logits = logits_out ? logits_out : reinterpret_cast<float*>(ws + L.logits);
     // A workgroup takes a wave's sum and exchange (some 0.4 us) for every fourth answer, and every example streams the weights through
     // its own CU; the matrix product pays two more launches.  us a pass (bf16, F = 256 but where stated), product / one workgroup:
@@ -358,21 +411,8 @@ extern "C" int dynbatch_classify(const dynb_head_shape* s, const dynb_head_weigh
     // answers, 256: 29 / 26, 1000: 29 / 33.
     const bool answers = s->n_answers <= HEAD_ANSWERS && (long long)s->n_answers * s->F <= 65536 &&
                          (long long)s->n_answers * s->F * B <= (1 << 25);
-    if (s->dtype == DYNB_BF16) {
-        bf16_t* z = reinterpret_cast<bf16_t*>(ws + L.z);
-        bf16_t* h1 = reinterpret_cast<bf16_t*>(ws + L.h1);
-        launch_layer<bf16_t, true>(s->dtype, roots, w->wc, w->bc, z, part, M1, s->Cc, s->C, L.s1, st);
-        launch_layer<bf16_t, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, J, L.s2, st);
-        if (answers) hipLaunchKernelGGL((k_head_answers<bf16_t>), dim3(unsigned(B)), dim3(256), 0, st, h1, static_cast<const bf16_t*>(w->wf2), w->bf2, logits, probs, s->F, s->n_answers);
-        else launch_layer<float, false>(s->dtype, h1, w->wf2, w->bf2, logits, part, B, s->n_answers, s->F, L.s3, st);
-    } else {
-        float* z = reinterpret_cast<float*>(ws + L.z);
-        float* h1 = reinterpret_cast<float*>(ws + L.h1);
-        launch_layer<float, true>(s->dtype, roots, w->wc, w->bc, z, part, M1, s->Cc, s->C, L.s1, st);
-        launch_layer<float, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, J, L.s2, st);
-        if (answers) hipLaunchKernelGGL((k_head_answers<float>), dim3(unsigned(B)), dim3(256), 0, st, h1, static_cast<const float*>(w->wf2), w->bf2, logits, probs, s->F, s->n_answers);
-        else launch_layer<float, false>(s->dtype, h1, w->wf2, w->bf2, logits, part, B, s->n_answers, s->F, L.s3, st);
-    }
+    if (s->dtype == DYNB_BF16) launch_head<bf16_t>(s, w, L, roots, B, ws, logits, probs, answers, st);
+    else launch_head<float>(s, w, L, roots, B, ws, logits, probs, answers, st);
     if (!answers) hipLaunchKernelGGL(k_head_softmax, dim3(unsigned((B + 3) / 4)), dim3(256), 0, st, logits, probs, B, s->n_answers);
     HIP_TRY(hipGetLastError(), "dynbatch_classify");
     return DYNB_OK;
