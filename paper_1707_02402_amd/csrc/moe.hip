@@ -1069,8 +1069,7 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__
 }
 
 // The expert layers for few tiles (the rule stands where it is applied).  There a layer is a stream of weights, each multiplied with a handful of rows: what
-// counts is how much of it is in flight.  k_grouped_gemm asks for one K-chunk at a time and for 256 features per workgroup;
-// with some 40 live experts that is 160 workgroups with 40 KB in flight each, 31 to 39 us for 38 MB.  Here a workgroup
+// counts is how much of it is in flight.  k_grouped_gemm asks for one K-chunk at a time and for 256 features per workgroup.  Here a workgroup
 // owns 64 features of a row tile, a wave 16 of them, and weights go straight from memory into registers, SK_RD K-steps (1 KB
 // each) ahead; two consecutive steps read one 128-byte line per row.  The rows pass through LDS, 32 KB of them at a time: four
 // waves that read their fragments from global memory are answered at 16 bytes per clock (neighbouring lanes hold different
@@ -1092,10 +1091,11 @@ __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ in, const
     const bf16_t* const pw = We + size_t(min(n0 + r, N - 1)) * K;
     const int S = (K + 31) / 32, last = S - 1;
     u32x4 w[U];
-    // past the end the last step again; behind K (a multiple of 8) anything, replaced by zeros
+    // past the end the last step again; behind K (a multiple of 8) anything, replaced by zeros where it is used (here, the
+    // replacement would wait for every piece as it is requested)
     auto fetch = [&](int s, u32x4& v) {
         const int k = min(s, last) * 32 + g * 8;
-        v = *reinterpret_cast<const u32x4*>(pw + (k < K ? k : 0)) & (k < K ? ~0u : 0u);
+        v = *reinterpret_cast<const u32x4*>(pw + (k < K ? k : 0));
     };
 #pragma unroll
     for (int u = 0; u < U; ++u) fetch(u, w[u]);
@@ -1120,10 +1120,11 @@ __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ in, const
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (s + u < S) {
+                    const u32x4 wu = w[u] & ((s + u) * 32 + g * 8 < K ? ~0u : 0u);
 #pragma unroll
                     for (int m = 0; m < ML; ++m) {
                         const u32x4 x = *reinterpret_cast<const u32x4*>(lds + (m * 16 + r) * PITCH + (s + u - b) * 64 + g * 16);
-                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[u]), __builtin_bit_cast(bf16x8, x), acc[m], 0, 0, 0);
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wu), __builtin_bit_cast(bf16x8, x), acc[m], 0, 0, 0);
                     }
                 }
                 fetch(s + u + U, w[u]);
@@ -1319,24 +1320,22 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
     // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
-    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.  Where the expert layers
-    // have too few 64 x 256 tiles to keep the chip's memory busy with k_grouped_gemm they run on small tiles.  The line, us
-    // a layer pair with k_grouped_gemm / k_grouped_skinny by the number of its tiles: 200: 99 / 57, 256: 77 / 53, 520: 190 /
-    // 109, 768: 118 / 124, 1024: 225 / 239, 9000: 1640 / 1950.  (The number is a bound; of up to 1024 uses fewer experts are
-    // live: 1040: 108 / 81, 1088: 148 / 141, 1152: 290 / 268.)  Of the two layers each takes its own kernel: k_grouped_skinny pays some
-    // 11 us for every round of 768 workgroups (three a CU) whatever they sum, so a layer of many features and short sums is not for
-    // it, nor is one of a few workgroups and short sums.  us a layer, features x summed channels, rounds: 512 x 64, 2.4: 13 / 33;
-    // 1024 x 128, 4.4: 16 / 50; 256 x 256, 1.2: 27 / 19, 2.8: 26 / 34; 1024 x 512, 1.6: 37 / 28, 2.1: 36 / 35; 2048 x 512, 4.8: 50 / 59; 2048 x
-    // 1024, 3.3: 84 / 70, 4.8: 90 / 99; 512 x 2048, 1.2: 120 / 63; 448 x 128, 0.1: 7 / 10; 72 x 120, 0.4: 14 / 7.6; tiles of 49 rows on average, 1024 x 1024, 2.6: 54 / 78.
+    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.  An expert
+    // layer of few tiles and long sums runs on k_grouped_skinny, each layer for itself: k_grouped_gemm pays 1.2 to 1.5 us for every 64 summed channels
+    // however few tiles there are, k_grouped_skinny some 11 us for every round of 768 workgroups (three a CU) whatever they sum.  us a layer,
+    // k_grouped_gemm / k_grouped_skinny, features x summed channels, rounds: 256 x 2048, 0.1 30 / 15; 768 x 2048, 0.9 47 / 29; 256 x 1024,
+    // 0.1 18 / 11, 0.6 20 / 14; 512 x 1024, 0.25 21 / 12; 256 x 512, 0.7 13.4 / 9.3; 240 x 432, 0.2 12 / 8.6; 128 x 216, 0.6 10.4 / 8.8; 512 x 512,
+    // 1.4 16 / 24; 2048 x 512, 2.0 18 / 31; 1024 x 256, 1.4 10 / 20; 192 x 320, 1.2 15 / 23; 128 x 192, 0.6 10.3 / 14; 128 x 128, 0.5 7.5 / 10; full tiles:
+    // 128 x 1296, 0.1 24 / 17; 248 x 1024, 0.5 21 / 19.  (400 layers of up to 65536 uses: the rule takes 1.2 % longer than the better kernel
+    // of each would, in the mean.  The lines drawn while k_grouped_gemm gave all of up to 128 tiles to one XCD took 10 %.)
     // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
     // each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
     const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
-    const bool few_tiles = (small || mid) && fused_permute && (long long)skinny_tiles * ((std::max(h, d) + TN - 1) / TN) <= (small ? 1200 : 640);
-    auto skinny_layer = [&](int N, int K) {                        // rounds <= 1.6 + K / 300 (1.6 for full tiles); not too little in all
+    auto skinny_layer = [&](int N, int K) {                            // rounds <= (K - 128) / 600
         const long long groups = (long long)skinny_tiles * ((N + 63) / 64);
-        return few_tiles && groups * 300 <= 768 * (480ll + (A < 32ll * skinny_tiles ? K : 0)) && (K >= 224 || A >= 128 || groups * 5 >= 768);
+        return (small || mid) && fused_permute && groups * 600 <= 768ll * (K - 128);
     };
     const bool skinny1 = skinny_layer(h, d), skinny2 = skinny_layer(d, h), skinny = skinny1 || skinny2;
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
