@@ -719,6 +719,7 @@ struct WgArgs {
     const bf16_t* sv_dm;
     const bf16_t* sv_dc;
     float* partial;               // [unit][3][C][C] weight gradient ([tap][co][ci]; conv1x1: tap 0 only), then [C] bias gradient
+    float* dw3a; float* db3a; float* dw3b; float* db3b; float* dw1; float* db1;
 };
 constexpr size_t WG_PARTIAL = size_t(3) * 128 * 128 + 128;           // floats per unit
 constexpr int WG_ROW = 16 * 128, WG_MAP = mf::S * WG_ROW;            // LDS: bytes of an image row (columns 14, 15 are zeros), of a half map
@@ -731,9 +732,10 @@ __device__ __forceinline__ i16x4 lds_read_pixels(uint32_t addr)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>((__attribute__((address_space(3))) unsigned char*)lds_raw + addr));
 }
 
-// CONV: un is the first of the chunk's three units (kernel row 0), the others follow `stride` units apart
+// chunks: the function's; a single one is the whole sum and goes where the gradients go.  CONV: un is the first of the chunk's three units (kernel
+// row 0), the others follow `chunks` units apart
 template <bool CONV>
-__device__ __forceinline__ void wgrad_chunk(const WgArgs& a, const dynb_wg_unit un, const int32_t unit, const int32_t stride, const int quad)
+__device__ __forceinline__ void wgrad_chunk(const WgArgs& a, const dynb_wg_unit un, const int32_t unit, const int32_t chunks, const int quad)
 {
     using namespace mf;
     constexpr int K = CONV ? 3 : 1, NTHR = 256;
@@ -868,18 +870,24 @@ __device__ __forceinline__ void wgrad_chunk(const WgArgs& a, const dynb_wg_unit 
         multiply();
     }
     // D[co][ci]: lane ci = lane % 32, element i: co = 8 (i / 4) + 4 (lane / 32) + i % 4; a store writes two rows of 128 bytes
-    float* out = a.partial + size_t(unit) * WG_PARTIAL;
-    const int m = lane & 31, hk = lane >> 5;
-    float* const to = out + (size_t(co_half * 64 + wj * 32 + 4 * hk) * C + ci_half * 64 + wi * 32 + m);
+    const int m = lane & 31, hk = lane >> 5, co = co_half * 64 + wj * 32 + 4 * hk, ci = ci_half * 64 + wi * 32 + m;
+    const bool whole = chunks == 1;
+    float* const out = a.partial + size_t(unit) * WG_PARTIAL;
+    // elements between kernel rows, taps of a row, output channels
+    const size_t to_row = CONV ? (whole ? size_t(3 * C) : size_t(chunks) * WG_PARTIAL) : 0;
+    const uint32_t to_tap = whole ? C : C * C, to_co = !whole ? C : CONV ? 9 * C : 2 * C;
+    float* const dw = !whole ? out : !CONV ? a.dw1 + (size_t(un.type) * C * 2 + un.part) * C : (un.mode == 0 ? a.dw3b : a.dw3a) + size_t(un.type) * C * 9 * C;
+    float* const to = dw + size_t(co) * to_co + ci;
 #pragma unroll
     for (int kh = 0; kh < K; ++kh)
 #pragma unroll
         for (int kw = 0; kw < K; ++kw)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) to[size_t(kh) * stride * WG_PARTIAL + (kw * C + 8 * (i / 4) + i % 4) * C] = acc[kh][kw][i];
+            for (int i = 0; i < 16; ++i) (to + kh * to_row)[kw * to_tap + uint32_t(8 * (i / 4) + i % 4) * to_co] = acc[kh][kw][i];
     if (with_bias) {
         bias += __shfl_xor(bias, 32);
-        if (hk == 0) out[size_t(3) * C * C + co_half * 64 + wj * 32 + m] = bias;
+        float* const db = !whole ? out + size_t(3) * C * C : (!CONV ? a.db1 : un.mode == 0 ? a.db3b : a.db3a) + size_t(un.type) * C;
+        if (hk == 0) db[co_half * 64 + wj * 32 + m] = bias;
     }
 }
 
@@ -888,16 +896,18 @@ __device__ __forceinline__ void wgrad_chunk(const WgArgs& a, const dynb_wg_unit 
 __global__ __launch_bounds__(256, 2) void k_bwd_wgrad_mfma(WgArgs a)
 {
     const int set = int(blockIdx.x >> 5), x = blockIdx.x & 7, quad = (blockIdx.x >> 3) & 3, conv_sets = (a.n_chunks + 7) / 8;
+    auto chunks_of = [&](int type) { return (a.fn_first[type + 1] - a.fn_first[type] + DYNB_WG_CHUNK - 1) / DYNB_WG_CHUNK; };
     if (set < conv_sets) {
         if (set * 8 + x >= a.n_chunks) return;
         const int32_t u = a.order[set * 24 + x];                      // (the parts of eight chunks follow each other in the order)
         const dynb_wg_unit un = a.units[u];
-        wgrad_chunk<true>(a, un, u, (a.fn_first[un.type + 1] - a.fn_first[un.type] + DYNB_WG_CHUNK - 1) / DYNB_WG_CHUNK, quad);
+        wgrad_chunk<true>(a, un, u, chunks_of(un.type), quad);
     } else {
         const int j = (set - conv_sets) * 8 + x;
         if (j >= a.n_joins) return;
         const int32_t u = 3 * a.n_chunks + j;
-        wgrad_chunk<false>(a, a.units[u], u, 0, quad);
+        const dynb_wg_unit un = a.units[u];
+        wgrad_chunk<false>(a, un, u, chunks_of(un.type), quad);
     }
 }
 
@@ -912,6 +922,7 @@ __global__ void k_bwd_wgrad_sum(WsArgs a)
 {
     constexpr int C = 128;
     const dynb_wg_group g = a.groups[blockIdx.y];
+    if (g.n_units == 1) return;                                       // written by k_bwd_wgrad_mfma
     const int ntap = g.mode == 2 ? 1 : 3;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;              // float4 index inside [tap][co][ci]
     if (e < ntap * C * C / 4) {
@@ -1173,6 +1184,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         q.feats = a.feats; q.slots = a.slots;
         q.sv_u = a.sv_u; q.sv_m = a.sv_m; q.sv_g = a.sv_g; q.sv_dm = a.sv_dm; q.sv_dc = a.sv_dc;
         q.partial = reinterpret_cast<float*>(ws + L.partial);
+        q.dw3a = g->dw3a; q.db3a = g->db3a; q.dw3b = g->dw3b; q.db3b = g->db3b; q.dw1 = g->dw1; q.db1 = g->db1;
         const unsigned sets = unsigned((q.n_chunks + 7) / 8 + (q.n_joins + 7) / 8);
         if (sets > 0) hipLaunchKernelGGL(k_bwd_wgrad_mfma, dim3(sets * 32), dim3(256), 2 * WG_MAP, st, q);
         WsArgs r;
