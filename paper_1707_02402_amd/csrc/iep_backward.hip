@@ -387,14 +387,17 @@ __device__ __forceinline__ float* route_mf(const BmArgs& a, int32_t r)
 // forward pass's packed weights), k = (lane/32)*64 + j*8 + i, (tap, j) of the fragment as in iep_mfma.h, where
 //   ntap 9: W = src[function][k][8 - tap][o]             conv3x3 transposed, taps flipped
 //   ntap 2: W = src[function][k][tap*128 + o]            conv1x1 transposed, half `tap`
-__global__ void k_bwd_pack(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int n_types, int ntap)
+// blockIdx.y: w3a, w3b, w1
+__global__ void k_bwd_pack(PackArgs a)
 {
-    const size_t total = size_t(n_types) * 4 * ntap * 8 * 64;
+    const bf16_t* __restrict__ const src = a.src[blockIdx.y];
+    u32x4* __restrict__ const dst = a.dst[blockIdx.y];
+    const int ntap = blockIdx.y == 2 ? 2 : 9;
+    const size_t total = size_t(a.n_types) * 4 * ntap * 8 * 64;
     for (size_t q = size_t(blockIdx.x) * blockDim.x + threadIdx.x; q < total; q += size_t(gridDim.x) * blockDim.x) {
-        const int lane = int(q & 63);
-        const size_t rest = q >> 6;
-        const int f = int(rest % (size_t(ntap) * 8)), tile = int((rest / (size_t(ntap) * 8)) & 3);
-        const size_t type = rest / (size_t(ntap) * 32);
+        // a workgroup's four waves take the four channel tiles of a fragment: together they read whole rows
+        const int lane = int(q & 63), tile = int(q >> 6) & 3, f = int((q >> 8) % (size_t(ntap) * 8));
+        const size_t type = (q >> 8) / (size_t(ntap) * 8);
         const int tap = ntap == 9 ? mf::frag_kh(f) * 3 + mf::frag_kw(f) : f >> 3, j = ntap == 9 ? mf::frag_step(f) : f & 7;
         const int m = lane & 31;
         const int o = tile * 32 + ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3), k0 = (lane >> 5) * 64 + j * 8;
@@ -404,7 +407,7 @@ __global__ void k_bwd_pack(const bf16_t* __restrict__ src, u32x4* __restrict__ d
             const int k = k0 + i;
             v[i] = src[ntap == 9 ? ((type * 128 + k) * 9 + (8 - tap)) * 128 + o : (type * 128 + k) * 256 + tap * 128 + o];
         }
-        dst[q] = u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+        dst[((type * 4 + tile) * (size_t(ntap) * 8) + f) * 64 + lane] = u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
     }
 }
 
@@ -1137,14 +1140,15 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     }
 
     // weights in fragment order, as given and transposed
-    auto pack = [&](const void* src, size_t at, int ntap) {
-        const size_t pieces = size_t(nt) * 4 * ntap * 512;
-        hipLaunchKernelGGL(k_bwd_pack, dim3(unsigned(std::min<size_t>((pieces + 255) / 256, 4096))), dim3(256), 0, st,
-                           static_cast<const bf16_t*>(src), reinterpret_cast<u32x4*>(ws + at), nt, ntap);
-    };
-    pack(w->w3b, L.pk3bT, 9);
-    pack(w->w3a, L.pk3aT, 9);
-    if (p->has_binary) pack(w->w1, L.pk1T, 2);
+    PackArgs pa = {};
+    const void* const src[3] = {w->w3a, w->w3b, w->w1};
+    const size_t at[3] = {L.pk3aT, L.pk3bT, L.pk1T};
+    for (int i = 0; i < 3; ++i) {
+        pa.src[i] = static_cast<const bf16_t*>(src[i]);
+        pa.dst[i] = reinterpret_cast<u32x4*>(ws + at[i]);
+    }
+    pa.n_types = nt;
+    hipLaunchKernelGGL(k_bwd_pack, dim3(unsigned(std::min<size_t>((size_t(nt) * 4 * 9 * 512 + 255) / 256, 4096)), p->has_binary ? 3 : 2), dim3(256), 0, st, pa);
 
     float* gy = reinterpret_cast<float*>(ws + L.gy);
     launch_seed(p, dout, d_root_item, gy, chw, st);

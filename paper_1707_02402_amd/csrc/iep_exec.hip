@@ -84,23 +84,32 @@ struct MfArgs {
 
 
 // dst[function][tile][fragment][lane][i] = src[function][co = tile*32 + rho(lane%32)][tap][ci = (lane/32)*64 + j*8 + i] with
-// (tap, j) of the fragment as in iep_mfma.h; one thread per 16-byte piece; ntap = 9 for a conv3x3, 2 for the two halves
-// of the conv1x1 over 2C inputs.
+// (tap, j) of the fragment as in iep_mfma.h; a thread takes a row's half for one tap, the 128 bytes of all eight j; ntap = 9 for a conv3x3, 2 for the two
+// halves of the conv1x1 over 2C inputs.
 // rho permutes the channels inside a tile: MFMA output row m = 8b + 4h + c (accumulator element 4b + c
 // of lane half h) is given channel 16h + 4b + c, so that the 16 accumulator elements of a lane are 16
 // consecutive channels and leave the kernel as two 16-byte stores.
-__global__ void k_pack_weights(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int n_types, int ntap)
+// blockIdx.y: w3a, w3b, w1.  (In a launch each, a thread per 16-byte piece, so that up to eight XCDs fetched every line, they took 18, 11 and 4 us for 41
+// functions; in one launch 28; with whole lines 13.4.)
+__global__ void k_pack_weights(PackArgs a)
 {
-    const size_t total = size_t(n_types) * 4 * ntap * 8 * 64;
+    const u32x4* __restrict__ const src = reinterpret_cast<const u32x4*>(a.src[blockIdx.y]);
+    u32x4* __restrict__ const dst = a.dst[blockIdx.y];
+    const int ntap = blockIdx.y == 2 ? 2 : 9;
+    const size_t total = size_t(a.n_types) * ntap * 4 * 64;
     for (size_t q = size_t(blockIdx.x) * blockDim.x + threadIdx.x; q < total; q += size_t(gridDim.x) * blockDim.x) {
-        const int lane = int(q & 63);
-        const size_t rest = q >> 6;
-        const int f = int(rest % (size_t(ntap) * 8)), tile = int((rest / (size_t(ntap) * 8)) & 3);
-        const size_t type = rest / (size_t(ntap) * 32);
-        const int tap = ntap == 9 ? mf::frag_kh(f) * 3 + mf::frag_kw(f) : f >> 3, j = ntap == 9 ? mf::frag_step(f) : f & 7;
-        const int m = lane & 31;
-        const int co = tile * 32 + ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3), ci0 = (lane >> 5) * 64 + j * 8;
-        dst[q] = src[(((type * 128 + co) * ntap + tap) * 128 + ci0) >> 3];
+        const int lane = int(q & 63), tile = int(q >> 6) & 3, tap = int((q >> 8) % ntap), m = lane & 31;
+        const size_t type = (q >> 8) / ntap;
+        const int co = tile * 32 + ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3), kh = tap / 3;
+        const u32x4* const from = src + ((((type * 128 + co) * ntap + tap) * 128 + (lane >> 5) * 64) >> 3);
+        // fragments of this tap: one per step
+        const int f0 = ntap == 9 ? tap % 3 * 24 + (kh == 0 ? 0 : 3 - kh) : tap * 8, step = ntap == 9 ? 3 : 1;
+        u32x4* const to = dst + ((type * 4 + tile) * (size_t(ntap) * 8) + f0) * 64 + lane;
+        u32x4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = from[j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) to[j * step * 64] = v[j];
     }
 }
 
@@ -600,14 +609,15 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
 static void launch_pack(const dynb_module_weights* w, int n_types, char* pk, hipStream_t st)
 {
     const size_t tap_bytes = size_t(n_types) * 128 * 128 * 2;
-    const unsigned g9 = unsigned(std::min<size_t>((size_t(n_types) * 4 * 9 * 512 + 255) / 256, 4096));
-    hipLaunchKernelGGL(k_pack_weights, dim3(g9), dim3(256), 0, st, static_cast<const u32x4*>(w->w3a),
-                       reinterpret_cast<u32x4*>(pk), n_types, 9);
-    hipLaunchKernelGGL(k_pack_weights, dim3(g9), dim3(256), 0, st, static_cast<const u32x4*>(w->w3b),
-                       reinterpret_cast<u32x4*>(pk + 9 * tap_bytes), n_types, 9);
-    if (w->w1)
-        hipLaunchKernelGGL(k_pack_weights, dim3(g9), dim3(256), 0, st, static_cast<const u32x4*>(w->w1),
-                           reinterpret_cast<u32x4*>(pk + 18 * tap_bytes), n_types, 2);
+    PackArgs a = {};
+    const void* const src[3] = {w->w3a, w->w3b, w->w1};
+    for (int i = 0; i < 3; ++i) {
+        a.src[i] = static_cast<const bf16_t*>(src[i]);
+        a.dst[i] = reinterpret_cast<u32x4*>(pk + size_t(i) * 9 * tap_bytes);
+    }
+    a.n_types = n_types;
+    const unsigned grid = unsigned(std::min<size_t>(size_t(n_types) * 9, 4096));
+    hipLaunchKernelGGL(k_pack_weights, dim3(grid, w->w1 ? 3 : 2), dim3(256), 0, st, a);
 }
 
 static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void* feats, void* out, char* ws,

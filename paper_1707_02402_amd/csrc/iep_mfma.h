@@ -70,6 +70,9 @@ __host__ __device__ constexpr int frag_step(int f) { return f / 3 % 8; }
 __host__ __device__ constexpr int frag_kh(int f) { return f % 3 == 0 ? 0 : f % 3 == 1 ? 2 : 1; }
 }
 
+// The three weight tensors that are brought into fragment order, by blockIdx.y: one launch.
+struct PackArgs { const bf16_t* src[3]; u32x4* dst[3]; int n_types; };
+
 // LDS byte offset, from the tile's first byte, of what lane `lane` reads for the tile row pair that starts at tile row 0,
 // tap column 0: image row lane%32/16, column lane%16 (for columns 14, 15 the zeros from column 15 on), its half of the channels
 __device__ __forceinline__ uint32_t pair_lane_addr(int lane)
