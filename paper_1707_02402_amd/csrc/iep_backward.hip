@@ -543,18 +543,19 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     };
     // Accumulators of the second window -> the fp32 staging area, four pixel tiles per round; then every thread takes 16-byte pieces
     // (8 channels of a pixel) out of it: fn(c, lo, hi, pre(c)) with c the piece's index in the whole map.  pre(c)
-    // is evaluated for all of a thread's pieces before the round's barriers, so what it loads is there afterwards.
+    // is evaluated for all of a thread's pieces before the round's barriers, so what it loads is there afterwards.  Where there is one
+    // round (parts), its i-th piece is also known before the second conv, pre(c, i).
+    constexpr int NI = ((MTB < 4 ? MTB : 4) * 28 * 16 + NTHR - 1) / NTHR;     // pieces per thread of the larger round
     auto through_lds = [&](auto&& pre, auto&& fn) {
 #pragma unroll
         for (int round = 0; round < (MTB + 3) / 4; ++round) {
             const int t0 = round * 4, t1 = min(t0 + 4, MTB), p0 = row_b * S + t0 * 28;
             const int lo = PARTS == 1 ? p0 * 16 : own_lo, hi = PARTS == 1 ? p0 * 16 + (t1 - t0) * 28 * 16 : own_hi;   // (parts: one round)
-            constexpr int NI = ((MTB < 4 ? MTB : 4) * 28 * 16 + NTHR - 1) / NTHR;     // pieces per thread of the larger round
-            decltype(pre(0)) ahead[NI];
+            decltype(pre(0, 0)) ahead[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int c = lo + tid + i * NTHR;
-                if (c < hi && mine(c)) ahead[i] = pre(c);
+                if (c < hi && mine(c)) ahead[i] = pre(c, i);
             }
             __syncthreads();                                          // the area (and, the first time, the tile) is free
 #pragma unroll
@@ -628,6 +629,17 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     // ---- du = g + conv(dmid; W_a flipped, transposed).  The residual term g is added in fp32, from the gradient map
     // itself, not from its bf16 copy in the tile: down a chain of modules the convolution's share is small against
     // the residual's and would vanish below the bfloat16 quantum of the latter at every level.
+    const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
+    // (a part's pieces of it are requested here: behind the loop they were a trip to memory that nothing hid)
+    Grad residue[PARTS > 1 ? NI : 1];
+    if constexpr (PARTS > 1) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int c = own_lo + tid + i * NTHR;
+            if (c < own_hi && mine(c)) residue[i] = Grad{gy4[2 * c], gy4[2 * c + 1]};
+        }
+    }
+    auto grad = [&](int c, int i) -> Grad { if constexpr (PARTS > 1) return residue[i]; else return Grad{gy4[2 * c], gy4[2 * c + 1]}; };
     zero(acc);
     NCLK(3);
     if (second) kloop3<MTB, RW, XB, false>(acc, x_b, ring, wrow_aT, wrow_aT);
@@ -637,10 +649,9 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         lo.x += yb & 1u ? g0.x : 0.f; lo.y += yb & 2u ? g0.y : 0.f; lo.z += yb & 4u ? g0.z : 0.f; lo.w += yb & 8u ? g0.w : 0.f;
         hi.x += yb & 16u ? g1.x : 0.f; hi.y += yb & 32u ? g1.y : 0.f; hi.z += yb & 64u ? g1.z : 0.f; hi.w += yb & 128u ? g1.w : 0.f;
     };
-    const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
     if (!binary) {
         float* dst = route_mf(a, a.gdst0[node]);
-        through_lds([&](int c) { return Grad{gy4[2 * c], gy4[2 * c + 1]}; },
+        through_lds([&](int c, int i) { return grad(c, i); },
                     [&](int c, f32x4 lo, f32x4 hi, const Grad& g) {
                         residual(c, lo, hi, g.g0, g.g1);
                         store_piece(dst, c, lo, hi);
@@ -657,7 +668,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     {
         const u32x4* u4 = reinterpret_cast<const u32x4*>(a.sv_u + item_off);
         u32x4* sdc4 = reinterpret_cast<u32x4*>(a.sv_dc + item_off);
-        through_lds([&](int c) { return GradU{gy4[2 * c], gy4[2 * c + 1], u4[c]}; },
+        through_lds([&](int c, int i) { const Grad g = grad(c, i); return GradU{g.g0, g.g1, u4[c]}; },
                     [&](int c, f32x4 lo, f32x4 hi, const GradU& g) {
                         residual(c, lo, hi, g.g0, g.g1);
                         const uint32_t ub = piece_mask(g.u);
@@ -680,11 +691,11 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         zero(acc);
         kloop1<MTB, true>(acc, caddr, w1f, t1row + 8 * FRAG);
         float* d0 = route_mf(a, a.gdst0[node]);
-        through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d0, c, lo, hi); });
+        through_lds([](int, int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d0, c, lo, hi); });
         zero(acc);
         kloop1<MTB, false>(acc, caddr, w1f, nullptr);
         float* d1 = route_mf(a, a.gdst1[node]);
-        through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d1, c, lo, hi); });
+        through_lds([](int, int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d1, c, lo, hi); });
     }
 }
 
