@@ -366,6 +366,7 @@ struct BmArgs {
     const bf16_t* pk3aT;          //                   conv_a, taps flipped, channels exchanged
     const bf16_t* pk1T;           //                   conv1x1 halves, channels exchanged
     float* gy;                    // [n_items][P*C]
+    const float* dout;            // the gradient of a root's result, read where it is (null: it has been copied to gy)
     float* gleaf;                 // [n_leaves][P*C]
     const bf16_t* sv_u;           // [n_items][P*C] each; u and mid: in the forward pass's workspace
     const bf16_t* sv_m;
@@ -478,7 +479,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         for (int i = 0; i < 4; ++i) bits |= (bf16_lo_positive(w[i]) ? 1u : 0u) << (2 * i) | (bf16_hi_positive(w[i]) ? 1u : 0u) << (2 * i + 1);
         return bits;
     };
-    const float* gyp = a.gy + item_off;
+    const float* gyp = a.dout && it.dst < 0 ? a.dout + size_t(-1 - it.dst) * (P * C) : a.gy + item_off;
     const bf16_t* yp = it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C);
 
     // ---- g = gy * [y > 0] as bf16 into the tile, saved for dW_b and db_b; mask bytes of y and mid; all loads are
@@ -1161,8 +1162,10 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     pa.n_types = nt;
     hipLaunchKernelGGL(k_bwd_pack, dim3(unsigned(std::min<size_t>((size_t(nt) * 4 * 9 * 512 + 255) / 256, 4096)), p->has_binary ? 3 : 2), dim3(256), 0, st, pa);
 
+    // 16-byte aligned: roots read dout itself (the copy took 12 us for 256 examples)
     float* gy = reinterpret_cast<float*>(ws + L.gy);
-    launch_seed(p, dout, d_root_item, gy, chw, st);
+    const bool in_place = wide_maps(chw, dout);
+    if (!in_place) launch_seed(p, dout, d_root_item, gy, chw, st);
 
     const char* d = static_cast<const char*>(p->dev_buf);
     const dynb_item* d_items = reinterpret_cast<const dynb_item*>(d);
@@ -1170,7 +1173,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     a.feats = static_cast<const bf16_t*>(feats); a.out = static_cast<const bf16_t*>(out); a.slots = static_cast<const bf16_t*>(fwd_ws);
     a.pk3bT = reinterpret_cast<const bf16_t*>(ws + L.pk3bT); a.pk3aT = reinterpret_cast<const bf16_t*>(ws + L.pk3aT);
     a.pk1T = reinterpret_cast<const bf16_t*>(ws + L.pk1T);
-    a.gy = gy; a.gleaf = reinterpret_cast<float*>(ws + L.gleaf);
+    a.gy = gy; a.dout = in_place ? dout : nullptr; a.gleaf = reinterpret_cast<float*>(ws + L.gleaf);
     // u and mid of every item: where the forward pass of a DYNB_PLAN_KEEP plan put them
     a.sv_m = reinterpret_cast<const bf16_t*>(static_cast<const char*>(fwd_ws) + dynb_fast_keep_offset(p));
     a.sv_u = a.sv_m + n_items_all * chw;

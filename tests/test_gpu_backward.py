@@ -304,6 +304,28 @@ def test_parameter_gradients_over_chunks_of_items(dyn, util, oracle, ones, twos)
         assert (again[name] == got[name]).all(), name
 
 
+@pytest.mark.parametrize("B", [2, 40])
+def test_output_gradients_at_any_address(dyn, util, B):
+    """The fused shape reads dout where it is if it starts on 16 bytes, else a copy of it: the same bits."""
+    import torch
+    w = iep.small_mixed(seed=B, B=B, C=128, H=14, W=14, dtype="bf16", min_len=1, max_len=6)
+    dout = np.random.default_rng(B).standard_normal(w.feats.shape).astype(np.float32)
+    plan = dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, dyn.DYNB_PLAN_BALANCE | dyn.DYNB_PLAN_KEEP)
+    dyn.dynbatch_plan_upload(plan)
+    weights, feats = util.iep_weights_dev(w), util.to_dev(w.feats, w.dtype)
+    ws = torch.empty(dyn.dynbatch_workspace_bytes(plan, 128, 14, 14, dyn.DYNB_BF16), dtype=torch.uint8, device="cuda")
+    out = dyn.dynbatch_execute(plan, weights, feats, workspace=ws)
+    got = []
+    for shift in (0, 1):
+        buf = torch.empty(dout.size + shift, device="cuda")
+        d = buf[shift:].view(dout.shape)
+        d.copy_(torch.from_numpy(dout))
+        g = dyn.dynbatch_backward(plan, weights, feats, out, ws, d)
+        got.append({k: v.clone() for k, v in g.items()})
+    for name in NAMES:
+        assert torch.equal(got[0][name], got[1][name]), name
+
+
 def _sampled(w, seed):
     """dout that is zero outside a sample of the examples, and the sample as a workload of its own.  The backward
     pass is linear in dout and examples are independent, so every parameter gradient of the full batch equals that
