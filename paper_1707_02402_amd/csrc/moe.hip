@@ -1362,8 +1362,8 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // m5 grouped expert FFN: at most ceil(A/TM) + E row tiles exist
     const long long max_mtiles = (long long)(A + TM - 1) / TM + E;
     const int nt1 = (h + TN - 1) / TN, nt2 = (d + TN - 1) / TN;
+    const long long span = 8ll * XCD_CHUNK;                   // every XCD's longest run
     if (naive_stride <= 0) {
-        const long long span = 8ll * XCD_CHUNK;
         if (skinny1)
             hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(skinny_tiles * ((h + 63) / 64))), dim3(256), 0, st, xb,
                                static_cast<const bf16_t*>(W1), hid, tiles, h, d, (h + 63) / 64, perm, k);
@@ -1380,7 +1380,9 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                                hid, static_cast<const bf16_t*>(W2), y, offsets, tile_start, E, d, h, nt2, nullptr, 1);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else {
-        // the paper's naive version: loop over the k*b expert uses, one expert call (two layers) per use
+        // the paper's naive version: loop over the k*b expert uses, one expert call (two layers) per use; where the tiles are more than
+        // a run for every XCD, the runs are rounded up one by one, and the grid has to be whole runs
+        auto unit_grid = [&](int nt) { return dim3(unsigned(nt <= span ? (nt + 7) / 8 * 8 : (nt + span - 1) / span * span)); };
         std::vector<int32_t> off(size_t(E) + 1);
         int32_t* unit = lrank;                                // free again after k_place
         hipLaunchKernelGGL(k_unit_group, dim3(1), dim3(64), 0, st, unit);
@@ -1391,9 +1393,9 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         for (int e = 0; e < E; ++e)
             for (int pos = off[e]; pos < off[e + 1]; ++pos) {
                 if (pos % naive_stride) continue;
-                hipLaunchKernelGGL((k_grouped_gemm<true>), dim3((nt1 + 7) / 8 * 8), dim3(256), 0, st, xs + size_t(pos) * d,
+                hipLaunchKernelGGL((k_grouped_gemm<true>), unit_grid(nt1), dim3(256), 0, st, xs + size_t(pos) * d,
                                    w1 + size_t(e) * h * d, hid + size_t(pos) * h, unit, unit + 2, 1, h, d, nt1, nullptr, 1);
-                hipLaunchKernelGGL((k_grouped_gemm<false>), dim3((nt2 + 7) / 8 * 8), dim3(256), 0, st, hid + size_t(pos) * h,
+                hipLaunchKernelGGL((k_grouped_gemm<false>), unit_grid(nt2), dim3(256), 0, st, hid + size_t(pos) * h,
                                    w2 + size_t(e) * d * h, y + size_t(pos) * d, unit, unit + 2, 1, d, h, nt2, nullptr, 1);
             }
         if (timed) { dynb::timing_mark(st, dynb::ST_FFN1, 0); dynb::timing_mark(st, dynb::ST_FFN2, 0); }

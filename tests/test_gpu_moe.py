@@ -328,6 +328,25 @@ def test_naive_per_use_loop_equals_batched_layer(dyn, util):
         dyn.moe_forward(dev["x"], dev["Wg"], dev["Wn"], dev["noise"], dev["W1"], dev["W2"], m.k, naive_stride=-1)
 
 
+@pytest.mark.parametrize("h", [262144, 262408])
+def test_naive_loop_over_experts_of_many_features(dyn, util, h):
+    """1024 and 1026 feature tiles: one run of tiles for every XCD and two, the second one shorter.  The workspace is NaN before, so a
+    tile left out would show.  Hidden units are rounded alike; the second layer's fp32 sums over h in another order and a rounding to
+    bfloat16 (2^-9 of a value) differ."""
+    import ctypes as ct
+    import torch
+    from paper_1707_02402_amd import binding
+    g = torch.Generator().manual_seed(h)
+    rnd = lambda *shape: torch.randn(shape, generator=g).to(torch.bfloat16).cuda()
+    T, d, E = 3, 8, 2
+    x, Wg, W1, W2 = rnd(T, d), rnd(E, d), rnd(E, h, d), rnd(E, d, h)
+    shape = binding._MoeShape(T, d, h, E, 1, binding.DYNB_BF16, 0)
+    ws = torch.full((int(binding.lib.moe_workspace_bytes(ct.byref(shape))),), 255, dtype=torch.uint8, device="cuda")
+    a = dyn.moe_forward(x, Wg, None, None, W1, W2, 1)
+    b = dyn.moe_forward(x, Wg, None, None, W1, W2, 1, workspace=ws, naive_stride=1)
+    assert util.normwise(util.to_host(b), util.to_host(a)) < 1e-2
+
+
 def test_moe_error_paths(dyn, util):
     import torch
     m = moe.small(seed=1, T=16, d=32, h=32, E=4, k=2)
