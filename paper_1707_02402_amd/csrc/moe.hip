@@ -42,6 +42,7 @@ constexpr int NTW = TN / 64;      // 16-feature sub-tiles per wave (4 waves spli
 constexpr int MAX_K = 8;          // uses of a token whose places are kept in registers (more are looked up)
 constexpr int MG = 8;             // row tiles of one expert that walk the feature tiles together
 constexpr int XCD_CHUNK = 128;    // most consecutive grouped-GEMM tiles dealt to one XCD
+constexpr uint32_t XCD_CUS = 32;
 
 __device__ __forceinline__ bf16x8 ldg_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
@@ -1037,7 +1038,10 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(const bf16_t* __restrict__
     // its own L2), so the numbering is dealt to the XCDs in equal runs of at most XCD_CHUNK tiles:
     // everything that shares weights or activation rows stays behind one L2, and every XCD gets as many runs.
     const uint32_t total = uint32_t(tile_start[E]) * uint32_t(n_tiles_n);      // (below 2^31: check_shape bounds the grid; at least one tile)
-    const uint32_t runs = (total + 8 * XCD_CHUNK - 1) / (8 * XCD_CHUNK), chunk = (total + 8 * runs - 1) / (8 * runs);
+    const uint32_t runs = (total + 8 * XCD_CHUNK - 1) / (8 * XCD_CHUNK);
+    // (as few tiles as one XCD has CUs stay on one, behind whose L2 the next layer finds their rows: one token, layers of 768 x 64, 6 uses, 30.2
+    // us dealt to all, 28.4 so; 248 x 136, 8 uses, 26.4 / 25.5.  The per-use loop's small grids do not reach that far)
+    const uint32_t chunk = total <= XCD_CUS && gridDim.x >= 8 * XCD_CUS ? XCD_CUS : (total + 8 * runs - 1) / (8 * runs);
     const uint32_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     const uint32_t lin = (j / chunk * 8 + xcd) * chunk + j % chunk;
     if (j >= runs * chunk || lin >= total) return;
@@ -1326,16 +1330,16 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // k_grouped_gemm / k_grouped_skinny, features x summed channels, rounds: 256 x 2048, 0.1 30 / 15; 768 x 2048, 0.9 47 / 29; 256 x 1024,
     // 0.1 18 / 11, 0.6 20 / 14; 512 x 1024, 0.25 21 / 12; 256 x 512, 0.7 13.4 / 9.3; 240 x 432, 0.2 12 / 8.6; 128 x 216, 0.6 10.4 / 8.8; 512 x 512,
     // 1.4 16 / 24; 2048 x 512, 2.0 18 / 31; 1024 x 256, 1.4 10 / 20; 192 x 320, 1.2 15 / 23; 128 x 192, 0.6 10.3 / 14; 128 x 128, 0.5 7.5 / 10; full tiles:
-    // 128 x 1296, 0.1 24 / 17; 248 x 1024, 0.5 21 / 19.  (400 layers of up to 65536 uses: the rule takes 1.2 % longer than the better kernel
+    // 128 x 1296, 0.1 24 / 17; 248 x 1024, 0.5 21 / 19; a few workgroups of short sums pay for their start: one token, 160 x 184, 21.5 / 24.3 the pass.  (400 layers of up to 65536 uses: the rule takes 1.2 % longer than the better kernel
     // of each would, in the mean.  The lines drawn while k_grouped_gemm gave all of up to 128 tiles to one XCD took 10 %.)
     // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
     // each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
     const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
-    auto skinny_layer = [&](int N, int K) {                            // rounds <= (K - 128) / 600
+    auto skinny_layer = [&](int N, int K) {                            // rounds <= (K - 128) / 600, and not too little in all
         const long long groups = (long long)skinny_tiles * ((N + 63) / 64);
-        return (small || mid) && fused_permute && groups * 600 <= 768ll * (K - 128);
+        return (small || mid) && fused_permute && groups * 600 <= 768ll * (K - 128) && (K >= 224 || A >= 128 || groups * 5 >= 768);
     };
     const bool skinny1 = skinny_layer(h, d), skinny2 = skinny_layer(d, h), skinny = skinny1 || skinny2;
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
