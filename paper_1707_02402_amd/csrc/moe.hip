@@ -1324,22 +1324,33 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
     // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
-    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.  An expert
-    // layer of few tiles and long sums runs on k_grouped_skinny, each layer for itself: k_grouped_gemm pays 1.2 to 1.5 us for every 64 summed channels
-    // however few tiles there are, k_grouped_skinny some 11 us for every round of 768 workgroups (three a CU) whatever they sum.  us a layer,
-    // k_grouped_gemm / k_grouped_skinny, features x summed channels, rounds: 256 x 2048, 0.1 30 / 15; 768 x 2048, 0.9 47 / 29; 256 x 1024,
-    // 0.1 18 / 11, 0.6 20 / 14; 512 x 1024, 0.25 21 / 12; 256 x 512, 0.7 13.4 / 9.3; 240 x 432, 0.2 12 / 8.6; 128 x 216, 0.6 10.4 / 8.8; 512 x 512,
-    // 1.4 16 / 24; 2048 x 512, 2.0 18 / 31; 1024 x 256, 1.4 10 / 20; 192 x 320, 1.2 15 / 23; 128 x 192, 0.6 10.3 / 14; 128 x 128, 0.5 7.5 / 10; full tiles:
-    // 128 x 1296, 0.1 24 / 17; 248 x 1024, 0.5 21 / 19; a few workgroups of short sums pay for their start: one token, 160 x 184, 21.5 / 24.3 the pass.  (400 layers of up to 65536 uses: the rule takes 1.2 % longer than the better kernel
-    // of each would, in the mean.  The lines drawn while k_grouped_gemm gave all of up to 128 tiles to one XCD took 10 %.)
+    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.
+    // An expert layer of few tiles and long sums runs on k_grouped_skinny, each layer for itself.  k_grouped_gemm pays 1.2 to 1.5 us for
+    // every 64 summed channels however few tiles there are.  k_grouped_skinny reads an expert's weights once per row tile, and where a tile
+    // has many rows, every wave multiplies up to four fragments of them with each of the weights.  us, k_grouped_gemm / k_grouped_skinny, by
+    // features x summed channels and rounds of 768 workgroups (three a CU):
+    //   a layer of few rows a tile: 256 x 2048 0.1: 30 / 15;  768 x 2048 0.9: 47 / 29;  256 x 1024 0.1: 18 / 11, 0.6: 20 / 14;
+    //     512 x 1024 0.25: 21 / 12;  256 x 512 0.7: 13.4 / 9.3;  240 x 432 0.2: 12 / 8.6;  128 x 216 0.6: 10.4 / 8.8;  512 x 512 1.4: 16 / 24;
+    //     2048 x 512 2.0: 18 / 31;  1024 x 256 1.4: 10 / 20;  192 x 320 1.2: 15 / 23;  128 x 192 0.6: 10.3 / 14;  128 x 128 0.5: 7.5 / 10
+    //   a layer of few uses, 20 to 45 rows a tile: 1728 x 128 0.2: 6.4 / 4.8;  256 x 200 0.15: 7.8 / 5.2;  528 x 200 0.15: 8.0 / 4.2
+    //   the whole pass, 43 to 64 rows a tile: 512 x 2048 0.4: 69 / 62, 2.75: 160 / 200;  1024 x 4096 0.5: 133 / 103, 0.75: 122 / 124, 1.5: 171 / 197;
+    //     512 x 1024 0.75: 55 / 58;  1024 x 2048 1.5: 103 / 116, 2.8: 154 / 187;  1024 x 8192 21: 3076 / 4253
+    //   one token, 160 x 184: 21.5 / 24.3 the pass (a few workgroups of short sums pay for their start)
+    // (4646 passes of 64 to 2048 x 64 to 4096 channels and up to 65536 uses take 1.3 % longer than with the better kernel for each layer, in the
+    // mean, and 26 % at worst; with the first limit alone, whatever the rows, 1.8 and 90 %.)
     // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
     // each like the smallest token).
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
     const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
-    auto skinny_layer = [&](int N, int K) {                            // rounds <= (K - 128) / 600, and not too little in all
-        const long long groups = (long long)skinny_tiles * ((N + 63) / 64);
-        return (small || mid) && fused_permute && groups * 600 <= 768ll * (K - 128) && (K >= 224 || A >= 128 || groups * 5 >= 768);
+    auto skinny_layer = [&](int N, int K) {
+        const long long groups = (long long)skinny_tiles * ((N + 63) / 64), rows16 = A / (16ll * skinny_tiles);
+        if (!(small || mid) || !fused_permute) return false;
+        // few uses, 16 rows a tile and more: 0.1 to 0.25 rounds also of short sums
+        if (small && rows16 >= 1 && K >= 96 && groups * 10 >= 768 && groups * 4 <= 768) return true;
+        // rounds <= (K - 128) / 600 and 3; from 32 rows a tile 0.3 (few uses: 0.4), with long sums (K - 128) / 2560, at most 0.8
+        const long long most = rows16 < 2 ? 3 * 768 : std::max(small ? 307ll : 230ll, std::min(614ll, (K - 128) * 3ll / 10));
+        return groups * 600 <= 768ll * (K - 128) && groups <= most && (K >= 224 || A >= 128 || groups * 5 >= 768);
     };
     const bool skinny1 = skinny_layer(h, d), skinny2 = skinny_layer(d, h), skinny = skinny1 || skinny2;
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;

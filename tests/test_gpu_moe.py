@@ -282,7 +282,7 @@ def test_config4_targeted_tokens_with_empty_experts(dyn, util, oracle):
                                              (64, 1000, 520, 64, 8, True), (128, 64, 96, 64, 8, True), (129, 64, 64, 64, 8, False), (100, 64, 72, 4097, 2, True),
                                              (300, 48, 104, 40, 2, True), (700, 264, 520, 33, 2, True), (900, 1100 // 8 * 8, 64, 9, 3, False),
                                              (1200, 64, 16, 256, 1, True), (1201, 72, 16, 256, 1, False), (300, 64, 1024, 200, 2, False),
-                                             (300, 1024, 64, 200, 2, False)])
+                                             (300, 1024, 64, 200, 2, False), (173, 384, 192, 5, 5, True), (160, 768, 96, 4, 2, False)])
 def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
     """The kernels for a few tokens, at the edges of their tiles (16 tokens, experts, features; 32 summed channels; rows of an
     expert up to and over 16, 32 and 64; blocks of 1024, 512 and 256 summed channels) and of their range (1200 gate tiles, 1024
@@ -297,6 +297,29 @@ def test_few_uses(dyn, util, oracle, T, d, h, E, k, noise):
         assert (getattr(r, name) == aux[name]).all(), name
     ref = oracle.moe_experts(m.x, r.topk_idx, r.topk_w, W1, W2)
     assert per_token_errors(out, ref).max() < OUT_TOL
+
+
+@pytest.mark.parametrize("T,d,h,E,k", [(4096, 1024, 2048, 8, 2), (8192, 512, 2048, 8, 2)])
+def test_layers_of_full_tiles_keep_the_kernel_with_the_large_tiles(dyn, T, d, h, E, k):
+    """The second layer has 2.8 rounds of workgroups of the kernel with the small tiles, whose row tiles each stream the weights for themselves:
+    1.22 and 1.25 times the pass with the large tiles, which MOE_SEPARATE_PERMUTE always takes (and a launch more)."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(T)
+    rnd = lambda *shape: (torch.randn(shape, generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+    args = (rnd(T, d), rnd(E, d), None, None, rnd(E, h, d), rnd(E, d, h), k)
+    ws, out = torch.empty(dyn.moe_workspace_bytes(T, d, h, E, k), dtype=torch.uint8, device="cuda"), torch.empty_like(args[0])
+
+    def ms(flags):
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        start.record()
+        for _ in range(20):
+            dyn.moe_forward(*args, out=out, workspace=ws, flags=flags)
+        end.record()
+        end.synchronize()
+        return start.elapsed_time(end)
+
+    times = [(ms(0), ms(dyn.MOE_SEPARATE_PERMUTE)) for _ in range(7)][1:]
+    assert min(t[0] for t in times) < 1.1 * min(t[1] for t in times), times
 
 
 @pytest.mark.parametrize("T,E,k", [(1025, 7, 1), (1024, 4096, 2), (513, 300, 2), (8192, 40, 8), (8200, 33, 8), (600, 4097, 2), (2560, 4096, 8), (2561, 4096, 8)])
