@@ -201,13 +201,17 @@ __global__ __launch_bounds__(256) void k_head_finish_slices(const float* __restr
     }
 }
 
-// The last layer and the softmax of one example per workgroup: a wave takes every fourth (SLICES: sixteenth) answer, its lanes the hidden units.
+// The last layer and the softmax of one example per workgroup: a wave takes every fourth (few examples: sixteenth) answer, its lanes the hidden units.
 // (As a product, a sum of slices and a softmax they were three launches, 12 us for one example.)
 // SLICES: the hidden units themselves are still partial sums of n_slices slices, part[slice][example][unit]; they are added up here as
 // k_head_finish_slices does it, four threads a unit, each all of its slices in one trip to memory: one launch less, 2.4 us
-// of one program's 178, 3 of 23 programs' 287.
+// of one program's 178, 3 of 23 programs' 287.  An example's partial sums all pass through one CU, so there are HEAD_PARTS of them at most;
+// where there are more they get their launch, and the last layer its sixteen waves.  us a pass by hidden units x slices (bf16, 28 answers):
+// that launch and four waves / all in one / this: 256 x 64 16.5 / 14.8 / 14.8; 512 x 16 29.3 / 25.0 / 25.0, x 64 17.5 / 20.4 / 14.9; 1024 x 25
+// 19.1 / 22.0 / 15.5, x 32 20.4 / 21.8 / 16.6; 2048 x 13 21.8 / 23.7 / 16.2.
 constexpr int HEAD_ANSWERS = 64;                   // logits kept in LDS
-constexpr int HEAD_UNITS = 2048;                   // hidden units kept in LDS (SLICES)
+constexpr int HEAD_PARTS = 16384;
+constexpr int HEAD_UNITS = HEAD_PARTS / FINISH_SLICES;      // hidden units kept in LDS (SLICES)
 struct AnswerArgs {
     const void* h1;                                // [B][F]
     const float* part;                             // SLICES
@@ -218,10 +222,10 @@ struct AnswerArgs {
     float* probs;
     int B, F, A, n_slices;
 };
-template <typename T, bool SLICES>
-__global__ __launch_bounds__(SLICES ? 1024 : 256) void k_head_answers(AnswerArgs g)
+template <typename T, bool SLICES, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_head_answers(AnswerArgs g)
 {
-    constexpr int WAVES = SLICES ? 16 : 4;
+    static_assert(!SLICES || WAVES == 16, "four threads for each of 256 units");
     __shared__ float row[HEAD_ANSWERS];
     __shared__ float unit[SLICES ? HEAD_UNITS : 1], sum[SLICES ? 4 : 1][SLICES ? 256 : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, F = g.F, A = g.A;
@@ -338,10 +342,10 @@ int check_head(const dynb_head_shape* s, int32_t B, const char* who)
     return DYNB_OK;
 }
 
-// keep: the sum of FINISH_SLICES slices and more is left to the caller; returns their number then, else 0
+// keep: the sum of FINISH_SLICES slices and more, of up to `keep` partial sums a row, is left to the caller; returns their number then, else 0
 template <typename TO, bool RELU>
 int launch_layer(int dtype, const void* a, const void* w, const float* bias, TO* out, float* part, int M, int N, int K,
-                 int splits, hipStream_t st, bool keep = false)
+                 int splits, hipStream_t st, int keep = 0)
 {
     GemmArgs g{a, w, part, M, N, K, 0, nullptr, nullptr};
     if (splits == 1 && RELU) { g.out = out; g.bias = bias; }
@@ -354,7 +358,7 @@ int launch_layer(int dtype, const void* a, const void* w, const float* bias, TO*
     if (g.out) return 0;
     const size_t MN = size_t(M) * N;
     const int n_slices = int(grid.z);
-    if (keep && n_slices >= FINISH_SLICES) return n_slices;
+    if (n_slices >= FINISH_SLICES && (long long)n_slices * N <= keep) return n_slices;
     if (n_slices >= FINISH_SLICES)
         hipLaunchKernelGGL((k_head_finish_slices<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 63) / 64, 4096))), dim3(256), 0, st, part, bias, out, MN, N, n_slices);
     else
@@ -372,10 +376,11 @@ void launch_head(const dynb_head_shape* s, const dynb_head_weights* w, const Hea
     T* h1 = reinterpret_cast<T*>(ws + L.h1);
     float* part = reinterpret_cast<float*>(ws + L.part);
     launch_layer<T, true>(s->dtype, roots, w->wc, w->bc, z, part, B * P, s->Cc, s->C, L.s1, st);
-    const int slices = launch_layer<T, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, P * s->Cc, L.s2, st, answers && s->F <= HEAD_UNITS);
+    const int slices = launch_layer<T, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, P * s->Cc, L.s2, st, answers ? HEAD_PARTS : 0);
     const AnswerArgs g = {h1, part, w->bf1, w->wf2, w->bf2, logits, probs, B, s->F, s->n_answers, slices};
-    if (slices > 0) hipLaunchKernelGGL((k_head_answers<T, true>), dim3(unsigned(B)), dim3(1024), 0, st, g);
-    else if (answers) hipLaunchKernelGGL((k_head_answers<T, false>), dim3(unsigned(B)), dim3(256), 0, st, g);
+    if (slices > 0) hipLaunchKernelGGL((k_head_answers<T, true, 16>), dim3(unsigned(B)), dim3(1024), 0, st, g);
+    else if (answers && L.s2 >= FINISH_SLICES) hipLaunchKernelGGL((k_head_answers<T, false, 16>), dim3(unsigned(B)), dim3(1024), 0, st, g);
+    else if (answers) hipLaunchKernelGGL((k_head_answers<T, false, 4>), dim3(unsigned(B)), dim3(256), 0, st, g);
     else launch_layer<float, false>(s->dtype, h1, w->wf2, w->bf2, logits, part, B, s->n_answers, s->F, L.s3, st);
 }
 
