@@ -159,8 +159,9 @@ typedef struct {
     const int32_t* wg_units;     /* [n_wg_units][8]: mode (0 second conv3x3, 1 first conv3x3, 2 conv1x1),
                                     function, part (kernel row, or argument for mode 2), begin, end (a chunk
                                     fn_items[begin .. end) of at most 16 items), 3 unused            */
-    const int32_t* wg_order;     /* [n_wg_units] the units, longest chunks first: the order in which that kernel's
-                                    workgroups take the chunks                                     */
+    const int32_t* wg_order;     /* [n_wg_units] the units, in the order in which that kernel's workgroups take their
+                                    chunks: modes 0 and 1 before mode 2, of either the longest first; eight chunks
+                                    at a time, part by part                                        */
 } dynb_plan_view;
 
 /* Builds the plan for a minibatch of programs (Background / Visual Reasoning Programs: the fixed

@@ -721,11 +721,11 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
 struct WgArgs {
     const dynb_item* items;       // all items of the plan
     const dynb_wg_unit* units;
-    const int32_t* order;         // the units, longest chunks first
+    const int32_t* order;         // the units, longest chunks first (planner.cpp)
     const int32_t* fn_first;
     const int32_t* fn_items;
     int32_t n_chunks;             // chunks of the 3x3s: three units each
-    int32_t n_joins;              // units of the 1x1, behind the others
+    int32_t n_joins;              // units of the 1x1, behind the others in the order
     const bf16_t* feats;
     const bf16_t* slots;
     const bf16_t* sv_u;
@@ -920,7 +920,7 @@ __global__ __launch_bounds__(256, 2) void k_bwd_wgrad_mfma(WgArgs a)
     } else {
         const int j = (set - conv_sets) * 8 + x;
         if (j >= a.n_joins) return;
-        const int32_t u = 3 * a.n_chunks + j;
+        const int32_t u = a.order[3 * a.n_chunks + j];
         const dynb_wg_unit un = a.units[u];
         wgrad_chunk<false>(a, un, u, chunks_of(un.type), quad);
     }

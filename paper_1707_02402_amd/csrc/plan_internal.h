@@ -68,7 +68,7 @@ struct dynb_plan {
     // the units fill the chip evenly; a unit sums one chunk for one (convolution, kernel row or argument).
     std::vector<dynb_wg_unit> wg_units;  // grouped: the chunks of one (mode, function, part) are consecutive
     std::vector<dynb_wg_group> wg_groups;
-    std::vector<int32_t> wg_order;       // unit indices, longest chunks first: the order in which workgroups take them
+    std::vector<int32_t> wg_order;       // unit indices by chunks: the 3x3s', then the 1x1s', longest first (what the kernel reads of it: planner.cpp)
     std::vector<char> image;             // host image of the device buffer, filled by dynbatch_plan_upload
     void* dev_buf = nullptr;             // set by dynbatch_plan_upload
     size_t dev_bytes = 0;

@@ -372,9 +372,9 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
                     p->wg_groups.push_back(g);                     // a function without items has no units: its gradient is zero
                 }
             }
-        // Order in which workgroups take the units: chunks with the most items first (a short tail), the 3x3s' before the 1x1s', eight chunks
-        // at a time, first the first parts of the eight, then the second ones.  (A workgroup finds a chunk's first part there, and its kernel
-        // rows' units from that.  Chunks of equal length instead of 16 and a rest: no difference.)
+        // Order in which workgroups take the chunks: the 3x3s' before the 1x1s', of either those with the most items first (a short tail), eight at a
+        // time, first the first parts of the eight, then the second ones.  (A workgroup of a 3x3 finds a chunk's first part there, and its kernel
+        // rows' units from that; of a 1x1 the unit itself.  Chunks of equal length instead of 16 and a rest: no difference.)
         struct Chunk { int32_t first_group, n_parts, chunk, work; };
         std::vector<Chunk> chunks;
         for (size_t gi = 0; gi < p->wg_groups.size();) {
@@ -390,11 +390,12 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
             return a.n_parts != b.n_parts ? a.n_parts > b.n_parts : a.work > b.work;
         });
         p->wg_order.clear();
-        for (size_t b0 = 0; b0 < chunks.size(); b0 += 8)
-            for (int32_t part = 0; part < 3; ++part)
-                for (size_t x = b0; x < std::min(chunks.size(), b0 + 8); ++x)
-                    if (part < chunks[x].n_parts)
-                        p->wg_order.push_back(p->wg_groups[size_t(chunks[x].first_group) + part].first_unit + chunks[x].chunk);
+        for (size_t b0 = 0, b1; b0 < chunks.size(); b0 = b1) {
+            for (b1 = b0; b1 < std::min(chunks.size(), b0 + 8) && chunks[b1].n_parts == chunks[b0].n_parts;) ++b1;
+            for (int32_t part = 0; part < chunks[b0].n_parts; ++part)
+                for (size_t x = b0; x < b1; ++x)
+                    p->wg_order.push_back(p->wg_groups[size_t(chunks[x].first_group) + part].first_unit + chunks[x].chunk);
+        }
     }
     // 4. units of work of the dependency-driven launch, in claim order = execution order of the items
     // (arguments always come earlier in it).  Groups that leave half of the chip idle are run with two

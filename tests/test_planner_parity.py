@@ -305,17 +305,37 @@ def test_backward_tables_of_a_keep_plan(dyn):
                 if chunks:
                     assert chunks[0][0] == v.fn_first[t] and chunks[-1][1] == v.fn_first[t + 1]
                     assert all(a[1] == b[0] for a, b in zip(chunks, chunks[1:]))
-    # the parts of one chunk are taken by workgroups 8 apart (they run on one die at the same time)
-    pos = np.empty(v.n_wg_units, np.int64)
-    pos[v.wg_order] = np.arange(v.n_wg_units)
-    key = {tuple(u[[0, 1, 3]]): {} for u in v.wg_units}
-    for i, u in enumerate(v.wg_units):
-        key[tuple(u[[0, 1, 3]])][u[2]] = pos[i]
-    apart = [p[1] - p[0] for p in key.values()]
-    assert np.mean(np.array(apart) == 8) > 0.95
     # without the flag there are no such tables
     v0 = dyn.dynbatch_plan_view(dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, dyn.DYNB_PLAN_BALANCE))
     assert v0.n_wg_units == 0 and len(v0.fn_items) == 0 and len(v0.grad_dst0) == 0
+
+
+@pytest.mark.parametrize("B", [1, 3, 20, 64, 256, 700])
+def test_order_of_the_parameter_gradients_chunks(dyn, B):
+    """What the parameter-gradient kernel takes from wg_order: of every set of eight 3x3 chunks the first parts (the units of the other kernel rows lie as
+    many units further as the function has chunks), then every unit of the 1x1s, a set of eight chunks' first arguments and second ones; longest first."""
+    w = iep.config2(B=B)
+    v = dyn.dynbatch_plan_view(dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, dyn.DYNB_PLAN_BALANCE | dyn.DYNB_PLAN_KEEP))
+    units, order = v.wg_units, v.wg_order
+    items = units[:, 4] - units[:, 3]
+    n = int((units[:, 0] != 2).sum()) // 3                    # 3x3 chunks; their units come first, function by function, part by part
+    joins = v.n_wg_units - 3 * n
+    assert (units[:3 * n, 0] != 2).all() and (units[3 * n:, 0] == 2).all()
+    first = [int(order[i // 8 * 24 + i % 8]) for i in range(n)]
+    assert len(set(first)) == n and (units[first, 2] == 0).all() and (units[first, 0] != 2).all()
+    assert (np.diff(items[first]) <= 0).all()
+    for u in first:
+        mode, t, _, b, e = units[u, :5]
+        chunks = -(-(v.fn_first[t + 1] - v.fn_first[t]) // 16)
+        for part in (1, 2):
+            assert tuple(units[u + part * chunks, :5]) == (mode, t, part, b, e)
+    taken = order[3 * n:]
+    assert sorted(taken) == list(range(3 * n, v.n_wg_units)) and joins % 2 == 0
+    for x in range(0, joins, 16):
+        m = min(8, (joins - x) // 2)
+        one, two = units[taken[x:x + m]], units[taken[x + m:x + 2 * m]]
+        assert (one[:, 2] == 0).all() and (two[:, 2] == 1).all() and (one[:, [0, 1, 3, 4]] == two[:, [0, 1, 3, 4]]).all()
+    assert (np.diff(items[taken][units[taken, 2] == 0]) <= 0).all()
 
 
 @pytest.mark.parametrize("dtype,elt", [("f32", 4), ("bf16", 2)])
