@@ -45,7 +45,7 @@ namespace {
 //     D[32 co][32 ci] += G[32 co][2 pixels] * IN[2 pixels][32 ci]     (v_mfma_f32_32x32x2: fp32 products and sums)
 // Second 3x3: G = g, IN = mid; first 3x3: G = dmid, IN = u; JOIN: the 1x1 (G = dc, IN = the arguments).  The functions with the most items come
 // first, of both 3x3s: a workgroup takes some 14 us an item beside another on its CU, and the last
-// ones should be short (21 programs, fp32, C = 128, 14 x 14: a training step 2774 us with the functions in order, 2697 so).
+// ones should be short (fp32, C = 128, 14 x 14: a training step of 21 programs 2685 us with the functions in order, 2633 so; of 8 programs 1435 / 1387).
 // An item's 32 + 32 channels are staged into LDS as fp32, pixel-major without padding (a fragment, two pixels x 32
 // channels, is then 64 consecutive words), the input with its halo; a step of two pixels reads 1 + TAPS fragments
 // for TAPS MFMAs of 64 clocks.  The waves split an item's pixels and meet in LDS at the end, in wave order.  Maps that do
@@ -1141,8 +1141,8 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     const int32_t* d_leaf_first = reinterpret_cast<const int32_t*>(pd + KT.leaf_first);
     const int32_t* d_root_item = reinterpret_cast<const int32_t*>(pd + KT.root_item);
 
-    // (the parameter gradients of every function are written by k_bwd_wgrad_sum, zeros included; without a
-    // two-argument function in the batch there is no conv1x1 gradient to sum)
+    // (every function's parameter gradients are written below, by k_bwd_wgrad_mfma where they are one chunk's sum, else, and zeros
+    // too, by k_bwd_wgrad_sum; without a two-argument function in the batch there is no conv1x1 gradient to sum)
     if (!p->has_binary) {
         auto fill = [&](float* ptr, size_t n) {
             if (ptr && n) hipLaunchKernelGGL(k_bwd_fill, dim3(unsigned(std::min<size_t>((n + 255) / 256, 4096))), dim3(256), 0, st, ptr, n, 0.f);
@@ -1151,7 +1151,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         fill(g->db1, size_t(nt) * C);
     }
 
-    // weights in fragment order, as given and transposed
+    // transposed weights in fragment order
     PackArgs pa = {};
     const void* const src[3] = {w->w3a, w->w3b, w->w1};
     const size_t at[3] = {L.pk3aT, L.pk3bT, L.pk1T};
@@ -1162,7 +1162,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     pa.n_types = nt;
     hipLaunchKernelGGL(k_bwd_pack, dim3(unsigned(std::min<size_t>((size_t(nt) * 4 * 9 * 512 + 255) / 256, 4096)), p->has_binary ? 3 : 2), dim3(256), 0, st, pa);
 
-    // 16-byte aligned: roots read dout itself (the copy took 12 us for 256 examples)
+    // 16-byte aligned: roots read dout itself (the copy took 12 us for 256 examples; a training step 2507 -> 2491, of 16 examples 738 -> 730)
     float* gy = reinterpret_cast<float*>(ws + L.gy);
     const bool in_place = wide_maps(chw, dout);
     if (!in_place) launch_seed(p, dout, d_root_item, gy, chw, st);

@@ -683,7 +683,7 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         if (!p->keep) {
             a.items = reinterpret_cast<const dynb_item*>(d);
             a.count = int32_t(p->items.size());
-            const int resident = cu_count[dev & 63];          // one workgroup per CU (73 KB of LDS, all registers)
+            const int resident = cu_count[dev & 63];          // one workgroup per CU (78 KB of LDS, all registers)
             const unsigned grid = unsigned(std::min<int>(q.n_tickets, resident));
             hipLaunchKernelGGL(k_module_persist, dim3(grid), dim3(256), mf::LDS_BYTES, st, a, q);
             if (timed) dynb::timing_mark(st, 0, a.count);

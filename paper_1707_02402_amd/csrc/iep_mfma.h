@@ -17,7 +17,8 @@ constexpr int PIX_BYTES = 272;           // 128 channels bf16 + 16 bytes pad: 17
 // A row is 304 granules of 16 bytes apart from the next, a multiple of the banks: pixel (y, x) sits at granule x (mod 16), and the lanes
 // that an LDS pass takes from the two image rows of a fragment (four consecutive ones of either, shifted against each other) meet
 // distinct banks.  (17 pixels, 289 granules, put the second row one granule further: a conflict in every pass, 0.45 of the LDS
-// cycles.  With 304 the counters say 0.014.  The MFMAs above them hide most of it: 1000 programs 1924 -> 1911 us, 256 programs 621 -> 618.)
+// cycles.  With 304 the counters say 0.014.  The MFMAs above them hide most of it: with zero_border below, which came with it, 1000 programs
+// 2127 -> 2110 us, 256 programs 721 -> 716, 23 programs 285 -> 277.)
 // Of a row 14 pixels are the map's; the pixel before and all behind are zeros, which is what the two padding columns
 // of a pixel tile (below) read, whatever the tap.  (Zeros and not the last pixel again: the chip is at its power limit in
 // these kernels, and the matrix pipes take less of it for zeros: builds that run the K loop alone, on all CUs, reach 1.62 instead
@@ -230,7 +231,7 @@ template <> struct PartShape<7> { static constexpr int ROWS = 2, MTA = 2, MTB = 
 // Workgroups per node of a launch group of `count` nodes: as many as still fit the chip's 256 CUs in one round.  14 and 28: 7 parts whose
 // second conv is shared by 2 or 4 workgroups, 64 or 32 output channels each (SPLIT): what a part waits for are weights, 295 KB a conv at some
 // 30 bytes a clock, and of the second conv each then reads a half or a quarter.  (The first conv's channels are all needed by every
-// one.)  us a program's pass, 7 parts / shared: one program 204 / 182, three 258 / 230; 5 training programs 765 / 725.  (Requesting the first conv's weights
+// one.)  us a pass, 7 parts / shared: one program 193 / 170, three 230 / 205; 5 training programs 660 / 631.  (Requesting the first conv's weights
 // into the die's L2 while the argument is on its way, a share per workgroup: 3-5 % slower.)
 inline int parts_for(int count) { return count > 128 ? 1 : count > 64 ? 2 : count > 36 ? 4 : count > 18 ? 7 : count > 9 ? 14 : 28; }
 

@@ -1266,9 +1266,13 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // m1 gate
     // whole tiles of 256 tokens go to k_gate_big where the expert and model widths allow it and there are enough tiles (a workgroup of
     // it has a CU for itself, and takes as long however few there are), the tokens behind the last whole tile (and every other shape)
-    // to k_gate.  us, k_gate_big / k_gate by tiles and d; noisy: 32 x 512 22 / 13, 64 x 1024 31 / 22, 128 x 256 18.8 / 16.3, 128 x 512 23 / 22,
-    // 128 x 1024 32.5 / 33.7, 256 x 1024 43 / 62; without noise: 32 x 512 12.4 / 11.3, 64 x 512 13.2 / 12.8, 64 x 1024 18.4 / 18.5, 96 x 512
-    // 14.0 / 15.4, 128 x 256 12.1 / 13.3, 128 x 1024 20 / 27; 500 tokens, d 1024, 256 experts (2 tiles and a rest; k_gate_small): 45 / 11.
+    // to k_gate.  us, k_gate_big / k_gate by tiles and d:
+    //   noisy: 32 x 512 22 / 13, 64 x 1024 31 / 22, 128 x 256 18.8 / 16.3, 128 x 512 23 / 22, 128 x 1024 32.5 / 33.7, 256 x 1024 43 / 62
+    //   without noise: 32 x 512 12.4 / 11.3, 64 x 512 13.2 / 12.8, 64 x 1024 18.4 / 18.5, 96 x 512 14.0 / 15.4, 128 x 256 12.1 / 13.3, 128 x 1024
+    //   20 / 27; 500 tokens, d 1024, 256 experts (2 tiles and a rest; k_gate_small): 45 / 11
+    // The whole pass, noisy: 96 x 2048 143 / 140, 128 x 2048 142 / 150, 96 x 4096 249 / 249, 256 x 256 74 / 76; without noise: 16 x 4096 117 / 116,
+    // 32 x 2048 77 / 77, 32 x 4096 134 / 139, 64 x 2048 102 / 105.  (Of 120 shapes of 8 to 512 tiles, d 256 to 4096, three go to the slower one by more
+    // than 3 % of the pass, all without noise and by 2.8 us at most: 128 x 256 twice and 64 x 1024 in 4 x 16 tiles.)
     const size_t big_tiles = size_t(T / GB_TOK) * size_t(E / GB_EXP);
     const bool many_tiles = noise ? big_tiles * (size_t(d) + 5120) >= 128 * 6144 : big_tiles * (size_t(d) + 1280) >= 64 * 2304;
     const int T_big = (many_tiles && E % GB_EXP == 0 && d % GKC == 0 && d >= 4 * GKC && size_t(GB_TOK) * size_t(std::max(E, d)) < (size_t(1) << 30))

@@ -326,6 +326,26 @@ def test_output_gradients_at_any_address(dyn, util, B):
         assert torch.equal(got[0][name], got[1][name]), name
 
 
+@pytest.mark.parametrize("B", [2, 40])
+def test_gradients_at_any_address(dyn, util, B):
+    """Gradient tensors that start on 4 bytes: functions of one chunk of items (their sums are written where they are taken), of several
+    and of none.  The same bits as on 256 bytes, and nothing before or behind them."""
+    import torch
+    w = iep.small_mixed(seed=B, B=B, C=128, H=14, W=14, dtype="bf16", min_len=1, max_len=6)
+    plan = dyn.dynbatch_plan(w.prog, w.prog_off, w.arity, dyn.DYNB_PLAN_BALANCE | dyn.DYNB_PLAN_KEEP)
+    dyn.dynbatch_plan_upload(plan)
+    weights, feats = util.iep_weights_dev(w), util.to_dev(w.feats, w.dtype)
+    ws = torch.empty(dyn.dynbatch_workspace_bytes(plan, 128, 14, 14, dyn.DYNB_BF16), dtype=torch.uint8, device="cuda")
+    out = dyn.dynbatch_execute(plan, weights, feats, workspace=ws)
+    dout = torch.from_numpy(np.random.default_rng(B).standard_normal(w.feats.shape).astype(np.float32)).cuda()
+    ref = dyn.dynbatch_backward(plan, weights, feats, out, ws, dout)
+    bufs = {k: torch.full((v.numel() + 8,), -7.0, device="cuda") for k, v in ref.items()}
+    got = dyn.dynbatch_backward(plan, weights, feats, out, ws, dout, grads={k: bufs[k][1:1 + v.numel()].view(v.shape) for k, v in ref.items()})
+    for name in NAMES:
+        assert torch.equal(got[name], ref[name]), name
+        assert bufs[name][0] == -7 and (bufs[name][-7:] == -7).all(), name
+
+
 def _sampled(w, seed):
     """dout that is zero outside a sample of the examples, and the sample as a workload of its own.  The backward
     pass is linear in dout and examples are independent, so every parameter gradient of the full batch equals that

@@ -132,16 +132,15 @@ def test_noiseless_gate_and_ties(dyn, util, oracle):
     assert util.normwise(out, oracle.moe_experts(m.x, r.topk_idx, r.topk_w, W1, W2)) < OUT_TOL
 
 
-@pytest.mark.parametrize("T,d,h,E,k", [(256, 256, 32, 128, 2),      # one tile, the shortest K loop the wide kernel takes
+@pytest.mark.parametrize("T,d,h,E,k", [(256, 256, 32, 128, 2),      # one tile
                                         (512, 320, 32, 256, 4),      # 2 x 2 tiles, an odd number of K-chunks
-                                        (768, 1024, 32, 384, 8),     # 3 x 3 tiles: dies without a token tile
-                                        (2304, 256, 32, 128, 1),     # 9 token tiles: two for the first die
-                                        (700, 256, 32, 128, 2)])     # two whole token tiles, 188 tokens for the 64 x 64 tiles
+                                        (768, 1024, 32, 384, 8),     # 3 x 3 tiles
+                                        (2304, 256, 32, 128, 1),     # 9 token tiles
+                                        (700, 256, 32, 128, 2)])     # two whole token tiles and 188 tokens
 @pytest.mark.parametrize("noisy", [True, False])
 def test_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
-    """Whole 256-token x 128-expert tiles go to the wide gate kernel (tokens behind the last whole tile, and every
-    other shape in this file, to the 64 x 64 one): every logit against the oracle, with and without the noise term, routing on the GPU's logits;
-    duplicated gate columns tie exactly and the lower id wins."""
+    """Whole 256-token x 128-expert tiles, so few of them that the 16 x 16 gate kernel takes them (more: below): every logit against the
+    oracle, with and without the noise term, routing on the GPU's logits; duplicated gate columns tie exactly and the lower id wins."""
     m = moe.small(seed=T + E + d, T=T, d=d, h=h, E=E, k=k)
     if not noisy:
         m.Wg[:, 64:128] = m.Wg[:, :64]           # expert e and e+64: same tile, the other expert half of a workgroup
@@ -160,10 +159,12 @@ def test_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
 
 @pytest.mark.parametrize("T,d,h,E,k", [(3333, 256, 32, 1536, 2),     # 13 x 12 tiles and 5 tokens more, the shortest K loop
                                         (1801, 320, 32, 3072, 2),     # 7 x 24 tiles and 9 tokens, an odd number of K-chunks
-                                        (2048, 1024, 8, 2048, 1)])    # 8 x 16 tiles, as few as the wide kernel gets at this width
+                                        (2048, 1024, 8, 2048, 1),     # 8 x 16 tiles, as few as the wide kernel gets at this width with noise
+                                        (1024, 1024, 8, 2048, 1),     # 4 x 16 tiles, as few without
+                                        (2304, 1024, 8, 896, 1)])     # 9 x 7 tiles, one less: the 64 x 64 kernel (4 x 16 with noise, too)
 @pytest.mark.parametrize("noisy", [True, False])
 def test_many_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
-    """As many tiles as the wide gate kernel is chosen for (fewer, the shapes above, go to the 64 x 64 one)."""
+    """As many tiles as the wide gate kernel is chosen for; the tokens behind the last whole tile go to the 64 x 64 one."""
     test_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy)
 
 
@@ -324,7 +325,7 @@ def test_layers_of_full_tiles_keep_the_kernel_with_the_large_tiles(dyn, T, d, h,
 
 @pytest.mark.parametrize("T,E,k", [(1025, 7, 1), (1024, 4096, 2), (513, 300, 2), (8192, 40, 8), (8200, 33, 8), (600, 4097, 2), (2560, 4096, 8), (2561, 4096, 8)])
 def test_grouping_of_many_uses(dyn, util, oracle, T, E, k):
-    """Blocks of 1024 uses with a remainder of one, the most experts, uses and counts of that path, and what lies beyond."""
+    """Blocks of 1024 uses with a remainder of one, the most experts and uses of that path, and what lies beyond."""
     m = moe.small(seed=T + k, T=T, d=16, h=16, E=E, k=k, zipf_s=0.8)
     W1, W2 = stack(m)
     _, aux = util.moe_run(dyn, m, W1, W2)
