@@ -711,50 +711,97 @@ __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict_
 
 // The same for more uses, in two launches: blocks of 1024 uses are ranked with the experts' counts in LDS and leave all of their
 // counts, zeros included (nothing has to be cleared), as blockcnt[block][expert]; then every block adds up all blocks' counts for
-// itself, an expert per thread, and places its uses.  For up to SMALL_EXPERTS experts and MID_BLOCKS blocks; us, the five launches below
-// / three, with one workgroup that turned the counts into places for a third launch / these two, by blocks x experts: 2 x 64 20.6 / 14.0 / 12.5,
-// 8 x 256 21.2 / 14.6 / 13.1, 64 x 1024 23.8 / 20.1 / 16.4, 40 x 2048 24.6 / 23.2 / 18.8, 20 x 4096 26.9 / - / 22.8, 64 x 4096 30.6 / - / 29.4.
+// itself, four experts a thread, and places its uses.  For up to SMALL_EXPERTS experts and MID_BLOCKS blocks; us, the five launches
+// below / these two with sixteen waves a workgroup / with four (k_place_wide beyond 1024 experts: eight), by blocks x experts: 2 x 64 20.6 / 12.2 / 10.2,
+// 8 x 256 21.2 / 12.7 / 10.4, 32 x 1024 22.1 / 14.7 / 13.2, 64 x 1024 23.9 / 16.2 / 16.2, 40 x 2048 24.7 / 18.6 / 14.4, 20 x 4096 26.9 / 22.8 / 17.0,
+// 64 x 4096 31.3 / 29.3 / 22.3.  Beside other layers' expert GEMMs sixteen waves find no CU with room for them: three layers of 64 x 1024 in
+// flight 1.95 ms a layer with sixteen, 1.87 with eight in k_place_wide, 1.73 with four (the five launches: 1.81).
 constexpr int MID_BLOCKS = 64;
-__global__ __launch_bounds__(1024) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
+__host__ __device__ constexpr int mid_stride(int E) { return (E + 3) & ~3; }      // experts of a row of blockcnt
+
+__global__ __launch_bounds__(256) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
 {
-    __shared__ int32_t count[SMALL_EXPERTS];
-    const int a = blockIdx.x * 1024 + threadIdx.x;
-    const int my = a < A ? idx[a] : -1;
-    for (int e = threadIdx.x; e < E; e += 1024) count[e] = 0;
-    const int before = rank_in_block(my, min(1024, A - int(blockIdx.x) * 1024), count);
-    if (a < A) lrank[a] = before;
-    for (int e = threadIdx.x; e < E; e += 1024) blockcnt[size_t(blockIdx.x) * E + e] = count[e];
+    __shared__ __attribute__((aligned(16))) int32_t count[SMALL_EXPERTS];
+    using i32x4 = int32_t __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, stride = mid_stride(E);
+    // this wave's 256 uses, 64 at a time; among 64 the lanes with the same expert are those that agree in every bit of its number
+    const int a0 = blockIdx.x * 1024 + wave * 256 + lane;
+    int my[4], local[4], same[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) my[i] = a0 + i * 64 < A ? idx[a0 + i * 64] : -1;
+    for (int e = tid * 4; e < stride; e += 1024) *reinterpret_cast<i32x4*>(count + e) = i32x4{0, 0, 0, 0};
+    uint64_t peers[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) peers[i] = __ballot(my[i] >= 0);
+    for (int bit = 1; bit < E; bit <<= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t set = __ballot(my[i] & bit);
+            peers[i] &= my[i] & bit ? set : ~set;
+        }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        local[i] = __popcll(peers[i] & ((1ull << lane) - 1));
+        same[i] = __popcll(peers[i]);
+    }
+    __syncthreads();
+    // the waves add theirs in turn
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (my[i] >= 0) {
+                    const int before = count[my[i]] + local[i];
+                    if (local[i] == same[i] - 1) count[my[i]] = before + 1;          // (behind the wave's reads: its LDS accesses are executed in order)
+                    lrank[a0 + i * 64] = before;
+                }
+        }
+        __syncthreads();
+    }
+    for (int e = tid * 4; e < stride; e += 1024)
+        *reinterpret_cast<i32x4*>(blockcnt + size_t(blockIdx.x) * stride + e) = *reinterpret_cast<const i32x4*>(count + e);
 }
 
 // block 0 also writes the experts' tables; tiles as in k_group_small
-__global__ __launch_bounds__(1024) void k_place_wide(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank, const int32_t* __restrict__ blockcnt,
-                                                     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
-                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv, RowTile* __restrict__ tiles, int max_tiles,
-                                                     int A, int E, int nblk)
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank, const int32_t* __restrict__ blockcnt,
+                                                    int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
+                                                    int32_t* __restrict__ perm, int32_t* __restrict__ inv, RowTile* __restrict__ tiles, int max_tiles,
+                                                    int A, int E, int nblk)
 {
     __shared__ int32_t first[SMALL_EXPERTS];              // where this block's uses of an expert start
-    __shared__ int32_t wsum[16], wtsum[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, blk = blockIdx.x, a = blk * 1024 + tid;
+    constexpr int THREADS = WAVES * 64, USES = 1024 / THREADS;
+    __shared__ int32_t wsum[WAVES], wtsum[WAVES];
+    using i32x4 = int32_t __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, blk = blockIdx.x, stride = mid_stride(E);
     const bool tables = blk == 0;
-    const int my = a < A ? idx[a] : 0, rank = a < A ? lrank[a] : 0;
-    int carry = 0, tcarry = 0;
-    for (int e0 = 0; e0 < E; e0 += 1024) {
-        const int e = e0 + tid;
-        int c = 0, before = 0;                            // uses of this expert in all blocks, in the blocks before this one
-        if (e < E) {
-            for (int b0 = 0; b0 < nblk; b0 += 16) {
-                int v[16];
+    int my[USES], rank[USES];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) v[i] = b0 + i < nblk ? blockcnt[size_t(b0 + i) * E + e] : 0;
+    for (int i = 0; i < USES; ++i) {
+        const int a = blk * 1024 + i * THREADS + tid;
+        my[i] = a < A ? idx[a] : 0;
+        rank[i] = a < A ? lrank[a] : 0;
+    }
+    int carry = 0, tcarry = 0;
+    for (int e0 = 0; e0 < E; e0 += 4 * THREADS) {
+        const int e = e0 + tid * 4;                       // this thread: experts e .. e + 3 (behind E: no uses)
+        i32x4 c = {0, 0, 0, 0}, before = {0, 0, 0, 0};    // uses in all blocks, in the blocks before this one
+        if (e < E) {
+            const int32_t* p = blockcnt + e;
+            for (int b0 = 0; b0 < nblk; b0 += 16) {
+                i32x4 v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = b0 + i < nblk ? *reinterpret_cast<const i32x4*>(p + size_t(b0 + i) * stride) : i32x4{0, 0, 0, 0};
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     c += v[i];
-                    before += b0 + i < blk ? v[i] : 0;
+                    if (b0 + i < blk) before += v[i];
                 }
             }
         }
-        const int tl = (c + TM - 1) / TM;                 // from here on as k_offsets
-        int inc = c, tinc = tl;
+        const i32x4 tl = (c + (TM - 1)) / TM;             // from here on as k_offsets, four experts a thread
+        const int mine = c.x + c.y + c.z + c.w, tmine = tl.x + tl.y + tl.z + tl.w;
+        int inc = mine, tinc = tmine;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int o = __shfl_up(inc, off);
@@ -765,36 +812,45 @@ __global__ __launch_bounds__(1024) void k_place_wide(const int32_t* __restrict__
         __syncthreads();
         int earlier = 0, tearlier = 0, all = 0, tall = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             const int s = wsum[w], t = wtsum[w];
             if (w < wave) { earlier += s; tearlier += t; }
             all += s;
             tall += t;
         }
-        if (e < E) {
-            const int at = carry + earlier + inc - c, tat = tcarry + tearlier + tinc - tl;
-            first[e] = at + before;
-            if (tables) {
-                counts[e] = c;
-                offsets[e] = at;
-                tile_start[e] = tat;
-                if (tiles)
-                    for (int t = 0; t < tl; ++t) tiles[tat + t] = RowTile{e, at + t * TM, min(TM, c - t * TM), 0};
+        int at = carry + earlier + inc - mine, tat = tcarry + tearlier + tinc - tmine;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (e + i < E) {
+                first[e + i] = at + before[i];
+                if (tables) {
+                    counts[e + i] = c[i];
+                    offsets[e + i] = at;
+                    tile_start[e + i] = tat;
+                    if (tiles)
+                        for (int t = 0; t < tl[i]; ++t) tiles[tat + t] = RowTile{e + i, at + t * TM, min(TM, c[i] - t * TM), 0};
+                }
             }
+            at += c[i];
+            tat += tl[i];
         }
         carry += all;
         tcarry += tall;
         __syncthreads();
     }
-    if (a < A) {
-        const int pos = first[my] + rank;
-        perm[pos] = a;
-        inv[a] = pos;
+#pragma unroll
+    for (int i = 0; i < USES; ++i) {
+        const int a = blk * 1024 + i * THREADS + tid;
+        if (a < A) {
+            const int pos = first[my[i]] + rank[i];
+            perm[pos] = a;
+            inv[a] = pos;
+        }
     }
     if (!tables) return;
     if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
     if (tiles)
-        for (int t = tcarry + tid; t < max_tiles; t += 1024) tiles[t] = RowTile{0, 0, 0, 0};
+        for (int t = tcarry + tid; t < max_tiles; t += THREADS) tiles[t] = RowTile{0, 0, 0, 0};
 }
 
 // ------------------------------------------------------------------------------------------ permute / combine
@@ -1363,9 +1419,9 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                            skinny_tiles, A, E);
     } else if (mid) {
         const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for)
-        hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(1024), 0, st, topk_idx, lrank, blockcnt, A, E);
-        hipLaunchKernelGGL(k_place_wide, dim3(nblk), dim3(1024), 0, st, topk_idx, lrank, blockcnt, counts, offsets, tile_start, perm, inv, tiles,
-                           skinny_tiles, A, E, nblk);
+        hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(256), 0, st, topk_idx, lrank, blockcnt, A, E);
+        hipLaunchKernelGGL(E <= 1024 ? k_place_wide<4> : k_place_wide<8>, dim3(nblk), dim3(E <= 1024 ? 256 : 512), 0, st, topk_idx, lrank, blockcnt,
+                           counts, offsets, tile_start, perm, inv, tiles, skinny_tiles, A, E, nblk);
     } else {
         const size_t nbc = size_t(E) * L.nblk;
         hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
