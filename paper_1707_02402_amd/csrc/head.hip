@@ -201,17 +201,13 @@ __global__ __launch_bounds__(256) void k_head_finish_slices(const float* __restr
     }
 }
 
-// The last layer and the softmax of one example per workgroup: a wave takes every fourth (few examples: sixteenth) answer, its lanes the hidden units.
+// The last layer and the softmax of one example per workgroup: a wave takes every WAVES-th answer, its lanes the hidden units.
 // (As a product, a sum of slices and a softmax they were three launches, 12 us for one example.)
-// SLICES: the hidden units themselves are still partial sums of n_slices slices, part[slice][example][unit]; they are added up here as
+// SLICES: the hidden units, 256 at most, are still partial sums of n_slices slices, part[slice][example][unit]; they are added up here as
 // k_head_finish_slices does it, four threads a unit, each all of its slices in one trip to memory: one launch less, 2.4 us
-// of one program's 178, 3 of 23 programs' 287.  An example's partial sums all pass through one CU, so there are HEAD_PARTS of them at most;
-// where there are more they get their launch, and the last layer its sixteen waves.  us a pass by hidden units x slices (bf16, 28 answers):
-// that launch and four waves / all in one / this: 256 x 64 16.5 / 14.8 / 14.8; 512 x 16 29.3 / 25.0 / 25.0, x 64 17.5 / 20.4 / 14.9; 1024 x 25
-// 19.1 / 22.0 / 15.5, x 32 20.4 / 21.8 / 16.6; 2048 x 13 21.8 / 23.7 / 16.2.
+// of one program's 178, 3 of 23 programs' 287.  (More units: an example's partial sums all pass through one CU.  The rules stand in launch_head.)
 constexpr int HEAD_ANSWERS = 64;                   // logits kept in LDS
-constexpr int HEAD_PARTS = 16384;
-constexpr int HEAD_UNITS = HEAD_PARTS / FINISH_SLICES;      // hidden units kept in LDS (SLICES)
+constexpr int HEAD_UNITS = 256;                    // hidden units kept in LDS (SLICES)
 struct AnswerArgs {
     const void* h1;                                // [B][F]
     const float* part;                             // SLICES
@@ -225,30 +221,27 @@ struct AnswerArgs {
 template <typename T, bool SLICES, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_head_answers(AnswerArgs g)
 {
-    static_assert(!SLICES || WAVES == 16, "four threads for each of 256 units");
+    static_assert(!SLICES || WAVES * 64 == 4 * HEAD_UNITS, "four threads a unit");
     __shared__ float row[HEAD_ANSWERS];
-    __shared__ float unit[SLICES ? HEAD_UNITS : 1], sum[SLICES ? 4 : 1][SLICES ? 256 : 1];
+    __shared__ float unit[SLICES ? HEAD_UNITS : 1], sum[SLICES ? 4 : 1][SLICES ? HEAD_UNITS : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, F = g.F, A = g.A;
     const T* h = static_cast<const T*>(g.h1) + size_t(blockIdx.x) * F;
     if constexpr (SLICES) {
         const size_t MN = size_t(g.B) * F;
-        const int q = tid >> 8, r = tid & 255;     // this thread: slices q, q + 4, ... of unit f0 + r
-        for (int f0 = 0; f0 < F; f0 += 256) {
-            const int f = f0 + r;
-            float v = 0.f;
-            if (f < F) {
-                const float* p = g.part + size_t(blockIdx.x) * F + f;
+        const int q = tid / HEAD_UNITS, f = tid % HEAD_UNITS;     // this thread: slices q, q + 4, ... of unit f
+        float v = 0.f;
+        if (f < F) {
+            const float* p = g.part + size_t(blockIdx.x) * F + f;
 #pragma unroll 16
-                for (int z = q; z < g.n_slices; z += 4) v += p[size_t(z) * MN];
-            }
-            sum[q][r] = v;
-            __syncthreads();
-            if (q == 0 && f < F) {
-                v = ((sum[0][r] + sum[1][r]) + sum[2][r]) + sum[3][r] + (g.bf1 ? g.bf1[f] : 0.f);
-                unit[f] = round_to<T>(fmaxf(v, 0.f));
-            }
-            __syncthreads();
+            for (int z = q; z < g.n_slices; z += 4) v += p[size_t(z) * MN];
         }
+        sum[q][f] = v;
+        __syncthreads();
+        if (q == 0 && f < F) {
+            v = ((sum[0][f] + sum[1][f]) + sum[2][f]) + sum[3][f] + (g.bf1 ? g.bf1[f] : 0.f);
+            unit[f] = round_to<T>(fmaxf(v, 0.f));
+        }
+        __syncthreads();
     }
     for (int a = wave; a < A; a += WAVES) {
         const T* w = static_cast<const T*>(g.wf2) + size_t(a) * F;
@@ -342,7 +335,7 @@ int check_head(const dynb_head_shape* s, int32_t B, const char* who)
     return DYNB_OK;
 }
 
-// keep: the sum of FINISH_SLICES slices and more, of up to `keep` partial sums a row, is left to the caller; returns their number then, else 0
+// keep: the sum of FINISH_SLICES to `keep` slices is left to the caller; returns their number then, else 0
 template <typename TO, bool RELU>
 int launch_layer(int dtype, const void* a, const void* w, const float* bias, TO* out, float* part, int M, int N, int K,
                  int splits, hipStream_t st, int keep = 0)
@@ -358,7 +351,7 @@ int launch_layer(int dtype, const void* a, const void* w, const float* bias, TO*
     if (g.out) return 0;
     const size_t MN = size_t(M) * N;
     const int n_slices = int(grid.z);
-    if (n_slices >= FINISH_SLICES && (long long)n_slices * N <= keep) return n_slices;
+    if (n_slices >= FINISH_SLICES && n_slices <= keep) return n_slices;
     if (n_slices >= FINISH_SLICES)
         hipLaunchKernelGGL((k_head_finish_slices<TO, RELU>), dim3(unsigned(std::min<size_t>((MN + 63) / 64, 4096))), dim3(256), 0, st, part, bias, out, MN, N, n_slices);
     else
@@ -376,10 +369,19 @@ void launch_head(const dynb_head_shape* s, const dynb_head_weights* w, const Hea
     T* h1 = reinterpret_cast<T*>(ws + L.h1);
     float* part = reinterpret_cast<float*>(ws + L.part);
     launch_layer<T, true>(s->dtype, roots, w->wc, w->bc, z, part, B * P, s->Cc, s->C, L.s1, st);
-    const int slices = launch_layer<T, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, P * s->Cc, L.s2, st, answers ? HEAD_PARTS : 0);
+    // The last layer's workgroups have sixteen waves as long as two of them a CU are enough for all examples; as long as one is, they add up
+    // 8 to 32 slices of up to HEAD_UNITS units themselves.  A pass with a launch for the slices and four waves = 1, with sixteen waves / that add up the
+    // slices, by examples (1086 heads of both types, 16 to 2048 units):
+    //   28 answers, 128 to 256 units   1 to 256: 0.90 / 0.86   350: 0.92 / 0.97   512: 0.93 / 0.96   1000: 1.01 / 1.07   2000: 1.09 / 1.19
+    //   28 answers, 16 to 64 units     512: 0.94 / 1.0   4096: 1.13 / 1.40 (16 units, 16 pixels: 19 us for 1, 41 the latter)
+    //   28 answers, 512 and 2048 units 1 to 256: 0.89 / 0.96   1 to 128: 0.79 / 0.95
+    //   4 and 60 answers, 128 to 256   512: 1.01 / 1.02, 700: 1.04 / 1.06   256: 0.83 / 0.79, 700: 0.94 / 0.98
+    // and by slices, 28 answers, up to 256 units and examples: 8 0.90 / 0.83, 25 0.91 / 0.85, 64 0.92 / 0.93.
+    const int keep = answers && s->F <= HEAD_UNITS && B <= 256 ? 32 : 0;
+    const int slices = launch_layer<T, true>(s->dtype, z, w->wf1, w->bf1, h1, part, B, s->F, P * s->Cc, L.s2, st, keep);
     const AnswerArgs g = {h1, part, w->bf1, w->wf2, w->bf2, logits, probs, B, s->F, s->n_answers, slices};
     if (slices > 0) hipLaunchKernelGGL((k_head_answers<T, true, 16>), dim3(unsigned(B)), dim3(1024), 0, st, g);
-    else if (answers && L.s2 >= FINISH_SLICES) hipLaunchKernelGGL((k_head_answers<T, false, 16>), dim3(unsigned(B)), dim3(1024), 0, st, g);
+    else if (answers && B <= 512) hipLaunchKernelGGL((k_head_answers<T, false, 16>), dim3(unsigned(B)), dim3(1024), 0, st, g);
     else if (answers) hipLaunchKernelGGL((k_head_answers<T, false, 4>), dim3(unsigned(B)), dim3(256), 0, st, g);
     else launch_layer<float, false>(s->dtype, h1, w->wf2, w->bf2, logits, part, B, s->n_answers, s->F, L.s3, st);
 }

@@ -46,14 +46,16 @@ def run_head(dyn, util, roots, head, dtype):
     ("f32", 3, 8, 2, 2, 8, 64, 64),           # the most answers for one workgroup per example
     ("bf16", 512, 8, 1, 1, 8, 1024, 64),      # the most examples for that many weights, and one more
     ("bf16", 513, 8, 1, 1, 8, 1024, 64),
-    ("f32", 3, 16, 4, 8, 16, 257, 28),        # eight slices, added up by the last layer: one unit more than it has threads for, ...
-    ("bf16", 1, 16, 4, 8, 16, 300, 28),
-    ("bf16", 3, 16, 4, 8, 16, 2048, 31),      # ... the most units, ...
-    ("f32", 1, 16, 4, 8, 16, 2048, 32),
-    ("bf16", 2, 16, 8, 8, 32, 512, 28),       # ... the most slices for 512
-    ("bf16", 1, 16, 4, 8, 16, 2056, 31),      # more partial sums: by a launch of their own
-    ("f32", 3, 16, 4, 8, 16, 2056, 31),
-    ("bf16", 2, 16, 6, 11, 32, 512, 28),
+    ("bf16", 3, 16, 4, 8, 16, 256, 28),       # eight slices, added up by the last layer: as many units as it has room for, ...
+    ("f32", 256, 16, 4, 8, 16, 9, 28),        # ... as many examples, ...
+    ("f32", 3, 16, 4, 8, 16, 257, 28),        # ... more units: a launch for the slices, ...
+    ("bf16", 257, 16, 4, 8, 16, 72, 28),      # ... more examples
+    ("bf16", 2, 16, 8, 8, 32, 200, 28),       # 32 slices and 33
+    ("bf16", 2, 16, 6, 11, 32, 200, 28),
+    ("bf16", 512, 16, 4, 8, 16, 16, 17),      # the most examples for sixteen waves each, an answer more than waves
+    ("f32", 513, 16, 4, 8, 16, 16, 5),
+    ("bf16", 2, 16, 4, 8, 16, 2048, 32),      # the most weights
+    ("f32", 1, 16, 4, 8, 16, 2056, 31),
 ])
 def test_every_probability_against_the_oracle(dyn, util, oracle, dtype, B, C, H, W, Cc, F, A):
     roots = np.abs(iep.make_feats(B + C, B, H, W, C, dtype))          # root maps are outputs of a ReLU: non-negative
