@@ -1418,7 +1418,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         hipLaunchKernelGGL(k_group_small, dim3(1), dim3(1024), 0, st, topk_idx, counts, offsets, tile_start, perm, inv, tiles,
                            skinny_tiles, A, E);
     } else if (mid) {
-        const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for)
+        const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for; a single expert's rows of four counts fill that)
         hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(256), 0, st, topk_idx, lrank, blockcnt, A, E);
         hipLaunchKernelGGL(E <= 1024 ? k_place_wide<4> : k_place_wide<8>, dim3(nblk), dim3(E <= 1024 ? 256 : 512), 0, st, topk_idx, lrank, blockcnt,
                            counts, offsets, tile_start, perm, inv, tiles, skinny_tiles, A, E, nblk);

@@ -324,9 +324,10 @@ def test_layers_of_full_tiles_keep_the_kernel_with_the_large_tiles(dyn, T, d, h,
 
 
 @pytest.mark.parametrize("T,E,k", [(1025, 7, 1), (1024, 4096, 2), (513, 300, 2), (8192, 40, 8), (8200, 33, 8), (600, 4097, 2), (2560, 4096, 8), (2561, 4096, 8),
-                                   (9000, 1, 1), (1500, 2, 1), (700, 1024, 2), (2049, 1025, 2), (1300, 2051, 3)])
+                                   (9000, 1, 1), (65536, 1, 1), (1500, 2, 1), (700, 1024, 2), (2049, 1025, 2), (1300, 2051, 3)])
 def test_grouping_of_many_uses(dyn, util, oracle, T, E, k):
-    """Blocks of 1024 uses with a remainder of one, the most experts and uses of that path, and what lies beyond."""
+    """Blocks of 1024 uses with a remainder of one, the most experts and uses of that path, and what lies beyond; a single expert, whose
+    counts take all the room they have."""
     m = moe.small(seed=T + k, T=T, d=16, h=16, E=E, k=k, zipf_s=0.8)
     W1, W2 = stack(m)
     _, aux = util.moe_run(dyn, m, W1, W2)
