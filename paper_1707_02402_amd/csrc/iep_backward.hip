@@ -1058,8 +1058,15 @@ int run_backward(const dynb_plan* p, const dynb_shape* s, const dynb_module_weig
             int rc = launch_conv<T, CV_DSECOND>(items, a, cnt, st);
             a.w = w->w3a;
             if (rc == DYNB_OK) rc = launch_conv<T, CV_DFIRST>(items, a, cnt, st);
-            a.w = w->w1;
-            if (rc == DYNB_OK && l.any_binary) rc = launch_conv<T, CV_DJOIN>(items, a, cnt, st);
+            const int lo = std::max(l.bin_lo, l.start + off), hi = std::min(l.bin_hi, l.start + off + cnt);
+            if (rc == DYNB_OK && lo < hi) {
+                ConvArgs j = a;
+                const int skip = lo - (l.start + off);
+                j.w = w->w1;
+                j.first_item += skip; j.first_kept += skip;
+                j.gdst0 += skip; j.gdst1 += skip;
+                rc = launch_conv<T, CV_DJOIN>(items + skip, j, hi - lo, st);
+            }
             if (rc != DYNB_OK) return fail(rc, "dynbatch_backward: a convolution could not be launched");
         }
     }

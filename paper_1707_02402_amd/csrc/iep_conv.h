@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "plan_internal.h"
@@ -28,9 +29,12 @@ namespace {
 
 // forward: join (1x1 over two arguments), first and second 3x3; backward: data gradients of the second and the first 3x3
 // and of the join
-enum ConvMode { CV_JOIN, CV_FIRST, CV_SECOND, CV_DSECOND, CV_DFIRST, CV_DJOIN };
+// (CV_JOIN_BOTH: a join with both arguments in LDS, one behind the other)
+enum ConvMode { CV_JOIN, CV_FIRST, CV_SECOND, CV_DSECOND, CV_DFIRST, CV_DJOIN, CV_JOIN_BOTH };
 
 struct ConvArgs {
+    uint32_t runs;                // recip_of(workgroups of an item), or 0: they stay in their order.  (First: what a workgroup waits for before it knows its item.)
+    uint32_t pad;
     int32_t first_item;           // index of items[0] among the items that gy, dm and du hold a map for
     int32_t first_kept;           // index of items[0] among the maps of u and mid
     // (u and du of kept plans hold maps for two-argument functions only, and the pointers are such that the same indices find them)
@@ -133,8 +137,8 @@ __host__ __device__ constexpr uint32_t recip20_of(uint32_t d) { return ((1u << 2
 __device__ __forceinline__ uint32_t div20_by(uint32_t v, uint32_t m) { return v * m >> 20; }
 
 template <ConvMode MODE> struct ConvTraits {
-    static constexpr bool JOINS = MODE == CV_JOIN || MODE == CV_DJOIN;
-    static constexpr int TAPS = JOINS ? 1 : 9, HALO = JOINS ? 0 : 1;
+    static constexpr bool JOINS = MODE == CV_JOIN || MODE == CV_DJOIN || MODE == CV_JOIN_BOTH;
+    static constexpr int TAPS = MODE == CV_JOIN_BOTH ? 2 : JOINS ? 1 : 9, HALO = JOINS ? 0 : 1;
     static constexpr bool BWD = MODE == CV_DSECOND || MODE == CV_DFIRST || MODE == CV_DJOIN;
 };
 
@@ -151,21 +155,42 @@ __host__ __device__ inline int conv_rows(int first, int n_pix, int sw, int halo)
 // last step is requested again.  The pixels of the next step are read under the MFMAs of this one.
 // FULL: C is a multiple of KS, so that no piece is ever cut short.  (What handles the others doubles the code, and a launch of
 // a few microseconds feels every line of it that the instruction cache has to fetch.)
-template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+// G = 2 (FULL, panels of an even number of steps, forward): weights are requested for two steps together.  A fragment wants the pieces of 16
+// rows in neighbouring lanes; asked for like that, four lanes' 64 bytes come from four lines, and a CU is answered at 15.6 bytes a clock
+// however many waves ask (590 KB, all CUs or a quarter of them).  Here two neighbouring lanes ask for consecutive pieces of one row (four,
+// in groups of four steps, were no faster: 23 to 38 bytes a clock, but such groups divide badly among the waves and the exchange doubles),
+// and the two fragments are put together by an exchange between these lanes:
+__device__ __forceinline__ void exchange(u32x4& a, u32x4& b)           // a's odd lanes against b's even ones
+{
+    const bool odd = (threadIdx.x & 1) != 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int pa = __builtin_amdgcn_mov_dpp(int(a[e]), 0xB1, 0xF, 0xF, true), pb = __builtin_amdgcn_mov_dpp(int(b[e]), 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+        const uint32_t na = odd ? uint32_t(pb) : a[e], nb = odd ? b[e] : uint32_t(pa);
+        a[e] = na;
+        b[e] = nb;
+    }
+}
+
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL, int G = 1>
 struct ConvSteps {
     using Tr = ConvTraits<MODE>;
     using E = std::conditional_t<Tr::BWD, float, T>;      // element type of the staged input: gradients are fp32
     static constexpr bool F32 = sizeof(E) == 4;
     static constexpr int TAPS = Tr::TAPS, ES = int(sizeof(E)), KS = F32 ? 16 : 32, PE = 16 / ES;
+    static constexpr int X_LANE = G * 16;                 // bytes between the pixel data of the lane groups g
+    static_assert(G == 1 || (G == 2 && FULL && !Tr::BWD), "weights in groups of steps");
     // Steps that the weights are requested ahead: a step is 128 (fp32) or 16 (bf16) clocks of MFMAs per 16 x 16 tile, an
-    // answer takes 500 to 2000.  Even; at C = 128 a wave of k_conv has 18 or 9 steps.
-    static constexpr int RD = F32 ? 6 : 10;
+    // answer takes 500 to 2000.  Even; at C = 128 a wave of k_conv has 18 or up to 10 steps.
+    static constexpr int RD = F32 ? 6 : G == 2 ? 12 : 10, NG = RD / G;
+    static_assert(RD % G == 0 && RD % 2 == 0, "ring");
 
-    uint32_t w_at[NT], x_at[MT];      // this lane's weights (bytes from w_panel) and pixels (LDS address of the top left tap)
+    uint32_t w_at[G == 2 ? 1 : NT], x_at[MT];             // this lane's weights (bytes from w_panel) and pixels (LDS address of the top left tap)
+    uint32_t w_tile[G == 2 ? NT : 1];                     // G = 2: bytes from w_panel to the channel tiles, uniform
     const char* w_panel;
     int C, c0, nj, s0, n_steps, w_pitch, w_chan, w_tap, g, row_bytes, pix_bytes;
     uint32_t m_nj;
-    u32x4 ring[RD][NT];
+    u32x4 ring[NG][NT][G];
 
     // weights of `type` for output channels n0 .. of NO (the last one again behind the end, whose results are dropped)
     __device__ __forceinline__ const char* weights(const void* w, int type, int C_, int n0, int NO, int lane)
@@ -175,10 +200,16 @@ struct ConvSteps {
         w_pitch = (Tr::JOINS ? 2 : 9) * C;                // elements between two rows of weights
         w_chan = KS * (Tr::BWD ? w_pitch : 1);
         w_tap = Tr::BWD ? -C : C;
+        if constexpr (G == 2) {                           // request i of a group: row (lane % 16 / G) G + i, piece lane % G of the lane group's G
+            w_at[0] = (uint32_t(lane & 15 & ~(G - 1)) * uint32_t(w_pitch) + uint32_t((g * G + (lane & (G - 1))) * PE)) * uint32_t(sizeof(T));
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const uint32_t n = uint32_t(min(n0 + nt * 16 + (lane & 15), NO - 1) - n0);
-            w_at[nt] = Tr::BWD ? (uint32_t(g * PE) * uint32_t(w_pitch) + n) * uint32_t(sizeof(T)) : (n * uint32_t(w_pitch) + uint32_t(g * PE)) * uint32_t(sizeof(T));
+            for (int nt = 0; nt < NT; ++nt) w_tile[nt] = uint32_t(min(n0 + nt * 16, NO - 16) - n0) * uint32_t(w_pitch) * uint32_t(sizeof(T));
+        } else {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const uint32_t n = uint32_t(min(n0 + nt * 16 + (lane & 15), NO - 1) - n0);
+                w_at[nt] = Tr::BWD ? (uint32_t(g * PE) * uint32_t(w_pitch) + n) * uint32_t(sizeof(T)) : (n * uint32_t(w_pitch) + uint32_t(g * PE)) * uint32_t(sizeof(T));
+            }
         }
         return reinterpret_cast<const char*>((const T*)w + size_t(type) * C * w_pitch + (Tr::BWD ? size_t(n0) : size_t(n0) * w_pitch));
     }
@@ -190,31 +221,59 @@ struct ConvSteps {
         m_nj = recip20_of(nj);
         w_panel = w_tile + (Tr::BWD ? ptrdiff_t(c0) * w_pitch + (Tr::JOINS ? 0 : 8 * C) : ptrdiff_t(arg * C) + c0) * ptrdiff_t(sizeof(T));
     }
-    __device__ __forceinline__ void load_w(int step, u32x4 (&w)[NT]) const
+    // wave w of 4: its share of the panel's steps, whole groups
+    __device__ __forceinline__ void share(int w)
+    {
+        const int groups = nj * TAPS / G;
+        s0 = groups * w / 4 * G;
+        n_steps = groups * (w + 1) / 4 * G - s0;
+    }
+    // steps step .. step + G - 1 (one group)
+    __device__ __forceinline__ void load_w(int step, u32x4 (&w)[NT][G]) const
     {
         const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj;
         const char* p = w_panel + (ptrdiff_t(tap) * w_tap + ptrdiff_t(j) * w_chan) * ptrdiff_t(sizeof(T));
-        const bool inside = FULL || c0 + (j + 1) * KS <= C;              // uniform
-        const int c = c0 + j * KS + g * PE;               // first of this lane's PE summed channels
+        if constexpr (G == 2) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            if constexpr (!Tr::BWD) w[nt] = load_piece<FULL>(reinterpret_cast<const T*>(p + w_at[nt]), inside ? PE : C - c);
-            else {
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    w[nt][e] = inside || c + e < C ? __float_as_uint(load_f32(reinterpret_cast<const T*>(p + (w_at[nt] + uint32_t(e * w_pitch) * uint32_t(sizeof(T)))))) : 0u;
+                for (int i = 0; i < G; ++i)
+                    w[nt][i] = *reinterpret_cast<const u32x4_any*>(p + w_tile[nt] + uint32_t(i * w_pitch) * uint32_t(sizeof(T)) + w_at[0]);
+        } else {
+            const bool inside = FULL || c0 + (j + 1) * KS <= C;          // uniform
+            const int c = c0 + j * KS + g * PE;           // first of this lane's PE summed channels
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                if constexpr (!Tr::BWD) w[nt][0] = load_piece<FULL>(reinterpret_cast<const T*>(p + w_at[nt]), inside ? PE : C - c);
+                else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        w[nt][0][e] = inside || c + e < C ? __float_as_uint(load_f32(reinterpret_cast<const T*>(p + (w_at[nt] + uint32_t(e * w_pitch) * uint32_t(sizeof(T)))))) : 0u;
+                }
             }
         }
     }
-    __device__ __forceinline__ void read_x(int step, u32x4 (&v)[MT]) const
+    // a group as it was requested -> its steps' fragments: lane: row lane % 16, step i: piece g G + i of the group
+    static __device__ __forceinline__ void sort(u32x4 (&w)[NT][G])
+    {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if constexpr (G == 2) exchange(w[nt][0], w[nt][1]);
+        }
+    }
+    // LDS offset of a group's pixels: of its first step; step i lies i pieces further
+    __device__ __forceinline__ uint32_t x_group(int step) const
+    {
+        const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
+        return uint32_t(kh * row_bytes + kw * pix_bytes + j * (KS * ES));
+    }
+    __device__ __forceinline__ void read_x(uint32_t off, int i, u32x4 (&v)[MT]) const
     {
         extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-        const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
-        const uint32_t off = uint32_t(kh * row_bytes + kw * pix_bytes + j * (KS * ES));
 #pragma unroll
-        for (int t = 0; t < MT; ++t) v[t] = *reinterpret_cast<const u32x4*>(lds_raw + x_at[t] + off);
+        for (int t = 0; t < MT; ++t) v[t] = *reinterpret_cast<const u32x4*>(lds_raw + (x_at[t] + off) + i * 16);
     }
-    static __device__ __forceinline__ void multiply(f32x4 (&acc)[MT][NT], const u32x4 (&w)[NT], const u32x4 (&v)[MT])
+    template <typename W> static __device__ __forceinline__ void multiply(f32x4 (&acc)[MT][NT], const W& w, int i, const u32x4 (&v)[MT])
     {
         if constexpr (F32) {
 #pragma unroll
@@ -223,44 +282,56 @@ struct ConvSteps {
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                     for (int t = 0; t < MT; ++t)
-                        acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[nt][e]), __uint_as_float(v[t][e]), acc[t][nt], 0, 0, 0);
+                        acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[nt][i][e]), __uint_as_float(v[t][e]), acc[t][nt], 0, 0, 0);
         } else {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int t = 0; t < MT; ++t)
-                    acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[nt]), __builtin_bit_cast(bf16x8, v[t]), acc[t][nt], 0, 0, 0);
+                    acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[nt][i]), __builtin_bit_cast(bf16x8, v[t]), acc[t][nt], 0, 0, 0);
         }
     }
     __device__ __forceinline__ void request()
     {
 #pragma unroll
-        for (int u = 0; u < RD; ++u) load_w(max(0, min(u, n_steps - 1)), ring[u]);
+        for (int u = 0; u < NG; ++u) load_w(max(0, min(u * G, n_steps - G)), ring[u]);
     }
     __device__ __forceinline__ void run(f32x4 (&acc)[MT][NT])
     {
         if (n_steps <= 0) return;
         u32x4 x[2][MT];
-        const int last = n_steps - 1;
-        read_x(0, x[0]);
+        const int last = n_steps - G;                     // the last group
+        uint32_t off = x_group(0);
+        read_x(off, 0, x[0]);
+        // one group, its weights in w; what comes after it is read under its MFMAs
+        auto group = [&](u32x4 (&w)[NT][G], int u, int next) {
+            sort(w);
+            const uint32_t then = x_group(min(next, last));
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const int k = u * G + i;
+                if (i + 1 < G) read_x(off, i + 1, x[(k + 1) & 1]);
+                else read_x(then, 0, x[(k + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(acc, w, i, x[k & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            off = then;
+        };
         int s = 0;
 #pragma unroll 1
         for (; s + RD < n_steps; s += RD) {
 #pragma unroll
-            for (int u = 0; u < RD; ++u) {
-                read_x(min(s + u + 1, last), x[(u + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(acc, ring[u], x[u & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                load_w(min(s + u + RD, last), ring[u]);
+            for (int u = 0; u < NG; ++u) {
+                group(ring[u], u, s + (u + 1) * G);
+                load_w(min(s + u * G + RD, last), ring[u]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
-        for (int u = 0; u < RD; ++u) {
-            if (s + u >= n_steps) break;
-            read_x(min(s + u + 1, last), x[(u + 1) & 1]);
-            multiply(acc, ring[u], x[u & 1]);
+        for (int u = 0; u < NG; ++u) {
+            if (s + u * G >= n_steps) break;
+            group(ring[u], u, s + (u + 1) * G);
         }
     }
 };
@@ -299,23 +370,32 @@ __device__ __forceinline__ f32x4 direct_sum(const T* w, int C, int H, int W, int
     return sum;
 }
 
-template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL, int G>
 __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArgs a)
 {
     using Tr = ConvTraits<MODE>;
-    using Steps = ConvSteps<T, MODE, MT, NT, FULL>;
+    using Steps = ConvSteps<T, MODE, MT, NT, FULL, G>;
     using E = typename Steps::E;
     constexpr int HALO = Tr::HALO, ES = Steps::ES, KS = Steps::KS, PE = Steps::PE;
     constexpr int BM = MT * 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
-    const int i = blockIdx.y;
+    // Consecutive workgroups go to the chip's 8 dies in turn: every die gets one run of the items' tiles, so that an item's map and its function's
+    // weights (items are sorted by function) are fetched behind one L2 and not behind all (21 training programs, fp32, C = 128, 14 x 14: 2496 ->
+    // 2374 us; 64 programs, bf16, 7 x 7: 492 -> 470).
+    uint32_t i = blockIdx.y, tile = blockIdx.x;
+    if (a.runs) {
+        const uint32_t total = gridDim.x * gridDim.y, b = i * gridDim.x + tile, die = b & 7, q = total >> 3, r = total & 7;
+        const uint32_t l = die * q + min(die, r) + (b >> 3);
+        i = div_by(l, a.runs);
+        tile = l - i * gridDim.x;
+    }
     const dynb_item it = items[i];
     const bool binary = it.src1 != DYNB_NO_ARG;           // uniform over the workgroup
     if (Tr::JOINS && !binary) return;
     const int C = a.C, H = a.H, W = a.W, sw = a.sw;
     const size_t chw = size_t(H) * W * C;
-    const int ptile = int(blockIdx.x) / a.n_ctile, ctile = int(blockIdx.x) - ptile * a.n_ctile;   // channel tiles of the same pixels are neighbours
+    const int ptile = int(tile) / a.n_ctile, ctile = int(tile) - ptile * a.n_ctile;   // channel tiles of the same pixels are neighbours
     const int seg = sw == W ? 0 : ptile / a.tiles_per_seg, q0 = (ptile - seg * a.tiles_per_seg) * BM, n_q = H * sw;
     const int x0 = seg * sw, y0 = q0 / sw, r0 = q0 - y0 * sw;     // the tile's first pixel: row y0, column x0 + r0
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
@@ -332,7 +412,7 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int q = r0 + min(t * 16 + r, n_q - 1 - q0), y = int(div20_by(q, a.m_sw)), x = q - y * sw;
-        steps.x_at[t] = uint32_t(y * row_bytes + x * pix_bytes + g * 16);
+        steps.x_at[t] = uint32_t(y * row_bytes + x * pix_bytes + g * Steps::X_LANE);
     }
     f32x4 acc[MT][NT];
 #pragma unroll
@@ -342,7 +422,7 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
 
     // the map whose convolution this is (in the join: argument `arg`)
     auto input_map = [&](int arg) -> const E* {
-        if constexpr (MODE == CV_JOIN) return conv_src<E>(a, arg ? it.src1 : it.src0, chw);
+        if constexpr (MODE == CV_JOIN || MODE == CV_JOIN_BOTH) return conv_src<E>(a, arg ? it.src1 : it.src0, chw);
         else if constexpr (MODE == CV_FIRST) return binary ? (const E*)a.u + size_t(a.first_kept + i) * chw : conv_src<E>(a, it.src0, chw);
         else if constexpr (MODE == CV_SECOND) return (const E*)a.mid + size_t(a.first_kept + i) * chw;
         else if constexpr (MODE == CV_DSECOND) return a.gy + size_t(a.first_item + i) * chw;
@@ -384,41 +464,54 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
         const int c0 = (panel - arg * panels) * a.ck;
         const int nj = min(a.ck / KS, (C - c0 + KS - 1) / KS);
         steps.panel(w_tile, c0, nj, arg);
-        const int S = nj * Tr::TAPS;
-        steps.s0 = S * wave / 4;                          // this wave's share
-        steps.n_steps = S * (wave + 1) / 4 - steps.s0;
-        steps.request();
+        steps.share(wave);
+        if constexpr (MODE == CV_JOIN_BOTH) {
+            steps.row_bytes = 0;
+            steps.pix_bytes = rows * row_bytes;           // from one argument to the other
+        }
 
         // ---- stage rows x cols pixels x nj * KS channels
         if (panel > 0) __syncthreads();
-        {
-            const E* src = input_map(arg);
-            const int np = nj * (KS / PE), n_pieces = rows * cols * np;
-            const uint32_t m_np = recip_of(np), m_cols = recip20_of(cols);
-            constexpr int UN = 6;
-            for (int base = tid; base < n_pieces; base += 256 * UN) {
-                u32x4 v[UN];
-                uint32_t at[UN];
-                uint32_t keep[UN];
+        const int np = nj * (KS / PE), n_map = rows * cols * np, n_pieces = MODE == CV_JOIN_BOTH ? 2 * n_map : n_map;
+        const uint32_t m_np = recip_of(np), m_cols = recip20_of(cols);
+        const E* const src = input_map(arg);
+        const E* const src1 = MODE == CV_JOIN_BOTH ? input_map(1) : nullptr;
+        constexpr int UN = 6;
+        u32x4 v[UN];
+        uint32_t at[UN], keep[UN];
+        auto load = [&](int base) {
 #pragma unroll
-                for (int k = 0; k < UN; ++k) {
-                    const int c = base + k * 256;
-                    const uint32_t pix = div_by(c, m_np), part = c - pix * np, row = div20_by(pix, m_cols), col = pix - row * cols;
-                    at[k] = row * row_bytes + col * pix_bytes + part * 16;
-                    const int y = y0 - HALO + int(row), x = x0 - HALO + int(col), ch = c0 + int(part) * PE;
-                    const bool inside = c < n_pieces && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W);
-                    keep[k] = inside ? ~0u : 0u;
-                    const size_t e = inside ? (size_t(y) * W + x) * C + ch : 0;      // outside: any piece, replaced by zeros below
-                    if constexpr (MODE == CV_DSECOND) v[k] = __builtin_bit_cast(u32x4, masked_gy<FULL>(src + e, y_map + e, inside ? C - ch : 0));
-                    else v[k] = load_piece<FULL>(src + e, inside ? C - ch : 0);
-                }
-#pragma unroll
-                for (int k = 0; k < UN; ++k)
-                    if (base + k * 256 < n_pieces) *reinterpret_cast<u32x4*>(__builtin_assume_aligned(lds_raw + at[k], 16)) = v[k] & keep[k];
-                // Everything has arrived.  Said aloud, because pieces that were requested and not stored would otherwise count
-                // as outstanding, and every wait from here on would be for more than it needs.
-                __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0)
+            for (int k = 0; k < UN; ++k) {
+                const int c = base + k * 256;
+                const bool second = MODE == CV_JOIN_BOTH && c >= n_map;
+                const uint32_t cc = second ? c - n_map : c;
+                const uint32_t pix = div_by(cc, m_np), part = cc - pix * np, row = div20_by(pix, m_cols), col = pix - row * cols;
+                at[k] = row * row_bytes + col * pix_bytes + part * 16 + (second ? uint32_t(rows * row_bytes) : 0u);
+                const int y = y0 - HALO + int(row), x = x0 - HALO + int(col), ch = c0 + int(part) * PE;
+                const bool inside = c < n_pieces && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W);
+                keep[k] = inside ? ~0u : 0u;
+                const size_t e = inside ? (size_t(y) * W + x) * C + ch : 0;      // outside: any piece, replaced by zeros below
+                if constexpr (MODE == CV_DSECOND) v[k] = __builtin_bit_cast(u32x4, masked_gy<FULL>(src + e, y_map + e, inside ? C - ch : 0));
+                else v[k] = load_piece<FULL>((second ? src1 : src) + e, inside ? C - ch : 0);
             }
+        };
+        auto store = [&](int base) {
+#pragma unroll
+            for (int k = 0; k < UN; ++k)
+                if (base + k * 256 < n_pieces) *reinterpret_cast<u32x4*>(__builtin_assume_aligned(lds_raw + at[k], 16)) = v[k] & keep[k];
+        };
+        // the first pieces go ahead of the weights, which arrive while the pixels are written
+        load(tid);
+        __builtin_amdgcn_sched_barrier(0);
+        steps.request();
+        __builtin_amdgcn_sched_barrier(0);
+        store(tid);
+        for (int base = tid + 256 * UN; base < n_pieces; base += 256 * UN) {
+            load(base);
+            store(base);
+            // Everything has arrived.  Said aloud, because pieces that were requested and not stored would otherwise count
+            // as outstanding, and every wait from here on would be for more than it needs.
+            __builtin_amdgcn_s_waitcnt(0x0f70);           // vmcnt(0)
         }
         if (panel == 0) request_operands();
         __syncthreads();
@@ -441,7 +534,7 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
             if constexpr (MODE == CV_SECOND) { v.x += f.q.x; v.y += f.q.y; v.z += f.q.z; v.w += f.q.w; }
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c], 0.f);
-            T* dst = MODE == CV_SECOND ? conv_dst<T>(a, it.dst, chw) : (T*)(MODE == CV_JOIN ? a.u : a.mid) + size_t(a.first_kept + i) * chw;
+            T* dst = MODE == CV_SECOND ? conv_dst<T>(a, it.dst, chw) : (T*)(Tr::JOINS ? a.u : a.mid) + size_t(a.first_kept + i) * chw;
             store4<FULL>(dst + f.e, n, v);
         } else if constexpr (MODE == CV_DSECOND) {                       // dmid = result [mid > 0]
 #pragma unroll
@@ -613,11 +706,11 @@ __device__ __forceinline__ void node_again(bool mid_nan, bool nan)
         });
 }
 
-template <typename T, int MT, bool FULL>
+template <typename T, int MT, bool FULL, int G>
 __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* items, NodeArgs nw, ConvArgs a)
 {
-    using First = ConvSteps<T, CV_FIRST, MT, 1, FULL>;
-    using Second = ConvSteps<T, CV_SECOND, MT, 1, FULL>;
+    using First = ConvSteps<T, CV_FIRST, MT, 1, FULL, G>;
+    using Second = ConvSteps<T, CV_SECOND, MT, 1, FULL, G>;
     using Join = ConvSteps<T, CV_JOIN, MT, 1, FULL>;
     constexpr int ES = int(sizeof(T)), KS = First::KS, PE = First::PE, NTHR = 512, NWAVE = 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -658,7 +751,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
         steps.s0 = 0;
         steps.n_steps = nj * 9;
 #pragma unroll
-        for (int t = 0; t < MT; ++t) steps.x_at[t] = tile + at[t] + uint32_t(g * 16);
+        for (int t = 0; t < MT; ++t) steps.x_at[t] = tile + at[t] + uint32_t(g * First::X_LANE);
         steps.request();
     };
     auto bias_of = [&](const float* b) -> f32x4 {
@@ -724,7 +817,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
                 constexpr int UN = 4;
 #pragma unroll 1
                 for (int j0 = 0; j0 < nj; j0 += UN) {
-                    u32x4 w[UN][1], x[UN][MT];
+                    u32x4 w[UN][1][1], x[UN][MT];
 #pragma unroll
                     for (int k = 0; k < UN; ++k) {
                         const int j = min(j0 + k, nj - 1), c = j * KS + g * PE;
@@ -734,7 +827,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
                     }
 #pragma unroll
                     for (int k = 0; k < UN; ++k)
-                        if (j0 + k < nj) Join::multiply(acc, w[k], x[k]);
+                        if (j0 + k < nj) Join::multiply(acc, w[k], 0, x[k]);
                 }
             }
             results([&](int t, int p, int o, int n) {
@@ -802,6 +895,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
 
 // ---- launching
 constexpr int CONV_LDS_MAX = 80 * 1024;                                  // two workgroups per CU
+constexpr int CONV_LDS_BOTH = 160 * 1024;                                // both arguments of a join
 
 // staged pixels of a tile of mt x 16 pixels, which start anywhere in a row
 inline int conv_tile_pixels(const ConvArgs& a, int mt, int halo)
@@ -810,7 +904,20 @@ inline int conv_tile_pixels(const ConvArgs& a, int mt, int halo)
     return std::min(conv_rows(a.sw - 1, n_pix, a.sw, halo), a.H + 2 * halo) * (a.sw + 2 * halo);
 }
 
-template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+// Channels staged at a time: as many as fit beside the pixels of the largest tile, whatever this tile has, in panels of nearly equal
+// size: a panel is what the waves split, so the panels are part of the order of summation, and a launch group's width (which
+// picks the tile) must not change a result's bits.
+template <int HALO, int ES>
+int conv_panel(const ConvArgs& a)
+{
+    constexpr int KS = ES == 4 ? 16 : 32;
+    const int steps = (a.C + KS - 1) / KS;
+    const int fit = std::max(1, (CONV_LDS_MAX / conv_tile_pixels(a, 4, HALO) - 16) / (KS * ES));
+    const int panels = (steps + fit - 1) / fit;
+    return (steps + panels - 1) / panels * KS;
+}
+
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL, int G>
 int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t st)
 {
     using Tr = ConvTraits<MODE>;
@@ -819,7 +926,7 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return DYNB_E_HIP;
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv<T, MODE, MT, NT, FULL>), hipFuncAttributeMaxDynamicSharedMemorySize, CONV_LDS_MAX) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv<T, MODE, MT, NT, FULL, G>), hipFuncAttributeMaxDynamicSharedMemorySize, MODE == CV_JOIN_BOTH ? CONV_LDS_BOTH : CONV_LDS_MAX) != hipSuccess)
             return DYNB_E_HIP;
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
@@ -827,21 +934,16 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     a.tiles_per_seg = (n_q + MT * 16 - 1) / (MT * 16);
     a.n_ctile = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + NT * 16 - 1) / (NT * 16);
     const int pixels = conv_tile_pixels(a, MT, Tr::HALO);
-    // As many channels at a time as fit beside the pixels of the largest tile, whatever this tile has, in panels of nearly equal
-    // size: a panel is what the waves split, so the panels are part of the order of summation, and a launch group's width (which
-    // picks the tile) must not change a result's bits.
-    const int steps = (a.C + KS - 1) / KS;
-    const int fit = std::max(1, (CONV_LDS_MAX / conv_tile_pixels(a, 4, Tr::HALO) - 16) / (KS * ES));
-    const int panels = (steps + fit - 1) / fit;
-    a.ck = (steps + panels - 1) / panels * KS;
+    a.ck = MODE == CV_JOIN_BOTH ? (a.C + KS - 1) / KS * KS : conv_panel<Tr::HALO, ES>(a);
     a.m_sw = recip20_of(a.sw);
-    const size_t lds = std::max<size_t>(size_t(pixels) * conv_pixel_bytes(a.ck, ES), size_t(4) * MT * NT * 1024);
-    if (lds > CONV_LDS_MAX) return DYNB_E_UNSUPPORTED;                   // cannot happen: sw <= 32
+    const size_t lds = std::max<size_t>(size_t(MODE == CV_JOIN_BOTH ? 2 : 1) * pixels * conv_pixel_bytes(a.ck, ES), size_t(4) * MT * NT * 1024);
+    if (lds > (MODE == CV_JOIN_BOTH ? CONV_LDS_BOTH : CONV_LDS_MAX)) return DYNB_E_UNSUPPORTED;     // cannot happen: sw <= 32
     // A row of a grid holds less than 2^32 threads (and nobody says so: the launch just does less).  Only the gradients of maps of
     // half a billion pixels with fewer than 4 channels would need more, which a parameter gradient's workgroup walks for many seconds.
     const long long groups = (long long)n_seg * a.tiles_per_seg * a.n_ctile;
     if (groups >= 1 << 24) return DYNB_E_UNSUPPORTED;
-    hipLaunchKernelGGL((k_conv<T, MODE, MT, NT, FULL>), dim3(unsigned(groups), unsigned(count)), dim3(256), lds, st, items, a);
+    a.runs = groups > 1 && count >= 16 && groups * groups * count < 1ll << 32 ? recip_of(uint32_t(groups)) : 0;
+    hipLaunchKernelGGL((k_conv<T, MODE, MT, NT, FULL, G>), dim3(unsigned(groups), unsigned(count)), dim3(256), lds, st, items, a);
     return DYNB_OK;
 }
 
@@ -854,33 +956,49 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
 //     2 x 2    10.4  10.5  10.6  10.8  10.9  17.4  17.7  18.1  23.6  23.2
 //     2 x 1     7.6   7.6   7.9  11.5  11.6  15.4  19.7  21.7  23.3  26.3
 //     1 x 1     6.5   6.7   9.0  11.2  15.1  17.6  23.1  25.6  28.0  32.6
-template <typename T, ConvMode MODE, bool FULL>
+template <typename T, ConvMode MODE, bool FULL, int G>
 int launch_conv_full(const dynb_item* items, ConvArgs a, int count, hipStream_t st)
 {
     using Tr = ConvTraits<MODE>;
     constexpr int ES = Tr::BWD ? 4 : int(sizeof(T)), KS = ES == 4 ? 16 : 32, STEP_CLOCKS = ES == 4 ? 128 : 16;
-    const int n_seg = (a.W + 31) / 32;
-    a.sw = (a.W + n_seg - 1) / n_seg;
     const long long ptiles = (long long)((a.W + a.sw - 1) / a.sw) * ((a.H * a.sw + 15) / 16), ctiles = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + 15) / 16;
     const long long steps = (long long)((a.C + KS - 1) / KS) * Tr::TAPS * (MODE == CV_JOIN ? 2 : 1);
     auto clocks = [&](int mt, int nt) {
         const long long groups = (long long)count * ((ptiles + mt - 1) / mt) * ((ctiles + nt - 1) / nt);
-        const long long staged = (long long)conv_tile_pixels(a, mt, Tr::HALO) * a.C * ES * (MODE == CV_JOIN || MODE == CV_DSECOND ? 2 : 1);
+        const long long staged = (long long)conv_tile_pixels(a, mt, Tr::HALO) * a.C * ES * (MODE == CV_JOIN || MODE == CV_JOIN_BOTH || MODE == CV_DSECOND ? 2 : 1);
         return (groups + 255) / 256 * (mt * nt * ((steps + 3) / 4) * STEP_CLOCKS + staged / 24 + 1200);
     };
     const long long c42 = clocks(4, 2), c22 = clocks(2, 2), c21 = clocks(2, 1), c11 = clocks(1, 1);
     const long long best = std::min(std::min(c42, c22), std::min(c21, c11));
-    if (best == c42) return launch_conv_tile<T, MODE, 4, 2, FULL>(items, a, count, st);
-    if (best == c22) return launch_conv_tile<T, MODE, 2, 2, FULL>(items, a, count, st);
-    if (best == c21) return launch_conv_tile<T, MODE, 2, 1, FULL>(items, a, count, st);
-    return launch_conv_tile<T, MODE, 1, 1, FULL>(items, a, count, st);
+    if (best == c42) return launch_conv_tile<T, MODE, 4, 2, FULL, G>(items, a, count, st);
+    if (best == c22) return launch_conv_tile<T, MODE, 2, 2, FULL, G>(items, a, count, st);
+    if (best == c21) return launch_conv_tile<T, MODE, 2, 1, FULL, G>(items, a, count, st);
+    return launch_conv_tile<T, MODE, 1, 1, FULL, G>(items, a, count, st);
 }
 
 template <typename T, ConvMode MODE>
-int launch_conv(const dynb_item* items, const ConvArgs& a, int count, hipStream_t st)
+int launch_conv(const dynb_item* items, const ConvArgs& args, int count, hipStream_t st)
 {
-    constexpr int KS = ConvTraits<MODE>::BWD || sizeof(T) == 4 ? 16 : 32;
-    return a.C % KS == 0 ? launch_conv_full<T, MODE, true>(items, a, count, st) : launch_conv_full<T, MODE, false>(items, a, count, st);
+    ConvArgs a = args;
+    using Tr = ConvTraits<MODE>;
+    constexpr int ES = Tr::BWD ? 4 : int(sizeof(T)), KS = ES == 4 ? 16 : 32;
+    const int n_seg = (a.W + 31) / 32;
+    a.sw = (a.W + n_seg - 1) / n_seg;
+    // A join takes both arguments at once where the largest tile's fit (a rule by the shape: it is part of the order of summation).  One after the
+    // other they were two waits for memory: 8.0 us a lone workgroup of bf16, C = 128, 7 x 7; now 5 for the whole launch.
+    if constexpr (MODE == CV_JOIN) {
+        const int ck = (a.C + KS - 1) / KS * KS;
+        if (2ll * conv_tile_pixels(a, 4, 0) * conv_pixel_bytes(ck, ES) <= CONV_LDS_BOTH) {
+            if (a.C % KS != 0) return launch_conv_full<T, CV_JOIN_BOTH, false, 1>(items, a, count, st);
+            if (a.C % (2 * KS) == 0) return launch_conv_full<T, CV_JOIN_BOTH, true, 2>(items, a, count, st);
+            return launch_conv_full<T, CV_JOIN_BOTH, true, 1>(items, a, count, st);
+        }
+    }
+    if (a.C % KS != 0) return launch_conv_full<T, MODE, false, 1>(items, a, count, st);
+    if constexpr (!Tr::JOINS && !Tr::BWD) {
+        if (a.C % (KS * 2) == 0 && conv_panel<Tr::HALO, ES>(a) % (KS * 2) == 0) return launch_conv_full<T, MODE, true, 2>(items, a, count, st);
+    }
+    return launch_conv_full<T, MODE, true, 1>(items, a, count, st);
 }
 
 // The three ways to run a module's convolutions are chosen by the shape alone, never by how many modules there are: each adds up in
@@ -932,19 +1050,19 @@ bool node_shape(const ConvArgs& a)
     return rounds <= 2 && std::max(mfma, weights) <= 10000;
 }
 
-template <typename T, int MT, bool FULL>
+template <typename T, int MT, bool FULL, int G>
 int launch_node_tile(const dynb_item* items, const NodeArgs& nw, const ConvArgs& a, hipStream_t st)
 {
     static std::atomic<uint64_t> attr_set{0};                            // one bit per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return DYNB_E_HIP;
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_node<T, MT, FULL>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_node<T, MT, FULL, G>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return DYNB_E_HIP;
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
     const size_t lds = size_t(2) * (a.H + 2) * (a.W + 2) * conv_pixel_bytes(a.ck, int(sizeof(T)));
-    hipLaunchKernelGGL((k_node<T, MT, FULL>), dim3(unsigned((nw.count + 7) / 8 * 8)), dim3(512), lds, st, items, nw, a);
+    hipLaunchKernelGGL((k_node<T, MT, FULL, G>), dim3(unsigned((nw.count + 7) / 8 * 8)), dim3(512), lds, st, items, nw, a);
     return DYNB_OK;
 }
 
@@ -956,9 +1074,12 @@ int launch_node(const dynb_item* items, const NodeArgs& nw, ConvArgs a, hipStrea
     a.m_sw = recip20_of(a.W);
     const int pt = (a.H * a.W + 15) / 16, ct = (a.C + 15) / 16;
     const bool wide = node_wide(pt, ct);
-    const bool full = a.C % KS == 0;
-    if (wide) return full ? launch_node_tile<T, 4, true>(items, nw, a, st) : launch_node_tile<T, 4, false>(items, nw, a, st);
-    return full ? launch_node_tile<T, 1, true>(items, nw, a, st) : launch_node_tile<T, 1, false>(items, nw, a, st);
+    if (a.C % KS != 0) return wide ? launch_node_tile<T, 4, false, 1>(items, nw, a, st) : launch_node_tile<T, 1, false, 1>(items, nw, a, st);
+    auto with = [&](auto group) {
+        constexpr int G = decltype(group)::value;
+        return wide ? launch_node_tile<T, 4, true, G>(items, nw, a, st) : launch_node_tile<T, 1, true, G>(items, nw, a, st);
+    };
+    return a.C % (2 * KS) == 0 ? with(std::integral_constant<int, 2>{}) : with(std::integral_constant<int, 1>{});
 }
 
 }  // namespace

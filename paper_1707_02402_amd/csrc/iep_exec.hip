@@ -591,7 +591,14 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
                 continue;
             }
             int rc = DYNB_OK;
-            if (l.any_binary) { a.w = w->w1; a.bias = w->b1; rc = (plain ? launch_conv_plain<T, CV_JOIN> : launch_conv<T, CV_JOIN>)(items, a, count, st); }
+            // (only the items that may be joins: a launch group's others would each start workgroups that find nothing to do)
+            const int lo = std::max(l.bin_lo, l.start + off), hi = std::min(l.bin_hi, l.start + off + count);
+            if (lo < hi) {
+                ConvArgs j = a;
+                j.w = w->w1; j.bias = w->b1;
+                j.first_kept += lo - (l.start + off);
+                rc = (plain ? launch_conv_plain<T, CV_JOIN> : launch_conv<T, CV_JOIN>)(items + (lo - (l.start + off)), j, hi - lo, st);
+            }
             a.w = w->w3a; a.bias = w->b3a;
             if (rc == DYNB_OK) rc = (plain ? launch_conv_plain<T, CV_FIRST> : launch_conv<T, CV_FIRST>)(items, a, count, st);
             a.w = w->w3b; a.bias = w->b3b;

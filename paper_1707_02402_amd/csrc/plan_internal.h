@@ -23,10 +23,9 @@ struct dynb_item {
 struct dynb_launch {
     int32_t start;       // first item
     int32_t count;
-    int32_t any_binary;  // some item of the group is a two-argument function (the kernels take the conv1x1 path)
-    // DYNB_PLAN_KEEP: the group's items from its first to its last two-argument function have a kept u (and du) each
-    int32_t u_lo = 0;    // the first of them, an item of the plan
-    int32_t u_first = 0; // ... and its place among the kept maps
+    // from the group's first to its last two-argument function (items of the plan; none: bin_lo = bin_hi = 0)
+    int32_t bin_lo = 0, bin_hi = 0;
+    int32_t u_first = 0; // DYNB_PLAN_KEEP: those have a kept u (and du) each, and this is the first one's place among the kept maps
 };
 
 // mode 0: second conv3x3 (part = kernel row), 1: first conv3x3 (part = kernel row), 2: conv1x1 (part = argument)
@@ -122,11 +121,11 @@ inline size_t dynb_fast_keep_bytes(const dynb_plan* p) { return p->keep ? dynb_a
 inline size_t dynb_generic_mid_offset(const dynb_plan* p, size_t map) { return size_t(p->n_slots) * map; }
 inline size_t dynb_generic_mids(const dynb_plan* p) { return p->keep ? p->items.size() : size_t(p->max_launch); }
 inline size_t dynb_generic_us(const dynb_plan* p) { return !p->has_binary ? 0 : p->keep ? p->n_u : size_t(p->max_launch); }
-// What the kernels add an item's number to, to find its u among the kept ones of `maps`: the group's share starts with item u_lo
+// What the kernels add an item's number to, to find its u among the kept ones of `maps`: the group's share starts with item bin_lo
 // (items outside it have none, and their numbers are not used)
 template <typename T> T* dynb_u_of_group(T* maps, const dynb_launch& l, size_t map_elements)
 {
-    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(maps) + (uintptr_t(l.u_first) - uintptr_t(l.u_lo)) * map_elements * sizeof(T));
+    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(maps) + (uintptr_t(l.u_first) - uintptr_t(l.bin_lo)) * map_elements * sizeof(T));
 }
 
 namespace dynb {

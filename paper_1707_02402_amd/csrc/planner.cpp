@@ -282,7 +282,7 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
                 // slots of arguments consumed by the previous group may be reused from here on
                 free_slots.insert(free_slots.end(), release.begin(), release.end());
                 release.clear();
-                p->launches.push_back(dynb_launch{int32_t(p->items.size()), 0, 0});
+                p->launches.push_back(dynb_launch{int32_t(p->items.size()), 0});
                 cur = p->node_launch[n];
             }
             const bool is_root = (n == p->root[example[n]]);
@@ -305,7 +305,11 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
             it.dst = is_root ? -1 - example[n] : slot[n];
             it.type = p->type[n];
             ++p->launches.back().count;
-            if (arity[it.type] == 2) p->launches.back().any_binary = 1;
+            if (arity[it.type] == 2) {
+                dynb_launch& l = p->launches.back();
+                if (l.bin_hi == 0) l.bin_lo = int32_t(p->items.size());
+                l.bin_hi = int32_t(p->items.size()) + 1;
+            }
             p->items.push_back(it);
             p->item_node.push_back(n);
         }
@@ -348,13 +352,9 @@ void build_lists(dynb_plan* p, const uint8_t* arity, const int32_t* prog_off, co
         // room for u of two-argument functions: every group from its first to its last (they are sorted by function)
         p->u_at.assign(p->items.size(), 0);
         for (dynb_launch& l : p->launches) {
-            int32_t lo = l.start + l.count, hi = l.start;
-            for (int32_t i = l.start; i < l.start + l.count; ++i)
-                if (arity[p->items[i].type] == 2) { lo = std::min(lo, i); hi = i + 1; }
-            if (lo >= hi) continue;
-            l.u_lo = lo;
+            if (l.bin_lo >= l.bin_hi) continue;
             l.u_first = int32_t(p->n_u);
-            for (int32_t i = lo; i < hi; ++i) p->u_at[i] = int32_t(p->n_u++);
+            for (int32_t i = l.bin_lo; i < l.bin_hi; ++i) p->u_at[i] = int32_t(p->n_u++);
         }
         // units of the parameter-gradient kernel
         // (every function has its groups, also those without a gradient of that kind: their sum is zero; the

@@ -588,3 +588,24 @@ def test_a_launch_group_of_more_modules_than_one_grid_holds(dyn, util):
     out = dyn.dynbatch_execute(plan, weights, feats, out=torch.zeros_like(feats))
     for part in out.split(1 << 20):
         assert bool((part == one).all())
+
+
+@pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 32, 9, 33, 9), ("f32", 96, 7, 5, 9), ("f32", 64, 14, 14, 21), ("bf16", 64, 6, 7, 40), ("bf16", 192, 5, 9, 7),
+                                           ("bf16", 128, 9, 11, 30), ("f32", 288, 6, 6, 3), ("bf16", 128, 7, 7, 70)])
+def test_weights_in_pairs_of_steps_and_joins_anywhere_in_a_group(dyn, util, oracle, dtype, C, H, W, B):
+    """Channels that make an even number of steps, so that weights are requested for two at a time, with remainders of tiles and segments; joins of which
+    both arguments are staged at once or one after the other (288 channels); two-argument functions before, between and behind the others, so
+    that a group's joins lie anywhere in it.  Every schedule gives the same bits, with kept maps too."""
+    arity = np.array([0, 2, 1, 2, 1], np.uint8)
+    progs = [np.array(p, np.int32) for p in ([1, 0, 2, 0], [4, 3, 0, 0], [2, 0], [3, 1, 0, 0, 4, 0], [4, 2, 0])]
+    progs = [progs[i % 5] for i in range(B)]
+    off = np.concatenate([[0], np.cumsum([len(p) for p in progs])]).astype(np.int32)
+    w = iep.IepWorkload("pairs", dtype, arity, np.concatenate(progs), off, C, H, W, iep.make_feats(C + W, B, H, W, C, dtype),
+                        *iep.make_weights(C, arity, C, dtype))
+    got = util.iep_run(dyn, w)
+    for flags in (1, 2, 3, dyn.DYNB_PLAN_KEEP):
+        assert (util.iep_run(dyn, w, flags) == got).all(), flags
+    n = min(B, 5)
+    ref = oracle.iep_forward_workload(w.subset(range(n)))
+    for i in range(n):
+        assert util.normwise(got[i], ref[i]) < TOL[dtype], i
