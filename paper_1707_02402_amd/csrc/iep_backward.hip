@@ -355,29 +355,24 @@ void launch_leaves(const dynb_plan* p, const float* gleaf, const int32_t* leaf_f
 // function by function afterwards.
 struct BmArgs {
     const dynb_item* items;       // the launch group's items
+    int32_t per_xcd;              // workgroups of a die's run
     const int32_t* gdst0;         // routes of the group's items
     const int32_t* gdst1;
     int32_t first_item;
     int32_t count;
-    const bf16_t* feats;
-    const bf16_t* out;
-    const bf16_t* slots;
     const bf16_t* pk3bT;          // packed fragments: conv_b, taps flipped, channels exchanged
     const bf16_t* pk3aT;          //                   conv_a, taps flipped, channels exchanged
     const bf16_t* pk1T;           //                   conv1x1 halves, channels exchanged
     float* gy;                    // [n_items][P*C]
     const float* dout;            // the gradient of a root's result, read where it is (null: it has been copied to gy)
     float* gleaf;                 // [n_leaves][P*C]
-    const bf16_t* sv_u;           // [n_items][P*C] each; u and mid: in the forward pass's workspace
-    const bf16_t* sv_m;
+    const bf16_t* sv_u;           // [n_items][P*C] each; u: in the forward pass's workspace
+    const unsigned char* mask_y;  // [n_items][P*C/8], of the results and of mid: from the forward pass
+    const unsigned char* mask_m;
     bf16_t* sv_g;
     bf16_t* sv_dm;
     bf16_t* sv_dc;
 };
-
-// a bf16 is positive iff its bits, read as int16, are positive; for the two halves of a packed pair
-__device__ __forceinline__ bool bf16_lo_positive(uint32_t w) { return int16_t(w & 0xffffu) > 0; }
-__device__ __forceinline__ bool bf16_hi_positive(uint32_t w) { return int16_t(w >> 16) > 0; }
 
 __device__ __forceinline__ float* route_mf(const BmArgs& a, int32_t r)
 {
@@ -412,13 +407,13 @@ __global__ void k_bwd_pack(PackArgs a)
     }
 }
 
-// LDS of the backward node kernel: the halo tile, one mask byte per 16-byte piece of the y and the mid map, and an
+// LDS of the backward node kernel: the halo tile, parts: the mask bytes of their rows of y, and an
 // fp32 staging area through which accumulators (lane = pixel) leave as coalesced 16-byte pieces.  A global access in
-// which every lane touches a line of its own costs about 125 clocks to issue, so nothing is loaded or stored in the
-// accumulator layout: masks come from the LDS bytes, the residual term and the result go through the staging area.
+// which every lane touches a line of its own costs about 125 clocks to issue, so nothing but the mask of mid (two bytes a lane, eight lanes a line) is
+// loaded or stored in the accumulator layout: the residual term and the result go through the staging area.
 namespace bn {
-constexpr int MASK_OFF = (mf::TILE_BYTES + 255) / 256 * 256; // y mask bytes [P][16], then mid mask bytes [P][16]
-constexpr int MASK_BYTES = 2 * mf::P * 16 + 128;         // (+ padding to a multiple of 256)
+constexpr int MASK_OFF = (mf::TILE_BYTES + 255) / 256 * 256; // y mask bytes [P][16]
+constexpr int MASK_BYTES = mf::P * 16 + 192;             // (+ padding to a multiple of 256)
 constexpr int STAGE_OFF = MASK_OFF + MASK_BYTES;
 constexpr int STAGE_PITCH = mf::C * 4 + 16;              // bytes per pixel: 128 floats + a bank-shifting pad
 constexpr int STAGE_PIX = 112;                           // pixels per round: four pixel tiles (8 image rows)
@@ -437,8 +432,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     constexpr int MTA = Shape::MTA, MTB = Shape::MTB, UROWS = Shape::UROWS, RW = Shape::RW, NTHR = 256;
     constexpr int XA = PARTS == 1 ? 6 : Shape::XA, XB = PARTS == 1 ? 6 : Shape::XB;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int per_xcd = gridDim.x >> 3;
-    const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int logical = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
     const int node = logical / (PARTS * SPLIT), part = logical / SPLIT % PARTS, share = logical % SPLIT;
     if (node >= a.count) return;
     // image rows: results [orow0, orow1), windows of the two convs from row_a and row_b, g from urow0
@@ -471,31 +465,26 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         const int p = c >> 4, part = c & 15;
         return uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16);
     };
-    // bit i of the result: element i of the piece is positive
-    auto piece_mask = [](const u32x4& v) -> uint32_t {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        uint32_t bits = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bits |= (bf16_lo_positive(w[i]) ? 1u : 0u) << (2 * i) | (bf16_hi_positive(w[i]) ? 1u : 0u) << (2 * i + 1);
-        return bits;
-    };
     const float* gyp = a.dout && it.dst < 0 ? a.dout + size_t(-1 - it.dst) * (P * C) : a.gy + item_off;
-    const bf16_t* yp = it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C);
+    const unsigned char* const y_mask = a.mask_y + size_t(a.first_item + node) * (P * C / 8);
+    const unsigned char* const m_mask = a.mask_m + size_t(a.first_item + node) * (P * C / 8);
 
-    // ---- g = gy * [y > 0] as bf16 into the tile, saved for dW_b and db_b; mask bytes of y and mid; all loads are
-    // issued before the first use
+    // ---- g = gy * [y > 0] as bf16 into the tile, saved for dW_b and db_b; all loads are issued before the first use.
+    // A whole node's g stays in registers (half of them are free) until it is added to du: reading gy again was 100 of the 500 KB that a node
+    // moved, in a phase that waits for them.
     constexpr int NIT = (UROWS * S * 16 + NTHR - 1) / NTHR;
+    struct Grad { f32x4 g0, g1; };
+    Grad whole[PARTS == 1 ? NIT : 1];
     {
         const int c_lo = urow0 * S * 16 + tid, c_hi = (urow0 + UROWS) * S * 16;
         const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
-        const u32x4* y4 = reinterpret_cast<const u32x4*>(yp);
         u32x4* sg4 = reinterpret_cast<u32x4*>(a.sv_g + item_off);
-        f32x4 glo[NIT], ghi[NIT];
-        u32x4 yv[NIT];
+        Grad in[NIT];
+        uint32_t yb[NIT];
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
             const int c = c_lo + i * NTHR;
-            if (c < c_hi) { glo[i] = gy4[2 * c]; ghi[i] = gy4[2 * c + 1]; yv[i] = y4[c]; }
+            if (c < c_hi) { in[i].g0 = gy4[2 * c]; in[i].g1 = gy4[2 * c + 1]; yb[i] = y_mask[c]; }
         }
         __builtin_amdgcn_sched_barrier(0);
         ring_fill<RW>(ring, wrow_bT);                             // arrives while the tile is written
@@ -504,15 +493,17 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         for (int i = 0; i < NIT; ++i) {
             const int c = c_lo + i * NTHR;
             if (c < c_hi) {
-                const uint32_t yb = piece_mask(yv[i]);
-                u32x4 pk;
-                pk.x = pack_bf16x2(yb & 1u ? glo[i].x : 0.f, yb & 2u ? glo[i].y : 0.f);
-                pk.y = pack_bf16x2(yb & 4u ? glo[i].z : 0.f, yb & 8u ? glo[i].w : 0.f);
-                pk.z = pack_bf16x2(yb & 16u ? ghi[i].x : 0.f, yb & 32u ? ghi[i].y : 0.f);
-                pk.w = pack_bf16x2(yb & 64u ? ghi[i].z : 0.f, yb & 128u ? ghi[i].w : 0.f);
+                Grad g;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    g.g0[e] = masked_by(yb[i], mask_bit(e), in[i].g0[e]);
+                    g.g1[e] = masked_by(yb[i], mask_bit(e + 4), in[i].g1[e]);
+                }
+                const u32x4 pk = {pack_bf16x2(g.g0.x, g.g0.y), pack_bf16x2(g.g0.z, g.g0.w), pack_bf16x2(g.g1.x, g.g1.y), pack_bf16x2(g.g1.z, g.g1.w)};
                 *reinterpret_cast<u32x4*>(lds_raw + centre_addr(c)) = pk;
                 if (PARTS == 1 || (c >= own_lo && c < own_hi && mine(c))) sg4[c] = pk;
-                lds_raw[bn::MASK_OFF + c] = static_cast<unsigned char>(yb);
+                if constexpr (PARTS == 1) whole[i] = g;
+                else lds_raw[bn::MASK_OFF + c] = static_cast<unsigned char>(yb[i]);
             }
         }
     }
@@ -539,24 +530,24 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     auto packed_masked = [&](const f32x16& acc, int q, uint32_t bits) -> u32x4 {
         float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (bits >> (8 * q + i)) & 1u ? acc[8 * q + i] : 0.f;
+        for (int i = 0; i < 8; ++i) v[i] = masked_by(bits, 8 * q + mask_bit(i), acc[8 * q + i]);
         return u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
     };
     // Accumulators of the second window -> the fp32 staging area, four pixel tiles per round; then every thread takes 16-byte pieces
-    // (8 channels of a pixel) out of it: fn(c, lo, hi, pre(c)) with c the piece's index in the whole map.  pre(c)
-    // is evaluated for all of a thread's pieces before the round's barriers, so what it loads is there afterwards.  Where there is one
-    // round (parts), its i-th piece is also known before the second conv, pre(c, i).
+    // (8 channels of a pixel) out of it: fn(c, lo, hi, pre(c), i) with c the piece's index in the whole map and i its number among the thread's
+    // (of whole nodes the thread's i-th as it staged them).  pre(c) is evaluated for all of a thread's pieces before the round's barriers, so what it
+    // loads is there afterwards.
     constexpr int NI = ((MTB < 4 ? MTB : 4) * 28 * 16 + NTHR - 1) / NTHR;     // pieces per thread of the larger round
     auto through_lds = [&](auto&& pre, auto&& fn) {
 #pragma unroll
         for (int round = 0; round < (MTB + 3) / 4; ++round) {
             const int t0 = round * 4, t1 = min(t0 + 4, MTB), p0 = row_b * S + t0 * 28;
             const int lo = PARTS == 1 ? p0 * 16 : own_lo, hi = PARTS == 1 ? p0 * 16 + (t1 - t0) * 28 * 16 : own_hi;   // (parts: one round)
-            decltype(pre(0, 0)) ahead[NI];
+            decltype(pre(0)) ahead[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int c = lo + tid + i * NTHR;
-                if (c < hi && mine(c)) ahead[i] = pre(c, i);
+                if (c < hi && mine(c)) ahead[i] = pre(c);
             }
             __syncthreads();                                          // the area (and, the first time, the tile) is free
 #pragma unroll
@@ -573,14 +564,13 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
                 const int c = lo + tid + i * NTHR;
                 if (c < hi && mine(c)) {
                     const uint32_t at = bn::STAGE_OFF + uint32_t(((c >> 4) - p0) * bn::STAGE_PITCH + (c & 15) * 32);
-                    fn(c, *reinterpret_cast<const f32x4*>(lds_raw + at), *reinterpret_cast<const f32x4*>(lds_raw + at + 16), ahead[i]);
+                    fn(c, *reinterpret_cast<const f32x4*>(lds_raw + at), *reinterpret_cast<const f32x4*>(lds_raw + at + 16), ahead[i], round * NI + i);
                 }
             }
         }
     };
+    static_assert(PARTS > 1 || 4 * 28 * 16 % NTHR == 0, "a whole node's rounds begin where a thread's pieces do");
     struct Nothing {};
-    struct Grad { f32x4 g0, g1; };
-    struct GradU { f32x4 g0, g1; u32x4 u; };
     auto store_piece = [](float* dst, int c, const f32x4& lo, const f32x4& hi) {
         *reinterpret_cast<f32x4*>(dst + size_t(c) * 8) = lo;
         *reinterpret_cast<f32x4*>(dst + size_t(c) * 8 + 4) = hi;
@@ -589,33 +579,21 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     __syncthreads();
 
     // ---- dmid = conv(g; W_b flipped, transposed) * [mid > 0], written into the tile in place of g
-    // (mid is requested now and turned into mask bytes after the loop)
-    constexpr int NIM = (2 * MTA * S * 16 + NTHR - 1) / NTHR;
-    const int m_lo = row_a * S * 16 + tid, m_hi = (row_a + 2 * MTA) * S * 16;
-    u32x4 mv[NIM];
+    // (this lane's 16 bits of mid's mask, the bytes of the two pieces that hold its channels, are requested now)
+    uint32_t mm[MTA];
 #pragma unroll
-    for (int i = 0; i < NIM; ++i) {
-        const int c = m_lo + i * NTHR;
-        if (c < m_hi) mv[i] = reinterpret_cast<const u32x4*>(a.sv_m + item_off)[c];
-    }
+    for (int t = 0; t < MTA; ++t) mm[t] = real ? *reinterpret_cast<const uint16_t*>(m_mask + pixel(row_a, t) * 16 + (chan >> 3)) : 0u;
     zero(acc_a);
     NCLK(1);
     kloop3<MTA, RW, XA>(acc_a, x_a, ring, wrow_bT, wrow_aT);
     NCLK(2);
-#pragma unroll
-    for (int i = 0; i < NIM; ++i) {
-        const int c = m_lo + i * NTHR;
-        if (c < m_hi) lds_raw[bn::MASK_OFF + P * 16 + c] = static_cast<unsigned char>(piece_mask(mv[i]));
-    }
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < MTA; ++t)
         if (real) {
-            // this lane's 16 mask bits: the bytes of the two pieces that hold its channels
-            const uint32_t mm = *reinterpret_cast<const uint16_t*>(lds_raw + bn::MASK_OFF + P * 16 + pixel(row_a, t) * 16 + (chan >> 3));
 #pragma unroll
             for (int q = 0; q < 2; ++q)
-                *reinterpret_cast<u32x4*>(lds_raw + centre(x_a, t) + uint32_t((chan + q * 8) * 2)) = packed_masked(acc_a[t], q, mm);
+                *reinterpret_cast<u32x4*>(lds_raw + centre(x_a, t) + uint32_t((chan + q * 8) * 2)) = packed_masked(acc_a[t], q, mm[t]);
         }
     __syncthreads();
     {                                                                 // dmid saved for dW_a and db_a, out of the tile
@@ -630,31 +608,34 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     // ---- du = g + conv(dmid; W_a flipped, transposed).  The residual term g is added in fp32, from the gradient map
     // itself, not from its bf16 copy in the tile: down a chain of modules the convolution's share is small against
     // the residual's and would vanish below the bfloat16 quantum of the latter at every level.
-    const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
     // (a part's pieces of it are requested here: behind the loop they were a trip to memory that nothing hid)
     Grad residue[PARTS > 1 ? NI : 1];
     if constexpr (PARTS > 1) {
+        const f32x4* gy4 = reinterpret_cast<const f32x4*>(gyp);
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int c = own_lo + tid + i * NTHR;
             if (c < own_hi && mine(c)) residue[i] = Grad{gy4[2 * c], gy4[2 * c + 1]};
         }
     }
-    auto grad = [&](int c, int i) -> Grad { if constexpr (PARTS > 1) return residue[i]; else return Grad{gy4[2 * c], gy4[2 * c + 1]}; };
+    auto grad = [&](int i) -> const Grad& { if constexpr (PARTS > 1) return residue[i]; else return whole[i]; };
     zero(acc);
     NCLK(3);
     if (second) kloop3<MTB, RW, XB, false>(acc, x_b, ring, wrow_aT, wrow_aT);
     NCLK(4);
-    auto residual = [&](int c, f32x4& lo, f32x4& hi, const f32x4& g0, const f32x4& g1) {
-        const uint32_t yb = lds_raw[bn::MASK_OFF + c];
-        lo.x += yb & 1u ? g0.x : 0.f; lo.y += yb & 2u ? g0.y : 0.f; lo.z += yb & 4u ? g0.z : 0.f; lo.w += yb & 8u ? g0.w : 0.f;
-        hi.x += yb & 16u ? g1.x : 0.f; hi.y += yb & 32u ? g1.y : 0.f; hi.z += yb & 64u ? g1.z : 0.f; hi.w += yb & 128u ? g1.w : 0.f;
+    auto residual = [&](int c, f32x4& lo, f32x4& hi, const Grad& g) {
+        const uint32_t yb = PARTS > 1 ? lds_raw[bn::MASK_OFF + c] : 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            lo[e] += PARTS > 1 ? masked_by(yb, mask_bit(e), g.g0[e]) : g.g0[e];
+            hi[e] += PARTS > 1 ? masked_by(yb, mask_bit(e + 4), g.g1[e]) : g.g1[e];
+        }
     };
     if (!binary) {
         float* dst = route_mf(a, a.gdst0[node]);
-        through_lds([&](int c, int i) { return grad(c, i); },
-                    [&](int c, f32x4 lo, f32x4 hi, const Grad& g) {
-                        residual(c, lo, hi, g.g0, g.g1);
+        through_lds([](int) { return Nothing{}; },
+                    [&](int c, f32x4 lo, f32x4 hi, const Nothing&, int i) {
+                        residual(c, lo, hi, grad(i));
                         store_piece(dst, c, lo, hi);
                     });
         NCLK(5);
@@ -669,15 +650,13 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
     {
         const u32x4* u4 = reinterpret_cast<const u32x4*>(a.sv_u + item_off);
         u32x4* sdc4 = reinterpret_cast<u32x4*>(a.sv_dc + item_off);
-        through_lds([&](int c, int i) { const Grad g = grad(c, i); return GradU{g.g0, g.g1, u4[c]}; },
-                    [&](int c, f32x4 lo, f32x4 hi, const GradU& g) {
-                        residual(c, lo, hi, g.g0, g.g1);
-                        const uint32_t ub = piece_mask(g.u);
-                        u32x4 pk;
-                        pk.x = pack_bf16x2(ub & 1u ? lo.x : 0.f, ub & 2u ? lo.y : 0.f);
-                        pk.y = pack_bf16x2(ub & 4u ? lo.z : 0.f, ub & 8u ? lo.w : 0.f);
-                        pk.z = pack_bf16x2(ub & 16u ? hi.x : 0.f, ub & 32u ? hi.y : 0.f);
-                        pk.w = pack_bf16x2(ub & 64u ? hi.z : 0.f, ub & 128u ? hi.w : 0.f);
+        through_lds([&](int c) { return u4[c]; },
+                    [&](int c, f32x4 lo, f32x4 hi, const u32x4& u, int i) {
+                        residual(c, lo, hi, grad(i));
+                        const uint32_t ub = positive_mask(u);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { lo[e] = masked_by(ub, mask_bit(e), lo[e]); hi[e] = masked_by(ub, mask_bit(e + 4), hi[e]); }
+                        const u32x4 pk = {pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w), pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w)};
                         *reinterpret_cast<u32x4*>(lds_raw + centre_addr(c)) = pk;
                         sdc4[c] = pk;
                     });
@@ -692,11 +671,11 @@ __global__ __launch_bounds__(256, 1) void k_bwd_node_mfma(BmArgs a)
         zero(acc);
         kloop1<MTB, true>(acc, caddr, w1f, t1row + 8 * FRAG);
         float* d0 = route_mf(a, a.gdst0[node]);
-        through_lds([](int, int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d0, c, lo, hi); });
+        through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&, int) { store_piece(d0, c, lo, hi); });
         zero(acc);
         kloop1<MTB, false>(acc, caddr, w1f, nullptr);
         float* d1 = route_mf(a, a.gdst1[node]);
-        through_lds([](int, int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&) { store_piece(d1, c, lo, hi); });
+        through_lds([](int) { return Nothing{}; }, [&](int c, f32x4 lo, f32x4 hi, const Nothing&, int) { store_piece(d1, c, lo, hi); });
     }
 }
 
@@ -1177,13 +1156,14 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
     const char* d = static_cast<const char*>(p->dev_buf);
     const dynb_item* d_items = reinterpret_cast<const dynb_item*>(d);
     BmArgs a;
-    a.feats = static_cast<const bf16_t*>(feats); a.out = static_cast<const bf16_t*>(out); a.slots = static_cast<const bf16_t*>(fwd_ws);
     a.pk3bT = reinterpret_cast<const bf16_t*>(ws + L.pk3bT); a.pk3aT = reinterpret_cast<const bf16_t*>(ws + L.pk3aT);
     a.pk1T = reinterpret_cast<const bf16_t*>(ws + L.pk1T);
     a.gy = gy; a.dout = in_place ? dout : nullptr; a.gleaf = reinterpret_cast<float*>(ws + L.gleaf);
     // u and mid of every item: where the forward pass of a DYNB_PLAN_KEEP plan put them
-    a.sv_m = reinterpret_cast<const bf16_t*>(static_cast<const char*>(fwd_ws) + dynb_fast_keep_offset(p));
-    a.sv_u = a.sv_m + n_items_all * chw;
+    const bf16_t* const sv_m = reinterpret_cast<const bf16_t*>(static_cast<const char*>(fwd_ws) + dynb_fast_maps_offset(p));
+    a.sv_u = sv_m + n_items_all * chw;
+    a.mask_y = static_cast<const unsigned char*>(fwd_ws) + dynb_fast_keep_offset(p);
+    a.mask_m = a.mask_y + n_items_all * dynb_fast_mask_bytes();
     a.sv_g = reinterpret_cast<bf16_t*>(ws + L.sv_g); a.sv_dm = reinterpret_cast<bf16_t*>(ws + L.sv_dm);
     a.sv_dc = reinterpret_cast<bf16_t*>(ws + L.sv_dc);
     for (size_t li = p->launches.size(); li-- > 0;) {
@@ -1193,6 +1173,7 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         a.gdst1 = reinterpret_cast<const int32_t*>(pd + KT.gdst1) + l.start;
         const int parts = p->throughput ? 1 : parts_for(l.count);
         const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
+        a.per_xcd = int32_t(grid / 8);
         auto* kernel = parts == 28 ? k_bwd_node_mfma<7, 4> : parts == 14 ? k_bwd_node_mfma<7, 2> : parts == 7 ? k_bwd_node_mfma<7> : parts == 4 ? k_bwd_node_mfma<4> : parts == 2 ? k_bwd_node_mfma<2> : k_bwd_node_mfma<1>;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), bn::LDS_BYTES, st, a);
     }
@@ -1206,8 +1187,8 @@ int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const vo
         q.n_chunks = 0; q.n_joins = 0;
         for (const dynb_wg_group& wg : p->wg_groups) (wg.mode == 2 ? q.n_joins : q.n_chunks) += wg.n_units;
         q.n_chunks /= 3;                                      // (a unit for each kernel row)
-        q.feats = a.feats; q.slots = a.slots;
-        q.sv_u = a.sv_u; q.sv_m = a.sv_m; q.sv_g = a.sv_g; q.sv_dm = a.sv_dm; q.sv_dc = a.sv_dc;
+        q.feats = static_cast<const bf16_t*>(feats); q.slots = static_cast<const bf16_t*>(fwd_ws);
+        q.sv_u = a.sv_u; q.sv_m = sv_m; q.sv_g = a.sv_g; q.sv_dm = a.sv_dm; q.sv_dc = a.sv_dc;
         q.partial = reinterpret_cast<float*>(ws + L.partial);
         q.dw3a = g->dw3a; q.db3a = g->db3a; q.dw3b = g->dw3b; q.db3b = g->db3b; q.dw1 = g->dw1; q.db1 = g->db1;
         const unsigned sets = unsigned((q.n_chunks + 7) / 8 + (q.n_joins + 7) / 8);

@@ -67,6 +67,8 @@ __device__ long long* g_phase_clk = nullptr;      // [workgroup][wave][16]
 struct MfArgs {
     const dynb_item* items;
     int32_t count;
+    // workgroups of a die's run
+    int32_t per_xcd;
     const bf16_t* feats;
     bf16_t* out;
     bf16_t* slots;
@@ -76,10 +78,11 @@ struct MfArgs {
     const float* b3a;
     const bf16_t* w3b;
     const float* b3b;
-    // plans that keep what the backward pass needs: u of two-argument functions and mid, one map per item
+    // plans that keep what the backward pass needs (dynb_fast_keep_offset, plan_internal.h): masks of the results and of mid, mid, and u of two-argument
+    // functions, one of each per item
     int32_t first_item;       // index of items[0] in the plan
-    bf16_t* keep_u;           // [n_items][P*C]
-    bf16_t* keep_m;
+    int32_t n_items;
+    char* keep;
 };
 
 
@@ -119,7 +122,7 @@ __global__ void k_pack_weights(PackArgs a)
 // up to one node per CU, with twice the weight ring in 346 registers, was 3 % slower: the accumulators then live in
 // the upper half of the register file, and every other use of them is a copy.)
 // One workgroup's share of a launch group: position `logical` (a node, or a part of one) of the items a.items[0 .. a.count).
-// KEEP: u (two-argument functions) and mid are also written to a.keep_u / a.keep_m.  SPLIT: workgroups that share a part, each with
+// KEEP: u (two-argument functions) and mid are also written behind a.keep, and the masks of mid and the result.  SPLIT: workgroups that share a part, each with
 // 4 / SPLIT channel tiles of the second conv (parts_for).
 template <int PARTS, bool KEEP = false, int SPLIT = 1>
 __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
@@ -180,18 +183,32 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
             }
         }
     };
-    // the centre of the halo tile -> a map, this workgroup's output rows (and share of the channels), in coalesced 16-byte pieces
-    auto copy_out = [&](bf16_t* dst) {
+    // the centre of the halo tile -> a map, this workgroup's output rows (and share of the channels), in coalesced 16-byte pieces, and the map's mask
+    // (1 to 1.5 us of a whole node's 33.  Four lanes' bytes put together, for a quarter of the stores: the registers do not suffice, 41 us.)
+    auto copy_out = [&](bf16_t* dst, auto&& mask) {
         constexpr int OUTPIECES = Shape::ROWS * S * 16;
+        int t = tid;
+        if constexpr (KEEP) asm volatile("" : "+v"(t));          // (the pieces' addresses made anew, not kept beside the sums from one map to the next)
 #pragma unroll
         for (int i = 0; i < (OUTPIECES + NTHR - 1) / NTHR; ++i) {
-            const int c = orow0 * S * 16 + tid + i * NTHR;
+            const int c = orow0 * S * 16 + t + i * NTHR;
             if (c < orow1 * S * 16 && (SPLIT == 1 || (c & 15) / (16 / SPLIT) == share)) {
                 const int p = c >> 4, part = c & 15;
-                reinterpret_cast<u32x4*>(dst)[c] = *reinterpret_cast<const u32x4*>(
-                    lds_raw + uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16));
+                const u32x4 v = *reinterpret_cast<const u32x4*>(lds_raw + uint32_t((p / S + 1) * ROW_BYTES + (p % S + 1) * PIX_BYTES + part * 16));
+                reinterpret_cast<u32x4*>(dst)[c] = v;
+                mask(c, v);
             }
         }
+    };
+    auto no_mask = [](int, const u32x4&) {};
+    // kept: masks of the results | of mid | (256-byte aligned) mid | u
+    unsigned char* const mask_y = KEEP ? reinterpret_cast<unsigned char*>(a.keep) : nullptr;
+    unsigned char* const mask_m = KEEP ? mask_y + size_t(a.n_items) * (P * C / 8) : nullptr;
+    bf16_t* const keep_m = KEEP ? reinterpret_cast<bf16_t*>(a.keep + dynb_align256(2 * size_t(a.n_items) * (P * C / 8))) : nullptr;
+    bf16_t* const keep_u = KEEP ? keep_m + size_t(a.n_items) * (P * C) : nullptr;
+    auto mask_to = [&](unsigned char* masks) {
+        unsigned char* const m = masks + keep_at * (C / 8);
+        return [m](int c, const u32x4& v) { m[uint32_t(c)] = static_cast<unsigned char>(positive_mask(v)); };
     };
     auto arg_map = [&](int32_t s) { return s >= 0 ? a.slots + size_t(s) * (P * C) : a.feats + size_t(-1 - s) * (P * C); };
     // Loads return in the order they were issued: the argument map (needed first) goes ahead of the weight ring,
@@ -293,7 +310,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
                 }
             }
         __syncthreads();
-        if constexpr (KEEP) copy_out(a.keep_u + keep_at * C);
+        if constexpr (KEEP) copy_out(keep_u + keep_at * C, no_mask);
     }
 
     // ---- first conv3x3 + ReLU, result replaces the tile; the old centre values become the residual
@@ -351,7 +368,7 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
     __syncthreads();
     PHASE(7);
 
-    if constexpr (KEEP) copy_out(a.keep_m + keep_at * C);
+    if constexpr (KEEP) copy_out(keep_m + keep_at * C, mask_to(mask_m));
 
     // ---- second conv3x3 on top of (residual + bias), ReLU, scatter.  The result leaves through the tile: in the
     // accumulators a lane holds 32 bytes of a pixel, and stores in which every lane touches a line of its own take 4.4k
@@ -366,7 +383,9 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
             for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(lds_raw + centre_b(t) + uint32_t(q * 16)) = packed(acc_b[t], q);
     }
     __syncthreads();
-    copy_out(it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C));
+    bf16_t* const dst = it.dst >= 0 ? a.slots + size_t(it.dst) * (P * C) : a.out + size_t(-1 - it.dst) * (P * C);
+    if constexpr (KEEP) copy_out(dst, mask_to(mask_y));
+    else copy_out(dst, no_mask);
     PHASE(9);
 }
 
@@ -376,8 +395,7 @@ __global__ __launch_bounds__(256, 2) void k_module_mfma(MfArgs a)
     // Workgroup -> position in the launch group.  Consecutive workgroup ids land on different
     // XCDs; give every XCD one contiguous run of items (items are sorted by function id) so that
     // a function's weights stay in as few L2s as possible.
-    const int per_xcd = gridDim.x >> 3;
-    module_body<PARTS, KEEP, SPLIT>(a, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    module_body<PARTS, KEEP, SPLIT>(a, (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3));
 }
 
 // ---- one dependency-driven launch per batch ---------------------------------------------------------
@@ -585,7 +603,7 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
             const dynb_item* items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
             a.first_kept = p->keep ? l.start + off : off;
             if (whole) {
-                const NodeArgs nw = {w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b, count, p->keep ? 1 : 0};
+                const NodeArgs nw = {count, p->keep ? 1 : 0, (count + 7) / 8, 0, w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b};
                 const int rc = launch_node<T>(items, nw, a, st);
                 if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a launch group could not be launched");
                 continue;
@@ -649,7 +667,7 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
     const char* d = static_cast<const char*>(p->dev_buf);
-    MfArgs a;
+    MfArgs a = {};
     a.feats = static_cast<const bf16_t*>(feats);
     a.out = static_cast<bf16_t*>(out);
     a.slots = reinterpret_cast<bf16_t*>(ws);
@@ -666,11 +684,8 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
     a.w3a = pk3a; a.b3a = w->b3a;
     a.w3b = pk3b; a.b3b = w->b3b;
     a.first_item = 0;
-    a.keep_u = a.keep_m = nullptr;
-    if (p->keep) {
-        a.keep_m = reinterpret_cast<bf16_t*>(ws + dynb_fast_keep_offset(p));
-        a.keep_u = a.keep_m + p->items.size() * size_t(mf::P) * mf::C;
-    }
+    a.n_items = int32_t(p->items.size());
+    a.keep = p->keep ? ws + dynb_fast_keep_offset(p) : nullptr;
     const bool timed = dynb::timing_on(), coarse = dynb::timing_coarse();
     if (p->persistent) {
         // one launch for the whole batch: clear the ready flags, the ticket counter and the status word with a
@@ -709,6 +724,7 @@ static int run_mfma(const dynb_plan* p, const dynb_module_weights* w, const void
         // flight (their narrow groups share the chip), one node per workgroup
         const int parts = p->throughput ? 1 : parts_for(l.count);
         const unsigned grid = unsigned((parts * l.count + 7) / 8 * 8);
+        a.per_xcd = int32_t(grid / 8);
         auto* kernel = parts == 28  ? (p->keep ? k_module_mfma<7, true, 4> : k_module_mfma<7, false, 4>)
                        : parts == 14 ? (p->keep ? k_module_mfma<7, true, 2> : k_module_mfma<7, false, 2>)
                        : parts == 7 ? (p->keep ? k_module_mfma<7, true> : k_module_mfma<7>)

@@ -211,6 +211,25 @@ __device__ __forceinline__ void kloop1(f32x16 (&acc)[MTW], const Addr& xaddr, bf
     if (WNEXT) wf[7] = *reinterpret_cast<const bf16x8*>(wnext + 7 * mf::FRAG);
 }
 
+// ---- ReLU masks ---------------------------------------------------------------------------------------
+// What the backward pass wants to know of a result or of mid is which elements are positive.  The forward pass of a DYNB_PLAN_KEEP plan notes it
+// in one byte per 16-byte piece (8 channels of a pixel): 6 KB a node that the backward pass reads instead of 100 KB of maps.
+constexpr int mask_bit(int e) { return (e >> 1) + 4 * (e & 1); }       // element e's bit
+// of a piece behind a ReLU (no half is negative: positive is not zero), in the low eight bits
+__device__ __forceinline__ uint32_t positive_mask(const u32x4& v)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, uint32_t(v[i])), u16x2{1, 1})) << i;
+    return r | r >> 12;
+}
+// v where bit `bit` of m is set, else 0
+__device__ __forceinline__ float masked_by(uint32_t m, int bit, float v)
+{
+    return __uint_as_float(__float_as_uint(v) & uint32_t(__builtin_amdgcn_sbfe(int(m), bit, 1)));
+}
+
 // ---- parts of a node --------------------------------------------------------------------------------
 // A node is spread over PARTS workgroups, each with a share of the output rows:
 //   PARTS      output rows      rows of the first conv's window (pixel tiles)    of the second's

@@ -75,7 +75,7 @@ struct dynb_plan {
 
 // Device buffer of an uploaded plan: items | ids of single-SCENE examples | arity table | tickets | the backward
 // pass's tables (DYNB_PLAN_KEEP), each part padded to 256 bytes.
-inline size_t dynb_align256(size_t v) { return (v + 255) & ~size_t(255); }
+inline constexpr size_t dynb_align256(size_t v) { return (v + 255) & ~size_t(255); }
 inline size_t dynb_plan_items_bytes(const dynb_plan* p) { return dynb_align256(p->items.size() * sizeof(dynb_item)); }
 inline size_t dynb_plan_leaf_bytes(const dynb_plan* p) { return dynb_align256(p->leaf_roots.size() * sizeof(int32_t)); }
 inline size_t dynb_plan_arity_offset(const dynb_plan* p) { return dynb_plan_items_bytes(p) + dynb_plan_leaf_bytes(p); }
@@ -105,7 +105,8 @@ inline dynb_keep_tables dynb_plan_keep_tables(const dynb_plan* p)
 // Workspace of dynbatch_execute on the fused kernels' shape (bf16, C = 128, 14 x 14), in this order:
 //   slots | module weights in fragment order (w3a, w3b: 9 taps, w1: 2 halves; 128 x 128 bf16 per tap and function)
 //   | DYNB_PLAN_PERSISTENT: ready[n_slots], ticket counter, status word
-//   | DYNB_PLAN_KEEP: mid of every item, then u of every item (written for two-argument functions), for the backward pass
+//   | DYNB_PLAN_KEEP: which elements of every item's result are positive, then which ones of its mid (a byte for 8 channels of a pixel); mid of
+//     every item, then u of every item (written for two-argument functions), for the backward pass
 inline size_t dynb_fast_map_bytes() { return size_t(14) * 14 * 128 * 2; }
 inline size_t dynb_fast_packed_weight_bytes(int n_types) { return size_t(n_types) * (9 + 9 + 2) * 128 * 128 * 2; }
 inline size_t dynb_fast_sync_offset(const dynb_plan* p)
@@ -114,7 +115,13 @@ inline size_t dynb_fast_sync_offset(const dynb_plan* p)
 }
 inline size_t dynb_fast_sync_bytes(const dynb_plan* p) { return p->persistent ? dynb_align256((size_t(p->n_slots) + 2) * sizeof(int32_t)) : 0; }
 inline size_t dynb_fast_keep_offset(const dynb_plan* p) { return dynb_fast_sync_offset(p) + dynb_fast_sync_bytes(p); }
-inline size_t dynb_fast_keep_bytes(const dynb_plan* p) { return p->keep ? dynb_align256(2 * p->items.size() * dynb_fast_map_bytes()) : 0; }
+inline size_t dynb_fast_mask_bytes() { return size_t(14) * 14 * 128 / 8; }
+inline size_t dynb_fast_masks_bytes(const dynb_plan* p) { return dynb_align256(2 * p->items.size() * dynb_fast_mask_bytes()); }
+inline size_t dynb_fast_maps_offset(const dynb_plan* p) { return dynb_fast_keep_offset(p) + dynb_fast_masks_bytes(p); }
+inline size_t dynb_fast_keep_bytes(const dynb_plan* p)
+{
+    return p->keep ? dynb_fast_masks_bytes(p) + dynb_align256(2 * p->items.size() * dynb_fast_map_bytes()) : 0;
+}
 
 // ... and on every other shape: slots | mid | u; for a DYNB_PLAN_KEEP plan mid of every item and u of the two-argument functions (the
 // backward pass reads them), else both for the items of one launch group; `map` = bytes of one map
