@@ -355,7 +355,6 @@ void launch_leaves(const dynb_plan* p, const float* gleaf, const int32_t* leaf_f
 // function by function afterwards.
 struct BmArgs {
     const dynb_item* items;       // the launch group's items
-    int32_t per_xcd;              // workgroups of a die's run
     const int32_t* gdst0;         // routes of the group's items
     const int32_t* gdst1;
     int32_t first_item;
@@ -372,6 +371,7 @@ struct BmArgs {
     bf16_t* sv_g;
     bf16_t* sv_dm;
     bf16_t* sv_dc;
+    int32_t per_xcd;              // workgroups of a die's run
 };
 
 __device__ __forceinline__ float* route_mf(const BmArgs& a, int32_t r)

@@ -645,13 +645,11 @@ __global__ __launch_bounds__(256) void k_conv_plain(const dynb_item* items, Conv
 // work is MT x 16 pixels x 16 output channels, a wave takes every eighth.  Joins read their arguments' fragments straight
 // from global memory (every element is used once per channel tile) and leave u in the first tile.
 struct NodeArgs {
-    int32_t count;
-    int32_t keep;                 // u and mid are also written to the maps of the backward pass
-    int32_t per_xcd;              // workgroups of a die's run
-    int32_t pad;
     const void* w1; const float* b1;
     const void* w3a; const float* b3a;
     const void* w3b; const float* b3b;
+    int32_t count;
+    int32_t keep;                 // u and mid are also written to the maps of the backward pass
 };
 
 struct NodeKernelArgs { const dynb_item* items; NodeArgs nw; ConvArgs a; };             // k_node's parameters
@@ -667,7 +665,7 @@ __device__ __forceinline__ void node_again(bool mid_nan, bool nan)
     asm volatile("" : "+s"(args));
     const NodeKernelArgs k = *static_cast<const NodeKernelArgs*>(args);
     const ConvArgs& a = k.a;
-    const int i = int(blockIdx.x & 7) * k.nw.per_xcd + int(blockIdx.x >> 3);
+    const int i = int(blockIdx.x & 7) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
     const dynb_item it = k.items[i];
     const int C = a.C, H = a.H, W = a.W, P = H * W, pix_bytes = conv_pixel_bytes(a.ck, int(sizeof(T))), row_bytes = (W + 2) * pix_bytes;
     const uint32_t second = uint32_t((H + 2) * row_bytes);                              // the second tile
@@ -717,7 +715,7 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
     constexpr int ES = int(sizeof(T)), KS = First::KS, PE = First::PE, NTHR = 512, NWAVE = 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     // consecutive workgroups go to the chip's 8 dies in turn: every die gets one run of items (they are sorted by function)
-    const int i = int(blockIdx.x & 7) * nw.per_xcd + int(blockIdx.x >> 3);
+    const int i = int(blockIdx.x & 7) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
     if (i >= nw.count) return;
     const dynb_item it = items[i];
     const bool binary = it.src1 != DYNB_NO_ARG;           // uniform over the workgroup

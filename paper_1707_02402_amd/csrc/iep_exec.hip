@@ -67,8 +67,7 @@ __device__ long long* g_phase_clk = nullptr;      // [workgroup][wave][16]
 struct MfArgs {
     const dynb_item* items;
     int32_t count;
-    // workgroups of a die's run
-    int32_t per_xcd;
+    int32_t first_item;       // index of items[0] in the plan
     const bf16_t* feats;
     bf16_t* out;
     bf16_t* slots;
@@ -78,9 +77,12 @@ struct MfArgs {
     const float* b3a;
     const bf16_t* w3b;
     const float* b3b;
+    // Workgroups of a die's run.  (Here and not next to count: the arguments lie in host memory, a cache line of 64 bytes at a time, and what a workgroup wants
+    // first should bring both lines with it.  With the grid's size for it and two fields more, which put that into a third line, a launch took
+    // 0.15 us longer, and so it did with this field in the first: one program 162.6 / 166 us.)
+    int32_t per_xcd;
     // plans that keep what the backward pass needs (dynb_fast_keep_offset, plan_internal.h): masks of the results and of mid, mid, and u of two-argument
     // functions, one of each per item
-    int32_t first_item;       // index of items[0] in the plan
     int32_t n_items;
     char* keep;
 };
@@ -603,7 +605,7 @@ static int run_generic(const dynb_plan* p, const dynb_shape* s, const dynb_modul
             const dynb_item* items = reinterpret_cast<const dynb_item*>(d) + l.start + off;
             a.first_kept = p->keep ? l.start + off : off;
             if (whole) {
-                const NodeArgs nw = {count, p->keep ? 1 : 0, (count + 7) / 8, 0, w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b};
+                const NodeArgs nw = {w->w1, w->b1, w->w3a, w->b3a, w->w3b, w->b3b, count, p->keep ? 1 : 0};
                 const int rc = launch_node<T>(items, nw, a, st);
                 if (rc != DYNB_OK) return fail(rc, "dynbatch_execute: a launch group could not be launched");
                 continue;
