@@ -33,8 +33,6 @@ namespace {
 enum ConvMode { CV_JOIN, CV_FIRST, CV_SECOND, CV_DSECOND, CV_DFIRST, CV_DJOIN, CV_JOIN_BOTH };
 
 struct ConvArgs {
-    uint32_t runs;                // recip_of(workgroups of an item), or 0: they stay in their order.  (First: what a workgroup waits for before it knows its item.)
-    uint32_t pad;
     int32_t first_item;           // index of items[0] among the items that gy, dm and du hold a map for
     int32_t first_kept;           // index of items[0] among the maps of u and mid
     // (u and du of kept plans hold maps for two-argument functions only, and the pointers are such that the same indices find them)
@@ -59,6 +57,8 @@ struct ConvArgs {
     int32_t n_ctile;              // channel tiles
     int32_t ck;                   // input channels staged at a time
     uint32_t m_sw;                // recip20_of(sw)
+    // recip_of(workgroups of an item), or 0: they stay in their order.  (Last: what a workgroup waits for first brings these arguments' line with it.)
+    uint32_t runs;
 };
 
 typedef u32x4 u32x4_any __attribute__((aligned(2)));      // 16 and 8 bytes at any element's address

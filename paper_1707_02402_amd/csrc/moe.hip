@@ -66,10 +66,12 @@ __device__ __forceinline__ float softplus_f(float z)
     return fmaxf(z, 0.f) + fmaf(0.6931471805599453f, __builtin_amdgcn_logf(w), c);
 }
 
+// clear (if not null): a counter that the next launch wants at zero
 __global__ __launch_bounds__(256) void k_gate(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg,
                                               const bf16_t* __restrict__ Wn, const float* __restrict__ noise,
-                                              float* __restrict__ logits, int T, int d, int E)
+                                              float* __restrict__ logits, int T, int d, int E, int32_t* __restrict__ clear)
 {
+    if (clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear = 0;
     __shared__ __attribute__((aligned(16))) bf16_t Ws[128 * GLDP];   // rows 0..63 Wg, 64..127 Wn
     __shared__ __attribute__((aligned(16))) bf16_t Xs[64 * GLDP];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -146,8 +148,9 @@ constexpr int GS_UN = 4;               // K-steps of 32 requested together
 
 __global__ __launch_bounds__(256) void k_gate_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg,
                                                     const bf16_t* __restrict__ Wn, const float* __restrict__ noise,
-                                                    float* __restrict__ logits, int T, int d, int E)
+                                                    float* __restrict__ logits, int T, int d, int E, int32_t* __restrict__ clear)
 {
+    if (clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear = 0;
     __shared__ f32x4 part[4][2][64];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int t0 = blockIdx.y * 16, e0 = blockIdx.x * 16;
@@ -436,13 +439,11 @@ __device__ __forceinline__ int wave_max_step(int v)
 }
 
 template <int NV>
-__global__ __launch_bounds__(256) void k_topk_small(const float* __restrict__ logits, int32_t* __restrict__ topk_idx,
-                                                    float* __restrict__ topk_w, int T, int E, int k)
+__device__ __forceinline__ void topk_row(const float* __restrict__ logits, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, const int t,
+                                         int E, int k)
 {
     static_assert(NV % 4 == 0, "registers in groups of four consecutive experts");
     const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= T) return;
     const float* row = logits + size_t(t) * E;
     constexpr int TAKEN = int(0x80000000);           // below the key of -infinity (0x807fffff)
     // register 4 i + c holds expert 256 i + 4 lane + c: one 16-byte load per i where the row allows it
@@ -520,6 +521,14 @@ __global__ __launch_bounds__(256) void k_topk_small(const float* __restrict__ lo
             topk_idx[size_t(t) * k + j] = chosen[j];
             topk_w[size_t(t) * k + j] = ex[j] / den;
         }
+}
+
+template <int NV>
+__global__ __launch_bounds__(256) void k_topk_small(const float* __restrict__ logits, int32_t* __restrict__ topk_idx,
+                                                    float* __restrict__ topk_w, int T, int E, int k)
+{
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (t < T) topk_row<NV>(logits, topk_idx, topk_w, t, E, k);
 }
 
 // ------------------------------------------------------------------------------------------ grouping
@@ -719,17 +728,15 @@ __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict_
 constexpr int MID_BLOCKS = 64;
 __host__ __device__ constexpr int mid_stride(int E) { return (E + 3) & ~3; }      // experts of a row of blockcnt
 
-__global__ __launch_bounds__(256) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
+// A block of 256 threads ranks 1024 uses: thread's use i is first + wave * 256 + i * 64 + lane (my: its expert, -1: none), before: the number of earlier
+// ones of the block with that expert.  count[] (LDS): the experts' uses after
+__device__ __forceinline__ void rank_1024(const int (&my)[4], int (&before)[4], int32_t* count, int stride, int E)
 {
-    __shared__ __attribute__((aligned(16))) int32_t count[SMALL_EXPERTS];
     using i32x4 = int32_t __attribute__((ext_vector_type(4)));
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, stride = mid_stride(E);
-    // this wave's 256 uses, 64 at a time; among 64 the lanes with the same expert are those that agree in every bit of its number
-    const int a0 = blockIdx.x * 1024 + wave * 256 + lane;
-    int my[4], local[4], same[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) my[i] = a0 + i * 64 < A ? idx[a0 + i * 64] : -1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int local[4], same[4];
     for (int e = tid * 4; e < stride; e += 1024) *reinterpret_cast<i32x4*>(count + e) = i32x4{0, 0, 0, 0};
+    // among 64 the lanes with the same expert are those that agree in every bit of its number
     uint64_t peers[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) peers[i] = __ballot(my[i] >= 0);
@@ -751,15 +758,113 @@ __global__ __launch_bounds__(256) void k_rank_wide(const int32_t* __restrict__ i
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (my[i] >= 0) {
-                    const int before = count[my[i]] + local[i];
-                    if (local[i] == same[i] - 1) count[my[i]] = before + 1;          // (behind the wave's reads: its LDS accesses are executed in order)
-                    lrank[a0 + i * 64] = before;
+                    before[i] = count[my[i]] + local[i];
+                    if (local[i] == same[i] - 1) count[my[i]] = before[i] + 1;       // (behind the wave's reads: its LDS accesses are executed in order)
                 }
         }
         __syncthreads();
     }
+}
+
+__global__ __launch_bounds__(256) void k_rank_wide(const int32_t* __restrict__ idx, int32_t* __restrict__ lrank, int32_t* __restrict__ blockcnt, int A, int E)
+{
+    __shared__ __attribute__((aligned(16))) int32_t count[SMALL_EXPERTS];
+    using i32x4 = int32_t __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, stride = mid_stride(E);
+    const int a0 = blockIdx.x * 1024 + wave * 256 + lane;
+    int my[4], before[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) my[i] = a0 + i * 64 < A ? idx[a0 + i * 64] : -1;
+    rank_1024(my, before, count, stride, E);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (my[i] >= 0) lrank[a0 + i * 64] = before[i];
     for (int e = tid * 4; e < stride; e += 1024)
         *reinterpret_cast<i32x4*>(blockcnt + size_t(blockIdx.x) * stride + e) = *reinterpret_cast<const i32x4*>(count + e);
+}
+
+// Selection and grouping of at most SMALL_USES uses in one launch: the last workgroup to finish its tokens' selection groups all uses.  (A launch of
+// its own for the grouping waits for the selection's end, its arguments and the indices: one token, d 160, h 184, 82 experts 25.0 -> 22.3 us a pass, 37 tokens of
+// the small layer 42.2 -> 39.7.)
+// `done`: zero before the launch (the gate's kernels clear it).
+template <int NV>
+__global__ __launch_bounds__(256) void k_topk_group(const float* __restrict__ logits, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int T, int E,
+                                                    int k, int32_t* __restrict__ done, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                    int32_t* __restrict__ tile_start, int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                    RowTile* __restrict__ tiles, int max_tiles)
+{
+    __shared__ __attribute__((aligned(16))) int32_t first[64 * NV];           // counts, then the experts' first places
+    __shared__ int32_t wsum[4], wtsum[4], s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t = blockIdx.x * 4 + wave;
+    if (t < T) topk_row<NV>(logits, topk_idx, topk_w, t, E, k);
+    // every wave's stores have reached the L2, then one thread makes them visible to the chip and counts this workgroup in; the last one
+    // sees what all others have made visible
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __syncthreads();
+    if (tid == 0) s_last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == int(gridDim.x) - 1;
+    __syncthreads();
+    if (!s_last) return;
+    const int A = T * k, stride = mid_stride(E);
+    int my[4], before[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int a = wave * 256 + i * 64 + lane;
+        my[i] = a < A ? __hip_atomic_load(topk_idx + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+    }
+    rank_1024(my, before, first, stride, E);
+    using i32x4 = int32_t __attribute__((ext_vector_type(4)));
+    int carry = 0, tcarry = 0;
+    for (int e0 = 0; e0 < E; e0 += 1024) {                // as k_offsets, four experts a thread
+        const int e = e0 + tid * 4;
+        i32x4 c = {0, 0, 0, 0};
+        if (e < E) c = *reinterpret_cast<const i32x4*>(first + e);
+        const i32x4 tl = (c + (TM - 1)) / TM;
+        const int mine = c.x + c.y + c.z + c.w, tmine = tl.x + tl.y + tl.z + tl.w;
+        int inc = mine, tinc = tmine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            const int to = __shfl_up(tinc, off);
+            if (lane >= off) { inc += o; tinc += to; }
+        }
+        if (lane == 63) { wsum[wave] = inc; wtsum[wave] = tinc; }
+        __syncthreads();
+        int earlier = 0, tearlier = 0, all = 0, tall = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) { earlier += wsum[w]; tearlier += wtsum[w]; }
+            all += wsum[w];
+            tall += wtsum[w];
+        }
+        int at = carry + earlier + inc - mine, tat = tcarry + tearlier + tinc - tmine;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (e + i < E) {
+                first[e + i] = at;
+                counts[e + i] = c[i];
+                offsets[e + i] = at;
+                tile_start[e + i] = tat;
+                if (tiles)
+                    for (int q = 0; q < tl[i]; ++q) tiles[tat + q] = RowTile{e + i, at + q * TM, min(TM, c[i] - q * TM), 0};
+            }
+            at += c[i];
+            tat += tl[i];
+        }
+        carry += all;
+        tcarry += tall;
+        __syncthreads();
+    }
+    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
+    if (tiles)
+        for (int q = tcarry + tid; q < max_tiles; q += 256) tiles[q] = RowTile{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (my[i] >= 0) {
+            const int a = wave * 256 + i * 64 + lane, pos = first[my[i]] + before[i];
+            perm[pos] = a;
+            inv[a] = pos;
+        }
 }
 
 // block 0 also writes the experts' tables; tiles as in k_group_small
@@ -1356,31 +1461,18 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // up to some five 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d =
     // 1024, noisy: 500 21 / 11, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; without noise: 1000 15.5 / 12.8, 2000 16.4 / 20; d = 64: 1764
     // 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
+    // few uses, up to eight per token: the selection's last workgroup groups them (its counter lies where the ranks of many uses do)
+    const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
+    const bool joined = small && k <= MAX_K && E <= 32 * 64 && T > T_big;
+    int32_t* const done = joined ? lrank : nullptr;
     if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1200)
         hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),
-                           static_cast<const bf16_t*>(Wn), noise, logits, T, d, E);
+                           static_cast<const bf16_t*>(Wn), noise, logits, T, d, E, done);
     else if (T > T_big)
         hipLaunchKernelGGL(k_gate, dim3((E + 63) / 64, (T - T_big + 63) / 64), dim3(256), 0, st, xb + size_t(T_big) * d,
                            static_cast<const bf16_t*>(Wg), static_cast<const bf16_t*>(Wn), noise ? noise + size_t(T_big) * E : nullptr,
-                           logits + size_t(T_big) * E, T - T_big, d, E);
+                           logits + size_t(T_big) * E, T - T_big, d, E, done);
     if (timed) dynb::timing_mark(st, dynb::ST_GATE, 0);
-    // m2 top-k + softmax
-    const dim3 tk_grid((T + 3) / 4), tk_block(256);
-    if (k <= MAX_K && E <= 4 * 64)
-        hipLaunchKernelGGL((k_topk_small<4>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    else if (k <= MAX_K && E <= 16 * 64)
-        hipLaunchKernelGGL((k_topk_small<16>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    else if (k <= MAX_K && E <= 32 * 64)
-        hipLaunchKernelGGL((k_topk_small<32>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    else if (E <= 4 * 64)
-        hipLaunchKernelGGL((k_topk<4>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    else if (E <= 16 * 64)
-        hipLaunchKernelGGL((k_topk<16>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    else if (E <= 32 * 64)
-        hipLaunchKernelGGL((k_topk<32>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    else
-        hipLaunchKernelGGL((k_topk<0>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
-    if (timed) dynb::timing_mark(st, dynb::ST_TOPK, 0);
     // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
     // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
@@ -1400,7 +1492,6 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // mean, and 26 % at worst; with the first limit alone, whatever the rows, 1.8 and 90 %.)
     // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
     // each like the smallest token).
-    const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
     const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
     const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
     auto skinny_layer = [&](int N, int K) {
@@ -1414,7 +1505,28 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     };
     const bool skinny1 = skinny_layer(h, d), skinny2 = skinny_layer(d, h), skinny = skinny1 || skinny2;
     RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
-    if (small) {
+    // m2 top-k + softmax
+    const dim3 tk_grid((T + 3) / 4), tk_block(256);
+    if (joined) {
+        auto* const kernel = E <= 4 * 64 ? k_topk_group<4> : E <= 16 * 64 ? k_topk_group<16> : k_topk_group<32>;
+        hipLaunchKernelGGL(kernel, tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k, done, counts, offsets, tile_start, perm, inv, tiles, skinny_tiles);
+    } else if (k <= MAX_K && E <= 4 * 64)
+        hipLaunchKernelGGL((k_topk_small<4>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    else if (k <= MAX_K && E <= 16 * 64)
+        hipLaunchKernelGGL((k_topk_small<16>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    else if (k <= MAX_K && E <= 32 * 64)
+        hipLaunchKernelGGL((k_topk_small<32>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    else if (E <= 4 * 64)
+        hipLaunchKernelGGL((k_topk<4>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    else if (E <= 16 * 64)
+        hipLaunchKernelGGL((k_topk<16>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    else if (E <= 32 * 64)
+        hipLaunchKernelGGL((k_topk<32>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    else
+        hipLaunchKernelGGL((k_topk<0>), tk_grid, tk_block, 0, st, logits, topk_idx, topk_w, T, E, k);
+    if (timed) dynb::timing_mark(st, dynb::ST_TOPK, 0);
+    if (joined) {
+    } else if (small) {
         hipLaunchKernelGGL(k_group_small, dim3(1), dim3(1024), 0, st, topk_idx, counts, offsets, tile_start, perm, inv, tiles,
                            skinny_tiles, A, E);
     } else if (mid) {

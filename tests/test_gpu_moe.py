@@ -453,3 +453,22 @@ def test_random_small_shapes(dyn, util, oracle):
         r = check_routing(oracle, m, aux)
         ref = oracle.moe_experts(m.x, r.topk_idx, r.topk_w, W1, W2)
         assert util.normwise(out, ref) < OUT_TOL, shape
+
+
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1, 64, 8), (128, 8, 8), (1024, 3, 1), (1023, 2047, 1), (512, 257, 2), (341, 1025, 3), (127, 2048, 8), (128, 2048, 8),
+                                   (5, 2049, 2), (129, 300, 8), (114, 9, 9), (1024, 1, 1)])
+def test_selection_and_grouping_in_one_launch_and_around_its_limits(dyn, util, oracle, T, E, k):
+    """Up to 1024 uses, eight of a token and 2048 experts the selection's last workgroup groups the uses; one use, expert or token beyond, launches of their
+    own do.  Three passes over one workspace whose contents are arbitrary before the first: the counter is the layer's own affair."""
+    import torch
+    m = moe.small(seed=T + 3 * E + k, T=T, d=16, h=8, E=E, k=k, empty_frac=0.0)
+    W1, W2 = stack(m)
+    dev = util.moe_inputs_dev(m, W1, W2)
+    ws = torch.full((dyn.moe_workspace_bytes(T, 16, 8, E, k),), 0xA5, dtype=torch.uint8, device="cuda")
+    first = None
+    for _ in range(3):
+        out, aux = dyn.moe_forward(dev["x"], dev["Wg"], dev["Wn"], dev["noise"], dev["W1"], dev["W2"], k, want_aux=True, workspace=ws)
+        aux = {n: v.cpu().numpy() for n, v in vars(aux).items()}
+        check_routing(oracle, m, aux)
+        first = util.to_host(out) if first is None else first
+        assert (util.to_host(out) == first).all()
