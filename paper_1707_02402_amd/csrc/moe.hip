@@ -1461,9 +1461,12 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // up to some five 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d =
     // 1024, noisy: 500 21 / 11, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; without noise: 1000 15.5 / 12.8, 2000 16.4 / 20; d = 64: 1764
     // 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
-    // few uses, up to eight per token: the selection's last workgroup groups them (its counter lies where the ranks of many uses do)
+    // few uses, up to eight per token: the selection's last workgroup groups them (its counter lies where the ranks of many uses do), as long as the
+    // selection has no more than 128 workgroups to count.  us a pass replayed from a graph, d = h = 64, a launch more / so, by tokens x experts, uses of a
+    // token: 16 x 64, 2 20.0 / 17.7; 64 x 1024, 4 25.6 / 22.7; 128 x 256, 8 26.8 / 23.7; 256 x 64, 2 22.1 / 19.7; 512 x 256, 2 23.9 / 22.9; 512 x 2048,
+    // 2 34.9 / 32.7; 1024 x 64, 1 24.2 / 25.4; 1024 x 1024, 1 28.8 / 29.6
     const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
-    const bool joined = small && k <= MAX_K && E <= 32 * 64 && T > T_big;
+    const bool joined = small && k <= MAX_K && E <= 32 * 64 && T > T_big && T <= 512;
     int32_t* const done = joined ? lrank : nullptr;
     if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1200)
         hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),

@@ -455,10 +455,10 @@ def test_random_small_shapes(dyn, util, oracle):
         assert util.normwise(out, ref) < OUT_TOL, shape
 
 
-@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1, 64, 8), (128, 8, 8), (1024, 3, 1), (1023, 2047, 1), (512, 257, 2), (341, 1025, 3), (127, 2048, 8), (128, 2048, 8),
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1, 64, 8), (128, 8, 8), (1024, 3, 1), (1023, 2047, 1), (512, 257, 2), (513, 257, 1), (511, 2047, 2), (341, 1025, 3), (127, 2048, 8), (128, 2048, 8),
                                    (5, 2049, 2), (129, 300, 8), (114, 9, 9), (1024, 1, 1)])
 def test_selection_and_grouping_in_one_launch_and_around_its_limits(dyn, util, oracle, T, E, k):
-    """Up to 1024 uses, eight of a token and 2048 experts the selection's last workgroup groups the uses; one use, expert or token beyond, launches of their
+    """Up to 512 tokens, 1024 uses, eight of a token and 2048 experts the selection's last workgroup groups the uses; one use, expert or token beyond, launches of their
     own do.  Three passes over one workspace whose contents are arbitrary before the first: the counter is the layer's own affair."""
     import torch
     m = moe.small(seed=T + 3 * E + k, T=T, d=16, h=8, E=E, k=k, empty_frac=0.0)
