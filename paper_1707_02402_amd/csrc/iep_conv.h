@@ -13,7 +13,7 @@
 // fp32 operands use v_mfma_f32_16x16x4 (fp32 products and sums: 157 TFLOP/s on the chip, the vector unit without packed
 // instructions half of that), bf16 operands v_mfma_f32_16x16x32_bf16.  The kernel before this one gave every output element
 // to a thread that read its 9 C products' operands from the caches: 21 training programs in fp32 at C = 128, 14 x 14
-// went from 179 to 2.5 ms, 64 programs in bf16 at 7 x 7 from 45 to 0.6 ms.
+// went from 179 to 2.5 ms, 64 programs in bf16 at 7 x 7 from 45 to 0.6 ms (0.46 with what stands at ConvSteps, k_conv and launch_conv).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -1032,7 +1032,7 @@ inline bool node_wide(int pt, int ct) { return ((pt + 3) / 4 * ct + 7) / 8 * 4 <
 
 // Whole modules by k_node, where that takes one CU no longer than two or three launches of k_conv take to get going (5 us
 // each) and two tiles fit LDS.  A CU's time: its MFMAs, or its weights, of which one CU was seen to take in some 12 bytes a clock
-// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 24 to 32 us against 2 x 5 to 3 x 7),
+// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 16 to 22 us, in pairs of steps, against 2 x 5 to 5 + 2 x 9),
 // and with every round of units a wait for weights: one lone module, bf16 C = 48, 14 x 14, 5 rounds: 58 us against 15 by k_conv;
 // C = 20, 20 x 20, 7 rounds: 79 / 20 (and 35 by k_conv_plain); C = 24, 14 x 14, 1 round of wide units: 16 / 15.  Below 16 channels the
 // tiles are cut short and k_conv wins from two rounds on (bf16 C = 8, 14 x 14: 21 / 14) or with many modules (fp32 C = 6, 4 x 4,
