@@ -131,10 +131,16 @@ template <bool FULL, typename T> __device__ __forceinline__ f32x4 masked_gy(cons
 // v / d for d > 1, v * d < 2^32, with m = recip_of(d)
 __host__ __device__ constexpr uint32_t recip_of(uint32_t d) { return 0xffffffffu / d + 1u; }
 __device__ __forceinline__ uint32_t div_by(uint32_t v, uint32_t m) { return __umulhi(v, m); }
-// v / d for v < 4096, v * d < 2^20, with m = recip20_of(d); here v are the steps of a panel (at most 9 x 142: a 3x3 stages
+// v / d for v < 4096, v * d < 2^20, with m = recip20_of(d); here v are the steps of a 3x3's panel (at most 9 x 142: it stages
 // at least 9 pixels), pixels of a tile (1300) and columns of a segment (32)
 __host__ __device__ constexpr uint32_t recip20_of(uint32_t d) { return ((1u << 20) + d - 1) / d; }
-__device__ __forceinline__ uint32_t div20_by(uint32_t v, uint32_t m) { return v * m >> 20; }
+__host__ __device__ constexpr uint32_t div20_by(uint32_t v, uint32_t m) { return v * m >> 20; }
+// The tap of a panel's step s: nj steps a tap, m_nj = recip20_of(nj).  (Two taps, a join's arguments, are told apart without a division:
+// on maps of a pixel or two nj goes up to 1279, and s * nj beyond what div20_by is exact for.)
+template <int TAPS> __host__ __device__ constexpr int tap_of(int s, int nj, uint32_t m_nj)
+{
+    return TAPS == 1 ? 0 : TAPS == 2 ? int(s >= nj) : int(div20_by(uint32_t(s), m_nj));
+}
 
 template <ConvMode MODE> struct ConvTraits {
     static constexpr bool JOINS = MODE == CV_JOIN || MODE == CV_DJOIN || MODE == CV_JOIN_BOTH;
@@ -231,7 +237,7 @@ struct ConvSteps {
     // steps step .. step + G - 1 (one group)
     __device__ __forceinline__ void load_w(int step, u32x4 (&w)[NT][G]) const
     {
-        const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj;
+        const int s = s0 + step, tap = tap_of<TAPS>(s, nj, m_nj), j = s - tap * nj;
         const char* p = w_panel + (ptrdiff_t(tap) * w_tap + ptrdiff_t(j) * w_chan) * ptrdiff_t(sizeof(T));
         if constexpr (G == 2) {
 #pragma unroll
@@ -264,7 +270,7 @@ struct ConvSteps {
     // LDS offset of a group's pixels: of its first step; step i lies i pieces further
     __device__ __forceinline__ uint32_t x_group(int step) const
     {
-        const int s = s0 + step, tap = TAPS == 1 ? 0 : int(div20_by(s, m_nj)), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
+        const int s = s0 + step, tap = tap_of<TAPS>(s, nj, m_nj), j = s - tap * nj, kh = tap * 11 >> 5, kw = tap - 3 * kh;
         return uint32_t(kh * row_bytes + kw * pix_bytes + j * (KS * ES));
     }
     __device__ __forceinline__ void read_x(uint32_t off, int i, u32x4 (&v)[MT]) const
