@@ -55,3 +55,12 @@ template <> __device__ __forceinline__ void store_f32<bf16_t>(bf16_t* p, float v
 template <typename T> __device__ __forceinline__ float round_to(float v);
 template <> __device__ __forceinline__ float round_to<float>(float v) { return v; }
 template <> __device__ __forceinline__ float round_to<bf16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
+
+// Every store of this wave has been answered by the L2.  A workgroup-scope release and a barrier order a workgroup's accesses for its own
+// waves and do not wait for this: without it a wave may come to the barrier with its stores under way, and the agent-scope release of
+// another wave behind the barrier waits for that wave's only.
+__device__ __forceinline__ void wait_for_stores()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");    // (the compiler, too, keeps earlier stores ahead of what follows)
+    __builtin_amdgcn_s_waitcnt(0x0f70);                       // vmcnt(0)
+}

@@ -798,9 +798,9 @@ __global__ __launch_bounds__(256) void k_topk_group(const float* __restrict__ lo
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t = blockIdx.x * 4 + wave;
     if (t < T) topk_row<NV>(logits, topk_idx, topk_w, t, E, k);
-    // every wave's stores have reached the L2, then one thread makes them visible to the chip and counts this workgroup in; the last one
-    // sees what all others have made visible
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    // every wave waits until its stores have reached the L2, then one thread makes them visible to the chip and counts this workgroup in; the
+    // last one sees what all others have made visible
+    wait_for_stores();
     __syncthreads();
     if (tid == 0) s_last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == int(gridDim.x) - 1;
     __syncthreads();
