@@ -470,7 +470,7 @@ __global__ __launch_bounds__(256, 1) void k_module_persist(MfArgs a, PersistArgs
         // Publish: every wave waits until its stores of the result have reached the L2 (all waves of a
         // workgroup sit behind the same one), then one thread writes that L2's dirty lines back to memory,
         // where every CU can see them, and raises the flag (the agent-scope release does both).
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        wait_for_stores();
         __syncthreads();                                      // also frees the LDS tile for the next unit
         const int32_t dst = b.items[0].dst;
         if (threadIdx.x == 0 && dst >= 0)

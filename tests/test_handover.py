@@ -71,7 +71,7 @@ def undone(code):
     return total, bad
 
 
-@pytest.mark.parametrize("name,variants", [("k_topk_group", 3)])
+@pytest.mark.parametrize("name,variants", [("k_topk_group", 3), ("k_module_persist", 1)])
 def test_stores_are_done_before_the_barrier_of_a_handover(tmp_path, name, variants):
     found = kernels(tmp_path, name)
     assert len(found) == variants
