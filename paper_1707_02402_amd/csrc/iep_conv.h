@@ -57,8 +57,9 @@ struct ConvArgs {
     int32_t n_ctile;              // channel tiles
     int32_t ck;                   // input channels staged at a time
     uint32_t m_sw;                // recip20_of(sw)
-    // recip_of(workgroups of an item), or 0: they stay in their order.  (Last: what a workgroup waits for first brings these arguments' line with it.)
-    uint32_t runs;
+    // runs of items for the dies: recip_of(workgroups of an item) or 0 (they stay in their order); workgroups of an item; an eighth of all
+    // workgroups, and how many are left over.  (Last: what a workgroup waits for first brings these arguments' line with it.)
+    uint32_t runs, n_groups, run_q, run_r;
 };
 
 typedef u32x4 u32x4_any __attribute__((aligned(2)));      // 16 and 8 bytes at any element's address
@@ -390,12 +391,13 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
     // Consecutive workgroups go to the chip's 8 dies in turn: every die gets one run of the items' tiles, so that an item's map and its function's
     // weights (items are sorted by function) are fetched behind one L2 and not behind all (21 training programs, fp32, C = 128, 14 x 14: 2496 ->
     // 2374 us; 64 programs, bf16, 7 x 7: 492 -> 470).
+    // (Without a branch, and nothing of it from the grid's size: behind a branch the pointer to the items and the grid's size were waits of their own
+    // ahead of the item, 0.2 us a launch: training step of 3 programs, fp32, C = 16, 14 x 14 703 -> 697 us; of 9 programs, bf16, C = 64, 9 x 9 811 -> 798.)
     uint32_t i = blockIdx.y, tile = blockIdx.x;
-    if (a.runs) {
-        const uint32_t total = gridDim.x * gridDim.y, b = i * gridDim.x + tile, die = b & 7, q = total >> 3, r = total & 7;
-        const uint32_t l = die * q + min(die, r) + (b >> 3);
-        i = div_by(l, a.runs);
-        tile = l - i * gridDim.x;
+    {
+        const uint32_t b = i * a.n_groups + tile, die = b & 7, l = die * a.run_q + min(die, a.run_r) + (b >> 3), run_i = div_by(l, a.runs);
+        tile = a.runs ? l - run_i * a.n_groups : tile;
+        i = a.runs ? run_i : i;
     }
     const dynb_item it = items[i];
     const bool binary = it.src1 != DYNB_NO_ARG;           // uniform over the workgroup
@@ -950,6 +952,9 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     const long long groups = (long long)n_seg * a.tiles_per_seg * a.n_ctile;
     if (groups >= 1 << 24) return DYNB_E_UNSUPPORTED;
     a.runs = groups > 1 && count >= 16 && groups * groups * count < 1ll << 32 ? recip_of(uint32_t(groups)) : 0;
+    a.n_groups = uint32_t(groups);
+    a.run_q = uint32_t(groups * count >> 3);
+    a.run_r = uint32_t(groups * count & 7);
     hipLaunchKernelGGL((k_conv<T, MODE, MT, NT, FULL, G>), dim3(unsigned(groups), unsigned(count)), dim3(256), lds, st, items, a);
     return DYNB_OK;
 }
