@@ -378,8 +378,18 @@ __device__ __forceinline__ f32x4 direct_sum(const T* w, int C, int H, int W, int
     return sum;
 }
 
+// Waves per SIMD, which are workgroups per CU: three where the sums are in fp32 and 168 registers hold the tile.  (The staging of pixels ahead of the
+// weights took ten more and left two: kernel time of a pass over 64 balanced trees, fp32, the joins in 4 x 2 tiles, C = 256, 14 x 14 1233 us,
+// with three 1141; a training step's, C = 128, 14 x 14, the first convolution's data gradients in 2 x 2 790 / 725, the joins' 366 / 310.)
+template <typename T, ConvMode MODE, int MT, int NT, bool FULL>
+constexpr int conv_waves()
+{
+    constexpr int tiles = MODE == CV_DSECOND ? 2 : MODE == CV_DFIRST || MODE == CV_SECOND ? 4 : 8;
+    return FULL && (ConvTraits<MODE>::BWD || sizeof(T) == 4) && MT * NT <= tiles ? 3 : 2;
+}
+
 template <typename T, ConvMode MODE, int MT, int NT, bool FULL, int G>
-__global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArgs a)
+__global__ __launch_bounds__(256, (conv_waves<T, MODE, MT, NT, FULL>())) void k_conv(const dynb_item* items, ConvArgs a)
 {
     using Tr = ConvTraits<MODE>;
     using Steps = ConvSteps<T, MODE, MT, NT, FULL, G>;
@@ -509,18 +519,27 @@ __global__ __launch_bounds__(256, 2) void k_conv(const dynb_item* items, ConvArg
             for (int k = 0; k < UN; ++k)
                 if (base + k * 256 < n_pieces) *reinterpret_cast<u32x4*>(__builtin_assume_aligned(lds_raw + at[k], 16)) = v[k] & keep[k];
         };
-        // the first pieces go ahead of the weights, which arrive while the pixels are written
-        load(tid);
-        __builtin_amdgcn_sched_barrier(0);
-        steps.request();
-        __builtin_amdgcn_sched_barrier(0);
-        store(tid);
-        for (int base = tid + 256 * UN; base < n_pieces; base += 256 * UN) {
-            load(base);
-            store(base);
-            // Everything has arrived.  Said aloud, because pieces that were requested and not stored would otherwise count
-            // as outstanding, and every wait from here on would be for more than it needs.
-            __builtin_amdgcn_s_waitcnt(0x0f70);           // vmcnt(0)
+        if constexpr (Steps::F32) {
+            steps.request();
+            for (int base = tid; base < n_pieces; base += 256 * UN) {
+                load(base);
+                store(base);
+                // Everything has arrived.  Said aloud, because pieces that were requested and not stored would otherwise count
+                // as outstanding, and every wait from here on would be for more than it needs.
+                __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0)
+            }
+        } else {
+            // in bf16 the first pieces go ahead of the weights, which arrive while the pixels are written (fp32 has no registers for it, conv_waves)
+            load(tid);
+            __builtin_amdgcn_sched_barrier(0);
+            steps.request();
+            __builtin_amdgcn_sched_barrier(0);
+            store(tid);
+            for (int base = tid + 256 * UN; base < n_pieces; base += 256 * UN) {
+                load(base);
+                store(base);
+                __builtin_amdgcn_s_waitcnt(0x0f70);
+            }
         }
         if (panel == 0) request_operands();
         __syncthreads();

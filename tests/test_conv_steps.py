@@ -1,13 +1,16 @@
 """The arithmetic with which the general convolution kernels find a step's tap, in every panel that a launch can choose.
 
 Panels of many steps belong to maps of a few pixels with thousands of channels, whose weights take gigabytes; the arithmetic needs
-none of them.  A program of its own is compiled for the host from the kernels' header.
+none of them.  A program of its own is compiled for the host from the kernels' header.  The registers that the kernels take are
+read from the library's own build.
 """
 import os
 import shutil
 import subprocess
 
 import pytest
+
+from tests.test_handover import OBJDUMP, code_objects
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PACKAGE = os.path.join(ROOT, "paper_1707_02402_amd")
@@ -54,3 +57,19 @@ def test_tap_of_every_step_of_every_panel(tmp_path):
     largest2, largest9, wrong = map(int, subprocess.run([str(program)], check=True, capture_output=True, text=True, timeout=60).stdout.split())
     assert largest2 == 1279 and 120 <= largest9 <= 142      # the panels that the launches' limits on LDS allow
     assert wrong == 0
+
+
+@pytest.mark.parametrize("mode,tile", [(0, "42"), (1, "42"), (1, "22"), (2, "22"), (4, "22"), (5, "42"), (5, "22"), (6, "42"), (6, "22")])
+def test_three_workgroups_of_a_fp32_tile_fit_the_registers_of_a_cu(tmp_path, mode, tile):
+    """At most 168 registers and none spilled, in every variant of the kernel that whole steps run (512 registers a SIMD, three waves)."""
+    name = "k_convIfLNS_8ConvModeE%dELi%sELi%sELb1E" % (mode, *tile)
+    seen = 0
+    for path in code_objects(tmp_path):
+        table = subprocess.run([OBJDUMP, "-t", path], check=True, capture_output=True, text=True).stdout
+        value = {line.split()[-1]: int(line.split()[0], 16) for line in table.splitlines() if name in line}
+        for symbol in value:
+            if symbol.endswith(".num_vgpr"):
+                assert value[symbol] + value[symbol.replace(".num_vgpr", ".num_agpr")] <= 168, symbol
+                assert value[symbol.replace(".num_vgpr", ".private_seg_size")] == 0, symbol
+                seen += 1
+    assert seen >= 1
