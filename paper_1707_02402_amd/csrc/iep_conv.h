@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <type_traits>
 
 #include "device_utils.h"
@@ -136,8 +137,8 @@ __device__ __forceinline__ uint32_t div_by(uint32_t v, uint32_t m) { return __um
 // at least 9 pixels), pixels of a tile (1300) and columns of a segment (32)
 __host__ __device__ constexpr uint32_t recip20_of(uint32_t d) { return ((1u << 20) + d - 1) / d; }
 __host__ __device__ constexpr uint32_t div20_by(uint32_t v, uint32_t m) { return v * m >> 20; }
-// The tap of a panel's step s: nj steps a tap, m_nj = recip20_of(nj).  (Two taps, a join's arguments, are told apart without a division:
-// on maps of a pixel or two nj goes up to 1279, and s * nj beyond what div20_by is exact for.)
+// The tap of a panel's step s: nj steps a tap, m_nj = recip20_of(nj).  (Two taps, a join's arguments, are told apart without a division: on maps of a
+// pixel or two nj goes as far as LDS does, and from 756 on s * nj beyond what div20_by is exact for.)
 template <int TAPS> __host__ __device__ constexpr int tap_of(int s, int nj, uint32_t m_nj)
 {
     return TAPS == 1 ? 0 : TAPS == 2 ? int(s >= nj) : int(div20_by(uint32_t(s), m_nj));
@@ -923,7 +924,6 @@ __global__ __launch_bounds__(512, MT == 1 ? 4 : 2) void k_node(const dynb_item* 
 
 // ---- launching
 constexpr int CONV_LDS_MAX = 80 * 1024;                                  // two workgroups per CU
-constexpr int CONV_LDS_BOTH = 160 * 1024;                                // both arguments of a join
 
 // staged pixels of a tile of mt x 16 pixels, which start anywhere in a row
 inline int conv_tile_pixels(const ConvArgs& a, int mt, int halo)
@@ -945,6 +945,14 @@ int conv_panel(const ConvArgs& a)
     return (steps + panels - 1) / panels * KS;
 }
 
+// both arguments of a join, all channels, of a tile of mt x 16 pixels
+template <int ES>
+size_t conv_both_bytes(const ConvArgs& a, int mt)
+{
+    constexpr int KS = ES == 4 ? 16 : 32;
+    return size_t(2) * conv_tile_pixels(a, mt, 0) * conv_pixel_bytes((a.C + KS - 1) / KS * KS, ES);
+}
+
 template <typename T, ConvMode MODE, int MT, int NT, bool FULL, int G>
 int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t st)
 {
@@ -954,7 +962,7 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return DYNB_E_HIP;
     if (!(attr_set.load() >> (dev & 63) & 1)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv<T, MODE, MT, NT, FULL, G>), hipFuncAttributeMaxDynamicSharedMemorySize, MODE == CV_JOIN_BOTH ? CONV_LDS_BOTH : CONV_LDS_MAX) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv<T, MODE, MT, NT, FULL, G>), hipFuncAttributeMaxDynamicSharedMemorySize, CONV_LDS_MAX) != hipSuccess)
             return DYNB_E_HIP;
         attr_set.fetch_or(uint64_t(1) << (dev & 63));
     }
@@ -964,8 +972,8 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     const int pixels = conv_tile_pixels(a, MT, Tr::HALO);
     a.ck = MODE == CV_JOIN_BOTH ? (a.C + KS - 1) / KS * KS : conv_panel<Tr::HALO, ES>(a);
     a.m_sw = recip20_of(a.sw);
-    const size_t lds = std::max<size_t>(size_t(MODE == CV_JOIN_BOTH ? 2 : 1) * pixels * conv_pixel_bytes(a.ck, ES), size_t(4) * MT * NT * 1024);
-    if (lds > (MODE == CV_JOIN_BOTH ? CONV_LDS_BOTH : CONV_LDS_MAX)) return DYNB_E_UNSUPPORTED;     // cannot happen: sw <= 32
+    const size_t lds = std::max<size_t>(MODE == CV_JOIN_BOTH ? conv_both_bytes<ES>(a, MT) : size_t(pixels) * conv_pixel_bytes(a.ck, ES), size_t(4) * MT * NT * 1024);
+    if (lds > CONV_LDS_MAX) return DYNB_E_UNSUPPORTED;                   // cannot happen: sw <= 32
     // A row of a grid holds less than 2^32 threads (and nobody says so: the launch just does less).  Only the gradients of maps of
     // half a billion pixels with fewer than 4 channels would need more, which a parameter gradient's workgroup walks for many seconds.
     const long long groups = (long long)n_seg * a.tiles_per_seg * a.n_ctile;
@@ -995,6 +1003,7 @@ int launch_conv_full(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     const long long ptiles = (long long)((a.W + a.sw - 1) / a.sw) * ((a.H * a.sw + 15) / 16), ctiles = ((MODE == CV_DJOIN ? 2 * a.C : a.C) + 15) / 16;
     const long long steps = (long long)((a.C + KS - 1) / KS) * Tr::TAPS * (MODE == CV_JOIN ? 2 : 1);
     auto clocks = [&](int mt, int nt) {
+        if (MODE == CV_JOIN_BOTH && conv_both_bytes<ES>(a, mt) > CONV_LDS_MAX) return LLONG_MAX;
         const long long groups = (long long)count * ((ptiles + mt - 1) / mt) * ((ctiles + nt - 1) / nt);
         const long long staged = (long long)conv_tile_pixels(a, mt, Tr::HALO) * a.C * ES * (MODE == CV_JOIN || MODE == CV_JOIN_BOTH || MODE == CV_DSECOND ? 2 : 1);
         return (groups + 255) / 256 * (mt * nt * ((steps + 3) / 4) * STEP_CLOCKS + staged / 24 + 1200);
@@ -1015,11 +1024,13 @@ int launch_conv(const dynb_item* items, const ConvArgs& args, int count, hipStre
     constexpr int ES = Tr::BWD ? 4 : int(sizeof(T)), KS = ES == 4 ? 16 : 32;
     const int n_seg = (a.W + 31) / 32;
     a.sw = (a.W + n_seg - 1) / n_seg;
-    // A join takes both arguments at once where the largest tile's fit (a rule by the shape: it is part of the order of summation).  One after the
-    // other they were two waits for memory: 8.0 us a lone workgroup of bf16, C = 128, 7 x 7; now 5 for the whole launch.
+    // A join takes both arguments at once where a 2 x 2 tile's fit beside another workgroup's (a rule by the shape: it is part of the order of
+    // summation), and a 4 x 2 tile if its own do.  One after the other they were two waits for memory: 8.0 us a lone workgroup of bf16, C = 128, 7 x 7; at
+    // once 5 for the whole launch.  With one workgroup a CU, or in 1 x 1 tiles, both at once take longer: kernel time of the joins of 64
+    // balanced trees, fp32, one after the other / at once: C = 128, 14 x 14 354 / 430 us in 4 x 2 tiles, 349 in 2 x 2; C = 256, 7 x 7 263 / 337 in
+    // 4 x 2, 570 in 1 x 1; C = 512, 5 x 5 470 / 655 in 2 x 2; C = 1024, 4 x 4 1580 / 2640 in 1 x 1.
     if constexpr (MODE == CV_JOIN) {
-        const int ck = (a.C + KS - 1) / KS * KS;
-        if (2ll * conv_tile_pixels(a, 4, 0) * conv_pixel_bytes(ck, ES) <= CONV_LDS_BOTH) {
+        if (conv_both_bytes<ES>(a, 2) <= CONV_LDS_MAX) {
             if (a.C % KS != 0) return launch_conv_full<T, CV_JOIN_BOTH, false, 1>(items, a, count, st);
             if (a.C % (2 * KS) == 0) return launch_conv_full<T, CV_JOIN_BOTH, true, 2>(items, a, count, st);
             return launch_conv_full<T, CV_JOIN_BOTH, true, 1>(items, a, count, st);

@@ -29,9 +29,9 @@ template <int TAPS> int walk(int nj)
 
 int main()
 {
-    // a join with both arguments in LDS: as many steps as fit beside one pixel; a 3x3 stages at least the nine of a 1 x 1 map
+    // a join with both arguments in LDS: as many steps as fit it beside one pixel; a 3x3 stages at least the nine of a 1 x 1 map
     int largest2 = 0, largest9 = 0, wrong = 0;
-    for (int nj = 1; 2ll * conv_pixel_bytes(nj * 16, 4) <= CONV_LDS_BOTH; ++nj) { wrong += walk<2>(nj); largest2 = nj; }
+    for (int nj = 1; 2ll * conv_pixel_bytes(nj * 16, 4) <= 160 * 1024; ++nj) { wrong += walk<2>(nj); largest2 = nj; }
     for (int steps = 1; steps <= 4096; ++steps) {
         ConvArgs a = {};
         a.C = steps * 16;
@@ -55,7 +55,7 @@ def test_tap_of_every_step_of_every_panel(tmp_path):
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PACKAGE, "csrc"), "-x", "hip", str(source), "-o", str(program)],
                    check=True, capture_output=True, timeout=300)
     largest2, largest9, wrong = map(int, subprocess.run([str(program)], check=True, capture_output=True, text=True, timeout=60).stdout.split())
-    assert largest2 == 1279 and 120 <= largest9 <= 142      # the panels that the launches' limits on LDS allow
+    assert largest2 == 1279 and 120 <= largest9 <= 142      # the panels that a CU's LDS allows
     assert wrong == 0
 
 

@@ -591,10 +591,12 @@ def test_a_launch_group_of_more_modules_than_one_grid_holds(dyn, util):
 
 
 @pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 32, 9, 33, 9), ("f32", 96, 7, 5, 9), ("f32", 64, 14, 14, 21), ("bf16", 64, 6, 7, 40), ("bf16", 192, 5, 9, 7),
-                                           ("bf16", 128, 9, 11, 30), ("f32", 288, 6, 6, 3), ("bf16", 128, 7, 7, 70)])
+                                           ("bf16", 128, 9, 11, 30), ("f32", 288, 6, 6, 3), ("bf16", 128, 7, 7, 70), ("f32", 128, 14, 14, 40),
+                                           ("f32", 256, 14, 14, 3), ("bf16", 512, 14, 14, 3)])
 def test_weights_in_pairs_of_steps_and_joins_anywhere_in_a_group(dyn, util, oracle, dtype, C, H, W, B):
     """Channels that make an even number of steps, so that weights are requested for two at a time, with remainders of tiles and segments; joins of which
-    both arguments are staged at once or one after the other (288 channels); two-argument functions before, between and behind the others, so
+    both arguments are staged at once, in tiles of any size or of those that leave room for two workgroups (128 channels, 14 x 14), or one after the
+    other (256 channels and more), the convolutions then in several panels (14 x 14); two-argument functions before, between and behind the others, so
     that a group's joins lie anywhere in it.  Every schedule gives the same bits, with kept maps too."""
     arity = np.array([0, 2, 1, 2, 1], np.uint8)
     progs = [np.array(p, np.int32) for p in ([1, 0, 2, 0], [4, 3, 0, 0], [2, 0], [3, 1, 0, 0, 4, 0], [4, 2, 0])]
