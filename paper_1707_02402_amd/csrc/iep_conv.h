@@ -978,7 +978,12 @@ int launch_conv_tile(const dynb_item* items, ConvArgs a, int count, hipStream_t 
     // half a billion pixels with fewer than 4 channels would need more, which a parameter gradient's workgroup walks for many seconds.
     const long long groups = (long long)n_seg * a.tiles_per_seg * a.n_ctile;
     if (groups >= 1 << 24) return DYNB_E_UNSUPPORTED;
-    a.runs = groups > 1 && count >= 16 && groups * groups * count < 1ll << 32 ? recip_of(uint32_t(groups)) : 0;
+    // Runs of items for the dies as long as a function's weights stay in a die's L2 of 4 MB.  Larger ones every die would read for itself, for its
+    // items alone; in the plain order the items of a function run at the same time and a die reads its channel tiles' share for all of them.  Kernel
+    // time of the 3x3s of 64 balanced trees, runs / plain order: C = 1024 fp32, 4 x 4 10070 / 7740 us, bf16, 5 x 5 4800 / 2630; C = 512, 5 x 5,
+    // fp32 2730 / 2700; C = 256, 7 x 7, fp32 (2.4 MB) 1360 / 1390.
+    const long long weights = (long long)Tr::TAPS * a.C * (MODE == CV_DJOIN ? 2 * a.C : a.C) * int(sizeof(T));
+    a.runs = groups > 1 && count >= 16 && weights <= 4 << 20 && groups * groups * count < 1ll << 32 ? recip_of(uint32_t(groups)) : 0;
     a.n_groups = uint32_t(groups);
     a.run_q = uint32_t(groups * count >> 3);
     a.run_r = uint32_t(groups * count & 7);
