@@ -310,7 +310,9 @@ size_t dynbatch_backward_workspace_bytes(const dynb_plan* plan, const dynb_shape
  * dL/d(every module parameter), the latter summed over all nodes that use the function.
  *   plan               made with DYNB_PLAN_KEEP by dynbatch_plan (not dynbatch_plan_dag), uploaded
  *   w, feats           as passed to dynbatch_execute (w->packed is not used)
- *   out                device [B][H][W][C] dtype: what dynbatch_execute wrote
+ *   out                device [B][H][W][C] dtype: what dynbatch_execute wrote, unchanged since.  (Which elements of the results are
+ *                      positive is read from it, on the shape of the fused kernels from forward_workspace instead, where
+ *                      dynbatch_execute noted it.)
  *   forward_workspace  device: the workspace of that dynbatch_execute call, unchanged since
  *   dout               device [B][H][W][C] fp32
  *   grads              host struct of device pointers
@@ -461,7 +463,8 @@ int moe_forward_naive(const moe_shape* shape, const void* x, const void* Wg, con
 typedef struct {
     int32_t tag;    /* dynbatch_execute: index of the launch group, -2 for set-up; moe_forward: stage id
                        0 gate, 1 top-k, 2 grouping (counting sort), 3 permute, 4 expert layer 1,
-                       5 expert layer 2, 6 combine                                               */
+                       5 expert layer 2, 6 combine (few uses are selected and grouped by one
+                       kernel: stage 1 is then both and stage 2 empty)                           */
     int32_t units;  /* dynbatch_execute: module evaluations in the launch group; moe_forward: 0   */
     float ms;       /* GPU time between the HIP events that bracket the stage                    */
 } dynb_stage_time;

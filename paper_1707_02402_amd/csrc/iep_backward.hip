@@ -1105,8 +1105,8 @@ BmLayout bm_layout(const dynb_plan* p)
     return L;
 }
 
-int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const void* feats, const void* out, const void* fwd_ws,
-                      const float* dout, const dynb_module_grads* g, char* ws, hipStream_t st)
+int run_backward_mfma(const dynb_plan* p, const dynb_module_weights* w, const void* feats, const void* fwd_ws, const float* dout,
+                      const dynb_module_grads* g, char* ws, hipStream_t st)
 {
     static std::atomic<uint64_t> attr_set{0};                 // one bit per device
     int dev = 0;
@@ -1245,7 +1245,7 @@ extern "C" int dynbatch_backward(const dynb_plan* p, const dynb_shape* s, const 
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(DYNB_E_INVAL, "dynbatch_backward: workspace not 256-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
-    if (fast_shape(s)) return run_backward_mfma(p, w, feats, out, forward_workspace, dout, grads, ws, st);
+    if (fast_shape(s)) return run_backward_mfma(p, w, feats, forward_workspace, dout, grads, ws, st);
     if (s->dtype == DYNB_BF16) return run_backward<bf16_t>(p, s, w, feats, out, forward_workspace, dout, grads, ws, st);
     return run_backward<float>(p, s, w, feats, out, forward_workspace, dout, grads, ws, st);
 }

@@ -1079,7 +1079,9 @@ inline bool node_wide(int pt, int ct) { return ((pt + 3) / 4 * ct + 7) / 8 * 4 <
 
 // Whole modules by k_node, where that takes one CU no longer than two or three launches of k_conv take to get going (5 us
 // each) and two tiles fit LDS.  A CU's time: its MFMAs, or its weights, of which one CU was seen to take in some 12 bytes a clock
-// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 16 to 22 us, in pairs of steps, against 2 x 5 to 5 + 2 x 9),
+// (fp32, C = 16, 8 x 8: 8 us an item against 3 x 5; bf16, C = 128, 7 x 7, 590 KB of weights: 16 to 22 us, in pairs of steps, against 2 x 5 to 5 + 2 x 9,
+// which costs a pass over 1, 8 and 64 programs with their narrow labels 328, 520 and 658 us against 180, 293 and 484, and saves one over 256, and
+// over 256 balanced trees, 692 against 764 and 365 against 552: the rule goes by the shape alone and decides for the narrow ones),
 // and with every round of units a wait for weights: one lone module, bf16 C = 48, 14 x 14, 5 rounds: 58 us against 15 by k_conv;
 // C = 20, 20 x 20, 7 rounds: 79 / 20 (and 35 by k_conv_plain); C = 24, 14 x 14, 1 round of wide units: 16 / 15.  Below 16 channels the
 // tiles are cut short and k_conv wins from two rounds on (bf16 C = 8, 14 x 14: 21 / 14) or with many modules (fp32 C = 6, 4 x 4,
