@@ -186,7 +186,8 @@ __device__ __forceinline__ void module_body(const MfArgs& a, const int logical)
         }
     };
     // the centre of the halo tile -> a map, this workgroup's output rows (and share of the channels), in coalesced 16-byte pieces, and the map's mask
-    // (1 to 1.5 us of a whole node's 33.  Four lanes' bytes put together, for a quarter of the stores: the registers do not suffice, 41 us.)
+    // (a launch of whole nodes 31.9 -> 34.9 us, of halves 21.4 -> 22.4, of quarters 15.7 -> 16.2; the backward pass gains 8.1, 2.3 and 1.4.  Four lanes'
+    // bytes put together, for a quarter of the stores: the registers do not suffice, 41 us.)
     auto copy_out = [&](bf16_t* dst, auto&& mask) {
         constexpr int OUTPIECES = Shape::ROWS * S * 16;
         int t = tid;
