@@ -37,12 +37,15 @@ namespace {
 
 constexpr int SORT_BLOCK = 256;   // uses ranked together by one workgroup
 constexpr int TM = 64;            // rows of one grouped-GEMM tile
+constexpr int XR = 256, XF = 256; // rows and features of a whole tile of k_grouped_stream
+constexpr int XM = 128;           // most rows of its other kind
 constexpr int TN = 256;           // output features of one grouped-GEMM tile
 constexpr int NTW = TN / 64;      // 16-feature sub-tiles per wave (4 waves split the features)
 constexpr int MAX_K = 8;          // uses of a token whose places are kept in registers (more are looked up)
 constexpr int MG = 8;             // row tiles of one expert that walk the feature tiles together
 constexpr int XCD_CHUNK = 128;    // most consecutive grouped-GEMM tiles dealt to one XCD
 constexpr uint32_t XCD_CUS = 32;
+struct alignas(16) RowTile { int32_t expert, row0, rows, pad; };
 
 __device__ __forceinline__ bf16x8 ldg_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
@@ -582,11 +585,24 @@ __global__ __launch_bounds__(256) void k_scan_blocks(int32_t* __restrict__ block
     if (lane == 0) counts[e] = carry;
 }
 
+// Row tiles of k_grouped_stream: an expert's tiles of more than XM rows, up to XR, from the front of `tiles` on, and one of up to XM remaining rows, from the
+// back on.  They are counted together, 65536 a whole tile and 1 a rest; how many there are stands in tile_start[0] and [1].
+__device__ __forceinline__ int stream_tiles(int c) { return int(uint32_t((c + XR - XM - 1) / XR) << 16) | int(c % XR != 0 && c % XR <= XM); }
+__device__ __forceinline__ int whole_tiles(int n) { return int(uint32_t(n) >> 16); }
+__device__ __forceinline__ int rest_tiles(int n) { return n & 0xffff; }
+__device__ __forceinline__ void put_stream_tiles(RowTile* tiles, int max_tiles, int before, int e, int at, int c)
+{
+    RowTile* to = tiles + whole_tiles(before);
+    for (; c > XM; c -= XR, at += XR) *to++ = RowTile{e, at, min(XR, c), 0};
+    if (c > 0) tiles[max_tiles - 1 - rest_tiles(before)] = RowTile{e, at, c, 0};
+}
+
 // One workgroup of 16 waves: offsets = exclusive scan of counts; tile_start = exclusive scan of ceil(counts / TM).
 // 1024 experts per pass: a scan inside every wave, the waves' totals through LDS.
 constexpr int OFFS_THREADS = 1024;
+template <bool STREAM>
 __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                          int32_t* __restrict__ tile_start, int E)
+                                                          int32_t* __restrict__ tile_start, RowTile* __restrict__ tiles, int max_tiles, int E)
 {
     __shared__ int32_t wsum[OFFS_THREADS / 64], wtsum[OFFS_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -594,7 +610,7 @@ __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restr
     for (int e0 = 0; e0 < E; e0 += OFFS_THREADS) {
         const int e = e0 + tid;
         const int c = e < E ? counts[e] : 0;
-        const int tl = (c + TM - 1) / TM;
+        const int tl = STREAM ? stream_tiles(c) : (c + TM - 1) / TM;
         int inc = c, tinc = tl;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -612,12 +628,19 @@ __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restr
             all += a;
             tall += t;
         }
-        if (e < E) { offsets[e] = carry + before + inc - c; tile_start[e] = tcarry + tbefore + tinc - tl; }
+        if (e < E) {
+            offsets[e] = carry + before + inc - c;
+            if constexpr (STREAM) put_stream_tiles(tiles, max_tiles, tcarry + tbefore + tinc - tl, e, carry + before + inc - c, c);
+            else tile_start[e] = tcarry + tbefore + tinc - tl;
+        }
         carry += all;
         tcarry += tall;
         __syncthreads();                                     // the totals are overwritten by the next pass
     }
-    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
+    if (tid == 0) offsets[E] = carry;
+    if constexpr (STREAM) {
+        if (tid < 2) tile_start[tid] = tid ? rest_tiles(tcarry) : whole_tiles(tcarry);
+    } else if (tid == 0) tile_start[E] = tcarry;
 }
 
 __global__ __launch_bounds__(SORT_BLOCK) void k_place(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank,
@@ -660,7 +683,6 @@ __device__ __forceinline__ int rank_in_block(int my, int n, int32_t* count)
 // nothing to do (18 us for 74 uses): counts and places of the experts in LDS.  `tiles` (if not null): the row tiles of the expert layers, {expert, first row, rows, 0} each, rows = 0 from the
 // last one on to max_tiles, so that a workgroup of those layers finds its tile with one load.
 constexpr int SMALL_USES = 1024, SMALL_EXPERTS = 4096;
-struct alignas(16) RowTile { int32_t expert, row0, rows, pad; };
 
 __global__ __launch_bounds__(1024) void k_group_small(const int32_t* __restrict__ idx, int32_t* __restrict__ counts,
                                                       int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
@@ -867,8 +889,8 @@ __global__ __launch_bounds__(256) void k_topk_group(const float* __restrict__ lo
         }
 }
 
-// block 0 also writes the experts' tables; tiles as in k_group_small
-template <int WAVES>
+// block 0 also writes the experts' tables; tiles as in k_group_small, or (STREAM) as k_grouped_stream wants them
+template <int WAVES, bool STREAM>
 __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank, const int32_t* __restrict__ blockcnt,
                                                     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv, RowTile* __restrict__ tiles, int max_tiles,
@@ -904,7 +926,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __rest
                 }
             }
         }
-        const i32x4 tl = (c + (TM - 1)) / TM;             // from here on as k_offsets, four experts a thread
+        // from here on as k_offsets, four experts a thread
+        const i32x4 tl = STREAM ? i32x4{stream_tiles(c.x), stream_tiles(c.y), stream_tiles(c.z), stream_tiles(c.w)} : (c + (TM - 1)) / TM;
         const int mine = c.x + c.y + c.z + c.w, tmine = tl.x + tl.y + tl.z + tl.w;
         int inc = mine, tinc = tmine;
 #pragma unroll
@@ -931,9 +954,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __rest
                 if (tables) {
                     counts[e + i] = c[i];
                     offsets[e + i] = at;
-                    tile_start[e + i] = tat;
-                    if (tiles)
-                        for (int t = 0; t < tl[i]; ++t) tiles[tat + t] = RowTile{e + i, at + t * TM, min(TM, c[i] - t * TM), 0};
+                    if constexpr (STREAM) put_stream_tiles(tiles, max_tiles, tat, e + i, at, c[i]);
+                    else {
+                        tile_start[e + i] = tat;
+                        if (tiles)
+                            for (int t = 0; t < tl[i]; ++t) tiles[tat + t] = RowTile{e + i, at + t * TM, min(TM, c[i] - t * TM), 0};
+                    }
                 }
             }
             at += c[i];
@@ -953,7 +979,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __rest
         }
     }
     if (!tables) return;
-    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
+    if (tid == 0) offsets[E] = carry;
+    if constexpr (STREAM) {
+        if (tid < 2) tile_start[tid] = tid ? rest_tiles(tcarry) : whole_tiles(tcarry);
+        return;
+    }
+    if (tid == 0) tile_start[E] = tcarry;
     if (tiles)
         for (int t = tcarry + tid; t < max_tiles; t += THREADS) tiles[t] = RowTile{0, 0, 0, 0};
 }
@@ -1325,6 +1356,281 @@ __global__ __launch_bounds__(256, 3) void k_grouped_skinny(const bf16_t* __restr
     else skinny_tile<RELU, 4>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
 }
 
+// The expert layers for crowded experts (the rule stands where it is applied): one workgroup per CU that stays for the launch and sees its tiles as one stream
+// of K-chunks.  Chunks of 64 channels go from memory straight into LDS, one or two of them ahead, across the border of one tile to the next: the pipeline does
+// not run dry for a tile's first chunk or while its results leave, and a chunk costs one barrier.  A whole tile has 256 rows and 256 features, so that an
+// expert's weights and rows enter a CU at 31 bytes for every clock of its matrix instructions (k_grouped_gemm's tiles of 64 rows: 78; the L2 gives a CU
+// 64 a clock, 135 GB/s, to copies of 128 bytes of a row at a time, and memory all of them 6.3 TB/s, one alone 58 GB/s, with two chunks in flight or
+// four); an expert's remaining rows, up to 128, are another kind, a stream of weights with two chunks ahead.  Half of the workgroups of a die begin with
+// either kind: products beside the stream (one kind after the other on all CUs: 950 us a layer of 16384 tokens, 1024 experts, instead of 900).
+// What bounds it: whole tiles, the matrix instructions at the clock the card grants (16384 tokens, d 1024, h 2048, 16 experts, 4 uses: 0.92 PFLOP/s the
+// pass, k_grouped_gemm 0.68); the others, memory, where results that are written cost the reading six times their bytes (4 GiB of weights alone in 675
+// us, with 64 MB of results 737).
+// The sums are k_grouped_gemm's bit for bit: 32x32x16 MFMAs over the channels in the same order.
+constexpr int XBLOCK = 1040, XUNIT = 8 * XBLOCK;               // LDS: 64 rows of a chunk in eight blocks (slot_of)
+constexpr int XIDX = 18 * XUNIT;                               // behind the chunks (2 of 8 units, 3 of 6): the rows' places in `gather`, two tiles'
+constexpr int XLIST = XIDX + 2 * XR * 4, XLIST_LEN = 512;      // ... and the workgroup's next tiles
+constexpr int X_LDS = XLIST + XLIST_LEN * 16;
+constexpr int X_GRID = 256;
+
+__device__ __forceinline__ void lds_copy16(const char* base, uint32_t off, uint32_t lds_at)   // 64 lanes x 16 bytes -> LDS at lds_at, lane after lane
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    asm volatile("" : "+s"(base), "+v"(off));                                      // (a scalar base and a lane's offset, and no address of 64 bits per lane kept for every request)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(base + off),
+                                     (__attribute__((address_space(3))) uint32_t*)(lds_raw + lds_at), 16, 0, 0);
+}
+// *p by the scalar unit: the address is the same for the whole wave, and nobody writes there during the kernel
+__device__ __forceinline__ int32_t uniform_load(const int32_t* p)
+{
+    return __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(4))) int32_t*)(p));
+}
+// All but this wave's newest N requests and stores have been answered
+template <int N> __device__ __forceinline__ void answered_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// (Not __syncthreads, which waits for all requests into LDS)
+__device__ __forceinline__ void meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <bool RELU>
+__global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
+                                                           const RowTile* __restrict__ tiles, const int32_t* __restrict__ n_tiles, int max_tiles,
+                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane & 31, hk = lane >> 5;
+    const int fg = wave & 3, rg = wave >> 2;                   // this wave: features 64 fg .. of a tile, the first or second half of its rows
+    const int nchunk = K / 64;
+    const int die = blockIdx.x & 7, slot = blockIdx.x >> 3;
+
+    // ---- where things lie in LDS.  Eight neighbouring lanes copy 128 bytes of a row, in their order (in any other a request is answered lane by lane, 13.5
+    // bytes a clock instead of 64); wave w copies block w of every unit of 64 rows.  What an LDS pass of a fragment's read takes together, 16 of its
+    // 32 rows (lanes 0-3, 12-15, 20-23, 24-27 or the others), are two rows of every block, an even and an odd one, and the blocks are 16 bytes further
+    // apart than their size: all banks.  Lane l copies row l / 8 of the block, which lane s_q of fragment l / 32 reads
+    const int s_par = lane >> 3 & 1, s_g = lane >> 4 & 1;
+    const int s_q = (wave >> 1) * 8 + (s_g ^ (wave >> 1 & 1) ^ (wave >> 2 & 1)) * 4 + (wave & 1) * 2 + s_par;
+    const uint32_t x_slot = uint32_t(((q >> 3) * 2 + (q >> 1 & 1)) * XBLOCK + (((q >> 2 ^ q >> 3 ^ q >> 4) & 1) * 2 + (q & 1)) * 128 + hk * 16);
+    // accumulator row 8 b + 4 h + c of lane half h is given feature 16 h + 4 b + c: a lane ends up with 16 consecutive features of a row
+    const int x_row = (lane >> 5) * 32 + s_q, w_row = (lane >> 5) * 32 + (s_q >> 2 & 1) * 16 + (s_q >> 3) * 4 + (s_q & 3);
+    const size_t w_unit = size_t(K) * 128;                     // bytes from one unit of features to the next
+    const uint32_t piece = uint32_t(lane & 7) * 16u, w_off = uint32_t(w_row) * uint32_t(K) * 2u + piece;
+
+    struct Tile { int expert, row0, rows, nb; };
+    // this workgroup's tiles of one kind, of up to ROWS rows, BUFS chunks in LDS; find(s): the tile's place in `tiles` and its feature tile
+    auto run = [&](auto rows_const, auto bufs_const, const int count, auto&& find) {
+        constexpr int ROWS = decltype(rows_const)::value, BUFS = decltype(bufs_const)::value, AHEAD = BUFS - 1;
+        constexpr int RU = ROWS / 64, PIECES = 4 + RU;         // units of rows; of a chunk
+        constexpr uint32_t BUF = uint32_t(PIECES * XUNIT);
+        static_assert(BUFS * BUF <= uint32_t(XIDX) && ROWS <= XR && ROWS % 64 == 0, "room");
+        if (count == 0) return;
+        // where the tiles are is looked up for 512 of them at once (one at a time, it would be a trip to memory for each)
+        auto list_tiles = [&](int s0) {
+            if (s0 + tid < count) {
+                const int2 at = find(s0 + tid);
+                const RowTile t = tiles[at.x];
+                *reinterpret_cast<u32x4*>(lds_raw + XLIST + tid * 16) = u32x4{uint32_t(t.expert), uint32_t(t.row0), uint32_t(t.rows), uint32_t(at.y * XF)};
+            }
+            answered_but<0>();
+            meet();
+        };
+        auto tile_at = [&](int s) {
+            const u32x4 v = *reinterpret_cast<const u32x4*>(lds_raw + XLIST + s % XLIST_LEN * 16);
+            return Tile{int(__builtin_amdgcn_readfirstlane(v.x)), int(__builtin_amdgcn_readfirstlane(v.y)), int(__builtin_amdgcn_readfirstlane(v.z)),
+                        int(__builtin_amdgcn_readfirstlane(v.w))};
+        };
+        uint32_t x_off[RU];
+        bool x_on[RU];                                         // this lane's row is there (lane 0: always, so that every wave makes every request, which it counts)
+        const char* w_next = nullptr;                          // weights of the chunk that is requested next
+        const char* x_next = nullptr;
+        int w_units = 0;                                       // ... that exist (the last one is copied again)
+        uint32_t fill = 0, take = 0;                           // the chunk's place that is filled next, and the one that is read
+        auto request_rows = [&](const Tile& t, int buf) {      // the places of a tile's rows
+            if (gather && wave * 64 < t.rows)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(gather + t.row0 + min(wave * 64 + lane, t.rows - 1)),
+                                                 (__attribute__((address_space(3))) uint32_t*)(lds_raw + XIDX + buf * (XR * 4) + wave * 256), 4, 0, 0);
+        };
+        auto open = [&](const Tile& t, int buf) {
+            w_next = reinterpret_cast<const char*>(W + (size_t(t.expert) * N + t.nb) * K);
+            x_next = reinterpret_cast<const char*>(in);
+            w_units = (N - t.nb) / 64;
+#pragma unroll
+            for (int i = 0; i < RU; ++i) {
+                const int r = min(i * 64 + x_row, t.rows - 1);
+                x_on[i] = i * 64 + x_row < t.rows || lane == 0;
+                uint32_t row = uint32_t(t.row0 + r);
+                if (gather) {
+                    row = *reinterpret_cast<const uint32_t*>(lds_raw + XIDX + buf * (XR * 4) + r * 4);
+                    if (m_kdiv) row = __umulhi(row, m_kdiv);   // / k
+                }
+                x_off[i] = row * uint32_t(K) * 2u + piece;
+            }
+        };
+        auto request_piece = [&](int i) {
+            const uint32_t at = fill + uint32_t(i * XUNIT + wave * XBLOCK);
+            if (i < 4) lds_copy16(w_next + (i < w_units ? i : 0) * w_unit, w_off, at);
+            else if (x_on[(i - 4) % RU]) lds_copy16(x_next, x_off[(i - 4) % RU], at);
+        };
+        auto requested = [&]() {
+            w_next += 128;
+            x_next += 128;
+            fill = fill == AHEAD * BUF ? 0 : fill + BUF;
+        };
+
+        list_tiles(0);
+        Tile now = tile_at(0);
+        request_rows(now, 0);
+        answered_but<0>();
+        meet();
+        open(now, 0);
+        for (int c = 0; c < AHEAD; ++c) {
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) request_piece(i);
+            requested();
+        }
+        int stores = 0;                                        // of this wave, behind the last tile's last request
+#pragma unroll 1
+        for (int s = 0; s < count; ++s) {
+            if ((s + 1) % XLIST_LEN == 0 && s + 1 < count) list_tiles(s + 1);   // (all waves have met since they read the list's last)
+            const Tile then = tile_at(min(s + 1, count - 1));
+            const int rows = now.rows;
+            const bool few = RU < 4 && rows <= 64, more = s + 1 < count;      // few: one block of 32 rows a wave
+            const int first = few ? rg : rg * RU;              // this wave's first block
+            const int mine = now.nb + fg * 64 < N ? max(0, min(few ? 1 : RU, (rows + 31) / 32 - first)) : 0;
+            auto arrive = [&](int c) {                         // chunk c of this tile is there, and all waves are done with the one before
+                if (c < AHEAD && stores > 0) {
+                    constexpr int A = (AHEAD - 1) * PIECES;
+                    if (stores >= 16) answered_but<A + 16>();
+                    else if (stores >= 12) answered_but<A + 12>();
+                    else if (stores >= 8) answered_but<A + 8>();
+                    else answered_but<A + 4>();
+                } else answered_but<(AHEAD - 1) * PIECES>();
+                meet();
+            };
+            // the tile, with NB blocks for this wave
+            auto work = [&](auto nb_const) {
+                constexpr int NB = decltype(nb_const)::value;
+                f32x16 acc[2][NB > 0 ? NB : 1];
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+                // products of the chunk at `take`, and the requests for another one under them
+                auto chunk = [&](bool ask) {
+                    const uint32_t wu = take + uint32_t(fg * XUNIT) + x_slot;
+                    const uint32_t xu = take + uint32_t((4 + first / 2) * XUNIT + first % 2 * 512) + x_slot;
+                    bf16x8 wf[2][2], xf[2][NB > 0 ? NB : 1];
+                    auto read = [&](int ks) {
+#pragma unroll
+                        for (int a = 0; a < 2; ++a) wf[ks & 1][a] = *reinterpret_cast<const bf16x8*>(lds_raw + wu + (a * 512 + ks * 32));
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) xf[ks & 1][b] = *reinterpret_cast<const bf16x8*>(lds_raw + xu + (b / 2 * XUNIT + b % 2 * 512 + ks * 32));
+                    };
+                    auto request = [&](int ks) {
+                        if (ask && ks < 2) {
+#pragma unroll
+                            for (int i = ks * PIECES / 2; i < (ks + 1) * PIECES / 2; ++i) request_piece(i);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    if constexpr (NB == 0) { request(0); request(1); }
+                    else {
+                        if (RU < 4) { request(0); request(1); }           // (a stream of weights: first of all)
+                        read(0);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                                for (int a = 0; a < 2; ++a) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], xf[ks & 1][b], acc[a][b], 0, 0, 0);
+                                __builtin_amdgcn_sched_barrier(0);
+                                if (b == 0 && ks < 3) {
+                                    read(ks + 1);
+                                    __builtin_amdgcn_sched_barrier(0);
+                                }
+                                if (RU == 4 && b == NB / 2) request(ks);
+                            }
+                    }
+                    if (ask) requested();
+                    take = take == AHEAD * BUF ? 0 : take + BUF;
+                };
+#pragma unroll 1
+                for (int c = 0; c < nchunk - AHEAD; ++c) {
+                    arrive(c);
+                    if (c == 0 && more) request_rows(then, (s + 1) & 1);
+                    chunk(true);
+                }
+                // (the places of its rows: asked for ahead of chunk 0's requests, and there when all have met for chunk AHEAD)
+                if (nchunk < 2 * AHEAD + 1) { answered_but<0>(); meet(); }
+                if (more) open(then, (s + 1) & 1);
+#pragma unroll 1
+                for (int c = nchunk - AHEAD; c < nchunk; ++c) {
+                    if (more) arrive(c);
+                    else { answered_but<0>(); meet(); }
+                    chunk(more);
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int r = (first + b) * 32 + q;
+                    if (b < mine && r < rows) {
+                        bf16_t* const to = out + size_t(now.row0 + r) * N + now.nb + fg * 64 + 16 * hk;
+#pragma unroll
+                        for (int a = 0; a < 2; ++a)
+#pragma unroll
+                            for (int p = 0; p < 2; ++p) {
+                                const f32x16& v = acc[a][b];
+                                u32x4 o = {pack_bf16x2(v[8 * p + 0], v[8 * p + 1]), pack_bf16x2(v[8 * p + 2], v[8 * p + 3]),
+                                           pack_bf16x2(v[8 * p + 4], v[8 * p + 5]), pack_bf16x2(v[8 * p + 6], v[8 * p + 7])};
+                                if (RELU) { o.x = relu_bf16x2(o.x); o.y = relu_bf16x2(o.y); o.z = relu_bf16x2(o.z); o.w = relu_bf16x2(o.w); }
+                                *reinterpret_cast<u32x4*>(to + a * 32 + p * 8) = o;
+                            }
+                    }
+                }
+                // (an end of its own for every size: ends that the compiler has merged are reached from stores that only some lanes make, and what it
+                // then takes for different from lane to lane is all of the state above)
+                asm volatile("; %0" ::"n"(NB));
+            };
+            if constexpr (RU > 2) work(std::integral_constant<int, RU>{});
+            else if (mine == 0) work(std::integral_constant<int, 0>{});
+            else if (few) work(std::integral_constant<int, 1>{});
+            else work(std::integral_constant<int, RU>{});
+            stores = 4 * mine;
+            now = then;
+        }
+        meet();                                                // (the other kind's chunks lie in the same place)
+    };
+
+    // ---- this workgroup's tiles.  A sixteenth of either list goes to every half of a die, whose sixteen workgroups take its tiles in turn, one list after
+    // the other, and those of the last round, which is cut short, in reverse: the second list's not to who has a whole tile more.  Blocks of 4 row tiles x 4
+    // feature tiles of the first list are neighbours (what they share comes from one L2), all features of a row tile in the other
+    const int half = slot & 1, turn = slot >> 1, group = die * 2 + half;
+    const int n_whole = uniform_load(n_tiles), n_rest = uniform_load(n_tiles + 1);
+    auto share = [&](int n, int i) { return int((long long)n * nt * i / 16); };
+    const int whole0 = share(n_whole, group), whole1 = share(n_whole, group + 1), rest0 = share(n_rest, group), rest1 = share(n_rest, group + 1);
+    const int all = whole1 - whole0 + rest1 - rest0, rounds = all & ~15;
+#pragma unroll 1
+    for (int phase = 0; phase < 2; ++phase) {
+        const bool second = (phase ^ half) != 0;
+        const int from = second ? rest0 : whole0, n = second ? rest1 - rest0 : whole1 - whole0, dealt = second ? whole1 - whole0 : 0;
+        const int first = (turn - dealt) & 15, regular = max(0, (min(n, rounds - dealt) - first + 15) / 16);
+        const int last = rounds + 15 - turn - dealt;           // this workgroup's of the last round, if it is in this list
+        const int count = regular + (last >= 0 && last < n && last + dealt < all);
+        auto index = [&](int s) { return from + (s < regular ? first + 16 * s : last); };
+        auto find_whole = [&](int s) {
+            const int i = index(s);
+            const int strip = i / (4 * nt), i1 = i - strip * 4 * nt, rows4 = min(4, n_whole - strip * 4);   // 4 row tiles, all features
+            const int col = i1 / (rows4 * 4), i2 = i1 - col * rows4 * 4, cols4 = min(4, nt - col * 4);
+            return int2{strip * 4 + i2 / cols4, col * 4 + i2 % cols4};
+        };
+        auto find_rest = [&](int s) {
+            const int i = index(s), m = i / nt;
+            return int2{max_tiles - 1 - m, i - m * nt};
+        };
+        if (!second) run(std::integral_constant<int, XR>{}, std::integral_constant<int, 2>{}, count, find_whole);
+        else run(std::integral_constant<int, XM>{}, std::integral_constant<int, 3>{}, count, find_rest);
+    }
+}
+
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct Layout {
@@ -1506,8 +1812,16 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         const long long most = rows16 < 2 ? 3 * 768 : std::max(small ? 307ll : 230ll, std::min(614ll, (K - 128) * 3ll / 10));
         return groups * 600 <= 768ll * (K - 128) && groups <= most && (K >= 224 || A >= 128 || groups * 5 >= 768);
     };
-    const bool skinny1 = skinny_layer(h, d), skinny2 = skinny_layer(d, h), skinny = skinny1 || skinny2;
-    RowTile* const tiles = skinny ? reinterpret_cast<RowTile*>(xs) : nullptr;
+    const int stream_most = std::min(A, E + A / XR);           // at least as many tiles of k_grouped_stream as there are
+    // Crowded experts, 64 uses each and more in the mean, and products for a tile of 256 x 256 on every CU and more (2^24 = 256 of them, both layers
+    // together): k_grouped_stream.  Its tiles are few and large.  The whole pass, others / so in us, by mean uses of an expert and tiles: 2250, 692: 204 / 157;
+    // 3870, 1180: 288 / 217; 541, 1087: 343 / 271; 788, 863: 192 / 139; 553, 422: 103 / 92; 508, 283: 78 / 67; 370, 2430: 660 / 553; 116, 291: 154 / 136; 99, 525: 171 /
+    // 164; 64, 3072 (Zipf 1.2): 2010 / 1930; 152, 372: 91 / 94; and on the other side of the line 1190, 167: 51 / 55; 187, 135: 48 / 55; 399, 38: 40 / 49; 48, 561: 313 /
+    // 312; 63, 1127: 444 / 450; 37, 395: 301 / 303; 32, 192: 153 / 159
+    const bool streamed = fused_permute && naive_stride <= 0 && !small && d % 64 == 0 && h % 64 == 0 && d >= 256 && h >= 256 && E <= SMALL_EXPERTS && A < 1 << 22 && k <= 1024 &&
+                        size_t(A) * size_t(std::max(d, h)) < size_t(1) << 31 && A >= 64 * E && size_t(A) * size_t(d + h) >= size_t(1) << 24;
+    const bool skinny1 = !streamed && skinny_layer(h, d), skinny2 = !streamed && skinny_layer(d, h), skinny = skinny1 || skinny2;
+    RowTile* const tiles = skinny || streamed ? reinterpret_cast<RowTile*>(xs) : nullptr;
     // m2 top-k + softmax
     const dim3 tk_grid((T + 3) / 4), tk_block(256);
     if (joined) {
@@ -1535,14 +1849,15 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     } else if (mid) {
         const int nblk = (A + 1023) / 1024;                    // (a quarter of the blocks that blockcnt has room for; a single expert's rows of four counts fill that)
         hipLaunchKernelGGL(k_rank_wide, dim3(nblk), dim3(256), 0, st, topk_idx, lrank, blockcnt, A, E);
-        hipLaunchKernelGGL(E <= 1024 ? k_place_wide<4> : k_place_wide<8>, dim3(nblk), dim3(E <= 1024 ? 256 : 512), 0, st, topk_idx, lrank, blockcnt,
-                           counts, offsets, tile_start, perm, inv, tiles, skinny_tiles, A, E, nblk);
+        auto* const place = E <= 1024 ? (streamed ? k_place_wide<4, true> : k_place_wide<4, false>) : streamed ? k_place_wide<8, true> : k_place_wide<8, false>;
+        hipLaunchKernelGGL(place, dim3(nblk), dim3(E <= 1024 ? 256 : 512), 0, st, topk_idx, lrank, blockcnt,
+                           counts, offsets, tile_start, perm, inv, tiles, streamed ? stream_most : skinny_tiles, A, E, nblk);
     } else {
         const size_t nbc = size_t(E) * L.nblk;
         hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
         hipLaunchKernelGGL(k_rank_blocks, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, A, L.nblk);
         hipLaunchKernelGGL(k_scan_blocks, dim3((E + 3) / 4), dim3(256), 0, st, blockcnt, counts, E, L.nblk);
-        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, E);
+        hipLaunchKernelGGL(streamed ? k_offsets<true> : k_offsets<false>, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, tiles, stream_most, E);
         hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, L.nblk);
     }
     if (timed) dynb::timing_mark(st, dynb::ST_SORT, 0);
@@ -1553,7 +1868,22 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     const long long max_mtiles = (long long)(A + TM - 1) / TM + E;
     const int nt1 = (h + TN - 1) / TN, nt2 = (d + TN - 1) / TN;
     const long long span = 8ll * XCD_CHUNK;                   // every XCD's longest run
-    if (naive_stride <= 0) {
+    if (streamed) {
+        static std::atomic<uint64_t> attr_set{0};             // one bit per device
+        int dev = 0;
+        HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+        if (!(attr_set.load() >> (dev & 63) & 1)) {
+            for (const void* f : {reinterpret_cast<const void*>(k_grouped_stream<true>), reinterpret_cast<const void*>(k_grouped_stream<false>)})
+                HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, X_LDS), "hipFuncSetAttribute(k_grouped_stream)");
+            attr_set.fetch_or(uint64_t(1) << (dev & 63));
+        }
+        hipLaunchKernelGGL((k_grouped_stream<true>), dim3(X_GRID), dim3(512), X_LDS, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, tile_start,
+                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u);
+        if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
+        hipLaunchKernelGGL((k_grouped_stream<false>), dim3(X_GRID), dim3(512), X_LDS, st, hid, static_cast<const bf16_t*>(W2), y, tiles, tile_start,
+                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u);
+        if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
+    } else if (naive_stride <= 0) {
         if (skinny1)
             hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(skinny_tiles * ((h + 63) / 64))), dim3(256), 0, st, xb,
                                static_cast<const bf16_t*>(W1), hid, tiles, h, d, (h + 63) / 64, perm, k);

@@ -182,6 +182,42 @@ def test_crowded_experts(dyn, util, oracle, T, d, h, E, k, zipf):
     assert util.normwise(out, oracle_experts(oracle, m, r, W1, W2)) < OUT_TOL
 
 
+EDGES = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 191, 192, 255, 256, 257, 288, 384, 385, 512, 641, 0)
+
+
+@pytest.mark.parametrize("d,h,k,counts", [(256, 320, 1, EDGES + (14000, 13000)),              # 4 and 5 chunks a tile, features cut at 64
+                                          (1024, 1088, 1, EDGES + (5000,)),                   # ... and behind four whole tiles of them
+                                          (448, 256, 2, EDGES + (40000, 30000)),              # more than 65536 uses
+                                          (512, 1024, 3, EDGES + (9000,)),
+                                          (576, 1856, 1, (7000,)), (320, 256, 8, (4200,) * 8)])
+def test_crowded_experts_have_the_bits_of_the_small_tiles(dyn, util, d, h, k, counts):
+    """The kernel of the crowded experts against the one with tiles of 64 rows, which MOE_SEPARATE_PERMUTE always takes: both add up the channels in
+    the same order.  Experts at the edges of its kinds of tiles (32, 64, 128, 256 rows), of one row and of none; tokens whose other uses go to the
+    experts behind."""
+    import torch
+    E, uses = len(counts), sum(counts) * k
+    assert uses >= 64 * E and uses * (d + h) >= 1 << 24                                       # where that kernel is chosen
+    g = torch.Generator(device="cuda").manual_seed(d + h)
+    rnd = lambda *shape, std=1.0: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    first = torch.repeat_interleave(torch.arange(E, device="cuda"), torch.tensor(counts, device="cuda"))
+    first = first[torch.randperm(len(first), generator=g, device="cuda")]
+    T = len(first)
+    x, Wg = rnd(T, d), torch.zeros(E, d, device="cuda", dtype=torch.bfloat16)
+    x[:, :E] = 0
+    want = torch.zeros(E, dtype=torch.int64, device="cuda")
+    for j in range(k):                                                                        # logits: 8 k for the first expert, 8 less for every next
+        e = (first + j) % E
+        x[torch.arange(T, device="cuda"), e] = 8.0 * (k - j)
+        want += torch.bincount(e, minlength=E)
+    Wg[torch.arange(E), torch.arange(E)] = 1.0
+    args = (x, Wg, None, None, rnd(E, h, d, std=d ** -0.5), rnd(E, d, h, std=h ** -0.5), k)
+    a, aux = dyn.moe_forward(*args, want_aux=True)
+    assert (torch.as_tensor(aux.counts).cpu() == want.cpu()).all()
+    b = dyn.moe_forward(*args, flags=dyn.MOE_SEPARATE_PERMUTE)
+    assert torch.isfinite(a.float()).all() and a.float().abs().mean() > 0.1
+    assert (util.to_host(a) == util.to_host(b)).all()
+
+
 def full_layer(dyn, util, m):
     """Runs a benchmark-size layer with per-expert generated weights; returns (out, aux, device inputs)."""
     import torch
