@@ -95,6 +95,52 @@ def test_ragged_shapes_fp32_with_single_scene_programs(dyn, util, oracle, C, H, 
         assert (again[name] == got[name]).all(), name                     # fixed summation order: same bits
 
 
+@pytest.mark.parametrize("dtype,C,H,W", [("f32", 32, 14, 14), ("f32", 33, 9, 13), ("f32", 64, 17, 1), ("f32", 36, 2, 33), ("f32", 40, 5, 31), ("bf16", 64, 10, 14), ("bf16", 34, 21, 7)])
+def test_parameter_gradients_in_parts_are_as_close_as_fp32_products(dyn, util, oracle, dtype, C, H, W):
+    """Maps of one band and more, whole and cut blocks of 32 channels, one column, two segments.  Every unit active, so that no ReLU decision hangs on a rounding:
+    what is left are the sums.  One of n products that is rounded twice for every 16 of them is off by 2^-24 sqrt(n / 8) of itself at most in the mean: 2.5e-6 for
+    the longest here, gradients and activations that carry such errors into it included.  Of activations that are stored in bfloat16 a share of 3e-7 / 2^-8 = 8e-5
+    rounds to the neighbour, 2^-8 away: 2^-8 sqrt(8e-5) = 3.5e-5 of the norm for one module, 1e-4 for the five of a program."""
+    w = iep.small_mixed(seed=C + H, B=6, C=C, H=H, W=W, dtype=dtype, min_len=2, max_len=5)
+    for name in ("feats", "w1", "w3a", "w3b", "b1", "b3a", "b3b"):
+        v = getattr(w, name)
+        if v is not None:
+            setattr(w, name, np.abs(v))
+    dout = np.abs(np.random.default_rng(C).standard_normal(w.feats.shape)).astype(np.float32)
+    ref = oracle.iep_backward_workload(w, dout, round_bf16=dtype == "bf16")
+    got, _ = run_backward(dyn, util, w, dout)
+    for name in NAMES:
+        assert frob(got[name], getattr(ref, name)) < (2.5e-6 if dtype == "f32" else 1e-4), (name, frob(got[name], getattr(ref, name)))
+
+
+@pytest.mark.parametrize("value", [np.inf, 3.4e38])
+def test_parameter_gradients_of_values_without_finite_parts(dyn, util, oracle, value):
+    """An infinite gradient, and one beyond the largest bfloat16: the gradients that it reaches are what sums of fp32 products are, the others untouched."""
+    import torch
+    C, H, W = 32, 7, 7
+    prog, off, arity = np.array([1, 0], np.int32), np.array([0, 2], np.int32), np.array([0, 1], np.uint8)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.rand(s, generator=g, device="cuda") * 0.01
+    weights = dict(w1=rnd(2, C, 2 * C), b1=rnd(2, C), w3a=rnd(2, C, 3, 3, C), b3a=rnd(2, C), w3b=rnd(2, C, 3, 3, C), b3b=rnd(2, C))
+    feats = rnd(1, H, W, C)
+    plan = dyn.dynbatch_plan(prog, off, arity, dyn.DYNB_PLAN_KEEP)
+    dyn.dynbatch_plan_upload(plan)
+    ws = torch.empty(dyn.dynbatch_workspace_bytes(plan, C, H, W, dyn.DYNB_F32), dtype=torch.uint8, device="cuda")
+    out = dyn.dynbatch_execute(plan, weights, feats, workspace=ws)
+    dout = torch.zeros(1, H, W, C, device="cuda")
+    dout[0, 3, 3, 5] = value
+    dout[0, 2, 4, 6] = 1.0
+    grads = dyn.dynbatch_backward(plan, weights, feats, out, ws, dout)
+    mid = torch.relu(torch.nn.functional.conv2d(feats.permute(0, 3, 1, 2).double(), weights["w3a"][1].permute(0, 3, 1, 2).double(), weights["b3a"][1].double(), padding=1))[0]
+    got = grads["dw3b"][1].double()                                               # [Cout][kh][kw][Cin]
+    for kh in range(3):
+        for kw in range(3):
+            want = mid[:, 2 + kh, 2 + kw] * (float("inf") if value == np.inf else float(np.float32(value)))
+            assert torch.allclose(got[5, kh, kw], want, rtol=1e-5), (kh, kw)
+            assert torch.allclose(got[6, kh, kw], mid[:, 1 + kh, 3 + kw], rtol=1e-5), (kh, kw)
+    assert (got[[c for c in range(C) if c not in (5, 6)]] == 0).all()
+
+
 @pytest.mark.parametrize("dtype,C,H,W,B", [("f32", 3, 1, 1, 150), ("f32", 33, 2, 2, 90), ("f32", 20, 3, 3, 40), ("f32", 34, 4, 3, 37), ("f32", 5, 1, 16, 30),
                                            ("f32", 9, 1, 17, 20), ("bf16", 6, 2, 1, 70)])
 def test_parameter_gradients_of_many_items_on_tiny_maps(dyn, util, oracle, dtype, C, H, W, B):
