@@ -49,6 +49,40 @@ struct alignas(16) RowTile { int32_t expert, row0, rows, pad; };
 
 __device__ __forceinline__ bf16x8 ldg_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
+// ------------------------------------------------------------------------------------------ rows on their way into LDS
+// A unit: 64 rows x 64 channels of a matrix, copied without registers on the way.  Eight neighbouring lanes copy 128 bytes of a row, in their order (in any other a
+// request is answered lane by lane, 13.5 bytes a clock instead of 64); a unit is eight blocks of 8 rows.  What an LDS pass of a fragment's read takes
+// together, 16 of its 32 rows (lanes 0-3, 12-15, 20-23, 24-27 or the others), are two rows of every block, an even and an odd one, and the blocks are 16 bytes
+// further apart than their size: all banks.
+constexpr int XBLOCK = 1040, XUNIT = 8 * XBLOCK;
+// the row of its fragment (lane / 32) that lane `lane` copies into block `block`
+__device__ __forceinline__ int copied_row(int block, int lane)
+{
+    const int odd = lane >> 3 & 1, g = lane >> 4 & 1;
+    return (block >> 1) * 8 + (g ^ (block >> 1 & 1) ^ (block >> 2 & 1)) * 4 + (block & 1) * 2 + odd;
+}
+// where in a unit lane q + 32 hk reads row q of the first fragment (the second lies 512 bytes further), its half of K-step 0 (each next one 32 bytes further)
+__device__ __forceinline__ uint32_t fragment_at(int q, int hk)
+{
+    return uint32_t(((q >> 3) * 2 + (q >> 1 & 1)) * XBLOCK + (((q >> 2 ^ q >> 3 ^ q >> 4) & 1) * 2 + (q & 1)) * 128 + hk * 16);
+}
+__device__ __forceinline__ void lds_copy16(const char* base, uint32_t off, uint32_t lds_at)   // 64 lanes x 16 bytes -> LDS at lds_at, lane after lane
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    asm volatile("" : "+s"(base), "+v"(off));                                      // (a scalar base and a lane's offset, and no address of 64 bits per lane kept for every request)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(base + off),
+                                     (__attribute__((address_space(3))) uint32_t*)(lds_raw + lds_at), 16, 0, 0);
+}
+// *p by the scalar unit: the address is the same for the whole wave, and nobody writes there during the kernel
+__device__ __forceinline__ int32_t uniform_load(const int32_t* p)
+{
+    return __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(4))) int32_t*)(p));
+}
+// All but this wave's newest N requests and stores have been answered
+template <int N> __device__ __forceinline__ void answered_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// (Not __syncthreads, which waits for all requests into LDS)
+__device__ __forceinline__ void meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ------------------------------------------------------------------------------------------ gate
 // Workgroup tile: 64 tokens x 64 experts, both gate matrices at once.  Operands are staged through
 // LDS in K-chunks of 64 with coalesced 128-byte row reads (see the grouped GEMM below for why), the
@@ -139,6 +173,85 @@ __global__ __launch_bounds__(256) void k_gate(const bf16_t* __restrict__ x, cons
     for (int i = 0; i < 16; ++i) {
         float v = ag[i];
         if (noise) v += nz[i] * softplus_f(an[i]);
+        if (token(i) < T) logits[size_t(token(i)) * E + e] = v;
+    }
+}
+
+// The same tiles where d is a multiple of 64: the K-chunks go straight into LDS, two ahead, with one barrier each, instead of one ahead by way of registers
+// with two.  (What k_gate waits for are d / 64 trips to memory, one after the other.)  The sums are k_gate's bit for bit.
+constexpr int GS_BUFS = 3, GS_LDS = GS_BUFS * 3 * XUNIT;     // x rows, Wg rows, Wn rows of three chunks: two workgroups a CU
+
+template <bool NOISY>
+__global__ __launch_bounds__(256, 2) void k_gate_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg, const bf16_t* __restrict__ Wn,
+                                                        const float* __restrict__ noise, float* __restrict__ logits, int T, int d, int E, int32_t* __restrict__ clear)
+{
+    if (clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear = 0;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    constexpr int UNITS = NOISY ? 3 : 2, PIECES = 2 * UNITS;
+    constexpr uint32_t BUF = uint32_t(UNITS * XUNIT);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane & 31, hk = lane >> 5;
+    const int t0 = blockIdx.y * 64, e0 = blockIdx.x * 64, th = wave & 1, eh = wave >> 1;
+    // wave w copies blocks 2 w and 2 w + 1 of every unit
+    uint32_t x_off[2], w_off[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = (lane >> 5) * 32 + copied_row(2 * wave + i, lane);
+        x_off[i] = (uint32_t(min(t0 + row, T - 1) - t0) * uint32_t(d) + uint32_t(lane & 7) * 8u) * 2u;
+        w_off[i] = (uint32_t(min(e0 + row, E - 1) - e0) * uint32_t(d) + uint32_t(lane & 7) * 8u) * 2u;
+    }
+    const char* x_next = reinterpret_cast<const char*>(x + size_t(t0) * d);
+    const char* g_next = reinterpret_cast<const char*>(Wg + size_t(e0) * d);
+    const char* n_next = reinterpret_cast<const char*>((NOISY ? Wn : Wg) + size_t(e0) * d);
+    uint32_t fill = 0, take = 0;
+    auto request = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t at = fill + uint32_t((2 * wave + i) * XBLOCK);
+            lds_copy16(x_next, x_off[i], at);
+            lds_copy16(g_next, w_off[i], at + XUNIT);
+            if (NOISY) lds_copy16(n_next, w_off[i], at + 2 * XUNIT);
+        }
+        x_next += 128;
+        g_next += 128;
+        n_next += 128;
+        fill = fill == (GS_BUFS - 1) * BUF ? 0 : fill + BUF;
+    };
+    const int nchunk = d / 64;
+    // the noise values first (k_gate): they are there when the first chunk is
+    const int e = e0 + eh * 32 + q;
+    auto token = [&](int i) { return t0 + th * 32 + 8 * (i / 4) + 4 * hk + (i % 4); };
+    float nz[16];
+    if (NOISY) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) nz[i] = noise[size_t(min(token(i), T - 1)) * E + min(e, E - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    request();
+    if (nchunk > 1) request();
+    f32x16 ag, an;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { ag[i] = 0.f; an[i] = 0.f; }
+    const uint32_t slot = fragment_at(q, hk);
+#pragma unroll 1
+    for (int c = 0; c < nchunk; ++c) {
+        if (c + 1 < nchunk) answered_but<PIECES>();
+        else answered_but<0>();
+        meet();
+        if (c + 2 < nchunk) request();                         // (into the place of chunk c - 1, which all waves are done with)
+        const uint32_t xf = take + uint32_t(th * 512) + slot, wf = take + XUNIT + uint32_t(eh * 512) + slot;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const bf16x8 fx = *reinterpret_cast<const bf16x8*>(lds_raw + xf + ks * 32);
+            ag = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx, *reinterpret_cast<const bf16x8*>(lds_raw + wf + ks * 32), ag, 0, 0, 0);
+            if (NOISY) an = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx, *reinterpret_cast<const bf16x8*>(lds_raw + wf + XUNIT + ks * 32), an, 0, 0, 0);
+        }
+        take = take == (GS_BUFS - 1) * BUF ? 0 : take + BUF;
+    }
+    if (e >= E) return;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        float v = ag[i];
+        if (NOISY) v += nz[i] * softplus_f(an[i]);
         if (token(i) < T) logits[size_t(token(i)) * E + e] = v;
     }
 }
@@ -1367,28 +1480,10 @@ __global__ __launch_bounds__(256, 3) void k_grouped_skinny(const bf16_t* __restr
 // pass, k_grouped_gemm 0.68); the others, memory, where results that are written cost the reading six times their bytes (4 GiB of weights alone in 675
 // us, with 64 MB of results 737).
 // The sums are k_grouped_gemm's bit for bit: 32x32x16 MFMAs over the channels in the same order.
-constexpr int XBLOCK = 1040, XUNIT = 8 * XBLOCK;               // LDS: 64 rows of a chunk in eight blocks (slot_of)
 constexpr int XIDX = 18 * XUNIT;                               // behind the chunks (2 of 8 units, 3 of 6): the rows' places in `gather`, two tiles'
 constexpr int XLIST = XIDX + 2 * XR * 4, XLIST_LEN = 512;      // ... and the workgroup's next tiles
 constexpr int X_LDS = XLIST + XLIST_LEN * 16;
 constexpr int X_GRID = 256;
-
-__device__ __forceinline__ void lds_copy16(const char* base, uint32_t off, uint32_t lds_at)   // 64 lanes x 16 bytes -> LDS at lds_at, lane after lane
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    asm volatile("" : "+s"(base), "+v"(off));                                      // (a scalar base and a lane's offset, and no address of 64 bits per lane kept for every request)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(base + off),
-                                     (__attribute__((address_space(3))) uint32_t*)(lds_raw + lds_at), 16, 0, 0);
-}
-// *p by the scalar unit: the address is the same for the whole wave, and nobody writes there during the kernel
-__device__ __forceinline__ int32_t uniform_load(const int32_t* p)
-{
-    return __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(4))) int32_t*)(p));
-}
-// All but this wave's newest N requests and stores have been answered
-template <int N> __device__ __forceinline__ void answered_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// (Not __syncthreads, which waits for all requests into LDS)
-__device__ __forceinline__ void meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <bool RELU>
 __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
@@ -1401,13 +1496,9 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
     const int nchunk = K / 64;
     const int die = blockIdx.x & 7, slot = blockIdx.x >> 3;
 
-    // ---- where things lie in LDS.  Eight neighbouring lanes copy 128 bytes of a row, in their order (in any other a request is answered lane by lane, 13.5
-    // bytes a clock instead of 64); wave w copies block w of every unit of 64 rows.  What an LDS pass of a fragment's read takes together, 16 of its
-    // 32 rows (lanes 0-3, 12-15, 20-23, 24-27 or the others), are two rows of every block, an even and an odd one, and the blocks are 16 bytes further
-    // apart than their size: all banks.  Lane l copies row l / 8 of the block, which lane s_q of fragment l / 32 reads
-    const int s_par = lane >> 3 & 1, s_g = lane >> 4 & 1;
-    const int s_q = (wave >> 1) * 8 + (s_g ^ (wave >> 1 & 1) ^ (wave >> 2 & 1)) * 4 + (wave & 1) * 2 + s_par;
-    const uint32_t x_slot = uint32_t(((q >> 3) * 2 + (q >> 1 & 1)) * XBLOCK + (((q >> 2 ^ q >> 3 ^ q >> 4) & 1) * 2 + (q & 1)) * 128 + hk * 16);
+    // ---- where things lie in LDS: wave w copies block w of every unit
+    const int s_q = copied_row(wave, lane);
+    const uint32_t x_slot = fragment_at(q, hk);
     // accumulator row 8 b + 4 h + c of lane half h is given feature 16 h + 4 b + c: a lane ends up with 16 consecutive features of a row
     const int x_row = (lane >> 5) * 32 + s_q, w_row = (lane >> 5) * 32 + (s_q >> 2 & 1) * 16 + (s_q >> 3) * 4 + (s_q & 3);
     const size_t w_unit = size_t(K) * 128;                     // bytes from one unit of features to the next
@@ -1777,7 +1868,24 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1200)
         hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),
                            static_cast<const bf16_t*>(Wn), noise, logits, T, d, E, done);
-    else if (T > T_big)
+    // (Of k_gate's tiles, those of whole K-chunks go to k_gate_stream: all of them without noise, and with noise as many as two workgroups a CU hold at once;
+    // beyond that the five of k_gate hide more.  The whole pass in us, k_gate / k_gate_stream, by tiles and d: noisy 256 x 512 153.6 / 150.5, 306 x 576 300.0 / 298.2,
+    // 222 x 768 101.1 / 97.6, 80 x 320 54.1 / 52.1, 376 x 192 47.5 / 47.6, and on the other side 518 x 192 79.2 / 80.5, 845 x 256 81.1 / 82.6, 2370 x 768 312 / 321; without
+    // noise 90 x 384 62.1 / 59.0, 240 x 832 91.1 / 85.1, 430 x 128 38.2 / 36.8, 2057 x 448 191.3 / 186.2)
+    else if (const long long tiles = (long long)((E + 63) / 64) * ((T - T_big + 63) / 64); T > T_big && d % 64 == 0 && d <= 1 << 20 && (!noise || tiles <= 512)) {
+        static std::atomic<uint64_t> attr_set{0};             // one bit per device: LDS beyond 64 KB
+        int dev = 0;
+        HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+        if (!(attr_set.load() >> (dev & 63) & 1)) {
+            for (const void* f : {reinterpret_cast<const void*>(k_gate_stream<true>), reinterpret_cast<const void*>(k_gate_stream<false>)})
+                HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS), "hipFuncSetAttribute(k_gate_stream)");
+            attr_set.fetch_or(uint64_t(1) << (dev & 63));
+        }
+        hipLaunchKernelGGL(noise ? k_gate_stream<true> : k_gate_stream<false>, dim3((E + 63) / 64, (T - T_big + 63) / 64), dim3(256),
+                           noise ? GS_LDS : GS_LDS / 3 * 2, st, xb + size_t(T_big) * d,
+                           static_cast<const bf16_t*>(Wg), static_cast<const bf16_t*>(Wn), noise ? noise + size_t(T_big) * E : nullptr,
+                           logits + size_t(T_big) * E, T - T_big, d, E, done);
+    } else if (T > T_big)
         hipLaunchKernelGGL(k_gate, dim3((E + 63) / 64, (T - T_big + 63) / 64), dim3(256), 0, st, xb + size_t(T_big) * d,
                            static_cast<const bf16_t*>(Wg), static_cast<const bf16_t*>(Wn), noise ? noise + size_t(T_big) * E : nullptr,
                            logits + size_t(T_big) * E, T - T_big, d, E, done);

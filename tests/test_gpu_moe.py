@@ -168,6 +168,24 @@ def test_many_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
     test_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy)
 
 
+@pytest.mark.parametrize("T,d,E,noisy", [(397, 64, 801, True), (513, 128, 640, True), (641, 192, 511, False), (700, 256, 463, True), (1217, 320, 258, False),
+                                         (2049, 64, 1000, False), (2049, 64, 1000, True)])
+def test_gate_tiles_of_whole_chunks(dyn, util, oracle, T, d, E, noisy):
+    """One to five chunks of 64 channels, tokens and experts that end inside a tile; as many tiles as two workgroups a CU hold, and more."""
+    m = moe.small(seed=T + E, T=T, d=d, h=64, E=E, k=2)
+    W1, W2 = stack(m)
+    dev = util.moe_inputs_dev(m, W1, W2)
+    _, aux = dyn.moe_forward(dev["x"], dev["Wg"], dev["Wn"] if noisy else None, dev["noise"] if noisy else None, dev["W1"], dev["W2"], 2, want_aux=True)
+    x, Wg, Wn = (dev[n].double() for n in ("x", "Wg", "Wn"))
+    want = x @ Wg.T
+    if noisy:
+        want += dev["noise"].double() * (x @ Wn.T).logaddexp(x.new_zeros(1))
+    got = aux.logits if hasattr(aux, "logits") else aux["logits"]
+    import torch
+    got = torch.as_tensor(got).to(want.device).double()
+    assert float((got - want).abs().max() / want.abs().max()) < 1e-4
+
+
 @pytest.mark.parametrize("T,d,h,E,k,zipf", [(1536, 256, 512, 6, 2, 1.5),      # most groups beyond 256 rows, ragged rests
                                              (2048, 128, 256, 3, 1, 0.0),      # near-equal groups, short K loops
                                              (700, 256, 256, 2, 2, 0.0)])      # every token to both experts: 700 rows each
