@@ -1064,15 +1064,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __rest
         for (int i = 0; i < 4; ++i) {
             if (e + i < E) {
                 first[e + i] = at + before[i];
+                if (!STREAM && tiles)
+                    for (int t = blk; t < tl[i]; t += nblk) tiles[tat + t] = RowTile{e + i, at + t * TM, min(TM, c[i] - t * TM), 0};
                 if (tables) {
                     counts[e + i] = c[i];
                     offsets[e + i] = at;
                     if constexpr (STREAM) put_stream_tiles(tiles, max_tiles, tat, e + i, at, c[i]);
-                    else {
-                        tile_start[e + i] = tat;
-                        if (tiles)
-                            for (int t = 0; t < tl[i]; ++t) tiles[tat + t] = RowTile{e + i, at + t * TM, min(TM, c[i] - t * TM), 0};
-                    }
+                    else tile_start[e + i] = tat;
                 }
             }
             at += c[i];
@@ -1467,6 +1465,137 @@ __global__ __launch_bounds__(256, 3) void k_grouped_skinny(const bf16_t* __restr
     if (tile.rows <= 16) skinny_tile<RELU, 1>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
     else if (tile.rows <= 32) skinny_tile<RELU, 2>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
     else skinny_tile<RELU, 4>(in, We, out, tile, n0, N, K, gather, kdiv, lds);
+}
+
+// The expert layers of whole K-chunks (the rule stands where it is applied): a stream of weights, each used for a handful of rows, of which every CU should have
+// its share under way at once.  A workgroup owns up to 64 rows x 128 features; chunks of 64 channels go from memory straight into LDS, BUFS - 1 of them ahead, with one
+// barrier each (k_grouped_gemm and k_grouped_skinny wait for a trip to memory per 64 and 32 channels), the weights' first ones ahead of the look-up of the rows.  A wave
+// multiplies 32 features.  What bounds it is memory, at 4096 tokens, 256 experts, d 512, h 1024 (two layers of 268 MB, as many as 20 MB of results, which cost the
+// reading six times their bytes: 58 us a layer at the rate of a large copy): 62.7 and 63.6 us with k_grouped_gemm, 57.3 and 58.2 so.  (Workgroups that stay for the
+// launch and ask for the next tile's chunks ahead, as k_grouped_stream's: 60.0 and 62.9.  Without the two of __launch_bounds__ the sums move to AGPRs and back every
+// chunk: 59.2 and 62.0.)
+// The sums are k_grouped_gemm's bit for bit: 32x32x16 MFMAs over the channels in the same order.
+// `chunk` consecutive tiles are dealt to one XCD at a time: the features of a row tile, whose rows they share, and an expert's next row tile, whose weights it shares.
+constexpr int FEW_F = 128;
+constexpr int few_lds(int bufs) { return bufs * 3 * XUNIT + 4 * 256; }   // a chunk: two units of weights and one of rows; each wave's places of the rows
+
+template <bool RELU, int BUFS>
+__global__ __launch_bounds__(256, 2) void k_grouped_few(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
+                                                     const RowTile* __restrict__ tiles, int n_tiles_m, int chunk, int N, int K, int n_tiles_n,
+                                                     const int32_t* __restrict__ gather, uint32_t m_kdiv)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    constexpr uint32_t BUF = 3 * XUNIT;
+    constexpr uint32_t PLACES = BUFS * BUF;
+    constexpr int PIECES = 6;                                  // of a chunk, each wave's
+    const int j = blockIdx.x >> 3, run = j / chunk, lin = (run * 8 + int(blockIdx.x & 7)) * chunk + j - run * chunk;
+    const int m = lin / n_tiles_n, n0 = (lin - m * n_tiles_n) * FEW_F;
+    if (m >= n_tiles_m) return;
+    const int expert = uniform_load(&tiles[m].expert), row0 = uniform_load(&tiles[m].row0), rows = uniform_load(&tiles[m].rows);
+    if (rows == 0) return;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane & 31, hk = lane >> 5;
+    // wave w copies blocks 2 w and 2 w + 1 of every unit
+    uint32_t w_off[2][2], x_off[2];
+    int x_row[2];
+    bool x_on[2];                                              // this lane's row is there (lane 0: always, so that every wave makes every request, which it counts)
+    if constexpr (RELU)                                        // (the first layer: gathered rows.  Through LDS, for the compiler waits for all requests where it waits for a register's)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(gather + row0 + min(lane, rows - 1)),
+                                         (__attribute__((address_space(3))) uint32_t*)(lds_raw + PLACES + wave * 256), 4, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int s_q = copied_row(2 * wave + i, lane), f = (lane >> 5) * 32 + (s_q >> 2 & 1) * 16 + (s_q >> 3) * 4 + (s_q & 3);
+        x_row[i] = min((lane >> 5) * 32 + s_q, rows - 1);
+        x_on[i] = (lane >> 5) * 32 + s_q < rows || lane == 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) w_off[u][i] = (uint32_t(min(n0 + u * 64 + f, N - 1) - n0) * uint32_t(K) + uint32_t(lane & 7) * 8u) * 2u;
+    }
+    const char* w_next = reinterpret_cast<const char*>(W + (size_t(expert) * N + n0) * K);
+    const char* x_next = reinterpret_cast<const char*>(in);
+    uint32_t fill = 0, take = 0;
+    auto request_w = [&](uint32_t to) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) lds_copy16(w_next, w_off[u][i], to + uint32_t(u * XUNIT + (2 * wave + i) * XBLOCK));
+        w_next += 128;
+    };
+    auto request_x = [&](uint32_t to) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (x_on[i]) lds_copy16(x_next, x_off[i], to + uint32_t(2 * XUNIT + (2 * wave + i) * XBLOCK));
+        x_next += 128;
+    };
+    const int nchunk = K / 64;
+    // the weights first: the rows' places are on their way
+    request_w(0);
+    if (BUFS == 3 && nchunk > 1) request_w(BUF);
+    if constexpr (RELU) {
+        if (BUFS == 3 && nchunk > 1) answered_but<8>();
+        else answered_but<4>();
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        uint32_t row = uint32_t(row0 + x_row[i]);
+        if constexpr (RELU) {
+            row = *reinterpret_cast<const uint32_t*>(lds_raw + PLACES + wave * 256 + x_row[i] * 4);
+            if (m_kdiv) row = __umulhi(row, m_kdiv);           // / k
+        }
+        x_off[i] = (row * uint32_t(K) + uint32_t(lane & 7) * 8u) * 2u;
+    }
+    request_x(0);
+    if (BUFS == 3 && nchunk > 1) request_x(BUF);
+    fill = (BUFS - 1) * BUF;
+    f32x16 acc[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+    const uint32_t slot = fragment_at(q, hk);
+    auto multiply = [&](auto blocks) {                         // the tile, one or two blocks of 32 rows
+        constexpr int NB = decltype(blocks)::value;
+#pragma unroll 1
+        for (int c = 0; c < nchunk; ++c) {
+            if (BUFS == 2 || c + 1 >= nchunk) answered_but<0>();
+            else if (c == 0) answered_but<2>();                // (all but chunk 1's rows)
+            else answered_but<PIECES>();
+            meet();
+            if (c + BUFS - 1 < nchunk) {                       // (into the place of chunk c - 1, which all waves are done with)
+                request_w(fill);
+                request_x(fill);
+                fill = fill == (BUFS - 1) * BUF ? 0 : fill + BUF;
+            }
+            const uint32_t wu = take + uint32_t((wave >> 1) * XUNIT + (wave & 1) * 512) + slot, xu = take + 2 * XUNIT + slot;
+            bf16x8 wf[4], xf[NB][4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                wf[ks] = *reinterpret_cast<const bf16x8*>(lds_raw + wu + ks * 32);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) xf[b][ks] = *reinterpret_cast<const bf16x8*>(lds_raw + xu + b * 512 + ks * 32);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks], xf[b][ks], acc[b], 0, 0, 0);
+            take = take == (BUFS - 1) * BUF ? 0 : take + BUF;
+        }
+    };
+    if (rows > 32) multiply(std::integral_constant<int, 2>{});
+    else multiply(std::integral_constant<int, 1>{});
+    // lane: features n .. + 15 of row 32 b + q
+    const int n = n0 + wave * 32 + 16 * hk;
+    if (n >= N) return;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        if (32 * b + q >= rows) continue;
+        bf16_t* const to = out + size_t(row0 + 32 * b + q) * N + n;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const f32x16& v = acc[b];
+            u32x4 o = {pack_bf16x2(v[8 * p + 0], v[8 * p + 1]), pack_bf16x2(v[8 * p + 2], v[8 * p + 3]), pack_bf16x2(v[8 * p + 4], v[8 * p + 5]), pack_bf16x2(v[8 * p + 6], v[8 * p + 7])};
+            if (RELU) { o.x = relu_bf16x2(o.x); o.y = relu_bf16x2(o.y); o.z = relu_bf16x2(o.z); o.w = relu_bf16x2(o.w); }
+            *reinterpret_cast<u32x4*>(to + p * 8) = o;
+        }
+    }
 }
 
 // The expert layers for crowded experts (the rule stands where it is applied): one workgroup per CU that stays for the launch and sees its tiles as one stream
@@ -1894,7 +2023,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
     const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
     // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.
-    // An expert layer of few tiles and long sums runs on k_grouped_skinny, each layer for itself.  k_grouped_gemm pays 1.2 to 1.5 us for
+    // An expert layer of few tiles and long sums that k_grouped_few (below) does not take runs on k_grouped_skinny, each layer for itself.  k_grouped_gemm pays 1.2 to 1.5 us for
     // every 64 summed channels however few tiles there are.  k_grouped_skinny reads an expert's weights once per row tile, and where a tile
     // has many rows, every wave multiplies up to four fragments of them with each of the weights.  us, k_grouped_gemm / k_grouped_skinny, by
     // features x summed channels and rounds of 768 workgroups (three a CU):
@@ -1922,13 +2051,30 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     };
     const int stream_most = std::min(A, E + A / XR);           // at least as many tiles of k_grouped_stream as there are
     // Crowded experts, 64 uses each and more in the mean, and products for a tile of 256 x 256 on every CU and more (2^24 = 256 of them, both layers
-    // together): k_grouped_stream.  Its tiles are few and large.  The whole pass, others / so in us, by mean uses of an expert and tiles: 2250, 692: 204 / 157;
+    // together): k_grouped_stream.  Its tiles are few and large: where k_grouped_few can take the layers (up to 65536 uses), from 384 features on, which fill 256 + 128, and from
+    // 2^33 products a layer.  The whole pass, others / so in us: k_grouped_gemm, by mean uses of an expert and tiles: 2250, 692: 204 / 157;
     // 3870, 1180: 288 / 217; 541, 1087: 343 / 271; 788, 863: 192 / 139; 553, 422: 103 / 92; 508, 283: 78 / 67; 370, 2430: 660 / 553; 116, 291: 154 / 136; 99, 525: 171 /
     // 164; 64, 3072 (Zipf 1.2): 2010 / 1930; 152, 372: 91 / 94; and on the other side of the line 1190, 167: 51 / 55; 187, 135: 48 / 55; 399, 38: 40 / 49; 48, 561: 313 /
-    // 312; 63, 1127: 444 / 450; 37, 395: 301 / 303; 32, 192: 153 / 159
+    // 312; 63, 1127: 444 / 450; 37, 395: 301 / 303; 32, 192: 153 / 159.  k_grouped_few, by uses, experts, d x h: 20216, 54, 1536 x 384: 126 / 122; 15200, 7, 1600 x 768:
+    // 96 / 91; 10902, 54, 448 x 1280: 117 / 106; 17964, 22, 1792 x 1536 400 / 266; and on the other side 6435, 2, 512 x 3072 82 / 120; 7906, 16, 384 x 1792 66 / 81; 17965, 4, 448 x
+    // 896 80 / 91; 13256, 119, 320 x 2112 97 / 109; 28110, 3, 256 x 1920 121 / 129 (of 70 shapes within the old line 19 were faster with k_grouped_few, all others 2 to 50 % slower)
     const bool streamed = fused_permute && naive_stride <= 0 && !small && d % 64 == 0 && h % 64 == 0 && d >= 256 && h >= 256 && E <= SMALL_EXPERTS && A < 1 << 22 && k <= 1024 &&
-                        size_t(A) * size_t(std::max(d, h)) < size_t(1) << 31 && A >= 64 * E && size_t(A) * size_t(d + h) >= size_t(1) << 24;
-    const bool skinny1 = !streamed && skinny_layer(h, d), skinny2 = !streamed && skinny_layer(d, h), skinny = skinny1 || skinny2;
+                        size_t(A) * size_t(std::max(d, h)) < size_t(1) << 31 && A >= 64 * E && size_t(A) * size_t(d + h) >= size_t(1) << 24 &&
+                        (!mid || (std::min(d, h) >= 384 && double(A) * d * h >= double(1ll << 33)));
+    // All other layers of whole K-chunks whose row tiles have a table (up to 65536 uses and 4096 experts): k_grouped_few, but for single chunks of few rows a tile
+    // (where it saves no trip to memory), and long sums in a fraction of a tile for every fourth CU (a CU alone gets 58 GB/s: k_grouped_skinny has half the features).  Three chunks
+    // in LDS, two workgroups a CU, where that holds all of them and for long sums, else two chunks and three workgroups.  112 passes over 4 to 32768 tokens, 2 to 2048
+    // experts, 64 to 4096 channels, uniform and skewed, take 0.82 of the time in the geometric mean, 0.59 to 1.00 (always two chunks: 1.02 times as long as so, up to 1.23; always three 1.02, up to 1.13).  us a
+    // pass, before / so, by tokens x experts, uses, d x h: 37 x 256, 2, 512 x 1024 31.0 / 25.4; 4096 x 256, 2, 512 x 1024 86 / 80; 86 x 72, 1, 1856 x 1344 73 / 43;
+    // 542 x 51, 4, 896 x 256 54 / 36; 13879 x 184, 4, 64 x 640 98 / 72; 22 x 38, 4, 64 x 192 21.7 / 19.5; 15959 x 1631, 4, 448 x 512 469 / 446; what is left out: one chunk of few
+    // rows, 4811 x 1394, 1, 64 x 3904 279 / 286; few tiles of long sums, 55 x 57, 2, 128 x 3776 42.0 / 43.9
+    auto few_tiles = [&](int N) { return (long long)skinny_tiles * ((N + FEW_F - 1) / FEW_F); };
+    auto few_layer = [&](int N, int K) {
+        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 &&
+               (K >= 128 || A >= 16ll * skinny_tiles) && (few_tiles(N) >= 64 || K < 2560);
+    };
+    const bool few1 = few_layer(h, d), few2 = few_layer(d, h);
+    const bool skinny1 = !streamed && !few1 && skinny_layer(h, d), skinny2 = !streamed && !few2 && skinny_layer(d, h), skinny = skinny1 || skinny2 || few1 || few2;
     RowTile* const tiles = skinny || streamed ? reinterpret_cast<RowTile*>(xs) : nullptr;
     // m2 top-k + softmax
     const dim3 tk_grid((T + 3) / 4), tk_block(256);
@@ -1992,7 +2138,28 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                            stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else if (naive_stride <= 0) {
-        if (skinny1)
+        if (few1 || few2) {
+            static std::atomic<uint64_t> attr_set{0};         // one bit per device
+            int dev = 0;
+            HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+            if (!(attr_set.load() >> (dev & 63) & 1)) {
+                for (const void* f : {reinterpret_cast<const void*>(k_grouped_few<true, 3>), reinterpret_cast<const void*>(k_grouped_few<false, 3>)})
+                    HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, few_lds(3)), "hipFuncSetAttribute(k_grouped_few)");
+                attr_set.fetch_or(uint64_t(1) << (dev & 63));
+            }
+        }
+        auto few = [&](auto relu, const bf16_t* from, const void* W, bf16_t* to, int N, int K, const int32_t* rows_at) {
+            const long long all = few_tiles(N);
+            const bool three = all <= 512 || K >= 1024;
+            // (tiles dealt to an XCD at once: sixteen, or as many as leave all eight eight turns)
+            const int chunk = int(std::min(16ll, std::max(1ll, all / 64))), nt = (N + FEW_F - 1) / FEW_F;
+            hipLaunchKernelGGL((three ? k_grouped_few<decltype(relu)::value, 3> : k_grouped_few<decltype(relu)::value, 2>),
+                               dim3(unsigned((all + 8 * chunk - 1) / (8 * chunk) * (8 * chunk))), dim3(256), few_lds(three ? 3 : 2), st, from,
+                               static_cast<const bf16_t*>(W), to, tiles, skinny_tiles, chunk, N, K, nt, rows_at,
+                               k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u);   // (exact: places below 65536, and k no more)
+        };
+        if (few1) few(std::true_type{}, xb, W1, hid, h, d, perm);
+        else if (skinny1)
             hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(skinny_tiles * ((h + 63) / 64))), dim3(256), 0, st, xb,
                                static_cast<const bf16_t*>(W1), hid, tiles, h, d, (h + 63) / 64, perm, k);
         else
@@ -2000,7 +2167,8 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                                fused_permute ? xb : xs, static_cast<const bf16_t*>(W1), hid, offsets, tile_start, E, h, d, nt1,
                                fused_permute ? perm : nullptr, k);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
-        if (skinny2)
+        if (few2) few(std::false_type{}, hid, W2, y, d, h, nullptr);
+        else if (skinny2)
             hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(skinny_tiles * ((d + 63) / 64))), dim3(256), 0, st, hid,
                                static_cast<const bf16_t*>(W2), y, tiles, d, h, (d + 63) / 64, nullptr, 1);
         else

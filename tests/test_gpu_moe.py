@@ -203,18 +203,24 @@ def test_crowded_experts(dyn, util, oracle, T, d, h, E, k, zipf):
 EDGES = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 191, 192, 255, 256, 257, 288, 384, 385, 512, 641, 0)
 
 
-@pytest.mark.parametrize("d,h,k,counts", [(256, 320, 1, EDGES + (14000, 13000)),              # 4 and 5 chunks a tile, features cut at 64
+@pytest.mark.parametrize("d,h,k,counts", [(256, 320, 1, EDGES + (40000, 30000)),              # 4 and 5 chunks a tile, features cut at 64
                                           (1024, 1088, 1, EDGES + (5000,)),                   # ... and behind four whole tiles of them
                                           (448, 256, 2, EDGES + (40000, 30000)),              # more than 65536 uses
                                           (512, 1024, 3, EDGES + (9000,)),
-                                          (576, 1856, 1, (7000,)), (320, 256, 8, (4200,) * 8)])
+                                          (576, 1856, 1, (9000,)), (320, 256, 8, (1100,) * 8)])
 def test_crowded_experts_have_the_bits_of_the_small_tiles(dyn, util, d, h, k, counts):
     """The kernel of the crowded experts against the one with tiles of 64 rows, which MOE_SEPARATE_PERMUTE always takes: both add up the channels in
     the same order.  Experts at the edges of its kinds of tiles (32, 64, 128, 256 rows), of one row and of none; tokens whose other uses go to the
     experts behind."""
-    import torch
     E, uses = len(counts), sum(counts) * k
     assert uses >= 64 * E and uses * (d + h) >= 1 << 24                                       # where that kernel is chosen
+    assert uses > 65536 or min(d, h) >= 384 and uses * d * h >= 1 << 33
+    bits_of_both_ways(dyn, util, d, h, k, counts)
+
+
+def bits_of_both_ways(dyn, util, d, h, k, counts):
+    import torch
+    E = len(counts)
     g = torch.Generator(device="cuda").manual_seed(d + h)
     rnd = lambda *shape, std=1.0: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
     first = torch.repeat_interleave(torch.arange(E, device="cuda"), torch.tensor(counts, device="cuda"))
@@ -234,6 +240,19 @@ def test_crowded_experts_have_the_bits_of_the_small_tiles(dyn, util, d, h, k, co
     b = dyn.moe_forward(*args, flags=dyn.MOE_SEPARATE_PERMUTE)
     assert torch.isfinite(a.float()).all() and a.float().abs().mean() > 0.1
     assert (util.to_host(a) == util.to_host(b)).all()
+
+
+@pytest.mark.parametrize("d,h,k,counts", [(64, 128, 1, (1, 2, 31, 32, 33, 0, 63, 64, 65, 127, 128, 129)),   # one chunk and two
+                                          (128, 192, 2, (1, 0, 31, 33, 64, 65, 200)),             # features cut at 64
+                                          (192, 1024, 1, (1, 31, 32, 33, 64, 65, 0, 130) * 12),   # three chunks in two places, sixteen in three
+                                          (320, 2560, 3, (70, 0, 3)),                             # forty chunks; 64 features of a tile's 128
+                                          (512, 64, 8, (5, 60, 0, 64) * 16),
+                                          (960, 704, 1, (1, 64, 0, 65) * 120),                    # more than a round of the workgroups
+                                          (64, 64, 2, (1600,) * 32)])
+def test_layers_of_whole_chunks_have_the_bits_of_the_general_kernel(dyn, util, d, h, k, counts):
+    """k_grouped_few with two and three chunks in LDS against the kernel that MOE_SEPARATE_PERMUTE takes: both add up the channels in the same order.  Row
+    tiles of 1 to 64 rows around the halves that a wave multiplies, experts without uses, one chunk to forty."""
+    bits_of_both_ways(dyn, util, d, h, k, counts)
 
 
 def full_layer(dyn, util, m):
