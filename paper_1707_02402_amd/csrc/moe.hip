@@ -45,7 +45,7 @@ constexpr int MAX_K = 8;          // uses of a token whose places are kept in re
 constexpr int MG = 8;             // row tiles of one expert that walk the feature tiles together
 constexpr int XCD_CHUNK = 128;    // most consecutive grouped-GEMM tiles dealt to one XCD
 constexpr uint32_t XCD_CUS = 32;
-struct alignas(16) RowTile { int32_t expert, row0, rows, pad; };
+struct alignas(16) RowTile { int32_t expert, row0, rows, alone; };   // alone: k_grouped_stream's, no other tile has this expert
 
 __device__ __forceinline__ bf16x8 ldg_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
@@ -66,12 +66,13 @@ __device__ __forceinline__ uint32_t fragment_at(int q, int hk)
 {
     return uint32_t(((q >> 3) * 2 + (q >> 1 & 1)) * XBLOCK + (((q >> 2 ^ q >> 3 ^ q >> 4) & 1) * 2 + (q & 1)) * 128 + hk * 16);
 }
+template <bool ONCE = false>                                   // ONCE: nobody else wants these bytes, they need not stay in any cache
 __device__ __forceinline__ void lds_copy16(const char* base, uint32_t off, uint32_t lds_at)   // 64 lanes x 16 bytes -> LDS at lds_at, lane after lane
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     asm volatile("" : "+s"(base), "+v"(off));                                      // (a scalar base and a lane's offset, and no address of 64 bits per lane kept for every request)
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(base + off),
-                                     (__attribute__((address_space(3))) uint32_t*)(lds_raw + lds_at), 16, 0, 0);
+                                     (__attribute__((address_space(3))) uint32_t*)(lds_raw + lds_at), 16, 0, ONCE ? 2 : 0);
 }
 // *p by the scalar unit: the address is the same for the whole wave, and nobody writes there during the kernel
 __device__ __forceinline__ int32_t uniform_load(const int32_t* p)
@@ -706,8 +707,9 @@ __device__ __forceinline__ int rest_tiles(int n) { return n & 0xffff; }
 __device__ __forceinline__ void put_stream_tiles(RowTile* tiles, int max_tiles, int before, int e, int at, int c)
 {
     RowTile* to = tiles + whole_tiles(before);
+    const int alone = c <= XM;
     for (; c > XM; c -= XR, at += XR) *to++ = RowTile{e, at, min(XR, c), 0};
-    if (c > 0) tiles[max_tiles - 1 - rest_tiles(before)] = RowTile{e, at, c, 0};
+    if (c > 0) tiles[max_tiles - 1 - rest_tiles(before)] = RowTile{e, at, c, alone};
 }
 
 // One workgroup of 16 waves: offsets = exclusive scan of counts; tile_start = exclusive scan of ceil(counts / TM).
@@ -1617,7 +1619,7 @@ constexpr int X_GRID = 256;
 template <bool RELU>
 __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
                                                            const RowTile* __restrict__ tiles, const int32_t* __restrict__ n_tiles, int max_tiles,
-                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv)
+                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv, int once)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane & 31, hk = lane >> 5;
@@ -1633,7 +1635,7 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
     const size_t w_unit = size_t(K) * 128;                     // bytes from one unit of features to the next
     const uint32_t piece = uint32_t(lane & 7) * 16u, w_off = uint32_t(w_row) * uint32_t(K) * 2u + piece;
 
-    struct Tile { int expert, row0, rows, nb; };
+    struct Tile { int expert, row0, rows, nb; bool once; };
     // this workgroup's tiles of one kind, of up to ROWS rows, BUFS chunks in LDS; find(s): the tile's place in `tiles` and its feature tile
     auto run = [&](auto rows_const, auto bufs_const, const int count, auto&& find) {
         constexpr int ROWS = decltype(rows_const)::value, BUFS = decltype(bufs_const)::value, AHEAD = BUFS - 1;
@@ -1646,21 +1648,23 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
             if (s0 + tid < count) {
                 const int2 at = find(s0 + tid);
                 const RowTile t = tiles[at.x];
-                *reinterpret_cast<u32x4*>(lds_raw + XLIST + tid * 16) = u32x4{uint32_t(t.expert), uint32_t(t.row0), uint32_t(t.rows), uint32_t(at.y * XF)};
+                *reinterpret_cast<u32x4*>(lds_raw + XLIST + tid * 16) = u32x4{uint32_t(t.expert), uint32_t(t.row0), uint32_t(t.rows), uint32_t(at.y * XF + (once & t.alone))};
             }
             answered_but<0>();
             meet();
         };
         auto tile_at = [&](int s) {
             const u32x4 v = *reinterpret_cast<const u32x4*>(lds_raw + XLIST + s % XLIST_LEN * 16);
-            return Tile{int(__builtin_amdgcn_readfirstlane(v.x)), int(__builtin_amdgcn_readfirstlane(v.y)), int(__builtin_amdgcn_readfirstlane(v.z)),
-                        int(__builtin_amdgcn_readfirstlane(v.w))};
+            const int nb = int(__builtin_amdgcn_readfirstlane(v.w));
+            return Tile{int(__builtin_amdgcn_readfirstlane(v.x)), int(__builtin_amdgcn_readfirstlane(v.y)), int(__builtin_amdgcn_readfirstlane(v.z)), nb & ~1,
+                        (nb & 1) != 0};
         };
         uint32_t x_off[RU];
         bool x_on[RU];                                         // this lane's row is there (lane 0: always, so that every wave makes every request, which it counts)
         const char* w_next = nullptr;                          // weights of the chunk that is requested next
         const char* x_next = nullptr;
         int w_units = 0;                                       // ... that exist (the last one is copied again)
+        bool w_once = false;
         uint32_t fill = 0, take = 0;                           // the chunk's place that is filled next, and the one that is read
         auto request_rows = [&](const Tile& t, int buf) {      // the places of a tile's rows
             if (gather && wave * 64 < t.rows)
@@ -1671,6 +1675,7 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
             w_next = reinterpret_cast<const char*>(W + (size_t(t.expert) * N + t.nb) * K);
             x_next = reinterpret_cast<const char*>(in);
             w_units = (N - t.nb) / 64;
+            w_once = t.once;
 #pragma unroll
             for (int i = 0; i < RU; ++i) {
                 const int r = min(i * 64 + x_row, t.rows - 1);
@@ -1685,7 +1690,8 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
         };
         auto request_piece = [&](int i) {
             const uint32_t at = fill + uint32_t(i * XUNIT + wave * XBLOCK);
-            if (i < 4) lds_copy16(w_next + (i < w_units ? i : 0) * w_unit, w_off, at);
+            if (i < 4 && ROWS == XM && w_once) lds_copy16<true>(w_next + (i < w_units ? i : 0) * w_unit, w_off, at);
+            else if (i < 4) lds_copy16(w_next + (i < w_units ? i : 0) * w_unit, w_off, at);
             else if (x_on[(i - 4) % RU]) lds_copy16(x_next, x_off[(i - 4) % RU], at);
         };
         auto requested = [&]() {
@@ -2131,11 +2137,15 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                 HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, X_LDS), "hipFuncSetAttribute(k_grouped_stream)");
             attr_set.fetch_or(uint64_t(1) << (dev & 63));
         }
+        // Where a layer's weights are more than the memory side's cache holds (256 MB), those of an expert with a single tile pass by the caches.  The whole pass, without / so, by
+        // weights of a layer: 245 MiB 309 / 309 us (less than the cache, and all experts' rests so: 53 MB 134 / 157, 76 MB 102 / 122); 304 241 / 214; 504 252 / 227; 569 188 / 180; 894 650 / 651;
+        // 4096 1877 / 1849 (with all rests so, those of experts with whole tiles too: 569 188 / 200, 322 217 / 227 instead of 204)
+        const int once = size_t(E) * d * h >= size_t(1) << 27;
         hipLaunchKernelGGL((k_grouped_stream<true>), dim3(X_GRID), dim3(512), X_LDS, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, tile_start,
-                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u);
+                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
         hipLaunchKernelGGL((k_grouped_stream<false>), dim3(X_GRID), dim3(512), X_LDS, st, hid, static_cast<const bf16_t*>(W2), y, tiles, tile_start,
-                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u);
+                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else if (naive_stride <= 0) {
         if (few1 || few2) {
