@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <initializer_list>
 #include <type_traits>
 #include <mutex>
 #include <string>
@@ -1990,6 +1991,12 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             hipLaunchKernelGGL((k_gate_big<false>), grid, dim3(256), GB_LDS_BYTES, st, xb, static_cast<const bf16_t*>(Wg),
                                static_cast<const bf16_t*>(Wn), noise, logits, T_big, d, E, ntt, net, per_die);
     }
+    // requests into LDS want whole pieces of 16 bytes; registers are loaded from any address, by the other kernels
+    auto on16 = [](std::initializer_list<const void*> pointers) {
+        for (const void* at : pointers)
+            if (reinterpret_cast<uintptr_t>(at) & 15) return false;
+        return true;
+    };
     // up to some five 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d =
     // 1024, noisy: 500 21 / 11, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; without noise: 1000 15.5 / 12.8, 2000 16.4 / 20; d = 64: 1764
     // 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
@@ -2007,7 +2014,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // beyond that the five of k_gate hide more.  The whole pass in us, k_gate / k_gate_stream, by tiles and d: noisy 256 x 512 153.6 / 150.5, 306 x 576 300.0 / 298.2,
     // 222 x 768 101.1 / 97.6, 80 x 320 54.1 / 52.1, 376 x 192 47.5 / 47.6, and on the other side 518 x 192 79.2 / 80.5, 845 x 256 81.1 / 82.6, 2370 x 768 312 / 321; without
     // noise 90 x 384 62.1 / 59.0, 240 x 832 91.1 / 85.1, 430 x 128 38.2 / 36.8, 2057 x 448 191.3 / 186.2)
-    else if (const long long tiles = (long long)((E + 63) / 64) * ((T - T_big + 63) / 64); T > T_big && d % 64 == 0 && d <= 1 << 20 && (!noise || tiles <= 512)) {
+    else if (const long long tiles = (long long)((E + 63) / 64) * ((T - T_big + 63) / 64); T > T_big && d % 64 == 0 && d <= 1 << 20 && (!noise || tiles <= 512) && on16({x, Wg, noise ? Wn : nullptr})) {
         static std::atomic<uint64_t> attr_set{0};             // one bit per device: LDS beyond 64 KB
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
@@ -2064,7 +2071,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // 312; 63, 1127: 444 / 450; 37, 395: 301 / 303; 32, 192: 153 / 159.  k_grouped_few, by uses, experts, d x h: 20216, 54, 1536 x 384: 126 / 122; 15200, 7, 1600 x 768:
     // 96 / 91; 10902, 54, 448 x 1280: 117 / 106; 17964, 22, 1792 x 1536 400 / 266; and on the other side 6435, 2, 512 x 3072 82 / 120; 7906, 16, 384 x 1792 66 / 81; 17965, 4, 448 x
     // 896 80 / 91; 13256, 119, 320 x 2112 97 / 109; 28110, 3, 256 x 1920 121 / 129 (of 70 shapes within the old line 19 were faster with k_grouped_few, all others 2 to 50 % slower)
-    const bool streamed = fused_permute && naive_stride <= 0 && !small && d % 64 == 0 && h % 64 == 0 && d >= 256 && h >= 256 && E <= SMALL_EXPERTS && A < 1 << 22 && k <= 1024 &&
+    const bool streamed = fused_permute && on16({x, W1, W2}) && naive_stride <= 0 && !small && d % 64 == 0 && h % 64 == 0 && d >= 256 && h >= 256 && E <= SMALL_EXPERTS && A < 1 << 22 && k <= 1024 &&
                         size_t(A) * size_t(std::max(d, h)) < size_t(1) << 31 && A >= 64 * E && size_t(A) * size_t(d + h) >= size_t(1) << 24 &&
                         (!mid || (std::min(d, h) >= 384 && double(A) * d * h >= double(1ll << 33)));
     // All other layers of whole K-chunks whose row tiles have a table (up to 65536 uses and 4096 experts): k_grouped_few, but for single chunks of few rows a tile
@@ -2076,7 +2083,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // rows, 4811 x 1394, 1, 64 x 3904 279 / 286; few tiles of long sums, 55 x 57, 2, 128 x 3776 42.0 / 43.9
     auto few_tiles = [&](int N) { return (long long)skinny_tiles * ((N + FEW_F - 1) / FEW_F); };
     auto few_layer = [&](int N, int K) {
-        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 &&
+        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && on16({x, W1, W2}) && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 &&
                (K >= 128 || A >= 16ll * skinny_tiles) && (few_tiles(N) >= 64 || K < 2560);
     };
     const bool few1 = few_layer(h, d), few2 = few_layer(d, h);

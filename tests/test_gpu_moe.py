@@ -256,6 +256,22 @@ def test_layers_of_whole_chunks_have_the_bits_of_the_general_kernel(dyn, util, d
     bits_of_both_ways(dyn, util, d, h, k, counts)
 
 
+@pytest.mark.parametrize("T,d,h,E,k", [(300, 64, 128, 9, 2), (2600, 512, 448, 6, 4), (5000, 576, 1024, 4, 4)])
+def test_inputs_between_16_byte_borders(dyn, util, T, d, h, E, k):
+    """Tensors that start 4 bytes behind a border of 16 take the kernels that load registers: the results of aligned copies, bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(T)
+    def rnd(*shape, std=1.0):
+        n = int(np.prod(shape))
+        return (torch.randn(n + 8, generator=g, device="cuda") * std).to(torch.bfloat16)[2:n + 2].view(shape)
+    args = [rnd(T, d), rnd(E, d), rnd(E, d, std=0.1), torch.randn(T, E, generator=g, device="cuda"), rnd(E, h, d, std=d ** -0.5), rnd(E, d, h, std=h ** -0.5)]
+    assert all(t.data_ptr() % 16 == 4 for t in args if t.dtype == torch.bfloat16)
+    want = util.to_host(dyn.moe_forward(*[t.clone() for t in args], k))
+    assert (util.to_host(dyn.moe_forward(*args, k)) == want).all()
+    for i in (0, 1, 2, 4, 5):
+        assert (util.to_host(dyn.moe_forward(*[t if j == i else t.clone() for j, t in enumerate(args)], k)) == want).all()
+
+
 def full_layer(dyn, util, m):
     """Runs a benchmark-size layer with per-expert generated weights; returns (out, aux, device inputs)."""
     import torch
