@@ -474,7 +474,7 @@ def main():
         moe_roof.append(roof("k_permute", by_perm, permute_ms, note="as a kernel of its own (MOE_SEPARATE_PERMUTE); by default the "
                              "first expert layer gathers the token rows itself and this kernel does not run"))
         moe_roof.append(roof("k_combine", by_comb, stage_ms["combine"]))
-        moe_roof.append(roof("k_grouped_gemm (both expert layers)", by_ffn, ffn_ms, mfma_tflops=round(fl_ffn / ffn_ms / 1e9, 1)))
+        moe_roof.append(roof("k_grouped_stream / k_grouped_few (both expert layers)", by_ffn, ffn_ms, mfma_tflops=round(fl_ffn / ffn_ms / 1e9, 1)))
         if "gate" in stage_ms and "topk" in stage_ms:
             fl_gate = 4.0 * m.T * m.d * m.E                       # both gate matrices
             moe_roof.append(dict(kernel="k_gate_big / k_gate (gate stage)", bound="mfma",
@@ -549,8 +549,8 @@ def main():
     for r_ in moe_roof:
         key = r_["kernel"].split(" ")[0]
         key = "k_gate" if key.startswith("k_gate") else "k_topk" if key.startswith("k_topk") else key
-        if key == "k_grouped_gemm":
-            parts = [v for k_, v in moe_traffic.items() if k_.startswith("k_grouped_gemm")]
+        if key.startswith("k_grouped"):
+            parts = [v for k_, v in moe_traffic.items() if k_.startswith("k_grouped")]
             if parts:
                 r_["traffic"] = sum(parts)
         elif key in moe_traffic:
