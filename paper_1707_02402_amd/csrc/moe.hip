@@ -2083,7 +2083,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     // rows, 4811 x 1394, 1, 64 x 3904 279 / 286; few tiles of long sums, 55 x 57, 2, 128 x 3776 42.0 / 43.9
     auto few_tiles = [&](int N) { return (long long)skinny_tiles * ((N + FEW_F - 1) / FEW_F); };
     auto few_layer = [&](int N, int K) {
-        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && on16({x, W1, W2}) && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 &&
+        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && on16({x, W1, W2}) && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 && K <= 1 << 20 &&
                (K >= 128 || A >= 16ll * skinny_tiles) && (few_tiles(N) >= 64 || K < 2560);
     };
     const bool few1 = few_layer(h, d), few2 = few_layer(d, h);
