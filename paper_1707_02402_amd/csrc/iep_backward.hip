@@ -40,50 +40,16 @@ using dynb::fail;
 
 namespace {
 
-// A float is the sum of three bfloat16 (24 bits of mantissa, 8 each, rounded to nearest even: the third is exact), and a product of two floats that of six of
-// their parts' products, up to 2^-26 of it; a bfloat16 is one part, and its product with a float that of three.  v_mfma_f32_32x32x16_bf16 takes 32 clocks for 16
-// summands where v_mfma_f32_32x32x2_f32 takes 512: 192 for six products, 96 for three.  Against 64 bits sums of 1152 such products err by 2.5e-7 of their norm
-// (random signs; fp32 products 2.8e-7) and 0.99e-7 (positive ones; 1.16e-7): fewer roundings, of the same sums.
-// What is not finite, and what rounds to infinity (beyond 3.39e38), has parts that are NaN; such sums are taken again (k_wgrad's last lines).
-// Four channels: parts[0] the largest
-__device__ __forceinline__ void split4(const f32x4& v, u32x2 (&parts)[3])
-{
-    float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        parts[p] = u32x2{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
-        if (p < 2) {
-            f[0] -= __uint_as_float(parts[p].x << 16);
-            f[1] -= __uint_as_float(parts[p].x & 0xffff0000u);
-            f[2] -= __uint_as_float(parts[p].y << 16);
-            f[3] -= __uint_as_float(parts[p].y & 0xffff0000u);
-        }
-    }
-}
-// four pixels (at this lane's pixel address and its three neighbours') of one channel per lane
-__device__ __forceinline__ i16x4 lds_read_pixels(uint32_t addr)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    using lds_i16x4 = __attribute__((address_space(3))) i16x4;
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>((__attribute__((address_space(3))) unsigned char*)lds_raw + addr));
-}
-__device__ __forceinline__ bf16x8 eight_pixels(i16x4 lo, i16x4 hi) { return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)); }
-
 // Parameter gradients of every function, any shape: a workgroup owns a 32 x 32 block (output x input channels) of one
 // function's weight gradient, all taps of it, and sums it over the function's items and their pixels,
-//     D[32 co][32 ci] += G[32 co][16 pixels] * IN[16 pixels][32 ci]     in parts of bfloat16 (above)
+//     D[32 co][32 ci] += G[32 co][2 pixels] * IN[2 pixels][32 ci]     (v_mfma_f32_32x32x2: fp32 products and sums)
 // Second 3x3: G = g, IN = mid; first 3x3: G = dmid, IN = u; JOIN: the 1x1 (G = dc, IN = the arguments).  The functions with the most items come
-// first, of both 3x3s: the last ones should be short (fp32, C = 128, 14 x 14, with fp32 products: a training step of 21 programs 2685 us with the functions in
-// order, 2633 so; of 8 programs 1435 / 1387).
-// An item's 32 + 32 channels are staged into LDS as planes of parts, 64 bytes a pixel, both maps in the same geometry, the input's with its halo: row after row,
-// G's zero where it has no pixel.  A step is 16 pixels in a row, across the ends of rows: pixel p of G goes with pixel p + kh * columns + kw of the input.  The maps
-// lie pixel by pixel and the sums run over pixels: fragments are read by the transposing LDS load, one read of a plane for every tap.  The
-// waves split an item's steps and meet in LDS at the end, in wave order.  Maps that do not fit are taken in bands of rows and segments of columns.
-// Of maps of up to 16 pixels several items are staged at a time (MANY), as fp32, and multiplied with v_mfma_f32_32x32x2: a step is two pixels of a row, where 16 in a
-// row would be mostly halo (1 x 1: 9 pixels an item).
-// What bounds it: an item's way into LDS (a trip to memory and some 500 vector instructions a thread for a band) beside the other workgroup's products.  A training
-// step of 21 programs, fp32, C = 128, 14 x 14: 456 us (fp32 products in 512 clocks for 16 pixels, a trip for every 32 pixels) -> 365; with two trips a band and
-// map 362 with all products in one sum, which one trip made 320.
+// first, of both 3x3s: a workgroup takes some 14 us an item beside another on its CU, and the last
+// ones should be short (fp32, C = 128, 14 x 14: a training step of 21 programs 2685 us with the functions in order, 2633 so; of 8 programs 1435 / 1387).
+// An item's 32 + 32 channels are staged into LDS as fp32, pixel-major without padding (a fragment, two pixels x 32
+// channels, is then 64 consecutive words), the input with its halo; a step of two pixels reads 1 + TAPS fragments
+// for TAPS MFMAs of 64 clocks.  The waves split an item's pixels and meet in LDS at the end, in wave order.  Maps that do
+// not fit are taken in bands of rows and segments of columns; of maps of a few pixels several items are staged at a time.
 // (Per launch group, one thread per gradient element, the sums took most of a training step's 179 ms at 21 programs,
 // C = 128, 14 x 14.)
 struct WgradArgs {
@@ -109,15 +75,10 @@ struct WgradArgs {
     int32_t many;                 // MANY: items staged at a time (sw = W, band = H)
 };
 
-constexpr int WGRAD_PAD = 32;                                                   // pixels behind a map that the last step may touch: zeros
-constexpr int WGRAD_PIXELS = 160;                                               // most staged pixels of a band
-
 template <typename T, bool JOIN, bool MANY>
 __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 {
-    constexpr int TAPS = JOIN ? 1 : 9, HALO = JOIN ? 0 : 1, PIX = 32 * 2;       // bytes of a staged pixel in a plane
-    constexpr int PIN = sizeof(T) == 4 ? 3 : 1;                                 // planes of the input (G: three)
-    constexpr int FPIX = 32 * 4;                                                // MANY: bytes of a staged pixel
+    constexpr int TAPS = JOIN ? 1 : 9, HALO = JOIN ? 0 : 1, PIX = 32 * 4;       // bytes of a staged pixel
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int C = a.C, H = a.H, W = a.W, sw = a.sw;
     const int cb = (C + 31) / 32, n_in = JOIN ? 2 * cb : cb;                     // input blocks; of the join: per argument
@@ -129,9 +90,10 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
     const size_t chw = size_t(H) * W * C;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 31, hk = lane >> 5;
 
-    // MANY: staged pixels of G: band rows x wp columns (even: a step never crosses a row), of the input: with halo
-    const int wp = (sw + 1) & ~1, half = wp / 2, icols = (MANY ? wp : sw) + 2 * HALO, NI = MANY ? a.many : 1;
-    const uint32_t plane = uint32_t(((a.band + 2 * HALO) * icols + WGRAD_PAD) * PIX), in_off = MANY ? uint32_t(NI * a.band * wp * FPIX) : 3 * plane;
+    // staged pixels of G: band rows x wp columns (even: a step never crosses a row), of the input: with halo
+    const int wp = (sw + 1) & ~1, half = wp / 2, icols = wp + 2 * HALO;
+    const int NI = MANY ? a.many : 1;
+    const uint32_t in_off = uint32_t(NI * a.band * wp * PIX);
     const uint32_t m_wp = recip_of(wp), m_icols = recip_of(icols);
 
     f32x16 acc[TAPS];
@@ -139,7 +101,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
     for (int k = 0; k < TAPS; ++k)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[k][i] = 0.f;
-    float bias[4] = {0.f, 0.f, 0.f, 0.f};                                        // sums of the G values that this thread stages, channels 4 (tid % 8) ..  (MANY: of this lane's)
+    float bias = 0.f;                                                            // sum of this lane's G values
 
     const int lo = JOIN && ar != 2 ? 0 : a.fn_first[type], hi = JOIN && ar != 2 ? 0 : a.fn_first[type + 1];
     struct Maps { const float* G; const T* Y; const T* IN; };                    // Y: the item's result, whose ReLU masks G (which 0)
@@ -163,163 +125,82 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
             for (int y0 = 0; y0 < H; y0 += a.band) {
                 const int rows = min(a.band, H - y0), cols = min(sw, W - x0), irows = rows + 2 * HALO;
                 __syncthreads();                                                 // the last band's fragments have been read
-                if constexpr (!MANY) {
-                    // both maps in one trip to memory: up to WGRAD_PIXELS staged pixels, a piece of four channels of a pixel a time
-                    constexpr int UN = WGRAD_PIXELS * 8 / 256;
-                    const int np = irows * icols * 8;
-                    auto stage = [&](auto full) {                    // full: all 32 + 32 channels are there
-                        constexpr bool FULL = decltype(full)::value;
-                        f32x4 vg[UN], vi[UN];
-                        const int cg = co0 + (tid & 7) * 4, ci = ci0 + (tid & 7) * 4;
+                constexpr int UN = 4;
+                const int ng = n * rows * wp * 8, ni = n * irows * icols * 8;            // 16-byte pieces
+                for (int base = tid; base < ng; base += 256 * UN) {
+                    f32x4 v[UN];
 #pragma unroll
-                        for (int k = 0; k < UN; ++k) {
-                            const uint32_t pix = uint32_t(tid + k * 256) >> 3, row = icols > 1 ? div_by(pix, m_icols) : pix, col = pix - row * icols;
-                            vg[k] = vi[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-                            const int y = y0 + int(row) - HALO, x = x0 + int(col) - HALO;
-                            if (int(row) < irows && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) vi[k] = load4<FULL>(one.IN + (size_t(y) * W + x) * C + ci, C - ci);
-                            if (int(row) < rows && int(col) < cols) {
-                                const size_t e = (size_t(y0 + row) * W + x0 + col) * C + cg;
-                                vg[k] = !JOIN && which == 0 ? masked_gy<FULL>(one.G + e, one.Y + e, C - cg) : load4<FULL>(one.G + e, C - cg);
-                            }
+                    for (int k = 0; k < UN; ++k) {
+                        const int c = base + k * 256;
+                        const uint32_t pix = uint32_t(c) >> 3, line = div_by(pix, m_wp), col = pix - line * wp;
+                        const int it = MANY ? int(line) / rows : 0, row = int(line) - it * rows;
+                        const int ch = co0 + (c & 7) * 4;
+                        v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (c < ng && int(col) < cols) {
+                            const Maps m = MANY ? maps(idx + it) : one;
+                            const size_t e = (size_t(y0 + row) * W + x0 + col) * C + ch;
+                            v[k] = !JOIN && which == 0 ? masked_gy<false>(m.G + e, m.Y + e, C - ch) : load4<false>(m.G + e, C - ch);
                         }
+                    }
 #pragma unroll
-                        for (int k = 0; k < UN; ++k) {
-                            if (tid + k * 256 >= np) continue;
-                            unsigned char* const to = lds_raw + uint32_t(tid + k * 256) * 8;
-                            u32x2 parts[3];
-                            split4(vg[k], parts);
+                    for (int k = 0; k < UN; ++k)
+                        if (base + k * 256 < ng) *reinterpret_cast<f32x4*>(lds_raw + size_t(base + k * 256) * 16) = v[k];
+                }
+                for (int base = tid; base < ni; base += 256 * UN) {
+                    f32x4 v[UN];
 #pragma unroll
-                            for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(to + p * plane) = parts[p];
-                            bias[0] += vg[k].x; bias[1] += vg[k].y; bias[2] += vg[k].z; bias[3] += vg[k].w;
-                            if constexpr (PIN == 1) *reinterpret_cast<u32x2*>(to + in_off) = u32x2{pack_bf16x2(vi[k].x, vi[k].y), pack_bf16x2(vi[k].z, vi[k].w)};   // (exact)
-                            else {
-                                split4(vi[k], parts);
-#pragma unroll
-                                for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(to + in_off + p * plane) = parts[p];
-                            }
+                    for (int k = 0; k < UN; ++k) {
+                        const int c = base + k * 256;
+                        const uint32_t pix = uint32_t(c) >> 3, line = div_by(pix, m_icols), col = pix - line * icols;
+                        const int it = MANY ? int(line) / irows : 0, row = int(line) - it * irows;
+                        const int ch = ci0 + (c & 7) * 4, y = y0 + row - HALO, x = x0 + int(col) - HALO;
+                        v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) {
+                            const Maps m = MANY ? maps(idx + it) : one;
+                            v[k] = load4<false>(m.IN + (size_t(y) * W + x) * C + ch, C - ch);
                         }
+                    }
+#pragma unroll
+                    for (int k = 0; k < UN; ++k)
+                        if (base + k * 256 < ni) *reinterpret_cast<f32x4*>(lds_raw + in_off + size_t(base + k * 256) * 16) = v[k];
+                }
+                __syncthreads();
+                // this wave's steps: (row y, pixels 2 x and 2 x + 1), read one step ahead; the rows of the staged items follow each
+                // other, iy is the row of the input that goes with y
+                const int S = n * rows * half, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
+                struct Step { float g, in[TAPS]; };
+                auto read = [&](int y, int iy, int x, Step& v) {
+                    const uint32_t ga = uint32_t(((y * half + x) * 2 + hk) * PIX + r * 4);
+                    const uint32_t ia = in_off + uint32_t((iy * icols + x * 2 + hk) * PIX + r * 4);
+                    v.g = *reinterpret_cast<const float*>(lds_raw + ga);
+#pragma unroll
+                    for (int k = 0; k < TAPS; ++k)
+                        v.in[k] = *reinterpret_cast<const float*>(lds_raw + ia + uint32_t(((k / 3) * icols + k % 3) * PIX));
+                };
+                auto multiply = [&](const Step& v) {
+                    bias += v.g;
+#pragma unroll
+                    for (int k = 0; k < TAPS; ++k) acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.g, v.in[k], acc[k], 0, 0, 0);
+                };
+                if (s0 < s1) {
+                    int y = s0 / half, x = s0 - y * half, left = 0, iy = y;
+                    if constexpr (MANY) { const int it = y / rows; left = (it + 1) * rows - y; iy += it * 2 * HALO; }     // rows left of this item
+                    auto advance = [&]() {
+                        if (++x < half) return;
+                        x = 0; ++y; ++iy;
+                        if (MANY && --left == 0) { left = rows; iy += 2 * HALO; }
                     };
-                    if (C - co0 >= 32 && C - ci0 >= 32) stage(std::true_type{});
-                    else stage(std::false_type{});
-                    // zeros behind the maps
-                    for (int c = tid; c < (3 + PIN) * WGRAD_PAD * 4; c += 256)
-                        *reinterpret_cast<u32x4*>(lds_raw + uint32_t(c / (WGRAD_PAD * 4)) * plane + uint32_t(np * 8 + c % (WGRAD_PAD * 4) * 16)) = u32x4{0u, 0u, 0u, 0u};
-                    __syncthreads();
-                    // this wave's steps.  A lane reads pixels 8 hk .. + 7 of a step: four and four, of one channel (16 lanes read 4 pixels x 16 channels)
-                    const int S = (rows * icols + 15) / 16, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
-                    const uint32_t lane_at = uint32_t((hk * 8 + (lane >> 2 & 3)) * PIX + (lane >> 4 & 1) * 32 + (lane & 3) * 8);
-                    auto read = [&](uint32_t at) { return eight_pixels(lds_read_pixels(at), lds_read_pixels(at + 4 * PIX)); };
-                    auto mul = [](const bf16x8& g, const bf16x8& in, f32x16& to) { to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, in, to, 0, 0, 0); };
-                    // The small products have a sum of their own from step to step, so that the large one is rounded twice for 16 pixels and not six times.  (All in one sum:
-                    // 320 us instead of 365, but errors 1 to 5 % larger than those of fp32 products in sums of random signs.  Added a tap later, or for two steps
-                    // together: the registers do not suffice, 520 us and more.)
+                    Step p, q;
+                    read(y, iy, x, p);
 #pragma unroll 1
-                    for (int st = s0; st < s1; ++st) {
-                        const uint32_t at = uint32_t(st * 16 * PIX) + lane_at;
-                        bf16x8 g[3], in[2][PIN];
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) g[p] = read(at + p * plane);
-                        auto read_in = [&](int k) {
-#pragma unroll
-                            for (int p = 0; p < PIN; ++p) in[k & 1][p] = read(in_off + at + p * plane + uint32_t(((k / 3) * icols + k % 3) * PIX));
-                        };
-                        read_in(0);
-#pragma unroll
-                        for (int k = 0; k < TAPS; ++k) {
-                            if (k + 1 < TAPS) read_in(k + 1);
-                            __builtin_amdgcn_sched_barrier(0);
-                            const bf16x8 (&x)[PIN] = in[k & 1];
-                            f32x16 small;
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) small[i] = 0.f;
-                            mul(g[2], x[0], small);
-                            if constexpr (PIN == 3) { mul(g[0], x[2], small); mul(g[1], x[1], small); }
-                            mul(g[1], x[0], small);
-                            if constexpr (PIN == 3) mul(g[0], x[1], small);
-                            mul(g[0], x[0], acc[k]);
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) acc[k][i] += small[i];
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
-                } else {
-                    constexpr int UN = 4;
-                    const int ng = n * rows * wp * 8, ni = n * irows * icols * 8;            // 16-byte pieces
-                    for (int base = tid; base < ng; base += 256 * UN) {
-                        f32x4 v[UN];
-    #pragma unroll
-                        for (int k = 0; k < UN; ++k) {
-                            const int c = base + k * 256;
-                            const uint32_t pix = uint32_t(c) >> 3, line = div_by(pix, m_wp), col = pix - line * wp;
-                            const int it = int(line) / rows, row = int(line) - it * rows;
-                            const int ch = co0 + (c & 7) * 4;
-                            v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-                            if (c < ng && int(col) < cols) {
-                                const Maps m = maps(idx + it);
-                                const size_t e = (size_t(y0 + row) * W + x0 + col) * C + ch;
-                                v[k] = !JOIN && which == 0 ? masked_gy<false>(m.G + e, m.Y + e, C - ch) : load4<false>(m.G + e, C - ch);
-                            }
-                        }
-    #pragma unroll
-                        for (int k = 0; k < UN; ++k)
-                            if (base + k * 256 < ng) *reinterpret_cast<f32x4*>(lds_raw + size_t(base + k * 256) * 16) = v[k];
-                    }
-                    for (int base = tid; base < ni; base += 256 * UN) {
-                        f32x4 v[UN];
-    #pragma unroll
-                        for (int k = 0; k < UN; ++k) {
-                            const int c = base + k * 256;
-                            const uint32_t pix = uint32_t(c) >> 3, line = div_by(pix, m_icols), col = pix - line * icols;
-                            const int it = int(line) / irows, row = int(line) - it * irows;
-                            const int ch = ci0 + (c & 7) * 4, y = y0 + row - HALO, x = x0 + int(col) - HALO;
-                            v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-                            if (c < ni && unsigned(y) < unsigned(H) && unsigned(x) < unsigned(W)) {
-                                const Maps m = maps(idx + it);
-                                v[k] = load4<false>(m.IN + (size_t(y) * W + x) * C + ch, C - ch);
-                            }
-                        }
-    #pragma unroll
-                        for (int k = 0; k < UN; ++k)
-                            if (base + k * 256 < ni) *reinterpret_cast<f32x4*>(lds_raw + in_off + size_t(base + k * 256) * 16) = v[k];
-                    }
-                    __syncthreads();
-                    // this wave's steps: (row y, pixels 2 x and 2 x + 1), read one step ahead; the rows of the staged items follow each
-                    // other, iy is the row of the input that goes with y
-                    const int S = n * rows * half, s0 = S * wave / 4, s1 = S * (wave + 1) / 4;
-                    struct Step { float g, in[TAPS]; };
-                    auto read = [&](int y, int iy, int x, Step& v) {
-                        const uint32_t ga = uint32_t(((y * half + x) * 2 + hk) * FPIX + r * 4);
-                        const uint32_t ia = in_off + uint32_t((iy * icols + x * 2 + hk) * FPIX + r * 4);
-                        v.g = *reinterpret_cast<const float*>(lds_raw + ga);
-    #pragma unroll
-                        for (int k = 0; k < TAPS; ++k)
-                            v.in[k] = *reinterpret_cast<const float*>(lds_raw + ia + uint32_t(((k / 3) * icols + k % 3) * FPIX));
-                    };
-                    auto multiply = [&](const Step& v) {
-                        bias[0] += v.g;
-    #pragma unroll
-                        for (int k = 0; k < TAPS; ++k) acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.g, v.in[k], acc[k], 0, 0, 0);
-                    };
-                    if (s0 < s1) {
-                        int y = s0 / half, x = s0 - y * half;
-                        int left = (y / rows + 1) * rows - y, iy = y + y / rows * 2 * HALO;                // rows left of this item
-                        auto advance = [&]() {
-                            if (++x < half) return;
-                            x = 0; ++y; ++iy;
-                            if (--left == 0) { left = rows; iy += 2 * HALO; }
-                        };
-                        Step p, q;
-                        read(y, iy, x, p);
-    #pragma unroll 1
-                        for (int st = s0; st < s1; st += 2) {
-                            advance();
-                            if (st + 1 < s1) read(y, iy, x, q);
-                            multiply(p);
-                            if (st + 1 >= s1) break;
-                            advance();
-                            if (st + 2 < s1) read(y, iy, x, p);
-                            multiply(q);
-                        }
+                    for (int st = s0; st < s1; st += 2) {
+                        advance();
+                        if (st + 1 < s1) read(y, iy, x, q);
+                        multiply(p);
+                        if (st + 1 >= s1) break;
+                        advance();
+                        if (st + 2 < s1) read(y, iy, x, p);
+                        multiply(q);
                     }
                 }
             }
@@ -373,23 +254,14 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
                 }
         }
     }
-    if (ci0 == 0 && arg == 0) {                                                  // bias: the threads' in order
+    if (ci0 == 0 && arg == 0) {                                                  // bias: the lane halves and the waves in order
         __syncthreads();
         float* sum = reinterpret_cast<float*>(lds_raw);
-        if constexpr (MANY) sum[tid] = bias[0];                                  // [lane half][channel] of every wave
-        else
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sum[tid * 4 + e] = bias[e];              // [thread / 8][channel]
+        sum[tid] = bias;
         __syncthreads();
         if (tid < 32 && co0 + tid < C) {
             float v = 0.f;
-            if constexpr (MANY) {
-                for (int w = 0; w < 8; ++w) v += sum[w * 32 + tid];
-            } else                                                               // (pairs of pairs: thirty-two one after the other are rounded more)
-                for (int w = 0; w < 32; w += 8) {
-                    const float* const q = sum + w * 32 + tid;
-                    v += ((q[0] + q[32]) + (q[64] + q[96])) + ((q[128] + q[160]) + (q[192] + q[224]));
-                }
+            for (int w = 0; w < 8; ++w) v += sum[w * 32 + tid];
             a.db[which][size_t(type) * C + co0 + tid] = v;
         }
     }
@@ -846,6 +718,14 @@ struct WgArgs {
 constexpr size_t WG_PARTIAL = size_t(3) * 128 * 128 + 128;           // floats per unit
 constexpr int WG_ROW = 16 * 128, WG_MAP = mf::S * WG_ROW;            // LDS: bytes of an image row (columns 14, 15 are zeros), of a half map
 
+// four pixels (at this lane's pixel address and its three neighbours') of one channel per lane
+__device__ __forceinline__ i16x4 lds_read_pixels(uint32_t addr)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    using lds_i16x4 = __attribute__((address_space(3))) i16x4;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>((__attribute__((address_space(3))) unsigned char*)lds_raw + addr));
+}
+
 // chunks: the function's; a single one is the whole sum and goes where the gradients go.  CONV: un is the first of the chunk's three units (kernel
 // row 0), the others follow `chunks` units apart
 template <bool CONV>
@@ -1108,24 +988,14 @@ int launch_wgrad(WgradArgs a, int n_types, hipStream_t st)
     constexpr int HALO = JOIN ? 0 : 1;
     const int n_seg = (a.W + 31) / 32;
     a.sw = (a.W + n_seg - 1) / n_seg;
+    const int wp = (a.sw + 1) & ~1, icols = wp + 2 * HALO;
+    a.band = std::min(a.H, (WGRAD_LDS_MAX / 128 - 2 * HALO * icols) / (wp + icols));      // >= 8: sw <= 32
     // Maps of up to 16 pixels: several items at a time, some 64 pixels, where one item would be a trip to memory (3 us) for a few
     // MFMAs.  10000 programs of 2 modules, fp32, 1 x 1, a training step: C = 1 31 -> 4.0 ms, C = 16 30 -> 4.2.
-    const int wp = (a.W + 1) & ~1;
     const long long pixels = (long long)a.H * wp;
-    if (pixels <= 16) {
-        a.band = a.H;
-        a.many = int(64 / pixels);
-        const size_t lds = std::max<size_t>(size_t(a.many) * (a.band * wp + (a.band + 2 * HALO) * (wp + 2 * HALO)) * 128, size_t(JOIN ? 1 : 3) * 16 * 1024);
-        return launch_wgrad_items<T, JOIN, true>(a, n_types, lds, st);
-    }
-    const int icols = a.sw + 2 * HALO, planes = sizeof(T) == 4 ? 6 : 4;
-    // rows that fit, in bands of nearly equal height (two and more: sw <= 32)
-    static_assert((WGRAD_PIXELS + WGRAD_PAD) * 6 * 64 <= WGRAD_LDS_MAX, "two workgroups per CU");
-    const int fit = WGRAD_PIXELS / icols - 2 * HALO, bands = (a.H + fit - 1) / fit;
-    a.band = (a.H + bands - 1) / bands;
-    a.many = 1;
-    const size_t lds = std::max<size_t>(size_t(planes) * 64 * ((a.band + 2 * HALO) * icols + WGRAD_PAD), size_t(JOIN ? 1 : 3) * 16 * 1024);
-    return launch_wgrad_items<T, JOIN, false>(a, n_types, lds, st);
+    a.many = pixels <= 16 ? int(64 / pixels) : 1;
+    const size_t lds = std::max<size_t>(size_t(a.many) * (a.band * wp + (a.band + 2 * HALO) * icols) * 128, size_t(JOIN ? 1 : 3) * 16 * 1024);
+    return a.many > 1 ? launch_wgrad_items<T, JOIN, true>(a, n_types, lds, st) : launch_wgrad_items<T, JOIN, false>(a, n_types, lds, st);
 }
 
 template <typename T>

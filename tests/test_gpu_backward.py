@@ -96,7 +96,7 @@ def test_ragged_shapes_fp32_with_single_scene_programs(dyn, util, oracle, C, H, 
 
 
 @pytest.mark.parametrize("dtype,C,H,W", [("f32", 32, 14, 14), ("f32", 33, 9, 13), ("f32", 64, 17, 1), ("f32", 36, 2, 33), ("f32", 40, 5, 31), ("bf16", 64, 10, 14), ("bf16", 34, 21, 7)])
-def test_parameter_gradients_in_parts_are_as_close_as_fp32_products(dyn, util, oracle, dtype, C, H, W):
+def test_parameter_gradients_with_every_unit_active(dyn, util, oracle, dtype, C, H, W):
     """Maps of one band and more, whole and cut blocks of 32 channels, one column, two segments.  Every unit active, so that no ReLU decision hangs on a rounding:
     what is left are the sums.  One of n products that is rounded twice for every 16 of them is off by 2^-24 sqrt(n / 8) of itself at most in the mean: 2.5e-6 for
     the longest here, gradients and activations that carry such errors into it included.  Of activations that are stored in bfloat16 a share of 3e-7 / 2^-8 = 8e-5
@@ -111,6 +111,105 @@ def test_parameter_gradients_in_parts_are_as_close_as_fp32_products(dyn, util, o
     got, _ = run_backward(dyn, util, w, dout)
     for name in NAMES:
         assert frob(got[name], getattr(ref, name)) < (2.5e-6 if dtype == "f32" else 1e-4), (name, frob(got[name], getattr(ref, name)))
+
+
+def gradients_of_one_module(dyn, feats, dout, dtype, binary):
+    """One module whose convolutions pass their input on: mid = u = feats, dmid = g = dout, dc = 2 dout, all of them exactly."""
+    import torch
+    H, W, C = feats.shape
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    prog, arity = (np.array([1, 0, 0], np.int32), [0, 2]) if binary else (np.array([1, 0], np.int32), [0, 1])
+    eye, centre = torch.eye(C, device="cuda"), torch.zeros(2, C, 3, 3, C, device="cuda")
+    centre[:, :, 1, 1] = eye
+    w1 = torch.zeros(2, C, 2 * C, device="cuda")
+    w1[:, :, :C] = eye
+    zero = torch.zeros(2, C, device="cuda")
+    weights = dict(w1=w1.to(dt), b1=zero, w3a=centre.to(dt), b3a=zero, w3b=centre.to(dt), b3b=zero)
+    plan = dyn.dynbatch_plan(prog, np.array([0, len(prog)], np.int32), np.array(arity, np.uint8), dyn.DYNB_PLAN_KEEP)
+    dyn.dynbatch_plan_upload(plan)
+    ws = torch.empty(dyn.dynbatch_workspace_bytes(plan, C, H, W, dyn.DYNB_F32 if dtype == "f32" else dyn.DYNB_BF16), dtype=torch.uint8, device="cuda")
+    x = torch.from_numpy(feats[None]).cuda().to(dt)
+    out = dyn.dynbatch_execute(plan, weights, x, workspace=ws)
+    g = dyn.dynbatch_backward(plan, weights, x, out, ws, torch.from_numpy(dout[None]).cuda())
+    return {k: v.cpu().numpy()[1].astype(np.float64) for k, v in g.items() if k != "dfeats"}
+
+
+def mantissas(rng, *shape):
+    """Floats of 24 random bits in [1, 2); the first channel is 1 + 2^-8 - 2^-17, whose product with itself is farthest from that of its first bits."""
+    v = (rng.integers(1 << 23, 1 << 24, shape) / (1 << 23)).astype(np.float32)
+    v[..., 0] = 1 + 2.0 ** -8 - 2.0 ** -17
+    return v
+
+
+@pytest.mark.parametrize("dtype,C,H,W,scale_g,scale_in", [("f32", 32, 7, 7, 1, 1), ("f32", 40, 5, 9, 1, 1), ("f32", 32, 20, 33, 1, 1), ("bf16", 34, 7, 7, 1, 1), ("bf16", 32, 3, 40, 1, 1),
+                                                          ("f32", 32, 7, 7, 2.0 ** -63, 2.0 ** -31), ("f32", 33, 7, 7, 2.0 ** -118, 1), ("f32", 32, 7, 7, 1, 2.0 ** -110),
+                                                          ("f32", 32, 20, 33, 2.0 ** 39, 2.0 ** 38), ("f32", 32, 7, 7, 2.0 ** 70, 2.0 ** 50), ("bf16", 32, 7, 7, 2.0 ** -118, 1),
+                                                          ("f32", 32, 33, 1, 2.0 ** -118, 1), ("f32", 32, 160, 1, 2.0 ** -118, 1)])
+def test_parameter_gradients_of_one_product(dyn, dtype, C, H, W, scale_g, scale_in):
+    """One pixel has a gradient: every element is a single product, which fp32 rounds once, by 2^-24 of it.  Gradients and inputs of ordinary size, small ones (as
+    long as the product is a normal number) and large ones."""
+    rng = np.random.default_rng(C + H)
+    feats, at = mantissas(rng, H, W, C) * np.float32(scale_in), (H * 2 // 3, W * 2 // 3)
+    if dtype == "bf16":
+        feats = round_bf16(feats)
+    dout = np.zeros((H, W, C), np.float32)
+    dout[at] = mantissas(rng, C) * np.float32(scale_g) * rng.choice([-1, 1], C)
+    padded = np.zeros((H + 2, W + 2, C))
+    padded[1:-1, 1:-1] = feats
+    g = dout[at].astype(np.float64)
+    conv = g[:, None, None, None] * padded[at[0]:at[0] + 3, at[1]:at[1] + 3][None]
+    join = 2 * g[:, None] * np.concatenate([feats[at], feats[at]]).astype(np.float64)[None]
+    for binary in (False, True):
+        got = gradients_of_one_module(dyn, feats, dout, dtype, binary)
+        for name, want in (("dw3b", conv), ("dw3a", conv), ("dw1", join))[:2 + binary]:
+            assert (np.abs(got[name] - want) <= 2.0 ** -24 * np.abs(want)).all(), (name, binary, (np.abs(got[name] - want) / np.maximum(np.abs(want), 1e-300)).max())
+
+
+def as_fp32_products(g, x):
+    """sum over pixels of g[p, co] x[p, ci] as v_mfma_f32_32x32x2 takes it: product after product, each sum rounded, in four quarters"""
+    total = np.zeros((g.shape[1], x.shape[1]), np.float32)
+    for part in np.array_split(np.arange(len(g)), 4):
+        acc = np.zeros_like(total)
+        for p in part:
+            acc = (acc.astype(np.float64) + g[p].astype(np.float64)[:, None] * x[p].astype(np.float64)[None]).astype(np.float32)
+        total = total + acc
+    return total
+
+
+@pytest.mark.parametrize("signs", [True, False])
+@pytest.mark.parametrize("dtype,C,H,W", [("f32", 32, 14, 14), ("f32", 48, 9, 13), ("f32", 32, 20, 40), ("bf16", 32, 14, 14)])
+def test_parameter_gradients_are_as_close_as_fp32_products(dyn, dtype, C, H, W, signs):
+    """Against 64 bits, on inputs that are known exactly: the error's norm is that of fp32 products and sums, which differ by their order: by five
+    standard deviations of the quotient of two norms of 9 C C and C C independent errors, 5 / sqrt(N) with N >= 9216 and 1024."""
+    rng = np.random.default_rng(C + W)
+    feats = np.abs(rng.standard_normal((H, W, C))).astype(np.float32) + np.float32(2.0 ** -20)
+    if dtype == "bf16":
+        feats = round_bf16(feats)
+    dout = rng.standard_normal((H, W, C)).astype(np.float32)
+    if not signs:
+        dout = np.abs(dout)
+    padded = np.zeros((H + 2, W + 2, C), np.float32)
+    padded[1:-1, 1:-1] = feats
+    got = gradients_of_one_module(dyn, feats, dout, dtype, True)
+    g = dout.reshape(-1, C)
+    taps = [padded[t // 3:t // 3 + H, t % 3:t % 3 + W].reshape(-1, C) for t in range(9)]
+    want = np.stack([g.astype(np.float64).T @ x for x in taps], 1).reshape(C, 3, 3, C)
+    fp32 = np.stack([as_fp32_products(g, x) for x in taps], 1).reshape(C, 3, 3, C)
+    for name in ("dw3b", "dw3a"):
+        assert frob(got[name], want) <= 1.05 * frob(fp32, want), (name, frob(got[name], want), frob(fp32, want))
+    want, fp32 = 2 * want[:, 1, 1], 2 * fp32[:, 1, 1]
+    assert frob(got["dw1"][:, :C], want) <= 1.16 * frob(fp32, want), (frob(got["dw1"][:, :C], want), frob(fp32, want))
+
+
+def test_products_next_to_the_largest_float(dyn):
+    """3.384e38 x 1.005 is finite; the product of the two rounded up to 8 bits is not."""
+    C, H, W = 32, 7, 7
+    feats, dout = np.full((H, W, C), 1.005, np.float32), np.zeros((H, W, C), np.float32)
+    dout[3, 3] = 3.384e38
+    got = gradients_of_one_module(dyn, feats, dout, "f32", False)
+    want = np.float64(np.float32(3.384e38)) * np.float64(np.float32(1.005))
+    for name in ("dw3a", "dw3b"):
+        assert (np.abs(got[name] - want) <= 2.0 ** -23 * want).all(), name
 
 
 @pytest.mark.parametrize("value", [np.inf, 3.4e38])
