@@ -478,6 +478,17 @@ def moe_forward(x, Wg, Wn, noise, W1, W2, k: int, out=None, want_aux: bool = Fal
     return (out, aux_t) if want_aux else out
 
 
+MOE_KERNELS = ("gate_stream", "gate_small", "gate_big", "stream", "few1", "few2", "skinny1", "skinny2")
+
+
+def dynb_moe_kernels(T: int, d: int, h: int, E: int, k: int, noisy: bool = False, flags: int = 0) -> set:
+    """The kernels that moe_forward chooses for tensors on 16-byte borders (k_gate and k_grouped_gemm where none is named)."""
+    bits = lib.dynb_moe_kernels(ct.byref(_MoeShape(T, d, h, E, k, DYNB_BF16, flags)), int(noisy))
+    if bits < 0:
+        _check(bits)
+    return {name for i, name in enumerate(MOE_KERNELS) if bits >> i & 1}
+
+
 # ------------------------------------------------------------------------------------------ timing
 MOE_STAGES = ("gate", "topk", "sort", "permute", "ffn1", "ffn2", "combine")
 

@@ -1889,6 +1889,120 @@ Layout layout(const moe_shape* s)
     return L;
 }
 
+// Which kernels a pass runs on: by its sizes, by its tensors' addresses (the kernels that copy straight into LDS ask for pieces of 16 bytes; registers are loaded from any
+// address, by the others), and nothing else.
+struct Choice {
+    int T_big;                    // tokens of k_gate_big; the others' logits:
+    bool gate_small, gate_stream; // k_gate_small, k_gate_stream or k_gate
+    bool small, joined, mid;      // the grouping in one workgroup, in the selection's launch, in two launches, or (none) in five
+    bool fused_permute;
+    int skinny_tiles, stream_most;  // most row tiles
+    bool streamed, few1, few2, skinny1, skinny2;  // k_grouped_stream, or k_grouped_few, k_grouped_skinny, k_grouped_gemm for the first and the second expert layer
+    long long few_tiles(int N) const { return (long long)skinny_tiles * ((N + FEW_F - 1) / FEW_F); }
+    bool tables() const { return streamed || few1 || few2 || skinny1 || skinny2; }   // of the row tiles, in the stacked tokens' room
+};
+
+Choice choose(const moe_shape* s, bool noisy, bool gate_on16, bool layers_on16, int naive_stride)
+{
+    const int T = s->T, d = s->d, h = s->h, E = s->E, k = s->k, A = T * k;
+    Choice c = {};
+    // whole tiles of 256 tokens go to k_gate_big where the expert and model widths allow it and there are enough tiles (a workgroup of
+    // it has a CU for itself, and takes as long however few there are), the tokens behind the last whole tile (and every other shape)
+    // to k_gate.  us, k_gate_big / k_gate by tiles and d:
+    //   noisy: 32 x 512 22 / 13, 64 x 1024 31 / 22, 128 x 256 18.8 / 16.3, 128 x 512 23 / 22, 128 x 1024 32.5 / 33.7, 256 x 1024 43 / 62
+    //   without noise: 32 x 512 12.4 / 11.3, 64 x 512 13.2 / 12.8, 64 x 1024 18.4 / 18.5, 96 x 512 14.0 / 15.4, 128 x 256 12.1 / 13.3, 128 x 1024
+    //   20 / 27; 500 tokens, d 1024, 256 experts (2 tiles and a rest; k_gate_small): 45 / 11
+    // The whole pass, noisy: 96 x 2048 143 / 140, 128 x 2048 142 / 150, 96 x 4096 249 / 249, 256 x 256 74 / 76; without noise: 16 x 4096 117 / 116,
+    // 32 x 2048 77 / 77, 32 x 4096 134 / 139, 64 x 2048 102 / 105.  (Of 120 shapes of 8 to 512 tiles, d 256 to 4096, three go to the slower one by more
+    // than 3 % of the pass, all without noise and by 2.8 us at most: 128 x 256 twice and 64 x 1024 in 4 x 16 tiles.)
+    const size_t big_tiles = size_t(T / GB_TOK) * size_t(E / GB_EXP);
+    const bool many_tiles = noisy ? big_tiles * (size_t(d) + 5120) >= 128 * 6144 : big_tiles * (size_t(d) + 1280) >= 64 * 2304;
+    c.T_big = (many_tiles && E % GB_EXP == 0 && d % GKC == 0 && d >= 4 * GKC && size_t(GB_TOK) * size_t(std::max(E, d)) < (size_t(1) << 30))
+                          ? T / GB_TOK * GB_TOK : 0;
+    const int T_big = c.T_big;
+    // up to some five 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d =
+    // 1024, noisy: 500 21 / 11, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; without noise: 1000 15.5 / 12.8, 2000 16.4 / 20; d = 64: 1764
+    // 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
+    c.gate_small = T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1200;
+    // Of k_gate's tiles, those of whole K-chunks go to k_gate_stream: all of them without noise, and with noise as many as two workgroups a CU hold at once;
+    // beyond that the five of k_gate hide more.  The whole pass in us, k_gate / k_gate_stream, by tiles and d: noisy 256 x 512 153.6 / 150.5, 306 x 576 300.0 / 298.2,
+    // 222 x 768 101.1 / 97.6, 80 x 320 54.1 / 52.1, 376 x 192 47.5 / 47.6, and on the other side 518 x 192 79.2 / 80.5, 845 x 256 81.1 / 82.6, 2370 x 768 312 / 321; without
+    // noise 90 x 384 62.1 / 59.0, 240 x 832 91.1 / 85.1, 430 x 128 38.2 / 36.8, 2057 x 448 191.3 / 186.2
+    const long long tiles = (long long)((E + 63) / 64) * ((T - T_big + 63) / 64);
+    c.gate_stream = !c.gate_small && T > T_big && d % 64 == 0 && d <= 1 << 20 && (!noisy || tiles <= 512) && gate_on16;
+    // few uses, up to eight per token: the selection's last workgroup groups them (its counter lies where the ranks of many uses do), as long as the
+    // selection has no more than 128 workgroups to count.  us a pass replayed from a graph, d = h = 64, a launch more / so, by tokens x experts, uses of a
+    // token: 16 x 64, 2 20.0 / 17.7; 64 x 1024, 4 25.6 / 22.7; 128 x 256, 8 26.8 / 23.7; 256 x 64, 2 22.1 / 19.7; 512 x 256, 2 23.9 / 22.9; 512 x 2048,
+    // 2 34.9 / 32.7; 1024 x 64, 1 24.2 / 25.4; 1024 x 1024, 1 28.8 / 29.6
+    const bool small = c.small = A <= SMALL_USES && E <= SMALL_EXPERTS;
+    c.joined = small && k <= MAX_K && E <= 32 * 64 && T > T_big && T <= 512;
+    // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
+    // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
+    const bool fused_permute = c.fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
+    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.
+    // An expert layer of few tiles and long sums that k_grouped_few (below) does not take runs on k_grouped_skinny, each layer for itself.  k_grouped_gemm pays 1.2 to 1.5 us for
+    // every 64 summed channels however few tiles there are.  k_grouped_skinny reads an expert's weights once per row tile, and where a tile
+    // has many rows, every wave multiplies up to four fragments of them with each of the weights.  us, k_grouped_gemm / k_grouped_skinny, by
+    // features x summed channels and rounds of 768 workgroups (three a CU):
+    //   a layer of few rows a tile: 256 x 2048 0.1: 30 / 15;  768 x 2048 0.9: 47 / 29;  256 x 1024 0.1: 18 / 11, 0.6: 20 / 14;
+    //     512 x 1024 0.25: 21 / 12;  256 x 512 0.7: 13.4 / 9.3;  240 x 432 0.2: 12 / 8.6;  128 x 216 0.6: 10.4 / 8.8;  512 x 512 1.4: 16 / 24;
+    //     2048 x 512 2.0: 18 / 31;  1024 x 256 1.4: 10 / 20;  192 x 320 1.2: 15 / 23;  128 x 192 0.6: 10.3 / 14;  128 x 128 0.5: 7.5 / 10
+    //   a layer of few uses, 20 to 45 rows a tile: 1728 x 128 0.2: 6.4 / 4.8;  256 x 200 0.15: 7.8 / 5.2;  528 x 200 0.15: 8.0 / 4.2
+    //   the whole pass, 43 to 64 rows a tile: 512 x 2048 0.4: 69 / 62, 2.75: 160 / 200;  1024 x 4096 0.5: 133 / 103, 0.75: 122 / 124, 1.5: 171 / 197;
+    //     512 x 1024 0.75: 55 / 58;  1024 x 2048 1.5: 103 / 116, 2.8: 154 / 187;  1024 x 8192 21: 3076 / 4253
+    //   one token, 160 x 184: 21.5 / 24.3 the pass (a few workgroups of short sums pay for their start)
+    // (4646 passes of 64 to 2048 x 64 to 4096 channels and up to 65536 uses take 1.3 % longer than with the better kernel for each layer, in the
+    // mean, and 26 % at worst; with the first limit alone, whatever the rows, 1.8 and 90 %.)
+    // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
+    // each like the smallest token).
+    const bool mid = c.mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
+    const int skinny_tiles = c.skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
+    auto skinny_layer = [&](int N, int K) {
+        const long long groups = (long long)skinny_tiles * ((N + 63) / 64), rows16 = A / (16ll * skinny_tiles);
+        if (!(small || mid) || !fused_permute) return false;
+        // few uses, 16 rows a tile and more: 0.1 to 0.25 rounds also of short sums
+        if (small && rows16 >= 1 && K >= 96 && groups * 10 >= 768 && groups * 4 <= 768) return true;
+        // rounds <= (K - 128) / 600 and 3; from 32 rows a tile 0.3 (few uses: 0.4), with long sums (K - 128) / 2560, at most 0.8
+        const long long most = rows16 < 2 ? 3 * 768 : std::max(small ? 307ll : 230ll, std::min(614ll, (K - 128) * 3ll / 10));
+        return groups * 600 <= 768ll * (K - 128) && groups <= most && (K >= 224 || A >= 128 || groups * 5 >= 768);
+    };
+    c.stream_most = std::min(A, E + A / XR);           // at least as many tiles of k_grouped_stream as there are
+    // Crowded experts, 64 uses each and more in the mean, and products for a tile of 256 x 256 on every CU and more (2^24 = 256 of them, both layers
+    // together): k_grouped_stream.  Its tiles are few and large: where k_grouped_few can take the layers (up to 65536 uses), from 384 features on, which fill 256 + 128, and from
+    // 2^33 products a layer.  The whole pass, others / so in us: k_grouped_gemm, by mean uses of an expert and tiles: 2250, 692: 204 / 157;
+    // 3870, 1180: 288 / 217; 541, 1087: 343 / 271; 788, 863: 192 / 139; 553, 422: 103 / 92; 508, 283: 78 / 67; 370, 2430: 660 / 553; 116, 291: 154 / 136; 99, 525: 171 /
+    // 164; 64, 3072 (Zipf 1.2): 2010 / 1930; 152, 372: 91 / 94; and on the other side of the line 1190, 167: 51 / 55; 187, 135: 48 / 55; 399, 38: 40 / 49; 48, 561: 313 /
+    // 312; 63, 1127: 444 / 450; 37, 395: 301 / 303; 32, 192: 153 / 159.  k_grouped_few, by uses, experts, d x h: 20216, 54, 1536 x 384: 126 / 122; 15200, 7, 1600 x 768:
+    // 96 / 91; 10902, 54, 448 x 1280: 117 / 106; 17964, 22, 1792 x 1536 400 / 266; and on the other side 6435, 2, 512 x 3072 82 / 120; 7906, 16, 384 x 1792 66 / 81; 17965, 4, 448 x
+    // 896 80 / 91; 13256, 119, 320 x 2112 97 / 109; 28110, 3, 256 x 1920 121 / 129 (of 70 shapes within the old line 19 were faster with k_grouped_few, all others 2 to 50 % slower)
+    const bool streamed = c.streamed = fused_permute && layers_on16 && naive_stride <= 0 && !small && d % 64 == 0 && h % 64 == 0 && d >= 256 && h >= 256 && E <= SMALL_EXPERTS && A < 1 << 22 && k <= 1024 &&
+                        size_t(A) * size_t(std::max(d, h)) < size_t(1) << 31 && A >= 64 * E && size_t(A) * size_t(d + h) >= size_t(1) << 24 &&
+                        (!mid || (std::min(d, h) >= 384 && double(A) * d * h >= double(1ll << 33)));
+    // All other layers of whole K-chunks whose row tiles have a table (up to 65536 uses and 4096 experts): k_grouped_few, but for single chunks of few rows a tile
+    // (where it saves no trip to memory), and long sums in a fraction of a tile for every fourth CU (a CU alone gets 58 GB/s: k_grouped_skinny has half the features).  Three chunks
+    // in LDS, two workgroups a CU, where that holds all of them and for long sums, else two chunks and three workgroups.  112 passes over 4 to 32768 tokens, 2 to 2048
+    // experts, 64 to 4096 channels, uniform and skewed, take 0.82 of the time in the geometric mean, 0.59 to 1.00 (always two chunks: 1.02 times as long as so, up to 1.23; always three 1.02, up to 1.13).  us a
+    // pass, before / so, by tokens x experts, uses, d x h: 37 x 256, 2, 512 x 1024 31.0 / 25.4; 4096 x 256, 2, 512 x 1024 86 / 80; 86 x 72, 1, 1856 x 1344 73 / 43;
+    // 542 x 51, 4, 896 x 256 54 / 36; 13879 x 184, 4, 64 x 640 98 / 72; 22 x 38, 4, 64 x 192 21.7 / 19.5; 15959 x 1631, 4, 448 x 512 469 / 446; what is left out: one chunk of few
+    // rows, 4811 x 1394, 1, 64 x 3904 279 / 286; few tiles of long sums, 55 x 57, 2, 128 x 3776 42.0 / 43.9
+    auto few_layer = [&](int N, int K) {
+        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && layers_on16 && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 && K <= 1 << 20 &&
+               (K >= 128 || A >= 16ll * skinny_tiles) && (c.few_tiles(N) >= 64 || K < 2560);
+    };
+    c.few1 = few_layer(h, d);
+    c.few2 = few_layer(d, h);
+    c.skinny1 = !streamed && !c.few1 && skinny_layer(h, d);
+    c.skinny2 = !streamed && !c.few2 && skinny_layer(d, h);
+    return c;
+}
+
+bool on16(std::initializer_list<const void*> pointers)
+{
+    for (const void* at : pointers)
+        if (reinterpret_cast<uintptr_t>(at) & 15) return false;
+    return true;
+}
+
 int check_shape(const moe_shape* s, const char* who)
 {
     if (!s) return fail(DYNB_E_INVAL, std::string(who) + ": NULL shape");
@@ -1955,22 +2069,13 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     bf16_t* y = reinterpret_cast<bf16_t*>(ws + L.y);
     const bf16_t* xb = static_cast<const bf16_t*>(x);
 
+    const Choice c = choose(s, noise != nullptr, on16({x, Wg, noise ? Wn : nullptr}), on16({x, W1, W2}), naive_stride);
+    const bool joined = c.joined, small = c.small, mid = c.mid, fused_permute = c.fused_permute, streamed = c.streamed;
+    const int T_big = c.T_big, skinny_tiles = c.skinny_tiles, stream_most = c.stream_most;
+
     const bool timed = dynb::timing_on();
     if (timed) dynb::timing_begin(st);
     // m1 gate
-    // whole tiles of 256 tokens go to k_gate_big where the expert and model widths allow it and there are enough tiles (a workgroup of
-    // it has a CU for itself, and takes as long however few there are), the tokens behind the last whole tile (and every other shape)
-    // to k_gate.  us, k_gate_big / k_gate by tiles and d:
-    //   noisy: 32 x 512 22 / 13, 64 x 1024 31 / 22, 128 x 256 18.8 / 16.3, 128 x 512 23 / 22, 128 x 1024 32.5 / 33.7, 256 x 1024 43 / 62
-    //   without noise: 32 x 512 12.4 / 11.3, 64 x 512 13.2 / 12.8, 64 x 1024 18.4 / 18.5, 96 x 512 14.0 / 15.4, 128 x 256 12.1 / 13.3, 128 x 1024
-    //   20 / 27; 500 tokens, d 1024, 256 experts (2 tiles and a rest; k_gate_small): 45 / 11
-    // The whole pass, noisy: 96 x 2048 143 / 140, 128 x 2048 142 / 150, 96 x 4096 249 / 249, 256 x 256 74 / 76; without noise: 16 x 4096 117 / 116,
-    // 32 x 2048 77 / 77, 32 x 4096 134 / 139, 64 x 2048 102 / 105.  (Of 120 shapes of 8 to 512 tiles, d 256 to 4096, three go to the slower one by more
-    // than 3 % of the pass, all without noise and by 2.8 us at most: 128 x 256 twice and 64 x 1024 in 4 x 16 tiles.)
-    const size_t big_tiles = size_t(T / GB_TOK) * size_t(E / GB_EXP);
-    const bool many_tiles = noise ? big_tiles * (size_t(d) + 5120) >= 128 * 6144 : big_tiles * (size_t(d) + 1280) >= 64 * 2304;
-    const int T_big = (many_tiles && E % GB_EXP == 0 && d % GKC == 0 && d >= 4 * GKC && size_t(GB_TOK) * size_t(std::max(E, d)) < (size_t(1) << 30))
-                          ? T / GB_TOK * GB_TOK : 0;
     if (T_big > 0) {
         static std::atomic<uint64_t> attr_set{0};             // one bit per device: LDS beyond 64 KB
         int dev = 0;
@@ -1991,30 +2096,11 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             hipLaunchKernelGGL((k_gate_big<false>), grid, dim3(256), GB_LDS_BYTES, st, xb, static_cast<const bf16_t*>(Wg),
                                static_cast<const bf16_t*>(Wn), noise, logits, T_big, d, E, ntt, net, per_die);
     }
-    // requests into LDS want whole pieces of 16 bytes; registers are loaded from any address, by the other kernels
-    auto on16 = [](std::initializer_list<const void*> pointers) {
-        for (const void* at : pointers)
-            if (reinterpret_cast<uintptr_t>(at) & 15) return false;
-        return true;
-    };
-    // up to some five 16 x 16 tiles per CU: the kernel with the small tiles.  us, k_gate / k_gate_small by the number of small tiles: d =
-    // 1024, noisy: 500 21 / 11, 1008 20 / 18, 1764 21 / 25, 2000 21 / 31; without noise: 1000 15.5 / 12.8, 2000 16.4 / 20; d = 64: 1764
-    // 8.8 / 10.2; d = 512, few tokens: 48 12 / 6.5
-    // few uses, up to eight per token: the selection's last workgroup groups them (its counter lies where the ranks of many uses do), as long as the
-    // selection has no more than 128 workgroups to count.  us a pass replayed from a graph, d = h = 64, a launch more / so, by tokens x experts, uses of a
-    // token: 16 x 64, 2 20.0 / 17.7; 64 x 1024, 4 25.6 / 22.7; 128 x 256, 8 26.8 / 23.7; 256 x 64, 2 22.1 / 19.7; 512 x 256, 2 23.9 / 22.9; 512 x 2048,
-    // 2 34.9 / 32.7; 1024 x 64, 1 24.2 / 25.4; 1024 x 1024, 1 28.8 / 29.6
-    const bool small = A <= SMALL_USES && E <= SMALL_EXPERTS;
-    const bool joined = small && k <= MAX_K && E <= 32 * 64 && T > T_big && T <= 512;
     int32_t* const done = joined ? lrank : nullptr;
-    if (T_big == 0 && size_t((E + 15) / 16) * size_t((T + 15) / 16) <= 1200)
+    if (c.gate_small)
         hipLaunchKernelGGL(k_gate_small, dim3((E + 15) / 16, (T + 15) / 16), dim3(256), 0, st, xb, static_cast<const bf16_t*>(Wg),
                            static_cast<const bf16_t*>(Wn), noise, logits, T, d, E, done);
-    // (Of k_gate's tiles, those of whole K-chunks go to k_gate_stream: all of them without noise, and with noise as many as two workgroups a CU hold at once;
-    // beyond that the five of k_gate hide more.  The whole pass in us, k_gate / k_gate_stream, by tiles and d: noisy 256 x 512 153.6 / 150.5, 306 x 576 300.0 / 298.2,
-    // 222 x 768 101.1 / 97.6, 80 x 320 54.1 / 52.1, 376 x 192 47.5 / 47.6, and on the other side 518 x 192 79.2 / 80.5, 845 x 256 81.1 / 82.6, 2370 x 768 312 / 321; without
-    // noise 90 x 384 62.1 / 59.0, 240 x 832 91.1 / 85.1, 430 x 128 38.2 / 36.8, 2057 x 448 191.3 / 186.2)
-    else if (const long long tiles = (long long)((E + 63) / 64) * ((T - T_big + 63) / 64); T > T_big && d % 64 == 0 && d <= 1 << 20 && (!noise || tiles <= 512) && on16({x, Wg, noise ? Wn : nullptr})) {
+    else if (c.gate_stream) {
         static std::atomic<uint64_t> attr_set{0};             // one bit per device: LDS beyond 64 KB
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
@@ -2032,63 +2118,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                            static_cast<const bf16_t*>(Wg), static_cast<const bf16_t*>(Wn), noise ? noise + size_t(T_big) * E : nullptr,
                            logits + size_t(T_big) * E, T - T_big, d, E, done);
     if (timed) dynb::timing_mark(st, dynb::ST_GATE, 0);
-    // the tokens are stacked inside the first expert layer's operand load (token perm[pos] / k for sorted position pos), or
-    // by a kernel of its own (MOE_SEPARATE_PERMUTE, and for the per-use loop)
-    const bool fused_permute = !(s->flags & MOE_SEPARATE_PERMUTE) && naive_stride <= 0;
-    // m3 stable counting sort: few uses in one workgroup, more in two launches, beyond that in five.
-    // An expert layer of few tiles and long sums that k_grouped_few (below) does not take runs on k_grouped_skinny, each layer for itself.  k_grouped_gemm pays 1.2 to 1.5 us for
-    // every 64 summed channels however few tiles there are.  k_grouped_skinny reads an expert's weights once per row tile, and where a tile
-    // has many rows, every wave multiplies up to four fragments of them with each of the weights.  us, k_grouped_gemm / k_grouped_skinny, by
-    // features x summed channels and rounds of 768 workgroups (three a CU):
-    //   a layer of few rows a tile: 256 x 2048 0.1: 30 / 15;  768 x 2048 0.9: 47 / 29;  256 x 1024 0.1: 18 / 11, 0.6: 20 / 14;
-    //     512 x 1024 0.25: 21 / 12;  256 x 512 0.7: 13.4 / 9.3;  240 x 432 0.2: 12 / 8.6;  128 x 216 0.6: 10.4 / 8.8;  512 x 512 1.4: 16 / 24;
-    //     2048 x 512 2.0: 18 / 31;  1024 x 256 1.4: 10 / 20;  192 x 320 1.2: 15 / 23;  128 x 192 0.6: 10.3 / 14;  128 x 128 0.5: 7.5 / 10
-    //   a layer of few uses, 20 to 45 rows a tile: 1728 x 128 0.2: 6.4 / 4.8;  256 x 200 0.15: 7.8 / 5.2;  528 x 200 0.15: 8.0 / 4.2
-    //   the whole pass, 43 to 64 rows a tile: 512 x 2048 0.4: 69 / 62, 2.75: 160 / 200;  1024 x 4096 0.5: 133 / 103, 0.75: 122 / 124, 1.5: 171 / 197;
-    //     512 x 1024 0.75: 55 / 58;  1024 x 2048 1.5: 103 / 116, 2.8: 154 / 187;  1024 x 8192 21: 3076 / 4253
-    //   one token, 160 x 184: 21.5 / 24.3 the pass (a few workgroups of short sums pay for their start)
-    // (4646 passes of 64 to 2048 x 64 to 4096 channels and up to 65536 uses take 1.3 % longer than with the better kernel for each layer, in the
-    // mean, and 26 % at worst; with the first limit alone, whatever the rows, 1.8 and 90 %.)
-    // The tiles' table takes the room of the stacked tokens, which no kernel writes then (at most one tile per use, 16 bytes
-    // each like the smallest token).
-    const bool mid = !small && E <= SMALL_EXPERTS && A <= MID_BLOCKS * 1024;
-    const int skinny_tiles = std::min(A, std::min(A, E) + A / TM);     // at least as many row tiles as there are
-    auto skinny_layer = [&](int N, int K) {
-        const long long groups = (long long)skinny_tiles * ((N + 63) / 64), rows16 = A / (16ll * skinny_tiles);
-        if (!(small || mid) || !fused_permute) return false;
-        // few uses, 16 rows a tile and more: 0.1 to 0.25 rounds also of short sums
-        if (small && rows16 >= 1 && K >= 96 && groups * 10 >= 768 && groups * 4 <= 768) return true;
-        // rounds <= (K - 128) / 600 and 3; from 32 rows a tile 0.3 (few uses: 0.4), with long sums (K - 128) / 2560, at most 0.8
-        const long long most = rows16 < 2 ? 3 * 768 : std::max(small ? 307ll : 230ll, std::min(614ll, (K - 128) * 3ll / 10));
-        return groups * 600 <= 768ll * (K - 128) && groups <= most && (K >= 224 || A >= 128 || groups * 5 >= 768);
-    };
-    const int stream_most = std::min(A, E + A / XR);           // at least as many tiles of k_grouped_stream as there are
-    // Crowded experts, 64 uses each and more in the mean, and products for a tile of 256 x 256 on every CU and more (2^24 = 256 of them, both layers
-    // together): k_grouped_stream.  Its tiles are few and large: where k_grouped_few can take the layers (up to 65536 uses), from 384 features on, which fill 256 + 128, and from
-    // 2^33 products a layer.  The whole pass, others / so in us: k_grouped_gemm, by mean uses of an expert and tiles: 2250, 692: 204 / 157;
-    // 3870, 1180: 288 / 217; 541, 1087: 343 / 271; 788, 863: 192 / 139; 553, 422: 103 / 92; 508, 283: 78 / 67; 370, 2430: 660 / 553; 116, 291: 154 / 136; 99, 525: 171 /
-    // 164; 64, 3072 (Zipf 1.2): 2010 / 1930; 152, 372: 91 / 94; and on the other side of the line 1190, 167: 51 / 55; 187, 135: 48 / 55; 399, 38: 40 / 49; 48, 561: 313 /
-    // 312; 63, 1127: 444 / 450; 37, 395: 301 / 303; 32, 192: 153 / 159.  k_grouped_few, by uses, experts, d x h: 20216, 54, 1536 x 384: 126 / 122; 15200, 7, 1600 x 768:
-    // 96 / 91; 10902, 54, 448 x 1280: 117 / 106; 17964, 22, 1792 x 1536 400 / 266; and on the other side 6435, 2, 512 x 3072 82 / 120; 7906, 16, 384 x 1792 66 / 81; 17965, 4, 448 x
-    // 896 80 / 91; 13256, 119, 320 x 2112 97 / 109; 28110, 3, 256 x 1920 121 / 129 (of 70 shapes within the old line 19 were faster with k_grouped_few, all others 2 to 50 % slower)
-    const bool streamed = fused_permute && on16({x, W1, W2}) && naive_stride <= 0 && !small && d % 64 == 0 && h % 64 == 0 && d >= 256 && h >= 256 && E <= SMALL_EXPERTS && A < 1 << 22 && k <= 1024 &&
-                        size_t(A) * size_t(std::max(d, h)) < size_t(1) << 31 && A >= 64 * E && size_t(A) * size_t(d + h) >= size_t(1) << 24 &&
-                        (!mid || (std::min(d, h) >= 384 && double(A) * d * h >= double(1ll << 33)));
-    // All other layers of whole K-chunks whose row tiles have a table (up to 65536 uses and 4096 experts): k_grouped_few, but for single chunks of few rows a tile
-    // (where it saves no trip to memory), and long sums in a fraction of a tile for every fourth CU (a CU alone gets 58 GB/s: k_grouped_skinny has half the features).  Three chunks
-    // in LDS, two workgroups a CU, where that holds all of them and for long sums, else two chunks and three workgroups.  112 passes over 4 to 32768 tokens, 2 to 2048
-    // experts, 64 to 4096 channels, uniform and skewed, take 0.82 of the time in the geometric mean, 0.59 to 1.00 (always two chunks: 1.02 times as long as so, up to 1.23; always three 1.02, up to 1.13).  us a
-    // pass, before / so, by tokens x experts, uses, d x h: 37 x 256, 2, 512 x 1024 31.0 / 25.4; 4096 x 256, 2, 512 x 1024 86 / 80; 86 x 72, 1, 1856 x 1344 73 / 43;
-    // 542 x 51, 4, 896 x 256 54 / 36; 13879 x 184, 4, 64 x 640 98 / 72; 22 x 38, 4, 64 x 192 21.7 / 19.5; 15959 x 1631, 4, 448 x 512 469 / 446; what is left out: one chunk of few
-    // rows, 4811 x 1394, 1, 64 x 3904 279 / 286; few tiles of long sums, 55 x 57, 2, 128 x 3776 42.0 / 43.9
-    auto few_tiles = [&](int N) { return (long long)skinny_tiles * ((N + FEW_F - 1) / FEW_F); };
-    auto few_layer = [&](int N, int K) {
-        return (small || mid) && fused_permute && naive_stride <= 0 && !streamed && on16({x, W1, W2}) && N % 64 == 0 && K % 64 == 0 && size_t(A) * size_t(std::max(N, K)) < size_t(1) << 31 && K <= 1 << 20 &&
-               (K >= 128 || A >= 16ll * skinny_tiles) && (few_tiles(N) >= 64 || K < 2560);
-    };
-    const bool few1 = few_layer(h, d), few2 = few_layer(d, h);
-    const bool skinny1 = !streamed && !few1 && skinny_layer(h, d), skinny2 = !streamed && !few2 && skinny_layer(d, h), skinny = skinny1 || skinny2 || few1 || few2;
-    RowTile* const tiles = skinny || streamed ? reinterpret_cast<RowTile*>(xs) : nullptr;
+    RowTile* const tiles = c.tables() ? reinterpret_cast<RowTile*>(xs) : nullptr;
     // m2 top-k + softmax
     const dim3 tk_grid((T + 3) / 4), tk_block(256);
     if (joined) {
@@ -2155,7 +2185,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                            stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else if (naive_stride <= 0) {
-        if (few1 || few2) {
+        if (c.few1 || c.few2) {
             static std::atomic<uint64_t> attr_set{0};         // one bit per device
             int dev = 0;
             HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
@@ -2166,7 +2196,7 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
             }
         }
         auto few = [&](auto relu, const bf16_t* from, const void* W, bf16_t* to, int N, int K, const int32_t* rows_at) {
-            const long long all = few_tiles(N);
+            const long long all = c.few_tiles(N);
             const bool three = all <= 512 || K >= 1024;
             // (tiles dealt to an XCD at once: sixteen, or as many as leave all eight eight turns)
             const int chunk = int(std::min(16ll, std::max(1ll, all / 64))), nt = (N + FEW_F - 1) / FEW_F;
@@ -2175,8 +2205,8 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                                static_cast<const bf16_t*>(W), to, tiles, skinny_tiles, chunk, N, K, nt, rows_at,
                                k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u);   // (exact: places below 65536, and k no more)
         };
-        if (few1) few(std::true_type{}, xb, W1, hid, h, d, perm);
-        else if (skinny1)
+        if (c.few1) few(std::true_type{}, xb, W1, hid, h, d, perm);
+        else if (c.skinny1)
             hipLaunchKernelGGL((k_grouped_skinny<true>), dim3(unsigned(skinny_tiles * ((h + 63) / 64))), dim3(256), 0, st, xb,
                                static_cast<const bf16_t*>(W1), hid, tiles, h, d, (h + 63) / 64, perm, k);
         else
@@ -2184,8 +2214,8 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
                                fused_permute ? xb : xs, static_cast<const bf16_t*>(W1), hid, offsets, tile_start, E, h, d, nt1,
                                fused_permute ? perm : nullptr, k);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
-        if (few2) few(std::false_type{}, hid, W2, y, d, h, nullptr);
-        else if (skinny2)
+        if (c.few2) few(std::false_type{}, hid, W2, y, d, h, nullptr);
+        else if (c.skinny2)
             hipLaunchKernelGGL((k_grouped_skinny<false>), dim3(unsigned(skinny_tiles * ((d + 63) / 64))), dim3(256), 0, st, hid,
                                static_cast<const bf16_t*>(W2), y, tiles, d, h, (d + 63) / 64, nullptr, 1);
         else
@@ -2218,6 +2248,16 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
     if (timed) dynb::timing_mark(st, dynb::ST_COMBINE, 0);
     HIP_TRY(hipGetLastError(), "moe_forward");
     return DYNB_OK;
+}
+
+// The kernels of moe_forward for tensors on 16-byte borders, for the tests: bit 0 k_gate_stream, 1 k_gate_small, 2 k_gate_big, 3 k_grouped_stream, 4 and 5
+// k_grouped_few, 6 and 7 k_grouped_skinny (first and second layer); a negative code where the shape is refused
+extern "C" int dynb_moe_kernels(const moe_shape* s, int noisy)
+{
+    const int rc = check_shape(s, "dynb_moe_kernels");
+    if (rc != DYNB_OK) return rc;
+    const Choice c = choose(s, noisy != 0, true, true, 0);
+    return c.gate_stream | c.gate_small << 1 | (c.T_big > 0) << 2 | c.streamed << 3 | c.few1 << 4 | c.few2 << 5 | c.skinny1 << 6 | c.skinny2 << 7;
 }
 
 extern "C" int moe_forward(const moe_shape* s, const void* x, const void* Wg, const void* Wn, const float* noise,

@@ -32,6 +32,11 @@ def util():
     return gpu_util
 
 
+def kernels(*shape):
+    from paper_1707_02402_amd.binding import dynb_moe_kernels
+    return dynb_moe_kernels(*shape)
+
+
 def stack(m):
     W1 = np.stack([m.expert_weights(e)[0] for e in range(m.E)])
     W2 = np.stack([m.expert_weights(e)[1] for e in range(m.E)])
@@ -172,6 +177,7 @@ def test_many_wide_gate_tiles(dyn, util, oracle, T, d, h, E, k, noisy):
                                          (2049, 64, 1000, False), (2049, 64, 1000, True)])
 def test_gate_tiles_of_whole_chunks(dyn, util, oracle, T, d, E, noisy):
     """One to five chunks of 64 channels, tokens and experts that end inside a tile; as many tiles as two workgroups a CU hold, and more."""
+    assert ("gate_stream" in kernels(T, d, 64, E, 2, noisy)) == (not noisy or (T + 63) // 64 * ((E + 63) // 64) <= 512)
     m = moe.small(seed=T + E, T=T, d=d, h=64, E=E, k=2)
     W1, W2 = stack(m)
     dev = util.moe_inputs_dev(m, W1, W2)
@@ -213,9 +219,7 @@ def test_crowded_experts_have_the_bits_of_the_small_tiles(dyn, util, d, h, k, co
     """The kernel of the crowded experts against the one with tiles of 64 rows, which MOE_SEPARATE_PERMUTE always takes: both add up the channels in
     the same order.  Experts at the edges of its kinds of tiles (32, 64, 128, 256 rows), of one row and of none; tokens whose other uses go to the
     experts behind."""
-    E, uses = len(counts), sum(counts) * k
-    assert uses >= 64 * E and uses * (d + h) >= 1 << 24                                       # where that kernel is chosen
-    assert uses > 65536 or min(d, h) >= 384 and uses * d * h >= 1 << 33
+    assert "stream" in kernels(sum(counts), d, h, len(counts), k)
     bits_of_both_ways(dyn, util, d, h, k, counts)
 
 
@@ -246,13 +250,14 @@ def bits_of_both_ways(dyn, util, d, h, k, counts):
 @pytest.mark.parametrize("d,h,k,counts", [(64, 128, 1, (1, 2, 31, 32, 33, 0, 63, 64, 65, 127, 128, 129)),   # one chunk and two
                                           (128, 192, 2, (1, 0, 31, 33, 64, 65, 200)),             # features cut at 64
                                           (192, 1024, 1, (1, 31, 32, 33, 64, 65, 0, 130) * 12),   # three chunks in two places, sixteen in three
-                                          (320, 2560, 3, (70, 0, 3)),                             # forty chunks; 64 features of a tile's 128
+                                          (320, 2496, 3, (70, 0, 3)),                             # 39 chunks; 64 features of a tile's 128
                                           (512, 64, 8, (5, 60, 0, 64) * 16),
                                           (960, 704, 1, (1, 64, 0, 65) * 120),                    # more than a round of the workgroups
-                                          (64, 64, 2, (1600,) * 32)])
+                                          (64, 64, 2, (1000,) * 32)])
 def test_layers_of_whole_chunks_have_the_bits_of_the_general_kernel(dyn, util, d, h, k, counts):
     """k_grouped_few with two and three chunks in LDS against the kernel that MOE_SEPARATE_PERMUTE takes: both add up the channels in the same order.  Row
-    tiles of 1 to 64 rows around the halves that a wave multiplies, experts without uses, one chunk to forty."""
+    tiles of 1 to 64 rows around the halves that a wave multiplies, experts without uses, one chunk to 39."""
+    assert kernels(sum(counts), d, h, len(counts), k) >= {"few1", "few2"}
     bits_of_both_ways(dyn, util, d, h, k, counts)
 
 
