@@ -701,24 +701,25 @@ __global__ __launch_bounds__(256) void k_scan_blocks(int32_t* __restrict__ block
 }
 
 // Row tiles of k_grouped_stream: an expert's tiles of more than XM rows, up to XR, from the front of `tiles` on, and one of up to XM remaining rows, from the
-// back on.  They are counted together, 65536 a whole tile and 1 a rest; how many there are stands in tile_start[0] and [1].
+// back on.  They are counted together, 65536 a whole tile and 1 a rest; how many there are stands in tile_start[E].
 __device__ __forceinline__ int stream_tiles(int c) { return int(uint32_t((c + XR - XM - 1) / XR) << 16) | int(c % XR != 0 && c % XR <= XM); }
 __device__ __forceinline__ int whole_tiles(int n) { return int(uint32_t(n) >> 16); }
 __device__ __forceinline__ int rest_tiles(int n) { return n & 0xffff; }
-__device__ __forceinline__ void put_stream_tiles(RowTile* tiles, int max_tiles, int before, int e, int at, int c)
+// Every step-th one of an expert's tiles, whole ones first, from number i on.  (All workgroups or a wave share a crowded expert's: by one thread, 2000000 uses of 8 experts took
+// k_offsets 65.5 us, 4.7 without them, k_place 9.0 with and without; 65536 uses of 1024 experts k_place_wide 14.5, 12.1 so, 11.2 with the other kernels' table)
+__device__ __forceinline__ void put_stream_tiles(RowTile* tiles, int max_tiles, int before, int e, int at, int c, int i, int step)
 {
-    RowTile* to = tiles + whole_tiles(before);
-    const int alone = c <= XM;
-    for (; c > XM; c -= XR, at += XR) *to++ = RowTile{e, at, min(XR, c), 0};
-    if (c > 0) tiles[max_tiles - 1 - rest_tiles(before)] = RowTile{e, at, c, alone};
+    const int n = stream_tiles(c), whole = whole_tiles(n);
+    for (; i < whole; i += step) tiles[whole_tiles(before) + i] = RowTile{e, at + i * XR, min(XR, c - i * XR), 0};
+    if (i == whole && rest_tiles(n)) tiles[max_tiles - 1 - rest_tiles(before)] = RowTile{e, at + i * XR, c - i * XR, c <= XM};
 }
 
 // One workgroup of 16 waves: offsets = exclusive scan of counts; tile_start = exclusive scan of ceil(counts / TM).
 // 1024 experts per pass: a scan inside every wave, the waves' totals through LDS.
 constexpr int OFFS_THREADS = 1024;
-template <bool STREAM>
+template <bool STREAM>                                       // STREAM: tile_start = exclusive scan of stream_tiles(counts)
 __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                          int32_t* __restrict__ tile_start, RowTile* __restrict__ tiles, int max_tiles, int E)
+                                                          int32_t* __restrict__ tile_start, int E)
 {
     __shared__ int32_t wsum[OFFS_THREADS / 64], wtsum[OFFS_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -744,25 +745,24 @@ __global__ __launch_bounds__(OFFS_THREADS) void k_offsets(const int32_t* __restr
             all += a;
             tall += t;
         }
-        if (e < E) {
-            offsets[e] = carry + before + inc - c;
-            if constexpr (STREAM) put_stream_tiles(tiles, max_tiles, tcarry + tbefore + tinc - tl, e, carry + before + inc - c, c);
-            else tile_start[e] = tcarry + tbefore + tinc - tl;
-        }
+        if (e < E) { offsets[e] = carry + before + inc - c; tile_start[e] = tcarry + tbefore + tinc - tl; }
         carry += all;
         tcarry += tall;
         __syncthreads();                                     // the totals are overwritten by the next pass
     }
-    if (tid == 0) offsets[E] = carry;
-    if constexpr (STREAM) {
-        if (tid < 2) tile_start[tid] = tid ? rest_tiles(tcarry) : whole_tiles(tcarry);
-    } else if (tid == 0) tile_start[E] = tcarry;
+    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
 }
 
+// STREAM: also k_grouped_stream's tiles, a wave for every expert (there are 64 uses for each, so waves enough)
+template <bool STREAM>
 __global__ __launch_bounds__(SORT_BLOCK) void k_place(const int32_t* __restrict__ idx, const int32_t* __restrict__ lrank,
                                                       const int32_t* __restrict__ blockoff, const int32_t* __restrict__ offsets,
-                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv, int A, int nblk)
+                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv, int A, int nblk,
+                                                      const int32_t* __restrict__ tile_start, RowTile* __restrict__ tiles, int max_tiles, int E)
 {
+    if constexpr (STREAM)
+        for (int t = blockIdx.x * (SORT_BLOCK / 64) + (threadIdx.x >> 6); t < E; t += nblk * (SORT_BLOCK / 64))
+            put_stream_tiles(tiles, max_tiles, tile_start[t], t, offsets[t], offsets[t + 1] - offsets[t], threadIdx.x & 63, 64);
     const int a = blockIdx.x * SORT_BLOCK + threadIdx.x;
     if (a >= A) return;
     const int e = idx[a];
@@ -1069,11 +1069,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __rest
                 first[e + i] = at + before[i];
                 if (!STREAM && tiles)
                     for (int t = blk; t < tl[i]; t += nblk) tiles[tat + t] = RowTile{e + i, at + t * TM, min(TM, c[i] - t * TM), 0};
+                if (STREAM) put_stream_tiles(tiles, max_tiles, tat, e + i, at, c[i], blk, nblk);
                 if (tables) {
                     counts[e + i] = c[i];
                     offsets[e + i] = at;
-                    if constexpr (STREAM) put_stream_tiles(tiles, max_tiles, tat, e + i, at, c[i]);
-                    else tile_start[e + i] = tat;
+                    tile_start[e + i] = tat;
                 }
             }
             at += c[i];
@@ -1093,13 +1093,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_place_wide(const int32_t* __rest
         }
     }
     if (!tables) return;
-    if (tid == 0) offsets[E] = carry;
-    if constexpr (STREAM) {
-        if (tid < 2) tile_start[tid] = tid ? rest_tiles(tcarry) : whole_tiles(tcarry);
-        return;
-    }
-    if (tid == 0) tile_start[E] = tcarry;
-    if (tiles)
+    if (tid == 0) { offsets[E] = carry; tile_start[E] = tcarry; }
+    if (!STREAM && tiles)
         for (int t = tcarry + tid; t < max_tiles; t += THREADS) tiles[t] = RowTile{0, 0, 0, 0};
 }
 
@@ -1831,7 +1826,7 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
     // the other, and those of the last round, which is cut short, in reverse: the second list's not to who has a whole tile more.  Blocks of 4 row tiles x 4
     // feature tiles of the first list are neighbours (what they share comes from one L2), all features of a row tile in the other
     const int half = slot & 1, turn = slot >> 1, group = die * 2 + half;
-    const int n_whole = uniform_load(n_tiles), n_rest = uniform_load(n_tiles + 1);
+    const int n_all = uniform_load(n_tiles), n_whole = whole_tiles(n_all), n_rest = rest_tiles(n_all);
     auto share = [&](int n, int i) { return int((long long)n * nt * i / 16); };
     const int whole0 = share(n_whole, group), whole1 = share(n_whole, group + 1), rest0 = share(n_rest, group), rest1 = share(n_rest, group + 1);
     const int all = whole1 - whole0 + rest1 - rest0, rounds = all & ~15;
@@ -2154,8 +2149,9 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         hipLaunchKernelGGL(k_zero_i32, dim3(unsigned(std::min<size_t>((nbc + 255) / 256, 2048))), dim3(256), 0, st, blockcnt, nbc);
         hipLaunchKernelGGL(k_rank_blocks, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, A, L.nblk);
         hipLaunchKernelGGL(k_scan_blocks, dim3((E + 3) / 4), dim3(256), 0, st, blockcnt, counts, E, L.nblk);
-        hipLaunchKernelGGL(streamed ? k_offsets<true> : k_offsets<false>, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, tiles, stream_most, E);
-        hipLaunchKernelGGL(k_place, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A, L.nblk);
+        hipLaunchKernelGGL(streamed ? k_offsets<true> : k_offsets<false>, dim3(1), dim3(OFFS_THREADS), 0, st, counts, offsets, tile_start, E);
+        hipLaunchKernelGGL(streamed ? k_place<true> : k_place<false>, dim3(L.nblk), dim3(SORT_BLOCK), 0, st, topk_idx, lrank, blockcnt, offsets, perm, inv, A,
+                           L.nblk, tile_start, tiles, stream_most, E);
     }
     if (timed) dynb::timing_mark(st, dynb::ST_SORT, 0);
     // m4 permute
@@ -2178,10 +2174,10 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         // weights of a layer: 245 MiB 309 / 309 us (less than the cache, and all experts' rests so: 53 MB 134 / 157, 76 MB 102 / 122); 304 241 / 214; 504 252 / 227; 569 188 / 180; 894 650 / 651;
         // 4096 1877 / 1849 (with all rests so, those of experts with whole tiles too: 569 188 / 200, 322 217 / 227 instead of 204)
         const int once = size_t(E) * d * h >= size_t(1) << 27;
-        hipLaunchKernelGGL((k_grouped_stream<true>), dim3(X_GRID), dim3(512), X_LDS, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, tile_start,
+        hipLaunchKernelGGL((k_grouped_stream<true>), dim3(X_GRID), dim3(512), X_LDS, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, tile_start + E,
                            stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
-        hipLaunchKernelGGL((k_grouped_stream<false>), dim3(X_GRID), dim3(512), X_LDS, st, hid, static_cast<const bf16_t*>(W2), y, tiles, tile_start,
+        hipLaunchKernelGGL((k_grouped_stream<false>), dim3(X_GRID), dim3(512), X_LDS, st, hid, static_cast<const bf16_t*>(W2), y, tiles, tile_start + E,
                            stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else if (naive_stride <= 0) {
