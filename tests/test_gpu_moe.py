@@ -261,20 +261,26 @@ def test_layers_of_whole_chunks_have_the_bits_of_the_general_kernel(dyn, util, d
     bits_of_both_ways(dyn, util, d, h, k, counts)
 
 
-@pytest.mark.parametrize("T,d,h,E,k", [(300, 64, 128, 9, 2), (2600, 512, 448, 6, 4), (5000, 576, 1024, 4, 4)])
-def test_inputs_between_16_byte_borders(dyn, util, T, d, h, E, k):
-    """Tensors that start 4 bytes behind a border of 16 take the kernels that load registers: the results of aligned copies, bit for bit."""
+@pytest.mark.parametrize("T,d,h,E,k,noisy,taken", [(300, 64, 128, 9, 2, True, {"few1", "few2"}), (2600, 512, 448, 6, 4, True, {"few1", "few2"}), (5000, 576, 1024, 4, 4, True, {"stream"}),
+                                                   (700, 256, 64, 463, 2, True, {"gate_stream"}), (650, 128, 64, 500, 1, False, {"gate_stream"})])
+def test_inputs_between_16_byte_borders(dyn, util, T, d, h, E, k, noisy, taken):
+    """Tensors that start 4 bytes behind a border of 16 take the kernels that load registers: the logits and results of aligned copies, bit for bit."""
     import torch
+    assert taken <= kernels(T, d, h, E, k, noisy)
     g = torch.Generator(device="cuda").manual_seed(T)
     def rnd(*shape, std=1.0):
         n = int(np.prod(shape))
         return (torch.randn(n + 8, generator=g, device="cuda") * std).to(torch.bfloat16)[2:n + 2].view(shape)
-    args = [rnd(T, d), rnd(E, d), rnd(E, d, std=0.1), torch.randn(T, E, generator=g, device="cuda"), rnd(E, h, d, std=d ** -0.5), rnd(E, d, h, std=h ** -0.5)]
-    assert all(t.data_ptr() % 16 == 4 for t in args if t.dtype == torch.bfloat16)
-    want = util.to_host(dyn.moe_forward(*[t.clone() for t in args], k))
-    assert (util.to_host(dyn.moe_forward(*args, k)) == want).all()
+    args = [rnd(T, d), rnd(E, d), rnd(E, d, std=0.1), torch.randn(T, E, generator=g, device="cuda") if noisy else None, rnd(E, h, d, std=d ** -0.5), rnd(E, d, h, std=h ** -0.5)]
+    assert all(t.data_ptr() % 16 == 4 for t in args if t is not None and t.dtype == torch.bfloat16)
+    aligned = [t if t is None else t.clone() for t in args]
+    def both(*tensors):
+        out, aux = dyn.moe_forward(*tensors, k, want_aux=True)
+        return util.to_host(out), util.to_host(aux.logits)
+    want = both(*aligned)
+    assert all((a == b).all() for a, b in zip(both(*args), want))
     for i in (0, 1, 2, 4, 5):
-        assert (util.to_host(dyn.moe_forward(*[t if j == i else t.clone() for j, t in enumerate(args)], k)) == want).all()
+        assert all((a == b).all() for a, b in zip(both(*[args[j] if j == i else aligned[j] for j in range(6)]), want)), i
 
 
 def full_layer(dyn, util, m):
