@@ -1597,12 +1597,12 @@ __global__ __launch_bounds__(256, 2) void k_grouped_few(const bf16_t* __restrict
 }
 
 // The expert layers for crowded experts (the rule stands where it is applied): one workgroup per CU that stays for the launch and sees its tiles as one stream
-// of K-chunks.  Chunks of 64 channels go from memory straight into LDS, one or two of them ahead, across the border of one tile to the next: the pipeline does
+// of K-chunks (but for the last four of a die, where they leave early).  Chunks of 64 channels go from memory straight into LDS, one or two of them ahead, across the border of one tile to the next: the pipeline does
 // not run dry for a tile's first chunk or while its results leave, and a chunk costs one barrier.  A whole tile has 256 rows and 256 features, so that an
 // expert's weights and rows enter a CU at 31 bytes for every clock of its matrix instructions (k_grouped_gemm's tiles of 64 rows: 78; the L2 gives a CU
 // 64 a clock, 135 GB/s, to copies of 128 bytes of a row at a time, and memory all of them 6.3 TB/s, one alone 58 GB/s, with two chunks in flight or
-// four); an expert's remaining rows, up to 128, are another kind, a stream of weights with two chunks ahead.  Half of the workgroups of a die begin with
-// either kind: products beside the stream (one kind after the other on all CUs: 950 us a layer of 16384 tokens, 1024 experts, instead of 900).
+// four); an expert's remaining rows, up to 128, are another kind, a stream of weights with two chunks ahead.  18 workgroups of a die begin with the
+// whole tiles, 14 with the rests: products beside the stream (one kind after the other on all CUs: 950 us a layer of 16384 tokens, 1024 experts, instead of 900).
 // What bounds it: whole tiles, the matrix instructions at the clock the card grants (16384 tokens, d 1024, h 2048, 16 experts, 4 uses: 0.92 PFLOP/s the
 // pass, k_grouped_gemm 0.68); the others, memory, where results that are written cost the reading six times their bytes (4 GiB of weights alone in 675
 // us, with 64 MB of results 737).
@@ -1615,7 +1615,7 @@ constexpr int X_GRID = 256;
 template <bool RELU>
 __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
                                                            const RowTile* __restrict__ tiles, const int32_t* __restrict__ n_tiles, int max_tiles,
-                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv, int once)
+                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv, int once, int leave)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane & 31, hk = lane >> 5;
@@ -1822,34 +1822,36 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
         meet();                                                // (the other kind's chunks lie in the same place)
     };
 
-    // ---- this workgroup's tiles.  A sixteenth of either list goes to every half of a die, whose sixteen workgroups take its tiles in turn, one list after
-    // the other, and those of the last round, which is cut short, in reverse: the second list's not to who has a whole tile more.  Blocks of 4 row tiles x 4
-    // feature tiles of the first list are neighbours (what they share comes from one L2), all features of a row tile in the other
-    const int half = slot & 1, turn = slot >> 1, group = die * 2 + half;
+    // ---- this workgroup's tiles.  The workgroups of a die are two teams, 18 that begin with the whole tiles and 14 that begin with the rests.  A team takes the
+    // tiles of its share of a list in turn, and those of the rests' last round, which is cut short, in reverse: not to who has a whole tile more.  Blocks of 4 row
+    // tiles x 4 feature tiles of the whole ones are neighbours (what they share comes from one L2), all features of a row tile of the rests.
+    // leave: the last four of a die (one for each of its four shader engines, to which a launch's workgroups go in turn) take whole tiles only, and go
+    const int half = slot < 28 ? slot & 1 : 0, turn = slot < 28 ? slot >> 1 : slot - 14, team = half ? 14 : 18, rest_team = leave ? 14 : team;
     const int n_all = uniform_load(n_tiles), n_whole = whole_tiles(n_all), n_rest = rest_tiles(n_all);
-    auto share = [&](int n, int i) { return int((long long)n * nt * i / 16); };
-    const int whole0 = share(n_whole, group), whole1 = share(n_whole, group + 1), rest0 = share(n_rest, group), rest1 = share(n_rest, group + 1);
-    const int all = whole1 - whole0 + rest1 - rest0, rounds = all & ~15;
+    auto share = [&](int n, int i, int of) { return int((long long)n * nt * i / of); };
+    const int at = die * 32 + half * 18, rest_at = leave ? die * 28 + half * 14 : at, rest_of = leave ? X_GRID - 32 : X_GRID;
+    const int whole0 = share(n_whole, at, X_GRID), wholes = share(n_whole, at + team, X_GRID) - whole0;
+    const int rest0 = share(n_rest, rest_at, rest_of), rests = share(n_rest, rest_at + rest_team, rest_of) - rest0;
+    const int ahead = min(wholes % team, rest_team) % rest_team, rounds = (ahead + rests) / rest_team * rest_team;   // the first round of rests begins behind who has a whole tile more
 #pragma unroll 1
     for (int phase = 0; phase < 2; ++phase) {
-        const bool second = (phase ^ half) != 0;
-        const int from = second ? rest0 : whole0, n = second ? rest1 - rest0 : whole1 - whole0, dealt = second ? whole1 - whole0 : 0;
-        const int first = (turn - dealt) & 15, regular = max(0, (min(n, rounds - dealt) - first + 15) / 16);
-        const int last = rounds + 15 - turn - dealt;           // this workgroup's of the last round, if it is in this list
-        const int count = regular + (last >= 0 && last < n && last + dealt < all);
-        auto index = [&](int s) { return from + (s < regular ? first + 16 * s : last); };
-        auto find_whole = [&](int s) {
-            const int i = index(s);
-            const int strip = i / (4 * nt), i1 = i - strip * 4 * nt, rows4 = min(4, n_whole - strip * 4);   // 4 row tiles, all features
-            const int col = i1 / (rows4 * 4), i2 = i1 - col * rows4 * 4, cols4 = min(4, nt - col * 4);
-            return int2{strip * 4 + i2 / cols4, col * 4 + i2 % cols4};
-        };
-        auto find_rest = [&](int s) {
-            const int i = index(s), m = i / nt;
-            return int2{max_tiles - 1 - m, i - m * nt};
-        };
-        if (!second) run(std::integral_constant<int, XR>{}, std::integral_constant<int, 2>{}, count, find_whole);
-        else run(std::integral_constant<int, XM>{}, std::integral_constant<int, 3>{}, count, find_rest);
+        if (phase == half) {
+            auto find_whole = [&](int s) {
+                const int i = whole0 + turn + team * s;
+                const int strip = i / (4 * nt), i1 = i - strip * 4 * nt, rows4 = min(4, n_whole - strip * 4);   // 4 row tiles, all features
+                const int col = i1 / (rows4 * 4), i2 = i1 - col * rows4 * 4, cols4 = min(4, nt - col * 4);
+                return int2{strip * 4 + i2 / cols4, col * 4 + i2 % cols4};
+            };
+            run(std::integral_constant<int, XR>{}, std::integral_constant<int, 2>{}, (wholes - turn + team - 1) / team, find_whole);
+        } else if (turn < rest_team) {
+            const int first = turn < ahead ? turn - ahead + rest_team : turn - ahead, regular = max(0, (min(rests, rounds - ahead) - first + rest_team - 1) / rest_team);
+            const int last = rounds + rest_team - 1 - turn - ahead;   // this workgroup's of the last round, if it has one
+            auto find_rest = [&](int s) {
+                const int i = rest0 + (s < regular ? first + rest_team * s : last), m = i / nt;
+                return int2{max_tiles - 1 - m, i - m * nt};
+            };
+            run(std::integral_constant<int, XM>{}, std::integral_constant<int, 3>{}, regular + (last >= 0 && last < rests), find_rest);
+        }
     }
 }
 
@@ -2174,11 +2176,17 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         // weights of a layer: 245 MiB 309 / 309 us (less than the cache, and all experts' rests so: 53 MB 134 / 157, 76 MB 102 / 122); 304 241 / 214; 504 252 / 227; 569 188 / 180; 894 650 / 651;
         // 4096 1877 / 1849 (with all rests so, those of experts with whole tiles too: 569 188 / 200, 322 217 / 227 instead of 204)
         const int once = size_t(E) * d * h >= size_t(1) << 27;
+        // From 1 GB of weights a layer, a launch of 0.2 ms and more, four of a die's CUs are left to other streams behind the whole tiles, or these would wait for the launch's end.  A pass of 37
+        // tokens, 256 experts, 512 x 1024, beside 16384 tokens on another stream, with none left / so, median and longest us (k_grouped_gemm in that place), by experts and weights of a layer: 1024
+        // experts, 4 GB 867, 1700 / 117, 406 (266, 603); 512, 2 GB 541, 1085 / 133, 505 (232, 513); 1024, 2 GB 499, 995 / 114, 275 (186, 562); 256, 1 GB 397, 805 / 93, 400 (210, 406).  The 16384 tokens alone:
+        // 1844 / 1896 (2001), 1196 / 1223 (1363), 1083 / 1112 (1182), 861 / 875 (1035), 1878 / 1972 uniform.  Smaller layers' launches are about as long as the wait was, and would
+        // pay as much: 512 MB 319 / 340, 265 / 278; 300 MB 306 / 316.  (Always 28 CUs a die: 1907, 120 beside; the launch handed from one workgroup to the next half-way, each at another time: 1960, 141)
+        const int leave = size_t(E) * d * h >= size_t(1) << 29;
         hipLaunchKernelGGL((k_grouped_stream<true>), dim3(X_GRID), dim3(512), X_LDS, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, tile_start + E,
-                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u, once);
+                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u, once, leave);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
         hipLaunchKernelGGL((k_grouped_stream<false>), dim3(X_GRID), dim3(512), X_LDS, st, hid, static_cast<const bf16_t*>(W2), y, tiles, tile_start + E,
-                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once);
+                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once, leave);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else if (naive_stride <= 0) {
         if (c.few1 || c.few2) {

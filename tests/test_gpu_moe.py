@@ -214,7 +214,9 @@ EDGES = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 191, 192, 255, 256, 257, 
                                           (448, 256, 2, EDGES + (40000, 30000)),              # more than 65536 uses
                                           (512, 1024, 3, EDGES + (9000,)),
                                           (576, 1856, 1, (9000,)), (320, 256, 8, (1100,) * 8),
-                                          (1024, 2048, 1, (1, 64, 128, 129, 257, 385, 0, 100) * 8)])   # 2^28 bytes of weights: lone tiles past the caches
+                                          (1024, 2048, 1, (1, 64, 128, 129, 257, 385, 0, 100) * 8),    # 2^28 bytes of weights: lone tiles past the caches
+                                          (1024, 2048, 1, (1, 64, 128, 129, 257, 385, 0, 100) * 32),   # 2^30: four CUs of a die take whole tiles only
+                                          (1024, 2048, 1, (256,) * 256), (1024, 2048, 1, (64,) * 256)])    # ... no rests, no whole tiles
 def test_crowded_experts_have_the_bits_of_the_small_tiles(dyn, util, d, h, k, counts):
     """The kernel of the crowded experts against the one with tiles of 64 rows, which MOE_SEPARATE_PERMUTE always takes: both add up the channels in
     the same order.  Experts at the edges of its kinds of tiles (32, 64, 128, 256 rows), of one row and of none; tokens whose other uses go to the
@@ -245,6 +247,77 @@ def bits_of_both_ways(dyn, util, d, h, k, counts):
     b = dyn.moe_forward(*args, flags=dyn.MOE_SEPARATE_PERMUTE)
     assert torch.isfinite(a.float()).all() and a.float().abs().mean() > 0.1
     assert (util.to_host(a) == util.to_host(b)).all()
+
+
+def test_a_workgroup_of_more_tiles_than_its_list_holds(dyn, util):
+    """k_grouped_stream looks up 512 of a workgroup's tiles at once.  4096 experts with a rest each and 8128 features are 131072 rests' tiles, 585 for each of the 224
+    workgroups that take them."""
+    import torch
+    E, d, h, c = 4096, 256, 8128, 64
+    T = E * c + 256                                                                            # expert 77: 256 rows and 64
+    assert "stream" in kernels(T, d, h, E, 1)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    e = torch.cat([torch.arange(E, device="cuda").repeat_interleave(c), torch.full((256,), 77, device="cuda")])[torch.randperm(T, generator=g, device="cuda")]
+    x = torch.randn(T, d, generator=g, device="cuda").to(torch.bfloat16)
+    x[:, :128] = 0
+    Wg = torch.zeros(E, d, device="cuda", dtype=torch.bfloat16)                                # an expert's logit: 8 for each of its number's two halves
+    for rows, number, value in ((x, e, 8.0), (Wg, torch.arange(E, device="cuda"), 1.0)):
+        at = torch.arange(len(rows), device="cuda")
+        rows[at, number // 64] = value
+        rows[at, 64 + number % 64] = value
+    def weights(rows, cols):
+        w = torch.empty(E, rows, cols, dtype=torch.bfloat16, device="cuda")
+        for i in range(0, E, 256):
+            w[i:i + 256] = torch.randn(256, rows, cols, generator=g, device="cuda") * cols ** -0.5
+        return w
+    args = (x, Wg, None, None, weights(h, d), weights(d, h), 1)
+    a, aux = dyn.moe_forward(*args, want_aux=True)
+    want = torch.full((E,), c, device="cuda")
+    want[77] += 256
+    assert (aux.counts == want).all()
+    b = dyn.moe_forward(*args, flags=dyn.MOE_SEPARATE_PERMUTE)
+    assert torch.isfinite(a.float()).all() and a.float().abs().mean() > 0.1
+    assert (util.to_host(a) == util.to_host(b)).all()
+
+
+def test_a_small_layer_does_not_wait_for_a_large_one(dyn):
+    """37 tokens on one stream while another runs layers whose weights are read for 0.8 ms a launch: k_grouped_stream leaves CUs to others.  A wait for one such
+    launch's end is half of a large layer's time and more, in the median; 0.07 of it where there is none."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3)
+    def layer(T, d, h, E, k):
+        rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+        w = [torch.empty(E, r, c, dtype=torch.bfloat16, device="cuda") for r, c in ((h, d), (d, h))]
+        for t in w:
+            for i in range(0, E, 128):
+                t[i:i + 128] = rnd(*t[i:i + 128].shape) * t.shape[2] ** -0.5
+        x, Wg = rnd(T, d).to(torch.bfloat16), (rnd(E, d) * d ** -0.5).to(torch.bfloat16)
+        ws, out = torch.empty(dyn.moe_workspace_bytes(T, d, h, E, k), dtype=torch.uint8, device="cuda"), torch.empty_like(x)
+        return lambda: dyn.moe_forward(x, Wg, None, None, *w, k, out=out, workspace=ws)
+    large, small = layer(16384, 1024, 2048, 1024, 4), layer(37, 512, 1024, 256, 2)
+    assert "stream" in kernels(16384, 1024, 2048, 1024, 4)
+    for run in (large, small, large, small):
+        run()
+    torch.cuda.synchronize()
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    event = lambda: torch.cuda.Event(enable_timing=True)
+    begin, end, calls = event(), event(), []
+    with torch.cuda.stream(one):
+        begin.record()
+        for _ in range(60):
+            large()
+        end.record()
+    while not end.query():
+        with torch.cuda.stream(other):
+            calls.append((event(), event()))
+            calls[-1][0].record()
+            small()
+            calls[-1][1].record()
+        other.synchronize()
+    torch.cuda.synchronize()
+    waits = sorted(a.elapsed_time(b) for a, b in calls[:-1])
+    assert len(waits) > 20
+    assert waits[len(waits) // 2] < 0.25 * begin.elapsed_time(end) / 60, (waits[len(waits) // 2], waits[-1], begin.elapsed_time(end) / 60)
 
 
 @pytest.mark.parametrize("d,h,k,counts", [(64, 128, 1, (1, 2, 31, 32, 33, 0, 63, 64, 65, 127, 128, 129)),   # one chunk and two
