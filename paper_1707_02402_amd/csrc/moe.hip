@@ -1597,7 +1597,7 @@ __global__ __launch_bounds__(256, 2) void k_grouped_few(const bf16_t* __restrict
 }
 
 // The expert layers for crowded experts (the rule stands where it is applied): one workgroup per CU that stays for the launch and sees its tiles as one stream
-// of K-chunks (but for the last four of a die, where they leave early).  Chunks of 64 channels go from memory straight into LDS, one or two of them ahead, across the border of one tile to the next: the pipeline does
+// of K-chunks (but for the last four of a die, where they leave ahead of the others).  Chunks of 64 channels go from memory straight into LDS, one or two of them ahead, across the border of one tile to the next: the pipeline does
 // not run dry for a tile's first chunk or while its results leave, and a chunk costs one barrier.  A whole tile has 256 rows and 256 features, so that an
 // expert's weights and rows enter a CU at 31 bytes for every clock of its matrix instructions (k_grouped_gemm's tiles of 64 rows: 78; the L2 gives a CU
 // 64 a clock, 135 GB/s, to copies of 128 bytes of a row at a time, and memory all of them 6.3 TB/s, one alone 58 GB/s, with two chunks in flight or
@@ -1615,7 +1615,7 @@ constexpr int X_GRID = 256;
 template <bool RELU>
 __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
                                                            const RowTile* __restrict__ tiles, const int32_t* __restrict__ n_tiles, int max_tiles,
-                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv, int once, int leave)
+                                                           int N, int K, int nt, const int32_t* __restrict__ gather, uint32_t m_kdiv, int once)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane & 31, hk = lane >> 5;
@@ -1825,9 +1825,15 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
     // ---- this workgroup's tiles.  The workgroups of a die are two teams, 18 that begin with the whole tiles and 14 that begin with the rests.  A team takes the
     // tiles of its share of a list in turn, and those of the rests' last round, which is cut short, in reverse: not to who has a whole tile more.  Blocks of 4 row
     // tiles x 4 feature tiles of the whole ones are neighbours (what they share comes from one L2), all features of a row tile of the rests.
-    // leave: the last four of a die (one for each of its four shader engines, to which a launch's workgroups go in turn) take whole tiles only, and go
-    const int half = slot < 28 ? slot & 1 : 0, turn = slot < 28 ? slot >> 1 : slot - 14, team = half ? 14 : 18, rest_team = leave ? 14 : team;
     const int n_all = uniform_load(n_tiles), n_whole = whole_tiles(n_all), n_rest = rest_tiles(n_all);
+    // leave: where the rests are a stream of 12 rounds and 0.3 ms (256 features x 1024 channels a round) and more, the last four of a die (one for each of its four shader engines, to which a
+    // launch's workgroups go in turn) take whole tiles only, and go: other streams' launches find CUs, instead of waiting for this one's end.  A pass of 37 tokens, 256 experts, 512 x 1024,
+    // median and longest us, beside layers of 16384 tokens, 4 uses, with all CUs held / so (with k_grouped_gemm in that place), and these layers alone: 1024 experts of 1024 x 2048
+    // 867, 1700 / 118, 403 (259, 613), 1855 / 1877 (2010), loaded evenly 1876 / 1945 (2017); 512 529, 1062 / 132, 602 (185, 511), 1190 / 1201 (1350); 1024 of 512 x 2048 503, 990 / 113, 558 (187,
+    // 559), 1069 / 1079 (1169).  On the other side of the line, leaving from 1 GB of weights on, whatever the rounds, alone: 256 experts, 2048 x 2048, 64 uses each 869 / 950; 64, 1024 x 8192 475 / 584
+    // (nine rounds instead of eight, two instead of one); 512, 1024 x 1024 489 / 526.  (28 workgroups a die from the start: 1907, 120 us beside it; 31 or 30: no better beside it than 32)
+    const bool leave = n_rest * nt >= 12 * X_GRID && (long long)n_rest * nt * K >= 12ll * X_GRID * 1024;
+    const int half = slot < 28 ? slot & 1 : 0, turn = slot < 28 ? slot >> 1 : slot - 14, team = half ? 14 : 18, rest_team = leave ? 14 : team;
     auto share = [&](int n, int i, int of) { return int((long long)n * nt * i / of); };
     const int at = die * 32 + half * 18, rest_at = leave ? die * 28 + half * 14 : at, rest_of = leave ? X_GRID - 32 : X_GRID;
     const int whole0 = share(n_whole, at, X_GRID), wholes = share(n_whole, at + team, X_GRID) - whole0;
@@ -2176,17 +2182,11 @@ static int moe_run(const moe_shape* s, const void* x, const void* Wg, const void
         // weights of a layer: 245 MiB 309 / 309 us (less than the cache, and all experts' rests so: 53 MB 134 / 157, 76 MB 102 / 122); 304 241 / 214; 504 252 / 227; 569 188 / 180; 894 650 / 651;
         // 4096 1877 / 1849 (with all rests so, those of experts with whole tiles too: 569 188 / 200, 322 217 / 227 instead of 204)
         const int once = size_t(E) * d * h >= size_t(1) << 27;
-        // From 1 GB of weights a layer, a launch of 0.2 ms and more, four of a die's CUs are left to other streams behind the whole tiles, or these would wait for the launch's end.  A pass of 37
-        // tokens, 256 experts, 512 x 1024, beside 16384 tokens on another stream, with none left / so, median and longest us (k_grouped_gemm in that place), by experts and weights of a layer: 1024
-        // experts, 4 GB 867, 1700 / 117, 406 (266, 603); 512, 2 GB 541, 1085 / 133, 505 (232, 513); 1024, 2 GB 499, 995 / 114, 275 (186, 562); 256, 1 GB 397, 805 / 93, 400 (210, 406).  The 16384 tokens alone:
-        // 1844 / 1896 (2001), 1196 / 1223 (1363), 1083 / 1112 (1182), 861 / 875 (1035), 1878 / 1972 uniform.  Smaller layers' launches are about as long as the wait was, and would
-        // pay as much: 512 MB 319 / 340, 265 / 278; 300 MB 306 / 316.  (Always 28 CUs a die: 1907, 120 beside; the launch handed from one workgroup to the next half-way, each at another time: 1960, 141)
-        const int leave = size_t(E) * d * h >= size_t(1) << 29;
         hipLaunchKernelGGL((k_grouped_stream<true>), dim3(X_GRID), dim3(512), X_LDS, st, xb, static_cast<const bf16_t*>(W1), hid, tiles, tile_start + E,
-                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u, once, leave);
+                           stream_most, h, d, (h + XF - 1) / XF, perm, k > 1 ? 0xffffffffu / uint32_t(k) + 1u : 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN1, 0);
         hipLaunchKernelGGL((k_grouped_stream<false>), dim3(X_GRID), dim3(512), X_LDS, st, hid, static_cast<const bf16_t*>(W2), y, tiles, tile_start + E,
-                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once, leave);
+                           stream_most, d, h, (d + XF - 1) / XF, nullptr, 0u, once);
         if (timed) dynb::timing_mark(st, dynb::ST_FFN2, 0);
     } else if (naive_stride <= 0) {
         if (c.few1 || c.few2) {

@@ -215,8 +215,7 @@ EDGES = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 191, 192, 255, 256, 257, 
                                           (512, 1024, 3, EDGES + (9000,)),
                                           (576, 1856, 1, (9000,)), (320, 256, 8, (1100,) * 8),
                                           (1024, 2048, 1, (1, 64, 128, 129, 257, 385, 0, 100) * 8),    # 2^28 bytes of weights: lone tiles past the caches
-                                          (1024, 2048, 1, (1, 64, 128, 129, 257, 385, 0, 100) * 32),   # 2^30: four CUs of a die take whole tiles only
-                                          (1024, 2048, 1, (256,) * 256), (1024, 2048, 1, (64,) * 256)])    # ... no rests, no whole tiles
+                                          (1024, 2048, 1, (1, 64, 128, 257, 100, 0, 129, 90, 40, 120) * 48)])  # 12 rounds of rests: four CUs of a die take whole tiles only
 def test_crowded_experts_have_the_bits_of_the_small_tiles(dyn, util, d, h, k, counts):
     """The kernel of the crowded experts against the one with tiles of 64 rows, which MOE_SEPARATE_PERMUTE always takes: both add up the channels in
     the same order.  Experts at the edges of its kinds of tiles (32, 64, 128, 256 rows), of one row and of none; tokens whose other uses go to the
