@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "device_utils.h"
+#include "moe_deal.h"
 #include "plan_internal.h"
 #include "timing.h"
 
@@ -1610,7 +1611,7 @@ __global__ __launch_bounds__(256, 2) void k_grouped_few(const bf16_t* __restrict
 constexpr int XIDX = 18 * XUNIT;                               // behind the chunks (2 of 8 units, 3 of 6): the rows' places in `gather`, two tiles'
 constexpr int XLIST = XIDX + 2 * XR * 4, XLIST_LEN = 512;      // ... and the workgroup's next tiles
 constexpr int X_LDS = XLIST + XLIST_LEN * 16;
-constexpr int X_GRID = 256;
+constexpr int X_GRID = StreamDeal::WORKGROUPS;
 
 template <bool RELU>
 __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restrict__ in, const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
@@ -1822,41 +1823,20 @@ __global__ __launch_bounds__(512, 1) void k_grouped_stream(const bf16_t* __restr
         meet();                                                // (the other kind's chunks lie in the same place)
     };
 
-    // ---- this workgroup's tiles.  The workgroups of a die are two teams, 18 that begin with the whole tiles and 14 that begin with the rests.  A team takes the
-    // tiles of its share of a list in turn, and those of the rests' last round, which is cut short, in reverse: not to who has a whole tile more.  Blocks of 4 row
-    // tiles x 4 feature tiles of the whole ones are neighbours (what they share comes from one L2), all features of a row tile of the rests.
-    const int n_all = uniform_load(n_tiles), n_whole = whole_tiles(n_all), n_rest = rest_tiles(n_all);
-    // leave: where the rests are a stream of 12 rounds and 0.3 ms (256 features x 1024 channels a round) and more, the last four of a die (one for each of its four shader engines, to which a
-    // launch's workgroups go in turn) take whole tiles only, and go: other streams' launches find CUs, instead of waiting for this one's end.  A pass of 37 tokens, 256 experts, 512 x 1024,
-    // median and longest us, beside layers of 16384 tokens, 4 uses, with all CUs held / so (with k_grouped_gemm in that place), and these layers alone: 1024 experts of 1024 x 2048
-    // 867, 1700 / 118, 403 (259, 613), 1855 / 1877 (2010), loaded evenly 1876 / 1945 (2017); 512 529, 1062 / 132, 602 (185, 511), 1190 / 1201 (1350); 1024 of 512 x 2048 503, 990 / 113, 558 (187,
-    // 559), 1069 / 1079 (1169).  On the other side of the line, leaving from 1 GB of weights on, whatever the rounds, alone: 256 experts, 2048 x 2048, 64 uses each 869 / 950; 64, 1024 x 8192 475 / 584
-    // (nine rounds instead of eight, two instead of one); 512, 1024 x 1024 489 / 526.  (28 workgroups a die from the start: 1907, 120 us beside it; 31 or 30: no better beside it than 32)
-    const bool leave = n_rest * nt >= 12 * X_GRID && (long long)n_rest * nt * K >= 12ll * X_GRID * 1024;
-    const int half = slot < 28 ? slot & 1 : 0, turn = slot < 28 ? slot >> 1 : slot - 14, team = half ? 14 : 18, rest_team = leave ? 14 : team;
-    auto share = [&](int n, int i, int of) { return int((long long)n * nt * i / of); };
-    const int at = die * 32 + half * 18, rest_at = leave ? die * 28 + half * 14 : at, rest_of = leave ? X_GRID - 32 : X_GRID;
-    const int whole0 = share(n_whole, at, X_GRID), wholes = share(n_whole, at + team, X_GRID) - whole0;
-    const int rest0 = share(n_rest, rest_at, rest_of), rests = share(n_rest, rest_at + rest_team, rest_of) - rest0;
-    const int ahead = min(wholes % team, rest_team) % rest_team, rounds = (ahead + rests) / rest_team * rest_team;   // the first round of rests begins behind who has a whole tile more
+    const int n_all = uniform_load(n_tiles);
+    const StreamDeal deal(blockIdx.x, whole_tiles(n_all), rest_tiles(n_all), nt, K);
 #pragma unroll 1
     for (int phase = 0; phase < 2; ++phase) {
-        if (phase == half) {
-            auto find_whole = [&](int s) {
-                const int i = whole0 + turn + team * s;
-                const int strip = i / (4 * nt), i1 = i - strip * 4 * nt, rows4 = min(4, n_whole - strip * 4);   // 4 row tiles, all features
-                const int col = i1 / (rows4 * 4), i2 = i1 - col * rows4 * 4, cols4 = min(4, nt - col * 4);
-                return int2{strip * 4 + i2 / cols4, col * 4 + i2 % cols4};
-            };
-            run(std::integral_constant<int, XR>{}, std::integral_constant<int, 2>{}, (wholes - turn + team - 1) / team, find_whole);
-        } else if (turn < rest_team) {
-            const int first = turn < ahead ? turn - ahead + rest_team : turn - ahead, regular = max(0, (min(rests, rounds - ahead) - first + rest_team - 1) / rest_team);
-            const int last = rounds + rest_team - 1 - turn - ahead;   // this workgroup's of the last round, if it has one
-            auto find_rest = [&](int s) {
-                const int i = rest0 + (s < regular ? first + rest_team * s : last), m = i / nt;
-                return int2{max_tiles - 1 - m, i - m * nt};
-            };
-            run(std::integral_constant<int, XM>{}, std::integral_constant<int, 3>{}, regular + (last >= 0 && last < rests), find_rest);
+        if (phase == deal.half) {
+            run(std::integral_constant<int, XR>{}, std::integral_constant<int, 2>{}, deal.whole_count(), [&](int s) {
+                const StreamDeal::Place at = deal.whole(s);
+                return int2{at.row, at.column};
+            });
+        } else {
+            run(std::integral_constant<int, XM>{}, std::integral_constant<int, 3>{}, deal.rest_count(), [&](int s) {
+                const StreamDeal::Place at = deal.rest(s);
+                return int2{max_tiles - 1 - at.row, at.column};
+            });
         }
     }
 }

@@ -249,7 +249,7 @@ def bits_of_both_ways(dyn, util, d, h, k, counts):
 
 
 def test_a_workgroup_of_more_tiles_than_its_list_holds(dyn, util):
-    """k_grouped_stream looks up 512 of a workgroup's tiles at once.  4096 experts with a rest each and 8128 features are 131072 rests' tiles, 585 for each of the 224
+    """k_grouped_stream looks up 512 of a workgroup's tiles at once.  4096 experts with a rest each and 8128 features are 131072 rests' tiles, 585 or 586 for each of the 224
     workgroups that take them."""
     import torch
     E, d, h, c = 4096, 256, 8128, 64
