@@ -23,7 +23,7 @@ def oracle():
 
 class _RefCache:
     """Oracle results of the full-size program-tree configurations, computed once per session
-    (config 2 takes about 10 s on the 16 host cores of a GPU machine)."""
+    (config 2 takes about 10 s on 16 host cores)."""
 
     def __init__(self, oracle):
         self.oracle = oracle

@@ -98,8 +98,8 @@ def test_ragged_shapes_fp32_with_single_scene_programs(dyn, util, oracle, C, H, 
 @pytest.mark.parametrize("dtype,C,H,W", [("f32", 32, 14, 14), ("f32", 33, 9, 13), ("f32", 64, 17, 1), ("f32", 36, 2, 33), ("f32", 40, 5, 31), ("bf16", 64, 10, 14), ("bf16", 34, 21, 7)])
 def test_parameter_gradients_with_every_unit_active(dyn, util, oracle, dtype, C, H, W):
     """Maps of one band and more, whole and cut blocks of 32 channels, one column, two segments.  Every unit active, so that no ReLU decision hangs on a rounding:
-    what is left are the sums.  One of n products that is rounded twice for every 16 of them is off by 2^-24 sqrt(n / 8) of itself at most in the mean: 2.5e-6 for
-    the longest here, gradients and activations that carry such errors into it included.  Of activations that are stored in bfloat16 a share of 3e-7 / 2^-8 = 8e-5
+    what is left are the sums.  One of n products of one sign that is rounded with every product, by 2^-24 / sqrt(3) in the mean at most, its i-th partial sum being i / n
+    of it, is off by 2^-24 sqrt(n / 9) of itself at most: 2.5e-6 for the longest here, gradients and activations that carry such errors into it included.  Of activations that are stored in bfloat16 a share of 3e-7 / 2^-8 = 8e-5
     rounds to the neighbour, 2^-8 away: 2^-8 sqrt(8e-5) = 3.5e-5 of the norm for one module, 1e-4 for the five of a program."""
     w = iep.small_mixed(seed=C + H, B=6, C=C, H=H, W=W, dtype=dtype, min_len=2, max_len=5)
     for name in ("feats", "w1", "w3a", "w3b", "b1", "b3a", "b3b"):
